@@ -1,6 +1,7 @@
 """Python binding of the C ABI in include/cer.h -- argument marshalling only.
 
-Every function has the name of the C entry point it calls.  Device buffers are passed as torch
+Every function has the name of the C entry point it calls; the product calls (cer_matmul, cser_matmul, cer_matmul_noalloc,
+csr_matmul) are native functions of _cerpy (csrc/pybind.cpp), because a small product takes less time than ctypes does.  Device buffers are passed as torch
 tensors (their ``data_ptr()`` is handed to the library) or as raw integer addresses; streams as
 ``torch.cuda.Stream`` objects, raw ``hipStream_t`` integers, or None for the current torch stream.
 No step of the product runs in Python or in torch, and there is no CPU fallback: if the built
@@ -12,6 +13,11 @@ import ctypes
 import os
 
 import numpy as np
+
+try:
+    from . import _cerpy  # built together with the library
+except ImportError:
+    _cerpy = None         # lib() raises
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 # CER_HIP_LIB selects another build of the same library (e.g. one compiled with other tuning constants)
@@ -83,8 +89,8 @@ def lib() -> ctypes.CDLL:
     """Loads paper_1805_10692_amd/libcer_hip.so (built by `python -m paper_1805_10692_amd.build`)."""
     global _lib
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise ImportError(f"{LIB_PATH} is not built; run `python -m paper_1805_10692_amd.build` "
+        if _cerpy is None or not os.path.exists(LIB_PATH):
+            raise ImportError(f"{LIB_PATH} or _cerpy.so is not built; run `python -m paper_1805_10692_amd.build` "
                               "(there is no fallback implementation)")
         # One HIP runtime per process: PyTorch ships its own copy of it, and the tensors whose pointers this binding
         # passes live in that one.  Loaded after torch, the library binds to the copy that is already there; loaded
@@ -174,6 +180,8 @@ def lib() -> ctypes.CDLL:
         L.cer_strerror.argtypes = [ctypes.c_int]
         L.cer_last_hip_error.restype = ctypes.c_int
         L.cer_last_hip_error.argtypes = []
+        _cerpy.bind(*(ctypes.cast(getattr(L, f), vp).value
+                      for f in ("cer_matmul", "cser_matmul", "cer_matmul_noalloc", "csr_matmul")))
         _lib = L
     return _lib
 
@@ -198,6 +206,18 @@ def _stream_ptr(stream) -> int:
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
+
+
+if _cerpy is not None:
+    _cerpy.setup(lib, _check, _stream_ptr)
+    # f(h, X, Y, batch, stream=None) -> None
+    cer_matmul, cser_matmul = _cerpy.cer_matmul, _cerpy.cser_matmul
+    cer_matmul_noalloc, csr_matmul = _cerpy.cer_matmul_noalloc, _cerpy.csr_matmul
+else:
+    def cer_matmul(h, X, Y, batch: int, stream=None) -> None:
+        lib()  # raises: not built
+
+    cser_matmul = cer_matmul_noalloc = csr_matmul = cer_matmul
 
 
 class Handle:
@@ -275,10 +295,6 @@ def cer_quantize_encode_device(W, m: int, n: int, bits: int, fmt: str = "cer", s
     return Handle(out.value, fmt), cb[:K.value].copy()
 
 
-def cer_matmul(h: Handle, X, Y, batch: int, stream=None) -> None:
-    _check(lib().cer_matmul(h.ptr, _dev_ptr(X), _dev_ptr(Y), batch, _stream_ptr(stream)), "cer_matmul")
-
-
 def cer_decode_device(h: Handle, W_out, stream=None) -> None:
     """Writes the dense m x n matrix into the fp32 device tensor W_out."""
     d = cer_get_dims(h)
@@ -311,19 +327,11 @@ def cer_prepare_strips(h: Handle) -> None:
     _check(lib().cer_prepare_strips(h.ptr), "cer_prepare_strips")
 
 
-def cer_matmul_noalloc(h: Handle, X, Y, batch: int, stream=None) -> None:
-    _check(lib().cer_matmul_noalloc(h.ptr, _dev_ptr(X), _dev_ptr(Y), batch, _stream_ptr(stream)), "cer_matmul_noalloc")
-
-
 def cer_matmul_path_ex(h: Handle, batch: int, opts: "MatmulOpts | None" = None) -> int:
     rc = lib().cer_matmul_path_ex(h.ptr, batch, ctypes.byref(opts) if opts is not None else None)
     if rc < 0:
         _check(rc, "cer_matmul_path_ex")
     return rc
-
-
-def cser_matmul(h: Handle, X, Y, batch: int, stream=None) -> None:
-    _check(lib().cser_matmul(h.ptr, _dev_ptr(X), _dev_ptr(Y), batch, _stream_ptr(stream)), "cser_matmul")
 
 
 def _decode(name: str, h: Handle) -> np.ndarray:
@@ -433,10 +441,6 @@ def csr_encode(W: np.ndarray) -> CsrHandle:
     out = ctypes.c_void_p()
     _check(lib().csr_encode(W.ctypes.data, W.shape[0], W.shape[1], ctypes.byref(out)), "csr_encode")
     return CsrHandle(out.value, W.shape[0], W.shape[1])
-
-
-def csr_matmul(h: CsrHandle, X, Y, batch: int, stream=None) -> None:
-    _check(lib().csr_matmul(h.ptr, _dev_ptr(X), _dev_ptr(Y), batch, _stream_ptr(stream)), "csr_matmul")
 
 
 def csr_decode(h: CsrHandle) -> np.ndarray:
