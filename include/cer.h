@@ -144,11 +144,10 @@ int cer_matmul_noalloc(const cer_handle_t* h, const float* X_dev, float* Y_dev, 
 /*
  * cer_trim -- gives the device memory of released temporaries back to the system.  The products and
  * conversions that need a temporary (see each call) take it, ordered on the caller's stream, from
- * a memory pool of the library's own on the current device; the pool keeps what it has handed out
- * once, because getting a few hundred megabytes from the system again costs more than the product
- * that needs them.  Its size settles at the largest amount in use at one time.  cer_trim releases
- * whatever is not in use at the moment of the call on the current device; it does not synchronise
- * and may be called at any time.  Errors: CER_E_HIP.
+ * blocks the library keeps on the current device; they are kept (at most 2 GiB of them) because getting
+ * a few hundred megabytes from the system again costs more than the product that needs them.  cer_trim
+ * releases whatever is not in use at the moment of the call on the current device; it may wait for
+ * work queued on the null stream and may be called at any time.  Errors: CER_E_HIP.
  */
 int cer_trim(void);
 

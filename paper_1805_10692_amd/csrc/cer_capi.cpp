@@ -6,6 +6,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <vector>
 
 #include "../../include/cer.h"
 #include "cer_internal.hpp"
@@ -65,13 +66,144 @@ hipMemPool_t temp_pool() {
 }
 }  // namespace
 
-int cer::temp_alloc(void** p, size_t bytes, void* stream) {
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    hipMemPool_t pool = temp_pool();
-    return (int)(pool ? hipMallocFromPoolAsync(p, bytes, pool, s) : hipMallocAsync(p, bytes, s));
+// Blocks that a product has given back, kept for the next one.  A release to the runtime's pool (hipFreeAsync) waits on
+// the host until the stream has drained -- 8 us on an idle stream, the whole product on a busy one: AlexNet-fc6 shape
+// batch 99 was enqueued in 66 us per call, its own duration -- so blocks go through this list instead:
+//   * a block released on the null stream serves later requests of the null stream, which are ordered behind its last use;
+//   * a block released on any other stream carries an event: any stream may take it once the event has passed, the same
+//     stream at once, behind a wait for the event (a stream's handle may be that of a new stream at the same address).
+// The list is bounded (kBlocksKept blocks, kBytesKept bytes per device; the oldest goes first) and cer_trim empties it.
+// Under stream capture the runtime's pool is used directly.
+namespace {
+struct TempBlock {
+    void* p = nullptr;
+    size_t bytes = 0;
+    hipStream_t stream = nullptr;
+    hipEvent_t done = nullptr;  // null: released on the null stream
+};
+constexpr size_t kBlocksKept = 32, kBlocksOut = 256, kBytesKept = (size_t)2 << 30;
+struct TempCache {
+    TempCache() {  // never grown later: no allocation, no exception in a product
+        kept.reserve(kBlocksKept + 1);
+        in_use.reserve(kBlocksOut);
+        events.reserve(kBlocksKept + 1);
+    }
+    void spare(hipEvent_t e) {
+        if (events.size() < kBlocksKept) events.push_back(e); else (void)hipEventDestroy(e);
+    }
+    std::mutex mu;
+    std::vector<TempBlock> kept;       // oldest first
+    std::vector<TempBlock> in_use;     // handed out through this list
+    std::vector<hipEvent_t> events;    // spare ones
+    size_t kept_bytes = 0;
+};
+TempCache g_temp_caches[16];
+
+TempCache* temp_cache() {
+    int dev = 0;
+    return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 16 ? &g_temp_caches[dev] : nullptr;
 }
 
-int cer::temp_free(void* p, void* stream) { return (int)hipFreeAsync(p, static_cast<hipStream_t>(stream)); }
+bool capturing(hipStream_t s) {
+    if (!s) return false;  // the null stream cannot be captured
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
+// Gives kept block i back to the runtime's pool.
+void release_kept(TempCache& c, size_t i) {
+    const TempBlock b = c.kept[i];
+    c.kept.erase(c.kept.begin() + (ptrdiff_t)i);
+    c.kept_bytes -= b.bytes;
+    if (b.done) {
+        (void)hipEventSynchronize(b.done);
+        c.spare(b.done);
+    }
+    (void)hipFreeAsync(b.p, nullptr);
+}
+}  // namespace
+
+int cer::temp_alloc(void** p, size_t bytes, void* stream) {
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    TempCache* c = temp_cache();
+    const bool listed = c && !capturing(s);
+    if (listed) {
+        std::lock_guard<std::mutex> lock(c->mu);
+        size_t best = SIZE_MAX;
+        bool wait = false;
+        for (size_t i = 0; i < c->kept.size(); ++i) {
+            const TempBlock& b = c->kept[i];
+            if (b.bytes < bytes || (best != SIZE_MAX && b.bytes >= c->kept[best].bytes)) continue;
+            if (b.bytes > (16u << 20) && b.bytes / 4 > bytes) continue;  // a large block is not spent on a small request
+            if (!b.done) {
+                if (s) continue;
+                wait = false;
+            } else if (hipEventQuery(b.done) == hipSuccess) {
+                wait = false;
+            } else {
+                (void)hipGetLastError();  // hipErrorNotReady
+                if (b.stream != s) continue;
+                wait = true;
+            }
+            best = i;
+        }
+        if (best != SIZE_MAX && c->in_use.size() < kBlocksOut) {
+            TempBlock b = c->kept[best];
+            if (!wait || hipStreamWaitEvent(s, b.done, 0) == hipSuccess) {
+                c->kept.erase(c->kept.begin() + (ptrdiff_t)best);
+                c->kept_bytes -= b.bytes;
+                if (b.done) c->spare(b.done);
+                b.done = nullptr;
+                c->in_use.push_back(b);
+                *p = b.p;
+                return (int)hipSuccess;
+            }
+            (void)hipGetLastError();
+        }
+    }
+    hipMemPool_t pool = temp_pool();
+    const size_t rounded = (bytes + 65535) & ~(size_t)65535;
+    const hipError_t e = pool ? hipMallocFromPoolAsync(p, rounded, pool, s) : hipMallocAsync(p, rounded, s);
+    if (e == hipSuccess && listed) {
+        std::lock_guard<std::mutex> lock(c->mu);
+        if (c->in_use.size() < kBlocksOut) c->in_use.push_back(TempBlock{*p, rounded, s, nullptr});
+    }
+    return (int)e;
+}
+
+int cer::temp_free(void* p, void* stream) {
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    TempCache* c = temp_cache();
+    if (c) {
+        std::lock_guard<std::mutex> lock(c->mu);
+        for (size_t i = c->in_use.size(); i-- > 0;) {
+            if (c->in_use[i].p != p) continue;
+            TempBlock b = c->in_use[i];
+            c->in_use.erase(c->in_use.begin() + (ptrdiff_t)i);
+            b.stream = s;
+            bool keep = b.bytes <= kBytesKept;
+            if (keep && s) {
+                if (c->events.empty()) {
+                    keep = hipEventCreateWithFlags(&b.done, hipEventDisableTiming) == hipSuccess;
+                } else {
+                    b.done = c->events.back();
+                    c->events.pop_back();
+                }
+                if (keep && hipEventRecord(b.done, s) != hipSuccess) {
+                    c->spare(b.done);
+                    keep = false;
+                }
+                if (!keep) (void)hipGetLastError();
+            }
+            if (!keep) break;
+            while (!c->kept.empty() && (c->kept.size() >= kBlocksKept || c->kept_bytes + b.bytes > kBytesKept)) release_kept(*c, 0);
+            c->kept.push_back(b);
+            c->kept_bytes += b.bytes;
+            return (int)hipSuccess;
+        }
+    }
+    return (int)hipFreeAsync(p, s);
+}
 
 
 namespace {
@@ -728,6 +860,17 @@ int cer_trim(void) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return hip_fail(hipGetLastError());
     if (dev < 0 || dev >= 16) return CER_OK;
+    {
+        TempCache& c = g_temp_caches[dev];
+        std::lock_guard<std::mutex> lock(c.mu);
+        for (size_t i = c.kept.size(); i-- > 0;) {
+            if (c.kept[i].done && hipEventQuery(c.kept[i].done) != hipSuccess) {
+                (void)hipGetLastError();  // still in use
+                continue;
+            }
+            release_kept(c, i);
+        }
+    }
     TempPool& t = g_temp_pools[dev];
     std::lock_guard<std::mutex> lock(t.mu);
     if (!t.pool) return CER_OK;

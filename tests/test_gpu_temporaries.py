@@ -1,0 +1,54 @@
+"""Products that need temporaries, on several streams and from several threads: the blocks the library keeps between calls
+never serve two products at once, whichever stream or thread returns them."""
+import threading
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1805_10692_amd import binding as B
+from paper_1805_10692_amd import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("threads", [1, 3])
+def test_streams_and_threads_share_the_kept_blocks(threads):
+    dev = torch.device("cuda:0")
+    w = wl.conv3x3(L=96, nonzero_dominant=True, scale=4)   # column sums, and a decoded matrix or strips' partial sums
+    want = oracle.dot(oracle.encode(w.W, w.codebook, "cer"), w.X, threads=8)
+    bound = 1e-5 * oracle.abs_dot_dense(w.W, w.X, threads=8)
+    h = B.cer_encode(w.W, w.codebook)
+    B.cer_prepare_strips(h)
+    X = torch.from_numpy(w.X).to(dev)
+    scales = [1.0, 2.0, 4.0, 8.0]                          # powers of two: the same rounding, another result
+    Xs = [X * s for s in scales]
+    torch.cuda.synchronize()
+    bad = []
+
+    def work():
+        streams = [None, torch.cuda.Stream(), torch.cuda.Stream()]
+        for path in (B.CER_PATH_STRIP, B.CER_PATH_DENSE):
+            outs = []
+            for i in range(24):
+                Y = torch.empty((w.m, w.L), device=dev)
+                torch.cuda.current_stream().synchronize()
+                B.cer_matmul_ex(h, Xs[i % 4], Y, w.L, streams[i % 3], B.MatmulOpts(path=path))
+                outs.append(Y)
+            del streams[2]                                 # a stream that is gone while its blocks are kept
+            torch.cuda.synchronize()
+            streams.append(torch.cuda.Stream())
+            for i, Y in enumerate(outs):
+                err = np.abs(Y.cpu().numpy().astype(np.float64) / scales[i % 4] - want)
+                if not (err <= bound).all():
+                    bad.append((path, i))
+
+    pool = [threading.Thread(target=work) for _ in range(threads)]
+    for t in pool:
+        t.start()
+    for t in pool:
+        t.join()
+    B.cer_trim()
+    assert not bad, bad
+    B.cer_free(h)
