@@ -23,6 +23,7 @@
 #include <cmath>
 #include <mutex>
 #include <numeric>
+#include <tuple>
 #include <type_traits>
 
 #include "cer_internal.hpp"
@@ -332,6 +333,19 @@ inline KView make_kview(const DeviceView& d) {
     k.rank_tab = d.rank_tab;
     k.rank_tab_shift = d.rank_tab_shift;
     return k;
+}
+
+// Launches a kernel and returns the launch's own status.  hipLaunchKernelGGL followed by hipGetLastError takes 0.6 us more
+// of host time (2.4 against 3.0 us; a batch-1 product of a small layer lasts 3.3 us on the GPU).
+template <typename... Params, typename... Args>
+hipError_t launch_kernel(void (*kern)(Params...), dim3 grid, dim3 block, size_t lds, hipStream_t stream, Args... args) {
+    std::tuple<std::remove_cv_t<Params>...> values{static_cast<Params>(args)...};
+    return std::apply(
+        [&](auto&... v) {
+            void* ptrs[] = {const_cast<void*>(static_cast<const void*>(&v))...};
+            return hipLaunchKernel(reinterpret_cast<const void*>(kern), grid, block, ptrs, lds, stream);
+        },
+        values);
 }
 
 inline uint32_t pow2_ceil(uint32_t x) {

@@ -465,13 +465,11 @@ hipError_t launch_expand_split(Kern kern, const KView& k, const float* X, float*
     }
     sp.out = out;
     sp.part_blocks = (uint32_t)part_blocks;
-    hipLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(256), 0, stream, k.rowInfo, k.colI, X, Y, L, ntiles, rowblocks, ipx,
+    e = launch_kernel(kern, dim3((uint32_t)blocks), dim3(256), 0, stream, k.rowInfo, k.colI, X, Y, L, ntiles, rowblocks, ipx,
                        k.m, T, k, sp);
-    e = hipGetLastError();
     if (sp.nparts > 0) {
         if (e == hipSuccess) {
-            hipLaunchKernelGGL(split_add_kernel, dim3(sp.nrows), dim3(256), 0, stream, sp.rows, out, Y, L);
-            e = hipGetLastError();
+            e = launch_kernel(split_add_kernel, dim3(sp.nrows), dim3(256), 0, stream, sp.rows, out, Y, L);
         }
         const hipError_t f = (hipError_t)temp_free(out, stream);
         if (e == hipSuccess) e = f;
@@ -503,22 +501,21 @@ hipError_t launch_gemm_vp(const KView& k, const float* X, float* Y, const float*
         const uint32_t ntiles_tab = ntiles | ((uint32_t)k.rank_tab_shift << 28);
         if (TW == 32 && V == 4 && short_rows) {
             if (tab)
-                hipLaunchKernelGGL((cer_gemm_expand_kernel<IdxT, 4, 8, false, kExpChunkShort, false, true>), dim3(ipx * 8), dim3(256),
+                return launch_kernel((cer_gemm_expand_kernel<IdxT, 4, 8, false, kExpChunkShort, false, true>), dim3(ipx * 8), dim3(256),
                                    0, stream, k.rank_tab, k.colI, X, Y, L, ntiles_tab, rowblocks, ipx, k.m, T, k, SplitArgs{});
             else
-                hipLaunchKernelGGL((cer_gemm_expand_kernel<IdxT, 4, 8, false, kExpChunkShort>), dim3(ipx * 8), dim3(256), 0, stream,
+                return launch_kernel((cer_gemm_expand_kernel<IdxT, 4, 8, false, kExpChunkShort>), dim3(ipx * 8), dim3(256), 0, stream,
                                    k.rowInfo, k.colI, X, Y, L, ntiles, rowblocks, ipx, k.m, T, k, SplitArgs{});
         } else if (tab && V == 4) {
-            hipLaunchKernelGGL((cer_gemm_expand_kernel<IdxT, 4, (V == 4 ? P : 8), false, kExpChunkLong, false, true>), dim3(ipx * 8),
+            return launch_kernel((cer_gemm_expand_kernel<IdxT, 4, (V == 4 ? P : 8), false, kExpChunkLong, false, true>), dim3(ipx * 8),
                                dim3(256), 0, stream, k.rank_tab, k.colI, X, Y, L, ntiles_tab, rowblocks, ipx, k.m, T, k, SplitArgs{});
         } else {
-            hipLaunchKernelGGL((cer_gemm_expand_kernel<IdxT, V, P, false>), dim3(ipx * 8), dim3(256), 0, stream, k.rowInfo, k.colI,
+            return launch_kernel((cer_gemm_expand_kernel<IdxT, V, P, false>), dim3(ipx * 8), dim3(256), 0, stream, k.rowInfo, k.colI,
                                X, Y, L, ntiles, rowblocks, ipx, k.m, T, k, SplitArgs{});
         }
     } else
-        hipLaunchKernelGGL((cer_gemm_kernel<IdxT, V, P>), dim3(ipx * 8), dim3(256), 0, stream, k, X, Y, T, L, ntiles,
+        return launch_kernel((cer_gemm_kernel<IdxT, V, P>), dim3(ipx * 8), dim3(256), 0, stream, k, X, Y, T, L, ntiles,
                            rowblocks, ipx);
-    return hipGetLastError();
 }
 
 // The default kernel on a batch whose width is not a multiple of 4, or whose X / Y are only 4-byte aligned (L >= 4).
@@ -539,12 +536,11 @@ hipError_t launch_gemm_ragged(const KView& k, const float* X, float* Y, const fl
                                    rowblocks, ipx, sp, stream);
     }
     if (P == 8 && short_rows)
-        hipLaunchKernelGGL((cer_gemm_expand_kernel<IdxT, 4, 8, true, kExpChunkShort>), dim3(ipx * 8), dim3(256), 0, stream,
+        return launch_kernel((cer_gemm_expand_kernel<IdxT, 4, 8, true, kExpChunkShort>), dim3(ipx * 8), dim3(256), 0, stream,
                            k.rowInfo, k.colI, X, Y, L, ntiles, rowblocks, ipx, k.m, T, k, SplitArgs{});
     else
-        hipLaunchKernelGGL((cer_gemm_expand_kernel<IdxT, 4, P, true>), dim3(ipx * 8), dim3(256), 0, stream, k.rowInfo, k.colI, X,
+        return launch_kernel((cer_gemm_expand_kernel<IdxT, 4, P, true>), dim3(ipx * 8), dim3(256), 0, stream, k.rowInfo, k.colI, X,
                            Y, L, ntiles, rowblocks, ipx, k.m, T, k, SplitArgs{});
-    return hipGetLastError();
 }
 
 // Tile width (32, 64 or 128 batch columns) for a batch wider than 32 columns.  A gather instruction costs what the

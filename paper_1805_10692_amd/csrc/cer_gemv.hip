@@ -1102,9 +1102,8 @@ hipError_t launch_gemv(const DeviceView& d, const KView& k, const float* X, floa
             if (c.load(std::memory_order_acquire) != 1) return hipErrorInvalidDeviceFunction;
         }
         const uint32_t meta = k.K | ((uint32_t)d.rank_tab_shift << 9) | (part_shift << 13) | ((uint32_t)waves << 16);
-        hipLaunchKernelGGL(tk, dim3(blocks), dim3(waves * kWave), lds, stream, d.rank_tab, X, k.omega, k.colI, Y, k.n, k.m,
+        return launch_kernel(tk, dim3(blocks), dim3(waves * kWave), lds, stream, d.rank_tab, X, k.omega, k.colI, Y, k.n, k.m,
                            rows_per_block, meta);
-        return hipGetLastError();
     }
     using Kern = void (*)(const void*, const uint2*, const float*, float*, const uint32_t*, const float*, uint32_t, uint32_t,
                           uint32_t, uint32_t, uint32_t, float, const void*, const float*, int, int);
@@ -1125,9 +1124,8 @@ hipError_t launch_gemv(const DeviceView& d, const KView& k, const float* X, floa
         const hipError_t e = grant.ensure(wslot * 12 + kslot, reinterpret_cast<const void*>(kern), budget);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(waves * kWave), lds, stream, k.colI, k.rowInfo, X, Y, k.omegaPtr, k.omega, k.n,
+    return launch_kernel(kern, dim3(blocks), dim3(waves * kWave), lds, stream, k.colI, k.rowInfo, X, Y, k.omegaPtr, k.omega, k.n,
                        k.m, k.K, rows_per_block | (part_shift << 28), gcap, k.omega0, k.omegaI, T, k.omegaI_bits, omega_in_lds ? 1 : 0);
-    return hipGetLastError();
 }
 
 // Launch shape of the expansion kernel; waves == 0: X, Omega and the value arrays of four waves do not fit in LDS.
@@ -1180,9 +1178,8 @@ hipError_t launch_gemv_expand(const DeviceView& d, const KView& k, const GemvExp
     }
     const uint32_t rows_per_block = (uint32_t)p.waves;
     const uint32_t blocks = (k.m + rows_per_block - 1) / rows_per_block;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(p.waves * kWave), p.lds, stream, k, X, Y, rows_per_block,
+    return launch_kernel(kern, dim3(blocks), dim3(p.waves * kWave), p.lds, stream, k, X, Y, rows_per_block,
                        p.omega_in_lds ? 1 : 0);
-    return hipGetLastError();
 }
 
 }  // namespace
@@ -1190,9 +1187,8 @@ hipError_t launch_gemv_expand(const DeviceView& d, const KView& k, const GemvExp
 int build_rank_table(const DeviceView& d, void* stream) {
     if (!d.rank_tab || d.m <= 0) return (int)hipSuccess;
     const KView k = make_kview(d);
-    hipLaunchKernelGGL(rank_table_kernel, dim3((uint32_t)((d.m + 3) / 4)), dim3(256), 0, static_cast<hipStream_t>(stream), k,
+    return (int)launch_kernel(rank_table_kernel, dim3((uint32_t)((d.m + 3) / 4)), dim3(256), 0, static_cast<hipStream_t>(stream), k,
                        const_cast<uint32_t*>(d.rank_tab), (uint32_t)d.rank_tab_shift);
-    return (int)hipGetLastError();
 }
 
 int gemv_path(const DeviceView& d, const MatmulOptions& o) { return gemv_expand_choice(d, o).waves > 0 ? 4 : 0; }

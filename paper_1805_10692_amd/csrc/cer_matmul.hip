@@ -83,14 +83,13 @@ __global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restri
 hipError_t launch_colsum(const float* X, uint32_t n, uint32_t L, float* part, uint32_t nslabs, uint32_t slab,
                          uint32_t CB, float* T, hipStream_t stream) {
     const uint32_t coltiles = (L + CB - 1) / CB;
+    hipError_t e;
     if (L >= 1024u && L % 4u == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0 && (reinterpret_cast<uintptr_t>(part) & 15u) == 0)
-        hipLaunchKernelGGL(colsum_partial4_kernel, dim3((L + 1023u) / 1024u, nslabs), dim3(256), 0, stream, X, n, L, slab, part);
+        e = launch_kernel(colsum_partial4_kernel, dim3((L + 1023u) / 1024u, nslabs), dim3(256), 0, stream, X, n, L, slab, part);
     else
-        hipLaunchKernelGGL(colsum_partial_kernel, dim3(coltiles, nslabs), dim3(256), 0, stream, X, n, L, CB, slab, part);
-    hipError_t e = hipGetLastError();
+        e = launch_kernel(colsum_partial_kernel, dim3(coltiles, nslabs), dim3(256), 0, stream, X, n, L, CB, slab, part);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(colsum_final_kernel, dim3((L + 255) / 256), dim3(256), 0, stream, part, nslabs, L, T);
-    return hipGetLastError();
+    return launch_kernel(colsum_final_kernel, dim3((L + 255) / 256), dim3(256), 0, stream, part, nslabs, L, T);
 }
 
 // Large batches of a matrix that is not sparse enough: the gathers move nnz.4.batch bytes through the L1/L2 path

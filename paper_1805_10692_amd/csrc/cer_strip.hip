@@ -389,21 +389,19 @@ hipError_t launch_strip(const DeviceView& d, const float* X, float* Y, const flo
                      : (aligned_x ? cer_strip_kernel<false, true> : cer_strip_kernel<false, false>);
     e = grant.ensure((half ? 2 : 0) + (aligned_x ? 1 : 0), reinterpret_cast<const void*>(kern), strip_lds_bytes(kStripMaxRows));
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(kern, dim3((uint32_t)sp.blocks), dim3(1024), strip_lds_bytes(sp.rows_per_split), stream,
+        e = launch_kernel(kern, dim3((uint32_t)sp.blocks), dim3(1024), strip_lds_bytes(sp.rows_per_split), stream,
                            static_cast<const uint4*>(d.strip_idx), d.strip_ptr, X, part, d.omega, m, n, L, (uint32_t)d.K,
                            sp.ntiles, sp.nsplit, sp.rows_per_split, (uint32_t)d.strip_chunks, d.strip_rows);
-        e = hipGetLastError();
     }
     if (e == hipSuccess) {
         const uint64_t plane_f4 = (uint64_t)m * row_f4;
         const dim3 grid((uint32_t)((plane_f4 + 255) / 256));
         if (aligned_y)
-            hipLaunchKernelGGL(cer_strip_sum_kernel<true>, grid, dim3(256), 0, stream, part, Y, T, d.omega0, d.n_strips, plane_f4,
+            e = launch_kernel(cer_strip_sum_kernel<true>, grid, dim3(256), 0, stream, part, Y, T, d.omega0, d.n_strips, plane_f4,
                                row_f4, L);
         else
-            hipLaunchKernelGGL(cer_strip_sum_kernel<false>, grid, dim3(256), 0, stream, part, Y, T, d.omega0, d.n_strips, plane_f4,
+            e = launch_kernel(cer_strip_sum_kernel<false>, grid, dim3(256), 0, stream, part, Y, T, d.omega0, d.n_strips, plane_f4,
                                row_f4, L);
-        e = hipGetLastError();
     }
     const hipError_t f = (hipError_t)temp_free(part, stream);
     return e == hipSuccess ? f : e;

@@ -247,9 +247,8 @@ hipError_t launch_xtile_v(const DeviceView& d, const KView& k, const XtilePlan& 
         const hipError_t e = grant.ensure(slot * 2 + (k.cser ? 1 : 0), reinterpret_cast<const void*>(kern), d.lds_per_block);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3(p.blocks), dim3(kXtWaves * kWave), p.lds, stream, k, Xp, Y, T, L, p.ntiles, p.rpw, p.pcap,
+    return launch_kernel(kern, dim3(p.blocks), dim3(kXtWaves * kWave), p.lds, stream, k, Xp, Y, T, L, p.ntiles, p.rpw, p.pcap,
                        raw_x);
-    return hipGetLastError();
 }
 
 template <typename IdxT>
@@ -266,10 +265,9 @@ hipError_t launch_xtile(const DeviceView& d, const KView& k, const XtilePlan& p,
         const int vec_ok = (L % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0) ? 1 : 0;
         const dim3 grid((k.n + 63) / 64, (p.ntiles + 15) / 16);
         if (p.V == 8)
-            hipLaunchKernelGGL(xtile_pack_kernel<8>, grid, dim3(256), 0, stream, X, k.n, L, p.ntiles, vec_ok, tmp);
+            e = launch_kernel(xtile_pack_kernel<8>, grid, dim3(256), 0, stream, X, k.n, L, p.ntiles, vec_ok, tmp);
         else
-            hipLaunchKernelGGL(xtile_pack_kernel<4>, grid, dim3(256), 0, stream, X, k.n, L, p.ntiles, vec_ok, tmp);
-        e = hipGetLastError();
+            e = launch_kernel(xtile_pack_kernel<4>, grid, dim3(256), 0, stream, X, k.n, L, p.ntiles, vec_ok, tmp);
         if (e != hipSuccess) {
             (void)temp_free(tmp, stream);
             return e;
