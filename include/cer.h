@@ -145,7 +145,8 @@ int cer_matmul_noalloc(const cer_handle_t* h, const float* X_dev, float* Y_dev, 
  * cer_trim -- gives the device memory of released temporaries back to the system.  The products and
  * conversions that need a temporary (see each call) take it, ordered on the caller's stream, from
  * blocks the library keeps on the current device; they are kept (at most 2 GiB of them) because getting
- * a few hundred megabytes from the system again costs more than the product that needs them.  cer_trim
+ * a few hundred megabytes from the system again costs more than the product that needs them.  The
+ * device memory of freed handles is kept in the same way for later handles (at most 1 GiB).  cer_trim
  * releases whatever is not in use at the moment of the call on the current device; it may wait for
  * work queued on the null stream and may be called at any time.  Errors: CER_E_HIP.
  */
@@ -309,7 +310,8 @@ int64_t cer_device_bytes(const cer_handle_t* h);
  * handles). */
 int64_t cer_long_row_parts(const cer_handle_t* h);
 
-/* Frees host and device memory.  NULL is allowed. */
+/* Frees host and device memory (the latter may be kept for later handles: cer_trim).  Work already
+ * queued on the handle may still be running.  NULL is allowed. */
 void cer_free(cer_handle_t* h);
 
 /*

@@ -205,6 +205,112 @@ int cer::temp_free(void* p, void* stream) {
     return (int)hipFreeAsync(p, s);
 }
 
+// ---- device memory of handles ------------------------------------------------------------------------------------
+namespace {
+struct HandleBlock {
+    void* p = nullptr;
+    size_t bytes = 0;
+    bool null_stream_only = false;
+    bool idle = false;  // the device has been waited for since the block came back
+};
+constexpr size_t kHandleBlocksKept = 16, kHandleBytesKept = (size_t)1 << 30;
+struct HandleCache {
+    std::mutex mu;
+    std::vector<HandleBlock> kept;    // oldest first
+    std::vector<HandleBlock> in_use;
+    size_t kept_bytes = 0;
+};
+HandleCache g_handle_caches[16];
+
+HandleCache* handle_cache() {
+    int dev = 0;
+    return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 16 ? &g_handle_caches[dev] : nullptr;
+}
+
+// Sizes in steps of an eighth of their power of two (at least 64 KiB), so that layers of about the same size share blocks.
+size_t handle_block_bytes(size_t bytes) {
+    size_t step = 65536;
+    while (step * 16 <= bytes) step <<= 1;
+    return (bytes + step - 1) / step * step;
+}
+}  // namespace
+
+int cer::handle_alloc(void** p, size_t bytes, void* stream) {
+    const size_t want = handle_block_bytes(bytes);
+    HandleCache* c = handle_cache();
+    if (c) {
+        std::lock_guard<std::mutex> lock(c->mu);
+        for (int pass = 0; pass < 2; ++pass) {  // blocks that need no wait come first
+            size_t best = SIZE_MAX;
+            for (size_t i = 0; i < c->kept.size(); ++i) {
+                const HandleBlock& b = c->kept[i];
+                if (b.bytes < want || b.bytes > want + want / 4) continue;
+                if (pass == 0 && !b.idle && !(b.null_stream_only && !stream)) continue;
+                if (best == SIZE_MAX || b.bytes < c->kept[best].bytes) best = i;
+            }
+            if (best == SIZE_MAX) continue;
+            if (pass == 1) {
+                if (hipDeviceSynchronize() != hipSuccess) {  // also under capture: a fresh block then
+                    (void)hipGetLastError();
+                    break;
+                }
+                for (HandleBlock& b : c->kept) b.idle = true;
+            }
+            const HandleBlock b = c->kept[best];
+            c->in_use.push_back(b);
+            c->kept.erase(c->kept.begin() + (ptrdiff_t)best);
+            c->kept_bytes -= b.bytes;
+            *p = b.p;
+            return (int)hipSuccess;
+        }
+    }
+    hipError_t e = hipMalloc(p, want);
+    if (e == hipErrorOutOfMemory && c) {  // what is kept may be what is missing
+        (void)hipGetLastError();
+        (void)cer_trim();
+        e = hipMalloc(p, want);
+    }
+    if (e == hipSuccess && c) {
+        std::lock_guard<std::mutex> lock(c->mu);
+        c->in_use.push_back(HandleBlock{*p, want, false, true});
+    }
+    return (int)e;
+}
+
+void cer::handle_free(void* p, bool null_stream_only) {
+    if (!p) return;
+    // the block may belong to a device that is not the current one
+    for (HandleCache& c : g_handle_caches) {
+        std::vector<void*> out;
+        bool found = false;
+        {
+            std::lock_guard<std::mutex> lock(c.mu);
+            for (size_t i = 0; i < c.in_use.size() && !found; ++i) {
+                if (c.in_use[i].p != p) continue;
+                found = true;
+                HandleBlock b = c.in_use[i];
+                c.in_use.erase(c.in_use.begin() + (ptrdiff_t)i);
+                b.null_stream_only = null_stream_only;
+                b.idle = false;
+                if (b.bytes > kHandleBytesKept) {
+                    out.push_back(b.p);
+                    break;
+                }
+                while (!c.kept.empty() && (c.kept.size() >= kHandleBlocksKept || c.kept_bytes + b.bytes > kHandleBytesKept)) {
+                    out.push_back(c.kept[0].p);
+                    c.kept_bytes -= c.kept[0].bytes;
+                    c.kept.erase(c.kept.begin());
+                }
+                c.kept.push_back(b);
+                c.kept_bytes += b.bytes;
+            }
+        }
+        for (void* q : out) (void)hipFree(q);
+        if (found) return;
+    }
+    (void)hipFree(p);
+}
+
 
 namespace {
 
@@ -400,14 +506,14 @@ int cer::build_row_schedule(cer_matrix* h, const std::vector<uint64_t>& start) {
     }
     const size_t order_bytes = (order.size() * 4 + 15) & ~(size_t)15, part_bytes = parts.size() * 4, row_bytes = rows.size() * 4;
     void* base = nullptr;
-    hipError_t e = hipMalloc(&base, order_bytes + part_bytes + row_bytes + 16);
+    hipError_t e = (hipError_t)handle_alloc(&base, order_bytes + part_bytes + row_bytes + 16, nullptr);
     if (e != hipSuccess) return hip_fail(e);
     auto* b8 = static_cast<unsigned char*>(base);
     e = hipMemcpy(b8, order.data(), order.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess && part_bytes) e = hipMemcpy(b8 + order_bytes, parts.data(), part_bytes, hipMemcpyHostToDevice);
     if (e == hipSuccess && row_bytes) e = hipMemcpy(b8 + order_bytes + part_bytes, rows.data(), row_bytes, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
-        (void)hipFree(base);
+        handle_free(base, true);
         return hip_fail(e);
     }
     h->d_split = base;
@@ -438,7 +544,7 @@ int upload(cer_matrix* h) {
 
     const cer::DeviceLayout l = cer::DeviceLayout::make(A.colI.bytes.size(), A.G, A.m, A.omegaI.bytes.size(), A.K);
     void* base = nullptr;
-    e = hipMalloc(&base, l.total);
+    e = (hipError_t)cer::handle_alloc(&base, l.total, nullptr);
     if (e != hipSuccess) return hip_fail(e);
     auto* b = static_cast<unsigned char*>(base);
     e = hipMemset(base, 0, l.total);
@@ -463,7 +569,7 @@ int upload(cer_matrix* h) {
     put(l.off_oi, A.omegaI.bytes.data(), l.omegaI_bytes);
     put(l.off_om, A.omega.data(), A.omega.size() * 4);
     if (e != hipSuccess) {
-        (void)hipFree(base);
+        cer::handle_free(base, true);
         return hip_fail(e);
     }
     cer::bind_device(h, dev, base, l);
@@ -520,6 +626,11 @@ bool read_options(const cer_matmul_opts_t* in, cer::MatmulOptions* out) {
     return true;
 }
 
+// Work on `stream` is about to use the handle's device arrays (cer_free wants to know).
+void note_stream(const cer_handle_t* h, void* stream) {
+    if (stream && !h->off_null_stream.load(std::memory_order_relaxed)) h->off_null_stream.store(true, std::memory_order_relaxed);
+}
+
 // The handle's device is the current one and holds its arrays; else the CER_* code to return.
 int check_device(const cer_handle_t* h) {
     if (h->device < 0 || !h->d_base) {
@@ -541,6 +652,7 @@ int matmul_any(const cer_handle_t* h, int want_cser /* -1: either */, const floa
     if (!read_options(opts, &o)) return CER_E_INVALID;
     const int dc = check_device(h);
     if (dc != CER_OK) return dc;
+    note_stream(h, stream);
     const int rc = cer::launch_matmul(h->view, X, Y, batch, stream, o);
     return rc == 0 ? CER_OK : hip_fail((hipError_t)rc);
 }
@@ -590,6 +702,7 @@ int cer_matmul_noalloc(const cer_handle_t* h, const float* X, float* Y, int64_t 
     if (we != 0) return hip_fail((hipError_t)we);
     const cer::MatmulOptions o;
     if (cer::matmul_workspace_floats(h->view, batch, o) > ws_floats) return CER_E_TOO_LARGE;
+    note_stream(h, stream);
     const int rc = cer::launch_matmul(h->view, X, Y, batch, stream, o, ws, ws_floats);
     return rc == 0 ? CER_OK : hip_fail((hipError_t)rc);
 }
@@ -736,6 +849,7 @@ int cer_decode_device(const cer_handle_t* h, float* W, void* stream) {
     if (e != hipSuccess) return hip_fail(e);
     if (dev != h->device) return hip_fail(hipErrorInvalidDevice);
     if (h->host->m * h->host->n > 0 && h->host->K < 1) return CER_E_INVALID;
+    note_stream(h, stream);
     return cer::decode_device(h->view, W, stream);
 }
 
@@ -800,13 +914,13 @@ int cer_prepare_strips(cer_handle_t* h) {
         });
         const size_t idx_bytes = (idx.size() * 2 + 255) & ~(size_t)255, ptr_bytes = (ptr.size() - 1) * 4;
         void* base = nullptr;
-        hipError_t e = hipMalloc(&base, idx_bytes + ptr_bytes + 256);
+        hipError_t e = (hipError_t)cer::handle_alloc(&base, idx_bytes + ptr_bytes + 256, nullptr);
         if (e != hipSuccess) return hip_fail(e);
         auto* b8 = static_cast<unsigned char*>(base);
         if (!idx.empty()) e = hipMemcpy(b8, idx.data(), idx.size() * 2, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(b8 + idx_bytes, ptr.data(), ptr_bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
-            (void)hipFree(base);
+            cer::handle_free(base, true);
             return hip_fail(e);
         }
         h->d_strip = base;
@@ -829,9 +943,10 @@ int64_t cer_long_row_parts(const cer_handle_t* h) { return (h && h->device >= 0)
 
 void cer_free(cer_handle_t* h) {
     if (!h) return;
-    if (h->d_base) (void)hipFree(h->d_base);
-    if (h->d_split) (void)hipFree(h->d_split);
-    if (h->d_strip) (void)hipFree(h->d_strip);
+    const bool null_only = !h->off_null_stream.load(std::memory_order_relaxed);
+    cer::handle_free(h->d_base, null_only);
+    cer::handle_free(h->d_split, null_only);
+    cer::handle_free(h->d_strip, null_only);
     delete h;
 }
 
@@ -870,6 +985,13 @@ int cer_trim(void) {
             }
             release_kept(c, i);
         }
+    }
+    {
+        HandleCache& c = g_handle_caches[dev];
+        std::lock_guard<std::mutex> lock(c.mu);
+        for (const HandleBlock& b : c.kept) (void)hipFree(b.p);
+        c.kept.clear();
+        c.kept_bytes = 0;
     }
     TempPool& t = g_temp_pools[dev];
     std::lock_guard<std::mutex> lock(t.mu);

@@ -158,6 +158,13 @@ int record_hip_error(int hip_error);
 int temp_alloc(void** p, size_t bytes, void* stream);
 int temp_free(void* p, void* stream);
 
+// Device memory of handles (cer_capi.cpp).  What cer_free gives back is kept, up to a bound, for the next handle: hipMalloc
+// and hipFree of a layer's 60 MB take 80 - 300 us each, more than the encoding itself.  handle_alloc: memory that `stream`
+// may write at once.  handle_free: null_stream_only says that nothing but the null stream has used the block; otherwise
+// it serves again only after the whole device has been waited for (hipFree would have waited at this point).
+int handle_alloc(void** p, size_t bytes, void* stream);
+void handle_free(void* p, bool null_stream_only);
+
 }  // namespace cer
 
 namespace cer {
@@ -178,6 +185,7 @@ struct cer_matrix {
     size_t d_bytes = 0;       // its size
     int64_t stream_bytes = 0; // bytes of format arrays a product reads
     cer::DeviceView view;
+    mutable std::atomic<bool> off_null_stream{false};  // some stream other than the null stream has used the device arrays
 };
 
 // CSR comparator (csr.hip)

@@ -1,14 +1,15 @@
 // Device front-end: a dense fp32 weight matrix that already lives in HBM goes to CER / CSER without a
 // trip through the host -- optionally through the uniform quantizer of Section V-B first.
 //
-//   range     min / max of W (quantizer only); the K = 2^b points of the codebook
-//   codes     element -> codebook position (quantizer: nearest point; otherwise: exact look-up),
-//             one byte per element, and a per-row histogram over the positions
-//   rank      global histogram -> frequency-major order Omega (Section III-A, step 1)
-//   layout    per row: number of indexed elements and of groups; exclusive scans over the rows give
-//             every row its slice of colI and of OmegaPtr / OmegaI
+//   range     min / max of W (quantizer only)
+//   codes     the K = 2^b points of the codebook; element -> codebook position (quantizer: nearest point;
+//             otherwise: exact look-up), one byte per element, and a per-row histogram over the positions
+//   hist      global histogram in partial sums
+//   layout    frequency-major order Omega (Section III-A, step 1); per row: number of indexed elements and of groups
+//   scan      exclusive scans over the rows give every row its slice of colI and of OmegaPtr / OmegaI; the sizes go to
+//             the host, which allocates the handle
 //   emit      per row: a stable counting sort of the columns by rank writes colI, the bucket ends are
-//             the row's pointers (steps 2-4)
+//             the row's pointers (steps 2-4) and its record of the rank table
 //
 // One wave owns one row in `layout` and `emit`, so no two waves ever write the same output element
 // and the result does not depend on scheduling: it is the same array, bit for bit, as the host
@@ -18,15 +19,16 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 
 #include "../../include/cer.h"
-#include "cer_internal.hpp"
+#include "cer_device.hpp"
 
 namespace {
 
-constexpr int kWave = 64;
+using cer::kWave;
 constexpr int kCodes = 256;  // most codebook positions a byte can name
 
 enum : uint32_t {
@@ -36,23 +38,29 @@ enum : uint32_t {
     kFlagTooLarge = 8u,   // 32-bit offsets do not reach
 };
 
-// Small block of device memory the kernels communicate through; copied to the host once.
+// Small block of device memory the kernels communicate through.
 struct FrontState {
-    float wmin, wmax, step;
     uint32_t flags;
     uint32_t K;         // codebook positions in use (caller's K, or the quantizer's point count)
     uint32_t Kp;        // values that occur = length of Omega
-    uint32_t max_row_groups;
-    uint32_t max_row_nnz;  // indexed elements of the longest row
-    unsigned long long nnz, G, nonempty;
-    unsigned long long hist[kCodes];   // occurrences by codebook position
     unsigned long long count[kCodes];  // occurrences by rank
     float codebook[kCodes];            // value by codebook position
-    float sorted_val[kCodes];          // look-up path: codebook sorted by value ...
-    uint32_t sorted_pos[kCodes];       // ... and the position each came from
     float omega[kCodes];               // value by rank
     uint32_t rank_of[kCodes];          // codebook position -> rank
     uint32_t pos_of[kCodes];           // rank -> codebook position
+};
+
+// What the host needs to know before it can allocate the handle; the last kernel of the first part writes it straight
+// into pinned host memory (`ready` last).
+struct FrontResult {
+    uint32_t flags, K, Kp;
+    uint32_t max_row_groups;
+    uint32_t max_row_nnz;  // indexed elements of the longest row
+    unsigned long long nnz, G, nonempty;
+    unsigned long long count[kCodes];
+    float codebook[kCodes];
+    float omega[kCodes];
+    uint32_t ready;
 };
 
 // LDS traffic of one wave is ordered; this only keeps the compiler from moving accesses across.
@@ -73,22 +81,39 @@ __device__ __forceinline__ void range_take(float w, float& lo, float& hi, uint32
     hi = fmaxf(hi, w);
 }
 
-__global__ __launch_bounds__(256) void range_kernel(const float* __restrict__ W, int64_t N, float* __restrict__ part_min,
-                                                    float* __restrict__ part_max, uint32_t* __restrict__ part_bad) {
+constexpr int kRangeParts = 1024;  // most workgroups of range_kernel: four per compute unit, eight loads in flight per thread
+
+// Partial results {min, max, not-finite flag}; the workgroups of codes_kernel finish the reduction themselves (one launch
+// less, 16 KiB of L2 reads per workgroup at most).  Bound by the read of W.
+__global__ __launch_bounds__(256) void range_kernel(const float* __restrict__ W, int64_t N, float4* __restrict__ part,
+                                                    FrontState* __restrict__ st) {
     float lo = INFINITY, hi = -INFINITY;
     uint32_t bad = 0;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
     // the bulk in 16-byte pieces (W is aligned by the caller's allocator or the scalar loop below takes it all)
     const int64_t N4 = ((reinterpret_cast<uintptr_t>(W) & 15u) == 0) ? N / 4 : 0;
     const float4* W4 = reinterpret_cast<const float4*>(W);
-    for (int64_t i = tid; i < N4; i += stride) {
+    int64_t i = tid;
+    for (; i + 7 * stride < N4; i += 8 * stride) {
+        float4 w[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w[k] = W4[i + k * stride];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            range_take(w[k].x, lo, hi, bad);
+            range_take(w[k].y, lo, hi, bad);
+            range_take(w[k].z, lo, hi, bad);
+            range_take(w[k].w, lo, hi, bad);
+        }
+    }
+    for (; i < N4; i += stride) {
         const float4 w = W4[i];
         range_take(w.x, lo, hi, bad);
         range_take(w.y, lo, hi, bad);
         range_take(w.z, lo, hi, bad);
         range_take(w.w, lo, hi, bad);
     }
-    for (int64_t i = N4 * 4 + tid; i < N; i += stride) range_take(W[i], lo, hi, bad);
+    for (i = N4 * 4 + tid; i < N; i += stride) range_take(W[i], lo, hi, bad);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         lo = fminf(lo, __shfl_xor(lo, off, kWave));
@@ -105,62 +130,24 @@ __global__ __launch_bounds__(256) void range_kernel(const float* __restrict__ W,
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        part_min[blockIdx.x] = fminf(fminf(s_lo[0], s_lo[1]), fminf(s_lo[2], s_lo[3]));
-        part_max[blockIdx.x] = fmaxf(fmaxf(s_hi[0], s_hi[1]), fmaxf(s_hi[2], s_hi[3]));
-        part_bad[blockIdx.x] = s_bad[0] | s_bad[1] | s_bad[2] | s_bad[3];
+        const uint32_t any = s_bad[0] | s_bad[1] | s_bad[2] | s_bad[3];
+        part[blockIdx.x] = make_float4(fminf(fminf(s_lo[0], s_lo[1]), fminf(s_lo[2], s_lo[3])),
+                                       fmaxf(fmaxf(s_hi[0], s_hi[1]), fmaxf(s_hi[2], s_hi[3])), any ? 1.f : 0.f, 0.f);
+        if (blockIdx.x == 0) st->flags = 0;
     }
 }
 
-// One block of 256 threads: finish the reduction, then lay the K = 2^bits points on the range
-// (Section V-B).  Every operation rounds once, to binary32: step = (max - min) / (K - 1),
-// point_j = min + j.step, the last point is max itself.  A constant matrix has one point.
-__global__ __launch_bounds__(256) void points_kernel(const float* __restrict__ part_min, const float* __restrict__ part_max,
-                                                     const uint32_t* __restrict__ part_bad, int nparts, int bits,
-                                                     FrontState* __restrict__ st) {
-#pragma clang fp contract(off)
-    __shared__ float s_lo[256], s_hi[256];
-    __shared__ uint32_t s_bad[256];
-    __shared__ float s_pts[kCodes];
+// The caller's codebook, handed over as a kernel argument, into the state.
+struct CodebookArg {
+    float v[kCodes];
+    uint32_t K;
+};
+__global__ __launch_bounds__(256) void codebook_kernel(CodebookArg cb, FrontState* __restrict__ st) {
     const uint32_t t = threadIdx.x;
-    float lo = INFINITY, hi = -INFINITY;
-    uint32_t bad = 0;
-    for (int i = (int)t; i < nparts; i += 256) {
-        lo = fminf(lo, part_min[i]);
-        hi = fmaxf(hi, part_max[i]);
-        bad |= part_bad[i];
-    }
-    s_lo[t] = lo;
-    s_hi[t] = hi;
-    s_bad[t] = bad;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)t < off) {
-            s_lo[t] = fminf(s_lo[t], s_lo[t + off]);
-            s_hi[t] = fmaxf(s_hi[t], s_hi[t + off]);
-            s_bad[t] |= s_bad[t + off];
-        }
-        __syncthreads();
-    }
-    const float wmin = s_lo[0] + 0.0f, wmax = s_hi[0] + 0.0f;  // -0.0 -> +0.0
-    const uint32_t K = (wmin == wmax) ? 1u : (1u << bits);
-    const float step = (K > 1) ? (wmax - wmin) / (float)(K - 1) : 0.0f;
-    float p = 0.f;
-    if (t < K) {
-        const float prod = (float)t * step;
-        p = prod + wmin;
-        if (t == K - 1) p = wmax;
-        if (K == 1) p = wmin;
-        st->codebook[t] = p;
-    }
-    s_pts[t] = p;
-    __syncthreads();
-    if (t + 1 < K && !(s_pts[t + 1] > s_pts[t])) atomicOr(&st->flags, kFlagCollide);
+    if (t < cb.K) st->codebook[t] = cb.v[t];
     if (t == 0) {
-        st->wmin = wmin;
-        st->wmax = wmax;
-        st->step = step;
-        st->K = K;
-        if (s_bad[0]) atomicOr(&st->flags, kFlagNonFinite);
+        st->flags = 0;
+        st->K = cb.K;
     }
 }
 
@@ -208,135 +195,219 @@ __device__ __forceinline__ uint32_t code_of(float w, const CodeCtx& c, bool& mis
 
 // Each thread takes four consecutive elements per round: one 16-byte load, four codes, one 4-byte
 // store (a row whose length or address does not allow that falls back to single elements).
+// kQuant: every workgroup first finishes the min / max reduction from the partial results of range_kernel and lays the
+// K = 2^bits points on the range (Section V-B).  Every operation rounds once, to binary32: step = (max - min) / (K - 1),
+// point_j = min + j.step, the last point is max itself.  A constant matrix has one point.  Workgroup 0 publishes them.
 template <bool kQuant>
-__global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W, int64_t total, int64_t row_len,
+__global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W, int64_t total, int64_t rows, int64_t row_len,
+                                                    const float4* __restrict__ part, int nparts, int bits,
                                                     FrontState* __restrict__ st, uint8_t* __restrict__ codes,
                                                     uint32_t* __restrict__ cnt, float* __restrict__ Wq, int vec_ok) {
+#pragma clang fp contract(off)
     __shared__ uint32_t s_hist[kCodes];
     __shared__ float s_val[kCodes];
     __shared__ uint32_t s_hkey[kQuant ? 1 : kHashSlots], s_hpos[kQuant ? 1 : kHashSlots];
+    __shared__ float s_lo[4], s_hi[4];
     const uint32_t t = threadIdx.x;
-    const int64_t r = blockIdx.x;
     CodeCtx c;
-    c.K = st->K;
     s_hist[t] = 0;
     if (kQuant) {
-        s_val[t] = t < c.K ? st->codebook[t] : 0.f;
+        float lo = INFINITY, hi = -INFINITY, bad = 0.f;
+        for (int i = (int)t; i < nparts; i += 256) {
+            const float4 p = part[i];
+            lo = fminf(lo, p.x);
+            hi = fmaxf(hi, p.y);
+            bad = fmaxf(bad, p.z);
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            lo = fminf(lo, __shfl_xor(lo, off, kWave));
+            hi = fmaxf(hi, __shfl_xor(hi, off, kWave));
+        }
+        if ((t & 63u) == 0) {
+            s_lo[t >> 6] = lo;
+            s_hi[t >> 6] = hi;
+        }
+        const bool any_bad = __syncthreads_or(bad > 0.f);
+        const float wmin = fminf(fminf(s_lo[0], s_lo[1]), fminf(s_lo[2], s_lo[3])) + 0.0f;  // -0.0 -> +0.0
+        const float wmax = fmaxf(fmaxf(s_hi[0], s_hi[1]), fmaxf(s_hi[2], s_hi[3])) + 0.0f;
+        const uint32_t K = (wmin == wmax) ? 1u : (1u << bits);
+        const float step = (K > 1) ? (wmax - wmin) / (float)(K - 1) : 0.0f;
+        float p = 0.f;
+        if (t < K) {
+            const float prod = (float)t * step;
+            p = prod + wmin;
+            if (t == K - 1) p = wmax;
+            if (K == 1) p = wmin;
+        }
+        s_val[t] = p;
+        c.K = K;
+        c.wmin = wmin;
+        c.step = step;
+        __syncthreads();
+        if (blockIdx.x == 0) {
+            if (t < K) st->codebook[t] = p;
+            if (t + 1 < K && !(s_val[t + 1] > s_val[t])) atomicOr(&st->flags, kFlagCollide);
+            if (t == 0) {
+                st->K = K;
+                if (any_bad) atomicOr(&st->flags, kFlagNonFinite);
+            }
+        }
     } else {
+        c.K = st->K;
+        c.wmin = c.step = 0.f;
         for (uint32_t i = t; i < kHashSlots; i += 256) s_hkey[i] = kHashFree;
         __syncthreads();
         if (t < c.K) {
-            const uint32_t bits = __float_as_uint(canonical(st->sorted_val[t]));
-            uint32_t h = hash_slot(bits);
-            while (atomicCAS(&s_hkey[h], kHashFree, bits) != kHashFree) h = (h + 1u) & (kHashSlots - 1u);
-            s_hpos[h] = st->sorted_pos[t];
+            const uint32_t key = __float_as_uint(canonical(st->codebook[t]));
+            uint32_t h = hash_slot(key);
+            while (atomicCAS(&s_hkey[h], kHashFree, key) != kHashFree) h = (h + 1u) & (kHashSlots - 1u);
+            s_hpos[h] = t;
         }
+        __syncthreads();
     }
-    __syncthreads();
-    c.wmin = st->wmin;
-    c.step = st->step;
     c.top = (float)(c.K - 1);
     c.val = s_val;
     c.hkey = s_hkey;
     c.hpos = s_hpos;
-    const float* row = W + r * row_len;
-    uint8_t* crow = codes ? codes + r * row_len : nullptr;
-    float* qrow = Wq ? Wq + r * row_len : nullptr;
-    const int64_t n = min(row_len, total - r * row_len);  // the last row of a flat array may be short
     bool missing = false;
-    // the next round's four elements are requested before this round's are coded
-    float4 ahead = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (vec_ok && 4 * (int64_t)t + 4 <= n) ahead = *reinterpret_cast<const float4*>(row + 4 * (int64_t)t);
-    for (int64_t j0 = 0; j0 < n; j0 += 1024) {
-        const int64_t j = j0 + 4 * (int64_t)t;
-        uint32_t code[4] = {0, 0, 0, 0};
-        const int valid = (int)max((int64_t)0, min((int64_t)4, n - j));
-        const float4 w = ahead;
-        if (vec_ok && j + 1024 + 4 <= n) ahead = *reinterpret_cast<const float4*>(row + j + 1024);
-        if (valid == 4 && vec_ok) {
-            code[0] = code_of<kQuant>(w.x, c, missing);
-            code[1] = code_of<kQuant>(w.y, c, missing);
-            code[2] = code_of<kQuant>(w.z, c, missing);
-            code[3] = code_of<kQuant>(w.w, c, missing);
-            if (crow) *reinterpret_cast<uint32_t*>(crow + j) = code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24);
-            if (kQuant && qrow)
-                *reinterpret_cast<float4*>(qrow + j) = make_float4(s_val[code[0]], s_val[code[1]], s_val[code[2]], s_val[code[3]]);
-        } else {
+    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
+        const float* row = W + r * row_len;
+        uint8_t* crow = codes ? codes + r * row_len : nullptr;
+        float* qrow = Wq ? Wq + r * row_len : nullptr;
+        const int64_t n = min(row_len, total - r * row_len);  // the last row of a flat array may be short
+        // the next round's four elements are requested before this round's are coded
+        float4 ahead = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (vec_ok && 4 * (int64_t)t + 4 <= n) ahead = *reinterpret_cast<const float4*>(row + 4 * (int64_t)t);
+        for (int64_t j0 = 0; j0 < n; j0 += 1024) {
+            const int64_t j = j0 + 4 * (int64_t)t;
+            uint32_t code[4] = {0, 0, 0, 0};
+            const int valid = (int)max((int64_t)0, min((int64_t)4, n - j));
+            const float4 w = ahead;
+            if (vec_ok && j + 1024 + 4 <= n) ahead = *reinterpret_cast<const float4*>(row + j + 1024);
+            if (valid == 4 && vec_ok) {
+                code[0] = code_of<kQuant>(w.x, c, missing);
+                code[1] = code_of<kQuant>(w.y, c, missing);
+                code[2] = code_of<kQuant>(w.z, c, missing);
+                code[3] = code_of<kQuant>(w.w, c, missing);
+                if (crow) *reinterpret_cast<uint32_t*>(crow + j) = code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24);
+                if (kQuant && qrow)
+                    *reinterpret_cast<float4*>(qrow + j) = make_float4(s_val[code[0]], s_val[code[1]], s_val[code[2]], s_val[code[3]]);
+            } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (e < valid) {
-                    code[e] = code_of<kQuant>(row[j + e], c, missing);
-                    if (crow) crow[j + e] = (uint8_t)code[e];
-                    if (kQuant && qrow) qrow[j + e] = s_val[code[e]];
+                for (int e = 0; e < 4; ++e) {
+                    if (e < valid) {
+                        code[e] = code_of<kQuant>(row[j + e], c, missing);
+                        if (crow) crow[j + e] = (uint8_t)code[e];
+                        if (kQuant && qrow) qrow[j + e] = s_val[code[e]];
+                    }
                 }
             }
-        }
-        // histogram: everything that equals the first active lane's first code is counted with one add
-        const uint64_t act = __ballot(valid > 0);
-        if (act) {
-            const uint32_t lead = (uint32_t)__builtin_amdgcn_readfirstlane((int)code[0]);
-            uint32_t same = 0;
+            if (!cnt) continue;  // uniform
+            // histogram: everything that equals the first active lane's first code is counted with one add
+            const uint64_t act = __ballot(valid > 0);
+            if (act) {
+                const uint32_t lead = (uint32_t)__builtin_amdgcn_readfirstlane((int)code[0]);
+                uint32_t same = 0;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const bool in = e < valid;
-                same += (uint32_t)__popcll(__ballot(in && code[e] == lead));
-                if (in && code[e] != lead) atomicAdd(&s_hist[code[e]], 1u);
+                for (int e = 0; e < 4; ++e) {
+                    const bool in = e < valid;
+                    same += (uint32_t)__popcll(__ballot(in && code[e] == lead));
+                    if (in && code[e] != lead) atomicAdd(&s_hist[code[e]], 1u);
+                }
+                if ((uint32_t)__builtin_ctzll(act) == (t & 63u)) atomicAdd(&s_hist[lead], same);
             }
-            if ((uint32_t)__builtin_ctzll(act) == (t & 63u)) atomicAdd(&s_hist[lead], same);
+        }
+        if (cnt) {
+            __syncthreads();
+            cnt[r * kCodes + t] = s_hist[t];
+            s_hist[t] = 0;
+            __syncthreads();
         }
     }
     if (__syncthreads_or(missing) && t == 0) atomicOr(&st->flags, kFlagMissing);
-    cnt[r * kCodes + t] = s_hist[t];
 }
 
-// Global histogram = column sums of the per-row histograms.
-__global__ __launch_bounds__(256) void hist_kernel(const uint32_t* __restrict__ cnt, int64_t m, int64_t rows_per_block,
-                                                   FrontState* __restrict__ st) {
+// Global histogram = column sums of the per-row histograms, in at most kHistParts partial sums (one per workgroup of 1024
+// threads: four rows at a time) that the next kernel adds up.
+constexpr int kHistParts = 64;
+__global__ __launch_bounds__(1024) void hist_kernel(const uint32_t* __restrict__ cnt, int64_t m, int64_t rows_per_block,
+                                                    unsigned long long* __restrict__ part) {
+    __shared__ unsigned long long s_sum[4][kCodes];
+    const uint32_t pos = threadIdx.x & 255u, sub = threadIdx.x >> 8;
     const int64_t r0 = (int64_t)blockIdx.x * rows_per_block, r1 = min(m, r0 + rows_per_block);
     unsigned long long s = 0;
-    for (int64_t r = r0; r < r1; ++r) s += cnt[r * kCodes + threadIdx.x];
-    if (s) atomicAdd(&st->hist[threadIdx.x], s);
-}
-
-// Frequency-major order: higher count first, equal counts in codebook order; values that never
-// occur are left out (Section III-A, step 1).  One block of 256 threads, K <= 256: each thread
-// finds its own position by counting who comes before it.
-__global__ __launch_bounds__(256) void rank_kernel(FrontState* __restrict__ st) {
-    __shared__ unsigned long long s_h[kCodes];
-    const uint32_t t = threadIdx.x, K = st->K;
-    const unsigned long long c = t < K ? st->hist[t] : 0ull;
-    s_h[t] = c;
+    int64_t r = r0 + sub;
+    for (; r + 28 < r1; r += 32) {
+        uint32_t c[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) c[k] = cnt[(r + 4 * k) * kCodes + pos];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += c[k];
+    }
+    for (; r < r1; r += 4) s += cnt[r * kCodes + pos];
+    s_sum[sub][pos] = s;
     __syncthreads();
-    uint32_t before = 0, occurring = 0;
-    for (uint32_t j = 0; j < K; ++j) {
-        const unsigned long long cj = s_h[j];
-        occurring += cj > 0;
-        before += (cj > c) || (cj == c && j < t);
-    }
-    st->rank_of[t] = c > 0 ? before : 0u;
-    if (c > 0) {
-        st->pos_of[before] = t;
-        st->omega[before] = canonical(st->codebook[t]);
-        st->count[before] = c;
-    }
-    if (t == 0) st->Kp = occurring;
+    if (sub == 0) part[(int64_t)blockIdx.x * kCodes + pos] = s_sum[0][pos] + s_sum[1][pos] + s_sum[2][pos] + s_sum[3][pos];
 }
 
 // ------------------------------------------------------------------------------------------------
-// layout: per row, the number of indexed elements, of groups and of non-empty groups.  One wave per row.
+// layout: per row, the number of indexed elements, of groups and of non-empty groups.  One wave per row, sixteen rows per
+// workgroup; every workgroup first ranks the values for itself (one launch less than a kernel of its own).
+//
+// Frequency-major order: higher count first, equal counts in codebook order; values that never occur are left out
+// (Section III-A, step 1).  Each thread finds its own value's position by counting who comes before it.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void row_layout_kernel(const uint32_t* __restrict__ cnt, int64_t m, int cser,
-                                                         const FrontState* __restrict__ st, uint32_t* __restrict__ rowG,
-                                                         uint32_t* __restrict__ rowN, uint32_t* __restrict__ rowP) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+__global__ __launch_bounds__(1024) void row_layout_kernel(const uint32_t* __restrict__ cnt, const unsigned long long* __restrict__ part,
+                                                          int nparts, int64_t m, int cser, FrontState* __restrict__ st,
+                                                          uint2* __restrict__ rowGN) {
+    __shared__ unsigned long long s_sum[4][kCodes];
+    __shared__ unsigned long long s_h[kCodes];
+    __shared__ uint32_t s_rank[kCodes];
+    const uint32_t t = threadIdx.x, lane = t & 63u, pos = t & 255u, sub = t >> 8, K = st->K;
+    {
+        unsigned long long s = 0;
+        for (int i = (int)sub; i < nparts; i += 4) s += part[(int64_t)i * kCodes + pos];
+        s_sum[sub][pos] = s;
+    }
+    __syncthreads();
+    if (sub == 0) s_h[pos] = pos < K ? s_sum[0][pos] + s_sum[1][pos] + s_sum[2][pos] + s_sum[3][pos] : 0ull;
+    __syncthreads();
+    // the four threads of a position compare it with a quarter of the others each
+    {
+        const unsigned long long c = s_h[pos];
+        uint32_t before = 0;
+        const uint32_t j0 = sub * 64u, j1 = min(K, j0 + 64u);
+        for (uint32_t j = j0; j < j1; ++j) {
+            const unsigned long long cj = s_h[j];
+            before += (cj > c) || (cj == c && j < pos);
+        }
+        s_sum[sub][pos] = before;
+    }
+    const int occurring = __syncthreads_count(sub == 0 && s_h[pos] > 0);
+    if (sub == 0) {
+        const unsigned long long c = s_h[pos];
+        const uint32_t before = (uint32_t)(s_sum[0][pos] + s_sum[1][pos] + s_sum[2][pos] + s_sum[3][pos]);
+        s_rank[pos] = c > 0 ? before : 0u;
+        if (blockIdx.x == 0) {
+            st->rank_of[pos] = c > 0 ? before : 0u;
+            if (c > 0) {
+                st->pos_of[before] = pos;
+                st->omega[before] = canonical(st->codebook[pos]);
+                st->count[before] = c;
+            }
+            if (t == 0) st->Kp = (uint32_t)occurring;
+        }
+    }
+    __syncthreads();
+    const int64_t r = (int64_t)blockIdx.x * 16 + (t >> 6);
     if (r >= m) return;
     uint32_t present = 0, topk = 0, nn = 0;
 #pragma unroll
     for (int i = 0; i < kCodes / kWave; ++i) {
-        const uint32_t pos = lane + 64u * i;
-        const uint32_t c = cnt[r * kCodes + pos];
-        const uint32_t k = st->rank_of[pos];
+        const uint32_t p = lane + 64u * i;
+        const uint32_t c = cnt[r * kCodes + p];
+        const uint32_t k = s_rank[p];
         if (c > 0 && k >= 1) {
             ++present;
             topk = max(topk, k);
@@ -349,33 +420,36 @@ __global__ __launch_bounds__(256) void row_layout_kernel(const uint32_t* __restr
         nn += __shfl_xor(nn, off, kWave);
         topk = max(topk, (uint32_t)__shfl_xor((int)topk, off, kWave));
     }
-    if (lane == 0) {
-        rowG[r] = cser ? present : topk;  // CER keeps the empty groups below the row's highest rank
-        rowN[r] = nn;
-        rowP[r] = present;
-    }
+    // groups (CER keeps the empty groups below the row's highest rank) | non-empty groups << 16, indexed elements
+    if (lane == 0) rowGN[r] = make_uint2((cser ? present : topk) | (present << 16), nn);
 }
 
-// Exclusive prefix sums of rowG and rowN over the rows (m + 1 entries each), the number of
-// non-empty groups and the largest group count of a row.  One block.
-__global__ __launch_bounds__(1024) void scan_rows_kernel(const uint32_t* __restrict__ rowG, const uint32_t* __restrict__ rowN,
-                                                         const uint32_t* __restrict__ rowP, int64_t m,
-                                                         uint32_t* __restrict__ rowPtr, uint32_t* __restrict__ rowOff,
-                                                         FrontState* __restrict__ st) {
+// Exclusive prefix sums of the rows' groups and indexed elements (m + 1 entries {groups, elements}), the number of
+// non-empty groups and the largest group count of a row.  One workgroup, kScanRows consecutive rows per thread and round
+// (a 4096-row matrix is one round: 12.6 -> 5 us against one row per thread).  The result goes to the host from here.
+constexpr int kScanRows = 4;
+__global__ __launch_bounds__(1024) void scan_rows_kernel(const uint2* __restrict__ rowGN, int64_t m, uint2* __restrict__ rowStart,
+                                                         FrontState* __restrict__ st, FrontResult* __restrict__ out) {
     __shared__ unsigned long long s_g[16], s_n[16], s_p[16];
     __shared__ uint32_t s_mx[16], s_ml[16];
-    __shared__ unsigned long long s_carry[2];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
-    if (t == 0) s_carry[0] = s_carry[1] = 0;
-    unsigned long long my_p = 0;
+    unsigned long long carry_g = 0, carry_n = 0, my_p = 0;
     uint32_t my_mx = 0, my_ml = 0;
-    __syncthreads();
-    for (int64_t base = 0; base < m; base += 1024) {
-        const int64_t r = base + t;
-        const unsigned long long g = r < m ? rowG[r] : 0u, nn = r < m ? rowN[r] : 0u;
-        my_p += r < m ? rowP[r] : 0u;
-        my_mx = max(my_mx, (uint32_t)g);
-        my_ml = max(my_ml, (uint32_t)nn);
+    for (int64_t base = 0; base < m; base += 1024 * kScanRows) {
+        const int64_t r0 = base + (int64_t)t * kScanRows;
+        uint2 v[kScanRows];
+        unsigned long long g = 0, nn = 0;
+#pragma unroll
+        for (int k = 0; k < kScanRows; ++k) v[k] = r0 + k < m ? rowGN[r0 + k] : make_uint2(0u, 0u);
+#pragma unroll
+        for (int k = 0; k < kScanRows; ++k) {
+            my_p += v[k].x >> 16;
+            v[k].x &= 0xFFFFu;
+            my_mx = max(my_mx, v[k].x);
+            my_ml = max(my_ml, v[k].y);
+            g += v[k].x;
+            nn += v[k].y;
+        }
         unsigned long long ig = g, in_ = nn;  // inclusive scans inside the wave
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1) {
@@ -390,19 +464,22 @@ __global__ __launch_bounds__(1024) void scan_rows_kernel(const uint32_t* __restr
             s_n[wave] = in_;
         }
         __syncthreads();
-        unsigned long long og = s_carry[0], on = s_carry[1];
-        for (uint32_t w = 0; w < wave; ++w) {
-            og += s_g[w];
-            on += s_n[w];
+        unsigned long long og = carry_g, on = carry_n;
+        for (uint32_t w = 0; w < 16; ++w) {
+            if (w < wave) {
+                og += s_g[w];
+                on += s_n[w];
+            }
+            carry_g += s_g[w];
+            carry_n += s_n[w];
         }
-        if (r < m) {
-            rowPtr[r] = (uint32_t)(og + ig - g);
-            rowOff[r] = (uint32_t)(on + in_ - nn);
-        }
-        __syncthreads();
-        if (t == 1023) {
-            s_carry[0] = og + ig;
-            s_carry[1] = on + in_;
+        og += ig - g;
+        on += in_ - nn;
+#pragma unroll
+        for (int k = 0; k < kScanRows; ++k) {
+            if (r0 + k < m) rowStart[r0 + k] = make_uint2((uint32_t)og, (uint32_t)on);
+            og += v[k].x;
+            on += v[k].y;
         }
         __syncthreads();
     }
@@ -417,6 +494,12 @@ __global__ __launch_bounds__(1024) void scan_rows_kernel(const uint32_t* __restr
         s_mx[wave] = my_mx;
         s_ml[wave] = my_ml;
     }
+    const uint32_t Kp = st->Kp, K = st->K;
+    if (t < Kp) {
+        out->count[t] = st->count[t];
+        out->omega[t] = st->omega[t];
+    }
+    if (t < K && t < (uint32_t)kCodes) out->codebook[t] = st->codebook[t];
     __syncthreads();
     if (t == 0) {
         unsigned long long p = 0;
@@ -426,18 +509,21 @@ __global__ __launch_bounds__(1024) void scan_rows_kernel(const uint32_t* __restr
             mx = max(mx, s_mx[w]);
             ml = max(ml, s_ml[w]);
         }
-        st->max_row_nnz = ml;
-        const unsigned long long G = s_carry[0], nnz = s_carry[1];
-        st->G = G;
-        st->nnz = nnz;
-        st->nonempty = p;
-        st->max_row_groups = mx;
-        rowPtr[m] = (uint32_t)G;
-        rowOff[m] = (uint32_t)nnz;
+        rowStart[m] = make_uint2((uint32_t)carry_g, (uint32_t)carry_n);
         // the product kernels address colI and OmegaPtr with 32-bit offsets and read ahead of a row's end
         const unsigned long long limit = 0xFFFFFFFFull - 65536;
-        if (G > limit || nnz > limit) atomicOr(&st->flags, kFlagTooLarge);
+        out->flags = st->flags | (carry_g > limit || carry_n > limit ? kFlagTooLarge : 0u);
+        out->K = K;
+        out->Kp = Kp;
+        out->max_row_groups = mx;
+        out->max_row_nnz = ml;
+        out->nnz = carry_n;
+        out->G = carry_g;
+        out->nonempty = p;
     }
+    __threadfence_system();
+    __syncthreads();
+    if (t == 0) __hip_atomic_store(&out->ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -477,17 +563,37 @@ __device__ __forceinline__ void scatter64(uint32_t k, int64_t j, uint32_t nbits,
 
 constexpr uint32_t kEmitStage = 1024;  // staged entries per wave
 
+// Where the parts of the handle's allocation start, and the gaps between them (cleared: the product reads ahead).
+struct EmitTarget {
+    unsigned char* base;
+    size_t off_optr, off_rptr, off_ri, off_oi, off_om, off_tab;
+    int32_t tab_shift;  // rank table: 1 << tab_shift words per row; 0: none
+    int32_t ngaps;
+    size_t gap_begin[8], gap_end[8];
+};
+
+// Four rows per workgroup; the last workgroup writes Omega and clears the gaps.
 template <typename ColT, typename OiT>
 __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ codes, const uint32_t* __restrict__ cnt,
-                                                   const uint32_t* __restrict__ rowPtrTmp, const uint32_t* __restrict__ rowOffTmp,
-                                                   const FrontState* __restrict__ st, int64_t m, int64_t n, int cser,
-                                                   int sparse, ColT* __restrict__ colI, uint32_t* __restrict__ omegaPtr,
-                                                   uint32_t* __restrict__ rowPtr, uint2* __restrict__ rowInfo,
-                                                   OiT* __restrict__ omegaI) {
+                                                   const uint2* __restrict__ rowStart, const FrontState* __restrict__ st,
+                                                   int64_t m, int64_t n, int cser, int sparse, EmitTarget to) {
     __shared__ uint32_t s_rank[kCodes];
     __shared__ uint32_t s_fill[4][kCodes];  // next free colI slot of each rank's bucket
     __shared__ uint32_t s_stage[4][kEmitStage];  // (column << 8) | rank of the columns waiting for the scatter
     __shared__ unsigned long long s_marks[4][kCodes];  // per rank: the lanes of the current batch that hold it
+    if (blockIdx.x == gridDim.x - 1) {
+        const uint32_t t = threadIdx.x;
+        if (t < st->Kp) reinterpret_cast<float*>(to.base + to.off_om)[t] = st->omega[t];
+        for (int g = 0; g < to.ngaps; ++g)
+            for (size_t o = to.gap_begin[g] + t; o < to.gap_end[g]; o += 256) to.base[o] = 0;
+        return;
+    }
+    ColT* colI = reinterpret_cast<ColT*>(to.base);
+    uint32_t* omegaPtr = reinterpret_cast<uint32_t*>(to.base + to.off_optr);
+    uint32_t* rowPtr = reinterpret_cast<uint32_t*>(to.base + to.off_rptr);
+    uint2* rowInfo = reinterpret_cast<uint2*>(to.base + to.off_ri);
+    OiT* omegaI = reinterpret_cast<OiT*>(to.base + to.off_oi);
+    uint32_t* tab = reinterpret_cast<uint32_t*>(to.base + to.off_tab);
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     s_rank[threadIdx.x] = st->rank_of[threadIdx.x];
 #pragma unroll
@@ -498,18 +604,20 @@ __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ c
     uint32_t* fill = s_fill[wave];
     unsigned long long* marks = s_marks[wave];
     const uint32_t Kp = st->Kp;
-    const uint32_t g0 = rowPtrTmp[r], off0 = rowOffTmp[r];
-    const uint32_t groups = rowPtrTmp[r + 1] - g0;
+    const uint2 here = rowStart[r], next = rowStart[r + 1];
+    const uint32_t g0 = here.x, off0 = here.y;
+    const uint32_t groups = next.x - g0;
     if (lane == 0) {
         rowPtr[r] = g0;
-        rowInfo[r] = make_uint2(g0, off0);
+        rowInfo[r] = here;
         if (r == 0) omegaPtr[0] = 0;
         if (r == m - 1) {
-            rowPtr[m] = rowPtrTmp[m];
-            rowInfo[m] = make_uint2(rowPtrTmp[m], rowOffTmp[m]);
+            rowPtr[m] = next.x;
+            rowInfo[m] = next;
         }
     }
-    // bucket sizes by rank -> bucket starts (exclusive scan over ranks 1, 2, ...) and the pointers
+    // bucket sizes by rank -> bucket starts (exclusive scan over ranks 1, 2, ...), the pointers and the row's record of the
+    // rank table
     uint32_t carry = 0, gcarry = 0;
 #pragma unroll
     for (int i = 0; i < kCodes / kWave; ++i) {
@@ -523,6 +631,7 @@ __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ c
         }
         const uint32_t end = off0 + carry + inc;
         fill[k] = end - c;
+        if (to.tab_shift && (k >> to.tab_shift) == 0) tab[((size_t)r << to.tab_shift) + k] = end;
         const uint64_t pres = __ballot(c > 0);
         if (cser) {
             if (c > 0) {
@@ -801,47 +910,96 @@ struct DeviceBuf {
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Runs range/points (bits > 0) or takes the caller's codebook, then codes + per-row histograms over
-// `rows` rows of row_len elements (the last one possibly shorter).  Returns after the stream has drained.
+// Enqueues range (bits > 0) or the caller's codebook, then codes + per-row histograms (cnt != nullptr) over `rows` rows of
+// row_len elements (the last one possibly shorter).  `part`: kRangeParts float4.
 int run_codes(const float* W, int64_t total, int64_t rows, int64_t row_len, const float* codebook, int32_t K, int32_t bits,
-              hipStream_t s, FrontState* st_dev, uint8_t* codes, uint32_t* cnt, float* Wq) {
-    FrontState init;
-    std::memset(&init, 0, sizeof init);
+              hipStream_t s, FrontState* st_dev, float4* part, uint8_t* codes, uint32_t* cnt, float* Wq) {
     const int vec_ok = (row_len % 4 == 0 && aligned16(W) && (!Wq || aligned16(Wq)) &&
                         (!codes || (reinterpret_cast<uintptr_t>(codes) & 3u) == 0)) ? 1 : 0;
-    DeviceBuf part;
+    // workgroups walk several rows where that still leaves eight of them per compute unit: their prologue is shared
+    const unsigned blocks = (unsigned)std::min<int64_t>(rows, 2048);
     if (bits > 0) {
-        const int nparts = (int)std::min<int64_t>(2048, (total + 1023) / 1024);
-        HIP_TRY(part.alloc((size_t)nparts * 12, s));
-        float* pmin = part.as<float>();
-        float* pmax = pmin + nparts;
-        uint32_t* pbad = reinterpret_cast<uint32_t*>(pmax + nparts);
-        HIP_TRY(hipMemcpyAsync(st_dev, &init, sizeof init, hipMemcpyHostToDevice, s));
-        range_kernel<<<nparts, 256, 0, s>>>(W, total, pmin, pmax, pbad);
-        points_kernel<<<1, 256, 0, s>>>(pmin, pmax, pbad, nparts, bits, st_dev);
-        codes_kernel<true><<<(unsigned)rows, 256, 0, s>>>(W, total, row_len, st_dev, codes, cnt, Wq, vec_ok);
+        const int nparts = (int)std::min<int64_t>(kRangeParts, (total + 1023) / 1024);
+        HIP_TRY(cer::launch_kernel(range_kernel, dim3(nparts), dim3(256), 0, s, W, total, part, st_dev));
+        HIP_TRY(cer::launch_kernel(codes_kernel<true>, dim3(blocks), dim3(256), 0, s, W, total, rows, row_len, part, nparts, bits,
+                                   st_dev, codes, cnt, Wq, vec_ok));
     } else {
-        // codebook sorted by value for the look-up; duplicates and non-finite values are refused
-        std::vector<uint32_t> order((size_t)K);
+        // duplicates and non-finite values are refused
+        CodebookArg cb;
+        std::memset(&cb, 0, sizeof cb);
         for (int32_t k = 0; k < K; ++k) {
             if (!std::isfinite(codebook[k])) return CER_E_BAD_CODEBOOK;
-            order[(size_t)k] = (uint32_t)k;
-            init.codebook[k] = codebook[k] == 0.0f ? 0.0f : codebook[k];
+            cb.v[k] = codebook[k] == 0.0f ? 0.0f : codebook[k];
         }
-        std::sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return init.codebook[a] < init.codebook[b]; });
-        for (int32_t k = 0; k < K; ++k) {
-            init.sorted_val[k] = init.codebook[order[(size_t)k]];
-            init.sorted_pos[k] = order[(size_t)k];
-            if (k > 0 && init.sorted_val[k] == init.sorted_val[k - 1]) return CER_E_BAD_CODEBOOK;
-        }
-        init.K = (uint32_t)K;
-        HIP_TRY(hipMemcpyAsync(st_dev, &init, sizeof init, hipMemcpyHostToDevice, s));
-        codes_kernel<false><<<(unsigned)rows, 256, 0, s>>>(W, total, row_len, st_dev, codes, cnt, nullptr, vec_ok);
+        float sorted[kCodes];
+        std::copy(cb.v, cb.v + K, sorted);
+        std::sort(sorted, sorted + K);
+        if (std::adjacent_find(sorted, sorted + K) != sorted + K) return CER_E_BAD_CODEBOOK;
+        cb.K = (uint32_t)K;
+        HIP_TRY(cer::launch_kernel(codebook_kernel, dim3(1), dim3(256), 0, s, cb, st_dev));
+        HIP_TRY(cer::launch_kernel(codes_kernel<false>, dim3(blocks), dim3(256), 0, s, W, total, rows, row_len, part, 0, 0, st_dev,
+                                   codes, cnt, (float*)nullptr, vec_ok));
     }
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipStreamSynchronize(s));  // `init` lives on this frame
     return CER_OK;
 }
+
+// Pinned host memory for FrontResult: a few blocks are kept for later calls.
+struct Mailboxes {
+    std::mutex mu;
+    FrontResult* spare[8] = {};
+    int count = 0;
+};
+Mailboxes g_mailboxes;
+
+struct Mailbox {
+    FrontResult* p = nullptr;
+    bool busy = false;  // a kernel that writes to it may still be running
+    ~Mailbox() {
+        if (!p || busy) return;
+        {
+            std::lock_guard<std::mutex> lock(g_mailboxes.mu);
+            if (g_mailboxes.count < 8) {
+                g_mailboxes.spare[g_mailboxes.count++] = p;
+                return;
+            }
+        }
+        (void)hipHostFree(p);
+    }
+    hipError_t get() {
+        {
+            std::lock_guard<std::mutex> lock(g_mailboxes.mu);
+            if (g_mailboxes.count > 0) p = g_mailboxes.spare[--g_mailboxes.count];
+        }
+        if (!p) {
+            void* q = nullptr;
+            const hipError_t e = hipHostMalloc(&q, sizeof(FrontResult), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent);
+            if (e != hipSuccess) return e;
+            p = static_cast<FrontResult*>(q);
+        }
+        __atomic_store_n(&p->ready, 0u, __ATOMIC_RELEASE);
+        return hipSuccess;
+    }
+    // Returns when the result is there.  A copy and a synchronisation of the stream take 30 us more than looking at the
+    // word that the kernel writes last; the stream is asked now and then, so that a failed launch ends the wait.
+    hipError_t wait(hipStream_t s) {
+        for (uint32_t spins = 1;; ++spins) {
+            if (__atomic_load_n(&p->ready, __ATOMIC_ACQUIRE)) break;
+            if (spins % 8192u == 0) {
+                hipError_t e = spins > (1u << 20) ? hipStreamSynchronize(s) : hipStreamQuery(s);
+                if (e == hipErrorNotReady) {
+                    (void)hipGetLastError();
+                    continue;
+                }
+                if (e == hipSuccess && !__atomic_load_n(&p->ready, __ATOMIC_ACQUIRE)) e = hipErrorLaunchFailure;
+                if (e != hipSuccess) return e;
+                break;
+            }
+            __builtin_ia32_pause();
+        }
+        busy = false;
+        return hipSuccess;
+    }
+};
 
 int flags_to_error(uint32_t flags) {
     if (flags & kFlagNonFinite) return CER_E_INVALID;
@@ -852,14 +1010,11 @@ int flags_to_error(uint32_t flags) {
 }
 
 template <typename ColT>
-void launch_emit(unsigned blocks, hipStream_t s, const uint8_t* codes, const uint32_t* cnt, const uint32_t* rowPtrTmp,
-                 const uint32_t* rowOffTmp, const FrontState* st, int64_t m, int64_t n, int cser, int sparse,
-                 unsigned char* b, const cer::DeviceLayout& l) {
+hipError_t launch_emit(hipStream_t s, const uint8_t* codes, const uint32_t* cnt, const uint2* rowStart, const FrontState* st,
+                       int64_t m, int64_t n, int cser, int sparse, const EmitTarget& to) {
     // rank < K <= 256, so OmegaI is always one byte wide here
-    emit_kernel<ColT, uint8_t><<<blocks, 256, 0, s>>>(
-        codes, cnt, rowPtrTmp, rowOffTmp, st, m, n, cser, sparse, reinterpret_cast<ColT*>(b + l.off_colI),
-        reinterpret_cast<uint32_t*>(b + l.off_optr), reinterpret_cast<uint32_t*>(b + l.off_rptr),
-        reinterpret_cast<uint2*>(b + l.off_ri), reinterpret_cast<uint8_t*>(b + l.off_oi));
+    return cer::launch_kernel(emit_kernel<ColT, uint8_t>, dim3((unsigned)((m + 3) / 4 + 1)), dim3(256), 0, s, codes, cnt, rowStart,
+                              st, m, n, cser, sparse, to);
 }
 
 }  // namespace
@@ -908,13 +1063,14 @@ int quantize_device(const float* W, int64_t count, int32_t bits, uint8_t* codes,
                     int32_t* K_out, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t row_len = 4096, rows = (count + row_len - 1) / row_len;
-    DeviceBuf st, cnt;
-    HIP_TRY(st.alloc(sizeof(FrontState), s));
-    HIP_TRY(cnt.alloc((size_t)rows * kCodes * 4, s));
-    int rc = run_codes(W, count, rows, row_len, nullptr, 0, bits, s, st.as<FrontState>(), codes, cnt.as<uint32_t>(), Wq);
+    DeviceBuf tmp;
+    HIP_TRY(tmp.alloc(kRangeParts * sizeof(float4) + sizeof(FrontState), s));
+    float4* part = tmp.as<float4>();
+    FrontState* st = reinterpret_cast<FrontState*>(part + kRangeParts);
+    int rc = run_codes(W, count, rows, row_len, nullptr, 0, bits, s, st, part, codes, nullptr, Wq);
     if (rc != CER_OK) return rc;
     FrontState h;
-    HIP_TRY(hipMemcpyAsync(&h, st.p, sizeof h, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(&h, st, sizeof h, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     rc = flags_to_error(h.flags);
     if (rc != CER_OK) return rc;
@@ -930,34 +1086,35 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
 
-    // one stream-ordered temporary: [state][codes: N bytes][per-row histograms][rowG, rowN, rowP [m], rowPtrTmp, rowOffTmp [m + 1]]
+    // one stream-ordered temporary: [state][codes: N bytes][per-row histograms][{groups, elements} per row: m][their prefix
+    // sums: m + 1][partial histograms][partial ranges]
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t off_codes = up(sizeof(FrontState)), off_cnt = off_codes + up((size_t)N);
-    const size_t off_rows = off_cnt + up((size_t)m * kCodes * 4), tmp_bytes = off_rows + up((size_t)(5 * m + 2) * 4);
+    const size_t off_gn = off_cnt + up((size_t)m * kCodes * 4), off_start = off_gn + up((size_t)m * 8);
+    const size_t off_hist = off_start + up((size_t)(m + 1) * 8), off_part = off_hist + (size_t)kHistParts * kCodes * 8;
+    Mailbox box;
+    HIP_TRY(box.get());
     DeviceBuf tmp;
-    HIP_TRY(tmp.alloc(tmp_bytes, s));
+    HIP_TRY(tmp.alloc(off_part + kRangeParts * sizeof(float4), s));
     unsigned char* tp = tmp.as<unsigned char>();
     FrontState* sd = reinterpret_cast<FrontState*>(tp);
     uint8_t* codes_d = tp + off_codes;
     uint32_t* cnt_d = reinterpret_cast<uint32_t*>(tp + off_cnt);
-    uint32_t* rowG = reinterpret_cast<uint32_t*>(tp + off_rows);
-    uint32_t* rowN = rowG + m;
-    uint32_t* rowP = rowN + m;
-    uint32_t* rowPtrTmp = rowP + m;
-    uint32_t* rowOffTmp = rowPtrTmp + m + 1;
+    uint2* rowGN = reinterpret_cast<uint2*>(tp + off_gn);
+    uint2* rowStart = reinterpret_cast<uint2*>(tp + off_start);
+    auto* hist = reinterpret_cast<unsigned long long*>(tp + off_hist);
 
-    int rc = run_codes(W, N, m, n, codebook, K, bits, s, sd, codes_d, cnt_d, nullptr);
+    int rc = run_codes(W, N, m, n, codebook, K, bits, s, sd, reinterpret_cast<float4*>(tp + off_part), codes_d, cnt_d, nullptr);
     if (rc != CER_OK) return rc;
-    const unsigned row_blocks = (unsigned)((m + 3) / 4);
-    const int64_t rows_per_block = 16;
-    hist_kernel<<<(unsigned)((m + rows_per_block - 1) / rows_per_block), 256, 0, s>>>(cnt_d, m, rows_per_block, sd);
-    rank_kernel<<<1, 256, 0, s>>>(sd);
-    row_layout_kernel<<<row_blocks, 256, 0, s>>>(cnt_d, m, cser ? 1 : 0, sd, rowG, rowN, rowP);
-    scan_rows_kernel<<<1, 1024, 0, s>>>(rowG, rowN, rowP, m, rowPtrTmp, rowOffTmp, sd);
-    HIP_TRY(hipGetLastError());
-    FrontState h;
-    HIP_TRY(hipMemcpyAsync(&h, sd, sizeof h, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    const int64_t rows_per_part = std::max<int64_t>(8, (m + kHistParts - 1) / kHistParts);
+    const int hist_parts = (int)((m + rows_per_part - 1) / rows_per_part);
+    HIP_TRY(launch_kernel(hist_kernel, dim3(hist_parts), dim3(1024), 0, s, cnt_d, m, rows_per_part, hist));
+    HIP_TRY(launch_kernel(row_layout_kernel, dim3((unsigned)((m + 15) / 16)), dim3(1024), 0, s, cnt_d, hist, hist_parts, m,
+                          cser ? 1 : 0, sd, rowGN));
+    box.busy = true;
+    HIP_TRY(launch_kernel(scan_rows_kernel, dim3(1), dim3(1024), 0, s, rowGN, m, rowStart, sd, box.p));
+    HIP_TRY(box.wait(s));
+    const FrontResult& h = *box.p;
     rc = flags_to_error(h.flags);
     if (rc != CER_OK) return rc;
     if (K_out) *K_out = (int32_t)h.K;
@@ -990,57 +1147,57 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     const size_t colI_bytes = (size_t)A->nnz * (size_t)(A->colI.bits / 8);
     const size_t oi_bytes = cser ? (size_t)A->G * (size_t)(A->omegaI.bits / 8) : 0;
     const DeviceLayout l = DeviceLayout::make(colI_bytes, A->G, m, oi_bytes, A->K);
+    std::unique_ptr<cer_matrix, void (*)(cer_handle_t*)> hnd(new cer_matrix(), cer_free);
+    hnd->host = std::move(A);
+    if (s) hnd->off_null_stream.store(true, std::memory_order_relaxed);
     void* base = nullptr;
-    HIP_TRY(hipMalloc(&base, l.total));
-    auto* b = static_cast<unsigned char*>(base);
-    auto fail = [&](hipError_t e) {
-        (void)hipStreamSynchronize(s);
-        (void)hipFree(base);
-        return record_hip_error((int)e);
+    HIP_TRY((hipError_t)handle_alloc(&base, l.total, s));
+    bind_device(hnd.get(), dev, base, l);
+
+    EmitTarget to;
+    std::memset(&to, 0, sizeof to);
+    to.base = static_cast<unsigned char*>(base);
+    to.off_optr = l.off_optr;
+    to.off_rptr = l.off_rptr;
+    to.off_ri = l.off_ri;
+    to.off_oi = l.off_oi;
+    to.off_om = l.off_om;
+    to.off_tab = l.off_tab;
+    to.tab_shift = l.tab_shift;
+    // the read-ahead padding and the gaps are cleared; the arrays themselves are written completely
+    auto gap = [&](size_t begin, size_t end) {
+        to.gap_begin[to.ngaps] = begin;
+        to.gap_end[to.ngaps++] = end;
     };
-    // everything behind the indices is cleared (read-ahead padding, gaps); colI itself is written completely
-    hipError_t e = hipMemsetAsync(b + colI_bytes, 0, l.total - colI_bytes, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(b + l.off_om, h.omega, (size_t)h.Kp * 4, hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) return fail(e);
+    gap(colI_bytes, l.off_optr);
+    gap(l.off_optr + (size_t)(h.G + 1) * 4, l.off_rptr);
+    gap(l.off_rptr + (size_t)(m + 1) * 4, l.off_oi);
+    gap(l.off_oi + oi_bytes, l.off_om);
+    gap(l.off_om + (size_t)h.Kp * 4, l.off_ri);
+    gap(l.off_ri + (size_t)(m + 1) * 8, l.off_tab);
+    gap(l.off_tab + (l.tab_shift ? ((size_t)m << l.tab_shift) * 4 : 0), l.total);
     const int cs = cser ? 1 : 0;
     // with fewer than half of the elements indexed the emitter packs them in LDS before it scatters them
-    const int sp = (double)A->nnz * 2.0 < (double)m * (double)n ? 1 : 0;
-    switch (A->colI.bits) {
-        case 8: launch_emit<uint8_t>(row_blocks, s, codes_d, cnt_d, rowPtrTmp, rowOffTmp, sd, m, n, cs, sp, b, l); break;
-        case 16: launch_emit<uint16_t>(row_blocks, s, codes_d, cnt_d, rowPtrTmp, rowOffTmp, sd, m, n, cs, sp, b, l); break;
-        default: launch_emit<uint32_t>(row_blocks, s, codes_d, cnt_d, rowPtrTmp, rowOffTmp, sd, m, n, cs, sp, b, l);
+    const int sp = (double)h.nnz * 2.0 < (double)m * (double)n ? 1 : 0;
+    hipError_t e = hipSuccess;
+    switch (hnd->host->colI.bits) {
+        case 8: e = launch_emit<uint8_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to); break;
+        case 16: e = launch_emit<uint16_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to); break;
+        default: e = launch_emit<uint32_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to);
     }
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(s);  // `h.omega` lives on this frame; errors surface here
-    if (e != hipSuccess) return fail(e);
-
-    auto* hnd = new cer_matrix();
-    hnd->host = std::move(A);
-    bind_device(hnd, dev, base, l);
-    e = (hipError_t)build_rank_table(hnd->view, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-        cer_free(hnd);
-        return record_hip_error((int)e);
-    }
+    HIP_TRY(e);
+    HIP_TRY(hipStreamSynchronize(s));  // the handle is complete for every stream; errors surface here
     // rows of unequal length: the batched product wants them ordered (and the longest in parts); the row starts
     // come back from the device only when the longest row says that the table will be built
-    if (row_schedule_wanted((uint64_t)hnd->host->nnz, (uint64_t)m, (uint64_t)h.max_row_nnz)) {
+    if (row_schedule_wanted((uint64_t)h.nnz, (uint64_t)m, (uint64_t)h.max_row_nnz)) {
         std::vector<uint32_t> info((size_t)(m + 1) * 2);
-        e = hipMemcpy(info.data(), b + l.off_ri, info.size() * 4, hipMemcpyDeviceToHost);
-        if (e != hipSuccess) {
-            cer_free(hnd);
-            return record_hip_error((int)e);
-        }
+        HIP_TRY(hipMemcpy(info.data(), to.base + l.off_ri, info.size() * 4, hipMemcpyDeviceToHost));
         std::vector<uint64_t> start((size_t)m + 1);
         for (int64_t r = 0; r <= m; ++r) start[(size_t)r] = info[(size_t)r * 2 + 1];
-        const int rc = build_row_schedule(hnd, start);
-        if (rc != CER_OK) {
-            cer_free(hnd);
-            return rc;
-        }
+        rc = build_row_schedule(hnd.get(), start);
+        if (rc != CER_OK) return rc;
     }
-    *out = hnd;
+    *out = hnd.release();
     return CER_OK;
 }
 

@@ -52,3 +52,30 @@ def test_streams_and_threads_share_the_kept_blocks(threads):
     B.cer_trim()
     assert not bad, bad
     B.cer_free(h)
+
+
+@pytest.mark.parametrize("side_stream", [False, True])
+def test_a_freed_handles_memory_serves_the_next_one_in_order(side_stream):
+    """A handle is freed while its products are still queued; the next handle of the same size, encoded on the null stream,
+    takes over its device memory: every product shows its own matrix."""
+    dev = torch.device("cuda:0")
+    cb = np.array([-1.0, 0.0, 1.0, 2.0], np.float32)
+    rng = np.random.default_rng(3)
+    Ws = [rng.choice(cb, size=(700, 900), p=[0.1, 0.7, 0.1, 0.1]).astype(np.float32) for _ in range(4)]
+    X = torch.from_numpy(rng.standard_normal((900, 40)).astype(np.float32)).to(dev)
+    Wd = [torch.from_numpy(W).to(dev) for W in Ws]
+    stream = torch.cuda.Stream() if side_stream else None
+    torch.cuda.synchronize()
+    outs = []
+    for W in Wd:
+        h = B.cer_encode_device(W, 700, 900, cb, "cer")
+        for _ in range(20):
+            Y = torch.empty((700, 40), device=dev)
+            B.cer_matmul(h, X, Y, 40, stream)
+        outs.append(Y)
+        B.cer_free(h)
+    torch.cuda.synchronize()
+    for W, Y in zip(Ws, outs):
+        want = W.astype(np.float64) @ X.cpu().numpy().astype(np.float64)
+        bound = 1e-5 * (np.abs(W).astype(np.float64) @ np.abs(X.cpu().numpy()).astype(np.float64))
+        assert (np.abs(Y.cpu().numpy() - want) <= bound).all()
