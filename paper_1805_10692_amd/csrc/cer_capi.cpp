@@ -314,11 +314,53 @@ void cer::handle_free(void* p, bool null_stream_only) {
 
 namespace {
 
-std::vector<uint32_t> widen(const cer::HostArray& a) {
-    std::vector<uint32_t> out((size_t)a.len);
-    for (int64_t i = 0; i < a.len; ++i) out[(size_t)i] = (uint32_t)a.at(i);
-    return out;
+// The array's values as 32-bit words.
+void widen(const cer::HostArray& a, uint32_t* out) {
+    const size_t n = (size_t)a.len;
+    if (a.bits == 8) std::copy_n(a.bytes.data(), n, out);
+    else if (a.bits == 16) std::copy_n(reinterpret_cast<const uint16_t*>(a.bytes.data()), n, out);
+    else std::memcpy(out, a.bytes.data(), n * 4);
 }
+
+// Pinned host memory through which host-encoded handles go to the device (a copy out of pageable memory waits once per
+// array, 48 us each): one block is kept, of at most kStageKept bytes.
+constexpr size_t kStageKept = 16u << 20;
+std::mutex g_stage_mutex;
+void* g_stage = nullptr;
+size_t g_stage_bytes = 0;
+
+struct StageBlock {
+    void* p = nullptr;
+    size_t bytes = 0;
+    bool get(size_t need) {
+        {
+            std::lock_guard<std::mutex> lock(g_stage_mutex);
+            std::swap(p, g_stage);
+            std::swap(bytes, g_stage_bytes);
+        }
+        if (p && bytes >= need) return true;
+        if (p) (void)hipHostFree(p);
+        p = nullptr;
+        bytes = 65536;
+        while (bytes < need) bytes *= 2;
+        if (hipHostMalloc(&p, bytes, hipHostMallocPortable) == hipSuccess) return true;
+        (void)hipGetLastError();
+        p = nullptr;
+        return false;
+    }
+    ~StageBlock() {
+        if (!p) return;
+        if (bytes <= kStageKept) {
+            std::lock_guard<std::mutex> lock(g_stage_mutex);
+            if (!g_stage) {
+                g_stage = p;
+                g_stage_bytes = bytes;
+                return;
+            }
+        }
+        (void)hipHostFree(p);
+    }
+};
 
 }  // namespace
 
@@ -435,19 +477,6 @@ int cer::ensure_host_arrays(const cer_matrix* h) {
 }
 
 namespace {
-
-// The row schedule of a host-encoded handle, from its host arrays.
-int upload_split_table(cer_matrix* h) {
-    const cer::HostMatrix& A = *h->host;
-    if (A.m <= 0 || A.nnz <= 0) return CER_OK;
-    std::vector<uint64_t> start((size_t)A.m + 1);
-    for (int64_t r = 0; r <= A.m; ++r) start[(size_t)r] = A.omegaPtr.at((int64_t)A.rowPtr.at(r));
-    return cer::build_row_schedule(h, start);
-}
-
-}  // namespace
-
-namespace {
 // P: positions per part of a long row
 uint64_t part_length(uint64_t mean) { return ((std::max<uint64_t>(mean + mean / 2, 2048) + 2047) / 2048) * 2048; }
 }  // namespace
@@ -529,7 +558,8 @@ int cer::build_row_schedule(cer_matrix* h, const std::vector<uint64_t>& start) {
 
 namespace {
 
-// Copies the host arrays into one fresh device allocation (layout: cer::DeviceLayout).
+// Copies the host arrays into one fresh device allocation (layout: cer::DeviceLayout).  Everything but the rank table,
+// which the device derives, is laid out in host memory first and copied at once.
 int upload(cer_matrix* h) {
     const cer::HostMatrix& A = *h->host;
     int ndev = 0;
@@ -546,37 +576,51 @@ int upload(cer_matrix* h) {
     void* base = nullptr;
     e = (hipError_t)cer::handle_alloc(&base, l.total, nullptr);
     if (e != hipSuccess) return hip_fail(e);
-    auto* b = static_cast<unsigned char*>(base);
-    e = hipMemset(base, 0, l.total);
-    auto put = [&](size_t off, const void* src, size_t bytes) {
-        if (e == hipSuccess && bytes) e = hipMemcpy(b + off, src, bytes, hipMemcpyHostToDevice);
+    cer::bind_device(h, dev, base, l);  // from here on the caller frees the allocation with the handle
+
+    StageBlock stage;
+    std::vector<unsigned char> pageable;
+    unsigned char* img = nullptr;
+    if (l.off_tab <= kStageKept && stage.get(l.off_tab)) {
+        img = static_cast<unsigned char*>(stage.p);
+    } else {
+        pageable.resize(l.off_tab);
+        img = pageable.data();
+    }
+    auto put = [&](size_t off, const void* src, size_t bytes, size_t end) {  // an array and the zeros behind it
+        if (bytes) std::memcpy(img + off, src, bytes);
+        std::memset(img + off + bytes, 0, end - off - bytes);
     };
-    put(l.off_colI, A.colI.bytes.data(), l.colI_bytes);
-    {
-        std::vector<uint32_t> w = widen(A.omegaPtr);
-        put(l.off_optr, w.data(), w.size() * 4);
+    put(l.off_colI, A.colI.bytes.data(), l.colI_bytes, l.off_optr);
+    auto* optr = reinterpret_cast<uint32_t*>(img + l.off_optr);
+    auto* rptr = reinterpret_cast<uint32_t*>(img + l.off_rptr);
+    auto* info = reinterpret_cast<uint32_t*>(img + l.off_ri);
+    const size_t optr_bytes = (size_t)(A.G + 1) * 4, rptr_bytes = (size_t)(A.m + 1) * 4;
+    widen(A.omegaPtr, optr);
+    widen(A.rowPtr, rptr);
+    std::memset(img + l.off_optr + optr_bytes, 0, l.off_rptr - l.off_optr - optr_bytes);
+    std::memset(img + l.off_rptr + rptr_bytes, 0, l.off_oi - l.off_rptr - rptr_bytes);
+    put(l.off_oi, A.omegaI.bytes.data(), l.omegaI_bytes, l.off_om);
+    put(l.off_om, A.omega.data(), A.omega.size() * 4, l.off_ri);
+    for (int64_t r = 0; r <= A.m; ++r) {
+        info[(size_t)r * 2] = rptr[(size_t)r];
+        info[(size_t)r * 2 + 1] = optr[rptr[(size_t)r]];
     }
-    {
-        std::vector<uint32_t> w = widen(A.rowPtr);
-        put(l.off_rptr, w.data(), w.size() * 4);
-        std::vector<uint32_t> info((size_t)(A.m + 1) * 2);
-        for (int64_t r = 0; r <= A.m; ++r) {
-            info[(size_t)r * 2] = w[(size_t)r];
-            info[(size_t)r * 2 + 1] = (uint32_t)A.omegaPtr.at((int64_t)w[(size_t)r]);
-        }
-        put(l.off_ri, info.data(), info.size() * 4);
-    }
-    put(l.off_oi, A.omegaI.bytes.data(), l.omegaI_bytes);
-    put(l.off_om, A.omega.data(), A.omega.size() * 4);
-    if (e != hipSuccess) {
-        cer::handle_free(base, true);
-        return hip_fail(e);
-    }
-    cer::bind_device(h, dev, base, l);
-    e = (hipError_t)cer::build_rank_table(h->view, nullptr);
-    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-    if (e != hipSuccess) return hip_fail(e);  // the caller frees the handle and with it the allocation
-    return upload_split_table(h);
+    std::memset(img + l.off_ri + 2 * rptr_bytes, 0, l.off_tab - l.off_ri - 2 * rptr_bytes);
+    e = hipMemcpyAsync(base, img, l.off_tab, hipMemcpyHostToDevice, nullptr);
+    if (e == hipSuccess) e = (hipError_t)cer::build_rank_table(h->view, nullptr);
+    const hipError_t f = hipStreamSynchronize(nullptr);  // the image may be used again
+    if (e == hipSuccess) e = f;
+    if (e != hipSuccess) return hip_fail(e);
+    if (A.m <= 0 || A.nnz <= 0) return CER_OK;
+    // the row schedule: from the rows' first colI positions, where some row is long enough
+    uint64_t longest = 0;
+    for (int64_t r = 0; r < A.m; ++r)
+        longest = std::max<uint64_t>(longest, info[(size_t)r * 2 + 3] - info[(size_t)r * 2 + 1]);
+    if (!cer::row_schedule_wanted((uint64_t)A.nnz, (uint64_t)A.m, longest)) return CER_OK;
+    std::vector<uint64_t> start((size_t)A.m + 1);
+    for (int64_t r = 0; r <= A.m; ++r) start[(size_t)r] = info[(size_t)r * 2 + 1];
+    return cer::build_row_schedule(h, start);
 }
 
 int encode_any(const float* W, int64_t m, int64_t n, const float* codebook, int32_t K, bool cser, cer_handle_t** out) {
@@ -985,6 +1029,12 @@ int cer_trim(void) {
             }
             release_kept(c, i);
         }
+    }
+    {
+        std::lock_guard<std::mutex> lock(g_stage_mutex);
+        if (g_stage) (void)hipHostFree(g_stage);
+        g_stage = nullptr;
+        g_stage_bytes = 0;
     }
     {
         HandleCache& c = g_handle_caches[dev];

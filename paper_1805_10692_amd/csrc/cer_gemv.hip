@@ -833,6 +833,7 @@ __global__ __launch_bounds__(256) void rank_table_kernel(KView v, uint32_t* __re
     const uint2 d0 = v.rowInfo[r], d1 = v.rowInfo[r + 1];
     const uint32_t g0 = d0.x, ng = d1.x - g0;  // at most 255 groups
     const uint32_t words = 1u << tab_shift;
+    if (r == v.m - 1) tab[((size_t)v.m << tab_shift) + lane] = 0;  // 256 bytes that the product may read ahead
     for (uint32_t w0 = 0; w0 < words; w0 += kWave) {
         const uint32_t word = w0 + lane;
         // the number of the row's groups whose rank is at most `word`: CER numbers its groups by rank (padding groups

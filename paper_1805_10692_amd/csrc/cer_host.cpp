@@ -1,19 +1,22 @@
 // Host-side encoder and decoder of the CER / CSER formats (Section III-A of the paper).
 //
-// The encoder is a three-pass, row-parallel counting sort:
-//   pass 1  element -> codebook symbol through a hash of the fp32 bit pattern; global histogram
-//   (order) symbols ranked by count (Section III-A step 1: frequency-major Omega)
-//   pass 2  per row: histogram over ranks -> number of indexed elements and of groups
-//   (scan)  exclusive prefix sums give every row its slice of colI / OmegaPtr / OmegaI
-//   pass 3  per row: scatter the columns into their rank bucket (ascending inside a bucket because
-//           columns are visited in order) and write the bucket boundaries as the row's pointers
+// The encoder is a row-parallel counting sort; one team of threads goes through all its steps:
+//   symbols  element -> codebook symbol through a hash of the fp32 bit pattern; per-row histograms
+//   (order)  symbols ranked by count (Section III-A step 1: frequency-major Omega)
+//   sizes    per row: number of indexed elements and of groups
+//   (scan)   exclusive prefix sums give every row its slice of colI / OmegaPtr / OmegaI
+//   fill     per row: scatter the columns into their rank bucket (ascending inside a bucket because
+//            columns are visited in order) and write the bucket boundaries as the row's pointers
 // Conversion cost is O(m.n), as the paper notes in Section V.
 #include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstring>
 #include <numeric>
+#include <system_error>
 #include <thread>
+
+#include <emmintrin.h>
 
 #include "../../include/cer.h"
 #include "cer_internal.hpp"
@@ -22,81 +25,348 @@ namespace cer {
 namespace {
 
 inline uint32_t value_bits(float v) {
-    if (v == 0.0f) v = 0.0f;  // -0.0 and +0.0 are one value, stored as +0.0
     uint32_t u;
     std::memcpy(&u, &v, 4);
-    return u;
+    return u == 0x80000000u ? 0u : u;  // -0.0 and +0.0 are one value, stored as +0.0
 }
 
-// Open-addressing table: fp32 bit pattern -> position in the caller's codebook.
+// fp32 bit pattern -> position in the caller's codebook: a table without collisions where one of a few multipliers gives
+// one (always, in practice, up to a few hundred values: the table may be large, only the K occupied slots are touched), so
+// that a look-up is one load and no branch; else a table with open addressing.
 class SymbolTable {
 public:
-    explicit SymbolTable(int32_t K) {
-        size_t cap = 16;
-        while (cap < (size_t)K * 4) cap <<= 1;
-        mask_ = cap - 1;
-        keys_.assign(cap, 0);
-        vals_.assign(cap, -1);
-    }
-    // false if the key is already present
-    bool insert(uint32_t key, int32_t val) {
-        size_t h = slot(key);
-        while (vals_[h] >= 0) {
-            if (keys_[h] == key) return false;
-            h = (h + 1) & mask_;
+    struct Slot {
+        uint32_t key, sym;
+    };
+    static constexpr uint32_t kFree = 0xFFFFFFFFu;  // the pattern of a NaN: no codebook value
+
+    // false: a value occurs twice
+    bool build(const float* codebook, int32_t K) {
+        uint32_t bits = 4;
+        while ((1u << bits) < (uint32_t)K * 4u && bits < 31) ++bits;
+        const uint32_t first = bits, last = K <= 1024 ? first + 6 : first - 1;
+        for (; bits <= last; ++bits) {
+            for (uint32_t t = 0; t < 8; ++t) {
+                mul_ = 0x9E3779B1u + t * 0x7F4A7C16u;  // odd
+                shift_ = 32 - bits;
+                slots_.assign((size_t)1 << bits, Slot{kFree, 0});
+                bool ok = true;
+                for (int32_t k = 0; k < K && ok; ++k) {
+                    Slot& s = slots_[slot(value_bits(codebook[k]))];
+                    if (s.key == value_bits(codebook[k])) return false;
+                    ok = s.key == kFree;
+                    s = Slot{value_bits(codebook[k]), (uint32_t)k};
+                }
+                if (ok) {
+                    perfect_ = true;
+                    return true;
+                }
+            }
         }
-        keys_[h] = key;
-        vals_[h] = val;
+        perfect_ = false;
+        mul_ = 0x9E3779B1u;
+        shift_ = 32 - first;
+        slots_.assign((size_t)1 << first, Slot{kFree, 0});
+        for (int32_t k = 0; k < K; ++k) {
+            const uint32_t key = value_bits(codebook[k]);
+            size_t h = slot(key);
+            while (slots_[h].key != kFree) {
+                if (slots_[h].key == key) return false;
+                h = (h + 1) & (slots_.size() - 1);
+            }
+            slots_[h] = Slot{key, (uint32_t)k};
+        }
         return true;
     }
+    bool perfect() const { return perfect_; }
+    // the slot of a key in a table without collisions; the caller compares the key (kFree is never a codebook value)
+    const Slot& at(uint32_t key) const { return slots_[slot(key)]; }
     int32_t find(uint32_t key) const {
+        if (key == kFree) return -1;
         size_t h = slot(key);
-        while (vals_[h] >= 0) {
-            if (keys_[h] == key) return vals_[h];
-            h = (h + 1) & mask_;
+        while (slots_[h].key != kFree) {
+            if (slots_[h].key == key) return (int32_t)slots_[h].sym;
+            h = (h + 1) & (slots_.size() - 1);
         }
         return -1;
     }
 
 private:
-    size_t slot(uint32_t key) const { return (size_t)((key * 0x9E3779B1u) >> 7) & mask_; }
-    size_t mask_;
-    std::vector<uint32_t> keys_;
-    std::vector<int32_t> vals_;
+    size_t slot(uint32_t key) const { return (size_t)((key * mul_) >> shift_); }
+    uint32_t mul_ = 1, shift_ = 28;
+    bool perfect_ = false;
+    std::vector<Slot> slots_;
 };
 
-int worker_count(int64_t rows) {
+// Threads for `work` elements: one for every 64 Ki of them, at most 16 and never more than there are rows.
+int worker_count(int64_t rows, int64_t work) {
     unsigned hw = std::thread::hardware_concurrency();
-    int t = (int)std::min<unsigned>(hw ? hw : 1, 16);
+    const int64_t t = std::min<int64_t>(std::min<unsigned>(hw ? hw : 1, 16), (work + 65535) / 65536);
     return (int)std::max<int64_t>(1, std::min<int64_t>(t, rows));
 }
 
-template <typename F>
-void parallel_rows(int64_t m, int nthreads, F&& body) {
-    if (nthreads <= 1 || m < 2) {
-        body(0, (int64_t)0, m);
-        return;
+// A team runs body(t, r0, r1, team) on its threads, each with a contiguous share of m rows; sync() waits for all of them.
+// The bodies must not throw (what they need is allocated before).  Threads are started once per call: 16 of them take
+// about as long as one pass over a layer.
+class Team {
+public:
+    template <typename F>
+    static void run(int threads, int64_t m, F&& body) {
+        Team team;
+        std::vector<std::thread> pool;
+        auto work = [&](int t) {
+            while (team.size_.load(std::memory_order_acquire) == 0) std::this_thread::yield();
+            const int n = team.size_.load(std::memory_order_relaxed);
+            body(t, m * t / n, m * (t + 1) / n, team);
+        };
+        pool.reserve((size_t)std::max(threads - 1, 0));
+        try {
+            for (int t = 1; t < threads; ++t) pool.emplace_back(work, t);
+        } catch (const std::system_error&) {  // no more threads to be had: the ones there are share the rows
+        }
+        team.size_.store((int)pool.size() + 1, std::memory_order_release);
+        work(0);
+        for (auto& th : pool) th.join();
     }
-    std::vector<std::thread> pool;
-    int64_t per = (m + nthreads - 1) / nthreads;
-    for (int t = 0; t < nthreads; ++t) {
-        int64_t r0 = std::min<int64_t>(m, t * per), r1 = std::min<int64_t>(m, r0 + per);
-        pool.emplace_back([&body, t, r0, r1] { body(t, r0, r1); });
+    void sync() {
+        const int n = size_.load(std::memory_order_relaxed);
+        const int turn = turn_.load(std::memory_order_relaxed);
+        if (arrived_.fetch_add(1, std::memory_order_acq_rel) + 1 == n) {
+            arrived_.store(0, std::memory_order_relaxed);
+            turn_.store(turn + 1, std::memory_order_release);
+            return;
+        }
+        for (int spins = 0; turn_.load(std::memory_order_acquire) == turn; ++spins) {
+            if (spins < 2000) _mm_pause(); else std::this_thread::yield();
+        }
     }
-    for (auto& th : pool) th.join();
+
+private:
+    std::atomic<int> size_{0}, arrived_{0}, turn_{0};
+};
+
+void store(HostArray& a, uint64_t i, uint32_t v) {
+    switch (a.bits) {
+        case 8: a.bytes[(size_t)i] = (uint8_t)v; break;
+        case 16: reinterpret_cast<uint16_t*>(a.bytes.data())[i] = (uint16_t)v; break;
+        default: reinterpret_cast<uint32_t*>(a.bytes.data())[i] = v;
+    }
 }
 
-void narrow(const std::vector<uint32_t>& src, int bits, HostArray* dst) {
-    dst->len = (int64_t)src.size();
-    dst->bits = bits;
-    dst->bytes.resize(src.size() * (size_t)(bits / 8));
-    if (bits == 8) {
-        for (size_t i = 0; i < src.size(); ++i) dst->bytes[i] = (uint8_t)src[i];
-    } else if (bits == 16) {
-        auto* p = reinterpret_cast<uint16_t*>(dst->bytes.data());
-        for (size_t i = 0; i < src.size(); ++i) p[i] = (uint16_t)src[i];
+void shape(HostArray& a, uint64_t len, int bits) {
+    a.len = (int64_t)len;
+    a.bits = bits;
+    a.bytes.resize((size_t)len * (size_t)(bits / 8));
+}
+
+// Symbols of one row and their histogram (four interleaved ones: a value that follows itself does not wait for its own
+// last increment); false: an element is no codebook value.
+template <typename SymT>
+bool row_symbols(const SymbolTable& table, const float* W, int64_t n, int32_t K, SymT* sym, uint32_t* h4, uint32_t* c) {
+    std::fill(h4, h4 + 4 * (size_t)K, 0u);
+    uint32_t bad = 0;
+    int64_t j = 0;
+    if (table.perfect()) {
+        auto one = [&](int64_t i, uint32_t* h) {
+            const uint32_t key = value_bits(W[i]);
+            const SymbolTable::Slot s = table.at(key);
+            bad |= (s.key ^ key) | (uint32_t)(key == SymbolTable::kFree);
+            sym[i] = (SymT)s.sym;
+            ++h[s.sym];
+        };
+        for (; j + 4 <= n; j += 4) {
+            one(j, h4);
+            one(j + 1, h4 + K);
+            one(j + 2, h4 + 2 * (size_t)K);
+            one(j + 3, h4 + 3 * (size_t)K);
+        }
+        for (; j < n; ++j) one(j, h4);
     } else {
-        std::memcpy(dst->bytes.data(), src.data(), src.size() * 4);
+        for (; j < n; ++j) {
+            const int32_t s = table.find(value_bits(W[j]));
+            if (s < 0) return false;
+            sym[j] = (SymT)s;
+            ++h4[s];
+        }
+    }
+    for (int32_t k = 0; k < K; ++k) c[k] = h4[k] + h4[(size_t)K + k] + h4[2 * (size_t)K + k] + h4[3 * (size_t)K + k];
+    return bad == 0;
+}
+
+template <typename SymT>
+void row_histogram(const SymT* sym, int64_t n, int32_t K, uint32_t* c) {
+    std::fill(c, c + K, 0u);
+    for (int64_t j = 0; j < n; ++j) ++c[sym[j]];
+}
+
+// Columns of the row's elements that do not hold the symbol `dom`, each to the next slot of its symbol's bucket.
+template <typename SymT, typename ColT>
+void row_scatter(const SymT* sym, int64_t n, uint32_t dom, uint32_t* fill, ColT* colI) {
+    int64_t j = 0;
+    if (sizeof(SymT) == 1) {  // 64 symbols at a time; the ones to place come out of a bit mask
+        const __m128i d = _mm_set1_epi8((char)dom);
+        for (; j + 64 <= n; j += 64) {
+            uint64_t mask = 0;
+            for (int q = 0; q < 4; ++q) {
+                const __m128i v = _mm_loadu_si128(reinterpret_cast<const __m128i*>(sym + j + 16 * q));
+                mask |= (uint64_t)(uint16_t)~_mm_movemask_epi8(_mm_cmpeq_epi8(v, d)) << (16 * q);
+            }
+            while (mask) {
+                const int64_t i = j + __builtin_ctzll(mask);
+                mask &= mask - 1;
+                colI[fill[sym[i]]++] = (ColT)i;
+            }
+        }
+    }
+    for (; j < n; ++j)
+        if (sym[j] != dom) colI[fill[sym[j]]++] = (ColT)j;
+}
+
+template <typename SymT>
+int encode_rows(const float* W, int64_t m, int64_t n, const float* codebook, int32_t Kc, const SymbolTable& table,
+                HostMatrix& A) {
+    const int64_t N = m * n;
+    const bool cser = A.cser;
+    const int T = worker_count(m, N);
+    std::unique_ptr<SymT[]> sym(new SymT[(size_t)std::max<int64_t>(N, 1)]);
+    // the rows' histograms are kept unless they would be larger than the matrix (few columns, many values)
+    const bool keep = (int64_t)Kc <= n;
+    std::unique_ptr<uint32_t[]> rows_c(new uint32_t[keep ? (size_t)m * (size_t)Kc : 1]);
+    const size_t Kz = (size_t)std::max(Kc, 1);
+    std::vector<uint32_t> scratch((size_t)T * Kz * 6);  // per thread: four histograms, counts, bucket positions
+    std::vector<int64_t> total((size_t)T * Kz, 0);
+    std::vector<uint64_t> row_nnz((size_t)m + 1, 0), row_groups((size_t)m + 1, 0);
+    std::vector<int64_t> nonempty_part((size_t)T, 0);
+    std::vector<uint32_t> order;  // rank -> symbol
+    order.reserve(Kz);
+    std::vector<uint32_t> rank_of(Kz, 0);
+    std::atomic<bool> missing{false};
+    std::atomic<int> rc{CER_OK};
+
+    Team::run(T, m, [&](int t, int64_t r0, int64_t r1, Team& team) {
+        uint32_t* h4 = scratch.data() + (size_t)t * Kz * 6;
+        uint32_t* own = h4 + 4 * Kz;
+        uint32_t* fill = own + Kz;
+        int64_t* sum = total.data() + (size_t)t * Kz;
+        bool ok = true;
+        for (int64_t r = r0; r < r1 && ok; ++r) {
+            uint32_t* c = keep ? rows_c.get() + (size_t)r * Kz : own;
+            ok = row_symbols<SymT>(table, W + r * n, n, Kc, sym.get() + r * n, h4, c);
+            for (int32_t k = 0; k < Kc; ++k) sum[k] += c[k];
+        }
+        if (!ok) missing.store(true);
+        team.sync();
+        if (missing.load()) return;
+
+        if (t == 0) {
+            // Omega: occurring symbols by count, highest first; stable, so equal counts keep codebook order
+            for (int i = 1; i < T; ++i)
+                for (int32_t k = 0; k < Kc; ++k) total[(size_t)k] += total[(size_t)i * Kz + (size_t)k];
+            for (int32_t k = 0; k < Kc; ++k)
+                if (total[(size_t)k] > 0) order.push_back((uint32_t)k);
+            std::sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
+                return total[a] > total[b] || (total[a] == total[b] && a < b);
+            });
+            for (size_t k = 0; k < order.size(); ++k) rank_of[order[k]] = (uint32_t)k;
+        }
+        team.sync();
+        const int32_t K = (int32_t)order.size();
+
+        for (int64_t r = r0; r < r1; ++r) {
+            const uint32_t* c = keep ? rows_c.get() + (size_t)r * Kz : own;
+            if (!keep) row_histogram(sym.get() + r * n, n, Kc, own);
+            uint64_t present = 0, top = 0;
+            for (int32_t k = 1; k < K; ++k)
+                if (c[order[(size_t)k]]) { ++present; top = (uint64_t)k; }
+            row_nnz[(size_t)r] = (uint64_t)n - (K > 0 ? c[order[0]] : 0u);
+            row_groups[(size_t)r] = cser ? present : top;
+            nonempty_part[(size_t)t] += (int64_t)present;
+        }
+        team.sync();
+
+        if (t == 0) {
+            // exclusive scans
+            uint64_t acc_n = 0, acc_g = 0;
+            for (int64_t r = 0; r <= m; ++r) {
+                const uint64_t a = row_nnz[(size_t)r], g = row_groups[(size_t)r];
+                A.max_row_groups = std::max<int64_t>(A.max_row_groups, (int64_t)g);
+                row_nnz[(size_t)r] = acc_n;
+                row_groups[(size_t)r] = acc_g;
+                acc_n += a;
+                acc_g += g;
+            }
+            // the kernels address colI and OmegaPtr with 32-bit offsets and read ahead of a row's end
+            const uint64_t limit = 0xFFFFFFFFull - 65536;
+            if (acc_n > limit || acc_g > limit) {
+                rc.store(CER_E_TOO_LARGE);
+            } else {
+                try {
+                    A.K = K;
+                    A.omega.resize((size_t)K);
+                    A.count.resize((size_t)K);
+                    for (int32_t k = 0; k < K; ++k) {
+                        const float v = codebook[order[(size_t)k]];
+                        A.omega[(size_t)k] = (v == 0.0f) ? 0.0f : v;
+                        A.count[(size_t)k] = total[order[(size_t)k]];
+                    }
+                    A.nnz = (int64_t)acc_n;
+                    A.G = (int64_t)acc_g;
+                    A.nonempty_groups = std::accumulate(nonempty_part.begin(), nonempty_part.end(), (int64_t)0);
+                    shape(A.colI, acc_n, min_index_bits(n > 0 ? (uint64_t)(n - 1) : 0));
+                    shape(A.omegaPtr, acc_g + 1, min_index_bits(acc_n));
+                    shape(A.rowPtr, (uint64_t)m + 1, min_index_bits(acc_g));
+                    if (cser) shape(A.omegaI, acc_g, min_index_bits(K > 0 ? (uint64_t)(K - 1) : 0));
+                    store(A.omegaPtr, 0, 0);
+                    store(A.rowPtr, (uint64_t)m, (uint32_t)acc_g);
+                } catch (const std::bad_alloc&) {
+                    rc.store(CER_E_NOMEM);
+                }
+            }
+        }
+        team.sync();
+        if (rc.load() != CER_OK) return;
+
+        for (int64_t r = r0; r < r1; ++r) {
+            const SymT* s = sym.get() + r * n;
+            const uint32_t* c = keep ? rows_c.get() + (size_t)r * Kz : own;
+            if (!keep) row_histogram(s, n, Kc, own);
+            uint64_t g = row_groups[(size_t)r];
+            store(A.rowPtr, (uint64_t)r, (uint32_t)g);
+            const uint64_t g_end = row_groups[(size_t)r + 1];
+            uint32_t pos = (uint32_t)row_nnz[(size_t)r];
+            for (int32_t k = 1; k < K && g < g_end; ++k) {
+                const uint32_t len = c[order[(size_t)k]];
+                fill[order[(size_t)k]] = pos;
+                pos += len;
+                if (cser) {
+                    if (len == 0) continue;
+                    store(A.omegaI, g, (uint32_t)k);
+                }
+                store(A.omegaPtr, ++g, pos);
+            }
+            if (K == 0) continue;
+            if (A.colI.bits == 8) row_scatter<SymT>(s, n, order[0], fill, A.colI.bytes.data());
+            else if (A.colI.bits == 16) row_scatter<SymT>(s, n, order[0], fill, reinterpret_cast<uint16_t*>(A.colI.bytes.data()));
+            else row_scatter<SymT>(s, n, order[0], fill, reinterpret_cast<uint32_t*>(A.colI.bytes.data()));
+        }
+    });
+    return missing.load() ? (int)CER_E_NOT_IN_CODEBOOK : rc.load();
+}
+
+template <typename ColT>
+void decode_rows(const HostMatrix& A, float* W, int64_t r0, int64_t r1) {
+    const ColT* colI = reinterpret_cast<const ColT*>(A.colI.bytes.data());
+    for (int64_t r = r0; r < r1; ++r) {
+        float* row = W + r * A.n;
+        std::fill(row, row + A.n, A.omega[0]);
+        const int64_t g0 = (int64_t)A.rowPtr.at(r), g1 = (int64_t)A.rowPtr.at(r + 1);
+        uint64_t i = A.omegaPtr.at(g0);
+        for (int64_t g = g0; g < g1; ++g) {
+            const int64_t rank = A.cser ? (int64_t)A.omegaI.at(g) : g - g0 + 1;
+            const float v = A.omega[(size_t)rank];
+            const uint64_t e = A.omegaPtr.at(g + 1);
+            for (; i < e; ++i) row[colI[i]] = v;
+        }
     }
 }
 
@@ -109,152 +379,27 @@ int min_index_bits(uint64_t max_value) {
 int encode_host(const float* W, int64_t m, int64_t n, const float* codebook, int32_t Kc, bool cser,
                 std::shared_ptr<HostMatrix>* out) {
     if (n > (int64_t)0xFFFFFFFFll) return CER_E_TOO_LARGE;
-    const int64_t N = m * n;
-
-    SymbolTable table(Kc);
-    for (int32_t k = 0; k < Kc; ++k) {
-        if (!std::isfinite(codebook[k])) return CER_E_BAD_CODEBOOK;
-        if (!table.insert(value_bits(codebook[k]), k)) return CER_E_BAD_CODEBOOK;
-    }
-
-    // pass 1: symbols and the global histogram
-    std::vector<uint32_t> sym((size_t)N);
-    const int T = worker_count(m);
-    std::vector<std::vector<int64_t>> hist((size_t)T, std::vector<int64_t>((size_t)Kc, 0));
-    std::atomic<bool> missing{false};
-    parallel_rows(m, T, [&](int t, int64_t r0, int64_t r1) {
-        auto& h = hist[(size_t)t];
-        uint32_t last_key = 0;
-        int32_t last_sym = -1;
-        for (int64_t i = r0 * n; i < r1 * n; ++i) {
-            uint32_t key = value_bits(W[i]);
-            if (last_sym < 0 || key != last_key) {
-                int32_t s = table.find(key);
-                if (s < 0) { missing.store(true); return; }
-                last_key = key;
-                last_sym = s;
-            }
-            sym[(size_t)i] = (uint32_t)last_sym;
-            ++h[(size_t)last_sym];
-        }
-    });
-    if (missing.load()) return CER_E_NOT_IN_CODEBOOK;
-    std::vector<int64_t> total((size_t)Kc, 0);
-    for (auto& h : hist)
-        for (int32_t k = 0; k < Kc; ++k) total[(size_t)k] += h[(size_t)k];
-
-    // Omega: occurring symbols by count, highest first; stable, so equal counts keep codebook order
-    std::vector<int32_t> order;
     for (int32_t k = 0; k < Kc; ++k)
-        if (total[(size_t)k] > 0) order.push_back(k);
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return total[(size_t)a] > total[(size_t)b]; });
-    const int32_t K = (int32_t)order.size();
-    std::vector<uint32_t> rank_of((size_t)std::max(Kc, 1), 0);
+        if (!std::isfinite(codebook[k])) return CER_E_BAD_CODEBOOK;
+    SymbolTable table;
+    if (!table.build(codebook, Kc)) return CER_E_BAD_CODEBOOK;
     auto A = std::make_shared<HostMatrix>();
-    A->cser = cser; A->m = m; A->n = n; A->K = K;
-    A->omega.resize((size_t)K);
-    A->count.resize((size_t)K);
-    for (int32_t k = 0; k < K; ++k) {
-        rank_of[(size_t)order[(size_t)k]] = (uint32_t)k;
-        float v = codebook[order[(size_t)k]];
-        A->omega[(size_t)k] = (v == 0.0f) ? 0.0f : v;
-        A->count[(size_t)k] = total[(size_t)order[(size_t)k]];
-    }
-    for (auto& s : sym) s = rank_of[s];  // from here on: rank of every element
-
-    // pass 2: per-row sizes
-    std::vector<uint64_t> row_nnz((size_t)m + 1, 0), row_groups((size_t)m + 1, 0);
-    std::vector<int64_t> nonempty_part((size_t)T, 0);
-    parallel_rows(m, T, [&](int t, int64_t r0, int64_t r1) {
-        std::vector<uint32_t> c((size_t)std::max(K, 1));
-        for (int64_t r = r0; r < r1; ++r) {
-            std::fill(c.begin(), c.end(), 0u);
-            const uint32_t* s = sym.data() + r * n;
-            for (int64_t j = 0; j < n; ++j) ++c[s[j]];
-            uint64_t present = 0, top = 0;
-            for (int32_t k = 1; k < K; ++k)
-                if (c[(size_t)k]) { ++present; top = (uint64_t)k; }
-            row_nnz[(size_t)r] = (uint64_t)n - c[0];
-            row_groups[(size_t)r] = cser ? present : top;
-            nonempty_part[(size_t)t] += (int64_t)present;
-        }
-    });
-    // exclusive scans
-    uint64_t acc_n = 0, acc_g = 0;
-    for (int64_t r = 0; r <= m; ++r) {
-        uint64_t a = row_nnz[(size_t)r], g = row_groups[(size_t)r];
-        row_nnz[(size_t)r] = acc_n;
-        row_groups[(size_t)r] = acc_g;
-        acc_n += a;
-        acc_g += g;
-    }
-    // the kernels address colI and OmegaPtr with 32-bit offsets and read ahead of a row's end
-    const uint64_t limit = 0xFFFFFFFFull - 65536;
-    if (acc_n > limit || acc_g > limit) return CER_E_TOO_LARGE;
-    A->nnz = (int64_t)acc_n;
-    A->G = (int64_t)acc_g;
-    A->nonempty_groups = std::accumulate(nonempty_part.begin(), nonempty_part.end(), (int64_t)0);
-    for (int64_t r = 0; r < m; ++r)
-        A->max_row_groups = std::max<int64_t>(A->max_row_groups, (int64_t)(row_groups[(size_t)r + 1] - row_groups[(size_t)r]));
-
-    // pass 3: fill
-    std::vector<uint32_t> colI((size_t)acc_n), omegaPtr((size_t)acc_g + 1), rowPtr((size_t)m + 1),
-        omegaI(cser ? (size_t)acc_g : 0);
-    omegaPtr[0] = 0;
-    for (int64_t r = 0; r <= m; ++r) rowPtr[(size_t)r] = (uint32_t)row_groups[(size_t)r];
-    parallel_rows(m, T, [&](int, int64_t r0, int64_t r1) {
-        std::vector<uint32_t> start((size_t)std::max(K, 1) + 1), fill((size_t)std::max(K, 1));
-        for (int64_t r = r0; r < r1; ++r) {
-            const uint32_t* s = sym.data() + r * n;
-            std::fill(start.begin(), start.end(), 0u);
-            for (int64_t j = 0; j < n; ++j) ++start[(size_t)s[j] + 1];
-            start[1] = 0;  // rank 0 owns no indices
-            for (int32_t k = 2; k <= K; ++k) start[(size_t)k] += start[(size_t)k - 1];
-            // start[k] = offset of rank k's bucket inside the row, start[K] = row nnz (K >= 1)
-            const uint32_t base = (uint32_t)row_nnz[(size_t)r];
-            for (int32_t k = 1; k < K; ++k) fill[(size_t)k] = start[(size_t)k];
-            for (int64_t j = 0; j < n; ++j) {
-                uint32_t k = s[j];
-                if (k) colI[(size_t)base + fill[k]++] = (uint32_t)j;
-            }
-            uint64_t g = row_groups[(size_t)r];
-            const uint64_t g_end = row_groups[(size_t)r + 1];
-            for (int32_t k = 1; k < K && g < g_end; ++k) {
-                uint32_t b0 = start[(size_t)k], b1 = (k + 1 <= K) ? start[(size_t)k + 1] : b0;
-                if (cser) {
-                    if (b1 == b0) continue;
-                    omegaI[(size_t)g] = (uint32_t)k;
-                }
-                omegaPtr[(size_t)++g] = base + b1;
-            }
-        }
-    });
-
-    narrow(colI, min_index_bits(n > 0 ? (uint64_t)(n - 1) : 0), &A->colI);
-    narrow(omegaPtr, min_index_bits((uint64_t)A->nnz), &A->omegaPtr);
-    narrow(rowPtr, min_index_bits((uint64_t)A->G), &A->rowPtr);
-    if (cser) narrow(omegaI, min_index_bits(K > 0 ? (uint64_t)(K - 1) : 0), &A->omegaI);
-    *out = std::move(A);
-    return CER_OK;
+    A->cser = cser;
+    A->m = m;
+    A->n = n;
+    const int rc = Kc <= 256 ? encode_rows<uint8_t>(W, m, n, codebook, Kc, table, *A)
+                             : encode_rows<uint32_t>(W, m, n, codebook, Kc, table, *A);
+    if (rc == CER_OK) *out = std::move(A);
+    return rc;
 }
 
 int decode_host(const HostMatrix& A, float* W) {
-    const int64_t N = A.m * A.n;
-    if (N == 0) return CER_OK;
+    if (A.m * A.n == 0) return CER_OK;
     if (A.K < 1) return CER_E_INVALID;
-    std::fill(W, W + N, A.omega[0]);
-    parallel_rows(A.m, worker_count(A.m), [&](int, int64_t r0, int64_t r1) {
-        for (int64_t r = r0; r < r1; ++r) {
-            float* row = W + r * A.n;
-            const int64_t g0 = (int64_t)A.rowPtr.at(r), g1 = (int64_t)A.rowPtr.at(r + 1);
-            for (int64_t g = g0; g < g1; ++g) {
-                const int64_t rank = A.cser ? (int64_t)A.omegaI.at(g) : g - g0 + 1;
-                const float v = A.omega[(size_t)rank];
-                const int64_t e = (int64_t)A.omegaPtr.at(g + 1);
-                for (int64_t i = (int64_t)A.omegaPtr.at(g); i < e; ++i) row[A.colI.at(i)] = v;
-            }
-        }
+    Team::run(worker_count(A.m, A.m * A.n), A.m, [&](int, int64_t r0, int64_t r1, Team&) {
+        if (A.colI.bits == 8) decode_rows<uint8_t>(A, W, r0, r1);
+        else if (A.colI.bits == 16) decode_rows<uint16_t>(A, W, r0, r1);
+        else decode_rows<uint32_t>(A, W, r0, r1);
     });
     return CER_OK;
 }
