@@ -1,0 +1,91 @@
+// fp32 numbers as sums of bf16 numbers, for the bf16 matrix cores (gfx950).
+//
+// A binary32 significand has 24 bits, a bf16 one has 8: x = p0 + p1 + p2 with p0 = bf16(x), p1 = bf16(x - p0),
+// p2 = x - p0 - p1 is exact (both differences are exact in binary32, the last one fits 8 bits), for |x| from 2^-109 up to the
+// largest number.  Products of two pieces are exact in binary32 and the matrix cores add them up in binary32, so a
+// contraction over pieces has the inputs and the accumulation of the fp32 one.  Where both factors have three pieces the
+// three smallest of the nine products are left out: together below 2^-25 of the product, half a unit of what rounding a
+// binary32 product costs.  The bf16 matrix instructions run at 16 times the rate of the fp32 ones: three products (one
+// factor with 8-bit significands) or six cost a fifth to three eighths of the fp32 instruction's time.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+namespace cer {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
+}
+
+// Pieces of a pair of numbers that are finite and round to finite bf16 numbers; for other numbers the return value is a NaN.
+__device__ __forceinline__ float split3_pair(float a, float b, uint32_t p[3]) {
+    p[0] = bf16_pair(a, b);
+    const float ra = a - __uint_as_float(p[0] << 16), rb = b - __uint_as_float(p[0] & 0xFFFF0000u);
+    p[1] = bf16_pair(ra, rb);
+    const float qa = ra - __uint_as_float(p[1] << 16), qb = rb - __uint_as_float(p[1] & 0xFFFF0000u);
+    p[2] = bf16_pair(qa, qb);
+    return qa + qb;
+}
+
+// The same for any number: infinities and NaNs are one piece, and numbers that would round to infinity are cut instead.
+__device__ __forceinline__ void split3_any(float x, uint32_t p[3]) {
+    const uint32_t u = __float_as_uint(x), mag = u & 0x7FFFFFFFu;
+    if (mag >= 0x7F800000u) {
+        p[0] = mag > 0x7F800000u ? 0x7FC0u : u >> 16;
+        p[1] = p[2] = 0;
+        return;
+    }
+    p[0] = mag >= 0x7F7F0000u ? u >> 16 : bf16_pair(x, 0.f) & 0xFFFFu;
+    const float r = x - __uint_as_float(p[0] << 16);
+    p[1] = bf16_pair(r, 0.f) & 0xFFFFu;
+    p[2] = bf16_pair(r - __uint_as_float(p[1] << 16), 0.f) & 0xFFFFu;
+}
+
+// Eight numbers -> three times eight bf16, in the order given.
+__device__ __forceinline__ void split3_8(const float x[8], uint4 out[3]) {
+    uint32_t w[3][4];
+    float odd = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t p[3];
+        odd += split3_pair(x[2 * i], x[2 * i + 1], p);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) w[j][i] = p[j];
+    }
+    if (__ballot(odd != odd)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            uint32_t a[3], b[3];
+            split3_any(x[2 * i], a);
+            split3_any(x[2 * i + 1], b);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) w[j][i] = a[j] | (b[j] << 16);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) out[j] = make_uint4(w[j][0], w[j][1], w[j][2], w[j][3]);
+}
+
+__device__ __forceinline__ floatx16 mfma_bf16(uint4 a, uint4 b, floatx16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// The products of PW pieces of one factor with three of the other that reach 2^-25 of the result, smallest first.
+template <int PW>
+__device__ __forceinline__ floatx16 mfma_pieces(const uint4* a, const uint4* b, floatx16 c) {
+#pragma unroll
+    for (int s = 2; s >= 0; --s)
+#pragma unroll
+        for (int i = 0; i < PW; ++i)
+            if (s - i >= 0) c = mfma_bf16(a[i], b[s - i], c);
+    return c;
+}
+
+}  // namespace cer

@@ -25,6 +25,7 @@
 
 #include "../../include/cer.h"
 #include "cer_device.hpp"
+#include "cer_split3.hpp"
 
 namespace {
 
@@ -753,129 +754,188 @@ __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ c
 }
 
 // ------------------------------------------------------------------------------------------------
-// decode: format arrays -> dense matrix (Section III-A: M is reconstructed uniquely).  One workgroup
-// per row (large matrices) or per (row, every gridDim.y-th segment).  A segment of up to kDecSeg
-// columns is assembled in LDS -- filled with Omega[0], then every indexed position of the row whose
-// column falls into the segment writes its group's value -- and written out once with 16-byte stores,
-// so that HBM sees every line of W exactly once.  Positions are spread over the threads, kDecPer per
-// thread with all index loads issued together; a position finds its group by a binary search in the
-// row's pointers (up to kDecThreads groups at a time in LDS; repeated pointers, CER's empty groups,
-// are skipped by the search).  A row of at most kDecThreads groups and kDecThreads.kDecPer positions
-// keeps its columns and values in registers for all its segments; a larger row reloads them per
-// segment.
+// decode: format arrays -> dense matrix (Section III-A: M is reconstructed uniquely), as fp32 or as bf16 pieces for the
+// matrix cores.  One workgroup per (row, every gridDim.y-th segment of its columns).  A segment is assembled in LDS as one
+// byte per column, the element's rank (codebooks of more than 256 values: as its value), and written out with 16-byte
+// stores, so that HBM sees every line of the output once.  A thread takes eight consecutive positions of colI per step with
+// one load (the next step's is in flight), finds the group of the first one by a binary search in the row's pointers
+// (kThreads groups at a time in LDS; repeated pointers, CER's empty groups, fall to the last of them) and walks on from
+// there.  A row with several segments is read once per segment.
+// Bound by the bytes written and the indices read: 4096 x 9216, 75 % indexed, 83 -> 33 us (one position per thread and
+// search, values of a segment in LDS as fp32, before).
 // ------------------------------------------------------------------------------------------------
-constexpr uint32_t kDecSeg = 4096;
+struct DecodeArgs {
+    const uint32_t* omegaPtr;
+    const uint32_t* rowPtr;
+    const uint8_t* omegaI;
+    const float* omega;
+    int oi_bits, cser;
+    uint32_t K;
+    int64_t n;
+    uint32_t seg, nseg;  // columns per segment: a multiple of 8
+    int64_t pitch;       // output: elements per row (bf16: a multiple of 8, columns n .. pitch - 1 are written as zeros)
+    int64_t plane;       // bf16: elements from one piece's matrix to the next one's
+};
 
-// kDecThreads = workgroup size: 256, or 64 for matrices of short rows (a row is then little work, and four times as
-// many workgroups are in flight).  kDecPer = positions a thread keeps in registers: 8 for sparse rows, 32 where rows
-// hold thousands of indices.
-template <typename ColT, uint32_t kDecThreads, uint32_t kDecPer>
-__global__ __launch_bounds__(kDecThreads) void decode_kernel(
-    const ColT* __restrict__ colI, const uint32_t* __restrict__ omegaPtr, const uint32_t* __restrict__ rowPtr,
-    const uint8_t* __restrict__ omegaI, int oi_bits, const float* __restrict__ omega, int cser, int64_t n,
-    uint32_t seg, uint32_t nseg, float* __restrict__ W) {
-    extern __shared__ __align__(16) float s_row[];  // seg floats
-    __shared__ uint32_t s_ptr[kDecThreads + 1];
-    __shared__ float s_val[kDecThreads];
-    constexpr uint32_t T = kDecThreads, P = kDecPer;
+__device__ __forceinline__ void load_eight(const uint8_t* p, uint32_t v[8]) {
+    const uint2 q = *reinterpret_cast<const uint2*>(p);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[i] = (q.x >> (8 * i)) & 0xFFu;
+        v[4 + i] = (q.y >> (8 * i)) & 0xFFu;
+    }
+}
+__device__ __forceinline__ void load_eight(const uint16_t* p, uint32_t v[8]) {
+    const uint4 q = *reinterpret_cast<const uint4*>(p);
+    v[0] = q.x & 0xFFFFu; v[1] = q.x >> 16; v[2] = q.y & 0xFFFFu; v[3] = q.y >> 16;
+    v[4] = q.z & 0xFFFFu; v[5] = q.z >> 16; v[6] = q.w & 0xFFFFu; v[7] = q.w >> 16;
+}
+__device__ __forceinline__ void load_eight(const uint32_t* p, uint32_t v[8]) {
+    const uint4 a = reinterpret_cast<const uint4*>(p)[0], b = reinterpret_cast<const uint4*>(p)[1];
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+}
+
+// CodeT: uint8_t (rank) or float (value).  kPieces: 0 = fp32 output, 1 .. 3 = that many bf16 matrices.
+template <typename ColT, typename CodeT, int kPieces, uint32_t kThreads>
+__global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict__ colI, DecodeArgs a, void* __restrict__ out) {
+    constexpr bool kRanks = sizeof(CodeT) == 1;
+    constexpr uint32_t T = kThreads;
+    extern __shared__ __align__(16) unsigned char s_seg[];  // seg codes
+    __shared__ uint32_t s_ptr[T + 1];
+    __shared__ CodeT s_grp[T];
+    __shared__ uint32_t s_val[kRanks ? kCodes : 1];        // fp32 value, or pieces 0 | 1 << 16, by rank
+    __shared__ uint32_t s_val2[kRanks && kPieces == 3 ? kCodes : 1];
+    CodeT* code = reinterpret_cast<CodeT*>(s_seg);
     const uint32_t tid = threadIdx.x;
     const int64_t r = blockIdx.x;
-    const float w0 = omega[0];
-    const uint32_t g0 = rowPtr[r], g1 = rowPtr[r + 1];
+    const uint32_t g0 = a.rowPtr[r], g1 = a.rowPtr[r + 1];
+    const uint32_t cnt0 = min(g1 - g0, T);
 
-    // pointers and values of the groups gb .. gb + cnt - 1 of this row -> LDS
+    // pointers and ranks (values) of the groups gb .. gb + cnt - 1 of this row -> LDS
     auto stage_groups = [&](uint32_t gb, uint32_t cnt) {
         if (tid < cnt) {
             const uint32_t g = gb + tid;
             uint32_t rank = g - g0 + 1u;  // Algorithm 3: position in the row; Algorithm 4: OmegaI
-            if (cser) {
-                rank = oi_bits == 8 ? omegaI[g]
-                                    : (oi_bits == 16 ? reinterpret_cast<const uint16_t*>(omegaI)[g]
-                                                     : reinterpret_cast<const uint32_t*>(omegaI)[g]);
+            if (a.cser) {
+                rank = a.oi_bits == 8 ? a.omegaI[g]
+                                      : (a.oi_bits == 16 ? reinterpret_cast<const uint16_t*>(a.omegaI)[g]
+                                                         : reinterpret_cast<const uint32_t*>(a.omegaI)[g]);
             }
-            s_ptr[tid] = omegaPtr[g];
-            s_val[tid] = omega[rank];
+            s_ptr[tid] = a.omegaPtr[g];
+            if constexpr (kRanks) s_grp[tid] = (uint8_t)rank; else s_grp[tid] = a.omega[rank];
         }
-        if (tid == 0) s_ptr[cnt] = omegaPtr[gb + cnt];
+        if (tid == 0) s_ptr[cnt] = a.omegaPtr[gb + cnt];
     };
-    // columns and values of the positions pb + tid + k.T < pe (k < P) of the staged groups -> registers
-    uint32_t col[P];
-    float val[P];
-    uint32_t ok = 0;
-    auto load_positions = [&](uint32_t pb, uint32_t pe, uint32_t cnt) {
-        ok = 0;
-        const uint32_t last = pe > pb ? pe - 1u : pb;  // loads behind the last position are redirected to it
-#pragma unroll
-        for (uint32_t k = 0; k < P; ++k) col[k] = (uint32_t)colI[min(pb + tid + k * T, last)];
-        uint32_t lo = 0;  // a thread's positions grow with k, and so do their groups: the search resumes where it was
-#pragma unroll
-        for (uint32_t k = 0; k < P; ++k) {
-            const uint32_t p = pb + tid + k * T;
-            val[k] = 0.f;
-            if (p < pe) {
-                if (s_ptr[lo + 1u] <= p) {  // not the same group as the previous position
-                    uint32_t hi = cnt;      // s_ptr[lo] <= p < s_ptr[hi]
-                    while (hi - lo > 1u) {
-                        const uint32_t mid = (lo + hi) >> 1;
-                        if (s_ptr[mid] <= p) lo = mid; else hi = mid;
-                    }
-                }
-                val[k] = s_val[lo];
-                ok |= 1u << k;
+    if constexpr (kRanks) {
+        for (uint32_t k = tid; k < a.K; k += T) {
+            const float w = a.omega[k];
+            if constexpr (kPieces == 0) {
+                s_val[k] = __float_as_uint(w);
+            } else {
+                uint32_t p[3];
+                cer::split3_any(w, p);
+                s_val[k] = p[0] | (p[1] << 16);
+                if constexpr (kPieces == 3) s_val2[k] = p[2];
             }
         }
-    };
-    auto scatter = [&](int64_t c0, uint32_t len) {
-#pragma unroll
-        for (uint32_t k = 0; k < P; ++k) {
-            const uint64_t rel = (uint64_t)col[k] - (uint64_t)c0;  // huge when left of the segment
-            if (((ok >> k) & 1u) && rel < len) s_row[rel] = val[k];
-        }
-    };
-
-    const uint32_t ngroups = g1 - g0;
-    bool resident = ngroups <= T;
-    if (resident && ngroups > 0) {
-        stage_groups(g0, ngroups);
-        __syncthreads();
-        const uint32_t pb = s_ptr[0], pe = s_ptr[ngroups];
-        resident = pe - pb <= T * P;  // uniform over the workgroup
-        if (resident) load_positions(pb, pe, ngroups);
     }
+    const float w0 = kRanks ? 0.f : a.omega[0];
+    if (cnt0) stage_groups(g0, cnt0);
 
-    for (uint32_t si = blockIdx.y; si < nseg; si += gridDim.y) {  // uniform over the workgroup
-        const int64_t c0 = (int64_t)si * seg;
-        if (c0 >= n) break;
-        const uint32_t len = (uint32_t)((n - c0) < (int64_t)seg ? (n - c0) : (int64_t)seg);  // 1 .. seg
-        {
-            const float4 f4 = make_float4(w0, w0, w0, w0);
-            const uint32_t n4 = (len + 3u) >> 2;
-            for (uint32_t j = tid; j < n4; j += T) reinterpret_cast<float4*>(s_row)[j] = f4;
+    for (uint32_t si = blockIdx.y; si < a.nseg; si += gridDim.y) {  // uniform over the workgroup
+        const int64_t c0 = (int64_t)si * a.seg;
+        if (c0 >= a.n) break;
+        const uint32_t len = (uint32_t)min((int64_t)a.seg, a.n - c0);  // 1 .. seg
+        if constexpr (kRanks) {
+            for (uint32_t j = tid; j < (len + 15u) / 16u; j += T) reinterpret_cast<uint4*>(s_seg)[j] = make_uint4(0, 0, 0, 0);
+        } else {
+            for (uint32_t j = tid; j < (len + 3u) / 4u; j += T) reinterpret_cast<float4*>(s_seg)[j] = make_float4(w0, w0, w0, w0);
         }
         __syncthreads();
-        if (resident) {
-            scatter(c0, len);
-        } else {
-            for (uint32_t gb = g0; gb < g1; gb += T) {
-                const uint32_t cnt = g1 - gb < T ? g1 - gb : T;
-                __syncthreads();  // nobody still searches the previous groups
+        for (uint32_t gb = g0; gb < g1; gb += T) {
+            const uint32_t cnt = min(g1 - gb, T);
+            if (g1 - g0 > T) {  // not staged once and for all
+                __syncthreads();
                 stage_groups(gb, cnt);
                 __syncthreads();
-                const uint32_t pe = s_ptr[cnt];
-                for (uint32_t pb = s_ptr[0]; pb < pe; pb += T * P) {
-                    load_positions(pb, pe, cnt);
-                    scatter(c0, len);
+            }
+            const uint32_t pb = s_ptr[0], pe = s_ptr[cnt];
+            uint32_t lo = 0;
+            uint32_t v = (pb & ~7u) + tid * 8u;
+            uint32_t ahead[8];
+            if (v < pe) load_eight(colI + v, ahead);  // up to seven positions on either side belong to others
+            for (; v < pe; v += T * 8u) {
+                uint32_t col[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) col[i] = ahead[i];
+                if (v + T * 8u < pe) load_eight(colI + v + T * 8u, ahead);
+                const uint32_t first = max(v, pb);
+                uint32_t hi = cnt;  // s_ptr[lo] <= first < s_ptr[hi]
+                while (hi - lo > 1u) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if (s_ptr[mid] <= first) lo = mid; else hi = mid;
+                }
+                uint32_t end = s_ptr[lo + 1u];
+                CodeT c = s_grp[lo];
+#pragma unroll
+                for (uint32_t i = 0; i < 8; ++i) {
+                    const uint32_t p = v + i;
+                    if (p >= pb && p < pe) {
+                        if (p >= end) {
+                            do end = s_ptr[++lo + 1u]; while (end <= p);
+                            c = s_grp[lo];
+                        }
+                        const uint64_t rel = (uint64_t)col[i] - (uint64_t)c0;  // huge when left of the segment
+                        if (rel < len) code[rel] = c;
+                    }
                 }
             }
         }
         __syncthreads();
-        float* out = W + r * n + c0;
-        if ((reinterpret_cast<uintptr_t>(out) & 15u) == 0) {
-            const uint32_t n4 = len >> 2;
-            for (uint32_t j = tid; j < n4; j += T) reinterpret_cast<float4*>(out)[j] = reinterpret_cast<const float4*>(s_row)[j];
-            for (uint32_t j = (n4 << 2) + tid; j < len; j += T) out[j] = s_row[j];
+        if constexpr (kPieces == 0) {
+            float* o = static_cast<float*>(out) + r * a.pitch + c0;
+            const bool wide = (reinterpret_cast<uintptr_t>(o) & 15u) == 0;
+            if constexpr (kRanks) {
+                const uint32_t n4 = wide ? len >> 2 : 0u;
+                for (uint32_t j = tid; j < n4; j += T) {
+                    const uint32_t q = reinterpret_cast<const uint32_t*>(s_seg)[j];
+                    reinterpret_cast<uint4*>(o)[j] = make_uint4(s_val[q & 0xFFu], s_val[(q >> 8) & 0xFFu], s_val[(q >> 16) & 0xFFu], s_val[q >> 24]);
+                }
+                for (uint32_t j = (n4 << 2) + tid; j < len; j += T) o[j] = __uint_as_float(s_val[code[j]]);
+            } else {
+                const uint32_t n4 = wide ? len >> 2 : 0u;
+                for (uint32_t j = tid; j < n4; j += T) reinterpret_cast<float4*>(o)[j] = reinterpret_cast<const float4*>(s_seg)[j];
+                for (uint32_t j = (n4 << 2) + tid; j < len; j += T) o[j] = (float)code[j];
+            }
         } else {
-            for (uint32_t j = tid; j < len; j += T) out[j] = s_row[j];
+            // eight columns per thread and step; the last segment also writes the zeros up to the pitch
+            uint16_t* o = static_cast<uint16_t*>(out) + r * a.pitch + c0;
+            const uint32_t wlen = c0 + a.seg >= a.n ? (uint32_t)(a.pitch - c0) : a.seg;
+            for (uint32_t j = tid * 8u; j < wlen; j += T * 8u) {
+                uint32_t w[3][4] = {};
+#pragma unroll
+                for (uint32_t i = 0; i < 8; ++i) {
+                    uint32_t p01 = 0, p2 = 0;
+                    if (j + i < len) {
+                        if constexpr (kRanks) {
+                            p01 = s_val[code[j + i]];
+                            if constexpr (kPieces == 3) p2 = s_val2[code[j + i]];
+                        } else {
+                            uint32_t p[3];
+                            cer::split3_any((float)code[j + i], p);
+                            p01 = p[0] | (p[1] << 16);
+                            p2 = p[2];
+                        }
+                    }
+                    const uint32_t sh = 16u * (i & 1u);
+                    w[0][i >> 1] |= (p01 & 0xFFFFu) << sh;
+                    w[1][i >> 1] |= (p01 >> 16) << sh;
+                    w[2][i >> 1] |= p2 << sh;
+                }
+#pragma unroll
+                for (int q = 0; q < kPieces; ++q)
+                    *reinterpret_cast<uint4*>(o + q * a.plane + j) = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
+            }
         }
         __syncthreads();  // the segment has been read before the next one is filled
     }
@@ -1022,40 +1082,63 @@ hipError_t launch_emit(hipStream_t s, const uint8_t* codes, const uint32_t* cnt,
 namespace cer {
 
 namespace {
-template <typename ColT>
-int launch_decode(const DeviceView& v, float* W, hipStream_t s) {
-    // segments of equal length (a multiple of 4 columns, so that aligned rows give aligned segments)
-    const int64_t nseg = (v.n + kDecSeg - 1) / kDecSeg;
-    const uint32_t seg = (uint32_t)((((v.n + nseg - 1) / nseg) + 3) & ~(int64_t)3);
-    if (v.m > 0x7FFFFFFFll || nseg > 0x7FFFFFFFll) return CER_E_INVALID;
-    // one workgroup per row walks all its segments, unless that gives too few workgroups to fill the chip
-    const int64_t split = std::min<int64_t>(std::min<int64_t>(nseg, 65535), std::max<int64_t>(1, 4096 / v.m));
-    const dim3 grid((unsigned)v.m, (unsigned)split);
-    const size_t lds = (size_t)seg * sizeof(float);
-    if (v.nnz > v.m * 1500)  // rows of thousands of indices: keep up to 8192 of them in registers over the row's segments
-        decode_kernel<ColT, 256, 32><<<grid, 256, lds, s>>>(
-            static_cast<const ColT*>(v.colI), v.omegaPtr, v.rowPtr, static_cast<const uint8_t*>(v.omegaI), v.omegaI_bits,
-            v.omega, v.cser, v.n, seg, (uint32_t)nseg, W);
-    else if (v.n <= 1024)  // short rows: one wave per row
-        decode_kernel<ColT, 64, 8><<<grid, 64, lds, s>>>(
-            static_cast<const ColT*>(v.colI), v.omegaPtr, v.rowPtr, static_cast<const uint8_t*>(v.omegaI), v.omegaI_bits,
-            v.omega, v.cser, v.n, seg, (uint32_t)nseg, W);
-    else
-        decode_kernel<ColT, 256, 8><<<grid, 256, lds, s>>>(
-            static_cast<const ColT*>(v.colI), v.omegaPtr, v.rowPtr, static_cast<const uint8_t*>(v.omegaI), v.omegaI_bits,
-            v.omega, v.cser, v.n, seg, (uint32_t)nseg, W);
-    HIP_TRY(hipGetLastError());
-    return CER_OK;
+template <typename ColT, typename CodeT, int kPieces>
+hipError_t launch_decode(const DeviceView& v, void* out, int64_t pitch, int64_t plane, hipStream_t s) {
+    // Segments of equal length, at most 32 KiB of LDS; more of them where the rows alone give fewer than eight workgroups
+    // per compute unit, but not below 1024 columns (every segment reads the whole row's indices).
+    const int64_t most = 32768 / (int64_t)sizeof(CodeT);
+    int64_t nseg = std::max<int64_t>((v.n + most - 1) / most, std::min<int64_t>((2048 + v.m - 1) / v.m, v.n / 1024));
+    nseg = std::min<int64_t>(std::max<int64_t>(nseg, 1), 0x7FFFFFFF);
+    const uint32_t seg = (uint32_t)((((v.n + nseg - 1) / nseg) + 7) & ~(int64_t)7);
+    nseg = (v.n + seg - 1) / seg;
+    DecodeArgs a;
+    a.omegaPtr = v.omegaPtr;
+    a.rowPtr = v.rowPtr;
+    a.omegaI = static_cast<const uint8_t*>(v.omegaI);
+    a.omega = v.omega;
+    a.oi_bits = v.omegaI_bits;
+    a.cser = v.cser;
+    a.K = (uint32_t)v.K;
+    a.n = v.n;
+    a.seg = seg;
+    a.nseg = (uint32_t)nseg;
+    a.pitch = pitch;
+    a.plane = plane;
+    const dim3 grid((unsigned)v.m, (unsigned)std::min<int64_t>(nseg, 65535));
+    const size_t lds = ((size_t)seg * sizeof(CodeT) + 15) & ~(size_t)15;
+    const ColT* colI = static_cast<const ColT*>(v.colI);
+    // short rows: one wave per row, four times as many workgroups in flight
+    if (v.n <= 1024) return launch_kernel(decode_kernel<ColT, CodeT, kPieces, 64>, grid, dim3(64), lds, s, colI, a, out);
+    return launch_kernel(decode_kernel<ColT, CodeT, kPieces, 256>, grid, dim3(256), lds, s, colI, a, out);
+}
+
+template <int kPieces>
+hipError_t launch_decode_any(const DeviceView& v, void* out, int64_t pitch, int64_t plane, hipStream_t s) {
+    const bool ranks = v.K <= kCodes;
+    switch (v.colI_bits) {
+        case 8: return ranks ? launch_decode<uint8_t, uint8_t, kPieces>(v, out, pitch, plane, s)
+                             : launch_decode<uint8_t, float, kPieces>(v, out, pitch, plane, s);
+        case 16: return ranks ? launch_decode<uint16_t, uint8_t, kPieces>(v, out, pitch, plane, s)
+                              : launch_decode<uint16_t, float, kPieces>(v, out, pitch, plane, s);
+        default: return ranks ? launch_decode<uint32_t, uint8_t, kPieces>(v, out, pitch, plane, s)
+                              : launch_decode<uint32_t, float, kPieces>(v, out, pitch, plane, s);
+    }
 }
 }  // namespace
 
 int decode_device(const DeviceView& v, float* W, void* stream) {
-    hipStream_t s = static_cast<hipStream_t>(stream);
     if (v.m == 0 || v.n == 0) return CER_OK;
-    switch (v.colI_bits) {
-        case 8: return launch_decode<uint8_t>(v, W, s);
-        case 16: return launch_decode<uint16_t>(v, W, s);
-        default: return launch_decode<uint32_t>(v, W, s);
+    if (v.m > 0x7FFFFFFFll) return CER_E_INVALID;
+    HIP_TRY(launch_decode_any<0>(v, W, v.n, 0, static_cast<hipStream_t>(stream)));
+    return CER_OK;
+}
+
+int decode_pieces(const DeviceView& v, uint16_t* W, int64_t pitch, int64_t plane, int pieces, void* stream) {
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    switch (pieces) {
+        case 1: return (int)launch_decode_any<1>(v, W, pitch, plane, s);
+        case 2: return (int)launch_decode_any<2>(v, W, pitch, plane, s);
+        default: return (int)launch_decode_any<3>(v, W, pitch, plane, s);
     }
 }
 
