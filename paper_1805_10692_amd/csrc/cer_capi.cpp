@@ -409,6 +409,23 @@ const DeviceProps& device_props(int dev) {
 }
 }  // namespace
 
+namespace {
+// bf16 numbers that add up to `x` exactly (csrc/cer_split3.hpp: the same split); 0 if one of them is subnormal.
+int value_pieces(float x) {
+    auto bits = [](float v) { uint32_t u; std::memcpy(&u, &v, 4); return u; };
+    auto value = [](uint32_t u) { float v; std::memcpy(&v, &u, 4); return v; };
+    int used = 0;
+    for (int i = 1; i <= 3 && x != 0.f; ++i) {
+        const uint32_t u = bits(x), mag = u & 0x7FFFFFFFu;
+        const uint32_t p = (mag >= 0x7F7F0000u ? u : u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u;  // nearest, ties to even
+        if ((p & 0x7F800000u) == 0) return 0;
+        x -= value(p);
+        used = i;
+    }
+    return x == 0.f ? std::max(used, 1) : 0;
+}
+}  // namespace
+
 void cer::bind_device(cer_matrix* h, int dev, void* base, const DeviceLayout& l) {
     const HostMatrix& A = *h->host;
     auto* b = static_cast<unsigned char*>(base);
@@ -436,6 +453,11 @@ void cer::bind_device(cer_matrix* h, int dev, void* base, const DeviceLayout& l)
     v.nnz = A.nnz;
     v.nonempty_groups = A.nonempty_groups;
     v.omega0 = A.K > 0 ? A.omega[0] : 0.f;
+    v.pieces = A.K > 0 ? 1 : 0;
+    for (float w : A.omega) {
+        const int p = value_pieces(w);
+        v.pieces = p && v.pieces ? std::max(v.pieces, p) : 0;
+    }
     const DeviceProps& dp = device_props(dev);
     v.cus = dp.cus;
     v.lds_per_block = dp.lds_per_block;

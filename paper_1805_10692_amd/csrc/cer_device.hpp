@@ -398,6 +398,12 @@ XtilePlan plan_xtile(const DeviceView& d, uint32_t L);
 hipError_t launch_xtile_any(const DeviceView& d, const XtilePlan& p, const float* X, float* Y, const float* T, uint32_t L,
                             hipStream_t stream);
 
+// cer_mfma.hip -- batch > 1, decoded into bf16 pieces and multiplied on the matrix cores.  mfma_applicable: the codebook and
+// the sizes allow it; mfma_estimate_us: the product without the decode.
+bool mfma_applicable(const DeviceView& d, uint32_t L);
+double mfma_estimate_us(const DeviceView& d, uint32_t L);
+hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream);
+
 // cer_strip.hip -- batch > 1, strips of X resident in LDS (needs the strip-major index of cer_prepare_strips)
 bool strip_applicable(const DeviceView& d, const float* X, const float* Y, uint32_t L);
 struct StripPlan {

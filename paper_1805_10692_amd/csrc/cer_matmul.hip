@@ -93,43 +93,44 @@ hipError_t launch_colsum(const float* X, uint32_t n, uint32_t L, float* part, ui
 }
 
 // Large batches of a matrix that is not sparse enough: the gathers move nnz.4.batch bytes through the L1/L2 path
-// (measured 18 - 31 TB/s chip-wide, 24 taken here), the fp32 matrix cores need 2.m.n.batch flops (the dense kernel
-// of this library: 12 - 20 us + flops / 90 ... 120 TFLOP/s, rising with the size), so from about one indexed
-// element in five upwards the dense contraction is the faster way to the same Y.  The matrix is then decoded into a
-// stream-ordered temporary (4.m.n bytes, bounded here; written at about 4.5 TB/s) and multiplied on the matrix
-// cores.  Measured on MI355X, gathers against decode + dense: 3x3 convolution shape (60 % zeros) batch 3136
-// 391 / 201 us, batch 784 165 / 75 us, batch 256 44 / 45 us; AlexNet-fc6 shape (85 %) batch 2048 1917 / 1466 us,
-// batch 512 419 / 421 us; VGG-fc6 shape (95 %) batch 1024 1187 / 2017 us; 2048 x 2048, batch 1024: 70 % zeros
-// 187 / 119 us, 80 % 139 / 119 us, 90 % 89 / 118 us.
-// Narrow batches of a dense-ish matrix take the same route: a gather moves a whole 128-byte line however narrow the
-// batch, so a 4096 x 9216 layer quantized to 7 bits (71 % of the elements indexed) costs 171 us at batch 32 by
-// gathers, 70 us decoded (30 us) and multiplied by the dense kernel (40 us, itself bound by reading the matrix).
+// (measured 18 - 31 TB/s chip-wide, 24 taken here), the matrix cores need 2.m.n.batch flops however many elements are
+// indexed.  The matrix is then decoded into a stream-ordered temporary (bounded here) and multiplied on the matrix cores:
+// as bf16 pieces (cer_mfma.hip: 2 to 6 bytes per element written, three to six products at about 1000 TFLOP/s), or, where
+// the values or the sizes rule that out, as fp32 (4 bytes per element; 90 - 120 TFLOP/s).  Measured on MI355X, gathers against
+// decode + product: 3x3 convolution shape (60 % zeros) batch 3136 391 / 64 us (fp32: 149 us); 7-bit quantizer of the same shape
+// 550 / 112 us.
 // Estimated durations (seconds) of the gathers and of decode + dense; false where the dense route is not available.
 bool densify_estimates(const DeviceView& d, uint32_t L, double* t_gather_out, double* t_dense_out) {
     if (L < 2 || d.m < 128 || d.n < 256) return false;
     const double mn = (double)d.m * (double)d.n;
-    if (mn * 4.0 > (double)(1ull << 30)) return false;
+    if ((double)d.nnz * 10.0 < mn) return false;  // far below one indexed element in five
+    const bool pieces = mfma_applicable(d, L);
+    if (mn * (pieces ? 2.0 * d.pieces : 4.0) > (double)(1ull << 30)) return false;
     const double flops = 2.0 * mn * L;
     // every (row, tile) is a wave whose start-up chain (descriptor -> pointers -> indices -> first gathers) takes about
     // 4 us, 4096 of them in flight: what bounds matrices of many short rows (16384 x 512: batch 128 64 - 84 us,
     // batch 512 160 - 440 us by gathers; 44 - 49 us and 94 - 103 us decoded and multiplied)
     const double tiles = std::ceil((double)L / 32.0);
-    const double t_gather = std::max((double)d.nnz * std::max(4.0 * L, 128.0) / 24e12, (double)d.m * tiles * 4e-6 / 4096.0);
-    const double rate = flops < 1.5e10 ? 90e12 : (flops < 1e11 ? 105e12 : 120e12);
-    const double t_write = 4.0 * mn / 4.5e12;  // the decoded matrix goes to memory once and is read back at least once
-    const double t_decode = t_write + (double)d.nnz * 1.5e-12 + 3e-6;  // measured 30 us (5.7 M indices) ... 88 us (28.7 M)
-    const double t_dense = (flops < 5e9 ? 20e-6 : 12e-6) + std::max(flops / rate, t_write) + t_decode;
+    // rows of X that do not start on a 128-byte line: a 32-column tile touches two of them (measured: a third more time)
+    const double ragged = L % 32u == 0 || (L < 32u && 32u % L == 0) ? 1.0 : 1.35;
+    const double t_gather = std::max((double)d.nnz * std::max(4.0 * L, 128.0) * ragged / 24e12, (double)d.m * tiles * 4e-6 / 4096.0);
+    double t_dense;
+    if (pieces) {
+        // the decoder: 10 us (conv shape), 22 us (4096 x 9216, one piece, 5.7 M indices), 80 us (three pieces, 28 M)
+        t_dense = mfma_estimate_us(d, L) * 1e-6 + 4e-6 + mn * 2.0 * d.pieces / 4e12 + (double)d.nnz * 0.7e-12;
+    } else {
+        const double rate = flops < 1.5e10 ? 90e12 : (flops < 1e11 ? 105e12 : 120e12);
+        const double t_write = 4.0 * mn / 4.5e12;  // the decoded matrix goes to memory once and is read back at least once
+        const double t_decode = t_write + (double)d.nnz * 0.7e-12 + 3e-6;
+        t_dense = (flops < 5e9 ? 20e-6 : 12e-6) + std::max(flops / rate, t_write) + t_decode;
+    }
     *t_gather_out = t_gather;
     *t_dense_out = t_dense;
     return true;
 }
 
-bool densify_pays(const DeviceView& d, uint32_t L) {
-    double t_gather = 0, t_dense = 0;
-    return densify_estimates(d, L, &t_gather, &t_dense) && t_gather > 1.1 * t_dense;
-}
-
 hipError_t launch_densified(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream) {
+    if (mfma_applicable(d, L)) return launch_mfma(d, X, Y, L, stream);
     float* W = nullptr;
     hipError_t e = (hipError_t)temp_alloc(reinterpret_cast<void**>(&W), (size_t)d.m * (size_t)d.n * sizeof(float), stream);
     if (e != hipSuccess) return e;

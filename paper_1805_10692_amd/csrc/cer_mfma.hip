@@ -1,0 +1,271 @@
+// Decode + matrix-core product: Y = W.X with the decoded matrix as bf16 pieces (cer_split3.hpp) and X split into its three
+// pieces on the way into LDS.
+//
+// Workgroup of four waves, one above the other: 256 rows x BN columns of Y, each wave 64 rows, k steps of BK = 2048 / BN.
+// W's pieces go from memory straight into the registers of the wave that owns the rows: the decoder has left them in operand
+// order, a tile of 32 rows x 16 columns in 1 KiB (row-major pieces cost four times as many cache lines per load and ran at 40 %
+// of this speed).  X is loaded as fp32, eight rows of one column per thread, split, and stored to LDS as
+// [piece][k / 8][column][8], so that both the stores and the operand reads are 16 bytes per lane at consecutive addresses.
+// X is loaded D - 1 steps ahead, W one step, and the LDS stores go one step ahead into the other buffer: one barrier per step,
+// no branch in between (rows of X behind the last one read as zeros: buffer loads with bounds).
+// Per wave and 16 k: 3 . 2 . TN matrix instructions of 32 cycles (one-piece codebook) against TN . 3 KiB out of LDS for all four
+// waves and 2 KiB out of L1: about half of what LDS and L1 deliver, two thirds of the matrix cores' time for the splitting.
+#include "cer_device.hpp"
+#include "cer_split3.hpp"
+
+namespace cer {
+namespace {
+
+constexpr uint32_t kFlush = 256;
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+
+// A buffer descriptor over `bytes` bytes: loads beyond them return zero.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+
+template <int PW, int TN, int D>
+struct MfmaTile {
+    static constexpr int TM = 2, BM = 256, BN = 32 * TN, BK = 2048 / BN, KG = BK / 8, KS = BK / 16;
+    uint4 b[2][3][KG][BN];
+
+    // sum: what is finished; acc: the sum over the current kFlush columns or so (a running sum of thousands of terms would
+    // round each of them to the size of the whole).  Returns a NaN if kAny is needed.
+    template <bool kAny>
+    __device__ __forceinline__ float run(const uint16_t* const (&wtile)[TM], size_t plane, const float* X, uint32_t n, uint32_t L,
+                                         uint32_t xcol, uint32_t k_begin, uint32_t k_end, floatx16 (&sum)[TM][TN]) {
+        const uint32_t tid = threadIdx.x, lane = tid & 63u;
+        const uint32_t xc = tid % BN, xg = tid / BN;  // this thread's share of X: rows 8 xg .. 8 xg + 7 of a step, one column
+        const __amdgpu_buffer_rsrc_t xbuf = buffer_of(X, n * L * 4u);
+        const uint32_t xoff = (8u * xg * L + xcol) * 4u, pitch4 = L * 4u;
+        float xr[D][8];
+        uint4 a[2][KS][TM][PW];
+        float odd = 0.f;
+        auto load_x = [&](uint32_t k0, int slot) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                xr[slot][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff, (k0 + i) * pitch4, 0));
+        };
+        auto load_w = [&](uint32_t k0, int slot) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int p = 0; p < PW; ++p)
+                        a[slot][s][i][p] = reinterpret_cast<const uint4*>(wtile[i] + p * plane + (size_t)(k0 + 16 * s) * 32)[lane];
+        };
+        auto store_x = [&](int slot, int buf) {
+            uint4 o[3];
+            odd += split3_8<kAny>(xr[slot], o);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) b[buf][p][xg][xc] = o[p];
+        };
+        floatx16 acc[TM][TN];
+        auto clear = [](floatx16 (&v)[TM][TN]) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) v[i][j][e] = 0.f;
+        };
+        clear(acc);
+        clear(sum);
+#pragma unroll
+        for (int s = 0; s + 1 < D; ++s) load_x(k_begin + s * BK, s);
+        load_w(k_begin, 0);
+        store_x(0, 0);
+        __syncthreads();
+        // D steps per round, so that the register slots are named at compile time; k_end - k_begin is a multiple of D BK
+        uint32_t held = 0;
+        for (uint32_t k0 = k_begin; k0 < k_end; k0 += D * BK) {
+#pragma unroll
+            for (int t = 0; t < D; ++t) {
+                // behind the end: the last step's once more
+                load_x(min(k0 + (t + D - 1) * BK, k_end - BK), (t + D - 1) % D);
+                load_w(min(k0 + (t + 1) * BK, k_end - BK), (t + 1) & 1);
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    uint4 bb[TN][3];
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) bb[j][p] = b[t & 1][p][2 * s + (lane >> 5)][j * 32 + (lane & 31u)];
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_pieces<PW>(a[t & 1][s][i], bb[j], acc[i][j]);
+                }
+                store_x((t + 1) % D, (t + 1) & 1);
+                __syncthreads();
+            }
+            held += D * BK;
+            if (held >= kFlush) {
+                held = 0;
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) sum[i][j] += acc[i][j];
+                clear(acc);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) sum[i][j] += acc[i][j];
+        return odd;
+    }
+};
+
+// D: steps in flight.
+template <int PW, int TN, int D>
+__global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
+    const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
+    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, size_t split_stride) {
+    using Tile = MfmaTile<PW, TN, D>;
+    __shared__ Tile tile;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Workgroups are dealt round-robin to the eight XCDs; every XCD takes a contiguous eighth of the list of work items, in
+    // which those that share columns of X (or, with few column tiles, rows of W) are neighbours: they meet in its L2.
+    const uint32_t items = row_tiles * col_tiles * splits, eighth = (items + 7u) >> 3;
+    const uint32_t item = (blockIdx.x & 7u) * eighth + (blockIdx.x >> 3);
+    if ((blockIdx.x >> 3) >= eighth || item >= items) return;
+    uint32_t rt, ct, sp;
+    if (row_tiles <= col_tiles) {
+        rt = item % row_tiles;
+        sp = (item / row_tiles) % splits;
+        ct = item / row_tiles / splits;
+    } else {
+        ct = item % col_tiles;
+        sp = (item / col_tiles) % splits;
+        rt = item / col_tiles / splits;
+    }
+    const uint32_t row0 = rt * Tile::BM + wave * 64u, col0 = ct * Tile::BN;
+    const uint32_t k_begin = sp * kchunk, k_end = min(pitch, k_begin + kchunk);
+    Out += sp * split_stride;
+    const uint16_t* wtile[Tile::TM];
+#pragma unroll
+    for (int i = 0; i < Tile::TM; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * 32 * pitch;
+    const uint32_t xcol = min(col0 + tid % Tile::BN, L - 1u);
+    floatx16 sum[Tile::TM][TN];
+    const float odd = tile.template run<false>(wtile, plane, X, n, L, xcol, k_begin, k_end, sum);
+    if (__syncthreads_or(odd != odd)) (void)tile.template run<true>(wtile, plane, X, n, L, xcol, k_begin, k_end, sum);
+
+    // accumulator element e of lane l: row = 8 (e / 4) + 4 (l / 32) + e % 4, column = l % 32
+#pragma unroll
+    for (int i = 0; i < Tile::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const uint32_t c = col0 + j * 32 + (lane & 31u);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const uint32_t r = row0 + 32 * i + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4);
+                if (r < m && c < L) Out[(size_t)r * L + c] = sum[i][j][e];
+            }
+        }
+}
+
+__global__ __launch_bounds__(256) void mfma_sum_kernel(const float* __restrict__ part, float* __restrict__ Y, size_t count,
+                                                       uint32_t splits) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= count) return;
+    float a = 0.f, b = 0.f;
+    uint32_t s = 0;
+    for (; s + 1 < splits; s += 2) {
+        a += part[(size_t)s * count + i];
+        b += part[(size_t)(s + 1) * count + i];
+    }
+    if (s < splits) a += part[(size_t)s * count + i];
+    Y[i] = a + b;
+}
+
+constexpr uint32_t kPitchStep = 128;  // W's rows are padded to a multiple of this many columns: a round of every variant
+
+// Steps in flight: as many as the registers allow next to TM x TN tiles of sums.
+constexpr int mfma_depth(int pieces, uint32_t BN) { return pieces == 1 && BN == 64 ? 4 : 2; }
+
+struct MfmaShape {
+    uint32_t BM, BN, row_tiles, col_tiles, splits, kchunk;
+    double us;  // estimate of the product (without the decode)
+};
+
+// The launch lasts as long as the busiest compute unit: its share of the workgroups, one after the other (two resident ones
+// overlap, but share the matrix cores).  Measured per unit: 4.1 - 4.7 TFLOP/s with BN = 64, bound by the operands' bytes with
+// BN = 32.  A split along n costs its partial sums, written and read again.
+MfmaShape mfma_shape(const DeviceView& d, uint32_t L) {
+    MfmaShape s;
+    s.BN = L <= 32 ? 32 : 64;
+    s.BM = 256;
+    s.row_tiles = (uint32_t)((d.m + s.BM - 1) / s.BM);
+    s.col_tiles = (L + s.BN - 1) / s.BN;
+    const uint32_t round = mfma_depth(d.pieces, s.BN) * 2048 / s.BN;  // columns per round of the kernel
+    const uint32_t pitch = ((uint32_t)d.n + kPitchStep - 1) / kPitchStep * kPitchStep, rounds = (pitch + round - 1) / round;
+    const double tiles = (double)s.row_tiles * s.col_tiles, units = std::max(d.cus, 1);
+    const double products = d.pieces == 1 ? 3 : (d.pieces == 2 ? 5 : 6);
+    const double flops = 2.0 * s.BM * s.BN * round * products, bytes = (double)round * (s.BM * 2.0 * d.pieces + s.BN * 4.0);
+    const double round_us = std::max(flops / 4.3e6, bytes / 3.0e4);
+    double best = 1e300;
+    const uint32_t most = (uint32_t)std::min<double>(std::max(1u, rounds / 4), std::max(1.0, 4.0 * units / tiles));
+    for (uint32_t sp = 1; sp <= std::min(most, 64u); ++sp) {
+        const uint32_t per = (rounds + sp - 1) / sp, used = (rounds + per - 1) / per;
+        double us = std::ceil(tiles * used / units) * per * round_us + 4.0;
+        if (used > 1) us += 3.0 + (double)used * d.m * L * 8.0 / 6.5e6;
+        if (us < best) {
+            best = us;
+            s.splits = used;
+            s.kchunk = per * round;
+            s.us = us;
+        }
+    }
+    return s;
+}
+
+template <int PW>
+hipError_t launch_shape(const MfmaShape& s, const uint16_t* W, const float* X, float* out, uint32_t m, uint32_t n, uint32_t L,
+                        uint32_t pitch, size_t plane, hipStream_t stream) {
+    const dim3 grid((s.row_tiles * s.col_tiles * s.splits + 7) / 8 * 8);
+    const size_t count = (size_t)m * L;
+    if (s.BN == 32)
+        return launch_kernel(mfma_product_kernel<PW, 1, mfma_depth(PW, 32)>, grid, dim3(256), 0, stream, W, X, out, m, n, L, pitch, plane,
+                             s.row_tiles, s.col_tiles, s.splits, s.kchunk, count);
+    return launch_kernel(mfma_product_kernel<PW, 2, mfma_depth(PW, 64)>, grid, dim3(256), 0, stream, W, X, out, m, n, L, pitch, plane,
+                         s.row_tiles, s.col_tiles, s.splits, s.kchunk, count);
+}
+
+}  // namespace
+
+// Whether the codebook and the sizes allow the route at all, and its estimated duration without the decode.
+bool mfma_applicable(const DeviceView& d, uint32_t L) {
+    return d.pieces > 0 && d.m > 0 && d.n > 0 && L > 1 && d.n < (1ll << 31) && d.m < (1ll << 31) && (uint64_t)d.m * L < (1ull << 40) &&
+           ((uint64_t)d.n + kPitchStep) * L * 4u < (1ull << 32);  // X is addressed with 32-bit offsets
+}
+double mfma_estimate_us(const DeviceView& d, uint32_t L) { return mfma_shape(d, L).us; }
+
+hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream) {
+    const MfmaShape s = mfma_shape(d, L);
+    const int64_t pitch = (d.n + kPitchStep - 1) / kPitchStep * kPitchStep, plane = pitch * ((d.m + 31) / 32 * 32);
+    const size_t count = (size_t)d.m * L;
+    // one temporary: the partial sums, then the pieces
+    const size_t part_bytes = s.splits > 1 ? (count * s.splits * 4 + 255) & ~(size_t)255 : 0;
+    unsigned char* tmp = nullptr;
+    hipError_t e = (hipError_t)temp_alloc(reinterpret_cast<void**>(&tmp), part_bytes + (size_t)plane * 2 * d.pieces, stream);
+    if (e != hipSuccess) return e;
+    auto* W = reinterpret_cast<uint16_t*>(tmp + part_bytes);
+    float* out = s.splits > 1 ? reinterpret_cast<float*>(tmp) : Y;
+    e = (hipError_t)decode_pieces(d, W, pitch, plane, stream);
+    if (e == hipSuccess) {
+        const uint32_t m = (uint32_t)d.m, n = (uint32_t)d.n;
+        switch (d.pieces) {
+            case 1: e = launch_shape<1>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, stream); break;
+            case 2: e = launch_shape<2>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, stream); break;
+            default: e = launch_shape<3>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, stream);
+        }
+    }
+    if (e == hipSuccess && s.splits > 1)
+        e = launch_kernel(mfma_sum_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, stream, out, Y, count, s.splits);
+    const hipError_t f = (hipError_t)temp_free(tmp, stream);
+    return e == hipSuccess ? f : e;
+}
+
+}  // namespace cer

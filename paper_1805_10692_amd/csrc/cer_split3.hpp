@@ -48,29 +48,30 @@ __device__ __forceinline__ void split3_any(float x, uint32_t p[3]) {
     p[2] = bf16_pair(r - __uint_as_float(p[1] << 16), 0.f) & 0xFFFFu;
 }
 
-// Eight numbers -> three times eight bf16, in the order given.
-__device__ __forceinline__ void split3_8(const float x[8], uint4 out[3]) {
+// Eight numbers -> three times eight bf16, in the order given.  kAny: any numbers; else the return value is a NaN unless all
+// of them are finite and round to finite bf16 numbers.
+template <bool kAny>
+__device__ __forceinline__ float split3_8(const float x[8], uint4 out[3]) {
     uint32_t w[3][4];
     float odd = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        uint32_t p[3];
-        odd += split3_pair(x[2 * i], x[2 * i + 1], p);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) w[j][i] = p[j];
-    }
-    if (__ballot(odd != odd)) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        if constexpr (kAny) {
             uint32_t a[3], b[3];
             split3_any(x[2 * i], a);
             split3_any(x[2 * i + 1], b);
 #pragma unroll
             for (int j = 0; j < 3; ++j) w[j][i] = a[j] | (b[j] << 16);
+        } else {
+            uint32_t p[3];
+            odd += split3_pair(x[2 * i], x[2 * i + 1], p);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) w[j][i] = p[j];
         }
     }
 #pragma unroll
     for (int j = 0; j < 3; ++j) out[j] = make_uint4(w[j][0], w[j][1], w[j][2], w[j][3]);
+    return odd;
 }
 
 __device__ __forceinline__ floatx16 mfma_bf16(uint4 a, uint4 b, floatx16 c) {

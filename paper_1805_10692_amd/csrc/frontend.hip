@@ -773,8 +773,6 @@ struct DecodeArgs {
     uint32_t K;
     int64_t n;
     uint32_t seg, nseg;  // columns per segment: a multiple of 8
-    int64_t pitch;       // output: elements per row (bf16: a multiple of 8, columns n .. pitch - 1 are written as zeros)
-    int64_t plane;       // bf16: elements from one piece's matrix to the next one's
 };
 
 __device__ __forceinline__ void load_eight(const uint8_t* p, uint32_t v[8]) {
@@ -795,24 +793,19 @@ __device__ __forceinline__ void load_eight(const uint32_t* p, uint32_t v[8]) {
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
-// CodeT: uint8_t (rank) or float (value).  kPieces: 0 = fp32 output, 1 .. 3 = that many bf16 matrices.
-template <typename ColT, typename CodeT, int kPieces, uint32_t kThreads>
-__global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict__ colI, DecodeArgs a, void* __restrict__ out) {
-    constexpr bool kRanks = sizeof(CodeT) == 1;
-    constexpr uint32_t T = kThreads;
-    extern __shared__ __align__(16) unsigned char s_seg[];  // seg codes
-    __shared__ uint32_t s_ptr[T + 1];
-    __shared__ CodeT s_grp[T];
-    __shared__ uint32_t s_val[kRanks ? kCodes : 1];        // fp32 value, or pieces 0 | 1 << 16, by rank
-    __shared__ uint32_t s_val2[kRanks && kPieces == 3 ? kCodes : 1];
-    CodeT* code = reinterpret_cast<CodeT*>(s_seg);
-    const uint32_t tid = threadIdx.x;
-    const int64_t r = blockIdx.x;
-    const uint32_t g0 = a.rowPtr[r], g1 = a.rowPtr[r + 1];
-    const uint32_t cnt0 = min(g1 - g0, T);
-
-    // pointers and ranks (values) of the groups gb .. gb + cnt - 1 of this row -> LDS
-    auto stage_groups = [&](uint32_t gb, uint32_t cnt) {
+// Ranks (CodeT = uint8_t) or values (float) of columns c0 .. c0 + len - 1 of row r -> code, by T threads: a workgroup, or
+// (kWave) one wave of it with its own LDS.  Only indexed elements are written.
+template <bool kWave>
+__device__ __forceinline__ void team_sync() {
+    if constexpr (kWave) wave_lds_sync(); else __syncthreads();
+}
+template <typename ColT, typename CodeT, uint32_t T, bool kWave>
+__device__ __forceinline__ void scatter_row(const ColT* __restrict__ colI, const DecodeArgs& a, uint32_t g0, uint32_t g1, uint32_t tid,
+                                            int64_t c0, uint32_t len, uint32_t* s_ptr /* T + 1 */, CodeT* s_grp /* T */, CodeT* code) {
+    for (uint32_t gb = g0; gb < g1; gb += T) {
+        // pointers and ranks (values) of the groups gb .. gb + cnt - 1 of this row -> LDS
+        const uint32_t cnt = min(g1 - gb, T);
+        team_sync<kWave>();
         if (tid < cnt) {
             const uint32_t g = gb + tid;
             uint32_t rank = g - g0 + 1u;  // Algorithm 3: position in the row; Algorithm 4: OmegaI
@@ -822,122 +815,153 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict
                                                          : reinterpret_cast<const uint32_t*>(a.omegaI)[g]);
             }
             s_ptr[tid] = a.omegaPtr[g];
-            if constexpr (kRanks) s_grp[tid] = (uint8_t)rank; else s_grp[tid] = a.omega[rank];
+            if constexpr (sizeof(CodeT) == 1) s_grp[tid] = (uint8_t)rank; else s_grp[tid] = a.omega[rank];
         }
         if (tid == 0) s_ptr[cnt] = a.omegaPtr[gb + cnt];
-    };
-    if constexpr (kRanks) {
-        for (uint32_t k = tid; k < a.K; k += T) {
-            const float w = a.omega[k];
-            if constexpr (kPieces == 0) {
-                s_val[k] = __float_as_uint(w);
-            } else {
-                uint32_t p[3];
-                cer::split3_any(w, p);
-                s_val[k] = p[0] | (p[1] << 16);
-                if constexpr (kPieces == 3) s_val2[k] = p[2];
+        team_sync<kWave>();
+        const uint32_t pb = s_ptr[0], pe = s_ptr[cnt];
+        uint32_t lo = 0;
+        uint32_t v = (pb & ~7u) + tid * 8u;
+        uint32_t ahead[8];
+        if (v < pe) load_eight(colI + v, ahead);  // up to seven positions on either side belong to others
+        for (; v < pe; v += T * 8u) {
+            uint32_t col[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) col[i] = ahead[i];
+            if (v + T * 8u < pe) load_eight(colI + v + T * 8u, ahead);
+            const uint32_t first = max(v, pb);
+            uint32_t hi = cnt;  // s_ptr[lo] <= first < s_ptr[hi]
+            while (hi - lo > 1u) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (s_ptr[mid] <= first) lo = mid; else hi = mid;
+            }
+            uint32_t end = s_ptr[lo + 1u];
+            CodeT c = s_grp[lo];
+#pragma unroll
+            for (uint32_t i = 0; i < 8; ++i) {
+                const uint32_t p = v + i;
+                if (p >= pb && p < pe) {
+                    if (p >= end) {
+                        do end = s_ptr[++lo + 1u]; while (end <= p);
+                        c = s_grp[lo];
+                    }
+                    const uint64_t rel = (uint64_t)col[i] - (uint64_t)c0;  // huge when left of the segment
+                    if (rel < len) code[rel] = c;
+                }
             }
         }
     }
+}
+
+// fp32 output.
+template <typename ColT, typename CodeT, uint32_t kThreads>
+__global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict__ colI, DecodeArgs a, float* __restrict__ out) {
+    constexpr bool kRanks = sizeof(CodeT) == 1;
+    constexpr uint32_t T = kThreads;
+    extern __shared__ __align__(16) unsigned char s_seg[];  // seg codes
+    __shared__ uint32_t s_ptr[T + 1];
+    __shared__ CodeT s_grp[T];
+    __shared__ uint32_t s_val[kRanks ? kCodes : 1];  // fp32 value by rank
+    CodeT* code = reinterpret_cast<CodeT*>(s_seg);
+    const uint32_t tid = threadIdx.x;
+    const int64_t r = blockIdx.x;
+    const uint32_t g0 = a.rowPtr[r], g1 = a.rowPtr[r + 1];
+    if constexpr (kRanks)
+        for (uint32_t k = tid; k < a.K; k += T) s_val[k] = __float_as_uint(a.omega[k]);
     const float w0 = kRanks ? 0.f : a.omega[0];
-    if (cnt0) stage_groups(g0, cnt0);
 
     for (uint32_t si = blockIdx.y; si < a.nseg; si += gridDim.y) {  // uniform over the workgroup
         const int64_t c0 = (int64_t)si * a.seg;
-        if (c0 >= a.n) break;
         const uint32_t len = (uint32_t)min((int64_t)a.seg, a.n - c0);  // 1 .. seg
         if constexpr (kRanks) {
             for (uint32_t j = tid; j < (len + 15u) / 16u; j += T) reinterpret_cast<uint4*>(s_seg)[j] = make_uint4(0, 0, 0, 0);
         } else {
             for (uint32_t j = tid; j < (len + 3u) / 4u; j += T) reinterpret_cast<float4*>(s_seg)[j] = make_float4(w0, w0, w0, w0);
         }
+        scatter_row<ColT, CodeT, T, false>(colI, a, g0, g1, tid, c0, len, s_ptr, s_grp, code);
         __syncthreads();
-        for (uint32_t gb = g0; gb < g1; gb += T) {
-            const uint32_t cnt = min(g1 - gb, T);
-            if (g1 - g0 > T) {  // not staged once and for all
-                __syncthreads();
-                stage_groups(gb, cnt);
-                __syncthreads();
+        float* o = out + r * a.n + c0;
+        const uint32_t n4 = (reinterpret_cast<uintptr_t>(o) & 15u) == 0 ? len >> 2 : 0u;
+        if constexpr (kRanks) {
+            for (uint32_t j = tid; j < n4; j += T) {
+                const uint32_t q = reinterpret_cast<const uint32_t*>(s_seg)[j];
+                reinterpret_cast<uint4*>(o)[j] = make_uint4(s_val[q & 0xFFu], s_val[(q >> 8) & 0xFFu], s_val[(q >> 16) & 0xFFu], s_val[q >> 24]);
             }
-            const uint32_t pb = s_ptr[0], pe = s_ptr[cnt];
-            uint32_t lo = 0;
-            uint32_t v = (pb & ~7u) + tid * 8u;
-            uint32_t ahead[8];
-            if (v < pe) load_eight(colI + v, ahead);  // up to seven positions on either side belong to others
-            for (; v < pe; v += T * 8u) {
-                uint32_t col[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) col[i] = ahead[i];
-                if (v + T * 8u < pe) load_eight(colI + v + T * 8u, ahead);
-                const uint32_t first = max(v, pb);
-                uint32_t hi = cnt;  // s_ptr[lo] <= first < s_ptr[hi]
-                while (hi - lo > 1u) {
-                    const uint32_t mid = (lo + hi) >> 1;
-                    if (s_ptr[mid] <= first) lo = mid; else hi = mid;
-                }
-                uint32_t end = s_ptr[lo + 1u];
-                CodeT c = s_grp[lo];
-#pragma unroll
-                for (uint32_t i = 0; i < 8; ++i) {
-                    const uint32_t p = v + i;
-                    if (p >= pb && p < pe) {
-                        if (p >= end) {
-                            do end = s_ptr[++lo + 1u]; while (end <= p);
-                            c = s_grp[lo];
-                        }
-                        const uint64_t rel = (uint64_t)col[i] - (uint64_t)c0;  // huge when left of the segment
-                        if (rel < len) code[rel] = c;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        if constexpr (kPieces == 0) {
-            float* o = static_cast<float*>(out) + r * a.pitch + c0;
-            const bool wide = (reinterpret_cast<uintptr_t>(o) & 15u) == 0;
-            if constexpr (kRanks) {
-                const uint32_t n4 = wide ? len >> 2 : 0u;
-                for (uint32_t j = tid; j < n4; j += T) {
-                    const uint32_t q = reinterpret_cast<const uint32_t*>(s_seg)[j];
-                    reinterpret_cast<uint4*>(o)[j] = make_uint4(s_val[q & 0xFFu], s_val[(q >> 8) & 0xFFu], s_val[(q >> 16) & 0xFFu], s_val[q >> 24]);
-                }
-                for (uint32_t j = (n4 << 2) + tid; j < len; j += T) o[j] = __uint_as_float(s_val[code[j]]);
-            } else {
-                const uint32_t n4 = wide ? len >> 2 : 0u;
-                for (uint32_t j = tid; j < n4; j += T) reinterpret_cast<float4*>(o)[j] = reinterpret_cast<const float4*>(s_seg)[j];
-                for (uint32_t j = (n4 << 2) + tid; j < len; j += T) o[j] = (float)code[j];
-            }
+            for (uint32_t j = (n4 << 2) + tid; j < len; j += T) o[j] = __uint_as_float(s_val[code[j]]);
         } else {
-            // eight columns per thread and step; the last segment also writes the zeros up to the pitch
-            uint16_t* o = static_cast<uint16_t*>(out) + r * a.pitch + c0;
-            const uint32_t wlen = c0 + a.seg >= a.n ? (uint32_t)(a.pitch - c0) : a.seg;
-            for (uint32_t j = tid * 8u; j < wlen; j += T * 8u) {
-                uint32_t w[3][4] = {};
-#pragma unroll
-                for (uint32_t i = 0; i < 8; ++i) {
-                    uint32_t p01 = 0, p2 = 0;
-                    if (j + i < len) {
-                        if constexpr (kRanks) {
-                            p01 = s_val[code[j + i]];
-                            if constexpr (kPieces == 3) p2 = s_val2[code[j + i]];
-                        } else {
-                            uint32_t p[3];
-                            cer::split3_any((float)code[j + i], p);
-                            p01 = p[0] | (p[1] << 16);
-                            p2 = p[2];
-                        }
-                    }
-                    const uint32_t sh = 16u * (i & 1u);
-                    w[0][i >> 1] |= (p01 & 0xFFFFu) << sh;
-                    w[1][i >> 1] |= (p01 >> 16) << sh;
-                    w[2][i >> 1] |= p2 << sh;
-                }
-#pragma unroll
-                for (int q = 0; q < kPieces; ++q)
-                    *reinterpret_cast<uint4*>(o + q * a.plane + j) = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
-            }
+            for (uint32_t j = tid; j < n4; j += T) reinterpret_cast<float4*>(o)[j] = reinterpret_cast<const float4*>(s_seg)[j];
+            for (uint32_t j = (n4 << 2) + tid; j < len; j += T) o[j] = (float)code[j];
         }
         __syncthreads();  // the segment has been read before the next one is filled
+    }
+}
+
+// bf16 pieces in the operand order of v_mfma_f32_32x32x16_bf16: tiles of 32 rows x 16 columns, 1 KiB each, [row / 32]
+// [column / 16][column / 8 % 2][row % 32][column % 8], rows padded with zeros to a multiple of 16 columns (pitch).  Eight
+// rows per workgroup, one wave each, so that a store of the workgroup covers whole 128-byte lines.
+template <typename ColT, typename CodeT, int kPieces>
+__global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restrict__ colI, DecodeArgs a, int64_t m, int64_t pitch,
+                                                           int64_t plane, uint16_t* __restrict__ out) {
+    constexpr bool kRanks = sizeof(CodeT) == 1;
+    extern __shared__ __align__(16) unsigned char s_seg[];  // eight rows of seg + 8 codes
+    __shared__ uint32_t s_ptr[8][kWave + 1];
+    __shared__ CodeT s_grp[8][kWave];
+    __shared__ uint32_t s_val[kRanks ? kCodes : 1];  // pieces 0 | 1 << 16, by rank
+    __shared__ uint32_t s_val2[kRanks && kPieces == 3 ? kCodes : 1];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const int64_t row0 = (int64_t)blockIdx.x * 8, r = row0 + wave;
+    const int64_t c0 = (int64_t)blockIdx.y * a.seg;
+    const uint32_t len = (uint32_t)min((int64_t)a.seg, a.n - c0);
+    const uint32_t stride = a.seg + 8u;
+    CodeT* code = reinterpret_cast<CodeT*>(s_seg);
+    if constexpr (kRanks) {
+        for (uint32_t k = tid; k < a.K; k += 512u) {
+            uint32_t p[3];
+            cer::split3_any(a.omega[k], p);
+            s_val[k] = p[0] | (p[1] << 16);
+            if constexpr (kPieces == 3) s_val2[k] = p[2];
+        }
+    }
+    {
+        const float w0 = kRanks ? 0.f : a.omega[0];
+        CodeT* mine = code + wave * stride;
+        for (uint32_t j = lane * (8u / sizeof(CodeT)); j < len; j += kWave * (8u / sizeof(CodeT))) {
+            if constexpr (kRanks) *reinterpret_cast<uint2*>(mine + j) = make_uint2(0, 0);
+            else *reinterpret_cast<float2*>(mine + j) = make_float2(w0, w0);
+        }
+        if (r < m) scatter_row<ColT, CodeT, kWave, true>(colI, a, a.rowPtr[r], a.rowPtr[r + 1], lane, c0, len, s_ptr[wave], s_grp[wave], mine);
+    }
+    __syncthreads();
+    const uint32_t wlen = c0 + a.seg >= a.n ? (uint32_t)(pitch - c0) : a.seg;  // the last segment also writes the padding
+    const uint32_t rr = tid & 7u;
+    if (row0 + rr >= m) return;
+    uint16_t* o = out + (row0 >> 5) * 32 * pitch + ((row0 & 31) + rr) * 8;
+    const CodeT* mine = code + rr * stride;
+    for (uint32_t j = (tid >> 3) * 8u; j < wlen; j += 512u) {
+        uint32_t w[3][4] = {};
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) {
+            uint32_t p01 = 0, p2 = 0;
+            if (j + i < len) {
+                if constexpr (kRanks) {
+                    p01 = s_val[mine[j + i]];
+                    if constexpr (kPieces == 3) p2 = s_val2[mine[j + i]];
+                } else {
+                    uint32_t p[3];
+                    cer::split3_any((float)mine[j + i], p);
+                    p01 = p[0] | (p[1] << 16);
+                    p2 = p[2];
+                }
+            }
+            const uint32_t sh = 16u * (i & 1u);
+            w[0][i >> 1] |= (p01 & 0xFFFFu) << sh;
+            w[1][i >> 1] |= (p01 >> 16) << sh;
+            w[2][i >> 1] |= p2 << sh;
+        }
+        const int64_t at = (c0 + j) * 32;  // (column / 8) . 32 rows . 8
+#pragma unroll
+        for (int q = 0; q < kPieces; ++q)
+            *reinterpret_cast<uint4*>(o + q * plane + at) = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
     }
 }
 
@@ -1082,15 +1106,7 @@ hipError_t launch_emit(hipStream_t s, const uint8_t* codes, const uint32_t* cnt,
 namespace cer {
 
 namespace {
-template <typename ColT, typename CodeT, int kPieces>
-hipError_t launch_decode(const DeviceView& v, void* out, int64_t pitch, int64_t plane, hipStream_t s) {
-    // Segments of equal length, at most 32 KiB of LDS; more of them where the rows alone give fewer than eight workgroups
-    // per compute unit, but not below 1024 columns (every segment reads the whole row's indices).
-    const int64_t most = 32768 / (int64_t)sizeof(CodeT);
-    int64_t nseg = std::max<int64_t>((v.n + most - 1) / most, std::min<int64_t>((2048 + v.m - 1) / v.m, v.n / 1024));
-    nseg = std::min<int64_t>(std::max<int64_t>(nseg, 1), 0x7FFFFFFF);
-    const uint32_t seg = (uint32_t)((((v.n + nseg - 1) / nseg) + 7) & ~(int64_t)7);
-    nseg = (v.n + seg - 1) / seg;
+DecodeArgs decode_args(const DeviceView& v, int64_t nseg, uint32_t multiple) {
     DecodeArgs a;
     a.omegaPtr = v.omegaPtr;
     a.rowPtr = v.rowPtr;
@@ -1100,28 +1116,39 @@ hipError_t launch_decode(const DeviceView& v, void* out, int64_t pitch, int64_t 
     a.cser = v.cser;
     a.K = (uint32_t)v.K;
     a.n = v.n;
-    a.seg = seg;
-    a.nseg = (uint32_t)nseg;
-    a.pitch = pitch;
-    a.plane = plane;
-    const dim3 grid((unsigned)v.m, (unsigned)std::min<int64_t>(nseg, 65535));
-    const size_t lds = ((size_t)seg * sizeof(CodeT) + 15) & ~(size_t)15;
-    const ColT* colI = static_cast<const ColT*>(v.colI);
-    // short rows: one wave per row, four times as many workgroups in flight
-    if (v.n <= 1024) return launch_kernel(decode_kernel<ColT, CodeT, kPieces, 64>, grid, dim3(64), lds, s, colI, a, out);
-    return launch_kernel(decode_kernel<ColT, CodeT, kPieces, 256>, grid, dim3(256), lds, s, colI, a, out);
+    nseg = std::min<int64_t>(std::max<int64_t>(nseg, 1), 65535);
+    a.seg = (uint32_t)(((v.n + nseg - 1) / nseg + multiple - 1) / multiple * multiple);
+    a.nseg = (uint32_t)((v.n + a.seg - 1) / a.seg);
+    return a;
 }
 
-template <int kPieces>
-hipError_t launch_decode_any(const DeviceView& v, void* out, int64_t pitch, int64_t plane, hipStream_t s) {
-    const bool ranks = v.K <= kCodes;
-    switch (v.colI_bits) {
-        case 8: return ranks ? launch_decode<uint8_t, uint8_t, kPieces>(v, out, pitch, plane, s)
-                             : launch_decode<uint8_t, float, kPieces>(v, out, pitch, plane, s);
-        case 16: return ranks ? launch_decode<uint16_t, uint8_t, kPieces>(v, out, pitch, plane, s)
-                              : launch_decode<uint16_t, float, kPieces>(v, out, pitch, plane, s);
-        default: return ranks ? launch_decode<uint32_t, uint8_t, kPieces>(v, out, pitch, plane, s)
-                              : launch_decode<uint32_t, float, kPieces>(v, out, pitch, plane, s);
+template <typename ColT, typename CodeT>
+hipError_t launch_decode(const DeviceView& v, float* out, hipStream_t s) {
+    // Segments of equal length, at most 32 KiB of LDS; more of them where the rows alone give fewer than eight workgroups
+    // per compute unit, but not below 1024 columns (every segment reads the whole row's indices).
+    const int64_t most = 32768 / (int64_t)sizeof(CodeT);
+    const DecodeArgs a = decode_args(v, std::max<int64_t>((v.n + most - 1) / most, std::min<int64_t>((2048 + v.m - 1) / v.m, v.n / 1024)), 8);
+    const dim3 grid((unsigned)v.m, a.nseg);
+    const size_t lds = ((size_t)a.seg * sizeof(CodeT) + 15) & ~(size_t)15;
+    const ColT* colI = static_cast<const ColT*>(v.colI);
+    // short rows: one wave per row, four times as many workgroups in flight
+    if (v.n <= 1024) return launch_kernel(decode_kernel<ColT, CodeT, 64>, grid, dim3(64), lds, s, colI, a, out);
+    return launch_kernel(decode_kernel<ColT, CodeT, 256>, grid, dim3(256), lds, s, colI, a, out);
+}
+
+template <typename ColT, typename CodeT>
+hipError_t launch_decode_tiles(const DeviceView& v, uint16_t* out, int64_t pitch, int64_t plane, hipStream_t s) {
+    // Segments of at most 64 KiB of LDS for eight rows; three workgroups for two compute units where segments of 512 columns
+    // or more allow it (every segment reads its rows' indices again).
+    const int64_t most = 8192 / (int64_t)sizeof(CodeT), groups = (v.m + 7) / 8;
+    const DecodeArgs a = decode_args(v, std::max<int64_t>((v.n + most - 1) / most, std::min<int64_t>((384 + groups - 1) / groups, v.n / 512)), 16);
+    const dim3 grid((unsigned)groups, a.nseg);
+    const size_t lds = (size_t)(a.seg + 8) * 8 * sizeof(CodeT);
+    const ColT* colI = static_cast<const ColT*>(v.colI);
+    switch (v.pieces) {
+        case 1: return launch_kernel(decode_tiles_kernel<ColT, CodeT, 1>, grid, dim3(512), lds, s, colI, a, v.m, pitch, plane, out);
+        case 2: return launch_kernel(decode_tiles_kernel<ColT, CodeT, 2>, grid, dim3(512), lds, s, colI, a, v.m, pitch, plane, out);
+        default: return launch_kernel(decode_tiles_kernel<ColT, CodeT, 3>, grid, dim3(512), lds, s, colI, a, v.m, pitch, plane, out);
     }
 }
 }  // namespace
@@ -1129,16 +1156,25 @@ hipError_t launch_decode_any(const DeviceView& v, void* out, int64_t pitch, int6
 int decode_device(const DeviceView& v, float* W, void* stream) {
     if (v.m == 0 || v.n == 0) return CER_OK;
     if (v.m > 0x7FFFFFFFll) return CER_E_INVALID;
-    HIP_TRY(launch_decode_any<0>(v, W, v.n, 0, static_cast<hipStream_t>(stream)));
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const bool ranks = v.K <= kCodes;
+    hipError_t e;
+    switch (v.colI_bits) {
+        case 8: e = ranks ? launch_decode<uint8_t, uint8_t>(v, W, s) : launch_decode<uint8_t, float>(v, W, s); break;
+        case 16: e = ranks ? launch_decode<uint16_t, uint8_t>(v, W, s) : launch_decode<uint16_t, float>(v, W, s); break;
+        default: e = ranks ? launch_decode<uint32_t, uint8_t>(v, W, s) : launch_decode<uint32_t, float>(v, W, s);
+    }
+    HIP_TRY(e);
     return CER_OK;
 }
 
-int decode_pieces(const DeviceView& v, uint16_t* W, int64_t pitch, int64_t plane, int pieces, void* stream) {
+int decode_pieces(const DeviceView& v, uint16_t* W, int64_t pitch, int64_t plane, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    switch (pieces) {
-        case 1: return (int)launch_decode_any<1>(v, W, pitch, plane, s);
-        case 2: return (int)launch_decode_any<2>(v, W, pitch, plane, s);
-        default: return (int)launch_decode_any<3>(v, W, pitch, plane, s);
+    const bool ranks = v.K <= kCodes;
+    switch (v.colI_bits) {
+        case 8: return (int)(ranks ? launch_decode_tiles<uint8_t, uint8_t>(v, W, pitch, plane, s) : launch_decode_tiles<uint8_t, float>(v, W, pitch, plane, s));
+        case 16: return (int)(ranks ? launch_decode_tiles<uint16_t, uint8_t>(v, W, pitch, plane, s) : launch_decode_tiles<uint16_t, float>(v, W, pitch, plane, s));
+        default: return (int)(ranks ? launch_decode_tiles<uint32_t, uint8_t>(v, W, pitch, plane, s) : launch_decode_tiles<uint32_t, float>(v, W, pitch, plane, s));
     }
 }
 

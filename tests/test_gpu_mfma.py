@@ -1,0 +1,54 @@
+"""Decode + matrix-core product over bf16 pieces (csrc/cer_mfma.hip): codebooks of one, two and three pieces at the edges of
+its tiles (256 rows, 32 or 64 columns, steps of 32 / 64 and rounds of 128 columns of W), against fp64 on the host."""
+import numpy as np
+import pytest
+
+from paper_1805_10692_amd import binding as B
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+CODEBOOKS = {  # significands of 8, 16 and 24 bits
+    "one": np.array([0.0, 1.0, -0.75, 3.0], np.float32),
+    "two": np.array([0.0, 1.0, -0.3330078125, 1.0009765625], np.float32),
+    "three": np.array([0.0, 1.0, -1.0 / 3.0, 0.1], np.float32),
+}
+
+
+def _product(W, cb, X, fmt="cer"):
+    h = (B.cer_encode if fmt == "cer" else B.cser_encode)(W, cb)
+    Xd = torch.from_numpy(X).cuda()
+    Y = torch.full((W.shape[0], X.shape[1]), float("nan"), device="cuda")
+    B.cer_matmul_ex(h, Xd, Y, X.shape[1], None, B.MatmulOpts(path=B.CER_PATH_DENSE))
+    torch.cuda.synchronize()
+    B.cer_free(h)
+    return Y.cpu().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("pieces", list(CODEBOOKS))
+@pytest.mark.parametrize("shape", [(1, 1, 2), (255, 127, 31), (256, 128, 32), (257, 129, 33), (31, 8200, 64), (513, 640, 65), (40, 300, 130)])
+def test_edges_of_the_tiles(shape, pieces):
+    m, n, L = shape
+    rng = np.random.default_rng(m + n)
+    cb = CODEBOOKS[pieces]
+    W = rng.choice(cb, size=(m, n), p=[0.4, 0.2, 0.2, 0.2]).astype(np.float32)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    Y = _product(W, cb, X, "cser" if m % 2 else "cer")
+    want = W.astype(np.float64) @ X.astype(np.float64)
+    # the bound of binary32 products and sums, with room for a few of the latter
+    assert (np.abs(Y - want) <= 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64))).all()
+
+
+def test_inputs_that_have_no_three_pieces():
+    """Infinities, NaNs and numbers that round to an infinite bf16: what fp32 gives."""
+    cb = np.array([1.0, 0.5], np.float32)
+    rng = np.random.default_rng(1)
+    W = rng.choice(cb, size=(64, 256)).astype(np.float32)
+    X = rng.standard_normal((256, 40)).astype(np.float32)
+    X[3, 5], X[7, 6], X[200, 7], X[255, 8] = np.inf, -np.inf, np.nan, 3.4e38
+    Y = _product(W, cb, X)
+    assert (Y[:, 5] == np.inf).all() and (Y[:, 6] == -np.inf).all() and np.isnan(Y[:, 7]).all()
+    assert np.allclose(Y[:, 8], W[:, 255] * np.float64(X[255, 8]), rtol=1e-6)
+    keep = np.r_[0:5, 9:40]
+    want = W.astype(np.float64) @ X[:, keep].astype(np.float64)
+    assert (np.abs(Y[:, keep] - want) <= 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X[:, keep]).astype(np.float64))).all()
