@@ -174,8 +174,11 @@ int cer_trim(void);
  *      n.16 bytes fit in LDS (n <= about 10000), K <= 64 and no row has more than 63 groups;
  *      for a batch of more than one tile a stream-ordered temporary of about the size of X is
  *      used (a tile-major copy of X).
- *   3  CER_PATH_DENSE: decode + dense: the matrix is decoded into a stream-ordered temporary of 4.m.n
- *      bytes and multiplied on the fp32 matrix cores.  Chosen when the estimated time of the gathers
+ *   3  CER_PATH_DENSE: decode + dense: the matrix is decoded into a stream-ordered temporary and multiplied
+ *      on the matrix cores: as one to three bf16 matrices that add up to it exactly (2.m.n bytes each), with
+ *      X split into three in the same way, or as fp32 (4.m.n bytes) where a value or an index range rules
+ *      that out.  The inputs keep all 24 bits of their significands (|X| >= 2^-109; smaller ones lose what
+ *      lies below 2^-133), products are exact or within 2^-25, sums are fp32.  Chosen when the estimated time of the gathers
  *      (max(4.batch, 128) bytes per indexed element through the L1/L2 path) exceeds that of the
  *      decode and the dense contraction: wide batches of matrices with more than about one
  *      indexed element in five, any batch > 1 of matrices with most elements indexed.  The
@@ -188,6 +191,9 @@ int cer_trim(void);
  * 128-byte line per index however narrow the batch) and loses for wide ones (random LDS gathers
  * are bank-conflict bound): it is chosen when it is applicable, batch <= 8 and the matrix holds
  * at least 2.5 million indices.
+ * Where batch <= 8, the codebook holds at most 256 values and the estimates say so, the library's own choice
+ * runs the batch-1 stream kernel for several columns at once instead of the kernel that is reported here
+ * (the number reported stays that of the kernel that serves the batch without it).
  * Errors: CER_E_INVALID, CER_E_HIP (no device copy).
  */
 int cer_matmul_path(const cer_handle_t* h, int64_t batch);

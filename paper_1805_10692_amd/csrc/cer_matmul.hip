@@ -62,22 +62,32 @@ __global__ __launch_bounds__(256) void colsum_partial4_kernel(const float* __res
     *reinterpret_cast<F4*>(part + (size_t)blockIdx.y * L + col) = (a0 + a1) + (a2 + a3);
 }
 
+// block: CB columns (a power of two up to 256), the slabs dealt to its 256 / CB groups of threads, eight in flight each (a
+// single thread per column took 15 us for 344 slabs).
 __global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restrict__ part, uint32_t nslabs, uint32_t L,
-                                                           float* __restrict__ T) {
-    const uint32_t col = blockIdx.x * 256u + threadIdx.x;
-    if (col >= L) return;
-    const float* p = part + col;
+                                                           uint32_t CB, float* __restrict__ T) {
+    __shared__ float red[256];
+    const uint32_t cl = threadIdx.x % CB, g = threadIdx.x / CB, G = 256u / CB, col = blockIdx.x * CB + cl;
     float a = 0.f;
-    uint32_t s = 0;
-    for (; s + 8 <= nslabs; s += 8) {  // eight slabs requested at a time, added in slab order
-        float b[8];
+    if (col < L) {
+        const float* p = part + col;
+        uint32_t s = g;
+        for (; s + 7u * G < nslabs; s += 8u * G) {  // added in slab order
+            float b[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) b[k] = p[(size_t)(s + k) * L];
+            for (int k = 0; k < 8; ++k) b[k] = p[(size_t)(s + k * G) * L];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) a += b[k];
+            for (int k = 0; k < 8; ++k) a += b[k];
+        }
+        for (; s < nslabs; s += G) a += p[(size_t)s * L];
     }
-    for (; s < nslabs; ++s) a += p[(size_t)s * L];
-    T[col] = a;
+    red[threadIdx.x] = a;
+    __syncthreads();
+    for (uint32_t s = G >> 1; s > 0; s >>= 1) {
+        if (g < s) red[threadIdx.x] += red[threadIdx.x + s * CB];
+        __syncthreads();
+    }
+    if (g == 0 && col < L) T[col] = red[cl];
 }
 
 hipError_t launch_colsum(const float* X, uint32_t n, uint32_t L, float* part, uint32_t nslabs, uint32_t slab,
@@ -89,7 +99,8 @@ hipError_t launch_colsum(const float* X, uint32_t n, uint32_t L, float* part, ui
     else
         e = launch_kernel(colsum_partial_kernel, dim3(coltiles, nslabs), dim3(256), 0, stream, X, n, L, CB, slab, part);
     if (e != hipSuccess) return e;
-    return launch_kernel(colsum_final_kernel, dim3((L + 255) / 256), dim3(256), 0, stream, part, nslabs, L, T);
+    const uint32_t FB = std::min<uint32_t>(CB, 32u);
+    return launch_kernel(colsum_final_kernel, dim3((L + FB - 1) / FB), dim3(256), 0, stream, part, nslabs, L, FB, T);
 }
 
 // Large batches of a matrix that is not sparse enough: the gathers move nnz.4.batch bytes through the L1/L2 path
@@ -199,6 +210,16 @@ int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o,
     return 1;
 }
 
+// Estimated duration of the kernel that choose_batched_path has named, for a batch of at most 8 columns.  Gathers from L2
+// touch one line per index there, in 0.6 of the time of a whole one (AlexNet-fc6 shape batch 4 20 us, VGG-fc6 shape batch 8 22 us);
+// the LDS tile kernel takes about as long per index.
+double path_estimate_us(const DeviceView& d, uint32_t L, int path) {
+    if (path == kPathStrip) return plan_strip(d, L).est_us;
+    double t_gather = 0, t_dense = 0;
+    if (path == 3 && densify_estimates(d, L, &t_gather, &t_dense)) return t_dense * 1e6;
+    return 4.0 + (double)d.nnz * 128.0 * 0.6 / 24e6;
+}
+
 // Column sums of X for a non-zero most frequent value: shape of the two-stage sum and the floats it needs
 // ([T: L rounded to 64][partials: nslabs x L]).
 struct ColsumPlan {
@@ -270,7 +291,12 @@ int launch_matmul(const DeviceView& d, const float* X, float* Y, int64_t L64, vo
     if (no_temporaries) o.flags |= kOptRowsWhole;  // the parts of split rows meet in a temporary
     XtilePlan plan;
     const int batched_path = L > 1 ? choose_batched_path(d, L, o, no_temporaries, &plan, X, Y) : 0;
+    // the library's own choice for a few columns
+    if (L > 1 && L <= 8 && o.path < 0 && o.flags == 0 && o.tile_cols == 0 && !no_temporaries &&
+        narrow_estimate_us(d, L) < path_estimate_us(d, L, batched_path))
+        return (int)launch_narrow(d, X, Y, L, stream);
     if (batched_path == 3) return (int)launch_densified(d, X, Y, L, stream);
+
 
     float* T = nullptr;
     float* scratch = nullptr;
