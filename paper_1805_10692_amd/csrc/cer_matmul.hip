@@ -127,8 +127,9 @@ bool densify_estimates(const DeviceView& d, uint32_t L, double* t_gather_out, do
     const double t_gather = std::max((double)d.nnz * std::max(4.0 * L, 128.0) * ragged / 24e12, (double)d.m * tiles * 4e-6 / 4096.0);
     double t_dense;
     if (pieces) {
-        // the decoder: 10 us (conv shape), 22 us (4096 x 9216, one piece, 5.7 M indices), 80 us (three pieces, 28 M)
-        t_dense = mfma_estimate_us(d, L) * 1e-6 + 4e-6 + mn * 2.0 * d.pieces / 4e12 + (double)d.nnz * 0.7e-12;
+        // the decoder: 7 us (578 x 1013), 10 us (conv shape), 17 us (633 x 5106, three pieces, 2.3 M indices), 22 us (4096 x
+        // 9216, one piece, 5.7 M), 80 us (three pieces, 28 M)
+        t_dense = mfma_estimate_us(d, L) * 1e-6 + 6e-6 + mn * 2.0 * d.pieces / 4.2e12 + (double)d.nnz * 0.6e-12;
     } else {
         const double rate = flops < 1.5e10 ? 90e12 : (flops < 1e11 ? 105e12 : 120e12);
         const double t_write = 4.0 * mn / 4.5e12;  // the decoded matrix goes to memory once and is read back at least once

@@ -166,6 +166,108 @@ __global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
         }
 }
 
+// The same for small problems: 64 x 32 CT outputs per workgroup, the four waves share its columns of W (32 at a time, in turn)
+// and add their sums up in LDS at the end.  A wave loads and splits the part of X that it multiplies straight into operand
+// registers, so there is no LDS and no barrier on the way; 128 columns take the workgroup 0.4 - 0.9 us instead of 2.7 (one
+// piece), and a matrix of 600 rows wastes 40 of them instead of 168.  Product of 700 x 1200, batch 60: 19 -> 9 us, 2048 x 2048, batch
+// 16: 9.2 -> 4.6 us, 2728 x 3378, batch 115: 20 -> 16 us; 512 x 4608, batch 3136: 48 us with the large tiles, 66 with these.  Bound by the splitting of X (PW = 1) or by what L2
+// delivers (80 KiB per 128 columns): the larger tile is the better one where it fills the chip.
+template <int PW, int CT, bool kAny>
+__device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2], size_t plane, __amdgpu_buffer_rsrc_t xbuf,
+                                                uint32_t L, const uint32_t (&xoff)[CT], uint32_t k_begin, uint32_t k_end,
+                                                floatx16 (&acc)[2][CT]) {
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pitch4 = L * 4u;
+    uint4 a[2][2][2][PW];
+    float x[2][2][CT][8];
+    float odd = 0.f;
+    auto load = [&](uint32_t k0, int slot) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+            for (int j = 0; j < CT; ++j)
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    x[slot][s][j][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff[j], (k0 + 16 * s + i) * pitch4, 0));
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int p = 0; p < PW; ++p)
+                    a[slot][s][i][p] = reinterpret_cast<const uint4*>(wtile[i] + p * plane + (size_t)(k0 + 16 * s) * 32)[lane];
+        }
+    };
+    auto step = [&](int slot) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int j = 0; j < CT; ++j) {
+                uint4 b[3];
+                odd += split3_8<kAny>(x[slot][s][j], b);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) acc[i][j] = mfma_pieces<PW>(a[slot][s][i], b, acc[i][j]);
+            }
+    };
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    uint32_t k0 = k_begin + 32u * wave;
+    if (k0 >= k_end) return odd;
+    load(k0, 0);
+    for (;;) {
+        load(min(k0 + 128u, k_end - 32u), 1);  // behind the end: the last columns once more
+        step(0);
+        if ((k0 += 128u) >= k_end) break;
+        load(min(k0 + 128u, k_end - 32u), 0);
+        step(1);
+        if ((k0 += 128u) >= k_end) break;
+    }
+    return odd;
+}
+
+template <int PW, int CT>
+__global__ __launch_bounds__(256, PW == 1 || (PW == 2 && CT == 1) ? 2 : 1) void mfma_small_kernel(
+    const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
+    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, size_t split_stride) {
+    __shared__ float s_acc[4][2 * CT][16][64];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t items = row_tiles * col_tiles * splits, eighth = (items + 7u) >> 3;
+    const uint32_t item = (blockIdx.x & 7u) * eighth + (blockIdx.x >> 3);  // as above
+    if ((blockIdx.x >> 3) >= eighth || item >= items) return;
+    const uint32_t rt = item % row_tiles, sp = (item / row_tiles) % splits, ct = item / row_tiles / splits;
+    const uint32_t row0 = rt * 64u, col0 = ct * 32u * CT;
+    const uint32_t k_begin = sp * kchunk, k_end = min(pitch, k_begin + kchunk);
+    Out += sp * split_stride;
+    const uint16_t* wtile[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * 32 * pitch;
+    const __amdgpu_buffer_rsrc_t xbuf = buffer_of(X, n * L * 4u);
+    uint32_t xoff[CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) xoff[j] = (8u * (lane >> 5) * L + min(col0 + 32u * j + (lane & 31u), L - 1u)) * 4u;
+    floatx16 acc[2][CT];
+    const float odd = mfma_small_run<PW, CT, false>(wtile, plane, xbuf, L, xoff, k_begin, k_end, acc);
+    if (__ballot(odd != odd)) (void)mfma_small_run<PW, CT, true>(wtile, plane, xbuf, L, xoff, k_begin, k_end, acc);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s_acc[wave][i * CT + j][e][lane] = acc[i][j][e];
+    __syncthreads();
+    // every wave adds up and stores a quarter of the workgroup's accumulators
+    constexpr int PER = 2 * CT * 16 / 4;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const uint32_t f = wave * PER + q, tile = f >> 4, e = f & 15u;
+        const float y = (s_acc[0][tile][e][lane] + s_acc[1][tile][e][lane]) + (s_acc[2][tile][e][lane] + s_acc[3][tile][e][lane]);
+        const uint32_t r = row0 + 32 * (tile / CT) + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4);
+        const uint32_t c = col0 + 32 * (tile % CT) + (lane & 31u);
+        if (r < m && c < L) Out[(size_t)r * L + c] = y;
+    }
+}
+
 __global__ __launch_bounds__(256) void mfma_sum_kernel(const float* __restrict__ part, float* __restrict__ Y, size_t count,
                                                        uint32_t splits) {
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -186,39 +288,53 @@ constexpr uint32_t kPitchStep = 128;  // W's rows are padded to a multiple of th
 constexpr int mfma_depth(int pieces, uint32_t BN) { return pieces == 1 && BN == 64 ? 4 : 2; }
 
 struct MfmaShape {
+    bool small;
     uint32_t BM, BN, row_tiles, col_tiles, splits, kchunk;
     double us;  // estimate of the product (without the decode)
 };
 
 // The launch lasts as long as the busiest compute unit: its share of the workgroups, one after the other (two resident ones
 // overlap, but share the matrix cores).  Measured per unit: 4.1 - 4.7 TFLOP/s with BN = 64, bound by the operands' bytes with
-// BN = 32.  A split along n costs its partial sums, written and read again.
-MfmaShape mfma_shape(const DeviceView& d, uint32_t L) {
-    MfmaShape s;
-    s.BN = L <= 32 ? 32 : 64;
-    s.BM = 256;
-    s.row_tiles = (uint32_t)((d.m + s.BM - 1) / s.BM);
-    s.col_tiles = (L + s.BN - 1) / s.BN;
-    const uint32_t round = mfma_depth(d.pieces, s.BN) * 2048 / s.BN;  // columns per round of the kernel
+// BN = 32; the small tiles 2.4 - 3.5 TFLOP/s.  A split along n costs its partial sums, written and read again.
+void shape_splits(const DeviceView& d, uint32_t L, uint32_t round, double round_us, double fixed_us, MfmaShape* s) {
     const uint32_t pitch = ((uint32_t)d.n + kPitchStep - 1) / kPitchStep * kPitchStep, rounds = (pitch + round - 1) / round;
-    const double tiles = (double)s.row_tiles * s.col_tiles, units = std::max(d.cus, 1);
-    const double products = d.pieces == 1 ? 3 : (d.pieces == 2 ? 5 : 6);
-    const double flops = 2.0 * s.BM * s.BN * round * products, bytes = (double)round * (s.BM * 2.0 * d.pieces + s.BN * 4.0);
-    const double round_us = std::max(flops / 4.3e6, bytes / 3.0e4);
-    double best = 1e300;
+    s->row_tiles = (uint32_t)((d.m + s->BM - 1) / s->BM);
+    s->col_tiles = (L + s->BN - 1) / s->BN;
+    const double tiles = (double)s->row_tiles * s->col_tiles, units = std::max(d.cus, 1);
     const uint32_t most = (uint32_t)std::min<double>(std::max(1u, rounds / 4), std::max(1.0, 4.0 * units / tiles));
+    s->us = 1e300;
     for (uint32_t sp = 1; sp <= std::min(most, 64u); ++sp) {
         const uint32_t per = (rounds + sp - 1) / sp, used = (rounds + per - 1) / per;
-        double us = std::ceil(tiles * used / units) * per * round_us + 4.0;
+        double us = std::ceil(tiles * used / units) * per * round_us + fixed_us;
         if (used > 1) us += 3.0 + (double)used * d.m * L * 8.0 / 6.5e6;
-        if (us < best) {
-            best = us;
-            s.splits = used;
-            s.kchunk = per * round;
-            s.us = us;
+        if (us < s->us) {
+            s->us = us;
+            s->splits = used;
+            s->kchunk = per * round;
         }
     }
-    return s;
+}
+
+MfmaShape mfma_shape(const DeviceView& d, uint32_t L) {
+    const double products = d.pieces == 1 ? 3 : (d.pieces == 2 ? 5 : 6);
+    MfmaShape big;
+    big.small = false;
+    big.BN = L <= 32 ? 32 : 64;
+    big.BM = 256;
+    {
+        const uint32_t round = mfma_depth(d.pieces, big.BN) * 2048 / big.BN;  // columns per round of the kernel
+        const double flops = 2.0 * big.BM * big.BN * round * products, bytes = (double)round * (big.BM * 2.0 * d.pieces + big.BN * 4.0);
+        shape_splits(d, L, round, std::max(flops / 4.3e6, bytes / 3.0e4), 4.0, &big);
+    }
+    MfmaShape small;
+    small.small = true;
+    small.BN = L <= 32 ? 32 : 64;
+    small.BM = 64;
+    {
+        const double flops = 2.0 * small.BM * small.BN * 128 * products;
+        shape_splits(d, L, 128, flops / (d.pieces == 1 ? 3.5e6 : (d.pieces == 2 ? 2.9e6 : 2.4e6)), 3.0, &small);
+    }
+    return small.us < big.us ? small : big;
 }
 
 template <int PW>
@@ -226,11 +342,10 @@ hipError_t launch_shape(const MfmaShape& s, const uint16_t* W, const float* X, f
                         uint32_t pitch, size_t plane, hipStream_t stream) {
     const dim3 grid((s.row_tiles * s.col_tiles * s.splits + 7) / 8 * 8);
     const size_t count = (size_t)m * L;
-    if (s.BN == 32)
-        return launch_kernel(mfma_product_kernel<PW, 1, mfma_depth(PW, 32)>, grid, dim3(256), 0, stream, W, X, out, m, n, L, pitch, plane,
-                             s.row_tiles, s.col_tiles, s.splits, s.kchunk, count);
-    return launch_kernel(mfma_product_kernel<PW, 2, mfma_depth(PW, 64)>, grid, dim3(256), 0, stream, W, X, out, m, n, L, pitch, plane,
-                         s.row_tiles, s.col_tiles, s.splits, s.kchunk, count);
+    auto* kern = s.small ? (s.BN == 32 ? mfma_small_kernel<PW, 1> : mfma_small_kernel<PW, 2>)
+                         : (s.BN == 32 ? mfma_product_kernel<PW, 1, mfma_depth(PW, 32)> : mfma_product_kernel<PW, 2, mfma_depth(PW, 64)>);
+    return launch_kernel(kern, grid, dim3(256), 0, stream, W, X, out, m, n, L, pitch, plane, s.row_tiles, s.col_tiles, s.splits,
+                         s.kchunk, count);
 }
 
 }  // namespace

@@ -773,6 +773,8 @@ struct DecodeArgs {
     uint32_t K;
     int64_t n;
     uint32_t seg, nseg;  // columns per segment: a multiple of 8
+    const uint32_t* tab;  // rank table
+    uint32_t tab_shift;
 };
 
 __device__ __forceinline__ void load_eight(const uint8_t* p, uint32_t v[8]) {
@@ -898,38 +900,132 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict
 
 // bf16 pieces in the operand order of v_mfma_f32_32x32x16_bf16: tiles of 32 rows x 16 columns, 1 KiB each, [row / 32]
 // [column / 16][column / 8 % 2][row % 32][column % 8], rows padded with zeros to a multiple of 16 columns (pitch).  Eight
-// rows per workgroup, one wave each, so that a store of the workgroup covers whole 128-byte lines.
+// rows per workgroup, so that a store of the workgroup covers whole 128-byte lines.
+// Ranks: the eight rows' records of the rank table come with one load, and their positions -- consecutive in colI -- are
+// dealt to all threads, eight at a time, two vectors in flight.  A position's group is the number of groups that begin at or
+// before it: a bitmap of the beginnings, counted up per word, as in the batch-1 kernel -- no search, no branch (a binary search
+// and a walk over the boundaries waited for LDS at every step: 633 x 5106, 112 values, 20 - 22 us).
+constexpr uint32_t kStretch = 32768;  // positions per bitmap
 template <typename ColT, typename CodeT, int kPieces>
 __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restrict__ colI, DecodeArgs a, int64_t m, int64_t pitch,
                                                            int64_t plane, uint16_t* __restrict__ out) {
     constexpr bool kRanks = sizeof(CodeT) == 1;
     extern __shared__ __align__(16) unsigned char s_seg[];  // eight rows of seg + 8 codes
-    __shared__ uint32_t s_ptr[8][kWave + 1];
-    __shared__ CodeT s_grp[8][kWave];
+    __shared__ uint32_t s_ptr[kRanks ? 8 * kCodes : 8 * (kWave + 1)];
+    __shared__ uint32_t s_list[kRanks ? 8 * kCodes + 1 : 1];
+    __shared__ uint32_t s_bits[kRanks ? kStretch / 32 : 1], s_pre[kRanks ? kStretch / 32 : 1];
+    __shared__ uint32_t s_cnt[8];
+    __shared__ CodeT s_grp[8][kRanks ? 1 : kWave];
     __shared__ uint32_t s_val[kRanks ? kCodes : 1];  // pieces 0 | 1 << 16, by rank
     __shared__ uint32_t s_val2[kRanks && kPieces == 3 ? kCodes : 1];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const int64_t row0 = (int64_t)blockIdx.x * 8, r = row0 + wave;
+    const int64_t row0 = (int64_t)blockIdx.x * 8;
     const int64_t c0 = (int64_t)blockIdx.y * a.seg;
     const uint32_t len = (uint32_t)min((int64_t)a.seg, a.n - c0);
     const uint32_t stride = a.seg + 8u;
     CodeT* code = reinterpret_cast<CodeT*>(s_seg);
     if constexpr (kRanks) {
+        const uint32_t rows = (uint32_t)min((int64_t)8, m - row0), words = rows << a.tab_shift;
+        for (uint32_t i = tid; i < words; i += 512u) s_ptr[i] = a.tab[((size_t)row0 << a.tab_shift) + i];
         for (uint32_t k = tid; k < a.K; k += 512u) {
             uint32_t p[3];
             cer::split3_any(a.omega[k], p);
             s_val[k] = p[0] | (p[1] << 16);
             if constexpr (kPieces == 3) s_val2[k] = p[2];
         }
-    }
-    {
-        const float w0 = kRanks ? 0.f : a.omega[0];
-        CodeT* mine = code + wave * stride;
-        for (uint32_t j = lane * (8u / sizeof(CodeT)); j < len; j += kWave * (8u / sizeof(CodeT))) {
-            if constexpr (kRanks) *reinterpret_cast<uint2*>(mine + j) = make_uint2(0, 0);
-            else *reinterpret_cast<float2*>(mine + j) = make_float2(w0, w0);
+        for (uint32_t j = tid; j < stride; j += 512u) reinterpret_cast<uint2*>(s_seg)[j] = make_uint2(0, 0);  // 8 rows of stride bytes
+        __syncthreads();
+        // list of the non-empty groups, in order of their positions: the row's place in s_seg | rank << 16; entry 0 is unused
+        auto begins = [&](uint32_t i, uint32_t& at) {  // boundary i closes a group that begins at position `at`
+            if (i == 0 || i >= words) return false;
+            at = s_ptr[i - 1u];
+            return s_ptr[i] > at;
+        };
+        uint32_t groups = 1;
+        for (uint32_t c = 0; c < words; c += 512u) {
+            uint32_t at;
+            const uint32_t i = c + tid;
+            const bool some = begins(i, at);
+            const uint64_t votes = __ballot(some);
+            if (lane == 0) s_cnt[wave] = (uint32_t)__popcll(votes);
+            __syncthreads();
+            uint32_t pos = groups + (uint32_t)__popcll(votes & ((1ull << lane) - 1ull));
+            for (uint32_t w = 0; w < 8; ++w) {
+                if (w < wave) pos += s_cnt[w];
+                groups += s_cnt[w];
+            }
+            if (some) s_list[pos] = (i >> a.tab_shift) * stride | ((i & ((1u << a.tab_shift) - 1u)) << 16);
+            __syncthreads();
         }
-        if (r < m) scatter_row<ColT, CodeT, kWave, true>(colI, a, a.rowPtr[r], a.rowPtr[r + 1], lane, c0, len, s_ptr[wave], s_grp[wave], mine);
+        const uint32_t pb = s_ptr[0], pe = s_ptr[words - 1u];
+        uint32_t seen = 0;  // groups that begin before the current stretch of positions
+        for (uint32_t base = pb & ~7u; base < pe; base += kStretch) {  // uniform over the workgroup
+            // bitmap of the positions that begin a group, and the number of such positions in front of every word
+            for (uint32_t i = tid; i < kStretch / 32u; i += 512u) s_bits[i] = 0u;
+            __syncthreads();
+            for (uint32_t i = tid; i < words; i += 512u) {
+                uint32_t at;
+                if (begins(i, at) && at - base < kStretch) atomicOr(&s_bits[(at - base) >> 5], 1u << ((at - base) & 31u));
+            }
+            __syncthreads();
+            const uint32_t n0 = (uint32_t)__builtin_popcount(s_bits[2u * tid]), n1 = (uint32_t)__builtin_popcount(s_bits[2u * tid + 1u]);
+            uint32_t incl = n0 + n1;
+#pragma unroll
+            for (int off = 1; off < kWave; off <<= 1) {
+                const uint32_t u = __shfl_up(incl, off, kWave);
+                if ((int)lane >= off) incl += u;
+            }
+            if (lane == 63u) s_cnt[wave] = incl;
+            __syncthreads();
+            uint32_t before = seen + incl - n0 - n1;
+            for (uint32_t w = 0; w < 8; ++w) {
+                if (w < wave) before += s_cnt[w];
+                seen += s_cnt[w];
+            }
+            s_pre[2u * tid] = before;
+            s_pre[2u * tid + 1u] = before + n0;
+            __syncthreads();
+            auto take = [&](uint32_t v, const uint32_t (&col)[8]) {
+                const uint32_t rel0 = v - base, word = s_bits[rel0 >> 5], sh = rel0 & 31u;
+                uint32_t g = s_pre[rel0 >> 5] + (uint32_t)__builtin_popcount(word & ((1u << sh) - 1u));
+                uint32_t e[8];
+#pragma unroll
+                for (uint32_t i = 0; i < 8; ++i) {
+                    g += (word >> (sh + i)) & 1u;
+                    e[i] = s_list[g];
+                }
+#pragma unroll
+                for (uint32_t i = 0; i < 8; ++i) {
+                    const uint32_t rel = col[i] - (uint32_t)c0;  // huge when left of the segment
+                    if (v + i >= pb && v + i < pe && rel < len) code[(e[i] & 0xFFFFu) + rel] = (CodeT)(e[i] >> 16);
+                }
+            };
+            const uint32_t stop = min(pe, base + kStretch);
+            uint32_t v = base + tid * 8u;
+            uint32_t ahead[2][8];
+            if (v < stop) load_eight(colI + v, ahead[0]);  // up to seven positions on either side of the rows belong to others
+            if (v + 4096u < stop) load_eight(colI + v + 4096u, ahead[1]);
+            for (; v < stop; v += 8192u) {
+                uint32_t col[2][8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    col[0][i] = ahead[0][i];
+                    col[1][i] = ahead[1][i];
+                }
+                if (v + 8192u < stop) load_eight(colI + v + 8192u, ahead[0]);
+                if (v + 12288u < stop) load_eight(colI + v + 12288u, ahead[1]);
+                take(v, col[0]);
+                if (v + 4096u < stop) take(v + 4096u, col[1]);
+            }
+            __syncthreads();
+        }
+    } else {
+        const int64_t r = row0 + wave;
+        const float w0 = a.omega[0];
+        CodeT* mine = code + wave * stride;
+        for (uint32_t j = lane * 2u; j < len; j += kWave * 2u) *reinterpret_cast<float2*>(mine + j) = make_float2(w0, w0);
+        if (r < m)
+            scatter_row<ColT, CodeT, kWave, true>(colI, a, a.rowPtr[r], a.rowPtr[r + 1], lane, c0, len, s_ptr + wave * (kWave + 1), s_grp[wave], mine);
     }
     __syncthreads();
     const uint32_t wlen = c0 + a.seg >= a.n ? (uint32_t)(pitch - c0) : a.seg;  // the last segment also writes the padding
@@ -938,25 +1034,35 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
     uint16_t* o = out + (row0 >> 5) * 32 * pitch + ((row0 & 31) + rr) * 8;
     const CodeT* mine = code + rr * stride;
     for (uint32_t j = (tid >> 3) * 8u; j < wlen; j += 512u) {
-        uint32_t w[3][4] = {};
+        uint32_t p01[8], p2[8];
+        if constexpr (kRanks) {
+            const uint2 q = *reinterpret_cast<const uint2*>(mine + j);  // the stride leaves eight more codes behind a segment
 #pragma unroll
-        for (uint32_t i = 0; i < 8; ++i) {
-            uint32_t p01 = 0, p2 = 0;
-            if (j + i < len) {
-                if constexpr (kRanks) {
-                    p01 = s_val[mine[j + i]];
-                    if constexpr (kPieces == 3) p2 = s_val2[mine[j + i]];
-                } else {
-                    uint32_t p[3];
-                    cer::split3_any((float)mine[j + i], p);
-                    p01 = p[0] | (p[1] << 16);
-                    p2 = p[2];
-                }
+            for (uint32_t i = 0; i < 8; ++i) {
+                const uint32_t k = ((i < 4 ? q.x : q.y) >> (8 * (i & 3u))) & 0xFFu;
+                p01[i] = s_val[k];
+                p2[i] = kPieces == 3 ? s_val2[k] : 0u;
             }
-            const uint32_t sh = 16u * (i & 1u);
-            w[0][i >> 1] |= (p01 & 0xFFFFu) << sh;
-            w[1][i >> 1] |= (p01 >> 16) << sh;
-            w[2][i >> 1] |= p2 << sh;
+        } else {
+#pragma unroll
+            for (uint32_t i = 0; i < 8; ++i) {
+                uint32_t p[3];
+                cer::split3_any((float)mine[min(j + i, len - 1u)], p);
+                p01[i] = p[0] | (p[1] << 16);
+                p2[i] = p[2];
+            }
+        }
+        if (j + 8u > len) {
+#pragma unroll
+            for (uint32_t i = 0; i < 8; ++i)
+                if (j + i >= len) p01[i] = p2[i] = 0u;
+        }
+        uint32_t w[3][4];
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+            w[0][i] = __builtin_amdgcn_perm(p01[2 * i + 1], p01[2 * i], 0x05040100u);
+            w[1][i] = __builtin_amdgcn_perm(p01[2 * i + 1], p01[2 * i], 0x07060302u);
+            w[2][i] = p2[2 * i] | (p2[2 * i + 1] << 16);
         }
         const int64_t at = (c0 + j) * 32;  // (column / 8) . 32 rows . 8
 #pragma unroll
@@ -1116,6 +1222,8 @@ DecodeArgs decode_args(const DeviceView& v, int64_t nseg, uint32_t multiple) {
     a.cser = v.cser;
     a.K = (uint32_t)v.K;
     a.n = v.n;
+    a.tab = v.rank_tab;
+    a.tab_shift = (uint32_t)v.rank_tab_shift;
     nseg = std::min<int64_t>(std::max<int64_t>(nseg, 1), 65535);
     a.seg = (uint32_t)(((v.n + nseg - 1) / nseg + multiple - 1) / multiple * multiple);
     a.nseg = (uint32_t)((v.n + a.seg - 1) / a.seg);
@@ -1138,9 +1246,9 @@ hipError_t launch_decode(const DeviceView& v, float* out, hipStream_t s) {
 
 template <typename ColT, typename CodeT>
 hipError_t launch_decode_tiles(const DeviceView& v, uint16_t* out, int64_t pitch, int64_t plane, hipStream_t s) {
-    // Segments of at most 64 KiB of LDS for eight rows; three workgroups for two compute units where segments of 512 columns
+    // Segments of at most 32 KiB of LDS for eight rows; three workgroups for two compute units where segments of 512 columns
     // or more allow it (every segment reads its rows' indices again).
-    const int64_t most = 8192 / (int64_t)sizeof(CodeT), groups = (v.m + 7) / 8;
+    const int64_t most = 4096 / (int64_t)sizeof(CodeT), groups = (v.m + 7) / 8;
     const DecodeArgs a = decode_args(v, std::max<int64_t>((v.n + most - 1) / most, std::min<int64_t>((384 + groups - 1) / groups, v.n / 512)), 16);
     const dim3 grid((unsigned)groups, a.nseg);
     const size_t lds = (size_t)(a.seg + 8) * 8 * sizeof(CodeT);
@@ -1170,7 +1278,7 @@ int decode_device(const DeviceView& v, float* W, void* stream) {
 
 int decode_pieces(const DeviceView& v, uint16_t* W, int64_t pitch, int64_t plane, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool ranks = v.K <= kCodes;
+    const bool ranks = v.rank_tab != nullptr;
     switch (v.colI_bits) {
         case 8: return (int)(ranks ? launch_decode_tiles<uint8_t, uint8_t>(v, W, pitch, plane, s) : launch_decode_tiles<uint8_t, float>(v, W, pitch, plane, s));
         case 16: return (int)(ranks ? launch_decode_tiles<uint16_t, uint8_t>(v, W, pitch, plane, s) : launch_decode_tiles<uint16_t, float>(v, W, pitch, plane, s));
