@@ -110,6 +110,22 @@ hipError_t launch_colsum(const float* X, uint32_t n, uint32_t L, float* part, ui
 // the values or the sizes rule that out, as fp32 (4 bytes per element; 90 - 120 TFLOP/s).  Measured on MI355X, gathers against
 // decode + product: 3x3 convolution shape (60 % zeros) batch 3136 391 / 64 us (fp32: 149 us); 7-bit quantizer of the same shape
 // 550 / 112 us.
+// Estimated duration (seconds) of the kernel that gathers from L2.
+//   * bytes: nnz lines of 128 bytes per 32 columns; rows of X that do not start on a line make a tile touch two of them (a third
+//     more time: AlexNet-fc6 shape batch 100 114 us, batch 128 107 us)
+//   * waves: every (row, tile) is a wave whose start-up chain (descriptor -> pointers -> indices -> first gathers) takes about
+//     4 us, 4096 of them in flight: what bounds matrices of many short rows (16384 x 512: batch 128 64 - 84 us)
+//   * few rows: a wave walks its row alone, 5.5 ns per position (543 x 7364, batch 28, 4900 positions per row: 28 us)
+//   * the column sums of X for a non-zero most frequent value: two launches and a pass over X
+double gather_estimate(const DeviceView& d, uint32_t L) {
+    const double tiles = std::ceil((double)L / 32.0);
+    const double ragged = L % 32u == 0 || (L < 32u && 32u % L == 0) ? 1.0 : 1.35;
+    const double t_bytes = (double)d.nnz * std::max(4.0 * L, 128.0) * ragged / 27e12;
+    const double t_waves = (double)d.m * tiles * 4e-6 / 4096.0;
+    const double t_row = d.split_min ? 0.0 : (double)d.nnz / (double)std::max<int64_t>(d.m, 1) * 5.5e-9 * ragged;
+    return 4e-6 + std::max(std::max(t_bytes, t_row), t_waves) + (d.omega0 != 0.f ? 5e-6 + (double)d.n * L * 4.0 / 4e12 : 0.0);
+}
+
 // Estimated durations (seconds) of the gathers and of decode + dense; false where the dense route is not available.
 bool densify_estimates(const DeviceView& d, uint32_t L, double* t_gather_out, double* t_dense_out) {
     if (L < 2 || d.m < 128 || d.n < 256) return false;
@@ -118,18 +134,12 @@ bool densify_estimates(const DeviceView& d, uint32_t L, double* t_gather_out, do
     const bool pieces = mfma_applicable(d, L);
     if (mn * (pieces ? 2.0 * d.pieces : 4.0) > (double)(1ull << 30)) return false;
     const double flops = 2.0 * mn * L;
-    // every (row, tile) is a wave whose start-up chain (descriptor -> pointers -> indices -> first gathers) takes about
-    // 4 us, 4096 of them in flight: what bounds matrices of many short rows (16384 x 512: batch 128 64 - 84 us,
-    // batch 512 160 - 440 us by gathers; 44 - 49 us and 94 - 103 us decoded and multiplied)
-    const double tiles = std::ceil((double)L / 32.0);
-    // rows of X that do not start on a 128-byte line: a 32-column tile touches two of them (measured: a third more time)
-    const double ragged = L % 32u == 0 || (L < 32u && 32u % L == 0) ? 1.0 : 1.35;
-    const double t_gather = std::max((double)d.nnz * std::max(4.0 * L, 128.0) * ragged / 24e12, (double)d.m * tiles * 4e-6 / 4096.0);
+    const double t_gather = gather_estimate(d, L);
     double t_dense;
     if (pieces) {
-        // the decoder: 7 us (578 x 1013), 10 us (conv shape), 17 us (633 x 5106, three pieces, 2.3 M indices), 22 us (4096 x
-        // 9216, one piece, 5.7 M), 80 us (three pieces, 28 M)
-        t_dense = mfma_estimate_us(d, L) * 1e-6 + 6e-6 + mn * 2.0 * d.pieces / 4.2e12 + (double)d.nnz * 0.6e-12;
+        // the decoder: 7 us (578 x 1013), 9 us (conv shape), 11 us (633 x 5106, three pieces, 2.3 M indices), 15 us (1084 x
+        // 13798, one piece, 4.5 M), 28 us (986 x 16765, three pieces, 9.7 M)
+        t_dense = mfma_estimate_us(d, L) * 1e-6 + 6e-6 + mn * 2.0 * d.pieces / 4.4e12 + (double)d.nnz * 0.35e-12;
     } else {
         const double rate = flops < 1.5e10 ? 90e12 : (flops < 1e11 ? 105e12 : 120e12);
         const double t_write = 4.0 * mn / 4.5e12;  // the decoded matrix goes to memory once and is read back at least once
@@ -179,11 +189,7 @@ int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o,
     double t_strip = 0;
     if (o.path < 0 && strips_ok && has_elements) {
         t_strip = plan_strip(d, L).est_us * 1e-6;
-        // bytes a gather moves per index: whole 128-byte lines; a width that is not a multiple of 32 columns touches
-        // about one line more per row of X (AlexNet-fc6 shape batch 100: 114 us, VGG-fc6 shape: 158 us), unless a row
-        // of X divides a line (8 and 16 columns)
-        const double lines = L % 32u == 0 ? L / 32.0 : (L < 32u && 32u % L == 0 ? 1.0 : 0.85 * ((L + 31u) / 32u + 1.0));
-        const double t_gather_l2 = 5e-6 + (double)d.nnz * 128.0 * lines / 27e12;
+        const double t_gather_l2 = gather_estimate(d, L);
         strips_beat_gathers = t_strip < 0.95 * t_gather_l2;
     }
     // (from 8 columns on the strips are ahead of the LDS tile of all input rows: AlexNet-fc6 shape batch 8 23 against 28 us)
@@ -204,7 +210,7 @@ int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o,
     if (o.path < 0 && !no_temporaries && has_elements) {
         double t_gather = 0, t_dense = 0;
         const bool dense_ok = densify_estimates(d, L, &t_gather, &t_dense);
-        const bool dense_pays = dense_ok && t_gather > 1.1 * t_dense;
+        const bool dense_pays = dense_ok && t_gather > 1.05 * t_dense;
         if (strips_beat_gathers && (!dense_pays || t_strip < t_dense)) return kPathStrip;
         if (dense_pays) return 3;
     }

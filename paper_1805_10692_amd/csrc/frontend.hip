@@ -775,6 +775,7 @@ struct DecodeArgs {
     uint32_t seg, nseg;  // columns per segment: a multiple of 8
     const uint32_t* tab;  // rank table
     uint32_t tab_shift;
+    uint32_t rows;        // decode_tiles_kernel: rows per workgroup, 8 or 4
 };
 
 __device__ __forceinline__ void load_eight(const uint8_t* p, uint32_t v[8]) {
@@ -900,11 +901,13 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict
 
 // bf16 pieces in the operand order of v_mfma_f32_32x32x16_bf16: tiles of 32 rows x 16 columns, 1 KiB each, [row / 32]
 // [column / 16][column / 8 % 2][row % 32][column % 8], rows padded with zeros to a multiple of 16 columns (pitch).  Eight
-// rows per workgroup, so that a store of the workgroup covers whole 128-byte lines.
-// Ranks: the eight rows' records of the rank table come with one load, and their positions -- consecutive in colI -- are
+// rows per workgroup, so that a store of the workgroup covers whole 128-byte lines; four where eight would leave compute
+// units without work (reading the rows' indices is what takes time, and segments do not divide it).
+// Ranks: the rows' records of the rank table come with one load, and their positions -- consecutive in colI -- are
 // dealt to all threads, eight at a time, two vectors in flight.  A position's group is the number of groups that begin at or
 // before it: a bitmap of the beginnings, counted up per word, as in the batch-1 kernel -- no search, no branch (a binary search
-// and a walk over the boundaries waited for LDS at every step: 633 x 5106, 112 values, 20 - 22 us).
+// and a walk over the boundaries waited for LDS at every step: 633 x 5106, 112 values, 22 us, now 11; 986 x 16765, three
+// values, 42 against 28).
 constexpr uint32_t kStretch = 32768;  // positions per bitmap
 template <typename ColT, typename CodeT, int kPieces>
 __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restrict__ colI, DecodeArgs a, int64_t m, int64_t pitch,
@@ -919,13 +922,13 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
     __shared__ uint32_t s_val[kRanks ? kCodes : 1];  // pieces 0 | 1 << 16, by rank
     __shared__ uint32_t s_val2[kRanks && kPieces == 3 ? kCodes : 1];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const int64_t row0 = (int64_t)blockIdx.x * 8;
+    const int64_t row0 = (int64_t)blockIdx.x * a.rows;
     const int64_t c0 = (int64_t)blockIdx.y * a.seg;
     const uint32_t len = (uint32_t)min((int64_t)a.seg, a.n - c0);
     const uint32_t stride = a.seg + 8u;
     CodeT* code = reinterpret_cast<CodeT*>(s_seg);
     if constexpr (kRanks) {
-        const uint32_t rows = (uint32_t)min((int64_t)8, m - row0), words = rows << a.tab_shift;
+        const uint32_t rows = (uint32_t)min((int64_t)a.rows, m - row0), words = rows << a.tab_shift;
         for (uint32_t i = tid; i < words; i += 512u) s_ptr[i] = a.tab[((size_t)row0 << a.tab_shift) + i];
         for (uint32_t k = tid; k < a.K; k += 512u) {
             uint32_t p[3];
@@ -933,7 +936,7 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
             s_val[k] = p[0] | (p[1] << 16);
             if constexpr (kPieces == 3) s_val2[k] = p[2];
         }
-        for (uint32_t j = tid; j < stride; j += 512u) reinterpret_cast<uint2*>(s_seg)[j] = make_uint2(0, 0);  // 8 rows of stride bytes
+        for (uint32_t j = tid; j < a.rows * stride >> 3; j += 512u) reinterpret_cast<uint2*>(s_seg)[j] = make_uint2(0, 0);
         __syncthreads();
         // list of the non-empty groups, in order of their positions: the row's place in s_seg | rank << 16; entry 0 is unused
         auto begins = [&](uint32_t i, uint32_t& at) {  // boundary i closes a group that begins at position `at`
@@ -1022,18 +1025,18 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
     } else {
         const int64_t r = row0 + wave;
         const float w0 = a.omega[0];
-        CodeT* mine = code + wave * stride;
-        for (uint32_t j = lane * 2u; j < len; j += kWave * 2u) *reinterpret_cast<float2*>(mine + j) = make_float2(w0, w0);
-        if (r < m)
+        CodeT* mine = code + min(wave, a.rows - 1u) * stride;
+        for (uint32_t j = lane * 2u; wave < a.rows && j < len; j += kWave * 2u) *reinterpret_cast<float2*>(mine + j) = make_float2(w0, w0);
+        if (wave < a.rows && r < m)
             scatter_row<ColT, CodeT, kWave, true>(colI, a, a.rowPtr[r], a.rowPtr[r + 1], lane, c0, len, s_ptr + wave * (kWave + 1), s_grp[wave], mine);
     }
     __syncthreads();
     const uint32_t wlen = c0 + a.seg >= a.n ? (uint32_t)(pitch - c0) : a.seg;  // the last segment also writes the padding
-    const uint32_t rr = tid & 7u;
+    const uint32_t rr = tid & (a.rows - 1u), columns = 8u * 512u / a.rows;  // columns per step of the workgroup
     if (row0 + rr >= m) return;
     uint16_t* o = out + (row0 >> 5) * 32 * pitch + ((row0 & 31) + rr) * 8;
     const CodeT* mine = code + rr * stride;
-    for (uint32_t j = (tid >> 3) * 8u; j < wlen; j += 512u) {
+    for (uint32_t j = tid / a.rows * 8u; j < wlen; j += columns) {
         uint32_t p01[8], p2[8];
         if constexpr (kRanks) {
             const uint2 q = *reinterpret_cast<const uint2*>(mine + j);  // the stride leaves eight more codes behind a segment
@@ -1246,12 +1249,21 @@ hipError_t launch_decode(const DeviceView& v, float* out, hipStream_t s) {
 
 template <typename ColT, typename CodeT>
 hipError_t launch_decode_tiles(const DeviceView& v, uint16_t* out, int64_t pitch, int64_t plane, hipStream_t s) {
-    // Segments of at most 32 KiB of LDS for eight rows; three workgroups for two compute units where segments of 512 columns
-    // or more allow it (every segment reads its rows' indices again).
-    const int64_t most = 4096 / (int64_t)sizeof(CodeT), groups = (v.m + 7) / 8;
-    const DecodeArgs a = decode_args(v, std::max<int64_t>((v.n + most - 1) / most, std::min<int64_t>((384 + groups - 1) / groups, v.n / 512)), 16);
+    uint32_t rows = 8;
+    while (rows > 4 && (v.m + rows - 1) / rows < v.cus) rows >>= 1;
+    // as few segments as 48 KiB of LDS allow (two workgroups per compute unit): each of them reads all indices of its rows
+    const int64_t most = 49152 / (int64_t)sizeof(CodeT) / rows, groups = (v.m + rows - 1) / rows;
+    DecodeArgs a = decode_args(v, (v.n + most - 1) / most, 16);
+    a.rows = rows;
     const dim3 grid((unsigned)groups, a.nseg);
-    const size_t lds = (size_t)(a.seg + 8) * 8 * sizeof(CodeT);
+    const size_t lds = (size_t)(a.seg + 8) * rows * sizeof(CodeT);
+    {   // with the static part more than 64 KiB
+        static cer::LdsGrant<3> grant;
+        const void* kern = v.pieces == 1 ? (const void*)decode_tiles_kernel<ColT, CodeT, 1>
+                                         : (v.pieces == 2 ? (const void*)decode_tiles_kernel<ColT, CodeT, 2> : (const void*)decode_tiles_kernel<ColT, CodeT, 3>);
+        const hipError_t e = grant.ensure(v.pieces - 1, kern, 56 * 1024);
+        if (e != hipSuccess) return e;
+    }
     const ColT* colI = static_cast<const ColT*>(v.colI);
     switch (v.pieces) {
         case 1: return launch_kernel(decode_tiles_kernel<ColT, CodeT, 1>, grid, dim3(512), lds, s, colI, a, v.m, pitch, plane, out);
