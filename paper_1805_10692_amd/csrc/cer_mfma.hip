@@ -17,12 +17,6 @@ namespace cer {
 namespace {
 
 constexpr uint32_t kFlush = 256;
-typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
-
-// A buffer descriptor over `bytes` bytes: loads beyond them return zero.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
-}
 
 template <int PW, int TN, int D>
 struct MfmaTile {
@@ -36,15 +30,16 @@ struct MfmaTile {
                                          uint32_t xcol, uint32_t k_begin, uint32_t k_end, floatx16 (&sum)[TM][TN]) {
         const uint32_t tid = threadIdx.x, lane = tid & 63u;
         const uint32_t xc = tid % BN, xg = tid / BN;  // this thread's share of X: rows 8 xg .. 8 xg + 7 of a step, one column
-        const __amdgpu_buffer_rsrc_t xbuf = buffer_of(X, n * L * 4u);
-        const uint32_t xoff = (8u * xg * L + xcol) * 4u, pitch4 = L * 4u;
+        uint32_t xoff[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) xoff[i] = ((8u * xg + i) * L + xcol) * 4u;
         float xr[D][8];
         uint4 a[2][KS][TM][PW];
         float odd = 0.f;
         auto load_x = [&](uint32_t k0, int slot) {
+            const __amdgpu_buffer_rsrc_t xbuf = x_rows(X, L, k0, n);
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                xr[slot][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff, (k0 + i) * pitch4, 0));
+            for (int i = 0; i < 8; ++i) xr[slot][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff[i], 0, 0));
         };
         auto load_w = [&](uint32_t k0, int slot) {
 #pragma unroll
@@ -173,21 +168,27 @@ __global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
 // 16: 9.2 -> 4.6 us, 2728 x 3378, batch 115: 20 -> 16 us; 512 x 4608, batch 3136: 48 us with the large tiles, 66 with these.  Bound by the splitting of X (PW = 1) or by what L2
 // delivers (80 KiB per 128 columns): the larger tile is the better one where it fills the chip.
 template <int PW, int CT, bool kAny>
-__device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2], size_t plane, __amdgpu_buffer_rsrc_t xbuf,
-                                                uint32_t L, const uint32_t (&xoff)[CT], uint32_t k_begin, uint32_t k_end,
-                                                floatx16 (&acc)[2][CT]) {
-    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pitch4 = L * 4u;
+__device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2], size_t plane, const float* X, uint32_t n,
+                                                uint32_t L, uint32_t col0, uint32_t k_begin, uint32_t k_end, floatx16 (&acc)[2][CT]) {
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t xoff[8];  // of the wave's first column tile
+#pragma unroll
+    for (int i = 0; i < 8; ++i) xoff[i] = ((8u * (lane >> 5) + i) * L + min(col0 + (lane & 31u), L - 1u)) * 4u;
+    uint32_t xstep[CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) xstep[j] = (min(col0 + 32u * j + (lane & 31u), L - 1u) - min(col0 + (lane & 31u), L - 1u)) * 4u;
     uint4 a[2][2][2][PW];
     float x[2][2][CT][8];
     float odd = 0.f;
     auto load = [&](uint32_t k0, int slot) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
+            const __amdgpu_buffer_rsrc_t xbuf = x_rows(X, L, k0 + 16 * s, n);
 #pragma unroll
             for (int j = 0; j < CT; ++j)
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
-                    x[slot][s][j][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff[j], (k0 + 16 * s + i) * pitch4, 0));
+                    x[slot][s][j][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff[i] + xstep[j], 0, 0));
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -242,13 +243,9 @@ __global__ __launch_bounds__(256, PW == 1 || (PW == 2 && CT == 1) ? 2 : 1) void 
     const uint16_t* wtile[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * 32 * pitch;
-    const __amdgpu_buffer_rsrc_t xbuf = buffer_of(X, n * L * 4u);
-    uint32_t xoff[CT];
-#pragma unroll
-    for (int j = 0; j < CT; ++j) xoff[j] = (8u * (lane >> 5) * L + min(col0 + 32u * j + (lane & 31u), L - 1u)) * 4u;
     floatx16 acc[2][CT];
-    const float odd = mfma_small_run<PW, CT, false>(wtile, plane, xbuf, L, xoff, k_begin, k_end, acc);
-    if (__ballot(odd != odd)) (void)mfma_small_run<PW, CT, true>(wtile, plane, xbuf, L, xoff, k_begin, k_end, acc);
+    const float odd = mfma_small_run<PW, CT, false>(wtile, plane, X, n, L, col0, k_begin, k_end, acc);
+    if (__ballot(odd != odd)) (void)mfma_small_run<PW, CT, true>(wtile, plane, X, n, L, col0, k_begin, k_end, acc);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll

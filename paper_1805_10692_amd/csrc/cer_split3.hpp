@@ -89,4 +89,10 @@ __device__ __forceinline__ floatx16 mfma_pieces(const uint4* a, const uint4* b, 
     return c;
 }
 
+// X from row `row` on, as a buffer that ends with row `end` - 1: loads behind it return zero.  The range check of a buffer load
+// covers its vector offset only, so the row goes into the base address (scalar arithmetic) and not into the scalar offset.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t x_rows(const float* X, uint32_t L, uint32_t row, uint32_t end) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(X + (size_t)row * L), 0, row < end ? (end - row) * L * 4u : 0u, 0x00020000);
+}
+
 }  // namespace cer

@@ -52,3 +52,22 @@ def test_inputs_that_have_no_three_pieces():
     keep = np.r_[0:5, 9:40]
     want = W.astype(np.float64) @ X[:, keep].astype(np.float64)
     assert (np.abs(Y[:, keep] - want) <= 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X[:, keep]).astype(np.float64))).all()
+
+
+@pytest.mark.parametrize("pieces", list(CODEBOOKS))
+def test_nothing_behind_the_inputs_reaches_the_result(pieces):
+    """NaNs right behind X, and the step of the kernels that crosses its end."""
+    rng = np.random.default_rng(5)
+    cb = CODEBOOKS[pieces]
+    for m, n, L in ((300, 130, 70), (64, 257, 33), (500, 1027, 3)):
+        W = rng.choice(cb, size=(m, n), p=[0.4, 0.2, 0.2, 0.2]).astype(np.float32)
+        X = rng.standard_normal((n, L)).astype(np.float32)
+        buf = torch.full((n * L + 200 * L,), float("nan"), device="cuda")
+        buf[:n * L].copy_(torch.from_numpy(X).reshape(-1))
+        h = B.cer_encode(W, cb)
+        Y = torch.full((m, L), float("nan"), device="cuda")
+        B.cer_matmul_ex(h, buf, Y, L, None, B.MatmulOpts(path=B.CER_PATH_DENSE))
+        torch.cuda.synchronize()
+        B.cer_free(h)
+        want = W.astype(np.float64) @ X.astype(np.float64)
+        assert (np.abs(Y.cpu().numpy() - want) <= 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64))).all()
