@@ -4,9 +4,8 @@
 //   range     min / max of W (quantizer only)
 //   codes     the K = 2^b points of the codebook; element -> codebook position (quantizer: nearest point;
 //             otherwise: exact look-up), one byte per element, and a per-row histogram over the positions
-//   hist      global histogram in partial sums
-//   layout    frequency-major order Omega (Section III-A, step 1); per row: number of indexed elements and of groups
-//   scan      exclusive scans over the rows give every row its slice of colI and of OmegaPtr / OmegaI; the sizes go to
+//   layout    frequency-major order Omega (Section III-A, step 1); per row: number of indexed elements and of groups;
+//             exclusive scans over the rows give every row its slice of colI and of OmegaPtr / OmegaI; the sizes go to
 //             the host, which allocates the handle
 //   emit      per row: a stable counting sort of the columns by rank writes colI, the bucket ends are
 //             the row's pointers (steps 2-4) and its record of the rank table
@@ -44,6 +43,7 @@ struct FrontState {
     uint32_t flags;
     uint32_t K;         // codebook positions in use (caller's K, or the quantizer's point count)
     uint32_t Kp;        // values that occur = length of Omega
+    uint32_t done;      // workgroups of row_layout_kernel that have finished
     unsigned long long count[kCodes];  // occurrences by rank
     float codebook[kCodes];            // value by codebook position
     float omega[kCodes];               // value by rank
@@ -51,17 +51,17 @@ struct FrontState {
     uint32_t pos_of[kCodes];           // rank -> codebook position
 };
 
-// What the host needs to know before it can allocate the handle; the last kernel of the first part writes it straight
-// into pinned host memory (`ready` last).
+// What the host needs to know, in pinned host memory: first the sizes, before it can allocate the handle (`ready` last);
+// the values with the handle's arrays (nobody waits for them on their way).
 struct FrontResult {
     uint32_t flags, K, Kp;
     uint32_t max_row_groups;
     uint32_t max_row_nnz;  // indexed elements of the longest row
     unsigned long long nnz, G, nonempty;
+    uint32_t ready;
     unsigned long long count[kCodes];
     float codebook[kCodes];
     float omega[kCodes];
-    uint32_t ready;
 };
 
 // LDS traffic of one wave is ordered; this only keeps the compiler from moving accesses across.
@@ -82,12 +82,24 @@ __device__ __forceinline__ void range_take(float w, float& lo, float& hi, uint32
     hi = fmaxf(hi, w);
 }
 
+// The global histogram is gathered in kHistParts copies (workgroups of codes_kernel add theirs to one of them each), cleared
+// by the kernel in front.
+constexpr int kHistParts = 16;
+__device__ __forceinline__ void clear_histogram(unsigned long long* hist, FrontState* st) {  // one workgroup of 256 threads
+    for (int i = 0; i < kHistParts; ++i) hist[i * kCodes + threadIdx.x] = 0ull;
+    if (threadIdx.x == 0) {
+        st->flags = 0;
+        st->done = 0;
+    }
+}
+
 constexpr int kRangeParts = 1024;  // most workgroups of range_kernel: four per compute unit, eight loads in flight per thread
 
 // Partial results {min, max, not-finite flag}; the workgroups of codes_kernel finish the reduction themselves (one launch
 // less, 16 KiB of L2 reads per workgroup at most).  Bound by the read of W.
 __global__ __launch_bounds__(256) void range_kernel(const float* __restrict__ W, int64_t N, float4* __restrict__ part,
-                                                    FrontState* __restrict__ st) {
+                                                    unsigned long long* __restrict__ hist, FrontState* __restrict__ st) {
+    if (blockIdx.x == 0 && hist) clear_histogram(hist, st);
     float lo = INFINITY, hi = -INFINITY;
     uint32_t bad = 0;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
@@ -134,7 +146,7 @@ __global__ __launch_bounds__(256) void range_kernel(const float* __restrict__ W,
         const uint32_t any = s_bad[0] | s_bad[1] | s_bad[2] | s_bad[3];
         part[blockIdx.x] = make_float4(fminf(fminf(s_lo[0], s_lo[1]), fminf(s_lo[2], s_lo[3])),
                                        fmaxf(fmaxf(s_hi[0], s_hi[1]), fmaxf(s_hi[2], s_hi[3])), any ? 1.f : 0.f, 0.f);
-        if (blockIdx.x == 0) st->flags = 0;
+        if (blockIdx.x == 0 && !hist) st->flags = 0;
     }
 }
 
@@ -143,13 +155,11 @@ struct CodebookArg {
     float v[kCodes];
     uint32_t K;
 };
-__global__ __launch_bounds__(256) void codebook_kernel(CodebookArg cb, FrontState* __restrict__ st) {
+__global__ __launch_bounds__(256) void codebook_kernel(CodebookArg cb, unsigned long long* __restrict__ hist, FrontState* __restrict__ st) {
     const uint32_t t = threadIdx.x;
+    clear_histogram(hist, st);
     if (t < cb.K) st->codebook[t] = cb.v[t];
-    if (t == 0) {
-        st->flags = 0;
-        st->K = cb.K;
-    }
+    if (t == 0) st->K = cb.K;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -203,7 +213,8 @@ template <bool kQuant>
 __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W, int64_t total, int64_t rows, int64_t row_len,
                                                     const float4* __restrict__ part, int nparts, int bits,
                                                     FrontState* __restrict__ st, uint8_t* __restrict__ codes,
-                                                    uint32_t* __restrict__ cnt, float* __restrict__ Wq, int vec_ok) {
+                                                    uint32_t* __restrict__ cnt, unsigned long long* __restrict__ hist,
+                                                    float* __restrict__ Wq, int vec_ok) {
 #pragma clang fp contract(off)
     __shared__ uint32_t s_hist[kCodes];
     __shared__ float s_val[kCodes];
@@ -272,6 +283,7 @@ __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W,
     c.hkey = s_hkey;
     c.hpos = s_hpos;
     bool missing = false;
+    unsigned long long total_t = 0;  // occurrences of codebook position t in this workgroup's rows
     for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
         const float* row = W + r * row_len;
         uint8_t* crow = codes ? codes + r * row_len : nullptr;
@@ -322,115 +334,39 @@ __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W,
         if (cnt) {
             __syncthreads();
             cnt[r * kCodes + t] = s_hist[t];
+            total_t += s_hist[t];
             s_hist[t] = 0;
             __syncthreads();
         }
     }
+    if (cnt && total_t) atomicAdd(&hist[(blockIdx.x & (kHistParts - 1)) * kCodes + t], total_t);
     if (__syncthreads_or(missing) && t == 0) atomicOr(&st->flags, kFlagMissing);
-}
-
-// Global histogram = column sums of the per-row histograms, in at most kHistParts partial sums (one per workgroup of 1024
-// threads: four rows at a time) that the next kernel adds up.
-constexpr int kHistParts = 64;
-__global__ __launch_bounds__(1024) void hist_kernel(const uint32_t* __restrict__ cnt, int64_t m, int64_t rows_per_block,
-                                                    unsigned long long* __restrict__ part) {
-    __shared__ unsigned long long s_sum[4][kCodes];
-    const uint32_t pos = threadIdx.x & 255u, sub = threadIdx.x >> 8;
-    const int64_t r0 = (int64_t)blockIdx.x * rows_per_block, r1 = min(m, r0 + rows_per_block);
-    unsigned long long s = 0;
-    int64_t r = r0 + sub;
-    for (; r + 28 < r1; r += 32) {
-        uint32_t c[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) c[k] = cnt[(r + 4 * k) * kCodes + pos];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) s += c[k];
-    }
-    for (; r < r1; r += 4) s += cnt[r * kCodes + pos];
-    s_sum[sub][pos] = s;
-    __syncthreads();
-    if (sub == 0) part[(int64_t)blockIdx.x * kCodes + pos] = s_sum[0][pos] + s_sum[1][pos] + s_sum[2][pos] + s_sum[3][pos];
 }
 
 // ------------------------------------------------------------------------------------------------
 // layout: per row, the number of indexed elements, of groups and of non-empty groups.  One wave per row, sixteen rows per
-// workgroup; every workgroup first ranks the values for itself (one launch less than a kernel of its own).
+// workgroup; every workgroup first ranks the values for itself, and the last one to finish scans the rows (two launches less
+// than kernels of their own: 20 of the 70 us that a layer of 300 x 700 took went into such steps).
 //
 // Frequency-major order: higher count first, equal counts in codebook order; values that never occur are left out
 // (Section III-A, step 1).  Each thread finds its own value's position by counting who comes before it.
+//
+// scan: exclusive prefix sums of the rows' groups and indexed elements (m + 1 entries {groups, elements}), the number of
+// non-empty groups and the largest group count of a row; kScanRows consecutive rows per thread and round.  The sizes go to
+// the host from here.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void row_layout_kernel(const uint32_t* __restrict__ cnt, const unsigned long long* __restrict__ part,
-                                                          int nparts, int64_t m, int cser, FrontState* __restrict__ st,
-                                                          uint2* __restrict__ rowGN) {
-    __shared__ unsigned long long s_sum[4][kCodes];
-    __shared__ unsigned long long s_h[kCodes];
-    __shared__ uint32_t s_rank[kCodes];
-    const uint32_t t = threadIdx.x, lane = t & 63u, pos = t & 255u, sub = t >> 8, K = st->K;
-    {
-        unsigned long long s = 0;
-        for (int i = (int)sub; i < nparts; i += 4) s += part[(int64_t)i * kCodes + pos];
-        s_sum[sub][pos] = s;
-    }
-    __syncthreads();
-    if (sub == 0) s_h[pos] = pos < K ? s_sum[0][pos] + s_sum[1][pos] + s_sum[2][pos] + s_sum[3][pos] : 0ull;
-    __syncthreads();
-    // the four threads of a position compare it with a quarter of the others each
-    {
-        const unsigned long long c = s_h[pos];
-        uint32_t before = 0;
-        const uint32_t j0 = sub * 64u, j1 = min(K, j0 + 64u);
-        for (uint32_t j = j0; j < j1; ++j) {
-            const unsigned long long cj = s_h[j];
-            before += (cj > c) || (cj == c && j < pos);
-        }
-        s_sum[sub][pos] = before;
-    }
-    const int occurring = __syncthreads_count(sub == 0 && s_h[pos] > 0);
-    if (sub == 0) {
-        const unsigned long long c = s_h[pos];
-        const uint32_t before = (uint32_t)(s_sum[0][pos] + s_sum[1][pos] + s_sum[2][pos] + s_sum[3][pos]);
-        s_rank[pos] = c > 0 ? before : 0u;
-        if (blockIdx.x == 0) {
-            st->rank_of[pos] = c > 0 ? before : 0u;
-            if (c > 0) {
-                st->pos_of[before] = pos;
-                st->omega[before] = canonical(st->codebook[pos]);
-                st->count[before] = c;
-            }
-            if (t == 0) st->Kp = (uint32_t)occurring;
-        }
-    }
-    __syncthreads();
-    const int64_t r = (int64_t)blockIdx.x * 16 + (t >> 6);
-    if (r >= m) return;
-    uint32_t present = 0, topk = 0, nn = 0;
-#pragma unroll
-    for (int i = 0; i < kCodes / kWave; ++i) {
-        const uint32_t p = lane + 64u * i;
-        const uint32_t c = cnt[r * kCodes + p];
-        const uint32_t k = s_rank[p];
-        if (c > 0 && k >= 1) {
-            ++present;
-            topk = max(topk, k);
-            nn += c;
-        }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        present += __shfl_xor(present, off, kWave);
-        nn += __shfl_xor(nn, off, kWave);
-        topk = max(topk, (uint32_t)__shfl_xor((int)topk, off, kWave));
-    }
-    // groups (CER keeps the empty groups below the row's highest rank) | non-empty groups << 16, indexed elements
-    if (lane == 0) rowGN[r] = make_uint2((cser ? present : topk) | (present << 16), nn);
+constexpr int kScanRows = 4;
+
+// Between workgroups of one launch: past the L1 and the XCD's L2.
+__device__ __forceinline__ void store_shared(unsigned long long* p, unsigned long long v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long load_shared(const unsigned long long* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Exclusive prefix sums of the rows' groups and indexed elements (m + 1 entries {groups, elements}), the number of
-// non-empty groups and the largest group count of a row.  One workgroup, kScanRows consecutive rows per thread and round
-// (a 4096-row matrix is one round: 12.6 -> 5 us against one row per thread).  The result goes to the host from here.
-constexpr int kScanRows = 4;
-__global__ __launch_bounds__(1024) void scan_rows_kernel(const uint2* __restrict__ rowGN, int64_t m, uint2* __restrict__ rowStart,
-                                                         FrontState* __restrict__ st, FrontResult* __restrict__ out) {
+__device__ void scan_rows(const unsigned long long* __restrict__ rowGN, int64_t m, uint2* __restrict__ rowStart, FrontState* __restrict__ st,
+                          FrontResult* __restrict__ out) {
     __shared__ unsigned long long s_g[16], s_n[16], s_p[16];
     __shared__ uint32_t s_mx[16], s_ml[16];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
@@ -441,7 +377,10 @@ __global__ __launch_bounds__(1024) void scan_rows_kernel(const uint2* __restrict
         uint2 v[kScanRows];
         unsigned long long g = 0, nn = 0;
 #pragma unroll
-        for (int k = 0; k < kScanRows; ++k) v[k] = r0 + k < m ? rowGN[r0 + k] : make_uint2(0u, 0u);
+        for (int k = 0; k < kScanRows; ++k) {
+            const unsigned long long q = r0 + k < m ? load_shared(rowGN + r0 + k) : 0ull;
+            v[k] = make_uint2((uint32_t)q, (uint32_t)(q >> 32));
+        }
 #pragma unroll
         for (int k = 0; k < kScanRows; ++k) {
             my_p += v[k].x >> 16;
@@ -495,12 +434,6 @@ __global__ __launch_bounds__(1024) void scan_rows_kernel(const uint2* __restrict
         s_mx[wave] = my_mx;
         s_ml[wave] = my_ml;
     }
-    const uint32_t Kp = st->Kp, K = st->K;
-    if (t < Kp) {
-        out->count[t] = st->count[t];
-        out->omega[t] = st->omega[t];
-    }
-    if (t < K && t < (uint32_t)kCodes) out->codebook[t] = st->codebook[t];
     __syncthreads();
     if (t == 0) {
         unsigned long long p = 0;
@@ -514,17 +447,91 @@ __global__ __launch_bounds__(1024) void scan_rows_kernel(const uint2* __restrict
         // the product kernels address colI and OmegaPtr with 32-bit offsets and read ahead of a row's end
         const unsigned long long limit = 0xFFFFFFFFull - 65536;
         out->flags = st->flags | (carry_g > limit || carry_n > limit ? kFlagTooLarge : 0u);
-        out->K = K;
-        out->Kp = Kp;
+        out->K = st->K;
+        out->Kp = __hip_atomic_load(&st->Kp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         out->max_row_groups = mx;
         out->max_row_nnz = ml;
         out->nnz = carry_n;
         out->G = carry_g;
         out->nonempty = p;
+        __hip_atomic_store(&out->ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    __threadfence_system();
+}
+
+__global__ __launch_bounds__(1024) void row_layout_kernel(const uint32_t* __restrict__ cnt, const unsigned long long* __restrict__ hist,
+                                                          int64_t m, int cser, FrontState* __restrict__ st, unsigned long long* __restrict__ rowGN,
+                                                          uint2* __restrict__ rowStart, FrontResult* __restrict__ out) {
+    __shared__ unsigned long long s_sum[4][kCodes];
+    __shared__ unsigned long long s_h[kCodes];
+    __shared__ uint32_t s_rank[kCodes];
+    __shared__ uint32_t s_last;
+    const uint32_t t = threadIdx.x, lane = t & 63u, pos = t & 255u, sub = t >> 8, K = st->K;
+    // the row's histogram is on its way while the values are ranked
+    const int64_t r = (int64_t)blockIdx.x * 16 + (t >> 6);
+    uint32_t c4[kCodes / kWave];
+#pragma unroll
+    for (int i = 0; i < kCodes / kWave; ++i) c4[i] = cnt[min(r, m - 1) * kCodes + lane + 64u * i];
+    {
+        unsigned long long s = 0;
+#pragma unroll
+        for (int i = 0; i < kHistParts / 4; ++i) s += hist[(sub + 4 * i) * kCodes + pos];
+        s_sum[sub][pos] = s;
+    }
     __syncthreads();
-    if (t == 0) __hip_atomic_store(&out->ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (sub == 0) s_h[pos] = pos < K ? s_sum[0][pos] + s_sum[1][pos] + s_sum[2][pos] + s_sum[3][pos] : 0ull;
+    __syncthreads();
+    // the four threads of a position compare it with a quarter of the others each
+    {
+        const unsigned long long c = s_h[pos];
+        uint32_t before = 0;
+        const uint32_t j0 = sub * 64u, j1 = min(K, j0 + 64u);
+        for (uint32_t j = j0; j < j1; ++j) {
+            const unsigned long long cj = s_h[j];
+            before += (cj > c) || (cj == c && j < pos);
+        }
+        s_sum[sub][pos] = before;
+    }
+    const int occurring = __syncthreads_count(sub == 0 && s_h[pos] > 0);
+    if (sub == 0) {
+        const unsigned long long c = s_h[pos];
+        const uint32_t before = (uint32_t)(s_sum[0][pos] + s_sum[1][pos] + s_sum[2][pos] + s_sum[3][pos]);
+        s_rank[pos] = c > 0 ? before : 0u;
+        if (blockIdx.x == 0) {
+            st->rank_of[pos] = c > 0 ? before : 0u;
+            if (c > 0) {
+                st->pos_of[before] = pos;
+                st->omega[before] = canonical(st->codebook[pos]);
+                st->count[before] = c;
+            }
+        }
+    }
+    if (blockIdx.x == 0 && t == 0) __hip_atomic_store(&st->Kp, (uint32_t)occurring, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    uint32_t present = 0, topk = 0, nn = 0;
+#pragma unroll
+    for (int i = 0; i < kCodes / kWave; ++i) {
+        const uint32_t k = s_rank[lane + 64u * i];
+        if (c4[i] > 0 && k >= 1) {
+            ++present;
+            topk = max(topk, k);
+            nn += c4[i];
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        present += __shfl_xor(present, off, kWave);
+        nn += __shfl_xor(nn, off, kWave);
+        topk = max(topk, (uint32_t)__shfl_xor((int)topk, off, kWave));
+    }
+    // groups (CER keeps the empty groups below the row's highest rank) | non-empty groups << 16, indexed elements
+    if (lane == 0 && r < m) store_shared(&rowGN[r], ((unsigned long long)nn << 32) | (cser ? present : topk) | (present << 16));
+    // The last workgroup scans the rows.  What it reads from the others goes past the caches of their XCDs and has arrived when
+    // their threads meet at the barrier; a fence per wave would write whole caches back (80 us for 4096 rows).
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (t == 0) s_last = __hip_atomic_fetch_add(&st->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u ? 1u : 0u;
+    __syncthreads();
+    if (s_last) scan_rows(rowGN, m, rowStart, st, out);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -573,18 +580,25 @@ struct EmitTarget {
     size_t gap_begin[8], gap_end[8];
 };
 
-// Four rows per workgroup; the last workgroup writes Omega and clears the gaps.
+// Four rows per workgroup; the last workgroup writes Omega, clears the gaps and tells the host the values.
 template <typename ColT, typename OiT>
 __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ codes, const uint32_t* __restrict__ cnt,
                                                    const uint2* __restrict__ rowStart, const FrontState* __restrict__ st,
-                                                   int64_t m, int64_t n, int cser, int sparse, EmitTarget to) {
+                                                   int64_t m, int64_t n, int cser, int sparse, EmitTarget to,
+                                                   FrontResult* __restrict__ out) {
     __shared__ uint32_t s_rank[kCodes];
     __shared__ uint32_t s_fill[4][kCodes];  // next free colI slot of each rank's bucket
     __shared__ uint32_t s_stage[4][kEmitStage];  // (column << 8) | rank of the columns waiting for the scatter
     __shared__ unsigned long long s_marks[4][kCodes];  // per rank: the lanes of the current batch that hold it
     if (blockIdx.x == gridDim.x - 1) {
         const uint32_t t = threadIdx.x;
-        if (t < st->Kp) reinterpret_cast<float*>(to.base + to.off_om)[t] = st->omega[t];
+        if (t < st->Kp) {
+            const float w = st->omega[t];
+            reinterpret_cast<float*>(to.base + to.off_om)[t] = w;
+            out->omega[t] = w;
+            out->count[t] = st->count[t];
+        }
+        if (t < st->K) out->codebook[t] = st->codebook[t];
         for (int g = 0; g < to.ngaps; ++g)
             for (size_t o = to.gap_begin[g] + t; o < to.gap_end[g]; o += 256) to.base[o] = 0;
         return;
@@ -1106,16 +1120,16 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // Enqueues range (bits > 0) or the caller's codebook, then codes + per-row histograms (cnt != nullptr) over `rows` rows of
 // row_len elements (the last one possibly shorter).  `part`: kRangeParts float4.
 int run_codes(const float* W, int64_t total, int64_t rows, int64_t row_len, const float* codebook, int32_t K, int32_t bits,
-              hipStream_t s, FrontState* st_dev, float4* part, uint8_t* codes, uint32_t* cnt, float* Wq) {
+              hipStream_t s, FrontState* st_dev, float4* part, uint8_t* codes, uint32_t* cnt, unsigned long long* hist, float* Wq) {
     const int vec_ok = (row_len % 4 == 0 && aligned16(W) && (!Wq || aligned16(Wq)) &&
                         (!codes || (reinterpret_cast<uintptr_t>(codes) & 3u) == 0)) ? 1 : 0;
     // workgroups walk several rows where that still leaves eight of them per compute unit: their prologue is shared
     const unsigned blocks = (unsigned)std::min<int64_t>(rows, 2048);
     if (bits > 0) {
         const int nparts = (int)std::min<int64_t>(kRangeParts, (total + 1023) / 1024);
-        HIP_TRY(cer::launch_kernel(range_kernel, dim3(nparts), dim3(256), 0, s, W, total, part, st_dev));
+        HIP_TRY(cer::launch_kernel(range_kernel, dim3(nparts), dim3(256), 0, s, W, total, part, hist, st_dev));
         HIP_TRY(cer::launch_kernel(codes_kernel<true>, dim3(blocks), dim3(256), 0, s, W, total, rows, row_len, part, nparts, bits,
-                                   st_dev, codes, cnt, Wq, vec_ok));
+                                   st_dev, codes, cnt, hist, Wq, vec_ok));
     } else {
         // duplicates and non-finite values are refused
         CodebookArg cb;
@@ -1129,9 +1143,9 @@ int run_codes(const float* W, int64_t total, int64_t rows, int64_t row_len, cons
         std::sort(sorted, sorted + K);
         if (std::adjacent_find(sorted, sorted + K) != sorted + K) return CER_E_BAD_CODEBOOK;
         cb.K = (uint32_t)K;
-        HIP_TRY(cer::launch_kernel(codebook_kernel, dim3(1), dim3(256), 0, s, cb, st_dev));
+        HIP_TRY(cer::launch_kernel(codebook_kernel, dim3(1), dim3(256), 0, s, cb, hist, st_dev));
         HIP_TRY(cer::launch_kernel(codes_kernel<false>, dim3(blocks), dim3(256), 0, s, W, total, rows, row_len, part, 0, 0, st_dev,
-                                   codes, cnt, (float*)nullptr, vec_ok));
+                                   codes, cnt, hist, (float*)nullptr, vec_ok));
     }
     return CER_OK;
 }
@@ -1204,10 +1218,10 @@ int flags_to_error(uint32_t flags) {
 
 template <typename ColT>
 hipError_t launch_emit(hipStream_t s, const uint8_t* codes, const uint32_t* cnt, const uint2* rowStart, const FrontState* st,
-                       int64_t m, int64_t n, int cser, int sparse, const EmitTarget& to) {
+                       int64_t m, int64_t n, int cser, int sparse, const EmitTarget& to, FrontResult* out) {
     // rank < K <= 256, so OmegaI is always one byte wide here
     return cer::launch_kernel(emit_kernel<ColT, uint8_t>, dim3((unsigned)((m + 3) / 4 + 1)), dim3(256), 0, s, codes, cnt, rowStart,
-                              st, m, n, cser, sparse, to);
+                              st, m, n, cser, sparse, to, out);
 }
 
 }  // namespace
@@ -1306,7 +1320,7 @@ int quantize_device(const float* W, int64_t count, int32_t bits, uint8_t* codes,
     HIP_TRY(tmp.alloc(kRangeParts * sizeof(float4) + sizeof(FrontState), s));
     float4* part = tmp.as<float4>();
     FrontState* st = reinterpret_cast<FrontState*>(part + kRangeParts);
-    int rc = run_codes(W, count, rows, row_len, nullptr, 0, bits, s, st, part, codes, nullptr, Wq);
+    int rc = run_codes(W, count, rows, row_len, nullptr, 0, bits, s, st, part, codes, nullptr, nullptr, Wq);
     if (rc != CER_OK) return rc;
     FrontState h;
     HIP_TRY(hipMemcpyAsync(&h, st, sizeof h, hipMemcpyDeviceToHost, s));
@@ -1339,25 +1353,19 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     FrontState* sd = reinterpret_cast<FrontState*>(tp);
     uint8_t* codes_d = tp + off_codes;
     uint32_t* cnt_d = reinterpret_cast<uint32_t*>(tp + off_cnt);
-    uint2* rowGN = reinterpret_cast<uint2*>(tp + off_gn);
+    auto* rowGN = reinterpret_cast<unsigned long long*>(tp + off_gn);
     uint2* rowStart = reinterpret_cast<uint2*>(tp + off_start);
     auto* hist = reinterpret_cast<unsigned long long*>(tp + off_hist);
 
-    int rc = run_codes(W, N, m, n, codebook, K, bits, s, sd, reinterpret_cast<float4*>(tp + off_part), codes_d, cnt_d, nullptr);
+    int rc = run_codes(W, N, m, n, codebook, K, bits, s, sd, reinterpret_cast<float4*>(tp + off_part), codes_d, cnt_d, hist, nullptr);
     if (rc != CER_OK) return rc;
-    const int64_t rows_per_part = std::max<int64_t>(8, (m + kHistParts - 1) / kHistParts);
-    const int hist_parts = (int)((m + rows_per_part - 1) / rows_per_part);
-    HIP_TRY(launch_kernel(hist_kernel, dim3(hist_parts), dim3(1024), 0, s, cnt_d, m, rows_per_part, hist));
-    HIP_TRY(launch_kernel(row_layout_kernel, dim3((unsigned)((m + 15) / 16)), dim3(1024), 0, s, cnt_d, hist, hist_parts, m,
-                          cser ? 1 : 0, sd, rowGN));
     box.busy = true;
-    HIP_TRY(launch_kernel(scan_rows_kernel, dim3(1), dim3(1024), 0, s, rowGN, m, rowStart, sd, box.p));
+    HIP_TRY(launch_kernel(row_layout_kernel, dim3((unsigned)((m + 15) / 16)), dim3(1024), 0, s, cnt_d, hist, m, cser ? 1 : 0, sd, rowGN,
+                          rowStart, box.p));
     HIP_TRY(box.wait(s));
     const FrontResult& h = *box.p;
     rc = flags_to_error(h.flags);
     if (rc != CER_OK) return rc;
-    if (K_out) *K_out = (int32_t)h.K;
-    if (codebook_out) std::memcpy(codebook_out, h.codebook, (size_t)h.K * 4);
 
     // sizes are known: the handle's own allocation, filled in place by the emit kernel
     auto A = std::make_shared<HostMatrix>();
@@ -1369,8 +1377,6 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     A->G = (int64_t)h.G;
     A->nonempty_groups = (int64_t)h.nonempty;
     A->max_row_groups = (int64_t)h.max_row_groups;
-    A->omega.assign(h.omega, h.omega + h.Kp);
-    A->count.assign(h.count, h.count + h.Kp);
     // the index arrays stay on the device until somebody asks for them on the host
     A->colI.len = A->nnz;
     A->colI.bits = min_index_bits(n > 0 ? (uint64_t)(n - 1) : 0);
@@ -1386,12 +1392,14 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     const size_t colI_bytes = (size_t)A->nnz * (size_t)(A->colI.bits / 8);
     const size_t oi_bytes = cser ? (size_t)A->G * (size_t)(A->omegaI.bits / 8) : 0;
     const DeviceLayout l = DeviceLayout::make(colI_bytes, A->G, m, oi_bytes, A->K);
+    A->omega.resize(h.Kp);
+    A->count.resize(h.Kp);
     std::unique_ptr<cer_matrix, void (*)(cer_handle_t*)> hnd(new cer_matrix(), cer_free);
-    hnd->host = std::move(A);
+    hnd->host = A;
     if (s) hnd->off_null_stream.store(true, std::memory_order_relaxed);
     void* base = nullptr;
     HIP_TRY((hipError_t)handle_alloc(&base, l.total, s));
-    bind_device(hnd.get(), dev, base, l);
+    hnd->d_base = base;
 
     EmitTarget to;
     std::memset(&to, 0, sizeof to);
@@ -1420,12 +1428,19 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     const int sp = (double)h.nnz * 2.0 < (double)m * (double)n ? 1 : 0;
     hipError_t e = hipSuccess;
     switch (hnd->host->colI.bits) {
-        case 8: e = launch_emit<uint8_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to); break;
-        case 16: e = launch_emit<uint16_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to); break;
-        default: e = launch_emit<uint32_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to);
+        case 8: e = launch_emit<uint8_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to, box.p); break;
+        case 16: e = launch_emit<uint16_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to, box.p); break;
+        default: e = launch_emit<uint32_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to, box.p);
     }
+    box.busy = true;
     HIP_TRY(e);
     HIP_TRY(hipStreamSynchronize(s));  // the handle is complete for every stream; errors surface here
+    box.busy = false;
+    std::copy_n(h.omega, h.Kp, A->omega.begin());
+    std::copy_n(h.count, h.Kp, A->count.begin());
+    bind_device(hnd.get(), dev, base, l);
+    if (K_out) *K_out = (int32_t)h.K;
+    if (codebook_out) std::memcpy(codebook_out, h.codebook, (size_t)h.K * 4);
     // rows of unequal length: the batched product wants them ordered (and the longest in parts); the row starts
     // come back from the device only when the longest row says that the table will be built
     if (row_schedule_wanted((uint64_t)h.nnz, (uint64_t)m, (uint64_t)h.max_row_nnz)) {
