@@ -146,7 +146,8 @@ int cer_matmul_noalloc(const cer_handle_t* h, const float* X_dev, float* Y_dev, 
  * conversions that need a temporary (see each call) take it, ordered on the caller's stream, from
  * blocks the library keeps on the current device; they are kept (at most 2 GiB of them) because getting
  * a few hundred megabytes from the system again costs more than the product that needs them.  The
- * device memory of freed handles is kept in the same way for later handles (at most 1 GiB).  cer_trim
+ * device memory of freed handles is kept in the same way for later handles (at most 1 GiB), and the host
+ * conversions keep up to 15 sleeping threads and 16 MiB of pinned memory.  cer_trim
  * releases whatever is not in use at the moment of the call on the current device; it may wait for
  * work queued on the null stream and may be called at any time.  Errors: CER_E_HIP.
  */

@@ -1038,6 +1038,7 @@ int cer_stream_read(const void* src, int64_t bytes, void* sink, void* stream) {
 }
 
 int cer_trim(void) {
+    cer::stop_host_threads();
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return hip_fail(hipGetLastError());
     if (dev < 0 || dev >= 16) return CER_OK;

@@ -1,6 +1,6 @@
 // Host-side encoder and decoder of the CER / CSER formats (Section III-A of the paper).
 //
-// The encoder is a row-parallel counting sort; one team of threads goes through all its steps:
+// The encoder is a row-parallel counting sort; a team of threads goes through all its steps:
 //   symbols  element -> codebook symbol through a hash of the fp32 bit pattern; per-row histograms
 //   (order)  symbols ranked by count (Section III-A step 1: frequency-major Omega)
 //   sizes    per row: number of indexed elements and of groups
@@ -14,9 +14,16 @@
 #include <cstring>
 #include <numeric>
 #include <system_error>
+#include <mutex>
+#include <new>
 #include <thread>
 
+#include <climits>
 #include <emmintrin.h>
+#include <linux/futex.h>
+#include <pthread.h>
+#include <sys/syscall.h>
+#include <unistd.h>
 
 #include "../../include/cer.h"
 #include "cer_internal.hpp"
@@ -105,23 +112,124 @@ int worker_count(int64_t rows, int64_t work) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(t, rows));
 }
 
+// Threads that wait between calls: starting 15 of them takes 160 us, waking them 20 (a 2048 x 2048 layer is encoded in
+// 500).  At most 15; they sleep on a futex after having looked for work for about 50 us; a fork leaves the child without them
+// (it starts its own).  One call at a time uses them, a call that finds them busy starts threads for itself.
+class Workers {
+public:
+    using Job = void (*)(void* ctx, int t);
+    // job(ctx, t) for t = 0 .. threads - 1, 0 on the calling thread; returns false (nothing has run) if they are busy
+    static bool run(int threads, Job job, void* ctx) {
+        Workers* w = instance();
+        if (!w || threads > kMost + 1 || !w->mu_.try_lock()) return false;
+        std::lock_guard<std::mutex> hold(w->mu_, std::adopt_lock);
+        while (w->started_ < threads - 1) {
+            try {
+                std::thread(&Workers::loop, w, w->started_ + 1, w->turn_.load(std::memory_order_relaxed)).detach();
+            } catch (const std::system_error&) {
+                return false;
+            }
+            ++w->started_;
+        }
+        w->job_ = job;
+        w->ctx_ = ctx;
+        w->members_ = threads;
+        w->left_.store(w->started_, std::memory_order_relaxed);
+        w->turn_.fetch_add(1, std::memory_order_seq_cst);
+        if (w->asleep_.load(std::memory_order_seq_cst) > 0) syscall(SYS_futex, &w->turn_, FUTEX_WAKE_PRIVATE, INT_MAX, nullptr, nullptr, 0);
+        job(ctx, 0);
+        for (int spins = 0; w->left_.load(std::memory_order_acquire) > 0; ++spins) {
+            if (spins < 4000) _mm_pause(); else std::this_thread::yield();
+        }
+        return true;
+    }
+
+    // Ends the threads (they are started again when needed), unless they are busy.
+    static void stop() {
+        Workers* w = slot().load(std::memory_order_acquire);
+        if (!w || !w->mu_.try_lock()) return;
+        std::lock_guard<std::mutex> hold(w->mu_, std::adopt_lock);
+        w->quit_ = true;
+        w->left_.store(w->started_, std::memory_order_relaxed);
+        w->turn_.fetch_add(1, std::memory_order_seq_cst);
+        syscall(SYS_futex, &w->turn_, FUTEX_WAKE_PRIVATE, INT_MAX, nullptr, nullptr, 0);
+        while (w->left_.load(std::memory_order_acquire) > 0) std::this_thread::yield();
+        w->started_ = 0;
+        w->quit_ = false;
+    }
+
+private:
+    static constexpr int kMost = 15;
+    static std::atomic<Workers*>& slot() {
+        static std::atomic<Workers*> s{nullptr};
+        return s;
+    }
+    static Workers* instance() {
+        Workers* w = slot().load(std::memory_order_acquire);
+        if (w) return w;
+        static std::mutex mu;
+        std::lock_guard<std::mutex> hold(mu);
+        w = slot().load(std::memory_order_acquire);
+        if (w) return w;
+        static bool once = pthread_atfork(nullptr, nullptr, [] { slot().store(nullptr); }) == 0;
+        if (!once) return nullptr;
+        w = new (std::nothrow) Workers();  // never destroyed: its threads wait in it until the process ends
+        slot().store(w, std::memory_order_release);
+        return w;
+    }
+    void loop(int t, uint32_t seen) {
+        for (;;) {
+            uint32_t now = turn_.load(std::memory_order_acquire);
+            for (int spins = 0; now == seen; now = turn_.load(std::memory_order_acquire)) {
+                if (++spins < 1500) {
+                    _mm_pause();
+                    continue;
+                }
+                asleep_.fetch_add(1, std::memory_order_seq_cst);
+                if (turn_.load(std::memory_order_seq_cst) == seen)
+                    syscall(SYS_futex, &turn_, FUTEX_WAIT_PRIVATE, seen, nullptr, nullptr, 0);
+                asleep_.fetch_sub(1, std::memory_order_relaxed);
+            }
+            seen = now;
+            const bool quit = quit_;
+            if (!quit && t < members_) job_(ctx_, t);
+            left_.fetch_sub(1, std::memory_order_acq_rel);
+            if (quit) return;
+        }
+    }
+    std::mutex mu_;
+    std::atomic<uint32_t> turn_{0};
+    std::atomic<int> asleep_{0}, left_{0};
+    int started_ = 0, members_ = 0;
+    bool quit_ = false;
+    Job job_ = nullptr;
+    void* ctx_ = nullptr;
+};
+
 // A team runs body(t, r0, r1, team) on its threads, each with a contiguous share of m rows; sync() waits for all of them.
-// The bodies must not throw (what they need is allocated before).  Threads are started once per call: 16 of them take
-// about as long as one pass over a layer.
+// The bodies must not throw (what they need is allocated before).
 class Team {
 public:
     template <typename F>
     static void run(int threads, int64_t m, F&& body) {
         Team team;
-        std::vector<std::thread> pool;
         auto work = [&](int t) {
-            while (team.size_.load(std::memory_order_acquire) == 0) std::this_thread::yield();
             const int n = team.size_.load(std::memory_order_relaxed);
             body(t, m * t / n, m * (t + 1) / n, team);
         };
-        pool.reserve((size_t)std::max(threads - 1, 0));
+        team.size_.store(threads, std::memory_order_relaxed);
+        if (threads == 1) return work(0);
+        using Work = decltype(work);
+        if (Workers::run(threads, [](void* ctx, int t) { (*static_cast<Work*>(ctx))(t); }, &work)) return;
+        team.size_.store(0, std::memory_order_relaxed);
+        std::vector<std::thread> pool;
+        pool.reserve((size_t)threads - 1);
         try {
-            for (int t = 1; t < threads; ++t) pool.emplace_back(work, t);
+            for (int t = 1; t < threads; ++t)
+                pool.emplace_back([&team, &work, t] {
+                    while (team.size_.load(std::memory_order_acquire) == 0) std::this_thread::yield();
+                    work(t);
+                });
         } catch (const std::system_error&) {  // no more threads to be had: the ones there are share the rows
         }
         team.size_.store((int)pool.size() + 1, std::memory_order_release);
@@ -137,7 +245,7 @@ public:
             return;
         }
         for (int spins = 0; turn_.load(std::memory_order_acquire) == turn; ++spins) {
-            if (spins < 2000) _mm_pause(); else std::this_thread::yield();
+            if (spins < 4000) _mm_pause(); else std::this_thread::yield();
         }
     }
 
@@ -160,9 +268,11 @@ void shape(HostArray& a, uint64_t len, int bits) {
 }
 
 // Symbols of one row and their histogram (four interleaved ones: a value that follows itself does not wait for its own
-// last increment); false: an element is no codebook value.
+// last increment); false: an element is no codebook value.  `likely`: the symbol to expect (and its bit pattern): sixteen
+// elements are compared with it at once, and only the others are looked up.
 template <typename SymT>
-bool row_symbols(const SymbolTable& table, const float* W, int64_t n, int32_t K, SymT* sym, uint32_t* h4, uint32_t* c) {
+bool row_symbols(const SymbolTable& table, const float* W, int64_t n, int32_t K, int32_t likely, uint32_t likely_key, SymT* sym,
+                 uint32_t* h4, uint32_t* c) {
     std::fill(h4, h4 + 4 * (size_t)K, 0u);
     uint32_t bad = 0;
     int64_t j = 0;
@@ -174,6 +284,24 @@ bool row_symbols(const SymbolTable& table, const float* W, int64_t n, int32_t K,
             sym[i] = (SymT)s.sym;
             ++h[s.sym];
         };
+        if (sizeof(SymT) == 1) {
+            const __m128i want = _mm_set1_epi32((int)likely_key), fill = _mm_set1_epi8((char)likely);
+            int64_t others = 0;
+            for (; j + 16 <= n; j += 16) {
+                const __m128i* p = reinterpret_cast<const __m128i*>(W + j);
+                const __m128i a = _mm_cmpeq_epi32(_mm_loadu_si128(p), want), b = _mm_cmpeq_epi32(_mm_loadu_si128(p + 1), want);
+                const __m128i d = _mm_cmpeq_epi32(_mm_loadu_si128(p + 2), want), e = _mm_cmpeq_epi32(_mm_loadu_si128(p + 3), want);
+                uint32_t rest = 0xFFFFu ^ (uint32_t)_mm_movemask_epi8(_mm_packs_epi16(_mm_packs_epi32(a, b), _mm_packs_epi32(d, e)));
+                _mm_storeu_si128(reinterpret_cast<__m128i*>(sym + j), fill);
+                others += __builtin_popcount(rest);
+                uint32_t* h = h4;
+                for (; rest; rest &= rest - 1u) {
+                    one(j + __builtin_ctz(rest), h);
+                    h = h == h4 ? h4 + K : h4;
+                }
+            }
+            h4[likely] += (uint32_t)(j - others);
+        }
         for (; j + 4 <= n; j += 4) {
             one(j, h4);
             one(j + 1, h4 + K);
@@ -249,10 +377,12 @@ int encode_rows(const float* W, int64_t m, int64_t n, const float* codebook, int
         uint32_t* fill = own + Kz;
         int64_t* sum = total.data() + (size_t)t * Kz;
         bool ok = true;
+        int32_t likely = 0;  // the most frequent symbol of the rows so far
         for (int64_t r = r0; r < r1 && ok; ++r) {
             uint32_t* c = keep ? rows_c.get() + (size_t)r * Kz : own;
-            ok = row_symbols<SymT>(table, W + r * n, n, Kc, sym.get() + r * n, h4, c);
+            ok = row_symbols<SymT>(table, W + r * n, n, Kc, likely, Kc > 0 ? value_bits(codebook[likely]) : 0u, sym.get() + r * n, h4, c);
             for (int32_t k = 0; k < Kc; ++k) sum[k] += c[k];
+            likely = (int32_t)(std::max_element(sum, sum + Kc) - sum);
         }
         if (!ok) missing.store(true);
         team.sync();
@@ -371,6 +501,8 @@ void decode_rows(const HostMatrix& A, float* W, int64_t r0, int64_t r1) {
 }
 
 }  // namespace
+
+void stop_host_threads() { Workers::stop(); }
 
 int min_index_bits(uint64_t max_value) {
     return max_value <= 0xFFu ? 8 : (max_value <= 0xFFFFu ? 16 : 32);

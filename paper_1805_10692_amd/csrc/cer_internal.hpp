@@ -110,6 +110,7 @@ int encode_host(const float* W, int64_t m, int64_t n, const float* codebook, int
                 std::shared_ptr<HostMatrix>* out);
 int decode_host(const HostMatrix& A, float* W_out);
 int min_index_bits(uint64_t max_value);
+void stop_host_threads();  // the threads that both keep asleep between calls
 
 // Per-call choices of cer_matmul_ex (include/cer.h: cer_matmul_opts_t); the defaults are what cer_matmul does.
 struct MatmulOptions {
