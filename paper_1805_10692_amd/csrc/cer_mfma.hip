@@ -290,10 +290,11 @@ struct MfmaShape {
     double us;  // estimate of the product (without the decode)
 };
 
-// The launch lasts as long as the busiest compute unit: its share of the workgroups, one after the other (two resident ones
-// overlap, but share the matrix cores).  Measured per unit: 4.1 - 4.7 TFLOP/s with BN = 64, bound by the operands' bytes with
+// The launch lasts as long as the busiest compute unit: its share of the workgroups, one after the other (two resident ones --
+// one-piece codebooks with BN = 64 -- overlap, but share the matrix cores: `alone` and `together` scale the time of a round).  Measured per unit: 4.1 - 4.7 TFLOP/s with BN = 64, bound by the operands' bytes with
 // BN = 32; the small tiles 2.4 - 3.5 TFLOP/s.  A split along n costs its partial sums, written and read again.
-void shape_splits(const DeviceView& d, uint32_t L, uint32_t round, double round_us, double fixed_us, MfmaShape* s) {
+void shape_splits(const DeviceView& d, uint32_t L, uint32_t round, double round_us, double alone, double together,
+                  double fixed_us, MfmaShape* s) {
     const uint32_t pitch = ((uint32_t)d.n + kPitchStep - 1) / kPitchStep * kPitchStep, rounds = (pitch + round - 1) / round;
     s->row_tiles = (uint32_t)((d.m + s->BM - 1) / s->BM);
     s->col_tiles = (L + s->BN - 1) / s->BN;
@@ -302,7 +303,8 @@ void shape_splits(const DeviceView& d, uint32_t L, uint32_t round, double round_
     s->us = 1e300;
     for (uint32_t sp = 1; sp <= std::min(most, 64u); ++sp) {
         const uint32_t per = (rounds + sp - 1) / sp, used = (rounds + per - 1) / per;
-        double us = std::ceil(tiles * used / units) * per * round_us + fixed_us;
+        const double share = std::ceil(tiles * used / units);
+        double us = share * per * round_us * (share < 2 ? alone : together) + fixed_us;
         if (used > 1) us += 3.0 + (double)used * d.m * L * 8.0 / 6.5e6;
         if (us < s->us) {
             s->us = us;
@@ -321,7 +323,8 @@ MfmaShape mfma_shape(const DeviceView& d, uint32_t L) {
     {
         const uint32_t round = mfma_depth(d.pieces, big.BN) * 2048 / big.BN;  // columns per round of the kernel
         const double flops = 2.0 * big.BM * big.BN * round * products, bytes = (double)round * (big.BM * 2.0 * d.pieces + big.BN * 4.0);
-        shape_splits(d, L, round, std::max(flops / 4.3e6, bytes / 3.0e4), 4.0, &big);
+        shape_splits(d, L, round, big.BN == 32 ? std::max(flops / 4.3e6, bytes / 3.0e4) : flops / 4.4e6,
+                     d.pieces == 1 ? 1.12 : 1.0, d.pieces == 1 ? 0.95 : 1.0, 4.0, &big);
     }
     MfmaShape small;
     small.small = true;
@@ -329,7 +332,8 @@ MfmaShape mfma_shape(const DeviceView& d, uint32_t L) {
     small.BM = 64;
     {
         const double flops = 2.0 * small.BM * small.BN * 128 * products;
-        shape_splits(d, L, 128, flops / (d.pieces == 1 ? 3.5e6 : (d.pieces == 2 ? 2.9e6 : 2.4e6)), 3.0, &small);
+        shape_splits(d, L, 128, flops / (d.pieces == 1 ? 3.5e6 : (d.pieces == 2 ? 2.9e6 : 2.4e6)), d.pieces == 1 && small.BN == 64 ? 1.5 : 1.0, 1.0,
+                     3.0, &small);
     }
     return small.us < big.us ? small : big;
 }
