@@ -639,6 +639,7 @@ int upload(cer_matrix* h) {
     uint64_t longest = 0;
     for (int64_t r = 0; r < A.m; ++r)
         longest = std::max<uint64_t>(longest, info[(size_t)r * 2 + 3] - info[(size_t)r * 2 + 1]);
+    h->view.longest_row = (uint32_t)longest;
     if (!cer::row_schedule_wanted((uint64_t)A.nnz, (uint64_t)A.m, longest)) return CER_OK;
     std::vector<uint64_t> start((size_t)A.m + 1);
     for (int64_t r = 0; r <= A.m; ++r) start[(size_t)r] = info[(size_t)r * 2 + 1];

@@ -386,6 +386,9 @@ hipError_t launch_gemv_any(const DeviceView& d, const float* X, float* Y, const 
 hipError_t launch_gemm_any(const DeviceView& d, const float* X, float* Y, const float* T, uint32_t L, hipStream_t stream,
                            const MatmulOptions& o);
 
+// Estimate of its time in microseconds: the lines it gathers, or the walk of its longest row.
+double gemm_gather_us(const DeviceView& d, uint32_t L);
+
 // cer_xtile.hip -- batch > 1, a tile of X resident in LDS.  valid == false: not applicable to this matrix / batch.
 struct XtilePlan {
     bool valid = false;

@@ -543,14 +543,26 @@ hipError_t launch_gemm_ragged(const KView& k, const float* X, float* Y, const fl
                            Y, L, ntiles, rowblocks, ipx, k.m, T, k, SplitArgs{});
 }
 
+struct RowLengths {
+    double nnz, longest;  // indexed elements; positions of the longest row (or part of a row) that one wave walks
+};
+RowLengths row_lengths(const DeviceView& d, bool whole) {
+    const double longest = (double)std::max<uint32_t>(d.longest_row, 1u);
+    return {(double)d.nnz, !whole && d.n_split_parts ? std::min(longest, (double)d.split_min) : longest};
+}
+
 // Tile width (32, 64 or 128 batch columns) for a batch wider than 32 columns.  A gather instruction costs what the
 // cache lines it touches cost: when a row of X is a whole number of 128-byte lines, 32-column tiles touch exactly the
 // lines they need; otherwise every piece of a row touches up to one line more than its width, and wider tiles mean
-// fewer pieces.  Against that stand the lanes a wide tile leaves idle on a narrow batch and the waves it leaves
-// unlaunched on a matrix of few rows.  Measured on MI355X (AlexNet-fc6 shape, 32 / 64 / 128 columns per tile):
-// batch 96: 91 / 115 / 107 us; batch 100: 186 / 145 / 120 us; batch 40: 99 / 67 / 105 us; 3x3 convolution shape,
-// batch 100 (512 rows): 35 / 30 / 44 us.
-uint32_t pick_wide_tile(uint32_t L, uint32_t m, const float* X, uint32_t max_tile) {
+// fewer pieces.  Against that stand the gather instructions, which take 8.5 ns of a CU's time each whether their lanes are used
+// or not, and the walk of the longest row: a wave takes 256 / (columns per tile) positions per step of about 42 ns.  Measured on MI355X (AlexNet-fc6 shape, 32 / 64 / 128 columns per tile): batch 96: 91 / 115 / 107 us; batch 100:
+// 186 / 145 / 120 us; batch 40: 99 / 67 / 105 us; 3x3 convolution shape, batch 100 (512 rows): 35 / 30 / 44 us; 1254 x 4277, 19 %
+// indexed, rows of up to 4277 positions, batch 74: 46 us with 32 columns, 94 with 128.
+struct WideTile {
+    uint32_t cols;
+    double us;  // estimate of the whole product
+};
+WideTile pick_wide_tile(uint32_t L, const RowLengths& rows, const float* X, uint32_t max_tile) {
     const uint32_t row_bytes = L * 4u, base = (uint32_t)(reinterpret_cast<uintptr_t>(X) & 127u);
     const uint32_t step = std::gcd(row_bytes, 128u);  // rows start at base + multiples of this within a line
     auto lines = [&](uint32_t offset, uint32_t bytes) {  // average number of lines a piece of a row touches
@@ -559,25 +571,21 @@ uint32_t pick_wide_tile(uint32_t L, uint32_t m, const float* X, uint32_t max_til
         for (uint32_t ph = 0; ph < 128u; ph += step, ++cnt) sum += (double)(((base + ph + offset) % 128u + bytes + 127u) / 128u);
         return sum / cnt;
     };
-    uint32_t best_tile = 32;
-    double best = 1e300;
+    WideTile best{32, 1e300};
     for (uint32_t tw = 32; tw <= max_tile; tw *= 2) {
         const uint32_t ntiles = (L + tw - 1) / tw, last_cols = L - (ntiles - 1) * tw;
-        const double fill = (double)L / ((double)ntiles * tw);
-        const double waves = (double)m * ntiles;
         double cost = (ntiles - 1) * lines(0, tw * 4u) + lines(((ntiles - 1) * tw * 4u) % 128u, last_cols * 4u);
-        cost *= std::max(1.0, 0.62 / fill) / std::min(1.0, waves / 1024.0);
-        if (cost < 0.95 * best) {
-            best = cost;
-            best_tile = tw;
-        }
+        const double traffic = std::max(cost * rows.nnz * 128.0 / 27e6, ntiles * rows.nnz * (tw / 256.0) * 33e-6);
+        const double walk = rows.longest * (tw / 256.0) * 0.042;
+        cost = std::max(traffic, walk) + 0.3 * std::min(traffic, walk);
+        if (cost < best.us) best = {tw, cost};
     }
-    return best_tile;
+    return best;
 }
 
 template <typename IdxT>
 hipError_t launch_gemm(const KView& k, const float* X, float* Y, const float* T, uint32_t L, hipStream_t stream,
-                       const SplitArgs& sp, bool short_rows, const MatmulOptions& o) {
+                       const SplitArgs& sp, bool short_rows, const RowLengths& rows, const MatmulOptions& o) {
     const bool expand = (o.flags & kOptSumThenMultiply) == 0;
     const bool no_tab = (o.flags & kOptNoRankTable) != 0;
     const bool vec4 = (L % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15u) == 0) &&
@@ -587,7 +595,7 @@ hipError_t launch_gemm(const KView& k, const float* X, float* Y, const float* T,
         // wider batch gives more waves (measured on MI355X: 32 beats 16, 64, 128 and 256 at L = 32, 64, 3136)
         uint32_t tw = std::min<uint32_t>(pow2_ceil(L), 32u);
         tw = std::max<uint32_t>(tw, 8u);  // 4-column tiles (64 distinct rows per gather instruction) measured 1.4 - 3 x slower
-        if (L > 32) tw = pick_wide_tile(L, k.m, X, 128u);
+        if (L > 32) tw = pick_wide_tile(L, rows, X, 128u).cols;
         if (o.tile_cols > 0) tw = (uint32_t)o.tile_cols;
         switch (tw) {
             case 4: return launch_gemm_vp<IdxT, 4, 1>(k, X, Y, T, L, stream, sp, expand, false, no_tab);
@@ -603,7 +611,7 @@ hipError_t launch_gemm(const KView& k, const float* X, float* Y, const float* T,
     if (L >= 4 && expand && (o.flags & kOptOneColumnPerLane) == 0) {
         // ragged width or 4-byte aligned buffers: still four columns per lane
         uint32_t rtw = std::max<uint32_t>(std::min<uint32_t>(pow2_ceil(L), 32u), 8u);
-        if (L > 32) rtw = pick_wide_tile(L, k.m, X, 128u);
+        if (L > 32) rtw = pick_wide_tile(L, rows, X, 128u).cols;
         switch (rtw) {
             case 8: return launch_gemm_ragged<IdxT, 2>(k, X, Y, T, L, stream, sp);
             case 16: return launch_gemm_ragged<IdxT, 4>(k, X, Y, T, L, stream, sp);
@@ -625,11 +633,20 @@ hipError_t launch_gemm(const KView& k, const float* X, float* Y, const float* T,
 
 }  // namespace
 
+double gemm_gather_us(const DeviceView& d, uint32_t L) {
+    const RowLengths rows = row_lengths(d, false);
+    if (L > 32) return pick_wide_tile(L, rows, nullptr, 128u).us;
+    const double tw = std::max<uint32_t>(pow2_ceil(L), 8u);
+    const double ragged = 32u % L == 0 ? 1.0 : 0.85 + L / 64.0;  // rows of X that straddle lines
+    return std::max(rows.nnz * 128.0 * ragged / 27e6, rows.longest * (tw / 256.0) * 0.042);
+}
+
 hipError_t launch_gemm_any(const DeviceView& d, const float* X, float* Y, const float* T, uint32_t L, hipStream_t stream,
                            const MatmulOptions& o) {
     const KView k = make_kview(d);
     // 512-position value chunks for matrices of short rows (32-column tiles); the options can force either size
     const bool short_rows = (o.flags & kOptShortChunks) != 0 || ((o.flags & kOptLongChunks) == 0 && d.nnz <= d.m * 384);
+    const RowLengths rows = row_lengths(d, (o.flags & kOptRowsWhole) != 0);
     SplitArgs sp;  // kOptRowsWhole: rows in their own order, long rows whole
     if (d.row_order && (o.flags & kOptRowsWhole) == 0) {
         sp.order = static_cast<const uint32_t*>(d.row_order);
@@ -641,9 +658,9 @@ hipError_t launch_gemm_any(const DeviceView& d, const float* X, float* Y, const 
         sp.min = d.split_min;
     }
     switch (d.colI_bits) {
-        case 8: return launch_gemm<uint8_t>(k, X, Y, T, L, stream, sp, short_rows, o);
-        case 16: return launch_gemm<uint16_t>(k, X, Y, T, L, stream, sp, short_rows, o);
-        default: return launch_gemm<uint32_t>(k, X, Y, T, L, stream, sp, short_rows, o);
+        case 8: return launch_gemm<uint8_t>(k, X, Y, T, L, stream, sp, short_rows, rows, o);
+        case 16: return launch_gemm<uint16_t>(k, X, Y, T, L, stream, sp, short_rows, rows, o);
+        default: return launch_gemm<uint32_t>(k, X, Y, T, L, stream, sp, short_rows, rows, o);
     }
 }
 

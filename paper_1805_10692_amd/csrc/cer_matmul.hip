@@ -115,15 +115,12 @@ hipError_t launch_colsum(const float* X, uint32_t n, uint32_t L, float* part, ui
 //     more time: AlexNet-fc6 shape batch 100 114 us, batch 128 107 us)
 //   * waves: every (row, tile) is a wave whose start-up chain (descriptor -> pointers -> indices -> first gathers) takes about
 //     4 us, 4096 of them in flight: what bounds matrices of many short rows (16384 x 512: batch 128 64 - 84 us)
-//   * few rows: a wave walks its row alone, 5.5 ns per position (543 x 7364, batch 28, 4900 positions per row: 28 us)
+//   * the longest row: a wave walks it alone (543 x 7364, batch 28, 4900 positions per row: 28 us)
 //   * the column sums of X for a non-zero most frequent value: two launches and a pass over X
 double gather_estimate(const DeviceView& d, uint32_t L) {
     const double tiles = std::ceil((double)L / 32.0);
-    const double ragged = L % 32u == 0 || (L < 32u && 32u % L == 0) ? 1.0 : 1.35;
-    const double t_bytes = (double)d.nnz * std::max(4.0 * L, 128.0) * ragged / 27e12;
     const double t_waves = (double)d.m * tiles * 4e-6 / 4096.0;
-    const double t_row = d.split_min ? 0.0 : (double)d.nnz / (double)std::max<int64_t>(d.m, 1) * 5.5e-9 * ragged;
-    return 4e-6 + std::max(std::max(t_bytes, t_row), t_waves) + (d.omega0 != 0.f ? 5e-6 + (double)d.n * L * 4.0 / 4e12 : 0.0);
+    return 4e-6 + std::max(gemm_gather_us(d, L) * 1e-6, t_waves) + (d.omega0 != 0.f ? 5e-6 + (double)d.n * L * 4.0 / 4e12 : 0.0);
 }
 
 // Estimated durations (seconds) of the gathers and of decode + dense; false where the dense route is not available.

@@ -1439,6 +1439,7 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     std::copy_n(h.omega, h.Kp, A->omega.begin());
     std::copy_n(h.count, h.Kp, A->count.begin());
     bind_device(hnd.get(), dev, base, l);
+    hnd->view.longest_row = h.max_row_nnz;
     if (K_out) *K_out = (int32_t)h.K;
     if (codebook_out) std::memcpy(codebook_out, h.codebook, (size_t)h.K * 4);
     // rows of unequal length: the batched product wants them ordered (and the longest in parts); the row starts
