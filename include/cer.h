@@ -192,7 +192,7 @@ int cer_trim(void);
  * 128-byte line per index however narrow the batch) and loses for wide ones (random LDS gathers
  * are bank-conflict bound): it is chosen when it is applicable, batch <= 8 and the matrix holds
  * at least 2.5 million indices.
- * Where batch <= 8, the codebook holds at most 256 values and the estimates say so, the library's own choice
+ * Where batch <= 16, the codebook holds at most 256 values and the estimates say so, the library's own choice
  * runs the batch-1 stream kernel for several columns at once instead of the kernel that is reported here
  * (the number reported stays that of the kernel that serves the batch without it).
  * Errors: CER_E_INVALID, CER_E_HIP (no device copy).

@@ -407,7 +407,7 @@ bool mfma_applicable(const DeviceView& d, uint32_t L);
 double mfma_estimate_us(const DeviceView& d, uint32_t L);
 hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream);
 
-// cer_narrow.hip -- batches of 2 to 8 columns, the stream kernel of batch 1 for several columns at once (sums X itself).
+// cer_narrow.hip -- batches of 2 to 16 columns, the stream kernel of batch 1 for several columns at once (sums X itself).
 // narrow_estimate_us: huge where it is not applicable.
 double narrow_estimate_us(const DeviceView& d, uint32_t L);
 hipError_t launch_narrow(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream);

@@ -637,6 +637,12 @@ double gemm_gather_us(const DeviceView& d, uint32_t L) {
     const RowLengths rows = row_lengths(d, false);
     if (L > 32) return pick_wide_tile(L, rows, nullptr, 128u).us;
     const double tw = std::max<uint32_t>(pow2_ceil(L), 8u);
+    if (L <= 16) {
+        // fitted to 180 random shapes of 2 to 16 columns: a line per index whatever the batch; the walk takes 32 or 16 positions
+        // per step and more lines per instruction
+        const double traffic = rows.nnz * 4.34e-6, walk = rows.longest * (tw / 256.0) * 0.072;
+        return std::max(traffic, walk) + 0.3 * std::min(traffic, walk);
+    }
     const double ragged = 32u % L == 0 ? 1.0 : 0.85 + L / 64.0;  // rows of X that straddle lines
     return std::max(rows.nnz * 128.0 * ragged / 27e6, rows.longest * (tw / 256.0) * 0.042);
 }

@@ -214,14 +214,13 @@ int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o,
     return 1;
 }
 
-// Estimated duration of the kernel that choose_batched_path has named, for a batch of at most 8 columns.  Gathers from L2
-// touch one line per index there, in 0.6 of the time of a whole one (AlexNet-fc6 shape batch 4 20 us, VGG-fc6 shape batch 8 22 us);
-// the LDS tile kernel takes about as long per index.
+// Estimated duration (microseconds) of the kernel that choose_batched_path has named, for a batch of at most 16 columns.
 double path_estimate_us(const DeviceView& d, uint32_t L, int path) {
     if (path == kPathStrip) return plan_strip(d, L).est_us;
+    if (path == 2) return 4.0 + (double)d.nnz * 3.2e-6;  // AlexNet-fc6 shape batch 2 / 4 / 8: 23 / 13 / 28 us
     double t_gather = 0, t_dense = 0;
     if (path == 3 && densify_estimates(d, L, &t_gather, &t_dense)) return t_dense * 1e6;
-    return 4.0 + (double)d.nnz * 128.0 * 0.6 / 24e6;
+    return gather_estimate(d, L) * 1e6;
 }
 
 // Column sums of X for a non-zero most frequent value: shape of the two-stage sum and the floats it needs
@@ -296,7 +295,7 @@ int launch_matmul(const DeviceView& d, const float* X, float* Y, int64_t L64, vo
     XtilePlan plan;
     const int batched_path = L > 1 ? choose_batched_path(d, L, o, no_temporaries, &plan, X, Y) : 0;
     // the library's own choice for a few columns
-    if (L > 1 && L <= 8 && o.path < 0 && o.flags == 0 && o.tile_cols == 0 && !no_temporaries &&
+    if (L > 1 && L <= 16 && o.path < 0 && o.flags == 0 && o.tile_cols == 0 && !no_temporaries &&
         narrow_estimate_us(d, L) < path_estimate_us(d, L, batched_path))
         return (int)launch_narrow(d, X, Y, L, stream);
     if (batched_path == 3) return (int)launch_densified(d, X, Y, L, stream);

@@ -1,4 +1,4 @@
-// Batches of 2 to 8 columns: the stream kernel of batch 1 (cer_gemv.hip) for V columns at once.
+// Batches of 2 to 16 columns: the stream kernel of batch 1 (cer_gemv.hip) for V columns at once.
 //
 // V columns of X are staged into LDS as [row][V] and gathered from there, 4 V bytes per indexed element; everything else -- one
 // wave per row (or several: matrices of few rows), 16-byte loads of the indices, boundary bitmap, one weight per position -- costs
@@ -17,8 +17,6 @@ struct alignas(4 * V) Cols {
     float v[V];
 };
 
-enum : int32_t { kRowVectors, kInOrder, kScalar };
-
 struct NarrowArgs {
     const uint32_t* tab;
     const float* X;
@@ -27,8 +25,6 @@ struct NarrowArgs {
     float* Y;
     uint32_t n, m, L, K;
     uint32_t tab_shift, part_shift, row_blocks, rows_per_block;
-    uint32_t magic;  // ceil(2^32 / L)
-    int32_t how;     // kRowVectors, kInOrder: X is aligned; kScalar: it is not
 };
 
 template <typename IdxT, int V>
@@ -50,7 +46,8 @@ __global__ __launch_bounds__(1024) void cer_narrow_kernel(NarrowArgs a) {
 
     const uint32_t parts = 1u << a.part_shift, part = wave & (parts - 1u), rows_at_once = nwaves >> a.part_shift;
     const uint32_t pass = blockIdx.x / a.row_blocks, rb = blockIdx.x % a.row_blocks;
-    const uint32_t col0 = pass * V, cols = min((uint32_t)V, a.L - col0);
+    // a last group that is not full moves back: its first columns are computed twice, to the same numbers
+    const uint32_t col0 = a.L > (uint32_t)V ? min(pass * V, a.L - (uint32_t)V) : 0u, cols = min((uint32_t)V, a.L);
     const uint32_t row_begin = rb * a.rows_per_block, row_end = min(a.m, row_begin + a.rows_per_block);
     const IdxT* colI = static_cast<const IdxT*>(a.colI);
     uint32_t r = row_begin + (wave >> a.part_shift);  // wave-uniform
@@ -69,46 +66,28 @@ __global__ __launch_bounds__(1024) void cer_narrow_kernel(NarrowArgs a) {
     for (uint32_t t = 0; t < 4; ++t)
         if (t < ntiles) wq[t] = a.omega[min(t * kWave + lane + 1u, a.K - 1u)];
 
-    // X to LDS.  A compute unit's memory pipeline accepts a load about every 26 clocks whatever its width, so 16 bytes at a
-    // time: a copy (L == V), one vector per row (L a multiple of V), or all of X in order, each number to its place or nowhere.
+    // X to LDS: one vector load per row, at whatever 4-byte address the row has there.  Fewer columns than V: a vector runs
+    // into the next row (those sums are not stored), and the last rows are read number by number.
     typedef float Vec __attribute__((ext_vector_type(V)));
-    if (a.how == kRowVectors) {
-        const Vec* src = reinterpret_cast<const Vec*>(a.X + col0);
+    struct __attribute__((packed, aligned(4))) Row {
+        Vec v;
+    };
+    {
+        const float* src = a.X + col0;
         Vec* dst = reinterpret_cast<Vec*>(xs);
-        const uint32_t step = a.L / V;
+        const uint32_t behind = (uint32_t)V > a.L ? ((uint32_t)V - 1u) / a.L : 0u, nvec = a.n > behind ? a.n - behind : 0u;
         uint32_t i = threadIdx.x;
-        for (; i + 3u * nthreads < a.n; i += 4u * nthreads) {
+        for (; i + 3u * nthreads < nvec; i += 4u * nthreads) {
             Vec q[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) q[k] = src[(size_t)(i + k * nthreads) * step];
+            for (int k = 0; k < 4; ++k) q[k] = reinterpret_cast<const Row*>(src + (size_t)(i + k * nthreads) * a.L)->v;
 #pragma unroll
             for (int k = 0; k < 4; ++k) dst[i + k * nthreads] = q[k];
         }
-        for (; i < a.n; i += nthreads) dst[i] = src[(size_t)i * step];
-    } else {
-        const uint32_t total = a.n * a.L, n4 = a.how == kInOrder ? total >> 2 : 0u;  // at most 36000 x 8 numbers
-        float* dst = reinterpret_cast<float*>(xs);
-        auto place = [&](uint32_t e, float x) {
-            const uint32_t row = __umulhi(e, a.magic), c = e - row * a.L - col0;
-            if (c < (uint32_t)V) dst[row * V + c] = x;
-        };
-        auto place4 = [&](uint32_t i, const float4& q) {
-            place(4u * i, q.x);
-            place(4u * i + 1u, q.y);
-            place(4u * i + 2u, q.z);
-            place(4u * i + 3u, q.w);
-        };
-        const float4* src = reinterpret_cast<const float4*>(a.X);
-        uint32_t i = threadIdx.x;
-        for (; i + 3u * nthreads < n4; i += 4u * nthreads) {
-            float4 q[4];
+        for (; i < nvec; i += nthreads) dst[i] = reinterpret_cast<const Row*>(src + (size_t)i * a.L)->v;
+        for (i = nvec + threadIdx.x; i < a.n; i += nthreads)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) q[k] = src[i + k * nthreads];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) place4(i + k * nthreads, q[k]);
-        }
-        for (; i < n4; i += nthreads) place4(i, src[i]);
-        for (i = (n4 << 2) + threadIdx.x; i < total; i += nthreads) place(i, a.X[i]);
+            for (int v = 0; v < V; ++v) xs[i].v[v] = (uint32_t)v < a.L ? src[(size_t)i * a.L + v] : 0.f;
     }
     __syncthreads();
     // Appendix A-A1: the constant term of a non-zero most frequent value
@@ -244,7 +223,6 @@ NarrowPlan plan_narrow_t(const DeviceView& d, uint32_t L) {
     NarrowPlan best;
     const size_t budget = d.lds_per_block - 256, rows4 = ((size_t)d.n + 3) & ~(size_t)3;
     const size_t lcap = std::max<size_t>(63, ((size_t)1 << d.rank_tab_shift) - 1) + 5;
-    double best_cost = 1e300;
     for (int V : {8, 4, 2, 1}) {
         if (V > 1 && (uint32_t)V / 2 >= L) continue;  // half of the columns would be repetitions
         NarrowPlan p;
@@ -261,25 +239,26 @@ NarrowPlan plan_narrow_t(const DeviceView& d, uint32_t L) {
         const uint64_t windows = ((uint64_t)d.nnz / (uint64_t)d.m + S::WIN - 1) / S::WIN;  // average row
         while ((2u << p.part_shift) * p.rows_per_block <= p.waves && (1u << p.part_shift) < 8u && (1u << p.part_shift) < windows) ++p.part_shift;
         p.row_blocks = (uint32_t)(((uint64_t)d.m + p.rows_per_block - 1) / p.rows_per_block);
-        // clocks of a compute unit: per 64 indexed elements (18, 19, 20, 52 for 1, 2, 4, 8 columns: the weights and their
-        // bookkeeping, and beyond 4 columns the LDS), per row its list, the staging, and what any launch takes.  Measured
-        // with the fit: AlexNet-fc6 shape batch 2 / 4 / 5 / 8: 6.6 / 7.6 / 14.2 / 11.6 us; VGG-fc6 shape batch 2 / 4: 10.4 / 17.7 us.
-        const double gather = V == 8 ? 52.0 : (V == 4 ? 20.0 : (V == 2 ? 19.0 : 18.0));
-        const double row = 150.0 * ((((1u << d.rank_tab_shift) - 1u) >> 6) + 1u);
-        const double clk = p.passes * ((double)d.nnz / 64.0 * gather * (p.waves < 16 ? 1.5 : 1.0) + (double)d.m * row) / d.cus +
-                           rows4 * V * 4 / 1024.0 * 26.0 + 6000.0;
+        // Clocks, fitted to 220 random shapes of 2 to 16 columns (the typical deviation is 12 %).  A compute unit: per 64 indexed
+        // elements, 13, 15, 23, 58 for 1, 2, 4, 8 columns -- the weights and their bookkeeping, and from 4 columns on the
+        // LDS -- and per row its list.  Against that the longest row, walked by its waves alone.  Before either, the staging: 21
+        // per load of 64 rows and two per line of X.  AlexNet-fc6 shape batch 2 / 4 / 5 / 8: 6.6 / 7.6 / 14.2 / 11.6 us.
+        const double gather = V == 8 ? 58.0 : (V == 4 ? 22.6 : (V == 2 ? 15.2 : 12.7));
+        const double lists = ((((1u << d.rank_tab_shift) - 1u) >> 6) + 1u);
+        const double work = p.passes * ((double)d.nnz / 64.0 * gather + (double)d.m * lists * 72.0) / d.cus * (p.waves < 16 ? 1.36 : 1.0);
+        const double rows_per_wave = (double)((p.rows_per_block << p.part_shift) + p.waves - 1) / p.waves;
+        const double walk = 2.06 * d.longest_row / (1u << p.part_shift) + rows_per_wave * lists * 535.0;
+        const double loads = (double)d.n * (V == 8 ? 2.0 : 1.0) / 64.0, lines = (double)d.n * std::min(L * 4.0, 128.0) / 128.0;
+        double clk = 8300.0 + std::max(work, walk) + loads * 21.0 + lines * 2.0 + (V == 8 ? 1700.0 : 0.0);
+        if (d.omega0 != 0.f) clk += 3200.0 + 3.3 * d.n * V / 64.0;
         p.us = clk / 2400.0;
-        const double cost = p.us;
-        if (cost < best_cost) {
-            best_cost = cost;
-            best = p;
-        }
+        if (best.V == 0 || p.us < best.us) best = p;
     }
     return best;
 }
 
 NarrowPlan plan_narrow(const DeviceView& d, uint32_t L) {
-    if (!d.rank_tab || L < 2 || L > 8 || d.m < 1 || d.n < 1 || d.nnz < 1) return NarrowPlan{};
+    if (!d.rank_tab || L < 2 || L > 16 || d.m < 1 || d.n < 1 || d.nnz < 1) return NarrowPlan{};
     switch (d.colI_bits) {
         case 8: return plan_narrow_t<uint8_t>(d, L);
         case 16: return plan_narrow_t<uint16_t>(d, L);
@@ -328,8 +307,6 @@ hipError_t launch_narrow(const DeviceView& d, const float* X, float* Y, uint32_t
     a.part_shift = p.part_shift;
     a.row_blocks = p.row_blocks;
     a.rows_per_block = p.rows_per_block;
-    a.magic = (uint32_t)(((1ull << 32) + L - 1) / L);
-    a.how = (reinterpret_cast<uintptr_t>(X) & 15u) != 0 ? kScalar : (L % (uint32_t)p.V == 0 ? kRowVectors : kInOrder);
     const size_t budget = d.lds_per_block - 256;
     return d.colI_bits == 8 ? launch_narrow_t<uint8_t>(p, a, budget, stream) : launch_narrow_t<uint16_t>(p, a, budget, stream);
 }

@@ -42,3 +42,10 @@ def test_narrow_batches(shape, L):
 def test_unaligned_input_and_non_zero_most_frequent_value(L):
     _check(130, 2500, L, 9, 0.6, 0, "cer", shift=1)
     _check(4100, 1030, L, 33, 0.8, 0, "cser", shift=0)
+
+
+@pytest.mark.parametrize("L", [9, 11, 13, 16])
+@pytest.mark.parametrize("shape", [(700, 600, 30), (520, 2900, 180), (1100, 4400, 85), (900, 9000, 60)])
+def test_groups_of_columns_that_overlap(shape, L):
+    m, n, K = shape
+    _check(m, n, L, K, 0.35, K // 2, "cser" if L % 2 else "cer", shift=L % 3)
