@@ -6,6 +6,8 @@
 // so that one XCD's L2 sees as few batch tiles of X as possible.  The default kernel expands the group values
 // into a per-position array in LDS and multiplies every gathered row by its position's value (no cursor in the
 // stream; a multiply-add costs what an add costs); the cursor variant sums a group before its one multiplication.
+#include <cmath>
+
 #include "cer_device.hpp"
 
 namespace cer {
@@ -554,15 +556,17 @@ RowLengths row_lengths(const DeviceView& d, bool whole) {
 // Tile width (32, 64 or 128 batch columns) for a batch wider than 32 columns.  A gather instruction costs what the
 // cache lines it touches cost: when a row of X is a whole number of 128-byte lines, 32-column tiles touch exactly the
 // lines they need; otherwise every piece of a row touches up to one line more than its width, and wider tiles mean
-// fewer pieces.  Against that stand the gather instructions, which take 8.5 ns of a CU's time each whether their lanes are used
-// or not, and the walk of the longest row: a wave takes 256 / (columns per tile) positions per step of about 42 ns.  Measured on MI355X (AlexNet-fc6 shape, 32 / 64 / 128 columns per tile): batch 96: 91 / 115 / 107 us; batch 100:
-// 186 / 145 / 120 us; batch 40: 99 / 67 / 105 us; 3x3 convolution shape, batch 100 (512 rows): 35 / 30 / 44 us; 1254 x 4277, 19 %
-// indexed, rows of up to 4277 positions, batch 74: 46 us with 32 columns, 94 with 128.
+// fewer pieces -- but the lines of a wide tile fall out of an XCD's 4 MB of L2 sooner.  Against that stand the gather
+// instructions, whose lanes take time used or not, and the walk of the longest row: a wave takes 256 / (columns per tile) positions
+// per step.  The terms overlap in part.  Fitted to 200 random shapes of 33 to 400 columns, where the tile so chosen takes 4 % more
+// time than the best of the three (7 % with lines and lanes alone).  Measured on MI355X (AlexNet-fc6 shape, 32 / 64 / 128 columns
+// per tile): batch 96: 76 / 96 / 88 us; batch 100: 177 / 136 / 101 us; batch 40: 92 / 55 / 94 us; 3x3 convolution shape, batch 100
+// (512 rows): 31 / 25 / 38 us; 1254 x 4277, rows of up to 4277 positions, batch 74: 46 us with 32 columns, 94 with 128.
 struct WideTile {
     uint32_t cols;
     double us;  // estimate of the whole product
 };
-WideTile pick_wide_tile(uint32_t L, const RowLengths& rows, const float* X, uint32_t max_tile) {
+WideTile pick_wide_tile(uint32_t L, const RowLengths& rows, uint32_t n, const float* X, uint32_t max_tile) {
     const uint32_t row_bytes = L * 4u, base = (uint32_t)(reinterpret_cast<uintptr_t>(X) & 127u);
     const uint32_t step = std::gcd(row_bytes, 128u);  // rows start at base + multiples of this within a line
     auto lines = [&](uint32_t offset, uint32_t bytes) {  // average number of lines a piece of a row touches
@@ -571,13 +575,16 @@ WideTile pick_wide_tile(uint32_t L, const RowLengths& rows, const float* X, uint
         for (uint32_t ph = 0; ph < 128u; ph += step, ++cnt) sum += (double)(((base + ph + offset) % 128u + bytes + 127u) / 128u);
         return sum / cnt;
     };
+    // whole lines: 27 TB/s of them, or the walk
+    if (step == 128u && base == 0u) return {32, std::max(rows.nnz * (L / 32) * 4.74e-6, rows.longest * 0.125 * 0.042)};
     WideTile best{32, 1e300};
     for (uint32_t tw = 32; tw <= max_tile; tw *= 2) {
         const uint32_t ntiles = (L + tw - 1) / tw, last_cols = L - (ntiles - 1) * tw;
         double cost = (ntiles - 1) * lines(0, tw * 4u) + lines(((ntiles - 1) * tw * 4u) % 128u, last_cols * 4u);
-        const double traffic = std::max(cost * rows.nnz * 128.0 / 27e6, ntiles * rows.nnz * (tw / 256.0) * 33e-6);
-        const double walk = rows.longest * (tw / 256.0) * 0.042;
-        cost = std::max(traffic, walk) + 0.3 * std::min(traffic, walk);
+        const double tile_mb = n * cost / ntiles * 128e-6;
+        const double traffic = rows.nnz * (cost * 2.63e-6 * (1.0 + 0.155 * tile_mb) + ntiles * 2.4e-6);
+        const double issue = ntiles * rows.nnz * (tw / 256.0) * 12.7e-6, walk = rows.longest * (tw / 256.0) * 0.026;
+        cost = std::pow(std::pow(traffic, 1.33) + std::pow(issue, 1.33) + std::pow(walk, 1.33), 1.0 / 1.33);
         if (cost < best.us) best = {tw, cost};
     }
     return best;
@@ -595,7 +602,7 @@ hipError_t launch_gemm(const KView& k, const float* X, float* Y, const float* T,
         // wider batch gives more waves (measured on MI355X: 32 beats 16, 64, 128 and 256 at L = 32, 64, 3136)
         uint32_t tw = std::min<uint32_t>(pow2_ceil(L), 32u);
         tw = std::max<uint32_t>(tw, 8u);  // 4-column tiles (64 distinct rows per gather instruction) measured 1.4 - 3 x slower
-        if (L > 32) tw = pick_wide_tile(L, rows, X, 128u).cols;
+        if (L > 32) tw = pick_wide_tile(L, rows, k.n, X, 128u).cols;
         if (o.tile_cols > 0) tw = (uint32_t)o.tile_cols;
         switch (tw) {
             case 4: return launch_gemm_vp<IdxT, 4, 1>(k, X, Y, T, L, stream, sp, expand, false, no_tab);
@@ -611,7 +618,7 @@ hipError_t launch_gemm(const KView& k, const float* X, float* Y, const float* T,
     if (L >= 4 && expand && (o.flags & kOptOneColumnPerLane) == 0) {
         // ragged width or 4-byte aligned buffers: still four columns per lane
         uint32_t rtw = std::max<uint32_t>(std::min<uint32_t>(pow2_ceil(L), 32u), 8u);
-        if (L > 32) rtw = pick_wide_tile(L, rows, X, 128u).cols;
+        if (L > 32) rtw = pick_wide_tile(L, rows, k.n, X, 128u).cols;
         switch (rtw) {
             case 8: return launch_gemm_ragged<IdxT, 2>(k, X, Y, T, L, stream, sp);
             case 16: return launch_gemm_ragged<IdxT, 4>(k, X, Y, T, L, stream, sp);
@@ -635,7 +642,7 @@ hipError_t launch_gemm(const KView& k, const float* X, float* Y, const float* T,
 
 double gemm_gather_us(const DeviceView& d, uint32_t L) {
     const RowLengths rows = row_lengths(d, false);
-    if (L > 32) return pick_wide_tile(L, rows, nullptr, 128u).us;
+    if (L > 32) return pick_wide_tile(L, rows, (uint32_t)d.n, nullptr, 128u).us;
     const double tw = std::max<uint32_t>(pow2_ceil(L), 8u);
     if (L <= 16) {
         // fitted to 180 random shapes of 2 to 16 columns: a line per index whatever the batch; the walk takes 32 or 16 positions
