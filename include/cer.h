@@ -183,7 +183,8 @@ int cer_trim(void);
  *      (max(4.batch, 128) bytes per indexed element through the L1/L2 path) exceeds that of the
  *      decode and the dense contraction: wide batches of matrices with more than about one
  *      indexed element in five, any batch > 1 of matrices with most elements indexed.  The
- *      arithmetic is then that of a dense fp32 product (same error bound), not Algorithm 3 / 4.
+ *      arithmetic is then that of a dense fp32 product (same error bound), not Algorithm 3 / 4.  An
+ *      infinity or NaN in X reaches every row, as it does there: 0 . inf is NaN
  *   5  CER_PATH_STRIP: batched kernel with strips of 1024 input rows resident in LDS; needs the strip-major
  *      index of cer_prepare_strips.  For a handle that has it the library chooses this kernel where its
  *      estimated duration is below that of kernels 1 and 3: wide batches of large matrices (AlexNet-fc6

@@ -34,12 +34,14 @@ __device__ __forceinline__ float split3_pair(float a, float b, uint32_t p[3]) {
     return qa + qb;
 }
 
-// The same for any number: infinities and NaNs are one piece, and numbers that would round to infinity are cut instead.
+// The same for any number: numbers that would round to infinity are cut instead, and infinities and NaNs are the third piece
+// alone -- the one that meets no other factor's second or third piece (mfma_pieces): inf . 0 and inf - inf of a partial
+// product would be NaN where the product is infinite.
 __device__ __forceinline__ void split3_any(float x, uint32_t p[3]) {
     const uint32_t u = __float_as_uint(x), mag = u & 0x7FFFFFFFu;
     if (mag >= 0x7F800000u) {
-        p[0] = mag > 0x7F800000u ? 0x7FC0u : u >> 16;
-        p[1] = p[2] = 0;
+        p[0] = p[1] = 0;
+        p[2] = mag > 0x7F800000u ? 0x7FC0u : u >> 16;
         return;
     }
     p[0] = mag >= 0x7F7F0000u ? u >> 16 : bf16_pair(x, 0.f) & 0xFFFFu;

@@ -54,6 +54,30 @@ def test_inputs_that_have_no_three_pieces():
     assert (np.abs(Y[:, keep] - want) <= 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X[:, keep]).astype(np.float64))).all()
 
 
+# (70, 300, 45): the small tiles; (2048, 1024, 2048): those of 256 rows; (2048, 260, 20): their 32-column form or the small one
+@pytest.mark.parametrize("pieces", list(CODEBOOKS))
+@pytest.mark.parametrize("shape", [(70, 300, 45), (2048, 1024, 2048), (2048, 260, 20)])
+def test_infinities_and_nans(shape, pieces):
+    """A column with infinities or a NaN is what the dense product gives in IEEE arithmetic, for codebooks of every kind: infinite
+    under a non-zero weight, NaN under a zero one or where two infinities meet; the other columns are untouched."""
+    m, n, L = shape
+    rng = np.random.default_rng(n)
+    W = rng.choice(CODEBOOKS[pieces], size=(m, n), p=[0.4, 0.2, 0.2, 0.2]).astype(np.float32)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    X[n // 3, 1], X[n - 1, 2], X[5, 3] = np.inf, -np.inf, np.nan
+    X[6, 4], X[7, 4], X[8, 9] = np.inf, -np.inf, np.inf
+    Y = _product(W, CODEBOOKS[pieces], X)
+    special = [1, 2, 3, 4, 9]
+    with np.errstate(invalid="ignore"):
+        for c in special:
+            want = (W.astype(np.float64) * X[:, c].astype(np.float64)).sum(1)
+            assert not np.isfinite(want).any()
+            assert np.array_equal(Y[:, c], want, equal_nan=True), c
+    keep = np.setdiff1d(np.arange(L), special)
+    want = W.astype(np.float64) @ X[:, keep].astype(np.float64)
+    assert (np.abs(Y[:, keep] - want) <= 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X[:, keep]).astype(np.float64))).all()
+
+
 @pytest.mark.parametrize("pieces", list(CODEBOOKS))
 def test_nothing_behind_the_inputs_reaches_the_result(pieces):
     """NaNs right behind X, and the step of the kernels that crosses its end."""
