@@ -178,8 +178,8 @@ int cer_trim(void);
  *   3  CER_PATH_DENSE: decode + dense: the matrix is decoded into a stream-ordered temporary and multiplied
  *      on the matrix cores: as one to three bf16 matrices that add up to it exactly (2.m.n bytes each), with
  *      X split into three in the same way, or as fp32 (4.m.n bytes) where a value or an index range rules
- *      that out.  The inputs keep all 24 bits of their significands (|X| >= 2^-109; smaller ones lose what
- *      lies below 2^-133), products are exact or within 2^-25, sums are fp32.  Chosen when the estimated time of the gathers
+ *      that out.  The inputs keep all 24 bits of their significands, products are exact or within 2^-25,
+ *      sums are fp32.  Chosen when the estimated time of the gathers
  *      (max(4.batch, 128) bytes per indexed element through the L1/L2 path) exceeds that of the
  *      decode and the dense contraction: wide batches of matrices with more than about one
  *      indexed element in five, any batch > 1 of matrices with most elements indexed.  The

@@ -457,6 +457,7 @@ void cer::bind_device(cer_matrix* h, int dev, void* base, const DeviceLayout& l)
     for (float w : A.omega) {
         const int p = value_pieces(w);
         v.pieces = p && v.pieces ? std::max(v.pieces, p) : 0;
+        v.omega_max = std::max(v.omega_max, std::fabs(w));
     }
     const DeviceProps& dp = device_props(dev);
     v.cus = dp.cus;

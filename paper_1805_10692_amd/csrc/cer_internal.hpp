@@ -60,6 +60,7 @@ struct DeviceView {
     int64_t nonempty_groups = 0;
     uint32_t longest_row = 0;  // indexed elements of the longest row
     float omega0 = 0.f;
+    float omega_max = 0.f;  // largest magnitude in the codebook
     int32_t pieces = 0;  // bf16 numbers that add up to every codebook value exactly (1 .. 3); 0: some piece would be subnormal
     // the device the arrays live on, as the launchers need it (read once, when the handle is bound to its memory)
     int32_t cus = 256;

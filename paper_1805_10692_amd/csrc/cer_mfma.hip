@@ -18,14 +18,94 @@ namespace {
 
 constexpr uint32_t kFlush = 256;
 
+// What a workgroup of either kernel below was given.
+struct Block {
+    const uint16_t* W;
+    const float* X;
+    float* Out;
+    size_t plane;
+    uint32_t m, n, L, pitch, row0, rows, col0, cols, k_begin, k_end;
+};
+
+// Products in binary32, the pieces of W added up again: the workgroup's outputs once more, over the ones from the matrix cores.
+// Called (by all threads, through a barrier) where X holds infinities, NaNs or numbers that round to infinity (must: some thread
+// has met one), and where a sum is faint -- so small that what the pieces of small inputs lose can show.  Faint sums alone
+// are mostly those of empty rows: the inputs are looked at first (odd: this thread's inputs had third pieces; without them nothing
+// is lost).  A function of its own, and behind the stores, so that nothing of it is held in registers while the matrix cores work.
+// Small inputs could also be caught on their way: 48 -> 53 us for 512 x 4608, batch 3136.
+// A wave takes tiles of 32 x 32 outputs, 64 columns of W per step, straight from memory; sums of kFlush columns as below.  Product of
+// 512 x 4608, batch 3136, one-piece codebook: 68 us, 80 with empty rows, 247 with an infinity in X, 331 with X of about 2^-120.
+template <int PW>
+__device__ __attribute__((noinline)) void exact_block(const Block b, bool must, bool odd) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
+    if (!__syncthreads_or(must)) {
+        bool some = false;
+        if (__syncthreads_or(odd)) {
+            const uint32_t xcol = min(b.col0 + tid % b.cols, b.L - 1u), step = 256u / b.cols;
+            for (uint32_t k0 = b.k_begin + tid / b.cols; k0 < b.k_end; k0 += 16u * step) {
+                float x[16];
+#pragma unroll
+                for (uint32_t i = 0; i < 16; ++i) x[i] = b.X[(size_t)min(k0 + i * step, b.n - 1u) * b.L + xcol];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) some |= split_lossy(x[i]);
+            }
+        }
+        if (!__syncthreads_or(some)) return;
+    }
+    const uint32_t across = b.cols / 32u;
+    for (uint32_t t = wave; t < b.rows / 32u * across; t += 4u) {
+        const uint32_t row32 = b.row0 + t / across * 32u, c = b.col0 + t % across * 32u + (lane & 31u);
+        if (row32 >= b.m) break;
+        const uint16_t* w = b.W + (size_t)(row32 >> 5) * 32 * b.pitch;
+        const uint32_t xoff = (8u * half * b.L + min(c, b.L - 1u)) * 4u;
+        floatx16 sum = {}, acc = {};
+        uint32_t held = 0;
+        for (uint32_t k0 = b.k_begin; k0 < b.k_end; k0 += 64u) {  // a multiple of 64 columns
+            float x[4][8];
+            uint4 q[4][PW];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const __amdgpu_buffer_rsrc_t xbuf = x_rows(b.X, b.L, k0 + 16 * s, b.n);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[s][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff + i * b.L * 4u, 0, 0));
+#pragma unroll
+                for (int p = 0; p < PW; ++p) q[s][p] = reinterpret_cast<const uint4*>(w + p * b.plane + (size_t)(k0 + 16 * s) * 32)[lane];
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    float v = 0.f;
+#pragma unroll
+                    for (int p = PW - 1; p >= 0; --p) {
+                        const uint32_t u = i < 4 ? (i < 2 ? q[s][p].x : q[s][p].y) : (i < 6 ? q[s][p].z : q[s][p].w);
+                        v += __uint_as_float(i & 1 ? u & 0xFFFF0000u : u << 16);
+                    }
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v, x[s][i], acc, 0, 0, 0);
+                }
+            if ((held += 64u) >= kFlush) {
+                held = 0;
+                sum += acc;
+                acc = floatx16{};
+            }
+        }
+        sum += acc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const uint32_t r = row32 + 8 * (e / 4) + 4 * half + (e % 4);
+            if (r < b.m && c < b.L) b.Out[(size_t)r * b.L + c] = sum[e];
+        }
+    }
+}
+
 template <int PW, int TN, int D>
 struct MfmaTile {
     static constexpr int TM = 2, BM = 256, BN = 32 * TN, BK = 2048 / BN, KG = BK / 8, KS = BK / 16;
     uint4 b[2][3][KG][BN];
 
     // sum: what is finished; acc: the sum over the current kFlush columns or so (a running sum of thousands of terms would
-    // round each of them to the size of the whole).  Returns a NaN if kAny is needed.
-    template <bool kAny>
+    // round each of them to the size of the whole).  Returns a NaN if this thread's share of X holds numbers without pieces, and
+    // 0 if none of them has a third piece.
     __device__ __forceinline__ float run(const uint16_t* const (&wtile)[TM], size_t plane, const float* X, uint32_t n, uint32_t L,
                                          uint32_t xcol, uint32_t k_begin, uint32_t k_end, floatx16 (&sum)[TM][TN]) {
         const uint32_t tid = threadIdx.x, lane = tid & 63u;
@@ -52,7 +132,7 @@ struct MfmaTile {
         };
         auto store_x = [&](int slot, int buf) {
             uint4 o[3];
-            odd += split3_8<kAny>(xr[slot], o);
+            odd += split3_8(xr[slot], o);
 #pragma unroll
             for (int p = 0; p < 3; ++p) b[buf][p][xg][xc] = o[p];
         };
@@ -117,7 +197,8 @@ struct MfmaTile {
 template <int PW, int TN, int D>
 __global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
-    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, size_t split_stride) {
+    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, size_t split_stride,
+    float faint) {
     using Tile = MfmaTile<PW, TN, D>;
     __shared__ Tile tile;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -144,8 +225,18 @@ __global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
     for (int i = 0; i < Tile::TM; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * 32 * pitch;
     const uint32_t xcol = min(col0 + tid % Tile::BN, L - 1u);
     floatx16 sum[Tile::TM][TN];
-    const float odd = tile.template run<false>(wtile, plane, X, n, L, xcol, k_begin, k_end, sum);
-    if (__syncthreads_or(odd != odd)) (void)tile.template run<true>(wtile, plane, X, n, L, xcol, k_begin, k_end, sum);
+    const float odd = tile.run(wtile, plane, X, n, L, xcol, k_begin, k_end, sum);
+
+    // The vote comes before the stores (behind them: 2 us more).
+    float least = INFINITY;
+#pragma unroll
+    for (int i = 0; i < Tile::TM; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            if (row0 + 32 * i + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4) < m)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) least = fminf(least, fabsf(sum[i][j][e]));
+    const int look = __syncthreads_or(odd != odd || least < faint);
 
     // accumulator element e of lane l: row = 8 (e / 4) + 4 (l / 32) + e % 4, column = l % 32
 #pragma unroll
@@ -159,6 +250,8 @@ __global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
                 if (r < m && c < L) Out[(size_t)r * L + c] = sum[i][j][e];
             }
         }
+    if (look)
+        exact_block<PW>(Block{W, X, Out, plane, m, n, L, pitch, rt * Tile::BM, Tile::BM, col0, Tile::BN, k_begin, k_end}, odd != odd, odd != 0.f);
 }
 
 // The same for small problems: 64 x 32 CT outputs per workgroup, the four waves share its columns of W (32 at a time, in turn)
@@ -167,7 +260,7 @@ __global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
 // piece), and a matrix of 600 rows wastes 40 of them instead of 168.  Product of 700 x 1200, batch 60: 19 -> 9 us, 2048 x 2048, batch
 // 16: 9.2 -> 4.6 us, 2728 x 3378, batch 115: 20 -> 16 us; 512 x 4608, batch 3136: 48 us with the large tiles, 66 with these.  Bound by the splitting of X (PW = 1) or by what L2
 // delivers (80 KiB per 128 columns): the larger tile is the better one where it fills the chip.
-template <int PW, int CT, bool kAny>
+template <int PW, int CT>
 __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2], size_t plane, const float* X, uint32_t n,
                                                 uint32_t L, uint32_t col0, uint32_t k_begin, uint32_t k_end, floatx16 (&acc)[2][CT]) {
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -202,7 +295,7 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
 #pragma unroll
             for (int j = 0; j < CT; ++j) {
                 uint4 b[3];
-                odd += split3_8<kAny>(x[slot][s][j], b);
+                odd += split3_8(x[slot][s][j], b);
 #pragma unroll
                 for (int i = 0; i < 2; ++i) acc[i][j] = mfma_pieces<PW>(a[slot][s][i], b, acc[i][j]);
             }
@@ -230,7 +323,8 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
 template <int PW, int CT>
 __global__ __launch_bounds__(256, PW == 1 || (PW == 2 && CT == 1) ? 2 : 1) void mfma_small_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
-    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, size_t split_stride) {
+    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, size_t split_stride,
+    float faint) {
     __shared__ float s_acc[4][2 * CT][16][64];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t items = row_tiles * col_tiles * splits, eighth = (items + 7u) >> 3;
@@ -244,8 +338,7 @@ __global__ __launch_bounds__(256, PW == 1 || (PW == 2 && CT == 1) ? 2 : 1) void 
 #pragma unroll
     for (int i = 0; i < 2; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * 32 * pitch;
     floatx16 acc[2][CT];
-    const float odd = mfma_small_run<PW, CT, false>(wtile, plane, X, n, L, col0, k_begin, k_end, acc);
-    if (__ballot(odd != odd)) (void)mfma_small_run<PW, CT, true>(wtile, plane, X, n, L, col0, k_begin, k_end, acc);
+    const float odd = mfma_small_run<PW, CT>(wtile, plane, X, n, L, col0, k_begin, k_end, acc);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -255,14 +348,23 @@ __global__ __launch_bounds__(256, PW == 1 || (PW == 2 && CT == 1) ? 2 : 1) void 
     __syncthreads();
     // every wave adds up and stores a quarter of the workgroup's accumulators
     constexpr int PER = 2 * CT * 16 / 4;
+    float y[PER], least = INFINITY;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         const uint32_t f = wave * PER + q, tile = f >> 4, e = f & 15u;
-        const float y = (s_acc[0][tile][e][lane] + s_acc[1][tile][e][lane]) + (s_acc[2][tile][e][lane] + s_acc[3][tile][e][lane]);
+        y[q] = (s_acc[0][tile][e][lane] + s_acc[1][tile][e][lane]) + (s_acc[2][tile][e][lane] + s_acc[3][tile][e][lane]);
+        if (row0 + 32 * (tile / CT) + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4) < m) least = fminf(least, fabsf(y[q]));
+    }
+    const int look = __syncthreads_or(odd != odd || least < faint);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const uint32_t f = wave * PER + q, tile = f >> 4, e = f & 15u;
         const uint32_t r = row0 + 32 * (tile / CT) + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4);
         const uint32_t c = col0 + 32 * (tile % CT) + (lane & 31u);
-        if (r < m && c < L) Out[(size_t)r * L + c] = y;
+        if (r < m && c < L) Out[(size_t)r * L + c] = y[q];
     }
+    if (look)
+        exact_block<PW>(Block{W, X, Out, plane, m, n, L, pitch, row0, 64u, col0, 32u * CT, k_begin, k_end}, odd != odd, odd != 0.f);
 }
 
 __global__ __launch_bounds__(256) void mfma_sum_kernel(const float* __restrict__ part, float* __restrict__ Y, size_t count,
@@ -340,13 +442,13 @@ MfmaShape mfma_shape(const DeviceView& d, uint32_t L) {
 
 template <int PW>
 hipError_t launch_shape(const MfmaShape& s, const uint16_t* W, const float* X, float* out, uint32_t m, uint32_t n, uint32_t L,
-                        uint32_t pitch, size_t plane, hipStream_t stream) {
+                        uint32_t pitch, size_t plane, float faint, hipStream_t stream) {
     const dim3 grid((s.row_tiles * s.col_tiles * s.splits + 7) / 8 * 8);
     const size_t count = (size_t)m * L;
     auto* kern = s.small ? (s.BN == 32 ? mfma_small_kernel<PW, 1> : mfma_small_kernel<PW, 2>)
                          : (s.BN == 32 ? mfma_product_kernel<PW, 1, mfma_depth(PW, 32)> : mfma_product_kernel<PW, 2, mfma_depth(PW, 64)>);
     return launch_kernel(kern, grid, dim3(256), 0, stream, W, X, out, m, n, L, pitch, plane, s.row_tiles, s.col_tiles, s.splits,
-                         s.kchunk, count);
+                         s.kchunk, count, faint);
 }
 
 }  // namespace
@@ -372,10 +474,12 @@ hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L
     e = (hipError_t)decode_pieces(d, W, pitch, plane, stream);
     if (e == hipSuccess) {
         const uint32_t m = (uint32_t)d.m, n = (uint32_t)d.n;
+        // An input loses at most half of 2^-133, a sum at most n max|w| 2^-134: less than 2^-26 of itself from here on.
+        const float faint = (float)std::min((double)d.n * d.omega_max * 0x1p-108, 1e38);
         switch (d.pieces) {
-            case 1: e = launch_shape<1>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, stream); break;
-            case 2: e = launch_shape<2>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, stream); break;
-            default: e = launch_shape<3>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, stream);
+            case 1: e = launch_shape<1>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, stream); break;
+            case 2: e = launch_shape<2>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, stream); break;
+            default: e = launch_shape<3>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, stream);
         }
     }
     if (e == hipSuccess && s.splits > 1)

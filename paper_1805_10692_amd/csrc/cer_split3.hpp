@@ -1,8 +1,9 @@
 // fp32 numbers as sums of bf16 numbers, for the bf16 matrix cores (gfx950).
 //
 // A binary32 significand has 24 bits, a bf16 one has 8: x = p0 + p1 + p2 with p0 = bf16(x), p1 = bf16(x - p0),
-// p2 = x - p0 - p1 is exact (both differences are exact in binary32, the last one fits 8 bits), for |x| from 2^-109 up to the
-// largest number.  Products of two pieces are exact in binary32 and the matrix cores add them up in binary32, so a
+// p2 = x - p0 - p1 is exact (both differences are exact in binary32, the last one fits 8 bits), for |x| from 2^-110 up to the
+// largest number that rounds to a finite bf16 one.  Other numbers have no such pieces -- those below lose what lies under 2^-133,
+// the smallest bf16 number -- and a product that meets them (below 2^-110: in which that shows) is formed in binary32.  Products of two pieces are exact in binary32 and the matrix cores add them up in binary32, so a
 // contraction over pieces has the inputs and the accumulation of the fp32 one.  Where both factors have three pieces the
 // three smallest of the nine products are left out: together below 2^-25 of the product, half a unit of what rounding a
 // binary32 product costs.  The bf16 matrix instructions run at 16 times the rate of the fp32 ones: three products (one
@@ -24,52 +25,39 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
 }
 
-// Pieces of a pair of numbers that are finite and round to finite bf16 numbers; for other numbers the return value is a NaN.
+// Pieces of a pair of numbers that are finite and round to finite bf16 numbers; the return value is a NaN for other numbers,
+// and else the size of the third pieces: 0 where the first two are all there is.
 __device__ __forceinline__ float split3_pair(float a, float b, uint32_t p[3]) {
     p[0] = bf16_pair(a, b);
     const float ra = a - __uint_as_float(p[0] << 16), rb = b - __uint_as_float(p[0] & 0xFFFF0000u);
     p[1] = bf16_pair(ra, rb);
     const float qa = ra - __uint_as_float(p[1] << 16), qb = rb - __uint_as_float(p[1] & 0xFFFF0000u);
     p[2] = bf16_pair(qa, qb);
-    return qa + qb;
+    return fabsf(qa) + fabsf(qb);
 }
 
-// The same for any number: numbers that would round to infinity are cut instead, and infinities and NaNs are the third piece
-// alone -- the one that meets no other factor's second or third piece (mfma_pieces): inf . 0 and inf - inf of a partial
-// product would be NaN where the product is infinite.
-__device__ __forceinline__ void split3_any(float x, uint32_t p[3]) {
-    const uint32_t u = __float_as_uint(x), mag = u & 0x7FFFFFFFu;
-    if (mag >= 0x7F800000u) {
-        p[0] = p[1] = 0;
-        p[2] = mag > 0x7F800000u ? 0x7FC0u : u >> 16;
-        return;
-    }
-    p[0] = mag >= 0x7F7F0000u ? u >> 16 : bf16_pair(x, 0.f) & 0xFFFFu;
+// A number with bits that the pieces may not reach: 0 < |x| < 2^-110.
+__device__ __forceinline__ bool split_lossy(float x) { return (__float_as_uint(x) << 1) - 1u < 2u * 0x08800000u - 1u; }
+
+// Pieces of one finite number; numbers that would round to infinity are cut instead.
+__device__ __forceinline__ void split3_finite(float x, uint32_t p[3]) {
+    const uint32_t u = __float_as_uint(x);
+    p[0] = (u & 0x7FFFFFFFu) >= 0x7F7F0000u ? u >> 16 : bf16_pair(x, 0.f) & 0xFFFFu;
     const float r = x - __uint_as_float(p[0] << 16);
     p[1] = bf16_pair(r, 0.f) & 0xFFFFu;
     p[2] = bf16_pair(r - __uint_as_float(p[1] << 16), 0.f) & 0xFFFFu;
 }
 
-// Eight numbers -> three times eight bf16, in the order given.  kAny: any numbers; else the return value is a NaN unless all
-// of them are finite and round to finite bf16 numbers.
-template <bool kAny>
+// Eight numbers -> three times eight bf16, in the order given; the return value is that of split3_pair, added up.
 __device__ __forceinline__ float split3_8(const float x[8], uint4 out[3]) {
     uint32_t w[3][4];
     float odd = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        if constexpr (kAny) {
-            uint32_t a[3], b[3];
-            split3_any(x[2 * i], a);
-            split3_any(x[2 * i + 1], b);
+        uint32_t p[3];
+        odd += split3_pair(x[2 * i], x[2 * i + 1], p);
 #pragma unroll
-            for (int j = 0; j < 3; ++j) w[j][i] = a[j] | (b[j] << 16);
-        } else {
-            uint32_t p[3];
-            odd += split3_pair(x[2 * i], x[2 * i + 1], p);
-#pragma unroll
-            for (int j = 0; j < 3; ++j) w[j][i] = p[j];
-        }
+        for (int j = 0; j < 3; ++j) w[j][i] = p[j];
     }
 #pragma unroll
     for (int j = 0; j < 3; ++j) out[j] = make_uint4(w[j][0], w[j][1], w[j][2], w[j][3]);

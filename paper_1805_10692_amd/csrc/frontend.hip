@@ -946,7 +946,7 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
         for (uint32_t i = tid; i < words; i += 512u) s_ptr[i] = a.tab[((size_t)row0 << a.tab_shift) + i];
         for (uint32_t k = tid; k < a.K; k += 512u) {
             uint32_t p[3];
-            cer::split3_any(a.omega[k], p);
+            cer::split3_finite(a.omega[k], p);
             s_val[k] = p[0] | (p[1] << 16);
             if constexpr (kPieces == 3) s_val2[k] = p[2];
         }
@@ -1064,7 +1064,7 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
 #pragma unroll
             for (uint32_t i = 0; i < 8; ++i) {
                 uint32_t p[3];
-                cer::split3_any((float)mine[min(j + i, len - 1u)], p);
+                cer::split3_finite((float)mine[min(j + i, len - 1u)], p);
                 p01[i] = p[0] | (p[1] << 16);
                 p2[i] = p[2];
             }

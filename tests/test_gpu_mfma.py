@@ -78,6 +78,56 @@ def test_infinities_and_nans(shape, pieces):
     assert (np.abs(Y[:, keep] - want) <= 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X[:, keep]).astype(np.float64))).all()
 
 
+def _tiny_cases():
+    """Inputs of one size (2^-k times normal ones), inputs over 140 powers of two in one column, and inputs of ordinary size that a
+    third of W's rows does not touch -- what these rows see is tiny."""
+    rng = np.random.default_rng(17)
+    for m, n, L in ((70, 300, 45), (2048, 1024, 2048), (2048, 260, 20)):
+        for k in (100, 108, 112, 120, 128, 140, 147):
+            yield f"{m}x{n}x{L} 2^-{k}", m, n, np.ldexp(rng.standard_normal((n, L)), -k).astype(np.float32), None
+        X = np.ldexp(rng.standard_normal((n, L)), -rng.integers(5, 146, size=(n, 1))).astype(np.float32)
+        yield f"{m}x{n}x{L} mixed", m, n, X, None
+        X = np.ldexp(rng.standard_normal((n, L)), -118).astype(np.float32)
+        X[::4] = rng.standard_normal(X[::4].shape)
+        X[1, 7], X[n - 1, 8] = np.float32(1e38), -np.inf  # together with what the other part of the repetition is for (3e38 is finite)
+        yield f"{m}x{n}x{L} rows apart", m, n, X, slice(0, None, 4)
+
+
+@pytest.mark.parametrize("pieces", list(CODEBOOKS))
+def test_inputs_with_bits_below_the_smallest_piece(pieces):
+    """Numbers whose last bits no bf16 number reaches (below 2^-110), down to the smallest subnormal, keep all of them: the bound of
+    binary32 products and sums, plus half of the smallest number for each of the n roundings of a sum that is subnormal itself
+    (and as much for each of the matrix instruction's partial products, at most 6)."""
+    cb = CODEBOOKS[pieces]
+    rng = np.random.default_rng(23)
+    for name, m, n, X, apart in _tiny_cases():
+        W = rng.choice(cb, size=(m, n), p=[0.1, 0.3, 0.3, 0.3]).astype(np.float32)
+        if apart is not None:
+            W[::3, apart] = 0.0
+        Y = _product(W, cb, X)
+        with np.errstate(invalid="ignore"):
+            want = W.astype(np.float64) @ X.astype(np.float64)
+            bound = 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64)) + 7 * n * 2.0 ** -150
+        odd = ~np.isfinite(want)
+        assert np.array_equal(Y[odd], want[odd], equal_nan=True), name
+        assert (np.abs(Y[~odd] - want[~odd]) <= bound[~odd]).all(), (name, np.nanmax((np.abs(Y - want) / bound)[~odd]))
+
+
+@pytest.mark.parametrize("pieces", list(CODEBOOKS))
+@pytest.mark.parametrize("shape", [(70, 300, 45), (2048, 1024, 2048)])
+def test_empty_rows_and_columns(shape, pieces):
+    """Sums that are exactly zero -- rows of W without an element, columns of X without one -- beside ordinary ones."""
+    m, n, L = shape
+    rng = np.random.default_rng(m)
+    W = rng.choice(CODEBOOKS[pieces], size=(m, n), p=[0.4, 0.2, 0.2, 0.2]).astype(np.float32)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    W[::9], X[:, ::7] = 0.0, 0.0
+    Y = _product(W, CODEBOOKS[pieces], X)
+    assert (Y[::9] == 0).all() and (Y[:, ::7] == 0).all()
+    want = W.astype(np.float64) @ X.astype(np.float64)
+    assert (np.abs(Y - want) <= 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64))).all()
+
+
 @pytest.mark.parametrize("pieces", list(CODEBOOKS))
 def test_nothing_behind_the_inputs_reaches_the_result(pieces):
     """NaNs right behind X, and the step of the kernels that crosses its end."""
