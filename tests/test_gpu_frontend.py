@@ -276,3 +276,21 @@ def test_device_encoded_handle_clones_and_inspects_lazily():
         B.cer_free(hc)
         B.cer_free(hh)
     del dev
+
+
+@pytest.mark.parametrize("fmt", ["cer", "cser"])
+def test_sizes_of_every_row_reach_the_scan(fmt):
+    """Row counts around the sixteen rows of a workgroup and the 4096 rows of a round of the scan, one after the other in the same
+    temporary: sizes that another workgroup's scan did not see would be those of the matrix before."""
+    _gpu()
+    rng = np.random.default_rng(11)
+    cb = np.array([0.0, 1.0, -1.0, 0.5, 2.0], np.float32)
+    for m in (5003, 1, 15, 4097, 16, 17, 4096, 33, 9000, 4111):
+        p0 = rng.uniform(0.3, 0.95)
+        W = rng.choice(cb, size=(m, 96), p=[p0] + [(1 - p0) / 4] * 4).astype(np.float32)
+        hd = B.cer_encode_device(_to_dev(W), m, 96, cb, fmt)
+        hh = (B.cer_encode if fmt == "cer" else B.cser_encode)(W, cb)
+        for which in (B.CER_ARRAY_ROWPTR, B.CER_ARRAY_OMEGAPTR, B.CER_ARRAY_COLI, B.CER_ARRAY_OMEGAI):
+            assert np.array_equal(B.cer_get_array(hd, which), B.cer_get_array(hh, which)), (m, which)
+        B.cer_free(hd)
+        B.cer_free(hh)
