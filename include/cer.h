@@ -148,8 +148,9 @@ int cer_matmul_noalloc(const cer_handle_t* h, const float* X_dev, float* Y_dev, 
  * a few hundred megabytes from the system again costs more than the product that needs them.  The
  * device memory of freed handles is kept in the same way for later handles (at most 1 GiB), and the host
  * conversions keep up to 15 sleeping threads and 16 MiB of pinned memory.  cer_trim
- * releases whatever is not in use at the moment of the call on the current device; it may wait for
- * work queued on the null stream and may be called at any time.  Errors: CER_E_HIP.
+ * releases whatever is not in use at the moment of the call on the current device; it may be called at
+ * any time.  It may wait for work queued on the null stream, and where it has memory of freed handles to
+ * release it waits for everything queued on the device (hipFree does).  Errors: CER_E_HIP.
  */
 int cer_trim(void);
 
@@ -318,8 +319,11 @@ int64_t cer_device_bytes(const cer_handle_t* h);
  * handles). */
 int64_t cer_long_row_parts(const cer_handle_t* h);
 
-/* Frees host and device memory (the latter may be kept for later handles: cer_trim).  Work already
- * queued on the handle may still be running.  NULL is allowed. */
+/* Frees host and device memory.  Work already queued on the handle may still be running; the call does not
+ * wait for it.  The device memory is kept for later handles, up to 16 blocks and 1 GiB per device (cer_trim
+ * gives it back): other allocators do not see it until then, and what goes beyond that is released at once,
+ * which waits for the device.  The encoder that takes such memory over may have to wait for the device, if the
+ * freed handle was used on a stream other than the null stream.  NULL is allowed. */
 void cer_free(cer_handle_t* h);
 
 /*

@@ -211,14 +211,23 @@ struct HandleBlock {
     void* p = nullptr;
     size_t bytes = 0;
     bool null_stream_only = false;
-    bool idle = false;  // the device has been waited for since the block came back
+    uint64_t returned = 0;  // which block it was that came back, counted from 1; 0: nothing has used it yet
 };
 constexpr size_t kHandleBlocksKept = 16, kHandleBytesKept = (size_t)1 << 30;
 struct HandleCache {
-    std::mutex mu;
+    HandleCache() { kept.reserve(kHandleBlocksKept); }  // never grown later: cer_free does not throw
+    HandleBlock take(size_t i) {
+        const HandleBlock b = kept[i];
+        kept.erase(kept.begin() + (ptrdiff_t)i);
+        kept_bytes -= b.bytes;
+        return b;
+    }
+    std::mutex mu;                    // held for the bookkeeping only, never while the device is waited for
     std::vector<HandleBlock> kept;    // oldest first
     std::vector<HandleBlock> in_use;
     size_t kept_bytes = 0;
+    uint64_t returned = 0;  // blocks that have come back so far
+    uint64_t waited = 0;    // for the first so many of them the device has been waited for since
 };
 HandleCache g_handle_caches[16];
 
@@ -239,29 +248,43 @@ int cer::handle_alloc(void** p, size_t bytes, void* stream) {
     const size_t want = handle_block_bytes(bytes);
     HandleCache* c = handle_cache();
     if (c) {
-        std::lock_guard<std::mutex> lock(c->mu);
-        for (int pass = 0; pass < 2; ++pass) {  // blocks that need no wait come first
-            size_t best = SIZE_MAX;
-            for (size_t i = 0; i < c->kept.size(); ++i) {
-                const HandleBlock& b = c->kept[i];
-                if (b.bytes < want || b.bytes > want + want / 4) continue;
-                if (pass == 0 && !b.idle && !(b.null_stream_only && !stream)) continue;
-                if (best == SIZE_MAX || b.bytes < c->kept[best].bytes) best = i;
+        std::unique_lock<std::mutex> lock(c->mu);
+        size_t best = SIZE_MAX;
+        bool best_waits = true;
+        for (size_t i = 0; i < c->kept.size(); ++i) {  // blocks that need no wait come first, then the smallest
+            const HandleBlock& b = c->kept[i];
+            if (b.bytes < want || b.bytes > want + want / 4) continue;
+            const bool waits = b.returned > c->waited && !(b.null_stream_only && !stream);
+            if (best != SIZE_MAX && (waits != best_waits ? waits : b.bytes >= c->kept[best].bytes)) continue;
+            best = i;
+            best_waits = waits;
+        }
+        if (best != SIZE_MAX) {
+            c->in_use.push_back(c->kept[best]);
+            const HandleBlock b = c->take(best);
+            *p = b.p;
+            if (!best_waits) return (int)hipSuccess;
+            const uint64_t until = c->returned;
+            lock.unlock();
+            const hipError_t e = hipDeviceSynchronize();  // what was queued on the blocks that have come back is done
+            lock.lock();
+            if (e == hipSuccess) {
+                c->waited = std::max(c->waited, until);
+                return (int)hipSuccess;
             }
-            if (best == SIZE_MAX) continue;
-            if (pass == 1) {
-                if (hipDeviceSynchronize() != hipSuccess) {  // also under capture: a fresh block then
-                    (void)hipGetLastError();
+            (void)hipGetLastError();  // also under capture: a fresh block then
+            for (size_t i = c->in_use.size(); i-- > 0;)
+                if (c->in_use[i].p == b.p) {
+                    c->in_use.erase(c->in_use.begin() + (ptrdiff_t)i);
                     break;
                 }
-                for (HandleBlock& b : c->kept) b.idle = true;
+            if (c->kept.size() < kHandleBlocksKept) {
+                c->kept.push_back(b);
+                c->kept_bytes += b.bytes;
+            } else {
+                lock.unlock();
+                (void)hipFree(b.p);
             }
-            const HandleBlock b = c->kept[best];
-            c->in_use.push_back(b);
-            c->kept.erase(c->kept.begin() + (ptrdiff_t)best);
-            c->kept_bytes -= b.bytes;
-            *p = b.p;
-            return (int)hipSuccess;
         }
     }
     hipError_t e = hipMalloc(p, want);
@@ -271,8 +294,13 @@ int cer::handle_alloc(void** p, size_t bytes, void* stream) {
         e = hipMalloc(p, want);
     }
     if (e == hipSuccess && c) {
-        std::lock_guard<std::mutex> lock(c->mu);
-        c->in_use.push_back(HandleBlock{*p, want, false, true});
+        try {
+            std::lock_guard<std::mutex> lock(c->mu);
+            c->in_use.push_back(HandleBlock{*p, want, false, 0});
+        } catch (...) {
+            (void)hipFree(*p);
+            throw;
+        }
     }
     return (int)e;
 }
@@ -281,7 +309,8 @@ void cer::handle_free(void* p, bool null_stream_only) {
     if (!p) return;
     // the block may belong to a device that is not the current one
     for (HandleCache& c : g_handle_caches) {
-        std::vector<void*> out;
+        void* out[kHandleBlocksKept + 1];
+        size_t n_out = 0;
         bool found = false;
         {
             std::lock_guard<std::mutex> lock(c.mu);
@@ -291,21 +320,18 @@ void cer::handle_free(void* p, bool null_stream_only) {
                 HandleBlock b = c.in_use[i];
                 c.in_use.erase(c.in_use.begin() + (ptrdiff_t)i);
                 b.null_stream_only = null_stream_only;
-                b.idle = false;
+                b.returned = ++c.returned;
                 if (b.bytes > kHandleBytesKept) {
-                    out.push_back(b.p);
+                    out[n_out++] = b.p;
                     break;
                 }
-                while (!c.kept.empty() && (c.kept.size() >= kHandleBlocksKept || c.kept_bytes + b.bytes > kHandleBytesKept)) {
-                    out.push_back(c.kept[0].p);
-                    c.kept_bytes -= c.kept[0].bytes;
-                    c.kept.erase(c.kept.begin());
-                }
+                while (!c.kept.empty() && (c.kept.size() >= kHandleBlocksKept || c.kept_bytes + b.bytes > kHandleBytesKept))
+                    out[n_out++] = c.take(0).p;
                 c.kept.push_back(b);
                 c.kept_bytes += b.bytes;
             }
         }
-        for (void* q : out) (void)hipFree(q);
+        for (size_t i = 0; i < n_out; ++i) (void)hipFree(out[i]);
         if (found) return;
     }
     (void)hipFree(p);
@@ -1063,10 +1089,13 @@ int cer_trim(void) {
     }
     {
         HandleCache& c = g_handle_caches[dev];
-        std::lock_guard<std::mutex> lock(c.mu);
-        for (const HandleBlock& b : c.kept) (void)hipFree(b.p);
-        c.kept.clear();
-        c.kept_bytes = 0;
+        void* out[kHandleBlocksKept];
+        size_t n_out = 0;
+        {
+            std::lock_guard<std::mutex> lock(c.mu);
+            while (!c.kept.empty()) out[n_out++] = c.take(0).p;
+        }
+        for (size_t i = 0; i < n_out; ++i) (void)hipFree(out[i]);
     }
     TempPool& t = g_temp_pools[dev];
     std::lock_guard<std::mutex> lock(t.mu);

@@ -79,3 +79,39 @@ def test_a_freed_handles_memory_serves_the_next_one_in_order(side_stream):
         want = W.astype(np.float64) @ X.cpu().numpy().astype(np.float64)
         bound = 1e-5 * (np.abs(W).astype(np.float64) @ np.abs(X.cpu().numpy()).astype(np.float64))
         assert (np.abs(Y.cpu().numpy() - want) <= bound).all()
+
+
+def test_freeing_a_handle_does_not_wait_for_another_threads_encoder():
+    """An encoder that takes over the memory of a handle with work still queued on a side stream waits for the device; a handle
+    that is freed by another thread in the meantime is not held up by that."""
+    dev = torch.device("cuda:0")
+    cb = np.array([-1.0, 0.0, 1.0, 2.0], np.float32)
+    rng = np.random.default_rng(5)
+    W = rng.choice(cb, size=(700, 900), p=[0.1, 0.7, 0.1, 0.1]).astype(np.float32)
+    other = B.cer_encode(rng.choice(cb, size=(2000, 1500)).astype(np.float32), cb)
+    x1, y1 = torch.randn((900, 1), device=dev), torch.empty((700, 1), device=dev)
+    big, xb, yb = (torch.randn((4096, 4096), device=dev) for _ in range(3))
+    stream, done = torch.cuda.Stream(), torch.cuda.Event()
+    torch.cuda.synchronize()
+    B.cer_trim()                                           # no other block of that size
+    first = B.cer_encode(W, cb)
+    B.cer_matmul(first, x1, y1, 1, stream)
+    for _ in range(600):                                   # about a second on the side stream
+        B.dense_matmul(big, xb, yb, 4096, 4096, 4096, stream)
+    done.record(stream)
+    B.cer_free(first)
+    taken = []
+    encoder = threading.Thread(target=lambda: taken.append(B.cer_encode(W, cb)))
+    encoder.start()
+    encoder.join(0.1)
+    waiting = encoder.is_alive()                           # it is in its wait for the device
+    B.cer_free(other)
+    pending = not done.query()
+    encoder.join()
+    torch.cuda.synchronize()
+    assert waiting and pending
+    Y = torch.empty((700, 1), device=dev)
+    B.cer_matmul(taken[0], x1, Y, 1)
+    assert torch.equal(Y, y1)
+    B.cer_free(taken[0])
+    B.cer_trim()
