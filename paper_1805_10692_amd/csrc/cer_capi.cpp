@@ -110,17 +110,26 @@ bool capturing(hipStream_t s) {
     return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
 }
 
-// Gives kept block i back to the runtime's pool.
-void release_kept(TempCache& c, size_t i) {
-    const TempBlock b = c.kept[i];
-    c.kept.erase(c.kept.begin() + (ptrdiff_t)i);
-    c.kept_bytes -= b.bytes;
-    if (b.done) {
-        (void)hipEventSynchronize(b.done);
-        c.spare(b.done);
+// Blocks on their way back to the runtime's pool: taken from the list under its lock, released without it (release may
+// have to wait for the work that used a block last).
+struct TempLeaving {
+    TempBlock block[kBlocksKept];
+    size_t count = 0;
+    void take(TempCache& c, size_t i) {
+        block[count++] = c.kept[i];
+        c.kept_bytes -= c.kept[i].bytes;
+        c.kept.erase(c.kept.begin() + (ptrdiff_t)i);
     }
-    (void)hipFreeAsync(b.p, nullptr);
-}
+    void release(TempCache& c) {
+        for (size_t i = 0; i < count; ++i) {
+            if (block[i].done) (void)hipEventSynchronize(block[i].done);
+            (void)hipFreeAsync(block[i].p, nullptr);
+        }
+        std::lock_guard<std::mutex> lock(c.mu);
+        for (size_t i = 0; i < count; ++i)
+            if (block[i].done) c.spare(block[i].done);
+    }
+};
 }  // namespace
 
 int cer::temp_alloc(void** p, size_t bytes, void* stream) {
@@ -175,7 +184,7 @@ int cer::temp_free(void* p, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     TempCache* c = temp_cache();
     if (c) {
-        std::lock_guard<std::mutex> lock(c->mu);
+        std::unique_lock<std::mutex> lock(c->mu);
         for (size_t i = c->in_use.size(); i-- > 0;) {
             if (c->in_use[i].p != p) continue;
             TempBlock b = c->in_use[i];
@@ -196,9 +205,12 @@ int cer::temp_free(void* p, void* stream) {
                 if (!keep) (void)hipGetLastError();
             }
             if (!keep) break;
-            while (!c->kept.empty() && (c->kept.size() >= kBlocksKept || c->kept_bytes + b.bytes > kBytesKept)) release_kept(*c, 0);
+            TempLeaving out;
+            while (!c->kept.empty() && (c->kept.size() >= kBlocksKept || c->kept_bytes + b.bytes > kBytesKept)) out.take(*c, 0);
             c->kept.push_back(b);
             c->kept_bytes += b.bytes;
+            lock.unlock();
+            if (out.count) out.release(*c);
             return (int)hipSuccess;
         }
     }
@@ -1072,14 +1084,17 @@ int cer_trim(void) {
     if (dev < 0 || dev >= 16) return CER_OK;
     {
         TempCache& c = g_temp_caches[dev];
-        std::lock_guard<std::mutex> lock(c.mu);
-        for (size_t i = c.kept.size(); i-- > 0;) {
-            if (c.kept[i].done && hipEventQuery(c.kept[i].done) != hipSuccess) {
-                (void)hipGetLastError();  // still in use
-                continue;
+        TempLeaving out;
+        {
+            std::lock_guard<std::mutex> lock(c.mu);
+            for (size_t i = c.kept.size(); i-- > 0;) {
+                if (c.kept[i].done && hipEventQuery(c.kept[i].done) != hipSuccess)
+                    (void)hipGetLastError();  // still in use
+                else
+                    out.take(c, i);
             }
-            release_kept(c, i);
         }
+        out.release(c);
     }
     {
         std::lock_guard<std::mutex> lock(g_stage_mutex);

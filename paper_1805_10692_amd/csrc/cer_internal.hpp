@@ -162,7 +162,8 @@ int record_hip_error(int hip_error);
 // released and, behind it, from a memory pool of the library's own on the current device, which keeps what it has
 // handed out once (release threshold: none) -- the default pool gives its memory back at every synchronisation, and
 // getting a few hundred megabytes again costs more than the product that needs them.  cer_trim() releases what is
-// cached.  Neither call waits for the stream.  Both return a hipError_t value as int.
+// cached.  Neither call waits for the stream, but a release that finds the list full (32 blocks, 2 GiB) gives the oldest
+// blocks back to the runtime and waits for their last use.  Both return a hipError_t value as int.
 int temp_alloc(void** p, size_t bytes, void* stream);
 int temp_free(void* p, void* stream);
 

@@ -115,3 +115,31 @@ def test_freeing_a_handle_does_not_wait_for_another_threads_encoder():
     assert torch.equal(Y, y1)
     B.cer_free(taken[0])
     B.cer_trim()
+
+
+def test_more_streams_than_kept_blocks():
+    """Forty streams with work queued in front of their products hold forty temporaries at once, more than the list keeps: the
+    oldest go back to the runtime while later ones are in use."""
+    dev = torch.device("cuda:0")
+    cb = np.array([0.0, 1.0, -0.75, 3.0], np.float32)
+    rng = np.random.default_rng(9)
+    W = rng.choice(cb, size=(300, 500), p=[0.4, 0.2, 0.2, 0.2]).astype(np.float32)
+    X = rng.standard_normal((500, 70)).astype(np.float32)
+    want = W.astype(np.float64) @ X.astype(np.float64)
+    bound = 1e-5 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64))
+    h = B.cer_encode(W, cb)
+    Xd = torch.from_numpy(X).to(dev)
+    big, xb, yb = (torch.randn((2048, 2048), device=dev) for _ in range(3))
+    streams = [torch.cuda.Stream() for _ in range(40)]
+    outs = [torch.full((300, 70), float("nan"), device=dev) for _ in streams]
+    torch.cuda.synchronize()
+    B.cer_trim()
+    for _ in range(3):
+        for s, Y in zip(streams, outs):
+            B.dense_matmul(big, xb, yb, 2048, 2048, 2048, s)
+            B.cer_matmul_ex(h, Xd, Y, 70, s, B.MatmulOpts(path=B.CER_PATH_DENSE))
+    torch.cuda.synchronize()
+    for Y in outs:
+        assert (np.abs(Y.cpu().numpy() - want) <= bound).all()
+    B.cer_trim()
+    B.cer_free(h)
