@@ -4,6 +4,7 @@
 
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -685,6 +686,9 @@ int upload(cer_matrix* h) {
     return cer::build_row_schedule(h, start);
 }
 
+// A handle under construction: also an exception (no host memory for the image of its arrays) gives its memory back.
+using HandleOwner = std::unique_ptr<cer_matrix, void (*)(cer_handle_t*)>;
+
 int encode_any(const float* W, int64_t m, int64_t n, const float* codebook, int32_t K, bool cser, cer_handle_t** out) {
     if (!out) return CER_E_INVALID;
     *out = nullptr;
@@ -696,14 +700,11 @@ int encode_any(const float* W, int64_t m, int64_t n, const float* codebook, int3
         std::shared_ptr<cer::HostMatrix> host;
         int rc = cer::encode_host(W, m, n, codebook, K, cser, &host);
         if (rc != CER_OK) return rc;
-        auto* h = new cer_matrix();
+        HandleOwner h(new cer_matrix(), cer_free);
         h->host = std::move(host);
-        rc = upload(h);
-        if (rc != CER_OK) {
-            cer_free(h);
-            return rc;
-        }
-        *out = h;
+        rc = upload(h.get());
+        if (rc != CER_OK) return rc;
+        *out = h.release();
         return CER_OK;
     } catch (const std::bad_alloc&) {
         return CER_E_NOMEM;
@@ -894,14 +895,11 @@ int cer_clone_device(const cer_handle_t* h, cer_handle_t** out) {
     try {
         int rc = cer::ensure_host_arrays(h);
         if (rc != CER_OK) return rc;
-        auto* c = new cer_matrix();
+        HandleOwner c(new cer_matrix(), cer_free);
         c->host = h->host;
-        rc = upload(c);
-        if (rc != CER_OK) {
-            cer_free(c);
-            return rc;
-        }
-        *out = c;
+        rc = upload(c.get());
+        if (rc != CER_OK) return rc;
+        *out = c.release();
         return CER_OK;
     } catch (const std::bad_alloc&) {
         return CER_E_NOMEM;
