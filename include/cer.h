@@ -194,12 +194,18 @@ int cer_trim(void);
  * 128-byte line per index however narrow the batch) and loses for wide ones (random LDS gathers
  * are bank-conflict bound): it is chosen when it is applicable, batch <= 8 and the matrix holds
  * at least 2.5 million indices.
- * Where batch <= 16, the codebook holds at most 256 values and the estimates say so, the library's own choice
- * runs the batch-1 stream kernel for several columns at once instead of the kernel that is reported here
- * (the number reported stays that of the kernel that serves the batch without it).
+ * Where batch <= 16, the codebook holds 2 to 256 values, X fits in LDS in one of its widths and the estimates say
+ * so, the library's own choice runs the batch-1 stream kernel for several columns at once instead of the kernel that
+ * is reported here (the number reported stays that of the kernel that serves the batch without it):
+ * cer_matmul_narrow_columns tells.
  * Errors: CER_E_INVALID, CER_E_HIP (no device copy).
  */
 int cer_matmul_path(const cer_handle_t* h, int64_t batch);
+
+/* Whether cer_matmul / cser_matmul run the stream kernel for several columns for this handle and batch, in place of the
+ * kernel that cer_matmul_path reports: the columns of X it takes per pass (1, 2, 4 or 8), 0 where they do not.  (cer_matmul_ex
+ * with a path, flags or a tile width, and cer_matmul_noalloc, never do.)  Errors: CER_E_INVALID, CER_E_HIP (no device copy). */
+int cer_matmul_narrow_columns(const cer_handle_t* h, int64_t batch);
 
 /*
  * cer_matmul_ex -- cer_matmul / cser_matmul (it accepts handles of both formats) with the caller's

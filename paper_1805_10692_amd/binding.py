@@ -42,6 +42,7 @@ EXPORTS = [
     "csr_clone_device", "csr_free", "cer_cost_model", "csr_cost_model", "dense_cost_model",
     "cer_encode_device", "cer_quantize_uniform", "cer_quantize_encode_device", "cer_matmul_path", "cer_stream_read",
     "cer_decode_device", "cer_trim", "cer_matmul_ex", "cer_matmul_path_ex", "cer_matmul_noalloc", "cer_prepare_strips",
+    "cer_matmul_narrow_columns",
 ]
 
 CER_FORMAT_CER, CER_FORMAT_CSER = 0, 1
@@ -160,6 +161,8 @@ def lib() -> ctypes.CDLL:
         L.cer_trim.argtypes = []
         L.cer_matmul_path.restype = ctypes.c_int
         L.cer_matmul_path.argtypes = [vp, i64]
+        L.cer_matmul_narrow_columns.restype = ctypes.c_int
+        L.cer_matmul_narrow_columns.argtypes = [vp, i64]
         L.cer_prepare_strips.restype = ctypes.c_int
         L.cer_prepare_strips.argtypes = [vp]
         L.cer_matmul_noalloc.restype = ctypes.c_int
@@ -309,11 +312,19 @@ def cer_trim() -> None:
 
 def cer_matmul_path(h: Handle, batch: int) -> int:
     """0 = batch-1 kernel, 1 = batched kernel gathering from L2, 2 = batched kernel with X resident in LDS,
-    3 = decode into a dense temporary + fp32 matrix-core product (large batches of not-so-sparse matrices),
-    4 = batch-1 kernel for rows of many short groups."""
+    3 = decode into a dense temporary + matrix-core product (large batches of not-so-sparse matrices),
+    4 = batch-1 kernel for rows of many short groups, 5 = batched kernel with strips of X in LDS."""
     rc = lib().cer_matmul_path(h.ptr, batch)
     if rc < 0:
         _check(rc, "cer_matmul_path")
+    return rc
+
+
+def cer_matmul_narrow_columns(h: Handle, batch: int) -> int:
+    """Columns per pass where cer_matmul runs the stream kernel for several columns instead; 0 where it does not."""
+    rc = lib().cer_matmul_narrow_columns(h.ptr, batch)
+    if rc < 0:
+        _check(rc, "cer_matmul_narrow_columns")
     return rc
 
 

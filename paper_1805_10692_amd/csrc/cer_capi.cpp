@@ -823,6 +823,12 @@ int cer_matmul_path_ex(const cer_handle_t* h, int64_t batch, const cer_matmul_op
 }
 int cer_matmul_path(const cer_handle_t* h, int64_t batch) { return cer_matmul_path_ex(h, batch, nullptr); }
 
+int cer_matmul_narrow_columns(const cer_handle_t* h, int64_t batch) {
+    if (!h || batch < 1) return CER_E_INVALID;
+    if (h->device < 0 || !h->d_base) return CER_E_HIP;
+    return cer::matmul_narrow_columns(h->view, batch);
+}
+
 int cer_decode(const cer_handle_t* h, float* W_out) { return decode_any(h, false, W_out); }
 int cser_decode(const cer_handle_t* h, float* W_out) { return decode_any(h, true, W_out); }
 

@@ -408,8 +408,12 @@ double mfma_estimate_us(const DeviceView& d, uint32_t L);
 hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream);
 
 // cer_narrow.hip -- batches of 2 to 16 columns, the stream kernel of batch 1 for several columns at once (sums X itself).
-// narrow_estimate_us: huge where it is not applicable.
-double narrow_estimate_us(const DeviceView& d, uint32_t L);
+// NarrowEstimate: the columns per pass it would take, 0 and a huge duration where it is not applicable.
+struct NarrowEstimate {
+    int columns = 0;
+    double us = 1e30;
+};
+NarrowEstimate narrow_estimate(const DeviceView& d, uint32_t L);
 hipError_t launch_narrow(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream);
 
 // cer_strip.hip -- batch > 1, strips of X resident in LDS (needs the strip-major index of cer_prepare_strips)

@@ -223,6 +223,14 @@ double path_estimate_us(const DeviceView& d, uint32_t L, int path) {
     return gather_estimate(d, L) * 1e6;
 }
 
+// Columns per pass of the stream kernel for several columns, where the library's own choice for a few columns is that kernel
+// instead of `path` (a path, flags or a tile width of the caller's speak of the others); else 0.
+int choose_narrow(const DeviceView& d, uint32_t L, const MatmulOptions& o, int path) {
+    if (L < 2 || L > 16 || o.path >= 0 || o.flags != 0 || o.tile_cols != 0) return 0;
+    const NarrowEstimate narrow = narrow_estimate(d, L);
+    return narrow.us < path_estimate_us(d, L, path) ? narrow.columns : 0;
+}
+
 // Column sums of X for a non-zero most frequent value: shape of the two-stage sum and the floats it needs
 // ([T: L rounded to 64][partials: nslabs x L]).
 struct ColsumPlan {
@@ -255,6 +263,11 @@ int matmul_path(const DeviceView& d, int64_t L, const MatmulOptions& o) {
     if (L <= 1) return gemv_path(d, o);
     if (L > 0x7FFFFFFFll) return 1;
     return choose_batched_path(d, (uint32_t)L, o, false, nullptr);
+}
+
+int matmul_narrow_columns(const DeviceView& d, int64_t L) {
+    const MatmulOptions o;
+    return L < 2 || L > 16 ? 0 : choose_narrow(d, (uint32_t)L, o, choose_batched_path(d, (uint32_t)L, o, false, nullptr));
 }
 
 size_t matmul_workspace_floats(const DeviceView& d, int64_t L, const MatmulOptions& o) {
@@ -294,12 +307,8 @@ int launch_matmul(const DeviceView& d, const float* X, float* Y, int64_t L64, vo
     if (no_temporaries) o.flags |= kOptRowsWhole;  // the parts of split rows meet in a temporary
     XtilePlan plan;
     const int batched_path = L > 1 ? choose_batched_path(d, L, o, no_temporaries, &plan, X, Y) : 0;
-    // the library's own choice for a few columns
-    if (L > 1 && L <= 16 && o.path < 0 && o.flags == 0 && o.tile_cols == 0 && !no_temporaries &&
-        narrow_estimate_us(d, L) < path_estimate_us(d, L, batched_path))
-        return (int)launch_narrow(d, X, Y, L, stream);
+    if (!no_temporaries && choose_narrow(d, L, o, batched_path) > 0) return (int)launch_narrow(d, X, Y, L, stream);
     if (batched_path == 3) return (int)launch_densified(d, X, Y, L, stream);
-
 
     float* T = nullptr;
     float* scratch = nullptr;

@@ -286,9 +286,9 @@ hipError_t launch_narrow_t(const NarrowPlan& p, const NarrowArgs& a, size_t budg
 
 }  // namespace
 
-double narrow_estimate_us(const DeviceView& d, uint32_t L) {
+NarrowEstimate narrow_estimate(const DeviceView& d, uint32_t L) {
     const NarrowPlan p = plan_narrow(d, L);
-    return p.V > 0 ? p.us : 1e30;
+    return p.V > 0 ? NarrowEstimate{p.V, p.us} : NarrowEstimate{};
 }
 
 hipError_t launch_narrow(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream) {

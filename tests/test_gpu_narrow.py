@@ -1,4 +1,4 @@
-"""Batches of 2 to 8 columns by the library's own choice (csrc/cer_narrow.hip): every number of columns per pass, 8- and 16-bit
+"""Batches of 2 to 16 columns by the library's own choice (csrc/cer_narrow.hip): every number of columns per pass, 8- and 16-bit
 indices, one to four tiles of groups, rows shared by several waves, rows of several windows, unaligned X, non-zero Omega[0]."""
 import numpy as np
 import pytest
@@ -49,3 +49,41 @@ def test_unaligned_input_and_non_zero_most_frequent_value(L):
 def test_groups_of_columns_that_overlap(shape, L):
     m, n, K = shape
     _check(m, n, L, K, 0.35, K // 2, "cser" if L % 2 else "cer", shift=L % 3)
+
+
+# (m, n, K, share of the most frequent value, columns of X, columns per pass): one to four tiles of groups, 8- and 16-bit indices,
+# a single wave and several per row; 0 per pass: the kernel that cer_matmul_path reports serves the batch
+CHOICES = [
+    (9, 36000, 4, 0.4, 8, 1), (40, 17000, 130, 0.4, 4, 1),
+    (300, 3000, 16, 0.4, 2, 2), (40, 17000, 130, 0.4, 7, 2), (256, 12000, 140, 0.8, 15, 2), (300, 100, 2, 0.4, 2, 2),
+    (300, 3000, 16, 0.4, 5, 4), (700, 600, 30, 0.4, 16, 4), (3000, 250, 100, 0.4, 11, 4), (1500, 1500, 200, 0.4, 3, 4),
+    (2100, 700, 256, 0.4, 12, 4),
+    (2100, 700, 256, 0.8, 5, 8), (2100, 700, 256, 0.8, 8, 8), (3000, 250, 100, 0.8, 13, 8), (3000, 250, 100, 0.8, 16, 8),
+    (2100, 700, 256, 0.4, 13, 0), (300, 3000, 16, 0.4, 17, 0),
+]
+
+
+@pytest.mark.parametrize("case", CHOICES, ids=[f"{c[0]}x{c[1]}_K{c[2]}_{c[3]}_L{c[4]}_{c[5]}" for c in CHOICES])
+def test_the_library_takes_the_kernel_this_file_is_about(case):
+    """... with the stated number of columns per pass; that it ran shows in the rounding, which is not that of the kernel that
+    cer_matmul_path reports (and is where the library does not take it)."""
+    m, n, K, p0, L, columns = case
+    rng = np.random.default_rng(1)
+    cb = (np.arange(K) - K // 2).astype(np.float32) / np.float32(K)
+    p = np.full(K, (1 - p0) / (K - 1))
+    p[K // 2] = p0
+    W = rng.choice(cb, size=(m, n), p=p).astype(np.float32)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    h = B.cer_encode(W, cb)
+    Xd = torch.from_numpy(X).cuda()
+    Y, other = (torch.full((m, L), float("nan"), device="cuda") for _ in range(2))
+    assert B.cer_matmul_narrow_columns(h, L) == columns
+    B.cer_matmul(h, Xd, Y, L)
+    B.cer_matmul_ex(h, Xd, other, L, None, B.MatmulOpts(path=B.cer_matmul_path(h, L)))
+    torch.cuda.synchronize()
+    B.cer_free(h)
+    assert torch.equal(Y, other) == (columns == 0)
+    want = W.astype(np.float64) @ X.astype(np.float64)
+    bound = 1e-5 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64)) + 1e-30
+    for y in (Y, other):
+        assert (np.abs(y.cpu().numpy() - want) <= bound).all()
