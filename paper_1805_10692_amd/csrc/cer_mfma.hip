@@ -136,7 +136,7 @@ struct MfmaTile {
 #pragma unroll
             for (int p = 0; p < 3; ++p) b[buf][p][xg][xc] = o[p];
         };
-        floatx16 acc[TM][TN];
+        floatx16 acc[TM][TN], lo[TM][TN];
         auto clear = [](floatx16 (&v)[TM][TN]) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
@@ -145,7 +145,14 @@ struct MfmaTile {
 #pragma unroll
                     for (int e = 0; e < 16; ++e) v[i][j][e] = 0.f;
         };
+        auto flush = [&] {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) sum[i][j] += PW > 1 ? acc[i][j] + lo[i][j] : acc[i][j];
+        };
         clear(acc);
+        clear(lo);
         clear(sum);
 #pragma unroll
         for (int s = 0; s + 1 < D; ++s) load_x(k_begin + s * BK, s);
@@ -170,7 +177,7 @@ struct MfmaTile {
 #pragma unroll
                     for (int i = 0; i < TM; ++i)
 #pragma unroll
-                        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_pieces<PW>(a[t & 1][s][i], bb[j], acc[i][j]);
+                        for (int j = 0; j < TN; ++j) mfma_pieces<PW>(a[t & 1][s][i], bb[j], acc[i][j], lo[i][j]);
                 }
                 store_x((t + 1) % D, (t + 1) & 1);
                 __syncthreads();
@@ -178,17 +185,12 @@ struct MfmaTile {
             held += D * BK;
             if (held >= kFlush) {
                 held = 0;
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) sum[i][j] += acc[i][j];
+                flush();
                 clear(acc);
+                clear(lo);
             }
         }
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) sum[i][j] += acc[i][j];
+        flush();
         return odd;
     }
 };
@@ -271,6 +273,7 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
 #pragma unroll
     for (int j = 0; j < CT; ++j) xstep[j] = (min(col0 + 32u * j + (lane & 31u), L - 1u) - min(col0 + (lane & 31u), L - 1u)) * 4u;
     uint4 a[2][2][2][PW];
+    floatx16 lo[2][CT];
     float x[2][2][CT][8];
     float odd = 0.f;
     auto load = [&](uint32_t k0, int slot) {
@@ -297,7 +300,7 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
                 uint4 b[3];
                 odd += split3_8(x[slot][s][j], b);
 #pragma unroll
-                for (int i = 0; i < 2; ++i) acc[i][j] = mfma_pieces<PW>(a[slot][s][i], b, acc[i][j]);
+                for (int i = 0; i < 2; ++i) mfma_pieces<PW>(a[slot][s][i], b, acc[i][j], lo[i][j]);
             }
     };
 #pragma unroll
@@ -305,7 +308,7 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
 #pragma unroll
         for (int j = 0; j < CT; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = lo[i][j][e] = 0.f;
     uint32_t k0 = k_begin + 32u * wave;
     if (k0 >= k_end) return odd;
     load(k0, 0);
@@ -316,6 +319,12 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
         load(min(k0 + 128u, k_end - 32u), 0);
         step(1);
         if ((k0 += 128u) >= k_end) break;
+    }
+    if (PW > 1) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < CT; ++j) acc[i][j] += lo[i][j];
     }
     return odd;
 }

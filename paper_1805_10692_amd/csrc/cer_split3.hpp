@@ -2,12 +2,19 @@
 //
 // A binary32 significand has 24 bits, a bf16 one has 8: x = p0 + p1 + p2 with p0 = bf16(x), p1 = bf16(x - p0),
 // p2 = x - p0 - p1 is exact (both differences are exact in binary32, the last one fits 8 bits), for |x| from 2^-110 up to the
-// largest number that rounds to a finite bf16 one.  Other numbers have no such pieces -- those below lose what lies under 2^-133,
-// the smallest bf16 number -- and a product that meets them (below 2^-110: in which that shows) is formed in binary32.  Products of two pieces are exact in binary32 and the matrix cores add them up in binary32, so a
-// contraction over pieces has the inputs and the accumulation of the fp32 one.  Where both factors have three pieces the
-// three smallest of the nine products are left out: together below 2^-25 of the product, half a unit of what rounding a
-// binary32 product costs.  The bf16 matrix instructions run at 16 times the rate of the fp32 ones: three products (one
-// factor with 8-bit significands) or six cost a fifth to three eighths of the fp32 instruction's time.
+// largest number that rounds to a finite bf16 one.  Other numbers have no such pieces -- those below lose what lies under
+// 2^-133, the smallest bf16 number -- and a product that meets them (below 2^-110: in which that shows) is formed in binary32.
+//
+// Products of two pieces are exact in binary32 and the matrix cores add them up in binary32, so a contraction over pieces has
+// the inputs and the accumulation of the fp32 one.  With two pieces of the weight one of its six products is left out, with
+// three pieces three of nine: together below 2^-25 of the product, half a unit of what rounding a binary32 product costs.
+// Against fp64 the sums come closer than with the fp32 matrix instructions (2-norm; X normal, and the same cut at 0):
+//                        one piece             two                   three                 fp32 instruction
+//   512 x 4608           1.3e-7  4.9e-8        7.3e-8  4.3e-8        8.9e-8  7.6e-8        2.3e-7  1.5e-7 - 5.6e-8
+//   700 x 1200           1.2e-7  5.4e-8        6.1e-8  4.3e-8        7.4e-8  6.3e-8        1.6e-7  1.2e-7 - 5.5e-8
+//   256 x 25088          1.6e-7  6.4e-8        1.1e-7  6.5e-8        1.2e-7  8.7e-8        3.6e-7  1.8e-7 - 6.7e-8
+// The bf16 matrix instructions run at 16 times the rate of the fp32 ones: three products (one piece), five or six cost a fifth
+// to three eighths of the fp32 instruction's time.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -68,15 +75,19 @@ __device__ __forceinline__ floatx16 mfma_bf16(uint4 a, uint4 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// The products of PW pieces of one factor with three of the other that reach 2^-25 of the result, smallest first.
+// The products of PW pieces of one factor with three of the other that reach 2^-25 of the result.  PW > 1: all but the largest
+// are added up apart, in lo -- every matrix instruction rounds the sum it adds to, and in one sum the four or five small
+// products rounded it as often as the large one: errors of 2.3e-7 against 1.6e-7 with binary32 products (700 x 1200, 2-norm).
 template <int PW>
-__device__ __forceinline__ floatx16 mfma_pieces(const uint4* a, const uint4* b, floatx16 c) {
+__device__ __forceinline__ void mfma_pieces(const uint4* a, const uint4* b, floatx16& hi, floatx16& lo) {
 #pragma unroll
     for (int s = 2; s >= 0; --s)
 #pragma unroll
         for (int i = 0; i < PW; ++i)
-            if (s - i >= 0) c = mfma_bf16(a[i], b[s - i], c);
-    return c;
+            if (s - i >= 0) {
+                floatx16& c = PW > 1 && s > 0 ? lo : hi;
+                c = mfma_bf16(a[i], b[s - i], c);
+            }
 }
 
 // X from row `row` on, as a buffer that ends with row `end` - 1: loads behind it return zero.  The range check of a buffer load

@@ -78,6 +78,26 @@ def test_infinities_and_nans(shape, pieces):
     assert (np.abs(Y[:, keep] - want) <= 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X[:, keep]).astype(np.float64))).all()
 
 
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("pieces", list(CODEBOOKS))
+@pytest.mark.parametrize("shape", [(700, 1200, 60), (2000, 500, 300), (512, 4608, 512)])
+def test_no_less_precise_than_fp32_products(shape, pieces, relu):
+    """Against fp64, in the 2-norm: not further off than the fp32 matrix cores, which serve the same matrix when one of its values has
+    no pieces (a subnormal one, in a row that is left out here)."""
+    m, n, L = shape
+    rng = np.random.default_rng(n)
+    cb = CODEBOOKS[pieces]
+    W = rng.choice(cb, size=(m, n), p=[0.4, 0.2, 0.2, 0.2]).astype(np.float32)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    if relu:
+        X = np.maximum(X, 0)
+    want = (W.astype(np.float64) @ X.astype(np.float64))[1:]
+    errors = [np.linalg.norm(_product(W, cb, X)[1:] - want)]
+    W[0, 0] = np.float32(1e-40)
+    errors.append(np.linalg.norm(_product(W, np.append(cb, W[0, 0]), X)[1:] - want))
+    assert errors[0] <= errors[1], errors
+
+
 def _tiny_cases():
     """Inputs of one size (2^-k times normal ones), inputs over 140 powers of two in one column, and inputs of ordinary size that a
     third of W's rows does not touch -- what these rows see is tiny."""
