@@ -76,16 +76,19 @@ def make_workload(name: str):
     raise SystemExit(f"unknown workload {name}")
 
 
-def kernel_name(fmt: str, L: int, path, K: int = 0, n: int = 0) -> str:
+def kernel_name(fmt: str, L: int, path, K: int = 0, n: int = 0, narrow: int = 0) -> str:
     """The kernel that dominates a product (cer_matmul_path's numbering for cer / cser).  Batch 1: handles of 2 - 256
-    values whose X fits in LDS (every benchmark configuration) run the rank-table kernel."""
+    values whose X fits in LDS (every benchmark configuration) run the rank-table kernel.  narrow: what
+    cer_matmul_narrow_columns says."""
+    if narrow:
+        return "cer_narrow_kernel"
     if fmt == "csr":
         return "csr_gemv_kernel" if L == 1 else "csr_gemm_kernel"
     if path == 0 and 2 <= K <= 256 and 0 < n <= 36000:
         return "cer_gemv_tab_kernel"
     return {0: "cer_gemv_kernel",
             1: "cer_gemm_expand_kernel",
-            2: "cer_xtile_kernel", 3: "decode_kernel + dense_gemm_mfma_kernel", 4: "cer_gemv_expand_kernel",
+            2: "cer_xtile_kernel", 3: "decode_tiles_kernel + mfma_product_kernel", 4: "cer_gemv_expand_kernel",
             5: "cer_strip_kernel"}[path]
 
 
@@ -275,6 +278,7 @@ def run_one(name: str, fmt: str, steps: int, warmup: int, warm: bool, with_cpu: 
         "gather_GBps_onchip": dims["nnz"] * 4.0 * L / (ev_ms * 1e-3) / 1e9,
         "dense_bytes": 4 * (w.m * w.n + w.n * L + w.m * L),
         "path": None if fmt == "csr" else B.cer_matmul_path_ex(h0, L, opts),
+        "narrow_columns": 0 if fmt == "csr" or opts is not None else B.cer_matmul_narrow_columns(h0, L),
     }
     for h in handles[1:]:
         free(h)
@@ -527,7 +531,7 @@ def main() -> int:
                                      "k_bar", "k_tilde", "cache_state", "path")},
         "roofline": {"bound": "hbm", "achieved": r["algorithmic_GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": r["algorithmic_GBps"] / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_source,
-                     "kernel": kernel_name(args.format, r["L"], r["path"], r["K"], r["n"]),
+                     "kernel": kernel_name(args.format, r["L"], r["path"], r["K"], r["n"], r["narrow_columns"]),
                      "algorithmic_bytes_per_launch": r["algorithmic_bytes"],
                      "event_us_per_launch": r["event_ms_per_step"] * 1e3},
         "cpu_baseline": r.get("cpu_baseline"),

@@ -180,10 +180,11 @@ int cer_trim(void);
  *      on the matrix cores: as one to three bf16 matrices that add up to it exactly (2.m.n bytes each), with
  *      X split into three in the same way, or as fp32 (4.m.n bytes) where a value or an index range rules
  *      that out.  The inputs keep all 24 bits of their significands, products are exact or within 2^-25,
- *      sums are fp32.  Chosen when the estimated time of the gathers
- *      (max(4.batch, 128) bytes per indexed element through the L1/L2 path) exceeds that of the
- *      decode and the dense contraction: wide batches of matrices with more than about one
- *      indexed element in five, any batch > 1 of matrices with most elements indexed.  The
+ *      sums are fp32.  Chosen when the estimated time of the gathers (the
+ *      128-byte lines of X per indexed element and tile, the gather instructions, the walk of the longest
+ *      row) exceeds 1.05 times that of the decode and the matrix-core product, for matrices of at least
+ *      128 x 256 with one element in ten or more indexed: wide batches of matrices that are not very
+ *      sparse, any batch of more than a few columns where most elements are indexed.  The
  *      arithmetic is then that of a dense fp32 product (same error bound), not Algorithm 3 / 4.  An
  *      infinity or NaN in X reaches every row, as it does there: 0 . inf is NaN
  *   5  CER_PATH_STRIP: batched kernel with strips of 1024 input rows resident in LDS; needs the strip-major
@@ -192,8 +193,9 @@ int cer_trim(void);
  *      shape, batch 32 / 64 / 128: 30 / 46 / 78 us against 33 / 57 / 107 us with kernel 1)
  * On MI355X kernel 2 beats kernel 1 for narrow batches of large matrices (kernel 1 moves a whole
  * 128-byte line per index however narrow the batch) and loses for wide ones (random LDS gathers
- * are bank-conflict bound): it is chosen when it is applicable, batch <= 8 and the matrix holds
- * at least 2.5 million indices.
+ * are bank-conflict bound): it is named when it is applicable, batch <= 8 and the matrix holds
+ * at least 2.5 million indices.  For most such handles the stream kernel for several columns (next paragraph)
+ * then runs in its place.
  * Where batch <= 16, the codebook holds 2 to 256 values, X fits in LDS in one of its widths and the estimates say
  * so, the library's own choice runs the batch-1 stream kernel for several columns at once instead of the kernel that
  * is reported here (the number reported stays that of the kernel that serves the batch without it):

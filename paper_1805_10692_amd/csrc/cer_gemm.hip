@@ -556,12 +556,16 @@ RowLengths row_lengths(const DeviceView& d, bool whole) {
 // Tile width (32, 64 or 128 batch columns) for a batch wider than 32 columns.  A gather instruction costs what the
 // cache lines it touches cost: when a row of X is a whole number of 128-byte lines, 32-column tiles touch exactly the
 // lines they need; otherwise every piece of a row touches up to one line more than its width, and wider tiles mean
-// fewer pieces -- but the lines of a wide tile fall out of an XCD's 4 MB of L2 sooner.  Against that stand the gather
+// fewer pieces -- but the lines of a wide tile fall out of an XCD's 4 MB of L2 sooner (rows lie behind one another, so that a
+// tile never holds more than X does).  The tiles are dealt to the XCDs in order, and the launch lasts as long as an XCD that has
+// none of the last, narrower tile: every tile counts like a full one.  Against that stand the gather
 // instructions, whose lanes take time used or not, and the walk of the longest row: a wave takes 256 / (columns per tile) positions
-// per step.  The terms overlap in part.  Fitted to 200 random shapes of 33 to 400 columns, where the tile so chosen takes 4 % more
-// time than the best of the three (7 % with lines and lanes alone).  Measured on MI355X (AlexNet-fc6 shape, 32 / 64 / 128 columns
-// per tile): batch 96: 76 / 96 / 88 us; batch 100: 177 / 136 / 101 us; batch 40: 92 / 55 / 94 us; 3x3 convolution shape, batch 100
-// (512 rows): 31 / 25 / 38 us; 1254 x 4277, rows of up to 4277 positions, batch 74: 46 us with 32 columns, 94 with 128.
+// per step.  The terms overlap in part.  Constants fitted to 200 random shapes of 33 to 400 columns; over 6000 others (256 - 4096
+// rows, 512 - 25088 columns, batch 36 - 440) the tile so chosen takes 3 % more time than the best of the three, from 15000 columns
+// on 5 % (4 and 9 % with the average of the tiles' lines and without the bound on what a tile holds).  Measured on MI355X, 32 / 64 /
+// 128 columns per tile: AlexNet-fc6 shape, batch 40: 91 / 54 / 93 us; batch 100: 175 / 137 / 100; batch 400: 530 / 445 / 513; VGG-fc6
+// shape, batch 100: 219 / 239 / 155; batch 200: 348 / 457 / 511; 1254 x 4277, rows of up to 4277 positions, batch 74: 46 us with
+// 32 columns, 94 with 128.
 struct WideTile {
     uint32_t cols;
     double us;  // estimate of the whole product
@@ -569,22 +573,22 @@ struct WideTile {
 WideTile pick_wide_tile(uint32_t L, const RowLengths& rows, uint32_t n, const float* X, uint32_t max_tile) {
     const uint32_t row_bytes = L * 4u, base = (uint32_t)(reinterpret_cast<uintptr_t>(X) & 127u);
     const uint32_t step = std::gcd(row_bytes, 128u);  // rows start at base + multiples of this within a line
-    auto lines = [&](uint32_t offset, uint32_t bytes) {  // average number of lines a piece of a row touches
+    auto lines = [&](uint32_t bytes) {  // average number of lines a piece of a row touches (pieces are whole lines apart)
         double sum = 0;
         uint32_t cnt = 0;
-        for (uint32_t ph = 0; ph < 128u; ph += step, ++cnt) sum += (double)(((base + ph + offset) % 128u + bytes + 127u) / 128u);
+        for (uint32_t ph = 0; ph < 128u; ph += step, ++cnt) sum += (double)(((base + ph) % 128u + bytes + 127u) / 128u);
         return sum / cnt;
     };
     // whole lines: 27 TB/s of them, or the walk
     if (step == 128u && base == 0u) return {32, std::max(rows.nnz * (L / 32) * 4.74e-6, rows.longest * 0.125 * 0.042)};
     WideTile best{32, 1e300};
     for (uint32_t tw = 32; tw <= max_tile; tw *= 2) {
-        const uint32_t ntiles = (L + tw - 1) / tw, last_cols = L - (ntiles - 1) * tw;
-        double cost = (ntiles - 1) * lines(0, tw * 4u) + lines(((ntiles - 1) * tw * 4u) % 128u, last_cols * 4u);
-        const double tile_mb = n * cost / ntiles * 128e-6;
-        const double traffic = rows.nnz * (cost * 2.63e-6 * (1.0 + 0.155 * tile_mb) + ntiles * 2.4e-6);
+        const uint32_t ntiles = (L + tw - 1) / tw;
+        const double piece = lines(std::min(tw, L) * 4u);
+        const double tile_mb = n * std::min(piece * 128.0, (double)row_bytes) * 1e-6;
+        const double traffic = rows.nnz * (ntiles * piece * 2.63e-6 * (1.0 + 0.155 * tile_mb) + ntiles * 2.4e-6);
         const double issue = ntiles * rows.nnz * (tw / 256.0) * 12.7e-6, walk = rows.longest * (tw / 256.0) * 0.026;
-        cost = std::pow(std::pow(traffic, 1.33) + std::pow(issue, 1.33) + std::pow(walk, 1.33), 1.0 / 1.33);
+        const double cost = std::pow(std::pow(traffic, 1.33) + std::pow(issue, 1.33) + std::pow(walk, 1.33), 1.0 / 1.33);
         if (cost < best.us) best = {tw, cost};
     }
     return best;

@@ -103,19 +103,18 @@ hipError_t launch_colsum(const float* X, uint32_t n, uint32_t L, float* part, ui
     return launch_kernel(colsum_final_kernel, dim3((L + FB - 1) / FB), dim3(256), 0, stream, part, nslabs, L, FB, T);
 }
 
-// Large batches of a matrix that is not sparse enough: the gathers move nnz.4.batch bytes through the L1/L2 path
-// (measured 18 - 31 TB/s chip-wide, 24 taken here), the matrix cores need 2.m.n.batch flops however many elements are
-// indexed.  The matrix is then decoded into a stream-ordered temporary (bounded here) and multiplied on the matrix cores:
-// as bf16 pieces (cer_mfma.hip: 2 to 6 bytes per element written, three to six products at about 1000 TFLOP/s), or, where
-// the values or the sizes rule that out, as fp32 (4 bytes per element; 90 - 120 TFLOP/s).  Measured on MI355X, gathers against
-// decode + product: 3x3 convolution shape (60 % zeros) batch 3136 391 / 64 us (fp32: 149 us); 7-bit quantizer of the same shape
-// 550 / 112 us.
+// Large batches of a matrix that is not sparse enough: the gathers move a line of X per indexed element and 32 columns
+// (gemm_gather_us), the matrix cores need 2.m.n.batch flops however many elements are indexed.  The matrix is then decoded into a
+// stream-ordered temporary (bounded here) and multiplied on the matrix cores: as bf16 pieces (cer_mfma.hip: 2 to 6 bytes per
+// element written, three to six products at about 900 TFLOP/s), or, where the values or the sizes rule that out, as fp32 (4 bytes
+// per element; 90 - 120 TFLOP/s).  Measured on MI355X, gathers against decode + product: 3x3 convolution shape (60 % zeros)
+// batch 3136 391 / 58 us (fp32: 149 us); 7-bit quantizer of the same shape 550 / 112 us.
+//
 // Estimated duration (seconds) of the kernel that gathers from L2.
-//   * bytes: nnz lines of 128 bytes per 32 columns; rows of X that do not start on a line make a tile touch two of them (a third
-//     more time: AlexNet-fc6 shape batch 100 114 us, batch 128 107 us)
+//   * bytes and steps: gemm_gather_us (lines per index, gather instructions, the walk of the longest row: 543 x 7364, batch 28, 4900
+//     positions per row, 28 us)
 //   * waves: every (row, tile) is a wave whose start-up chain (descriptor -> pointers -> indices -> first gathers) takes about
 //     4 us, 4096 of them in flight: what bounds matrices of many short rows (16384 x 512: batch 128 64 - 84 us)
-//   * the longest row: a wave walks it alone (543 x 7364, batch 28, 4900 positions per row: 28 us)
 //   * the column sums of X for a non-zero most frequent value: two launches and a pass over X
 double gather_estimate(const DeviceView& d, uint32_t L) {
     const double tiles = std::ceil((double)L / 32.0);
@@ -127,7 +126,7 @@ double gather_estimate(const DeviceView& d, uint32_t L) {
 bool densify_estimates(const DeviceView& d, uint32_t L, double* t_gather_out, double* t_dense_out) {
     if (L < 2 || d.m < 128 || d.n < 256) return false;
     const double mn = (double)d.m * (double)d.n;
-    if ((double)d.nnz * 10.0 < mn) return false;  // far below one indexed element in five
+    if ((double)d.nnz * 10.0 < mn) return false;  // the matrix cores spend ten times the multiply-adds: not worth estimating
     const bool pieces = mfma_applicable(d, L);
     if (mn * (pieces ? 2.0 * d.pieces : 4.0) > (double)(1ull << 30)) return false;
     const double flops = 2.0 * mn * L;

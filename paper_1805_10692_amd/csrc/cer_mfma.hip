@@ -9,7 +9,9 @@
 // X is loaded D - 1 steps ahead, W one step, and the LDS stores go one step ahead into the other buffer: one barrier per step,
 // no branch in between (rows of X behind the last one read as zeros: buffer loads with bounds).
 // Per wave and 16 k: 3 . 2 . TN matrix instructions of 32 cycles (one-piece codebook) against TN . 3 KiB out of LDS for all four
-// waves and 2 KiB out of L1: about half of what LDS and L1 deliver, two thirds of the matrix cores' time for the splitting.
+// waves and 2 KiB out of L1.  Counters for 512 x 4608, batch 3136 (48 us, 925 TFLOP/s of bf16): matrix pipes busy 47 % of the
+// launch, vector ALU 25 % (the splitting: half of the matrix cores' time), LDS 18 %, no bank conflicts, 8.8 TB/s from L2; a wave
+// waits 47 % of its time to issue and 21 % for data -- two waves per SIMD that meet at the matrix pipe, and a barrier per step.
 #include "cer_device.hpp"
 #include "cer_split3.hpp"
 
@@ -259,9 +261,11 @@ __global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
 // The same for small problems: 64 x 32 CT outputs per workgroup, the four waves share its columns of W (32 at a time, in turn)
 // and add their sums up in LDS at the end.  A wave loads and splits the part of X that it multiplies straight into operand
 // registers, so there is no LDS and no barrier on the way; 128 columns take the workgroup 0.4 - 0.9 us instead of 2.7 (one
-// piece), and a matrix of 600 rows wastes 40 of them instead of 168.  Product of 700 x 1200, batch 60: 19 -> 9 us, 2048 x 2048, batch
-// 16: 9.2 -> 4.6 us, 2728 x 3378, batch 115: 20 -> 16 us; 512 x 4608, batch 3136: 48 us with the large tiles, 66 with these.  Bound by the splitting of X (PW = 1) or by what L2
-// delivers (80 KiB per 128 columns): the larger tile is the better one where it fills the chip.
+// piece), and a matrix of 600 rows wastes 40 of them instead of 168.  This kernel alone, against the large tiles: 700 x 1200, batch
+// 60: 9 instead of 19 us, 2048 x 2048, batch 16: 4.6 instead of 9.2, 2728 x 3378, batch 115: 16 instead of 20; 512 x 4608, batch
+// 3136: 66 instead of 48.  Bound by the latency of its loads where the chip is not full (2048 x 2048, batch 16, 128 workgroups:
+// matrix pipes busy 6 % of the launch, vector ALU 11 %, half of a wave's time is waiting for data), else by what L2 delivers (80
+// KiB per 128 columns): the larger tile is the better one where it fills the chip.
 template <int PW, int CT>
 __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2], size_t plane, const float* X, uint32_t n,
                                                 uint32_t L, uint32_t col0, uint32_t k_begin, uint32_t k_end, floatx16 (&acc)[2][CT]) {
@@ -402,7 +406,8 @@ struct MfmaShape {
 };
 
 // The launch lasts as long as the busiest compute unit: its share of the workgroups, one after the other (two resident ones --
-// one-piece codebooks with BN = 64 -- overlap, but share the matrix cores: `alone` and `together` scale the time of a round).  Measured per unit: 4.1 - 4.7 TFLOP/s with BN = 64, bound by the operands' bytes with
+// one-piece codebooks with BN = 64 -- overlap, but share the matrix cores: `alone` and `together` scale the time of a round).
+// Measured per unit: 4.1 - 4.7 TFLOP/s with BN = 64, bound by the operands' bytes with
 // BN = 32; the small tiles 2.4 - 3.5 TFLOP/s.  A split along n costs its partial sums, written and read again.
 void shape_splits(const DeviceView& d, uint32_t L, uint32_t round, double round_us, double alone, double together,
                   double fixed_us, MfmaShape* s) {

@@ -4,9 +4,12 @@
 // wave per row (or several: matrices of few rows), 16-byte loads of the indices, boundary bitmap, one weight per position -- costs
 // the same as for one column and is shared by the V of them.  A launch covers all columns: the workgroups of the second,
 // third ... group of V columns follow those of the first.
-// Bound by the LDS: a 16-byte gather at 64 random rows takes about 12 clocks of it (four passes of 16 lanes, the busiest of the
-// 16 bank groups hit three times), the weight four.  AlexNet-fc6 shape, batch 4: 7.6 us; 12.8 with the tile kernel
-// (cer_xtile.hip), 20 gathering from L2.
+// While it streams it is bound by the LDS and the vector ALU about equally: a 16-byte gather at 64 random rows takes about 12
+// clocks of LDS (four passes of 16 lanes, the busiest of the 16 bank groups hit three times), the weight four.  AlexNet-fc6 shape,
+// batch 4: 7.8 us (12.6 with the tile kernel, cer_xtile.hip, 29 gathering from L2); over the launch the LDS pipe is busy 42 %
+// of the time (its conflicts 19 %), the vector ALU 41 %, and a wave waits for data 62 % of its own: the staging of 147 KB of X per
+// compute unit comes before the first gather.  2048 x 2048, 256 values, batch 16 (four passes, 255 groups per row): 12 us, LDS
+// 51 %, vector ALU 46 %, a wave's waits 59 %.
 #include "cer_stream.hpp"
 
 namespace cer {
