@@ -113,8 +113,8 @@ int cser_encode(const float* W_host, int64_t m, int64_t n, const float* codebook
  * (plus partial sums) is allocated and released on `stream`, and so is one for a batched product
  * of a matrix with split rows (cer_long_row_parts > 0); kernels 2, 3 and 5 have temporaries of
  * their own (a tile-major copy of X; the decoded matrix; strips x m x batch partial sums).
- * Otherwise (and when cer_matmul_path reports kernel 0 or 1) the call only launches kernels and may be recorded into a HIP graph
- * after one eager call on the device.
+ * Otherwise (and when cer_matmul_path reports kernel 0 or 1, or cer_matmul_narrow_columns is not 0) the call only
+ * launches kernels and may be recorded into a HIP graph after one eager call on the device.
  * fp32 arithmetic; the summation order differs from a sequential loop.  With Omega[0] != 0 the
  * rounding error is relative to sum|w||x| + |Omega[0]|.sum|x|: Appendix A-A1 adds that term and
  * subtracts it again inside the groups' weights.
@@ -131,7 +131,7 @@ int cser_matmul(const cer_handle_t* h, const float* X_dev, float* Y_dev, int64_t
  * 2 MiB device array that is part of the library's code object (one per GPU, kept until the process
  * ends), and only kernels that need no other temporary are chosen: the batch-1 kernels, the batched
  * kernel that gathers from L2 with every row whole, the LDS-resident kernel for batches of one tile;
- * never the decode + dense route.  Y equals cer_matmul's within the same error bound (bit for bit
+ * never the decode + dense route, the strips, or the stream kernel for several columns.  Y equals cer_matmul's within the same error bound (bit for bit
  * where both run the same kernel).  A product whose column sums would not fit the array (batch above
  * about 260 000 columns with Omega[0] != 0) is refused with CER_E_TOO_LARGE.
  * All calls on one GPU share the array: two such calls that overlap in time on one GPU (different
@@ -166,7 +166,7 @@ int cer_trim(void);
  *      needs X to fit in LDS
  *   1  CER_PATH_GEMM: batched kernel that gathers rows of X from L2, one wave per (row, tile of batch
  *      columns: 32 when a row of X is a whole number of 128-byte lines, else 32, 64 or 128 by the
- *      cache lines the gathers touch; any width and 4-byte aligned X / Y are served by 16-byte
+ *      cache lines the gathers touch, their number and the longest row; any width and 4-byte aligned X / Y are served by 16-byte
  *      gathers).  By default the group values are expanded per colI position into LDS and every
  *      gathered row is multiplied by its position's value; with CER_OPT_SUM_THEN_MULTIPLY the
  *      gathered rows of a group are summed first and multiplied once (slower on MI355X)
@@ -190,7 +190,7 @@ int cer_trim(void);
  *   5  CER_PATH_STRIP: batched kernel with strips of 1024 input rows resident in LDS; needs the strip-major
  *      index of cer_prepare_strips.  For a handle that has it the library chooses this kernel where its
  *      estimated duration is below that of kernels 1 and 3: wide batches of large matrices (AlexNet-fc6
- *      shape, batch 32 / 64 / 128: 30 / 46 / 78 us against 33 / 57 / 107 us with kernel 1)
+ *      shape, batch 32 / 64 / 128: 22 / 34 / 59 us against 32 / 57 / 106 us with kernel 1)
  * On MI355X kernel 2 beats kernel 1 for narrow batches of large matrices (kernel 1 moves a whole
  * 128-byte line per index however narrow the batch) and loses for wide ones (random LDS gathers
  * are bank-conflict bound): it is named when it is applicable, batch <= 8 and the matrix holds

@@ -163,10 +163,10 @@ hipError_t launch_densified(const DeviceView& d, const float* X, float* Y, uint3
 // 32 - 43 B/clk per CU, while the L2 kernel's gathers of whole 128-byte rows sustain 27 - 48 B/clk per CU and
 // amortise the group structure over 32 batch columns instead of 4 or 8 (AlexNet-fc6 shape, batch 32: 62 us against
 // 35 us; 3x3 convolution shape, batch 3136: 536 us against 378 us).  For narrow batches it does: the L2 kernel
-// still moves a whole 128-byte line per index, the LDS kernel 16 or 32 bytes (AlexNet-fc6 shape, batch 2 / 3 / 4 /
-// 6 / 8: 28 / 29 / 29 / 37 / 31 us from L2, 23 / 22 / 13 / 28 / 28 us from LDS with the tile-major copy, less
-// without it), provided the matrix is large enough for the gathers to dominate the launch (2048 x 2048 cells with
-// 0.2 - 2 million indices: 6 - 12 us either way, the L2 kernel ahead).
+// still moves a whole 128-byte line per index, the LDS kernel 16 or 32 bytes (AlexNet-fc6 shape, batch 2 / 4 / 8: 27 / 28 / 30 us
+// from L2, 15.6 / 12.5 / 22 us from LDS), provided the matrix is large enough for the gathers to dominate the launch (2048 x 2048
+// cells with 0.2 - 2 million indices: 6 - 12 us either way, the L2 kernel ahead).  The stream kernel for several columns
+// (cer_narrow.hip) is ahead of both there (7.7 / 8.6 / 12.5 us) and takes most of these products.
 bool xtile_pays(const DeviceView& d, uint32_t L) { return L <= 8 && d.nnz >= 2500000; }
 
 // Which kernel serves a batch of L > 1 columns (cer_matmul_path's numbering: 1, 2 or 3).  A preferred kernel is
@@ -188,7 +188,7 @@ int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o,
         const double t_gather_l2 = gather_estimate(d, L);
         strips_beat_gathers = t_strip < 0.95 * t_gather_l2;
     }
-    // (from 8 columns on the strips are ahead of the LDS tile of all input rows: AlexNet-fc6 shape batch 8 23 against 28 us)
+    // (from 8 columns on the strips are ahead of the LDS tile of all input rows: AlexNet-fc6 shape batch 8 15 against 22 us)
     if (o.path != 1 && o.path != 3 && !(strips_beat_gathers && L >= 8u)) {
         const XtilePlan plan = plan_xtile(d, L);
         if (plan.valid && (o.path == 2 || xtile_pays(d, L)) && (!no_temporaries || plan.ntiles == 1)) {
@@ -196,13 +196,11 @@ int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o,
             return 2;
         }
     }
-    // A handle whose strip-major index was prepared takes the strip kernel where its estimate beats that of the
-    // gathers from L2 (27 TB/s of whole 128-byte lines plus the start-up chain of a launch) and that of decode +
-    // dense: wide batches of large matrices -- AlexNet-fc6 shape, batch 32 / 64 / 128: 25 / 38 / 61 us against
-    // 33 / 57 / 107 us; VGG-fc6 shape, batch 64 / 128: 45 / 78 against 54 / 100 us (batch 32: 29 against 31 us: the
-    // estimate keeps the gathers; 3x3 convolution shape, batch 3136: 209 us against 159 us decoded and multiplied); batch widths
-    // that are multiples of 4 but not of 32: AlexNet-fc6 shape batch 100: 61 against 114 us; batches of 8 - 16 columns
-    // (one 16-byte piece of a row per lane): AlexNet-fc6 shape batch 16 20 against 31 us, VGG-fc6 shape 22 against 28 us.
+    // A handle whose strip-major index was prepared takes the strip kernel where its estimate is below 0.95 times that of the
+    // gathers from L2 and below that of decode + product, if the latter pays: wide batches of large matrices.  Measured, gathers /
+    // strips: AlexNet-fc6 shape, batch 8 / 16 / 32 / 64 / 100 / 128: 30 / 31 / 32 / 57 / 114 / 106 against 15 / 16 / 22 / 34 / 58 / 59
+    // us; VGG-fc6 shape, batch 8 / 16 / 64 / 128: 27 / 28 / 53 / 99 against 17 / 18 / 39 / 76 us (batch 32: 30 against 25 us, but the
+    // estimate keeps the gathers); 3x3 convolution shape, batch 3136: 191 us against 58 us decoded and multiplied.
     if (o.path < 0 && !no_temporaries && has_elements) {
         double t_gather = 0, t_dense = 0;
         const bool dense_ok = densify_estimates(d, L, &t_gather, &t_dense);
