@@ -13,7 +13,6 @@
 #include <cmath>
 #include <cstring>
 #include <numeric>
-#include <system_error>
 #include <mutex>
 #include <new>
 #include <thread>
@@ -126,7 +125,7 @@ public:
         while (w->started_ < threads - 1) {
             try {
                 std::thread(&Workers::loop, w, w->started_ + 1, w->turn_.load(std::memory_order_relaxed)).detach();
-            } catch (const std::system_error&) {
+            } catch (...) {  // no more threads, or no memory for one
                 return false;
             }
             ++w->started_;
@@ -230,7 +229,7 @@ public:
                     while (team.size_.load(std::memory_order_acquire) == 0) std::this_thread::yield();
                     work(t);
                 });
-        } catch (const std::system_error&) {  // no more threads to be had: the ones there are share the rows
+        } catch (...) {  // no more threads to be had, or no memory for one: the ones there are share the rows (and are joined)
         }
         team.size_.store((int)pool.size() + 1, std::memory_order_release);
         work(0);
