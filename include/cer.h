@@ -209,6 +209,15 @@ int cer_matmul_path(const cer_handle_t* h, int64_t batch);
  * with a path, flags or a tile width, and cer_matmul_noalloc, never do.)  Errors: CER_E_INVALID, CER_E_HIP (no device copy). */
 int cer_matmul_narrow_columns(const cer_handle_t* h, int64_t batch);
 
+/* Whether cer_matmul / cser_matmul decode and multiply in one launch for this handle and batch, in place of the kernel that
+ * cer_matmul_path reports (whose number stays that of the kernel that serves the batch without it): the rows of W per workgroup, 0
+ * where they do not.  The rows' elements are decoded into LDS and multiplied on the matrix cores as in kernel 3, in pieces that add
+ * up to the inputs exactly; batches of a few hundred columns, matrices of n <= 65000 and 2 to 256 values with more than 256
+ * columns, where the estimates say so.  Partial sums in a temporary only where the kernel reported has a temporary too.
+ * Infinities and NaNs in X count as in the kernel reported.  (cer_matmul_ex with a path, flags or a tile width, and
+ * cer_matmul_noalloc, never do it.)  Errors: CER_E_INVALID, CER_E_HIP (no device copy). */
+int cer_matmul_fused_rows(const cer_handle_t* h, int64_t batch);
+
 /*
  * cer_matmul_ex -- cer_matmul / cser_matmul (it accepts handles of both formats) with the caller's
  * choices instead of the library's; the result is the same Y within the same error bound.  The

@@ -829,6 +829,12 @@ int cer_matmul_narrow_columns(const cer_handle_t* h, int64_t batch) {
     return cer::matmul_narrow_columns(h->view, batch);
 }
 
+int cer_matmul_fused_rows(const cer_handle_t* h, int64_t batch) {
+    if (!h || batch < 1) return CER_E_INVALID;
+    if (h->device < 0 || !h->d_base) return CER_E_HIP;
+    return cer::matmul_fused_rows(h->view, batch);
+}
+
 int cer_decode(const cer_handle_t* h, float* W_out) { return decode_any(h, false, W_out); }
 int cser_decode(const cer_handle_t* h, float* W_out) { return decode_any(h, true, W_out); }
 

@@ -139,6 +139,8 @@ size_t matmul_workspace_floats(const DeviceView& v, int64_t L, const MatmulOptio
 int matmul_path(const DeviceView& v, int64_t L, const MatmulOptions& o);
 // Columns per pass where launch_matmul, left to itself, runs the stream kernel for several columns instead (0: it does not).
 int matmul_narrow_columns(const DeviceView& v, int64_t L);
+// Rows of W per workgroup where it runs decode + product in one launch instead (0: it does not).
+int matmul_fused_rows(const DeviceView& v, int64_t L);
 // Fills the handle's rank table (if its layout has one) from the format arrays already in device memory; the launch
 // is ordered on `stream`.  A hipError_t value as int.
 int build_rank_table(const DeviceView& v, void* stream);

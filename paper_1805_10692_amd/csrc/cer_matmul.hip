@@ -158,6 +158,10 @@ hipError_t launch_densified(const DeviceView& d, const float* X, float* Y, uint3
     return e == hipSuccess ? f : e;
 }
 
+// Decode + product in one launch is taken where its estimate is below this share of the other kernel's.  Over 438 random products
+// 0.85 / 0.9 / 0.95 / 1 give 1.125 / 1.133 / 1.132 / 1.138 times the speed on average and make 4 / 5 / 9 / 11 of them slower.
+constexpr double kFusedMargin = 0.9;
+
 // Whether the LDS variant is expected to beat the kernel that gathers from L2.  Measured on MI355X: for wide
 // batches it never does -- gathers of 16- or 32-byte pieces at random LDS addresses are bank-conflict bound at
 // 32 - 43 B/clk per CU, while the L2 kernel's gathers of whole 128-byte rows sustain 27 - 48 B/clk per CU and
@@ -211,7 +215,7 @@ int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o,
     return 1;
 }
 
-// Estimated duration (microseconds) of the kernel that choose_batched_path has named, for a batch of at most 16 columns.
+// Estimated duration (microseconds) of the kernel that choose_batched_path has named.
 double path_estimate_us(const DeviceView& d, uint32_t L, int path) {
     if (path == kPathStrip) return plan_strip(d, L).est_us;
     if (path == 2) return 4.0 + (double)d.nnz * 3.2e-6;  // AlexNet-fc6 shape batch 2 / 4 / 8: 23 / 13 / 28 us
@@ -220,12 +224,31 @@ double path_estimate_us(const DeviceView& d, uint32_t L, int path) {
     return gather_estimate(d, L) * 1e6;
 }
 
-// Columns per pass of the stream kernel for several columns, where the library's own choice for a few columns is that kernel
-// instead of `path` (a path, flags or a tile width of the caller's speak of the others); else 0.
-int choose_narrow(const DeviceView& d, uint32_t L, const MatmulOptions& o, int path) {
-    if (L < 2 || L > 16 || o.path >= 0 || o.flags != 0 || o.tile_cols != 0) return 0;
-    const NarrowEstimate narrow = narrow_estimate(d, L);
-    return narrow.us < path_estimate_us(d, L, path) ? narrow.columns : 0;
+// What the library's own choice runs instead of `path` (a path, flags or a tile width of the caller's speak of the others):
+// the stream kernel for several columns (narrow: its columns per pass), or decode + product in one launch (fused: its rows per
+// workgroup; temporaries: it may have partial sums -- only where the kernel it takes the place of has a temporary as well).
+struct Instead {
+    int narrow = 0, fused = 0;
+    bool temporaries = false;
+};
+Instead choose_instead(const DeviceView& d, uint32_t L, const MatmulOptions& o, int path) {
+    Instead r;
+    if (L < 2 || o.path >= 0 || o.flags != 0 || o.tile_cols != 0) return r;
+    double us = path_estimate_us(d, L, path);
+    if (L <= 16) {
+        const NarrowEstimate narrow = narrow_estimate(d, L);
+        if (narrow.us < us) {
+            us = narrow.us;
+            r.narrow = narrow.columns;
+        }
+    }
+    r.temporaries = r.narrow == 0 && (path == 3 || path == kPathStrip || d.omega0 != 0.f || d.n_split_parts > 0);
+    const FusedEstimate fused = fused_estimate(d, L, r.temporaries);
+    if (fused.us < kFusedMargin * us) {
+        r.narrow = 0;
+        r.fused = fused.rows;
+    }
+    return r;
 }
 
 // Column sums of X for a non-zero most frequent value: shape of the two-stage sum and the floats it needs
@@ -264,7 +287,12 @@ int matmul_path(const DeviceView& d, int64_t L, const MatmulOptions& o) {
 
 int matmul_narrow_columns(const DeviceView& d, int64_t L) {
     const MatmulOptions o;
-    return L < 2 || L > 16 ? 0 : choose_narrow(d, (uint32_t)L, o, choose_batched_path(d, (uint32_t)L, o, false, nullptr));
+    return L < 2 || L > 16 ? 0 : choose_instead(d, (uint32_t)L, o, choose_batched_path(d, (uint32_t)L, o, false, nullptr)).narrow;
+}
+
+int matmul_fused_rows(const DeviceView& d, int64_t L) {
+    const MatmulOptions o;
+    return L < 2 || L > 0x7FFFFFFFll ? 0 : choose_instead(d, (uint32_t)L, o, choose_batched_path(d, (uint32_t)L, o, false, nullptr)).fused;
 }
 
 size_t matmul_workspace_floats(const DeviceView& d, int64_t L, const MatmulOptions& o) {
@@ -304,7 +332,11 @@ int launch_matmul(const DeviceView& d, const float* X, float* Y, int64_t L64, vo
     if (no_temporaries) o.flags |= kOptRowsWhole;  // the parts of split rows meet in a temporary
     XtilePlan plan;
     const int batched_path = L > 1 ? choose_batched_path(d, L, o, no_temporaries, &plan, X, Y) : 0;
-    if (!no_temporaries && choose_narrow(d, L, o, batched_path) > 0) return (int)launch_narrow(d, X, Y, L, stream);
+    if (!no_temporaries && L > 1) {
+        const Instead instead = choose_instead(d, L, o, batched_path);
+        if (instead.narrow > 0) return (int)launch_narrow(d, X, Y, L, stream);
+        if (instead.fused > 0) return (int)launch_fused(d, X, Y, L, instead.temporaries, batched_path == 3, stream);
+    }
     if (batched_path == 3) return (int)launch_densified(d, X, Y, L, stream);
 
     float* T = nullptr;

@@ -1,0 +1,169 @@
+"""Decode + product in one launch by the library's own choice (csrc/cer_fused.hip): every width of a tile, one and several bf16 pieces,
+one to four tiles of groups, rows of several batches of positions, segments and parts of W's columns, ragged sizes, unaligned X
+and Y, empty and full rows, a non-zero most frequent value, infinities, NaNs and numbers down to the smallest subnormal."""
+import numpy as np
+import pytest
+
+from paper_1805_10692_amd import binding as B
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _matrix(m, n, K, p0, zero, seed):
+    rng = np.random.default_rng(seed)
+    cb = (np.arange(K) - zero).astype(np.float32) / np.float32(K)
+    p = np.full(K, (1 - p0) / (K - 1))
+    p[K // 2] = p0
+    W = rng.choice(cb, size=(m, n), p=p).astype(np.float32)
+    W[m // 2] = cb[K // 2]                                   # a row without indices
+    W[m - 1, :n // 4] = cb[K - 1 if K // 2 != K - 1 else 0]  # a long group
+    return W, cb, rng
+
+
+def _product(h, X, m, L, shift=0, opts=None, fmt="cer"):
+    n = X.shape[0]
+    xb, yb = torch.zeros(n * L + 4, device="cuda"), torch.full((m * L + 4,), float("nan"), device="cuda")
+    Xd, Yd = xb[shift:shift + n * L], yb[shift:shift + m * L]
+    Xd.copy_(torch.from_numpy(np.ascontiguousarray(X)).reshape(-1))
+    if opts is None:
+        (B.cer_matmul if fmt == "cer" else B.cser_matmul)(h, Xd, Yd, L)
+    else:
+        B.cer_matmul_ex(h, Xd, Yd, L, None, opts)
+    torch.cuda.synchronize()
+    assert torch.isnan(yb[:shift]).all() and torch.isnan(yb[shift + m * L:]).all()
+    return Yd.cpu().numpy().reshape(m, L)
+
+
+def _bound(W, X):
+    return 1e-5 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64)) + 1e-30
+
+
+# (m, n, L, K, share of the most frequent value, fmt, shift of the buffers in floats)
+CASES = [
+    (1600, 257, 100, 2, 0.4, "cer", 0), (1601, 257, 140, 3, 0.3, "cser", 1), (1500, 1600, 15, 256, 0.2, "cser", 1), (2048, 2048, 16, 256, 0.5, "cer", 0),
+    (1600, 9300, 20, 4, 0.5, "cser", 0), (1600, 12000, 40, 32, 0.7, "cer", 0), (900, 7000, 30, 200, 0.3, "cser", 2),
+    (785, 1000, 33, 64, 0.4, "cer", 3), (1030, 1537, 40, 65, 0.5, "cser", 1), (1000, 2000, 49, 128, 0.5, "cer", 0),
+    (900, 20000, 64, 7, 0.6, "cer", 0), (780, 1300, 70, 256, 0.3, "cser", 0), (900, 700, 130, 16, 0.6, "cer", 1),
+    (800, 3000, 200, 255, 0.2, "cser", 0), (3000, 900, 64, 5, 0.5, "cer", 0), (4000, 1500, 60, 3, 0.5, "cer", 2),
+    (1600, 40000, 40, 5, 0.6, "cser", 0),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[f"{c[0]}x{c[1]}_L{c[2]}_K{c[3]}" for c in CASES])
+def test_products(case):
+    m, n, L, K, p0, fmt, shift = case
+    W, cb, rng = _matrix(m, n, K, p0, K // 2, m + n)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    h = (B.cer_encode if fmt == "cer" else B.cser_encode)(W, cb)
+    assert B.cer_matmul_fused_rows(h, L) in (16, 32)
+    Y = _product(h, X, m, L, shift, fmt=fmt)
+    B.cer_free(h)
+    assert (np.abs(Y - W.astype(np.float64) @ X.astype(np.float64)) <= _bound(W, X)).all()
+
+
+@pytest.mark.parametrize("case", [(1000, 1100, 50, 9, 0.5), (1030, 2537, 40, 130, 0.5), (1500, 9000, 40, 16, 0.4)])
+def test_non_zero_most_frequent_value(case):
+    m, n, L, K, p0 = case
+    W, cb, rng = _matrix(m, n, K, p0, 0, m)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    h = B.cer_encode(W, cb)
+    assert B.cer_get_array(h, B.CER_ARRAY_OMEGA)[0] != 0 and B.cer_matmul_fused_rows(h, L) > 0
+    Y = _product(h, X, m, L)
+    B.cer_free(h)
+    assert (np.abs(Y - W.astype(np.float64) @ X.astype(np.float64)) <= _bound(W, X)).all()
+
+
+def test_rows_of_very_different_length():
+    rng = np.random.default_rng(3)
+    m, n, L = 1200, 5000, 70
+    cb = np.array([0.0, 0.5, -0.25, 1.0], np.float32)
+    W = np.where(rng.random((m, n)) < rng.choice([0.0, 0.02, 0.3, 1.0], size=(m, 1)), rng.choice(cb[1:], size=(m, n)), np.float32(0)).astype(np.float32)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    h = B.cer_encode(W, cb)
+    assert B.cer_matmul_fused_rows(h, L) > 0
+    Y = _product(h, X, m, L)
+    B.cer_free(h)
+    assert (np.abs(Y - W.astype(np.float64) @ X.astype(np.float64)) <= _bound(W, X)).all()
+    assert (Y[~W.any(1)] == 0).all()
+
+
+# codebooks of one and of three pieces; a call that the gathers served (infinities reach the rows that index them) and one that the
+# decoded matrix did (every row: 0 . inf is NaN)
+@pytest.mark.parametrize("shape", [(1000, 1100, 50), (900, 9000, 40)])
+@pytest.mark.parametrize("K", [16, 33])
+def test_infinities_and_nans(shape, K):
+    m, n, L = shape
+    W, cb, rng = _matrix(m, n, K, 0.5, K // 2, K)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    X[n // 3, 1], X[n - 1, 2], X[5, 3], X[6, 4], X[7, 4], X[40, 9], X[0, 0] = np.inf, -np.inf, np.nan, np.inf, -np.inf, 3.4e38, -3.4e38
+    h = B.cer_encode(W, cb)
+    path = B.cer_matmul_path(h, L)
+    assert B.cer_matmul_fused_rows(h, L) > 0 and path == (1 if n == 1100 else 3)
+    Y = _product(h, X, m, L)
+    B.cer_free(h)
+    with np.errstate(invalid="ignore"):
+        for c, rows in ((1, [n // 3]), (2, [n - 1]), (3, [5]), (4, [6, 7])):
+            want = np.zeros(m)
+            for k in rows:
+                product = W[:, k].astype(np.float64) * X[k, c]
+                want += product if path == 3 else np.where(W[:, k] == 0, 0.0, product)
+            odd = ~np.isfinite(want)
+            assert odd.any() and np.array_equal(Y[odd, c], want[odd], equal_nan=True), c
+            assert np.array_equal(np.isfinite(Y[:, c]), ~odd), c
+    X[np.abs(X) == np.inf], X[5, 3] = 0, 0
+    want, bound = W.astype(np.float64) @ X.astype(np.float64), _bound(W, X)
+    good = [c for c in range(L) if c not in (1, 2, 3, 4)]
+    assert (np.abs(Y - want) <= bound)[:, good].all()
+
+
+@pytest.mark.parametrize("K", [16, 33])
+def test_small_inputs_keep_their_bits(K):
+    """Inputs below 2^-110 lose bits in the pieces; sums in which that can show are formed again.  Exact: one group per row, and
+    powers of two as weights of the others, so that the sums of few terms are representable."""
+    m, n, L = 1000, 2000, 49
+    W, cb, rng = _matrix(m, n, K, 0.5, K // 2, K)
+    X = (rng.standard_normal((n, L)) * 2.0 ** rng.integers(-125, -100, size=(1, L))).astype(np.float32)
+    X[:, 7] = rng.integers(-50, 50, size=n) * np.float32(2.0) ** -149
+    h = B.cer_encode(W, cb)
+    assert B.cer_matmul_fused_rows(h, L) > 0
+    Y = _product(h, X, m, L)
+    B.cer_free(h)
+    want = W.astype(np.float64) @ X.astype(np.float64)
+    bound = 1e-5 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64)) + n * 2.0 ** -149  # every product may be subnormal
+    assert (np.abs(Y - want) <= bound).all()
+
+
+def test_precision():
+    """Not further from fp64 than the gathers (2-norm), whose sums are products in binary32."""
+    for m, n, L, K in ((1000, 2000, 49, 128), (1030, 1537, 40, 65), (900, 9000, 40, 200), (900, 9000, 40, 16)):
+        W, cb, rng = _matrix(m, n, K, 0.5, K // 2, 1)
+        X = rng.standard_normal((n, L)).astype(np.float32)
+        h = B.cer_encode(W, cb)
+        assert B.cer_matmul_fused_rows(h, L) > 0
+        want = W.astype(np.float64) @ X.astype(np.float64)
+        err = [np.linalg.norm(_product(h, X, m, L, opts=o) - want) for o in (None, B.MatmulOpts(path=B.CER_PATH_GEMM))]
+        B.cer_free(h)
+        assert err[0] <= err[1]
+
+
+def test_replayed_from_a_graph():
+    m, n, L, K = 1030, 1537, 40, 65
+    W, cb, rng = _matrix(m, n, K, 0.5, K // 2, 1)
+    h = B.cer_encode(W, cb)
+    assert B.cer_matmul_path(h, L) == 1 and B.cer_matmul_fused_rows(h, L) > 0      # no temporaries: kernels only
+    X, Y = torch.zeros((n, L), device="cuda"), torch.zeros((m, L), device="cuda")
+    B.cer_matmul(h, X, Y, L)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        B.cer_matmul(h, X, Y, L, torch.cuda.current_stream())
+    for rep in range(3):
+        X.copy_(torch.from_numpy(rng.standard_normal((n, L)).astype(np.float32)))
+        g.replay()
+        torch.cuda.synchronize()
+        eager = torch.empty_like(Y)
+        B.cer_matmul(h, X, eager, L)
+        torch.cuda.synchronize()
+        assert torch.equal(Y, eager), rep
+    B.cer_free(h)
