@@ -25,6 +25,7 @@
 #include "../../include/cer.h"
 #include "cer_device.hpp"
 #include "cer_split3.hpp"
+#include "cer_stream.hpp"
 
 namespace {
 
@@ -572,18 +573,9 @@ struct EmitTarget {
     size_t gap_begin[8], gap_end[8];
 };
 
-// Four rows per workgroup; the last workgroup writes Omega, clears the gaps and tells the host the values.
-template <typename ColT, typename OiT>
-__global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ codes, const uint32_t* __restrict__ cnt,
-                                                   const uint2* __restrict__ rowStart, const FrontState* __restrict__ st,
-                                                   int64_t m, int64_t n, int cser, int sparse, EmitTarget to,
-                                                   FrontResult* __restrict__ out) {
-    __shared__ uint32_t s_rank[kCodes];
-    __shared__ uint32_t s_fill[4][kCodes];  // next free colI slot of each rank's bucket
-    __shared__ uint32_t s_stage[4][kEmitStage];  // (column << 8) | rank of the columns waiting for the scatter
-    __shared__ unsigned long long s_marks[4][kCodes];  // per rank: the lanes of the current batch that hold it
-    if (blockIdx.x == gridDim.x - 1) {
-        const uint32_t t = threadIdx.x;
+// What one workgroup of an emitter does besides the rows: Omega, the gaps, and the values for the host.
+__device__ __forceinline__ void emit_values(const FrontState* __restrict__ st, const EmitTarget& to, FrontResult* __restrict__ out) {
+    for (uint32_t t = threadIdx.x; t < kCodes; t += blockDim.x) {
         if (t < st->Kp) {
             const float w = st->omega[t];
             reinterpret_cast<float*>(to.base + to.off_om)[t] = w;
@@ -591,26 +583,22 @@ __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ c
             out->count[t] = st->count[t];
         }
         if (t < st->K) out->codebook[t] = st->codebook[t];
-        for (int g = 0; g < to.ngaps; ++g)
-            for (size_t o = to.gap_begin[g] + t; o < to.gap_end[g]; o += 256) to.base[o] = 0;
-        return;
     }
-    ColT* colI = reinterpret_cast<ColT*>(to.base);
+    for (int g = 0; g < to.ngaps; ++g)
+        for (size_t o = to.gap_begin[g] + threadIdx.x; o < to.gap_end[g]; o += blockDim.x) to.base[o] = 0;
+}
+
+// One wave: everything of row r but its columns -- bucket sizes by rank -> bucket starts (exclusive scan over ranks 1, 2, ...), the
+// pointers and the row's record of the rank table.  place(rank, codebook position, first colI position of the bucket).
+template <typename OiT, typename Place>
+__device__ __forceinline__ void emit_row_pointers(int64_t r, const uint32_t* __restrict__ cnt, const uint2* __restrict__ rowStart,
+                                                  const FrontState* __restrict__ st, int64_t m, int cser, const EmitTarget& to, Place place) {
     uint32_t* omegaPtr = reinterpret_cast<uint32_t*>(to.base + to.off_optr);
     uint32_t* rowPtr = reinterpret_cast<uint32_t*>(to.base + to.off_rptr);
     uint2* rowInfo = reinterpret_cast<uint2*>(to.base + to.off_ri);
     OiT* omegaI = reinterpret_cast<OiT*>(to.base + to.off_oi);
     uint32_t* tab = reinterpret_cast<uint32_t*>(to.base + to.off_tab);
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    s_rank[threadIdx.x] = st->rank_of[threadIdx.x];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) s_marks[w][threadIdx.x] = 0ull;
-    __syncthreads();
-    const int64_t r = (int64_t)blockIdx.x * 4 + wave;
-    if (r >= m) return;
-    uint32_t* fill = s_fill[wave];
-    unsigned long long* marks = s_marks[wave];
-    const uint32_t Kp = st->Kp;
+    const uint32_t lane = threadIdx.x & 63u, Kp = st->Kp;
     const uint2 here = rowStart[r], next = rowStart[r + 1];
     const uint32_t g0 = here.x, off0 = here.y;
     const uint32_t groups = next.x - g0;
@@ -623,21 +611,21 @@ __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ c
             rowInfo[m] = next;
         }
     }
-    // bucket sizes by rank -> bucket starts (exclusive scan over ranks 1, 2, ...), the pointers and the row's record of the
-    // rank table
+    const uint32_t ranks = max(Kp, 1u << to.tab_shift);
+    uint32_t place_of[kCodes / kWave], size[kCodes / kWave];  // all on their way before the first is used
+#pragma unroll
+    for (uint32_t i = 0; i < kCodes / kWave; ++i) place_of[i] = i * kWave < ranks ? st->pos_of[i * kWave + lane] & (kCodes - 1u) : 0u;
+#pragma unroll
+    for (uint32_t i = 0; i < kCodes / kWave; ++i) size[i] = i * kWave < ranks ? cnt[r * kCodes + place_of[i]] : 0u;
     uint32_t carry = 0, gcarry = 0;
 #pragma unroll
-    for (int i = 0; i < kCodes / kWave; ++i) {
-        const uint32_t k = lane + 64u * i;
-        const uint32_t c = (k >= 1 && k < Kp) ? cnt[r * kCodes + st->pos_of[k]] : 0u;
-        uint32_t inc = c;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const uint32_t u = __shfl_up(inc, off, kWave);
-            if ((int)lane >= off) inc += u;
-        }
+    for (uint32_t i = 0; i < kCodes / kWave; ++i) {
+        if (i * kWave >= ranks) break;  // uniform
+        const uint32_t k = i * kWave + lane, pos = place_of[i];
+        const uint32_t c = (k >= 1 && k < Kp) ? size[i] : 0u;
+        const uint32_t inc = cer::wave_inclusive_scan(c);
         const uint32_t end = off0 + carry + inc;
-        fill[k] = end - c;
+        place(k, pos, end - c);
         if (to.tab_shift && (k >> to.tab_shift) == 0) tab[((size_t)r << to.tab_shift) + k] = end;
         const uint64_t pres = __ballot(c > 0);
         if (cser) {
@@ -650,8 +638,172 @@ __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ c
         } else if (k >= 1 && k <= groups) {
             omegaPtr[g0 + k] = end;  // an empty group repeats the previous pointer
         }
-        carry += (uint32_t)__shfl((int)inc, 63, kWave);
+        carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
     }
+}
+
+// One row per workgroup of one wave, whose columns are sorted in LDS; the last workgroup does emit_values.
+// A lane takes a run of consecutive columns and has a counter of its own per codebook position (16 bits, two lanes to a word), so
+// that counting and placing need neither a vote nor an order among the lanes: count the run's elements, turn the counters into
+// first slots (a scan over the lanes per position, two positions at a time, on top of the bucket starts), then take the slots one
+// after another and write the columns to their places in LDS.  The row goes to memory as it lies there, with 16-byte stores.
+// A row of 9216 columns and 128 positions takes 33000 clocks (start and pointers 6000, counting and the scan 13500, placing 10000, out
+// 4000) and 31 KiB, five of them on a compute unit: 60 us for 4096, against 69 with emit_kernel; bound by the LDS, which takes 14 clocks
+// per placed column and wave, and by the phases of five waves.  Where all rows run at once the gain is larger: 300 x 9000 115 -> 89 us.
+constexpr uint32_t kRowCounters = 32;  // words of counters per codebook position
+constexpr int64_t kSortedColumns = 64512;  // 64 runs of a multiple of 16 columns: below 65536, so that slots fit 16 bits
+inline uint32_t emit_stage_bytes(uint32_t longest) { return ((longest * 2u + 16u + 15u) & ~15u) + 256u; }
+
+__global__ __launch_bounds__(64) void emit_sorted_kernel(const uint8_t* __restrict__ codes, const uint32_t* __restrict__ cnt,
+                                                         const uint2* __restrict__ rowStart, const FrontState* __restrict__ st,
+                                                         int64_t m, uint32_t n, int cser, uint32_t positions, uint32_t stage_bytes,
+                                                         EmitTarget to, FrontResult* __restrict__ out) {
+    // LDS: [the row's columns][a word per lane for what is not indexed][counters: positions x kRowCounters][bucket start by position],
+    // positions rounded up to eight
+    extern __shared__ __align__(16) unsigned char s_row[];
+    if (blockIdx.x == gridDim.x - 1) {
+        emit_values(st, to, out);
+        return;
+    }
+    const int64_t r = blockIdx.x;
+    const uint32_t lane = threadIdx.x, eights = (positions + 7u) & ~7u;
+    const uint8_t* crow = codes + r * (int64_t)n;
+    const uint32_t run = ((n + 63u) / 64u + 15u) & ~15u, c0 = lane * run;
+    const uint32_t most = st->pos_of[0];
+    // f(first column, sixteen codes); behind the row's end stands the most frequent value, which takes no part.  Four loads are
+    // in flight (a trip to memory per sixteen columns took two thirds of the time).
+    const uint32_t pieces = run / 16u, blank = most * 0x01010101u;
+    constexpr int kAhead = 4;
+    uint4 ring[kAhead];
+    auto request = [&](uint32_t p, uint4& q) { __builtin_memcpy(&q, crow + min(c0 + 16u * min(p, pieces - 1u), n - 16u), 16); };
+    auto request_first = [&] {
+#pragma unroll
+        for (int d = 0; d < kAhead; ++d) request(d, ring[d]);
+    };
+    auto each_sixteen = [&](auto f) {
+        for (uint32_t p0 = 0; p0 < pieces; p0 += kAhead) {
+#pragma unroll
+            for (int d = 0; d < kAhead; ++d) {
+                const uint32_t p = p0 + d, c = c0 + 16u * p;
+                if (p >= pieces) break;  // uniform
+                uint32_t q[4] = {ring[d].x, ring[d].y, ring[d].z, ring[d].w};
+                request(p + kAhead, ring[d]);
+                if (c + 16u > n) {
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; ++i) {
+                        q[i] = blank;
+                        for (uint32_t b = 0; b < 4 && c + 4 * i + b < n; ++b)
+                            q[i] = (q[i] & ~(0xFFu << (8 * b))) | (uint32_t)crow[c + 4 * i + b] << (8 * b);
+                    }
+                }
+                f(c, q);
+            }
+        }
+    };
+    request_first();
+    uint32_t* counters = reinterpret_cast<uint32_t*>(s_row + stage_bytes);
+    uint32_t* begin = counters + eights * kRowCounters;
+    for (uint32_t i = lane; i < eights * kRowCounters / 4u; i += kWave) reinterpret_cast<uint4*>(counters)[i] = make_uint4(0, 0, 0, 0);
+    const uint32_t off0 = rowStart[r].y, count = rowStart[r + 1].y - off0;
+    for (uint32_t i = lane; i < eights; i += kWave) begin[i] = i == most ? count : 0u;  // the most frequent value: behind all others
+    emit_row_pointers<uint8_t>(r, cnt, rowStart, st, m, cser, to, [&](uint32_t k, uint32_t pos, uint32_t first) {
+        if (k >= 1u && k < st->Kp) begin[pos] = first - off0;
+    });
+    typedef unsigned char __attribute__((address_space(3))) * LdsByte;
+    const uint32_t mine = (uint32_t)(uintptr_t)(LdsByte)(unsigned char*)counters + (lane >> 1) * 4u;
+    const uint32_t half = 16u * (lane & 1u), one = 1u << half;
+    // the lane's counter of the i-th of four codes: one byte times the distance of the counters, a dot product of bytes
+    static_assert(kRowCounters * 4u < 256u, "distance of the counters");
+    typedef uint32_t __attribute__((address_space(3))) * LdsWord;
+    auto counter = [&](uint32_t four, int i) {
+        return reinterpret_cast<LdsWord>((uintptr_t)__builtin_amdgcn_udot4(four, (kRowCounters * 4u) << (8 * i), mine, false));
+    };
+    auto add = [&](LdsWord at) { return __hip_atomic_fetch_add(at, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+    wave_lds_sync();
+    each_sixteen([&](uint32_t, const uint32_t (&q)[4]) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) (void)add(counter(q[i >> 2], i & 3));
+    });
+    wave_lds_sync();
+    request_first();
+    // two positions per instruction, four instructions side by side
+    for (uint32_t i = lane; i < eights * kRowCounters; i += 4u * kWave) {
+        uint32_t word[4], incl[4], start[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            word[u] = counters[i + u * kWave];
+            start[u] = begin[(i + u * kWave) / kRowCounters];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) incl[u] = (word[u] & 0xFFFFu) + (word[u] >> 16);
+#define CER_HALF_SCAN(CTRL, ROWS) \
+    _Pragma("unroll") for (int u = 0; u < 4; ++u) incl[u] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl[u], CTRL, ROWS, 0xF, false);
+        CER_HALF_SCAN(0x111, 0xF)  // row_shr:1, 2, 4, 8
+        CER_HALF_SCAN(0x112, 0xF)
+        CER_HALF_SCAN(0x114, 0xF)
+        CER_HALF_SCAN(0x118, 0xF)
+        CER_HALF_SCAN(0x142, 0xA)  // row_bcast:15 into rows 1 and 3
+#undef CER_HALF_SCAN
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t lo = word[u] & 0xFFFFu, first = start[u] + incl[u] - lo - (word[u] >> 16);
+            counters[i + u * kWave] = first | ((first + lo) << 16);
+        }
+    }
+    wave_lds_sync();
+    // the row lies in LDS as far from a multiple of 16 bytes as in memory
+    uint16_t* colI = reinterpret_cast<uint16_t*>(to.base) + off0;
+    constexpr uint32_t kPer = 8;
+    const uint32_t shift = off0 & (kPer - 1u);
+    uint16_t* stage = reinterpret_cast<uint16_t*>(s_row) + shift;
+    typedef uint16_t __attribute__((address_space(3))) * LdsCol;
+    const uint32_t stage_at = (uint32_t)(uintptr_t)(LdsByte)(unsigned char*)stage;
+    const uint32_t aside = (uint32_t)(uintptr_t)(LdsByte)s_row + stage_bytes - 256u + lane * 4u;
+    each_sixteen([&](uint32_t c, const uint32_t (&q)[4]) {
+        uint32_t old[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) old[i] = add(counter(q[i >> 2], i & 3));
+#pragma unroll
+        for (uint32_t i = 0; i < 16; ++i)
+            *reinterpret_cast<LdsCol>((uintptr_t)min(stage_at + ((old[i] >> half) & 0xFFFFu) * 2u, aside)) = (uint16_t)(c | i);
+    });
+    wave_lds_sync();
+    const uint32_t total = shift + count;  // in units of columns, from the 16-byte boundary before the row on
+    for (uint32_t v = lane; v * kPer < total; v += kWave) {
+        if (v * kPer >= shift && (v + 1u) * kPer <= total) {
+            reinterpret_cast<uint4*>(colI - shift)[v] = reinterpret_cast<const uint4*>(s_row)[v];
+        } else {
+            for (uint32_t e = max(v * kPer, shift); e < min((v + 1u) * kPer, total); ++e) colI[e - shift] = stage[e - shift];
+        }
+    }
+}
+
+// Four rows per workgroup; the last workgroup does emit_values.
+template <typename ColT, typename OiT>
+__global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ codes, const uint32_t* __restrict__ cnt,
+                                                   const uint2* __restrict__ rowStart, const FrontState* __restrict__ st,
+                                                   int64_t m, int64_t n, int cser, int sparse, EmitTarget to,
+                                                   FrontResult* __restrict__ out) {
+    __shared__ uint32_t s_rank[kCodes];
+    __shared__ uint32_t s_fill[4][kCodes];  // next free colI slot of each rank's bucket
+    __shared__ uint32_t s_stage[4][kEmitStage];  // (column << 8) | rank of the columns waiting for the scatter
+    __shared__ unsigned long long s_marks[4][kCodes];  // per rank: the lanes of the current batch that hold it
+    if (blockIdx.x == gridDim.x - 1) {
+        emit_values(st, to, out);
+        return;
+    }
+    ColT* colI = reinterpret_cast<ColT*>(to.base);
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    s_rank[threadIdx.x] = st->rank_of[threadIdx.x];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) s_marks[w][threadIdx.x] = 0ull;
+    __syncthreads();
+    const int64_t r = (int64_t)blockIdx.x * 4 + wave;
+    if (r >= m) return;
+    uint32_t* fill = s_fill[wave];
+    unsigned long long* marks = s_marks[wave];
+    const uint32_t Kp = st->Kp;
+    emit_row_pointers<OiT>(r, cnt, rowStart, st, m, cser, to, [&](uint32_t k, uint32_t, uint32_t first) { fill[k] = first; });
     wave_lds_sync();
     // stable scatter of the row's columns into the buckets
     const uint32_t nbits = 32u - (uint32_t)__builtin_clz(Kp > 1 ? Kp - 1 : 1u);
@@ -1209,9 +1361,30 @@ int flags_to_error(uint32_t flags) {
     return CER_OK;
 }
 
+// Whether emit_sorted_kernel is expected to be ahead, for matrices of which half or more is indexed (the others are packed before
+// they are sorted).  Clocks: a row sorted in LDS takes 125 per 64 columns, 60 per codebook position and 10000 (its start, the pointers,
+// the way out), and its LDS limits how many of them a compute unit holds; emit_kernel takes 800 per 64 columns of a row, one after
+// another, or 72 of a compute unit's time.  Whole calls, emit_kernel / emit_sorted_kernel, us: 300 x 9000, 7 bits 115 / 90, 8 bits 118 / 97;
+// 1000 x 2000, 6 bits 74 / 67; 4096 x 9216, 7 bits 236 / 233, 8 bits 231 / 275; 2048 x 4096, 7 bits 101 / 99, 8 bits 102 / 122;
+// 4096 x 2050, 7 bits 112 / 119; equally frequent values 4096 x 9216, 100 of them 274 / 163, 256 323 / 226.
+bool sorted_rows_pay(int64_t m, int64_t n, uint32_t positions, size_t lds) {
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
+    const double columns = (double)n / 64.0, share = std::max((double)m / std::max(cus, 1), 1.0);  // rows per compute unit
+    const double rounds = std::ceil(share / std::floor(160.0 * 1024.0 / (double)lds));
+    return rounds * (125.0 * columns + 60.0 * positions + 10000.0) < std::max(800.0 * columns, 72.0 * columns * share) + 6000.0;
+}
+
 template <typename ColT>
 hipError_t launch_emit(hipStream_t s, const uint8_t* codes, const uint32_t* cnt, const uint2* rowStart, const FrontState* st,
                        int64_t m, int64_t n, int cser, int sparse, const EmitTarget& to, FrontResult* out) {
+    if constexpr (sizeof(ColT) == 2) {
+        const uint32_t stage = emit_stage_bytes(out->max_row_nnz), eights = (out->K + 7u) & ~7u;
+        const size_t lds = stage + (size_t)eights * (kRowCounters + 1u) * 4u;
+        if (!sparse && n >= 1024 && n <= kSortedColumns && lds <= 64 * 1024 && sorted_rows_pay(m, n, out->K, lds))
+            return cer::launch_kernel(emit_sorted_kernel, dim3((unsigned)m + 1u), dim3(64), lds, s, codes, cnt, rowStart, st, m, (uint32_t)n, cser,
+                                      out->K, stage, to, out);
+    }
     // rank < K <= 256, so OmegaI is always one byte wide here
     return cer::launch_kernel(emit_kernel<ColT, uint8_t>, dim3((unsigned)((m + 3) / 4 + 1)), dim3(256), 0, s, codes, cnt, rowStart,
                               st, m, n, cser, sparse, to, out);
