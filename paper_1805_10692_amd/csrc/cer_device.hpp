@@ -404,6 +404,7 @@ hipError_t launch_xtile_any(const DeviceView& d, const XtilePlan& p, const float
 // cer_mfma.hip -- batch > 1, decoded into bf16 pieces and multiplied on the matrix cores.  mfma_applicable: the codebook and
 // the sizes allow it; mfma_estimate_us: the product without the decode.
 bool mfma_applicable(const DeviceView& d, uint32_t L);
+int mfma_planes(const DeviceView& d);  // bf16 matrices the decoder writes
 double mfma_estimate_us(const DeviceView& d, uint32_t L);
 hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream);
 

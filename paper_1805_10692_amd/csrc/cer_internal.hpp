@@ -42,6 +42,11 @@ struct HostMatrix {
     mutable std::mutex fetch_mutex;
 };
 
+// Values on a uniform grid (uniform_pieces in cer_split3.hpp): whole multiples of scale . unit, plus offset.  scale 0: they are not.
+struct UniformGrid {
+    float scale = 0.f, unit = 0.f, offset = 0.f;
+};
+
 // What the kernels see: device pointers into the handle's single allocation.
 struct DeviceView {
     const void* colI = nullptr;        // minimal width, followed by 8 KiB of readable zero padding
@@ -62,6 +67,7 @@ struct DeviceView {
     float omega0 = 0.f;
     float omega_max = 0.f;  // largest magnitude in the codebook
     int32_t pieces = 0;  // bf16 numbers that add up to every codebook value exactly (1 .. 3); 0: some piece would be subnormal
+    UniformGrid grid;  // of the values
     // the device the arrays live on, as the launchers need it (read once, when the handle is bound to its memory)
     int32_t cus = 256;
     size_t lds_per_block = 64 * 1024;
@@ -152,7 +158,7 @@ int launch_stream_read(const void* src, int64_t bytes, void* sink, void* stream)
 int encode_device(const float* W_dev, int64_t m, int64_t n, const float* codebook, int32_t K, int32_t bits, bool cser,
                   void* stream, float* codebook_out, int32_t* K_out, cer_matrix** out);
 int decode_device(const DeviceView& v, float* W_dev, void* stream);
-// The same as v.pieces bf16 matrices, `plane` elements apart, in the operand order of the matrix cores: 32 x 16 tiles,
+// The same as bf16 matrices (v.pieces of them, or the two of a uniform grid), `plane` elements apart, in the operand order of the matrix cores: 32 x 16 tiles,
 // [row / 32][column / 16][column / 8 % 2][row % 32][column % 8], columns n .. pitch - 1 zero (pitch: a multiple of 16), rows
 // m .. not written.  A hipError_t value as int.
 int decode_pieces(const DeviceView& v, uint16_t* W_dev, int64_t pitch, int64_t plane, void* stream);

@@ -128,14 +128,14 @@ bool densify_estimates(const DeviceView& d, uint32_t L, double* t_gather_out, do
     const double mn = (double)d.m * (double)d.n;
     if ((double)d.nnz * 10.0 < mn) return false;  // the matrix cores spend ten times the multiply-adds: not worth estimating
     const bool pieces = mfma_applicable(d, L);
-    if (mn * (pieces ? 2.0 * d.pieces : 4.0) > (double)(1ull << 30)) return false;
+    if (mn * (pieces ? 2.0 * mfma_planes(d) : 4.0) > (double)(1ull << 30)) return false;
     const double flops = 2.0 * mn * L;
     const double t_gather = gather_estimate(d, L);
     double t_dense;
     if (pieces) {
         // the decoder: 7 us (578 x 1013), 9 us (conv shape), 11 us (633 x 5106, three pieces, 2.3 M indices), 15 us (1084 x
         // 13798, one piece, 4.5 M), 28 us (986 x 16765, three pieces, 9.7 M)
-        t_dense = mfma_estimate_us(d, L) * 1e-6 + 6e-6 + mn * 2.0 * d.pieces / 4.4e12 + (double)d.nnz * 0.35e-12;
+        t_dense = mfma_estimate_us(d, L) * 1e-6 + 6e-6 + mn * 2.0 * mfma_planes(d) / 4.4e12 + (double)d.nnz * 0.35e-12;
     } else {
         const double rate = flops < 1.5e10 ? 90e12 : (flops < 1e11 ? 105e12 : 120e12);
         const double t_write = 4.0 * mn / 4.5e12;  // the decoded matrix goes to memory once and is read back at least once

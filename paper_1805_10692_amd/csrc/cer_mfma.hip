@@ -20,6 +20,27 @@ namespace {
 
 constexpr uint32_t kFlush = 256;
 
+// offset . (v[0] + ... + v[7])
+__device__ __forceinline__ float offset_of(const float (&v)[8], float offset) {
+    float a = offset * v[0], b = offset * v[1];
+#pragma unroll
+    for (int i = 2; i < 8; i += 2) {
+        a = fmaf(offset, v[i], a);
+        b = fmaf(offset, v[i + 1], b);
+    }
+    return a + b;
+}
+
+// The two sums of mfma_pieces together.  kUniform: times the scale, with one rounding of the larger.
+template <int kForm>
+__device__ __forceinline__ floatx16 joined(floatx16 hi, floatx16 lo, float scale) {
+    if constexpr (kForm == 1) return hi;
+    if constexpr (kForm != kUniform) return hi + lo;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) hi[e] = fmaf(scale, hi[e], scale * lo[e]);
+    return hi;
+}
+
 // What a workgroup of either kernel below was given.
 struct Block {
     const uint16_t* W;
@@ -27,6 +48,7 @@ struct Block {
     float* Out;
     size_t plane;
     uint32_t m, n, L, pitch, row0, rows, col0, cols, k_begin, k_end;
+    float scale, offset;  // kUniform
 };
 
 // Products in binary32, the pieces of W added up again: the workgroup's outputs once more, over the ones from the matrix cores.
@@ -35,10 +57,11 @@ struct Block {
 // are mostly those of empty rows: the inputs are looked at first (odd: this thread's inputs had third pieces; without them nothing
 // is lost).  A function of its own, and behind the stores, so that nothing of it is held in registers while the matrix cores work.
 // Small inputs could also be caught on their way: 48 -> 53 us for 512 x 4608, batch 3136.
-// A wave takes tiles of 32 x 32 outputs, 64 columns of W per step, straight from memory; sums of kFlush columns as below.  Product of
+// A wave takes tiles of 32 x 32 outputs, 64 or 32 columns of W per step, straight from memory; sums of kFlush columns as below.  Product of
 // 512 x 4608, batch 3136, one-piece codebook: 68 us, 80 with empty rows, 247 with an infinity in X, 331 with X of about 2^-120.
-template <int PW>
+template <int kForm>
 __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, bool odd) {
+    constexpr int PW = weight_planes(kForm), NS = kForm == kUniform ? 2 : 4;  // 16 NS columns of W per step
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
     if (!__syncthreads_or(must)) {
         bool some = false;
@@ -62,11 +85,11 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
         const uint32_t xoff = (8u * half * b.L + min(c, b.L - 1u)) * 4u;
         floatx16 sum = {}, acc = {};
         uint32_t held = 0;
-        for (uint32_t k0 = b.k_begin; k0 < b.k_end; k0 += 64u) {  // a multiple of 64 columns
-            float x[4][8];
-            uint4 q[4][PW];
+        for (uint32_t k0 = b.k_begin; k0 < b.k_end; k0 += 16u * NS) {  // a multiple of 64 columns
+            float x[NS][8];
+            uint4 q[NS][PW];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < NS; ++s) {
                 const __amdgpu_buffer_rsrc_t xbuf = x_rows(b.X, b.L, k0 + 16 * s, b.n);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) x[s][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff + i * b.L * 4u, 0, 0));
@@ -74,7 +97,7 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
                 for (int p = 0; p < PW; ++p) q[s][p] = reinterpret_cast<const uint4*>(w + p * b.plane + (size_t)(k0 + 16 * s) * 32)[lane];
             }
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
+            for (int s = 0; s < NS; ++s)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     float v = 0.f;
@@ -83,9 +106,15 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
                         const uint32_t u = i < 4 ? (i < 2 ? q[s][p].x : q[s][p].y) : (i < 6 ? q[s][p].z : q[s][p].w);
                         v += __uint_as_float(i & 1 ? u & 0xFFFF0000u : u << 16);
                     }
+                    if constexpr (kForm == kUniform) {
+                        const uint32_t j = i < 4 ? (i < 2 ? q[s][0].x : q[s][0].y) : (i < 6 ? q[s][0].z : q[s][0].w);
+                        const uint32_t e = i < 4 ? (i < 2 ? q[s][1].x : q[s][1].y) : (i < 6 ? q[s][1].z : q[s][1].w);
+                        const double grid = (double)__uint_as_float(i & 1 ? j & 0xFFFF0000u : j << 16) + (double)__uint_as_float(i & 1 ? e & 0xFFFF0000u : e << 16);
+                        v = k0 + 16 * s + 8 * half + i < b.n ? (float)fma((double)b.scale, grid, (double)b.offset) : 0.f;
+                    }
                     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v, x[s][i], acc, 0, 0, 0);
                 }
-            if ((held += 64u) >= kFlush) {
+            if ((held += 16u * NS) >= kFlush) {
                 held = 0;
                 sum += acc;
                 acc = floatx16{};
@@ -100,8 +129,9 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
     }
 }
 
-template <int PW, int TN, int D>
+template <int kForm, int TN, int D>
 struct MfmaTile {
+    static constexpr int PW = weight_planes(kForm);
     static constexpr int TM = 2, BM = 256, BN = 32 * TN, BK = 2048 / BN, KG = BK / 8, KS = BK / 16;
     uint4 b[2][3][KG][BN];
 
@@ -109,7 +139,7 @@ struct MfmaTile {
     // round each of them to the size of the whole).  Returns a NaN if this thread's share of X holds numbers without pieces, and
     // 0 if none of them has a third piece.
     __device__ __forceinline__ float run(const uint16_t* const (&wtile)[TM], size_t plane, const float* X, uint32_t n, uint32_t L,
-                                         uint32_t xcol, uint32_t k_begin, uint32_t k_end, floatx16 (&sum)[TM][TN]) {
+                                         uint32_t xcol, uint32_t k_begin, uint32_t k_end, floatx16 (&sum)[TM][TN], float scale, float offset, float& shift) {
         const uint32_t tid = threadIdx.x, lane = tid & 63u;
         const uint32_t xc = tid % BN, xg = tid / BN;  // this thread's share of X: rows 8 xg .. 8 xg + 7 of a step, one column
         uint32_t xoff[8];
@@ -132,9 +162,15 @@ struct MfmaTile {
                     for (int p = 0; p < PW; ++p)
                         a[slot][s][i][p] = reinterpret_cast<const uint4*>(wtile[i] + p * plane + (size_t)(k0 + 16 * s) * 32)[lane];
         };
-        auto store_x = [&](int slot, int buf) {
+        float part = 0.f;  // kUniform: offset . (sum of this thread's share of X); `shift` takes it as `sum` does `acc`
+        auto store_x = [&](int slot, int buf, bool last) {
             uint4 o[3];
             odd += split3_8(xr[slot], o);
+            if constexpr (kForm == kUniform) {
+                const float(&v)[8] = xr[slot];
+                const float eight = offset_of(v, offset);
+                part += last ? 0.f : eight;  // behind the end the last step comes once more
+            }
 #pragma unroll
             for (int p = 0; p < 3; ++p) b[buf][p][xg][xc] = o[p];
         };
@@ -151,15 +187,18 @@ struct MfmaTile {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) sum[i][j] += PW > 1 ? acc[i][j] + lo[i][j] : acc[i][j];
+                for (int j = 0; j < TN; ++j) sum[i][j] += joined<kForm>(acc[i][j], lo[i][j], scale);
+            shift += part;
+            part = 0.f;
         };
+        shift = 0.f;
         clear(acc);
         clear(lo);
         clear(sum);
 #pragma unroll
         for (int s = 0; s + 1 < D; ++s) load_x(k_begin + s * BK, s);
         load_w(k_begin, 0);
-        store_x(0, 0);
+        store_x(0, 0, false);
         __syncthreads();
         // D steps per round, so that the register slots are named at compile time; k_end - k_begin is a multiple of D BK
         uint32_t held = 0;
@@ -179,9 +218,9 @@ struct MfmaTile {
 #pragma unroll
                     for (int i = 0; i < TM; ++i)
 #pragma unroll
-                        for (int j = 0; j < TN; ++j) mfma_pieces<PW>(a[t & 1][s][i], bb[j], acc[i][j], lo[i][j]);
+                        for (int j = 0; j < TN; ++j) mfma_pieces<kForm>(a[t & 1][s][i], bb[j], acc[i][j], lo[i][j]);
                 }
-                store_x((t + 1) % D, (t + 1) & 1);
+                store_x((t + 1) % D, (t + 1) & 1, k0 + (t + 1) * BK >= k_end);
                 __syncthreads();
             }
             held += D * BK;
@@ -198,12 +237,12 @@ struct MfmaTile {
 };
 
 // D: steps in flight.
-template <int PW, int TN, int D>
-__global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
+template <int kForm, int TN, int D>
+__global__ __launch_bounds__(256, kForm == 1 ? 2 : 1) void mfma_product_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
     uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, size_t split_stride,
-    float faint) {
-    using Tile = MfmaTile<PW, TN, D>;
+    float faint, float scale, float offset) {
+    using Tile = MfmaTile<kForm, TN, D>;
     __shared__ Tile tile;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroups are dealt round-robin to the eight XCDs; every XCD takes a contiguous eighth of the list of work items, in
@@ -229,7 +268,24 @@ __global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
     for (int i = 0; i < Tile::TM; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * 32 * pitch;
     const uint32_t xcol = min(col0 + tid % Tile::BN, L - 1u);
     floatx16 sum[Tile::TM][TN];
-    const float odd = tile.run(wtile, plane, X, n, L, xcol, k_begin, k_end, sum);
+    float shift;
+    float odd = tile.run(wtile, plane, X, n, L, xcol, k_begin, k_end, sum, scale, offset, shift);
+    if constexpr (kForm == kUniform) {
+        // what 256 / BN threads have of a column; every wave has passed the last step's barrier
+        float* s_shift = reinterpret_cast<float*>(&tile);
+        s_shift[tid] = shift;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            float t = 0.f;
+#pragma unroll
+            for (uint32_t q = 0; q < 256u / Tile::BN; ++q) t += s_shift[q * Tile::BN + j * 32 + (lane & 31u)];
+#pragma unroll
+            for (int i = 0; i < Tile::TM; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sum[i][j][e] += t;
+        }
+    }
 
     // The vote comes before the stores (behind them: 2 us more).
     float least = INFINITY;
@@ -239,7 +295,10 @@ __global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
         for (int e = 0; e < 16; ++e)
             if (row0 + 32 * i + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4) < m)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) least = fminf(least, fabsf(sum[i][j][e]));
+                for (int j = 0; j < TN; ++j) {
+                    least = fminf(least, fabsf(sum[i][j][e]));
+                    if constexpr (kForm == kUniform) odd = fmaf(0.f, sum[i][j][e], odd);  // NaN where a sum is not finite
+                }
     const int look = __syncthreads_or(odd != odd || least < faint);
 
     // accumulator element e of lane l: row = 8 (e / 4) + 4 (l / 32) + e % 4, column = l % 32
@@ -255,7 +314,7 @@ __global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
             }
         }
     if (look)
-        exact_block<PW>(Block{W, X, Out, plane, m, n, L, pitch, rt * Tile::BM, Tile::BM, col0, Tile::BN, k_begin, k_end}, odd != odd, odd != 0.f);
+        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, rt * Tile::BM, Tile::BM, col0, Tile::BN, k_begin, k_end, scale, offset}, odd != odd, odd != 0.f);
 }
 
 // The same for small problems: 64 x 32 CT outputs per workgroup, the four waves share its columns of W (32 at a time, in turn)
@@ -266,9 +325,11 @@ __global__ __launch_bounds__(256, PW == 1 ? 2 : 1) void mfma_product_kernel(
 // 3136: 66 instead of 48.  Bound by the latency of its loads where the chip is not full (2048 x 2048, batch 16, 128 workgroups:
 // matrix pipes busy 6 % of the launch, vector ALU 11 %, half of a wave's time is waiting for data), else by what L2 delivers (80
 // KiB per 128 columns): the larger tile is the better one where it fills the chip.
-template <int PW, int CT>
+template <int kForm, int CT>
 __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2], size_t plane, const float* X, uint32_t n,
-                                                uint32_t L, uint32_t col0, uint32_t k_begin, uint32_t k_end, floatx16 (&acc)[2][CT]) {
+                                                uint32_t L, uint32_t col0, uint32_t k_begin, uint32_t k_end, floatx16 (&acc)[2][CT],
+                                                float scale, float offset, float (&shift)[CT]) {
+    constexpr int PW = weight_planes(kForm);
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t xoff[8];  // of the wave's first column tile
 #pragma unroll
@@ -303,8 +364,9 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
             for (int j = 0; j < CT; ++j) {
                 uint4 b[3];
                 odd += split3_8(x[slot][s][j], b);
+                if constexpr (kForm == kUniform) shift[j] += offset_of(x[slot][s][j], offset);
 #pragma unroll
-                for (int i = 0; i < 2; ++i) mfma_pieces<PW>(a[slot][s][i], b, acc[i][j], lo[i][j]);
+                for (int i = 0; i < 2; ++i) mfma_pieces<kForm>(a[slot][s][i], b, acc[i][j], lo[i][j]);
             }
     };
 #pragma unroll
@@ -313,6 +375,8 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
         for (int j = 0; j < CT; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = lo[i][j][e] = 0.f;
+#pragma unroll
+    for (int j = 0; j < CT; ++j) shift[j] = 0.f;
     uint32_t k0 = k_begin + 32u * wave;
     if (k0 >= k_end) return odd;
     load(k0, 0);
@@ -328,17 +392,18 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < CT; ++j) acc[i][j] += lo[i][j];
+            for (int j = 0; j < CT; ++j) acc[i][j] = joined<kForm>(acc[i][j], lo[i][j], scale);
     }
     return odd;
 }
 
-template <int PW, int CT>
-__global__ __launch_bounds__(256, PW == 1 || (PW == 2 && CT == 1) ? 2 : 1) void mfma_small_kernel(
+template <int kForm, int CT>
+__global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUniform) && CT == 1) ? 2 : 1) void mfma_small_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
     uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, size_t split_stride,
-    float faint) {
+    float faint, float scale, float offset) {
     __shared__ float s_acc[4][2 * CT][16][64];
+    __shared__ float s_shift[kForm == kUniform ? 4 : 1][CT][64];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t items = row_tiles * col_tiles * splits, eighth = (items + 7u) >> 3;
     const uint32_t item = (blockIdx.x & 7u) * eighth + (blockIdx.x >> 3);  // as above
@@ -351,7 +416,12 @@ __global__ __launch_bounds__(256, PW == 1 || (PW == 2 && CT == 1) ? 2 : 1) void 
 #pragma unroll
     for (int i = 0; i < 2; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * 32 * pitch;
     floatx16 acc[2][CT];
-    const float odd = mfma_small_run<PW, CT>(wtile, plane, X, n, L, col0, k_begin, k_end, acc);
+    float shift[CT];
+    float odd = mfma_small_run<kForm, CT>(wtile, plane, X, n, L, col0, k_begin, k_end, acc, scale, offset, shift);
+    if constexpr (kForm == kUniform) {
+#pragma unroll
+        for (int j = 0; j < CT; ++j) s_shift[wave][j][lane] = shift[j];
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -361,12 +431,22 @@ __global__ __launch_bounds__(256, PW == 1 || (PW == 2 && CT == 1) ? 2 : 1) void 
     __syncthreads();
     // every wave adds up and stores a quarter of the workgroup's accumulators
     constexpr int PER = 2 * CT * 16 / 4;
-    float y[PER], least = INFINITY;
+    float y[PER], least = INFINITY, t[CT] = {};
+    if constexpr (kForm == kUniform) {  // what the lanes l and l + 32 of every wave have of a column
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            for (int w = 0; w < 4; ++w) t[j] += s_shift[w][j][lane & 31u] + s_shift[w][j][(lane & 31u) + 32u];
+        }
+    }
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         const uint32_t f = wave * PER + q, tile = f >> 4, e = f & 15u;
         y[q] = (s_acc[0][tile][e][lane] + s_acc[1][tile][e][lane]) + (s_acc[2][tile][e][lane] + s_acc[3][tile][e][lane]);
-        if (row0 + 32 * (tile / CT) + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4) < m) least = fminf(least, fabsf(y[q]));
+        if constexpr (kForm == kUniform) y[q] += CT == 1 || tile % CT == 0 ? t[0] : t[CT - 1];
+        if (row0 + 32 * (tile / CT) + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4) < m) {
+            least = fminf(least, fabsf(y[q]));
+            if constexpr (kForm == kUniform) odd = fmaf(0.f, y[q], odd);  // as above
+        }
     }
     const int look = __syncthreads_or(odd != odd || least < faint);
 #pragma unroll
@@ -377,7 +457,7 @@ __global__ __launch_bounds__(256, PW == 1 || (PW == 2 && CT == 1) ? 2 : 1) void 
         if (r < m && c < L) Out[(size_t)r * L + c] = y[q];
     }
     if (look)
-        exact_block<PW>(Block{W, X, Out, plane, m, n, L, pitch, row0, 64u, col0, 32u * CT, k_begin, k_end}, odd != odd, odd != 0.f);
+        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, row0, 64u, col0, 32u * CT, k_begin, k_end, scale, offset}, odd != odd, odd != 0.f);
 }
 
 __global__ __launch_bounds__(256) void mfma_sum_kernel(const float* __restrict__ part, float* __restrict__ Y, size_t count,
@@ -397,7 +477,9 @@ __global__ __launch_bounds__(256) void mfma_sum_kernel(const float* __restrict__
 constexpr uint32_t kPitchStep = 128;  // W's rows are padded to a multiple of this many columns: a round of every variant
 
 // Steps in flight: as many as the registers allow next to TM x TN tiles of sums.
-constexpr int mfma_depth(int pieces, uint32_t BN) { return pieces == 1 && BN == 64 ? 4 : 2; }
+constexpr int mfma_depth(int form, uint32_t BN) { return form == 1 && BN == 64 ? 4 : 2; }
+
+int weight_form(const DeviceView& d) { return d.grid.scale != 0.f ? kUniform : d.pieces; }
 
 struct MfmaShape {
     bool small;
@@ -409,8 +491,10 @@ struct MfmaShape {
 // one-piece codebooks with BN = 64 -- overlap, but share the matrix cores: `alone` and `together` scale the time of a round).
 // Measured per unit: 4.1 - 4.7 TFLOP/s with BN = 64, bound by the operands' bytes with
 // BN = 32; the small tiles 2.4 - 3.5 TFLOP/s.  A split along n costs its partial sums, written and read again.
+// each_us: what a workgroup takes besides its rounds, kUniform only, fitted with the rates to 60 products (8.8 us of the large tiles, 6.5
+// of the small ones with the launch's; per round of 64 columns of the large ones 2.1 us, of 128 columns of the small ones 1.45).
 void shape_splits(const DeviceView& d, uint32_t L, uint32_t round, double round_us, double alone, double together,
-                  double fixed_us, MfmaShape* s) {
+                  double fixed_us, double each_us, MfmaShape* s) {
     const uint32_t pitch = ((uint32_t)d.n + kPitchStep - 1) / kPitchStep * kPitchStep, rounds = (pitch + round - 1) / round;
     s->row_tiles = (uint32_t)((d.m + s->BM - 1) / s->BM);
     s->col_tiles = (L + s->BN - 1) / s->BN;
@@ -420,8 +504,8 @@ void shape_splits(const DeviceView& d, uint32_t L, uint32_t round, double round_
     for (uint32_t sp = 1; sp <= std::min(most, 64u); ++sp) {
         const uint32_t per = (rounds + sp - 1) / sp, used = (rounds + per - 1) / per;
         const double share = std::ceil(tiles * used / units);
-        double us = share * per * round_us * (share < 2 ? alone : together) + fixed_us;
-        if (used > 1) us += 3.0 + (double)used * d.m * L * 8.0 / 6.5e6;
+        double us = share * (per * round_us * (share < 2 ? alone : together) + each_us) + fixed_us;
+        if (used > 1) us += (each_us > 0 ? 4.0 : 3.0) + (double)used * d.m * L * 8.0 / 6.5e6;
         if (us < s->us) {
             s->us = us;
             s->splits = used;
@@ -431,16 +515,17 @@ void shape_splits(const DeviceView& d, uint32_t L, uint32_t round, double round_
 }
 
 MfmaShape mfma_shape(const DeviceView& d, uint32_t L) {
-    const double products = d.pieces == 1 ? 3 : (d.pieces == 2 ? 5 : 6);
+    const int form = weight_form(d), planes = weight_planes(form);
+    const double products = form == 1 ? 3 : (form == kUniform ? 4 : (form == 2 ? 5 : 6));
     MfmaShape big;
     big.small = false;
     big.BN = L <= 32 ? 32 : 64;
     big.BM = 256;
     {
-        const uint32_t round = mfma_depth(d.pieces, big.BN) * 2048 / big.BN;  // columns per round of the kernel
-        const double flops = 2.0 * big.BM * big.BN * round * products, bytes = (double)round * (big.BM * 2.0 * d.pieces + big.BN * 4.0);
-        shape_splits(d, L, round, big.BN == 32 ? std::max(flops / 4.3e6, bytes / 3.0e4) : flops / 4.4e6,
-                     d.pieces == 1 ? 1.12 : 1.0, d.pieces == 1 ? 0.95 : 1.0, 4.0, &big);
+        const uint32_t round = mfma_depth(form, big.BN) * 2048 / big.BN;  // columns per round of the kernel
+        const double flops = 2.0 * big.BM * big.BN * round * products, bytes = (double)round * (big.BM * 2.0 * planes + big.BN * 4.0);
+        shape_splits(d, L, round, big.BN == 32 ? std::max(flops / (form == kUniform ? 4.0e6 : 4.3e6), bytes / 3.0e4) : flops / (form == kUniform ? 4.1e6 : 4.4e6),
+                     form == 1 ? 1.12 : 1.0, form == 1 ? 0.95 : 1.0, form == kUniform ? 2.5 : 4.0, form == kUniform ? 6.5 : 0.0, &big);
     }
     MfmaShape small;
     small.small = true;
@@ -448,26 +533,27 @@ MfmaShape mfma_shape(const DeviceView& d, uint32_t L) {
     small.BM = 64;
     {
         const double flops = 2.0 * small.BM * small.BN * 128 * products;
-        shape_splits(d, L, 128, flops / (d.pieces == 1 ? 3.5e6 : (d.pieces == 2 ? 2.9e6 : 2.4e6)), d.pieces == 1 && small.BN == 64 ? 1.5 : 1.0, 1.0,
-                     3.0, &small);
+        shape_splits(d, L, 128, flops / (form == 1 ? 3.5e6 : (planes == 2 ? 2.9e6 : 2.4e6)), form == 1 && small.BN == 64 ? 1.5 : 1.0, 1.0,
+                     form == kUniform ? 3.5 : 3.0, form == kUniform ? 4.0 : 0.0, &small);
     }
     return small.us < big.us ? small : big;
 }
 
-template <int PW>
+template <int kForm>
 hipError_t launch_shape(const MfmaShape& s, const uint16_t* W, const float* X, float* out, uint32_t m, uint32_t n, uint32_t L,
-                        uint32_t pitch, size_t plane, float faint, hipStream_t stream) {
+                        uint32_t pitch, size_t plane, float faint, const DeviceView& d, hipStream_t stream) {
     const dim3 grid((s.row_tiles * s.col_tiles * s.splits + 7) / 8 * 8);
     const size_t count = (size_t)m * L;
-    auto* kern = s.small ? (s.BN == 32 ? mfma_small_kernel<PW, 1> : mfma_small_kernel<PW, 2>)
-                         : (s.BN == 32 ? mfma_product_kernel<PW, 1, mfma_depth(PW, 32)> : mfma_product_kernel<PW, 2, mfma_depth(PW, 64)>);
+    auto* kern = s.small ? (s.BN == 32 ? mfma_small_kernel<kForm, 1> : mfma_small_kernel<kForm, 2>)
+                         : (s.BN == 32 ? mfma_product_kernel<kForm, 1, mfma_depth(kForm, 32)> : mfma_product_kernel<kForm, 2, mfma_depth(kForm, 64)>);
     return launch_kernel(kern, grid, dim3(256), 0, stream, W, X, out, m, n, L, pitch, plane, s.row_tiles, s.col_tiles, s.splits,
-                         s.kchunk, count, faint);
+                         s.kchunk, count, faint, d.grid.scale, d.grid.offset);
 }
 
 }  // namespace
 
 // Whether the codebook and the sizes allow the route at all, and its estimated duration without the decode.
+int mfma_planes(const DeviceView& d) { return weight_planes(weight_form(d)); }
 bool mfma_applicable(const DeviceView& d, uint32_t L) {
     return d.pieces > 0 && d.m > 0 && d.n > 0 && L > 1 && d.n < (1ll << 31) && d.m < (1ll << 31) && (uint64_t)d.m * L < (1ull << 40) &&
            ((uint64_t)d.n + kPitchStep) * L * 4u < (1ull << 32);  // X is addressed with 32-bit offsets
@@ -481,7 +567,7 @@ hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L
     // one temporary: the partial sums, then the pieces
     const size_t part_bytes = s.splits > 1 ? (count * s.splits * 4 + 255) & ~(size_t)255 : 0;
     unsigned char* tmp = nullptr;
-    hipError_t e = (hipError_t)temp_alloc(reinterpret_cast<void**>(&tmp), part_bytes + (size_t)plane * 2 * d.pieces, stream);
+    hipError_t e = (hipError_t)temp_alloc(reinterpret_cast<void**>(&tmp), part_bytes + (size_t)plane * 2 * weight_planes(weight_form(d)), stream);
     if (e != hipSuccess) return e;
     auto* W = reinterpret_cast<uint16_t*>(tmp + part_bytes);
     float* out = s.splits > 1 ? reinterpret_cast<float*>(tmp) : Y;
@@ -489,11 +575,13 @@ hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L
     if (e == hipSuccess) {
         const uint32_t m = (uint32_t)d.m, n = (uint32_t)d.n;
         // An input loses at most half of 2^-133, a sum at most n max|w| 2^-134: less than 2^-26 of itself from here on.
-        const float faint = (float)std::min((double)d.n * d.omega_max * 0x1p-108, 1e38);
-        switch (d.pieces) {
-            case 1: e = launch_shape<1>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, stream); break;
-            case 2: e = launch_shape<2>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, stream); break;
-            default: e = launch_shape<3>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, stream);
+        // (on a grid the weights less the offset may be twice as large)
+        const float faint = (float)std::min((double)d.n * d.omega_max * (d.grid.scale != 0.f ? 0x1p-107 : 0x1p-108), 1e38);
+        switch (weight_form(d)) {
+            case 1: e = launch_shape<1>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, d, stream); break;
+            case 2: e = launch_shape<2>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, d, stream); break;
+            case 3: e = launch_shape<3>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, d, stream); break;
+            default: e = launch_shape<kUniform>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, d, stream);
         }
     }
     if (e == hipSuccess && s.splits > 1)

@@ -934,6 +934,7 @@ struct DecodeArgs {
     const uint32_t* tab;  // rank table
     uint32_t tab_shift;
     uint32_t rows;        // decode_tiles_kernel: rows per workgroup, 8 or 4
+    cer::UniformGrid grid;  // ... and the grid of the values
 };
 
 __device__ __forceinline__ void load_eight(const uint8_t* p, uint32_t v[8]) {
@@ -1090,6 +1091,10 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
         const uint32_t rows = (uint32_t)min((int64_t)a.rows, m - row0), words = rows << a.tab_shift;
         for (uint32_t i = tid; i < words; i += 512u) s_ptr[i] = a.tab[((size_t)row0 << a.tab_shift) + i];
         for (uint32_t k = tid; k < a.K; k += 512u) {
+            if (kPieces == 2 && a.grid.scale != 0.f) {
+                s_val[k] = cer::uniform_pieces(a.omega[k], a.grid);
+                continue;
+            }
             uint32_t p[3];
             cer::split3_finite(a.omega[k], p);
             s_val[k] = p[0] | (p[1] << 16);
@@ -1407,6 +1412,7 @@ DecodeArgs decode_args(const DeviceView& v, int64_t nseg, uint32_t multiple) {
     a.n = v.n;
     a.tab = v.rank_tab;
     a.tab_shift = (uint32_t)v.rank_tab_shift;
+    a.grid = v.grid;
     nseg = std::min<int64_t>(std::max<int64_t>(nseg, 1), 65535);
     a.seg = (uint32_t)(((v.n + nseg - 1) / nseg + multiple - 1) / multiple * multiple);
     a.nseg = (uint32_t)((v.n + a.seg - 1) / a.seg);
@@ -1429,6 +1435,7 @@ hipError_t launch_decode(const DeviceView& v, float* out, hipStream_t s) {
 
 template <typename ColT, typename CodeT>
 hipError_t launch_decode_tiles(const DeviceView& v, uint16_t* out, int64_t pitch, int64_t plane, hipStream_t s) {
+    const int pieces = v.grid.scale != 0.f ? 2 : v.pieces;
     uint32_t rows = 8;
     while (rows > 4 && (v.m + rows - 1) / rows < v.cus) rows >>= 1;
     // as few segments as 48 KiB of LDS allow (two workgroups per compute unit): each of them reads all indices of its rows
@@ -1439,13 +1446,13 @@ hipError_t launch_decode_tiles(const DeviceView& v, uint16_t* out, int64_t pitch
     const size_t lds = (size_t)(a.seg + 8) * rows * sizeof(CodeT);
     {   // with the static part more than 64 KiB
         static cer::LdsGrant<3> grant;
-        const void* kern = v.pieces == 1 ? (const void*)decode_tiles_kernel<ColT, CodeT, 1>
-                                         : (v.pieces == 2 ? (const void*)decode_tiles_kernel<ColT, CodeT, 2> : (const void*)decode_tiles_kernel<ColT, CodeT, 3>);
-        const hipError_t e = grant.ensure(v.pieces - 1, kern, 56 * 1024);
+        const void* kern = pieces == 1 ? (const void*)decode_tiles_kernel<ColT, CodeT, 1>
+                                         : (pieces == 2 ? (const void*)decode_tiles_kernel<ColT, CodeT, 2> : (const void*)decode_tiles_kernel<ColT, CodeT, 3>);
+        const hipError_t e = grant.ensure(pieces - 1, kern, 56 * 1024);
         if (e != hipSuccess) return e;
     }
     const ColT* colI = static_cast<const ColT*>(v.colI);
-    switch (v.pieces) {
+    switch (pieces) {
         case 1: return launch_kernel(decode_tiles_kernel<ColT, CodeT, 1>, grid, dim3(512), lds, s, colI, a, v.m, pitch, plane, out);
         case 2: return launch_kernel(decode_tiles_kernel<ColT, CodeT, 2>, grid, dim3(512), lds, s, colI, a, v.m, pitch, plane, out);
         default: return launch_kernel(decode_tiles_kernel<ColT, CodeT, 3>, grid, dim3(512), lds, s, colI, a, v.m, pitch, plane, out);

@@ -46,7 +46,7 @@ CASES = [
     (785, 1000, 33, 64, 0.4, "cer", 3), (1030, 1537, 40, 65, 0.5, "cser", 1), (1000, 2000, 49, 128, 0.5, "cer", 0),
     (900, 20000, 64, 7, 0.6, "cer", 0), (780, 1300, 70, 256, 0.3, "cser", 0), (900, 700, 130, 16, 0.6, "cer", 1),
     (800, 3000, 200, 255, 0.2, "cser", 0), (3000, 900, 64, 5, 0.5, "cer", 0), (4000, 1500, 60, 3, 0.5, "cer", 2),
-    (1600, 40000, 40, 5, 0.6, "cser", 0),
+    (1600, 40000, 40, 100, 0.8, "cser", 0),
 ]
 
 
