@@ -496,6 +496,7 @@ bool uniform_grid(const std::vector<float>& omega, cer::UniformGrid* grid) {
     grid->unit = std::ldexp(1.f, e - 1);
     grid->scale = s / grid->unit;
     grid->offset = c;
+    grid->inverse = 1.0 / s;
     return true;
 }
 }  // namespace

@@ -418,13 +418,9 @@ NarrowEstimate narrow_estimate(const DeviceView& d, uint32_t L);
 hipError_t launch_narrow(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream);
 
 // cer_fused.hip -- batch > 1, decode + matrix-core product in one launch.  temporaries: partial sums of parts of W's columns are
-// allowed (a second launch adds them up).  FusedEstimate: rows of W per workgroup, 0 and a huge duration where it is not applicable.
+// allowed (a second launch adds them up).  fused_rows: rows of W per workgroup, 0 where it is not applicable or would take `below` us.
 // dense_zeros: infinities and NaNs in X reach every row, as in launch_mfma; else those that index them, as with the gathers.
-struct FusedEstimate {
-    int rows = 0;
-    double us = 1e30;
-};
-FusedEstimate fused_estimate(const DeviceView& d, uint32_t L, bool temporaries);
+int fused_rows(const DeviceView& d, uint32_t L, bool temporaries, double below);
 hipError_t launch_fused(const DeviceView& d, const float* X, float* Y, uint32_t L, bool temporaries, bool dense_zeros, hipStream_t stream);
 
 // cer_strip.hip -- batch > 1, strips of X resident in LDS (needs the strip-major index of cer_prepare_strips)

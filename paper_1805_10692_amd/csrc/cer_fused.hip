@@ -61,8 +61,7 @@ struct FusedArgs : FusedRest {
 //   [per row: one byte per column of the segment, the entry its element has in that list]; later the waves' sums
 constexpr uint32_t kPrefixBytes = 2048, kBlankAt = kPrefixBytes + 16, kCallAt = kBlankAt + 64, kListsAt = kCallAt + 144;
 __host__ __device__ constexpr uint32_t table_at(uint32_t waves) { return kListsAt + waves * 2u * (uint32_t)Shape::NWORDS * 4u; }
-template <int PW>
-__host__ __device__ constexpr uint32_t entry_bytes() { return PW == 1 ? 2u : 8u; }
+__host__ __device__ constexpr uint32_t entry_bytes(int form) { return form == 1 ? 2u : (form == kUniform ? 4u : 8u); }
 __host__ __device__ __forceinline__ uint32_t values_at(uint32_t waves, uint32_t tab_shift, uint32_t entry) { return table_at(waves) + (entry << tab_shift); }
 
 __device__ __forceinline__ bool vote(unsigned char* smem, int slot, bool mine) {
@@ -250,6 +249,14 @@ __device__ __forceinline__ void split3_8_dot(const float x[8], uint4 out[3]) {
     for (int j = 0; j < 3; ++j) out[j] = make_uint4(p[j][0], p[j][1], p[j][2], p[j][3]);
 }
 
+// The sum of what lanes 16 or 32 apart hold.
+template <int kApart>
+__device__ __forceinline__ float with_lanes(float t) {
+    const uint32_t u = __float_as_uint(t);
+    const auto pair = kApart == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false) : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(pair[0]) + __uint_as_float(pair[1]);
+}
+
 // Outputs once more in binary32, for inputs that have no pieces (must) or whose pieces may lose what a faint sum shows; see
 // exact_block in cer_mfma.hip.  dense: the sum over all elements; else, as the gathers have it, over the indexed ones (of the
 // differences from the most frequent value) and that value times the column sum: a zero times an infinity does not count there.
@@ -319,10 +326,11 @@ __device__ __attribute__((noinline)) void exact_outputs(unsigned char* smem, boo
     }
 }
 
-template <int PW, int RT, int CT, int NW>
+template <int kForm, int RT, int CT, int NW>
 __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
     const uint32_t* tab, const float* X, const uint16_t* colI, const float* omega, uint32_t m, uint32_t n, uint32_t L, uint32_t row_magic,
-    uint32_t eighth, uint32_t packed, FusedRest rest) {
+    uint32_t eighth, uint32_t packed, FusedRest rest, UniformGrid grid) {
+    constexpr int PW = weight_planes(kForm), kWords = kForm == 3 ? 2 : 1;  // bf16 numbers and dwords per value
     constexpr uint32_t kWaves = NW, kThreads = NW * kWave;
     constexpr uint32_t R = 16 * RT, RW = R / kWaves, BN = 16 * CT;
     constexpr int D = NW == 16 ? 2 : (CT == 1 ? 4 : (CT == 2 ? 3 : 2));  // steps of X in registers: the current one and what is on its way
@@ -363,8 +371,16 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
         for (int i = 0; i < 8; ++i) load_columns<CT>(xbuf, xoff[i], v[i]);
     };
     floatx4 sum[RT][CT] = {}, acc[RT][CT] = {}, lo[RT][CT] = {};
+    float shift[CT] = {}, shifts[CT] = {};
+    auto joined = [&](int r, int c) {
+        floatx4 v = acc[r][c] + lo[r][c];
+        if constexpr (kForm == kUniform)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = fmaf(grid.scale, acc[r][c][e], grid.scale * lo[r][c][e]);
+        return v;
+    };
     typedef const uintx2 __attribute__((address_space(3))) * LdsU2;
-    typedef const uint16_t __attribute__((address_space(3))) * LdsU1;
+    typedef const typename std::conditional<kForm == 1, uint16_t, uint32_t>::type __attribute__((address_space(3))) * LdsOne;
     unsigned char *codes = nullptr, *values = nullptr;
     uint32_t codes0 = 0, values0 = 0;
 
@@ -394,12 +410,14 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
             }
             if (tid < 4u) reinterpret_cast<uint32_t*>(smem + kPrefixBytes)[tid] = 0u;
             codes = smem + rest.codes;
-            values = smem + values_at(kWaves, tab_shift, entry_bytes<PW>());
+            values = smem + values_at(kWaves, tab_shift, entry_bytes(kForm));
             codes0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)codes + c16 * rest.stride + 8u * g;
             values0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)values + c16 * rest.row_values;
         } else {
             __syncthreads();  // the bytes of the segment before have been read
         }
+        const double inverse = grid.inverse;
+        if constexpr (kForm == kUniform) asm volatile("" ::"s"(inverse));  // (loaded with the other arguments)
         for (uint32_t i = tid; i < R * rest.stride / 16u; i += kThreads) reinterpret_cast<uint4*>(codes)[i] = make_uint4(0, 0, 0, 0);
         uint4 first[RW][Shape::NW];
 #pragma unroll
@@ -415,8 +433,9 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
         unsigned char* table = smem + table_at(kWaves);
         if (s0 == k_begin && tid <= last_word) {
             uint32_t p[3];
-            split3_finite(value, p);
-            if constexpr (PW == 1) reinterpret_cast<uint16_t*>(table)[tid] = (uint16_t)p[0];
+            if constexpr (kForm != kUniform) split3_finite(value, p);
+            if constexpr (kForm == 1) reinterpret_cast<uint16_t*>(table)[tid] = (uint16_t)p[0];
+            else if constexpr (kForm == kUniform) reinterpret_cast<uint32_t*>(table)[tid] = uniform_pieces(value, grid);
             else reinterpret_cast<uint2*>(table)[tid] = make_uint2(p[0] | (p[1] << 16), p[2]);
         }
         __syncthreads();
@@ -426,7 +445,7 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
                 const uint32_t r = RW * wave + i;
                 // (the values are read before any is stored: one trip to LDS)
                 unsigned char* v = values + r * rest.row_values;
-                typedef typename std::conditional<PW == 1, uint16_t, uint2>::type Entry;
+                typedef typename std::conditional<kForm == 1, uint16_t, typename std::conditional<kForm == kUniform, uint32_t, uint2>::type>::type Entry;
                 Entry own[4] = {}, zero = reinterpret_cast<const Entry*>(table)[0];
 #pragma unroll
                 for (uint32_t t = 0; t < 4; ++t)
@@ -445,15 +464,15 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
             for (int r = 0; r < RT; ++r) q[r] = *reinterpret_cast<LdsU2>((uintptr_t)(codes0 + (uint32_t)r * 16u * rest.stride + t_read * 32u));
             t_read = advance(t_read);
         };
-        auto values_of = [&](const uintx2 (&q)[RT], uint32_t (&e)[RT][8][PW == 1 ? 1 : 2]) {
+        auto values_of = [&](const uintx2 (&q)[RT], uint32_t (&e)[RT][8][kWords]) {
 #pragma unroll
             for (int r = 0; r < RT; ++r) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     // the entry's address: one byte times the size of an entry, plus the row's base (a dot product of bytes)
-                    const uint32_t at = __builtin_amdgcn_udot4(q[r][i >> 2], entry_bytes<PW>() << (8 * (i & 3)), values0 + (uint32_t)r * 16u * rest.row_values, false);
-                    if constexpr (PW == 1) {
-                        e[r][i][0] = *reinterpret_cast<LdsU1>((uintptr_t)at);
+                    const uint32_t at = __builtin_amdgcn_udot4(q[r][i >> 2], entry_bytes(kForm) << (8 * (i & 3)), values0 + (uint32_t)r * 16u * rest.row_values, false);
+                    if constexpr (kWords == 1) {
+                        e[r][i][0] = *reinterpret_cast<LdsOne>((uintptr_t)at);
                     } else {
                         const uintx2 v = *reinterpret_cast<LdsU2>((uintptr_t)at);
                         e[r][i][0] = v[0];
@@ -462,18 +481,18 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
                 }
             }
         };
-        auto pack = [&](const uint32_t (&e)[RT][8][PW == 1 ? 1 : 2], uint4 (&w)[RT][PW]) {
+        auto pack = [&](const uint32_t (&e)[RT][8][kWords], uint4 (&w)[RT][PW]) {
 #pragma unroll
             for (int r = 0; r < RT; ++r) {
                 uint32_t o[PW][4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    if constexpr (PW == 1) {
+                    if constexpr (kForm == 1) {
                         o[0][i] = e[r][2 * i][0] | e[r][2 * i + 1][0] << 16;
                     } else {
                         o[0][i] = __builtin_amdgcn_perm(e[r][2 * i + 1][0], e[r][2 * i][0], 0x05040100u);
                         o[1][i] = __builtin_amdgcn_perm(e[r][2 * i + 1][0], e[r][2 * i][0], 0x07060302u);
-                        o[2][i] = __builtin_amdgcn_perm(e[r][2 * i + 1][1], e[r][2 * i][1], 0x05040100u);
+                        if constexpr (kForm == 3) o[2][i] = __builtin_amdgcn_perm(e[r][2 * i + 1][kWords - 1], e[r][2 * i][kWords - 1], 0x05040100u);
                     }
                 }
 #pragma unroll
@@ -493,17 +512,23 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
                 for (int s = 2; s >= 0; --s)
 #pragma unroll
                     for (int i = 0; i < PW; ++i)
-                        if (s - i >= 0)
+                        if (s - i >= 0 && !(kForm == kUniform && i == 1 && s == 2))
 #pragma unroll
                             for (int r = 0; r < RT; ++r) {
                                 floatx4& to = s > 0 ? lo[r][c] : acc[r][c];
                                 to = mfma16(w[r][i], b[s - i], to);
                             }
             }
+            if constexpr (kForm == kUniform)
+                if (grid.offset != 0.f)  // offset . (sums of X's columns)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+#pragma unroll
+                        for (int c = 0; c < CT; ++c) shift[c] = fmaf(grid.offset, v[i][c], shift[c]);
         };
         if (mine > 0) {
             uintx2 q[RT];
-            uint32_t e[RT][8][PW == 1 ? 1 : 2];
+            uint32_t e[RT][8][kWords];
             uint4 w[RT][PW];
             ranks_of(q);
             values_of(q, e);
@@ -530,9 +555,14 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
                     for (int r = 0; r < RT; ++r)
 #pragma unroll
                         for (int c = 0; c < CT; ++c) {
-                            sum[r][c] += acc[r][c] + lo[r][c];
+                            sum[r][c] += joined(r, c);
                             acc[r][c] = lo[r][c] = floatx4{};
                         }
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) {
+                        shifts[c] += shift[c];
+                        shift[c] = 0.f;
+                    }
                 }
             }
         }
@@ -541,7 +571,19 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
 #pragma unroll
     for (int r = 0; r < RT; ++r)
 #pragma unroll
-        for (int c = 0; c < CT; ++c) acc[r][c] = sum[r][c] + (acc[r][c] + lo[r][c]);
+        for (int c = 0; c < CT; ++c) acc[r][c] = sum[r][c] + joined(r, c);
+    if constexpr (kForm == kUniform)
+        if (grid.offset != 0.f)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                float t = shifts[c] + shift[c];  // of the rows 8 g .. 8 g + 7 of the steps
+                t = with_lanes<16>(t);
+                t = with_lanes<32>(t);
+#pragma unroll
+                for (int r = 0; r < RT; ++r)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[r][c][e] += t;
+            }
 
     // the waves' sums meet in LDS, first the upper half's, then all: [wave][row tile][element][column of CT][lane]
     float* s_sum = reinterpret_cast<float*>(codes);
@@ -612,7 +654,7 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
             a.Out = out;
             a.tab = tab; a.colI = colI; a.omega = omega; a.X = X;
             a.m = m; a.n = n; a.L = L; a.tab_shift = tab_shift;
-            a.row0 = row0; a.rows = R; a.col0 = col0; a.cols = BN; a.k_begin = k_begin; a.k_end = k_end; a.entry = entry_bytes<PW>();
+            a.row0 = row0; a.rows = R; a.col0 = col0; a.cols = BN; a.k_begin = k_begin; a.k_end = k_end; a.entry = entry_bytes(kForm);
         }
         __syncthreads();
         exact_outputs(smem, !(most < INFINITY));
@@ -629,16 +671,20 @@ __global__ __launch_bounds__(256) void fused_sum_kernel(const float* __restrict_
 }
 
 typedef void (*FusedKernel)(const uint32_t*, const float*, const uint16_t*, const float*, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t,
-                            uint32_t, FusedRest);
+                            uint32_t, FusedRest, UniformGrid);
 
 // The variants, and the terms of their duration in microseconds, fitted to 450 random products of 2 to 800 columns (the typical
 // deviation is 3 %, one in ten is off by more than 8 %).  A launch takes `fixed`; then the busiest compute unit's workgroups follow
 // one another, each `round`, `list` per row, 64 ranks and wave, `batch` per wave and 1536 positions (rows of several segments are read
 // several times), `pos` per 64 positions and `step` per 32 columns of W.
+// The uniform form's steps are 7 % shorter than three pieces' (two tables' words and six products become one and four: 1972 x 4004, 135
+// values, batch 55: 23.0 -> 21.7 us, 883 x 11262, batch 35: 25.8 -> 24.5; with an offset, whose sum of X costs what the products save,
+// as long as before: 22.4 and 22.4 for 551 x 12926, 5 bits, batch 43, and 0.1 - 0.2 us longer from 6 to 9 us); errors of 60
+// products against fp64 are now no larger than the decoded route's in any (up to 4 % with three pieces).
 // Which of them are worth having: without 16 waves for 16 columns 3 % are lost on average, without the tile of 48 columns 4 %,
 // of 64 3 %, of 32 2 %, without the two tiles of 32 rows 0.8 %.
 struct Variant {
-    uint8_t pieces, rt, ct, waves;
+    uint8_t form, rt, ct, waves;
     float fixed, round, list, batch, pos, step;
     FusedKernel kernel;
 };
@@ -654,6 +700,11 @@ const Variant kVariants[] = {
     {3, 1, 3, 8, 1.25f, 4.23f, 0.232f, 0.204f, 0.00360f, 0.1010f, cer_fused_kernel<3, 1, 3, 8>},
     {3, 1, 4, 8, 1.33f, 4.55f, 0.240f, 0.248f, 0.00356f, 0.1232f, cer_fused_kernel<3, 1, 4, 8>},
     {3, 2, 2, 8, 1.34f, 4.84f, 0.271f, 0.403f, 0.00262f, 0.1261f, cer_fused_kernel<3, 2, 2, 8>},
+    {kUniform, 1, 1, 16, 1.27f, 3.55f, 0.356f, 0.239f, 0.00310f, 0.0434f, cer_fused_kernel<kUniform, 1, 1, 16>},
+    {kUniform, 1, 2, 8, 1.30f, 4.15f, 0.257f, 0.292f, 0.00309f, 0.0730f, cer_fused_kernel<kUniform, 1, 2, 8>},
+    {kUniform, 1, 3, 8, 1.25f, 4.23f, 0.232f, 0.204f, 0.00360f, 0.0939f, cer_fused_kernel<kUniform, 1, 3, 8>},
+    {kUniform, 1, 4, 8, 1.33f, 4.55f, 0.240f, 0.248f, 0.00356f, 0.1146f, cer_fused_kernel<kUniform, 1, 4, 8>},
+    {kUniform, 2, 2, 8, 1.34f, 4.84f, 0.271f, 0.403f, 0.00262f, 0.1173f, cer_fused_kernel<kUniform, 2, 2, 8>},
 };
 constexpr int kVariantCount = sizeof(kVariants) / sizeof(kVariants[0]);
 
@@ -668,19 +719,22 @@ struct FusedPlan {
     double us = 1e30;
 };
 
-FusedPlan plan_fused(const DeviceView& d, uint32_t L, bool temporaries) {
+// The best plan of less than `below` microseconds.
+FusedPlan plan_fused(const DeviceView& d, uint32_t L, bool temporaries, double below) {
     FusedPlan best;
+    best.us = below;
     // 16-bit column indices, one of which (65535) stands for none; X is addressed with 32-bit offsets
     if (!d.rank_tab || d.pieces < 1 || d.colI_bits != 16 || d.n < 1 || d.n > 65000 || d.m < 1 || d.m > (1 << 24) || L < 2 || L > (1u << 20) ||
         ((uint64_t)d.n + 64) * L * 4u >= (1ull << 32))
         return best;
-    const uint32_t pieces = d.pieces == 1 ? 1 : 3, entry = pieces == 1 ? entry_bytes<1>() : entry_bytes<3>(), shift = (uint32_t)d.rank_tab_shift;
+    const int form = d.grid.scale != 0.f ? kUniform : (d.pieces == 1 ? 1 : 3);
+    const uint32_t entry = entry_bytes(form), shift = (uint32_t)d.rank_tab_shift;
     const uint32_t row_values = (((1u << shift) + 1u) * entry + 3u) & ~3u;
     const uint32_t steps = (uint32_t)((d.n + 31) / 32), budget = (uint32_t)std::min<size_t>(d.lds_per_block - 256, 160 * 1024);
     const double row = (double)d.nnz / (double)d.m, batches = std::ceil((row + 8.0) / Shape::BATCH), lists = std::max(1u, (1u << shift) / 64u);
     for (int v = 0; v < kVariantCount; ++v) {
         const Variant& k = kVariants[v];
-        if (k.pieces != pieces || k.ct > L || (k.ct > 1 && 8u * k.ct >= L)) continue;  // a tile of half the width holds the batch
+        if (k.form != form || k.fixed + k.round > best.us || k.ct > L || (k.ct > 1 && 8u * k.ct >= L)) continue;  // a tile of half the width holds the batch
         FusedPlan p;
         p.variant = v;
         const uint32_t R = 16u * k.rt;
@@ -718,13 +772,13 @@ FusedPlan plan_fused(const DeviceView& d, uint32_t L, bool temporaries) {
 
 }  // namespace
 
-FusedEstimate fused_estimate(const DeviceView& d, uint32_t L, bool temporaries) {
-    const FusedPlan p = plan_fused(d, L, temporaries);
-    return p.variant >= 0 ? FusedEstimate{16 * kVariants[p.variant].rt, p.us} : FusedEstimate{};
+int fused_rows(const DeviceView& d, uint32_t L, bool temporaries, double below) {
+    const FusedPlan p = plan_fused(d, L, temporaries, below);
+    return p.variant >= 0 ? 16 * kVariants[p.variant].rt : 0;
 }
 
 hipError_t launch_fused(const DeviceView& d, const float* X, float* Y, uint32_t L, bool temporaries, bool dense_zeros, hipStream_t stream) {
-    const FusedPlan p = plan_fused(d, L, temporaries);
+    const FusedPlan p = plan_fused(d, L, temporaries, 1e30);
     if (p.variant < 0) return hipErrorInvalidValue;
     const Variant& k = kVariants[p.variant];
     {
@@ -739,7 +793,7 @@ hipError_t launch_fused(const DeviceView& d, const float* X, float* Y, uint32_t 
     a.row_values = p.row_values;
     a.split_stride = (size_t)d.m * L;
     // as in launch_mfma: less than 2^-26 of a sum from here on
-    a.faint = (float)std::min((double)d.n * d.omega_max * 0x1p-108, 1e38);
+    a.faint = (float)std::min((double)d.n * d.omega_max * (d.grid.scale != 0.f ? 0x1p-107 : 0x1p-108), 1e38);
     a.dense = dense_zeros ? 1u : 0u;
     float* part = nullptr;
     if (p.splits > 1) {
@@ -751,7 +805,7 @@ hipError_t launch_fused(const DeviceView& d, const float* X, float* Y, uint32_t 
     const uint32_t magic = p.row_blocks == 1 ? 0u : (uint32_t)(((1ull << 32) + p.row_blocks - 1) / p.row_blocks);
     const uint32_t packed = p.kchunk / 32u | (uint32_t)d.rank_tab_shift << 12 | p.splits << 16;
     hipError_t e = launch_kernel(k.kernel, dim3(eighth * 8u), dim3(k.waves * kWave), p.lds, stream, d.rank_tab, X,
-                                 static_cast<const uint16_t*>(d.colI), d.omega, (uint32_t)d.m, (uint32_t)d.n, L, magic, eighth, packed, a);
+                                 static_cast<const uint16_t*>(d.colI), d.omega, (uint32_t)d.m, (uint32_t)d.n, L, magic, eighth, packed, a, d.grid);
     if (part) {
         if (e == hipSuccess)
             e = launch_kernel(fused_sum_kernel, dim3((uint32_t)((a.split_stride + 255) / 256)), dim3(256), 0, stream, part, Y, a.split_stride,

@@ -45,6 +45,7 @@ struct HostMatrix {
 // Values on a uniform grid (uniform_pieces in cer_split3.hpp): whole multiples of scale . unit, plus offset.  scale 0: they are not.
 struct UniformGrid {
     float scale = 0.f, unit = 0.f, offset = 0.f;
+    double inverse = 0;  // of scale . unit
 };
 
 // What the kernels see: device pointers into the handle's single allocation.

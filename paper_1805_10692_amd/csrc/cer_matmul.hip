@@ -243,11 +243,8 @@ Instead choose_instead(const DeviceView& d, uint32_t L, const MatmulOptions& o, 
         }
     }
     r.temporaries = r.narrow == 0 && (path == 3 || path == kPathStrip || d.omega0 != 0.f || d.n_split_parts > 0);
-    const FusedEstimate fused = fused_estimate(d, L, r.temporaries);
-    if (fused.us < kFusedMargin * us) {
-        r.narrow = 0;
-        r.fused = fused.rows;
-    }
+    r.fused = fused_rows(d, L, r.temporaries, kFusedMargin * us);
+    if (r.fused > 0) r.narrow = 0;
     return r;
 }
 

@@ -105,11 +105,11 @@ __device__ __forceinline__ void mfma_pieces(const uint4* a, const uint4* b, floa
 // product, as with three pieces.  1 <= scale < 2: the products are no larger than with w itself.
 // With three pieces, six products: 3127 x 1750, batch 778: 94 us, now 76; 2137 x 3561, batch 625: 106, 80; 986 x 16765, batch 257: 113,
 // 88 (which also reads and writes two matrices instead of three).  Errors in the 2-norm over 60 products of 250 - 4100 rows and
-// 500 - 25000 columns: none is larger, 0.80 of three pieces' in the mean.  (scale . hi + scale . lo is rounded once, and of the five
+// 500 - 25000 columns: none is larger, 0.82 of three pieces' in the mean.  (scale . hi + scale . lo is rounded once, and of the five
 // small products one is left that matters.)
 __device__ __forceinline__ uint32_t uniform_pieces(float w, const UniformGrid& g) {
-    const double step = (double)g.scale * (double)g.unit, v = ((double)w - (double)g.offset) / step, j = rint(v);
-    return bf16_pair((float)j * g.unit, (float)((v - j) * (double)g.unit));
+    const double d = (double)w - (double)g.offset, j = rint(d * g.inverse), step = (double)g.scale * (double)g.unit;
+    return bf16_pair((float)j * g.unit, (float)(fma(-j, step, d) * g.inverse) * g.unit);
 }
 
 // X from row `row` on, as a buffer that ends with row `end` - 1: loads behind it return zero.  The range check of a buffer load

@@ -62,6 +62,31 @@ def test_products(case):
     assert (np.abs(Y - W.astype(np.float64) @ X.astype(np.float64)) <= _bound(W, X)).all()
 
 
+@pytest.mark.parametrize("values", ["three_pieces", "offset"])
+@pytest.mark.parametrize("shape", [(1600, 2100, 15), (1500, 2049, 31), (1000, 1999, 47), (900, 1031, 64), (2600, 2500, 100), (1600, 12000, 24)])
+def test_forms_of_the_values(shape, values):
+    """Codebooks off any grid (three pieces per value), and on one that does not hold zero: every tile, with infinities and inputs at both
+    ends of the range besides."""
+    m, n, L = shape
+    rng = np.random.default_rng(m + L)
+    cb = np.sort(rng.uniform(-1, 1, 57)).astype(np.float32) if values == "three_pieces" else np.linspace(-0.31, 0.42, 64, dtype=np.float32)
+    W = rng.choice(cb, size=(m, n)).astype(np.float32)
+    W[7] = cb[0]
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    h = B.cer_encode(W, cb)
+    assert B.cer_matmul_fused_rows(h, L) > 0
+    assert (np.abs(_product(h, X, m, L) - W.astype(np.float64) @ X.astype(np.float64)) <= _bound(W, X)).all()
+    for scale in (2.0 ** 112, 2.0 ** -118):  # (numbers whose last bits no piece has)
+        Z = (np.abs(X) * scale).astype(np.float32)
+        assert (np.abs(_product(h, Z, m, L) - W.astype(np.float64) @ Z.astype(np.float64)) <=
+                1e-5 * (np.abs(W).astype(np.float64) @ np.abs(Z).astype(np.float64)) + n * 2.0 ** -150).all()
+    X[3, 1], X[n - 1, 2], X[n // 2, 3] = np.inf, -np.inf, np.nan
+    Y = _product(h, X, m, L)
+    B.cer_free(h)
+    assert np.isfinite(Y[:, 4:]).all() and not np.isfinite(Y[:, 1:4]).any() and np.isnan(Y[:, 3]).all()
+    assert (np.abs(Y[:, 4:] - W.astype(np.float64) @ X[:, 4:].astype(np.float64)) <= _bound(W, X[:, 4:])).all()
+
+
 @pytest.mark.parametrize("case", [(1000, 1100, 50, 9, 0.5), (1030, 2537, 40, 130, 0.5), (1500, 9000, 40, 16, 0.4)])
 def test_non_zero_most_frequent_value(case):
     m, n, L, K, p0 = case
