@@ -294,3 +294,28 @@ def test_sizes_of_every_row_reach_the_scan(fmt):
             assert np.array_equal(B.cer_get_array(hd, which), B.cer_get_array(hh, which)), (m, which)
         B.cer_free(hd)
         B.cer_free(hh)
+
+
+@pytest.mark.parametrize("at", [0, 1, 2, 3])
+@pytest.mark.parametrize("shape", [(1, 3), (5, 4), (7, 1021), (3, 1025), (6, 2050), (2100, 1030)])
+def test_codes_of_rows_at_any_address(shape, at):
+    """Rows that begin at any multiple of four bytes, codes at any byte; what lies around the outputs stays as it is.  Most elements
+    share three values (the copies of the histogram)."""
+    m, n = shape
+    W = wl.dense_weights(m, n, seed=n + at)
+    W[:, n // 3:] = W[:, :1]
+    codes, cb = oq.uniform_quantize(W, 7)
+    wb = torch.full((W.size + 4,), 1e30, dtype=torch.float32, device=_gpu())
+    wb[at:at + W.size] = _to_dev(W).reshape(-1)
+    cd = torch.full((W.size + 4,), 255, dtype=torch.uint8, device=_gpu())
+    qb = torch.full((W.size + 4,), 7.5, dtype=torch.float32, device=_gpu())
+    Wd, first = wb[at:at + W.size], at ^ 1
+    assert B.cer_quantize_uniform(Wd, W.size, 7, cd[first:first + W.size], qb[at:at + W.size]).tobytes() == cb.tobytes()
+    torch.cuda.synchronize()
+    assert np.array_equal(cd[first:first + W.size].cpu().numpy(), codes.reshape(-1))
+    assert qb[at:at + W.size].cpu().numpy().tobytes() == cb[codes].reshape(-1).tobytes()
+    assert (cd[:first] == 255).all() and (cd[first + W.size:] == 255).all() and (qb[:at] == 7.5).all() and (qb[at + W.size:] == 7.5).all()
+    for fmt in ("cer", "cser"):
+        h, _ = B.cer_quantize_encode_device(Wd, m, n, 7, fmt)
+        _compare(h, oracle.encode(cb[codes], cb, fmt))
+        B.cer_free(h)
