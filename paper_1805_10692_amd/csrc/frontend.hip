@@ -107,26 +107,25 @@ __global__ __launch_bounds__(256) void range_kernel(const float* __restrict__ W,
     // the bulk in 16-byte pieces (W is aligned by the caller's allocator or the scalar loop below takes it all)
     const int64_t N4 = ((reinterpret_cast<uintptr_t>(W) & 15u) == 0) ? N / 4 : 0;
     const float4* W4 = reinterpret_cast<const float4*>(W);
-    auto take = [&](const float4& w) {
-        range_take(w.x, lo, hi, bad);
-        range_take(w.y, lo, hi, bad);
-        range_take(w.z, lo, hi, bad);
-        range_take(w.w, lo, hi, bad);
-    };
     int64_t i = tid;
     for (; i + 7 * stride < N4; i += 8 * stride) {
         float4 w[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) w[k] = W4[i + k * stride];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) take(w[k]);
+        for (int k = 0; k < 8; ++k) {
+            range_take(w[k].x, lo, hi, bad);
+            range_take(w[k].y, lo, hi, bad);
+            range_take(w[k].z, lo, hi, bad);
+            range_take(w[k].w, lo, hi, bad);
+        }
     }
-    if (i < N4) {  // up to seven more, on their way together as well (behind the end the last one once more)
-        float4 w[7];
-#pragma unroll
-        for (int k = 0; k < 7; ++k) w[k] = W4[min(i + k * stride, N4 - 1)];
-#pragma unroll
-        for (int k = 0; k < 7; ++k) take(w[k]);
+    for (; i < N4; i += stride) {
+        const float4 w = W4[i];
+        range_take(w.x, lo, hi, bad);
+        range_take(w.y, lo, hi, bad);
+        range_take(w.z, lo, hi, bad);
+        range_take(w.w, lo, hi, bad);
     }
     for (i = N4 * 4 + tid; i < N; i += stride) range_take(W[i], lo, hi, bad);
 #pragma unroll
@@ -206,35 +205,37 @@ __device__ __forceinline__ uint32_t code_of(float w, const CodeCtx& c, bool& mis
     }
 }
 
-// Copies of a row's histogram: lane l counts in copy l % 4.  Weights have a few frequent values -- of 7-bit codes of Laplace weights one
+// Copies of a long row's histogram: lane l counts in copy l % 4.  Weights have a few frequent values -- of 7-bit codes of Laplace weights one
 // in four elements has the first, half of them the first three --, and adds to one address go one after the other: with one copy 4096 x
-// 9216, 7 bits, took 48 us instead of 37 (189 MB: what memory delivers; 8 and 4 bits, where fewer meet, took that all along).  With 16
-// copies rows of 2000 to 4000 elements, at whose end they are added up, took 1 us more.  The copies of a value are 16 banks apart.
+// 9216, 7 bits, took 48 us instead of 37 (189 MB: what memory delivers; 8 and 4 bits, where fewer meet, took that all along).  Shorter
+// rows (`aligned` ones below 4096 elements, others below 1024) keep one: 2836 x 704 11 instead of 13 us, 4096 x 2052 and 2048 x 4096 17
+// and 14 either way.  With 16 copies the sum at a row's end took 1 us more.  The copies of a value are 16 banks apart.
 constexpr uint32_t kHistCopies = 4, kHistPitch = kCodes + 16;
 
-// Each thread takes four consecutive elements per round: one 16-byte load, four codes, one 4-byte store, wherever the row starts (the
-// memory path takes floats and bytes at any address; with singles where a row is not a multiple of four floats
-// 4096 x 2050 took 20 us instead of 18, 4096 x 1501 19.4 instead of 15.3).  Only the last one to three of a row come singly.
+// Each thread takes four consecutive elements per round: one 16-byte load, four codes, one 4-byte store -- kCopies > 1: wherever the row
+// starts, the memory path takes floats and bytes at any address (with singles 4096 x 2050 took 20 us instead of 18, 4096 x 1501 19.4
+// instead of 15.3), and only the last one to three of a row come singly; else where `aligned`.
 typedef float FourFloats __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t FourBytes __attribute__((aligned(1)));
 // kQuant: every workgroup first finishes the min / max reduction from the partial results of range_kernel and lays the
 // K = 2^bits points on the range (Section V-B).  Every operation rounds once, to binary32: step = (max - min) / (K - 1),
 // point_j = min + j.step, the last point is max itself.  A constant matrix has one point.  Workgroup 0 publishes them.
-template <bool kQuant>
+template <bool kQuant, uint32_t kCopies>
 __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W, int64_t total, int64_t rows, int64_t row_len,
                                                     const float4* __restrict__ part, int nparts, int bits,
                                                     FrontState* __restrict__ st, uint8_t* __restrict__ codes,
                                                     uint32_t* __restrict__ cnt, unsigned long long* __restrict__ hist,
-                                                    float* __restrict__ Wq) {
+                                                    float* __restrict__ Wq, int aligned) {
 #pragma clang fp contract(off)
-    __shared__ uint32_t s_hist[kHistCopies][kHistPitch];
+    __shared__ uint32_t s_hist[kCopies][kHistPitch];
     __shared__ float s_val[kCodes];
     __shared__ uint32_t s_hkey[kQuant ? 1 : kHashSlots], s_hpos[kQuant ? 1 : kHashSlots];
     __shared__ float s_lo[4], s_hi[4];
     const uint32_t t = threadIdx.x;
     CodeCtx c;
-    for (uint32_t i = 0; i < kHistCopies; ++i) s_hist[i][t] = 0;
-    uint32_t* const copy = s_hist[t & (kHistCopies - 1)];
+#pragma unroll
+    for (uint32_t i = 0; i < kCopies; ++i) s_hist[i][t] = 0;
+    uint32_t* const copy = s_hist[t & (kCopies - 1)];
     if (kQuant) {
         float lo = INFINITY, hi = -INFINITY, bad = 0.f;
         for (int i = (int)t; i < nparts; i += 256) {
@@ -301,16 +302,17 @@ __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W,
         uint8_t* crow = codes ? codes + r * row_len : nullptr;
         float* qrow = Wq ? Wq + r * row_len : nullptr;
         const int64_t n = min(row_len, total - r * row_len);  // the last row of a flat array may be short
+        const bool any = kCopies > 1 || aligned;  // 16-byte pieces
         // the next round's four elements are requested before this round's are coded
         FourFloats ahead = {0.f, 0.f, 0.f, 0.f};
-        if (4 * (int64_t)t + 4 <= n) ahead = *reinterpret_cast<const FourFloats*>(row + 4 * (int64_t)t);
+        if (any && 4 * (int64_t)t + 4 <= n) ahead = *reinterpret_cast<const FourFloats*>(row + 4 * (int64_t)t);
         for (int64_t j0 = 0; j0 < n; j0 += 1024) {
             const int64_t j = j0 + 4 * (int64_t)t;
             uint32_t code[4] = {0, 0, 0, 0};
             const int valid = (int)max((int64_t)0, min((int64_t)4, n - j));
             const FourFloats w = ahead;
-            if (j + 1024 + 4 <= n) ahead = *reinterpret_cast<const FourFloats*>(row + j + 1024);
-            if (valid == 4) {
+            if (any && j + 1024 + 4 <= n) ahead = *reinterpret_cast<const FourFloats*>(row + j + 1024);
+            if (valid == 4 && any) {
                 code[0] = code_of<kQuant>(w.x, c, missing);
                 code[1] = code_of<kQuant>(w.y, c, missing);
                 code[2] = code_of<kQuant>(w.z, c, missing);
@@ -318,13 +320,14 @@ __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W,
                 if (crow) *reinterpret_cast<FourBytes*>(crow + j) = code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24);
                 if (kQuant && qrow)
                     *reinterpret_cast<FourFloats*>(qrow + j) = FourFloats{s_val[code[0]], s_val[code[1]], s_val[code[2]], s_val[code[3]]};
-            } else if (valid > 0) {
+            } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    if (e >= valid) break;
-                    code[e] = code_of<kQuant>(row[j + e], c, missing);
-                    if (crow) crow[j + e] = (uint8_t)code[e];
-                    if (kQuant && qrow) qrow[j + e] = s_val[code[e]];
+                    if (e < valid) {
+                        code[e] = code_of<kQuant>(row[j + e], c, missing);
+                        if (crow) crow[j + e] = (uint8_t)code[e];
+                        if (kQuant && qrow) qrow[j + e] = s_val[code[e]];
+                    }
                 }
             }
             if (!cnt) continue;  // uniform
@@ -345,12 +348,12 @@ __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W,
         if (cnt) {
             __syncthreads();
             uint32_t sum = 0;
-            if (t < c.K) {
-                uint32_t h[kHistCopies];
+            if (kCopies == 1 || t < c.K) {
+                uint32_t h[kCopies];
 #pragma unroll
-                for (uint32_t i = 0; i < kHistCopies; ++i) h[i] = s_hist[i][t];
+                for (uint32_t i = 0; i < kCopies; ++i) h[i] = s_hist[i][t];
 #pragma unroll
-                for (uint32_t i = 0; i < kHistCopies; ++i) {
+                for (uint32_t i = 0; i < kCopies; ++i) {
                     sum += h[i];
                     s_hist[i][t] = 0;
                 }
@@ -1285,17 +1288,21 @@ struct DeviceBuf {
         if (e_ != hipSuccess) return cer::record_hip_error((int)e_); \
     } while (0)
 
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+
 // Enqueues range (bits > 0) or the caller's codebook, then codes + per-row histograms (cnt != nullptr) over `rows` rows of
 // row_len elements (the last one possibly shorter).  `part`: kRangeParts float4.
 int run_codes(const float* W, int64_t total, int64_t rows, int64_t row_len, const float* codebook, int32_t K, int32_t bits,
               hipStream_t s, FrontState* st_dev, float4* part, uint8_t* codes, uint32_t* cnt, unsigned long long* hist, float* Wq) {
     // workgroups walk several rows where that still leaves eight of them per compute unit: their prologue is shared
     const unsigned blocks = (unsigned)std::min<int64_t>(rows, 2048);
+    const int aligned = row_len % 4 == 0 && aligned16(W) && (!Wq || aligned16(Wq)) && (reinterpret_cast<uintptr_t>(codes) & 3u) == 0;
+    const bool copies = cnt && row_len >= (aligned ? 4096 : 1024);
     if (bits > 0) {
         const int nparts = (int)std::min<int64_t>(kRangeParts, (total + 1023) / 1024);
         HIP_TRY(cer::launch_kernel(range_kernel, dim3(nparts), dim3(256), 0, s, W, total, part, hist, st_dev));
-        HIP_TRY(cer::launch_kernel(codes_kernel<true>, dim3(blocks), dim3(256), 0, s, W, total, rows, row_len, part, nparts, bits,
-                                   st_dev, codes, cnt, hist, Wq));
+        HIP_TRY(cer::launch_kernel(copies ? codes_kernel<true, kHistCopies> : codes_kernel<true, 1>, dim3(blocks), dim3(256), 0, s, W, total, rows, row_len, part, nparts, bits,
+                                   st_dev, codes, cnt, hist, Wq, aligned));
     } else {
         // duplicates and non-finite values are refused
         CodebookArg cb;
@@ -1310,8 +1317,8 @@ int run_codes(const float* W, int64_t total, int64_t rows, int64_t row_len, cons
         if (std::adjacent_find(sorted, sorted + K) != sorted + K) return CER_E_BAD_CODEBOOK;
         cb.K = (uint32_t)K;
         HIP_TRY(cer::launch_kernel(codebook_kernel, dim3(1), dim3(256), 0, s, cb, hist, st_dev));
-        HIP_TRY(cer::launch_kernel(codes_kernel<false>, dim3(blocks), dim3(256), 0, s, W, total, rows, row_len, part, 0, 0, st_dev,
-                                   codes, cnt, hist, (float*)nullptr));
+        HIP_TRY(cer::launch_kernel(copies ? codes_kernel<false, kHistCopies> : codes_kernel<false, 1>, dim3(blocks), dim3(256), 0, s, W, total, rows, row_len, part, 0, 0, st_dev,
+                                   codes, cnt, hist, (float*)nullptr, aligned));
     }
     return CER_OK;
 }

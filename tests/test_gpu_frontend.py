@@ -297,7 +297,7 @@ def test_sizes_of_every_row_reach_the_scan(fmt):
 
 
 @pytest.mark.parametrize("at", [0, 1, 2, 3])
-@pytest.mark.parametrize("shape", [(1, 3), (5, 4), (7, 1021), (3, 1025), (6, 2050), (2100, 1030)])
+@pytest.mark.parametrize("shape", [(1, 3), (5, 4), (7, 1021), (3, 1025), (6, 2050), (5, 4100), (2100, 1030)])
 def test_codes_of_rows_at_any_address(shape, at):
     """Rows that begin at any multiple of four bytes, codes at any byte; what lies around the outputs stays as it is.  Most elements
     share three values (the copies of the histogram)."""
