@@ -76,10 +76,12 @@ def make_workload(name: str):
     raise SystemExit(f"unknown workload {name}")
 
 
-def kernel_name(fmt: str, L: int, path, K: int = 0, n: int = 0, narrow: int = 0) -> str:
+def kernel_name(fmt: str, L: int, path, K: int = 0, n: int = 0, narrow: int = 0, fused: int = 0) -> str:
     """The kernel that dominates a product (cer_matmul_path's numbering for cer / cser).  Batch 1: handles of 2 - 256
-    values whose X fits in LDS (every benchmark configuration) run the rank-table kernel.  narrow: what
-    cer_matmul_narrow_columns says."""
+    values whose X fits in LDS (every benchmark configuration) run the rank-table kernel.  narrow, fused: what
+    cer_matmul_narrow_columns and cer_matmul_fused_rows say."""
+    if fused:
+        return "cer_fused_kernel"
     if narrow:
         return "cer_narrow_kernel"
     if fmt == "csr":
@@ -279,6 +281,7 @@ def run_one(name: str, fmt: str, steps: int, warmup: int, warm: bool, with_cpu: 
         "dense_bytes": 4 * (w.m * w.n + w.n * L + w.m * L),
         "path": None if fmt == "csr" else B.cer_matmul_path_ex(h0, L, opts),
         "narrow_columns": 0 if fmt == "csr" or opts is not None else B.cer_matmul_narrow_columns(h0, L),
+        "fused_rows": 0 if fmt == "csr" or opts is not None else B.cer_matmul_fused_rows(h0, L),
     }
     for h in handles[1:]:
         free(h)
@@ -531,7 +534,7 @@ def main() -> int:
                                      "k_bar", "k_tilde", "cache_state", "path")},
         "roofline": {"bound": "hbm", "achieved": r["algorithmic_GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": r["algorithmic_GBps"] / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_source,
-                     "kernel": kernel_name(args.format, r["L"], r["path"], r["K"], r["n"], r["narrow_columns"]),
+                     "kernel": kernel_name(args.format, r["L"], r["path"], r["K"], r["n"], r["narrow_columns"], r["fused_rows"]),
                      "algorithmic_bytes_per_launch": r["algorithmic_bytes"],
                      "event_us_per_launch": r["event_ms_per_step"] * 1e3},
         "cpu_baseline": r.get("cpu_baseline"),
