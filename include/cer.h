@@ -179,8 +179,9 @@ int cer_trim(void);
  *   3  CER_PATH_DENSE: decode + dense: the matrix is decoded into a stream-ordered temporary and multiplied
  *      on the matrix cores: as one to three bf16 matrices that add up to it exactly (2.m.n bytes each), with
  *      X split into three in the same way, or as fp32 (4.m.n bytes) where a value or an index range rules
- *      that out.  The inputs keep all 24 bits of their significands, products are exact or within 2^-25,
- *      sums are fp32.  Chosen when the estimated time of the gathers (the
+ *      that out (cer_matmul_planes tells).  Values that would take three but are whole multiples of one number, up
+ *      to their rounding and at most 256 of it, are two: the multiple, and what the rounding leaves to 2^-31 of the
+ *      value.  The inputs keep all 24 bits of their significands, products are exact or within 2^-25, sums are fp32.  Chosen when the estimated time of the gathers (the
  *      128-byte lines of X per indexed element and tile, the gather instructions, the walk of the longest
  *      row) exceeds 1.05 times that of the decode and the matrix-core product, for matrices of at least
  *      128 x 256 with one element in ten or more indexed: wide batches of matrices that are not very
@@ -211,12 +212,16 @@ int cer_matmul_narrow_columns(const cer_handle_t* h, int64_t batch);
 
 /* Whether cer_matmul / cser_matmul decode and multiply in one launch for this handle and batch, in place of the kernel that
  * cer_matmul_path reports (whose number stays that of the kernel that serves the batch without it): the rows of W per workgroup, 0
- * where they do not.  The rows' elements are decoded into LDS and multiplied on the matrix cores as in kernel 3, in pieces that add
- * up to the inputs exactly; batches of a few hundred columns, matrices of n <= 65000 and 2 to 256 values with more than 256
+ * where they do not.  The rows' elements are decoded into LDS and multiplied on the matrix cores as in kernel 3, in the same pieces;
+ * batches of a few hundred columns, matrices of n <= 65000 and 2 to 256 values with more than 256
  * columns, where the estimates say so.  Partial sums in a temporary only where the kernel reported has a temporary too.
  * Infinities and NaNs in X count as in the kernel reported.  (cer_matmul_ex with a path, flags or a tile width, and
  * cer_matmul_noalloc, never do it.)  Errors: CER_E_INVALID, CER_E_HIP (no device copy). */
 int cer_matmul_fused_rows(const cer_handle_t* h, int64_t batch);
+
+/* The bf16 matrices as which CER_PATH_DENSE writes the handle's matrix: 1 to 3, or 0 where it does not (fp32 instead).
+ * Errors: CER_E_INVALID, CER_E_HIP (no device copy). */
+int cer_matmul_planes(const cer_handle_t* h);
 
 /*
  * cer_matmul_ex -- cer_matmul / cser_matmul (it accepts handles of both formats) with the caller's

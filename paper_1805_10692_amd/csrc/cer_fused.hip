@@ -249,14 +249,6 @@ __device__ __forceinline__ void split3_8_dot(const float x[8], uint4 out[3]) {
     for (int j = 0; j < 3; ++j) out[j] = make_uint4(p[j][0], p[j][1], p[j][2], p[j][3]);
 }
 
-// The sum of what lanes 16 or 32 apart hold.
-template <int kApart>
-__device__ __forceinline__ float with_lanes(float t) {
-    const uint32_t u = __float_as_uint(t);
-    const auto pair = kApart == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false) : __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __uint_as_float(pair[0]) + __uint_as_float(pair[1]);
-}
-
 // Outputs once more in binary32, for inputs that have no pieces (must) or whose pieces may lose what a faint sum shows; see
 // exact_block in cer_mfma.hip.  dense: the sum over all elements; else, as the gathers have it, over the indexed ones (of the
 // differences from the most frequent value) and that value times the column sum: a zero times an infinity does not count there.
@@ -371,7 +363,6 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
         for (int i = 0; i < 8; ++i) load_columns<CT>(xbuf, xoff[i], v[i]);
     };
     floatx4 sum[RT][CT] = {}, acc[RT][CT] = {}, lo[RT][CT] = {};
-    float shift[CT] = {}, shifts[CT] = {};
     auto joined = [&](int r, int c) {
         floatx4 v = acc[r][c] + lo[r][c];
         if constexpr (kForm == kUniform)
@@ -519,12 +510,6 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
                                 to = mfma16(w[r][i], b[s - i], to);
                             }
             }
-            if constexpr (kForm == kUniform)
-                if (grid.offset != 0.f)  // offset . (sums of X's columns)
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-#pragma unroll
-                        for (int c = 0; c < CT; ++c) shift[c] = fmaf(grid.offset, v[i][c], shift[c]);
         };
         if (mine > 0) {
             uintx2 q[RT];
@@ -558,11 +543,6 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
                             sum[r][c] += joined(r, c);
                             acc[r][c] = lo[r][c] = floatx4{};
                         }
-#pragma unroll
-                    for (int c = 0; c < CT; ++c) {
-                        shifts[c] += shift[c];
-                        shift[c] = 0.f;
-                    }
                 }
             }
         }
@@ -572,18 +552,6 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
     for (int r = 0; r < RT; ++r)
 #pragma unroll
         for (int c = 0; c < CT; ++c) acc[r][c] = sum[r][c] + joined(r, c);
-    if constexpr (kForm == kUniform)
-        if (grid.offset != 0.f)
-#pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                float t = shifts[c] + shift[c];  // of the rows 8 g .. 8 g + 7 of the steps
-                t = with_lanes<16>(t);
-                t = with_lanes<32>(t);
-#pragma unroll
-                for (int r = 0; r < RT; ++r)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[r][c][e] += t;
-            }
 
     // the waves' sums meet in LDS, first the upper half's, then all: [wave][row tile][element][column of CT][lane]
     float* s_sum = reinterpret_cast<float*>(codes);
@@ -678,9 +646,7 @@ typedef void (*FusedKernel)(const uint32_t*, const float*, const uint16_t*, cons
 // one another, each `round`, `list` per row, 64 ranks and wave, `batch` per wave and 1536 positions (rows of several segments are read
 // several times), `pos` per 64 positions and `step` per 32 columns of W.
 // The uniform form's steps are 7 % shorter than three pieces' (two tables' words and six products become one and four: 1972 x 4004, 135
-// values, batch 55: 23.0 -> 21.7 us, 883 x 11262, batch 35: 25.8 -> 24.5; with an offset, whose sum of X costs what the products save,
-// as long as before: 22.4 and 22.4 for 551 x 12926, 5 bits, batch 43, and 0.1 - 0.2 us longer from 6 to 9 us); errors of 60
-// products against fp64 are now no larger than the decoded route's in any (up to 4 % with three pieces).
+// values, batch 55: 23.0 -> 21.7 us, 883 x 11262, batch 35: 25.8 -> 24.5).
 // Which of them are worth having: without 16 waves for 16 columns 3 % are lost on average, without the tile of 48 columns 4 %,
 // of 64 3 %, of 32 2 %, without the two tiles of 32 rows 0.8 %.
 struct Variant {
@@ -793,7 +759,7 @@ hipError_t launch_fused(const DeviceView& d, const float* X, float* Y, uint32_t 
     a.row_values = p.row_values;
     a.split_stride = (size_t)d.m * L;
     // as in launch_mfma: less than 2^-26 of a sum from here on
-    a.faint = (float)std::min((double)d.n * d.omega_max * (d.grid.scale != 0.f ? 0x1p-107 : 0x1p-108), 1e38);
+    a.faint = (float)std::min((double)d.n * d.omega_max * 0x1p-108, 1e38);
     a.dense = dense_zeros ? 1u : 0u;
     float* part = nullptr;
     if (p.splits > 1) {

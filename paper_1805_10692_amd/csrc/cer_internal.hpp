@@ -42,9 +42,9 @@ struct HostMatrix {
     mutable std::mutex fetch_mutex;
 };
 
-// Values on a uniform grid (uniform_pieces in cer_split3.hpp): whole multiples of scale . unit, plus offset.  scale 0: they are not.
+// Values on a uniform grid (uniform_pieces in cer_split3.hpp): whole multiples of scale . unit.  scale 0: they are not.
 struct UniformGrid {
-    float scale = 0.f, unit = 0.f, offset = 0.f;
+    float scale = 0.f, unit = 0.f;
     double inverse = 0;  // of scale . unit
 };
 
@@ -148,6 +148,8 @@ int matmul_path(const DeviceView& v, int64_t L, const MatmulOptions& o);
 int matmul_narrow_columns(const DeviceView& v, int64_t L);
 // Rows of W per workgroup where it runs decode + product in one launch instead (0: it does not).
 int matmul_fused_rows(const DeviceView& v, int64_t L);
+// bf16 matrices of decode + product (0: it multiplies in fp32).
+int matmul_planes(const DeviceView& v);
 // Fills the handle's rank table (if its layout has one) from the format arrays already in device memory; the launch
 // is ordered on `stream`.  A hipError_t value as int.
 int build_rank_table(const DeviceView& v, void* stream);

@@ -292,6 +292,8 @@ int matmul_fused_rows(const DeviceView& d, int64_t L) {
     return L < 2 || L > 0x7FFFFFFFll ? 0 : choose_instead(d, (uint32_t)L, o, choose_batched_path(d, (uint32_t)L, o, false, nullptr)).fused;
 }
 
+int matmul_planes(const DeviceView& d) { return mfma_applicable(d, 2) ? mfma_planes(d) : 0; }
+
 size_t matmul_workspace_floats(const DeviceView& d, int64_t L, const MatmulOptions& o) {
     if (d.m == 0 || L < 1 || L > 0x7FFFFFFFll || d.omega0 == 0.f) return 0;
     if (L == 1 && gemv_sums_x(d, o)) return 0;

@@ -20,17 +20,6 @@ namespace {
 
 constexpr uint32_t kFlush = 256;
 
-// offset . (v[0] + ... + v[7])
-__device__ __forceinline__ float offset_of(const float (&v)[8], float offset) {
-    float a = offset * v[0], b = offset * v[1];
-#pragma unroll
-    for (int i = 2; i < 8; i += 2) {
-        a = fmaf(offset, v[i], a);
-        b = fmaf(offset, v[i + 1], b);
-    }
-    return a + b;
-}
-
 // The two sums of mfma_pieces together.  kUniform: times the scale, with one rounding of the larger.
 template <int kForm>
 __device__ __forceinline__ floatx16 joined(floatx16 hi, floatx16 lo, float scale) {
@@ -48,7 +37,7 @@ struct Block {
     float* Out;
     size_t plane;
     uint32_t m, n, L, pitch, row0, rows, col0, cols, k_begin, k_end;
-    float scale, offset;  // kUniform
+    float scale;  // kUniform
 };
 
 // Products in binary32, the pieces of W added up again: the workgroup's outputs once more, over the ones from the matrix cores.
@@ -57,11 +46,11 @@ struct Block {
 // are mostly those of empty rows: the inputs are looked at first (odd: this thread's inputs had third pieces; without them nothing
 // is lost).  A function of its own, and behind the stores, so that nothing of it is held in registers while the matrix cores work.
 // Small inputs could also be caught on their way: 48 -> 53 us for 512 x 4608, batch 3136.
-// A wave takes tiles of 32 x 32 outputs, 64 or 32 columns of W per step, straight from memory; sums of kFlush columns as below.  Product of
+// A wave takes tiles of 32 x 32 outputs, 64 columns of W per step, straight from memory; sums of kFlush columns as below.  Product of
 // 512 x 4608, batch 3136, one-piece codebook: 68 us, 80 with empty rows, 247 with an infinity in X, 331 with X of about 2^-120.
 template <int kForm>
 __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, bool odd) {
-    constexpr int PW = weight_planes(kForm), NS = kForm == kUniform ? 2 : 4;  // 16 NS columns of W per step
+    constexpr int PW = weight_planes(kForm);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
     if (!__syncthreads_or(must)) {
         bool some = false;
@@ -85,11 +74,11 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
         const uint32_t xoff = (8u * half * b.L + min(c, b.L - 1u)) * 4u;
         floatx16 sum = {}, acc = {};
         uint32_t held = 0;
-        for (uint32_t k0 = b.k_begin; k0 < b.k_end; k0 += 16u * NS) {  // a multiple of 64 columns
-            float x[NS][8];
-            uint4 q[NS][PW];
+        for (uint32_t k0 = b.k_begin; k0 < b.k_end; k0 += 64u) {  // a multiple of 64 columns
+            float x[4][8];
+            uint4 q[4][PW];
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
+            for (int s = 0; s < 4; ++s) {
                 const __amdgpu_buffer_rsrc_t xbuf = x_rows(b.X, b.L, k0 + 16 * s, b.n);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) x[s][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff + i * b.L * 4u, 0, 0));
@@ -97,24 +86,19 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
                 for (int p = 0; p < PW; ++p) q[s][p] = reinterpret_cast<const uint4*>(w + p * b.plane + (size_t)(k0 + 16 * s) * 32)[lane];
             }
 #pragma unroll
-            for (int s = 0; s < NS; ++s)
+            for (int s = 0; s < 4; ++s)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     float v = 0.f;
 #pragma unroll
                     for (int p = PW - 1; p >= 0; --p) {
                         const uint32_t u = i < 4 ? (i < 2 ? q[s][p].x : q[s][p].y) : (i < 6 ? q[s][p].z : q[s][p].w);
-                        v += __uint_as_float(i & 1 ? u & 0xFFFF0000u : u << 16);
-                    }
-                    if constexpr (kForm == kUniform) {
-                        const uint32_t j = i < 4 ? (i < 2 ? q[s][0].x : q[s][0].y) : (i < 6 ? q[s][0].z : q[s][0].w);
-                        const uint32_t e = i < 4 ? (i < 2 ? q[s][1].x : q[s][1].y) : (i < 6 ? q[s][1].z : q[s][1].w);
-                        const double grid = (double)__uint_as_float(i & 1 ? j & 0xFFFF0000u : j << 16) + (double)__uint_as_float(i & 1 ? e & 0xFFFF0000u : e << 16);
-                        v = k0 + 16 * s + 8 * half + i < b.n ? (float)fma((double)b.scale, grid, (double)b.offset) : 0.f;
+                        const float piece = __uint_as_float(i & 1 ? u & 0xFFFF0000u : u << 16);
+                        v = kForm == kUniform ? fmaf(b.scale, piece, v) : v + piece;  // (the codebook's value: a binary32 number)
                     }
                     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v, x[s][i], acc, 0, 0, 0);
                 }
-            if ((held += 16u * NS) >= kFlush) {
+            if ((held += 64u) >= kFlush) {
                 held = 0;
                 sum += acc;
                 acc = floatx16{};
@@ -139,7 +123,7 @@ struct MfmaTile {
     // round each of them to the size of the whole).  Returns a NaN if this thread's share of X holds numbers without pieces, and
     // 0 if none of them has a third piece.
     __device__ __forceinline__ float run(const uint16_t* const (&wtile)[TM], size_t plane, const float* X, uint32_t n, uint32_t L,
-                                         uint32_t xcol, uint32_t k_begin, uint32_t k_end, floatx16 (&sum)[TM][TN], float scale, float offset, float& shift) {
+                                         uint32_t xcol, uint32_t k_begin, uint32_t k_end, floatx16 (&sum)[TM][TN], float scale) {
         const uint32_t tid = threadIdx.x, lane = tid & 63u;
         const uint32_t xc = tid % BN, xg = tid / BN;  // this thread's share of X: rows 8 xg .. 8 xg + 7 of a step, one column
         uint32_t xoff[8];
@@ -162,15 +146,9 @@ struct MfmaTile {
                     for (int p = 0; p < PW; ++p)
                         a[slot][s][i][p] = reinterpret_cast<const uint4*>(wtile[i] + p * plane + (size_t)(k0 + 16 * s) * 32)[lane];
         };
-        float part = 0.f;  // kUniform: offset . (sum of this thread's share of X); `shift` takes it as `sum` does `acc`
-        auto store_x = [&](int slot, int buf, bool last) {
+        auto store_x = [&](int slot, int buf) {
             uint4 o[3];
             odd += split3_8(xr[slot], o);
-            if constexpr (kForm == kUniform) {
-                const float(&v)[8] = xr[slot];
-                const float eight = offset_of(v, offset);
-                part += last ? 0.f : eight;  // behind the end the last step comes once more
-            }
 #pragma unroll
             for (int p = 0; p < 3; ++p) b[buf][p][xg][xc] = o[p];
         };
@@ -188,17 +166,14 @@ struct MfmaTile {
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j) sum[i][j] += joined<kForm>(acc[i][j], lo[i][j], scale);
-            shift += part;
-            part = 0.f;
         };
-        shift = 0.f;
         clear(acc);
         clear(lo);
         clear(sum);
 #pragma unroll
         for (int s = 0; s + 1 < D; ++s) load_x(k_begin + s * BK, s);
         load_w(k_begin, 0);
-        store_x(0, 0, false);
+        store_x(0, 0);
         __syncthreads();
         // D steps per round, so that the register slots are named at compile time; k_end - k_begin is a multiple of D BK
         uint32_t held = 0;
@@ -220,7 +195,7 @@ struct MfmaTile {
 #pragma unroll
                         for (int j = 0; j < TN; ++j) mfma_pieces<kForm>(a[t & 1][s][i], bb[j], acc[i][j], lo[i][j]);
                 }
-                store_x((t + 1) % D, (t + 1) & 1, k0 + (t + 1) * BK >= k_end);
+                store_x((t + 1) % D, (t + 1) & 1);
                 __syncthreads();
             }
             held += D * BK;
@@ -241,7 +216,7 @@ template <int kForm, int TN, int D>
 __global__ __launch_bounds__(256, kForm == 1 ? 2 : 1) void mfma_product_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
     uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, size_t split_stride,
-    float faint, float scale, float offset) {
+    float faint, float scale) {
     using Tile = MfmaTile<kForm, TN, D>;
     __shared__ Tile tile;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -268,24 +243,7 @@ __global__ __launch_bounds__(256, kForm == 1 ? 2 : 1) void mfma_product_kernel(
     for (int i = 0; i < Tile::TM; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * 32 * pitch;
     const uint32_t xcol = min(col0 + tid % Tile::BN, L - 1u);
     floatx16 sum[Tile::TM][TN];
-    float shift;
-    float odd = tile.run(wtile, plane, X, n, L, xcol, k_begin, k_end, sum, scale, offset, shift);
-    if constexpr (kForm == kUniform) {
-        // what 256 / BN threads have of a column; every wave has passed the last step's barrier
-        float* s_shift = reinterpret_cast<float*>(&tile);
-        s_shift[tid] = shift;
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            float t = 0.f;
-#pragma unroll
-            for (uint32_t q = 0; q < 256u / Tile::BN; ++q) t += s_shift[q * Tile::BN + j * 32 + (lane & 31u)];
-#pragma unroll
-            for (int i = 0; i < Tile::TM; ++i)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) sum[i][j][e] += t;
-        }
-    }
+    const float odd = tile.run(wtile, plane, X, n, L, xcol, k_begin, k_end, sum, scale);
 
     // The vote comes before the stores (behind them: 2 us more).
     float least = INFINITY;
@@ -295,10 +253,7 @@ __global__ __launch_bounds__(256, kForm == 1 ? 2 : 1) void mfma_product_kernel(
         for (int e = 0; e < 16; ++e)
             if (row0 + 32 * i + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4) < m)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    least = fminf(least, fabsf(sum[i][j][e]));
-                    if constexpr (kForm == kUniform) odd = fmaf(0.f, sum[i][j][e], odd);  // NaN where a sum is not finite
-                }
+                for (int j = 0; j < TN; ++j) least = fminf(least, fabsf(sum[i][j][e]));
     const int look = __syncthreads_or(odd != odd || least < faint);
 
     // accumulator element e of lane l: row = 8 (e / 4) + 4 (l / 32) + e % 4, column = l % 32
@@ -314,7 +269,7 @@ __global__ __launch_bounds__(256, kForm == 1 ? 2 : 1) void mfma_product_kernel(
             }
         }
     if (look)
-        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, rt * Tile::BM, Tile::BM, col0, Tile::BN, k_begin, k_end, scale, offset}, odd != odd, odd != 0.f);
+        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, rt * Tile::BM, Tile::BM, col0, Tile::BN, k_begin, k_end, scale}, odd != odd, odd != 0.f);
 }
 
 // The same for small problems: 64 x 32 CT outputs per workgroup, the four waves share its columns of W (32 at a time, in turn)
@@ -328,7 +283,7 @@ __global__ __launch_bounds__(256, kForm == 1 ? 2 : 1) void mfma_product_kernel(
 template <int kForm, int CT>
 __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2], size_t plane, const float* X, uint32_t n,
                                                 uint32_t L, uint32_t col0, uint32_t k_begin, uint32_t k_end, floatx16 (&acc)[2][CT],
-                                                float scale, float offset, float (&shift)[CT]) {
+                                                float scale) {
     constexpr int PW = weight_planes(kForm);
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t xoff[8];  // of the wave's first column tile
@@ -364,7 +319,6 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
             for (int j = 0; j < CT; ++j) {
                 uint4 b[3];
                 odd += split3_8(x[slot][s][j], b);
-                if constexpr (kForm == kUniform) shift[j] += offset_of(x[slot][s][j], offset);
 #pragma unroll
                 for (int i = 0; i < 2; ++i) mfma_pieces<kForm>(a[slot][s][i], b, acc[i][j], lo[i][j]);
             }
@@ -375,8 +329,6 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
         for (int j = 0; j < CT; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = lo[i][j][e] = 0.f;
-#pragma unroll
-    for (int j = 0; j < CT; ++j) shift[j] = 0.f;
     uint32_t k0 = k_begin + 32u * wave;
     if (k0 >= k_end) return odd;
     load(k0, 0);
@@ -401,9 +353,8 @@ template <int kForm, int CT>
 __global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUniform) && CT == 1) ? 2 : 1) void mfma_small_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
     uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, size_t split_stride,
-    float faint, float scale, float offset) {
+    float faint, float scale) {
     __shared__ float s_acc[4][2 * CT][16][64];
-    __shared__ float s_shift[kForm == kUniform ? 4 : 1][CT][64];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t items = row_tiles * col_tiles * splits, eighth = (items + 7u) >> 3;
     const uint32_t item = (blockIdx.x & 7u) * eighth + (blockIdx.x >> 3);  // as above
@@ -416,12 +367,7 @@ __global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUnifor
 #pragma unroll
     for (int i = 0; i < 2; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * 32 * pitch;
     floatx16 acc[2][CT];
-    float shift[CT];
-    float odd = mfma_small_run<kForm, CT>(wtile, plane, X, n, L, col0, k_begin, k_end, acc, scale, offset, shift);
-    if constexpr (kForm == kUniform) {
-#pragma unroll
-        for (int j = 0; j < CT; ++j) s_shift[wave][j][lane] = shift[j];
-    }
+    const float odd = mfma_small_run<kForm, CT>(wtile, plane, X, n, L, col0, k_begin, k_end, acc, scale);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -431,22 +377,12 @@ __global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUnifor
     __syncthreads();
     // every wave adds up and stores a quarter of the workgroup's accumulators
     constexpr int PER = 2 * CT * 16 / 4;
-    float y[PER], least = INFINITY, t[CT] = {};
-    if constexpr (kForm == kUniform) {  // what the lanes l and l + 32 of every wave have of a column
-#pragma unroll
-        for (int j = 0; j < CT; ++j) {
-            for (int w = 0; w < 4; ++w) t[j] += s_shift[w][j][lane & 31u] + s_shift[w][j][(lane & 31u) + 32u];
-        }
-    }
+    float y[PER], least = INFINITY;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         const uint32_t f = wave * PER + q, tile = f >> 4, e = f & 15u;
         y[q] = (s_acc[0][tile][e][lane] + s_acc[1][tile][e][lane]) + (s_acc[2][tile][e][lane] + s_acc[3][tile][e][lane]);
-        if constexpr (kForm == kUniform) y[q] += CT == 1 || tile % CT == 0 ? t[0] : t[CT - 1];
-        if (row0 + 32 * (tile / CT) + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4) < m) {
-            least = fminf(least, fabsf(y[q]));
-            if constexpr (kForm == kUniform) odd = fmaf(0.f, y[q], odd);  // as above
-        }
+        if (row0 + 32 * (tile / CT) + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4) < m) least = fminf(least, fabsf(y[q]));
     }
     const int look = __syncthreads_or(odd != odd || least < faint);
 #pragma unroll
@@ -457,7 +393,7 @@ __global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUnifor
         if (r < m && c < L) Out[(size_t)r * L + c] = y[q];
     }
     if (look)
-        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, row0, 64u, col0, 32u * CT, k_begin, k_end, scale, offset}, odd != odd, odd != 0.f);
+        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, row0, 64u, col0, 32u * CT, k_begin, k_end, scale}, odd != odd, odd != 0.f);
 }
 
 __global__ __launch_bounds__(256) void mfma_sum_kernel(const float* __restrict__ part, float* __restrict__ Y, size_t count,
@@ -547,7 +483,7 @@ hipError_t launch_shape(const MfmaShape& s, const uint16_t* W, const float* X, f
     auto* kern = s.small ? (s.BN == 32 ? mfma_small_kernel<kForm, 1> : mfma_small_kernel<kForm, 2>)
                          : (s.BN == 32 ? mfma_product_kernel<kForm, 1, mfma_depth(kForm, 32)> : mfma_product_kernel<kForm, 2, mfma_depth(kForm, 64)>);
     return launch_kernel(kern, grid, dim3(256), 0, stream, W, X, out, m, n, L, pitch, plane, s.row_tiles, s.col_tiles, s.splits,
-                         s.kchunk, count, faint, d.grid.scale, d.grid.offset);
+                         s.kchunk, count, faint, d.grid.scale);
 }
 
 }  // namespace
@@ -575,8 +511,7 @@ hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L
     if (e == hipSuccess) {
         const uint32_t m = (uint32_t)d.m, n = (uint32_t)d.n;
         // An input loses at most half of 2^-133, a sum at most n max|w| 2^-134: less than 2^-26 of itself from here on.
-        // (on a grid the weights less the offset may be twice as large)
-        const float faint = (float)std::min((double)d.n * d.omega_max * (d.grid.scale != 0.f ? 0x1p-107 : 0x1p-108), 1e38);
+        const float faint = (float)std::min((double)d.n * d.omega_max * 0x1p-108, 1e38);
         switch (weight_form(d)) {
             case 1: e = launch_shape<1>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, d, stream); break;
             case 2: e = launch_shape<2>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, d, stream); break;

@@ -98,18 +98,15 @@ __device__ __forceinline__ void mfma_pieces(const uint4* a, const uint4* b, floa
             }
 }
 
-// Weights on a uniform grid, as a uniform quantizer leaves them: w = scale . (unit . j + e) + offset with an integer j of at most
-// eight bits, one bf16 number with the power of two, and what the rounding of the grid's points leaves, |scale . e| <= 2^-16 |w|, as
-// another one.  The product of e needs X's first piece only, so that there are four products instead of six; offset . (sum of X) is
-// added at the end.  What is left out -- e's own rounding, and its products with the further pieces of X -- is below 2^-24 of the
-// product, as with three pieces.  1 <= scale < 2: the products are no larger than with w itself.
-// With three pieces, six products: 3127 x 1750, batch 778: 94 us, now 76; 2137 x 3561, batch 625: 106, 80; 986 x 16765, batch 257: 113,
-// 88 (which also reads and writes two matrices instead of three).  Errors in the 2-norm over 60 products of 250 - 4100 rows and
-// 500 - 25000 columns: none is larger, 0.82 of three pieces' in the mean.  (scale . hi + scale . lo is rounded once, and of the five
-// small products one is left that matters.)
+// Weights on a uniform grid through zero (uniform_grid in cer_capi.cpp): w = scale . (unit . j + e) with an integer j of at most eight
+// bits, one bf16 number with the power of two, and what the rounding of the grid's points leaves, |scale . e| <= 2^-22 |w|, as another
+// one.  The product of e needs X's first piece only, so that there are four products instead of six.  What is left out -- e's own
+// rounding, and its products with the further pieces of X -- is below 2^-29 of the product (2^-25 with three pieces).  1 <= scale < 2:
+// the products are no larger than with w itself.  Errors against fp64 are two thirds of three pieces' in the mean (uniform_grid):
+// scale . hi + scale . lo is rounded once, and of the five small products one is left that matters.
 __device__ __forceinline__ uint32_t uniform_pieces(float w, const UniformGrid& g) {
-    const double d = (double)w - (double)g.offset, j = rint(d * g.inverse), step = (double)g.scale * (double)g.unit;
-    return bf16_pair((float)j * g.unit, (float)(fma(-j, step, d) * g.inverse) * g.unit);
+    const double j = rint((double)w * g.inverse), step = (double)g.scale * (double)g.unit;
+    return bf16_pair((float)j * g.unit, (float)(fma(-j, step, (double)w) * g.inverse) * g.unit);
 }
 
 // X from row `row` on, as a buffer that ends with row `end` - 1: loads behind it return zero.  The range check of a buffer load

@@ -1,5 +1,6 @@
-"""Decode + matrix-core product of codebooks on a uniform grid (kUniform in csrc/cer_split3.hpp): with zero on the grid and off it, with
-values that do not occur, up to 256 steps, and next to values that are too far from the grid, at the edges of the tiles, against fp64."""
+"""Decode + matrix-core product of codebooks on a uniform grid (kUniform in csrc/cer_split3.hpp): with zero on the grid -- two numbers per
+value -- and off it, with values that do not occur, up to 256 steps, next to values that are too far from the grid, and with values
+beside it by what two binary32 roundings leave, at the edges of the tiles, against fp64."""
 import numpy as np
 import pytest
 
@@ -18,6 +19,68 @@ CODEBOOKS = {
     "ternary": np.array([-0.37, 0.0, 0.37], np.float32),
     "off_grid": np.append((_steps[::8] / np.float32(77)).astype(np.float32), np.float32(1.0003)),
 }
+
+
+def _beside(last, units):
+    """last values of a grid of 1/77, every other one moved by so many units of its last place."""
+    v = (np.arange(last + 1) / np.float32(77)).astype(np.float32)
+    u = v.view(np.int32)
+    u[1::2] += units * np.where(np.arange(last + 1)[1::2] % 4 == 1, 1, -1).astype(np.int32)
+    return np.append(v, -v[1:]).astype(np.float32)
+
+
+# values up to 2^-22 of themselves beside the grid: one unit is 2^-23 to 2^-24 of a value, eight are 2^-20 to 2^-21
+CODEBOOKS["beside"] = _beside(100, 1)
+CODEBOOKS["too_far"] = _beside(100, 8)
+PLANES = {"zero": 2, "offset": 3, "one_side": 3, "gaps": 2, "256": 3, "ternary": 2, "off_grid": 3, "beside": 2, "too_far": 3}
+
+
+@pytest.mark.parametrize("name", list(CODEBOOKS))
+def test_form_and_values(name):
+    """Which codebooks are two numbers, and what the pieces of a value add up to: one-hot inputs of 1 and 2 return the matrix bit for bit,
+    those of 24 bits its products to 2^-23 (one rounding, and left-out products below 2^-25), by both kernels that use the pieces."""
+    cb = CODEBOOKS[name]
+    m, n, L = 1600, 300, 100
+    rng = np.random.default_rng(5)
+    W = rng.choice(cb, size=(m, n)).astype(np.float32)
+    h = B.cer_encode(W, cb)
+    assert B.cer_matmul_planes(h) == PLANES[name] and B.cer_matmul_fused_rows(h, L) > 0
+    for first in range(0, n, L):
+        at = np.arange(first, first + L)
+        for full in (False, True):
+            x = rng.uniform(1, 2, L).astype(np.float32) if full else rng.choice([1.0, 2.0], L).astype(np.float32)
+            X = np.zeros((n, L), np.float32)
+            X[at, np.arange(L)] = x
+            Xd, want = torch.from_numpy(X).cuda(), W[:, at].astype(np.float64) * x
+            for opts in (None, B.MatmulOpts(path=B.CER_PATH_DENSE)):
+                Y = torch.full((m, L), float("nan"), device="cuda")
+                B.cer_matmul(h, Xd, Y, L) if opts is None else B.cer_matmul_ex(h, Xd, Y, L, None, opts)
+                torch.cuda.synchronize()
+                got = Y.cpu().numpy().astype(np.float64)
+                assert (np.abs(got - want) <= 2.0 ** -23 * np.abs(want)).all() if full else np.array_equal(got, want)
+    B.cer_free(h)
+
+
+@pytest.mark.parametrize("inputs", ["normal", "relu", "positive", "constant"])
+@pytest.mark.parametrize("name", ["offset", "one_side", "256", "zero", "beside"])
+@pytest.mark.parametrize("L", [60, 512])
+def test_no_less_precise_than_three_pieces(name, inputs, L):
+    """Inputs with a mean, where an offset's share and the integers' sum would cancel.  A value off every grid in a row that is left out
+    makes the codebook three pieces."""
+    m, n = 800, 3000
+    rng = np.random.default_rng(L)
+    cb = CODEBOOKS[name]
+    near = np.argsort(np.abs(cb))[:max(3, len(cb) // 4)]  # weights near zero, as layers have them
+    W = rng.choice(cb[near], size=(m, n)).astype(np.float32)
+    W[1] = rng.choice(cb, size=n)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    X = {"normal": X, "relu": np.maximum(X, 0), "positive": np.abs(X) + np.float32(1), "constant": np.full_like(X, 0.7243)}[inputs]
+    want = (W.astype(np.float64) @ X.astype(np.float64))[1:]
+    scale = (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64))[1:]
+    errors = [np.linalg.norm((_product(W, cb, X)[1:] - want) / scale)]
+    W[0, 0] = np.float32(0.123456789)
+    errors.append(np.linalg.norm((_product(W, np.append(cb, W[0, 0]), X)[1:] - want) / scale))
+    assert errors[0] <= 1.1 * errors[1], errors  # (two numbers: 0.65 of three pieces' in the mean, 1.03 at most)
 
 
 def _product(W, cb, X, fmt="cer"):
