@@ -28,7 +28,9 @@ typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t uintx3 __attribute__((ext_vector_type(3)));
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 
-constexpr uint32_t kFlush = 8;  // steps of a running sum
+// Steps of a running sum; the waves' sums are added up in binary64.  Against the decoded route, 31 products, 2-norm of the error, X
+// normal and cut at 0: at most 0.92 and 0.93 of its error; with eight steps and a binary32 sum up to 1.11 and 1.07.  Same time.
+constexpr uint32_t kFlush = 4;
 using Shape = GemvShape<uint16_t>;  // windows of 512 positions, three per batch
 
 // What a wave needs first comes as the kernel's first fourteen dwords of arguments, which are in registers when it starts;
@@ -590,11 +592,10 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
                 float part[kHalf];
 #pragma unroll
                 for (uint32_t h = 0; h < kHalf; ++h) part[h] = s[h * kPer];
+                double total = part[0];
 #pragma unroll
-                for (uint32_t h = kHalf / 2; h > 0; h >>= 1)
-#pragma unroll
-                    for (uint32_t k = 0; k < h; ++k) part[k] += part[k + h];
-                y[q][c] = part[0];
+                for (uint32_t h = 1; h < kHalf; ++h) total += part[h];
+                y[q][c] = (float)total;
                 if (row < m) {
                     most = fabsf(y[q][c]) < INFINITY ? most : INFINITY;  // (a NaN too)
                     if (!blank) least = fminf(least, fabsf(y[q][c]));

@@ -159,17 +159,39 @@ def test_small_inputs_keep_their_bits(K):
     assert (np.abs(Y - want) <= bound).all()
 
 
-def test_precision():
-    """Not further from fp64 than the gathers (2-norm), whose sums are products in binary32."""
-    for m, n, L, K in ((1000, 2000, 49, 128), (1030, 1537, 40, 65), (900, 9000, 40, 200), (900, 9000, 40, 16)):
-        W, cb, rng = _matrix(m, n, K, 0.5, K // 2, 1)
-        X = rng.standard_normal((n, L)).astype(np.float32)
-        h = B.cer_encode(W, cb)
-        assert B.cer_matmul_fused_rows(h, L) > 0
+# one piece, three (off any grid, and on one beside zero), two numbers
+CODEBOOKS = {"one_piece": (np.arange(16) - 8).astype(np.float32) / np.float32(8), "three_pieces": np.sort(np.random.default_rng(2).uniform(-1, 1, 57)).astype(np.float32),
+             "offset": np.linspace(-0.31, 0.42, 64, dtype=np.float32), "grid": (np.arange(65) - 20).astype(np.float32) / np.float32(65)}
+
+
+SHAPES = [(1600, 2100, 15), (1500, 2049, 31), (1000, 1999, 47), (900, 1031, 64), (2600, 2500, 100), (1725, 1690, 94), (1600, 12000, 24)]
+
+
+# (the two left out are decoded and multiplied in two launches)
+@pytest.mark.parametrize("shape,name", [(s, name) for name in CODEBOOKS for s in SHAPES if (s[2], name) not in ((100, "one_piece"), (24, "one_piece"))])
+def test_precision(shape, name):
+    """Not further from fp64 than the gathers (2-norm), whose sums are products in binary32, nor than the decoded matrix with the same
+    pieces; every output within 1e-6 |W| |X|, which a product without the third piece of either factor (2^-17) exceeds."""
+    m, n, L = shape
+    cb = CODEBOOKS[name]
+    rng = np.random.default_rng(m + L)
+    W = rng.choice(cb, size=(m, n)).astype(np.float32)
+    h = B.cer_encode(W, cb)
+    assert B.cer_matmul_fused_rows(h, L) > 0 and B.cer_matmul_planes(h) == {"one_piece": 1, "grid": 2}.get(name, 3)
+    normal = rng.standard_normal((n, L)).astype(np.float32)
+    for X in (normal, np.maximum(normal, 0), np.abs(normal) + np.float32(1)):
         want = W.astype(np.float64) @ X.astype(np.float64)
-        err = [np.linalg.norm(_product(h, X, m, L, opts=o) - want) for o in (None, B.MatmulOpts(path=B.CER_PATH_GEMM))]
-        B.cer_free(h)
-        assert err[0] <= err[1]
+        Y = _product(h, X, m, L)
+        assert (np.abs(Y - want) <= 0.1 * _bound(W, X)).all()
+        err = [np.linalg.norm(y - want) for y in (Y, *(_product(h, X, m, L, opts=B.MatmulOpts(path=p)) for p in (B.CER_PATH_GEMM, B.CER_PATH_DENSE)))]
+        assert err[0] <= err[1] and err[0] <= err[2], err
+    # one term per output: its error is that of the pieces
+    X = np.zeros((n, L), np.float32)
+    at = rng.integers(0, n, L)
+    X[at, np.arange(L)] = rng.uniform(1, 2, L).astype(np.float32) * np.float32(2.0) ** rng.integers(-100, 100, L)
+    want = W[:, at].astype(np.float64) * X[at, np.arange(L)]
+    assert (np.abs(_product(h, X, m, L) - want) <= 2.0 ** -23 * np.abs(want)).all()
+    B.cer_free(h)
 
 
 def test_replayed_from_a_graph():
