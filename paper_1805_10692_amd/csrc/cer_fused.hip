@@ -41,37 +41,36 @@ struct FusedRest {
     uint32_t seg, stride;        // columns of W per segment (a multiple of 32), bytes per row of them
     uint32_t codes, row_values;  // offset of the bytes in LDS, bytes per row of values
     float faint;
-    uint32_t dense;              // a zero weight times an infinity counts (exact_outputs)
+    uint32_t dense;              // a zero weight times an infinity counts (exact_dense)
 };
-struct FusedArgs : FusedRest {
+struct ExactArgs {
+    float* Out;
     const uint32_t* tab;
     const uint16_t* colI;
     const float* omega;
     const float* X;
-    uint32_t m, n, L, tab_shift;
-    uint32_t row0, rows, col0, cols, k_begin, k_end, entry;  // the workgroup's outputs
+    float scale;
+    uint32_t m, n, L, tab_shift, entry;
+    uint32_t row0, rows, col0, cols, k_begin, k_end;   // the workgroup's outputs
+    uint32_t seg, stride, codes, values, row_values;
 };
 
 // LDS:
 //   [prefix: 256 x 8 bytes]  byte k of entry f = number of set bits of f below bit k
-//   [flags of the votes, cleared at the kernel's start]
-//   [per row, one byte: the row is zero]
-//   [arguments of exact_outputs]
+//   [flags, cleared at the kernel's start, a bit per row: sums that are not finite, faint ones, rows without elements, rows with elements in
+//    this part of W's columns; and: lossy inputs]
+//   [arguments of the functions for those rows]
 //   [per wave: bitmap | counts per word]
 //   [pieces of the codebook's values, by rank]
 //   [per row: values of its groups, in list order (kEntry bytes each): entry 0 = the most frequent value]
 //   [per row: one byte per column of the segment, the entry its element has in that list]; later the waves' sums
-constexpr uint32_t kPrefixBytes = 2048, kBlankAt = kPrefixBytes + 16, kCallAt = kBlankAt + 64, kListsAt = kCallAt + 144;
+constexpr uint32_t kPrefixBytes = 2048, kCallAt = kPrefixBytes + 32, kListsAt = kCallAt + 112;
+constexpr int kOdd = 0, kFaint = 1, kEmpty = 2, kHolds = 3, kLossy = 4;  // the flags
 __host__ __device__ constexpr uint32_t table_at(uint32_t waves) { return kListsAt + waves * 2u * (uint32_t)Shape::NWORDS * 4u; }
 __host__ __device__ constexpr uint32_t entry_bytes(int form) { return form == 1 ? 2u : (form == kUniform ? 4u : 8u); }
 __host__ __device__ __forceinline__ uint32_t values_at(uint32_t waves, uint32_t tab_shift, uint32_t entry) { return table_at(waves) + (entry << tab_shift); }
 
-__device__ __forceinline__ bool vote(unsigned char* smem, int slot, bool mine) {
-    uint32_t* flag = reinterpret_cast<uint32_t*>(smem + kPrefixBytes) + slot;
-    if (__ballot(mine) != 0ull && (threadIdx.x & 63u) == 0u) atomicOr(flag, 1u);
-    __syncthreads();
-    return *flag != 0u;
-}
+__device__ __forceinline__ uint32_t& flag(unsigned char* smem, int which) { return reinterpret_cast<uint32_t*>(smem + kPrefixBytes)[which]; }
 
 __device__ __forceinline__ void request_batch(const uint16_t* colI, uint4 (&q)[Shape::NW], uint32_t b, uint32_t te, uint32_t lane) {
     const uint4* p = reinterpret_cast<const uint4*>(colI + b) + lane;
@@ -224,8 +223,23 @@ __device__ __forceinline__ floatx4 mfma16(uint4 a, uint4 b, floatx4 c) {
 // instruction where unpacking and subtracting take two; exact, as the difference is.  Written out: the compiler's choice is the
 // two-address form, which costs a move for every number of a wide load.  Results of dot products may be read by other
 // instructions three wait states later: the block ends with them.
-__device__ __forceinline__ void remainders8(const uint32_t p[4], const float x[8], float r[8]) {
+// lost: takes the bits of the remainders.  Those of the second pieces have eight significant bits at most, so that the lower half of their
+// binary32 form is zero unless they reach below 2^-133, the smallest bf16 number: then the third piece loses something.  (0.5 to 1 us
+// of 11 to 30; looking at the inputs instead, three instructions per two, took 24 -> 27 us for 4096 x 9216, 15 % indexed, batch 32, and
+// reading them again where a sum is faint 24 -> 37 with a column of zeros in X.)
+__device__ __forceinline__ void remainders8(const uint32_t p[4], const float x[8], float r[8], uint32_t* lost) {
     const uint32_t lo = 0x0000BF80u, hi = 0xBF800000u;  // (-1, 0), (0, -1)
+    if (lost != nullptr) {
+        asm("v_dot2_f32_bf16 %0, %9, %21, %13\n\tv_dot2_f32_bf16 %1, %9, %22, %14\n\t"
+            "v_dot2_f32_bf16 %2, %10, %21, %15\n\tv_dot2_f32_bf16 %3, %10, %22, %16\n\t"
+            "v_dot2_f32_bf16 %4, %11, %21, %17\n\tv_dot2_f32_bf16 %5, %11, %22, %18\n\t"
+            "v_dot2_f32_bf16 %6, %12, %21, %19\n\tv_dot2_f32_bf16 %7, %12, %22, %20\n\t"
+            "v_or3_b32 %8, %8, %0, %1\n\tv_or3_b32 %8, %8, %2, %3\n\tv_or3_b32 %8, %8, %4, %5\n\tv_or3_b32 %8, %8, %6, %7"
+            : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7]), "+&v"(*lost)
+            : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]),
+              "s"(lo), "s"(hi));
+        return;
+    }
     asm("v_dot2_f32_bf16 %0, %8, %20, %12\n\tv_dot2_f32_bf16 %1, %8, %21, %13\n\t"
         "v_dot2_f32_bf16 %2, %9, %20, %14\n\tv_dot2_f32_bf16 %3, %9, %21, %15\n\t"
         "v_dot2_f32_bf16 %4, %10, %20, %16\n\tv_dot2_f32_bf16 %5, %10, %21, %17\n\t"
@@ -236,87 +250,299 @@ __device__ __forceinline__ void remainders8(const uint32_t p[4], const float x[8
 }
 
 // Pieces of eight numbers as split3_8 has them, for numbers that are finite and round to finite bf16 numbers; others leave a NaN.
-__device__ __forceinline__ void split3_8_dot(const float x[8], uint4 out[3]) {
+__device__ __forceinline__ void split3_8_dot(const float x[8], uint4 out[3], uint32_t& lost) {
     float a[8], b[8];
     uint32_t p[3][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) p[0][i] = bf16_pair(x[2 * i], x[2 * i + 1]);
-    remainders8(p[0], x, a);
+    remainders8(p[0], x, a, nullptr);
 #pragma unroll
     for (int i = 0; i < 4; ++i) p[1][i] = bf16_pair(a[2 * i], a[2 * i + 1]);
-    remainders8(p[1], a, b);
+    remainders8(p[1], a, b, &lost);
 #pragma unroll
     for (int i = 0; i < 4; ++i) p[2][i] = bf16_pair(b[2 * i], b[2 * i + 1]);
 #pragma unroll
     for (int j = 0; j < 3; ++j) out[j] = make_uint4(p[j][0], p[j][1], p[j][2], p[j][3]);
 }
 
-// Outputs once more in binary32, for inputs that have no pieces (must) or whose pieces may lose what a faint sum shows; see
-// exact_block in cer_mfma.hip.  dense: the sum over all elements; else, as the gathers have it, over the indexed ones (of the
-// differences from the most frequent value) and that value times the column sum: a zero times an infinity does not count there.
-__device__ __attribute__((noinline)) void exact_outputs(unsigned char* smem, bool must) {
-    const FusedArgs& a = *reinterpret_cast<const FusedArgs*>(smem + kCallAt);
-    const uint32_t row0 = a.row0, rows = a.rows, col0 = a.col0, cols = a.cols, k_begin = a.k_begin, k_end = a.k_end;
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uniform(tid >> 6), threads = blockDim.x;
-    const uint32_t end = min(k_end, a.n);
-    if (!vote(smem, 1, must)) {
+// Pointers of a function that is not inlined: told to be to memory or to LDS, or its loads would be of the kind that may be to either.
+template <typename T>
+__device__ __forceinline__ T* uniform_pointer(T* p) {
+    const uint64_t u = (uint64_t)(uintptr_t)p;
+    return (T*)reinterpret_cast<__attribute__((address_space(1))) T*>((uintptr_t)((uint64_t)uniform((uint32_t)(u >> 32)) << 32 | uniform((uint32_t)u)));
+}
+__device__ __forceinline__ unsigned char* lds_pointer(uint32_t at) {
+    return (unsigned char*)reinterpret_cast<__attribute__((address_space(3))) unsigned char*>((uintptr_t)at);
+}
+
+// What the functions below know of the workgroup's outputs.
+struct ExactCtx {
+    uint32_t lane, wave, waves, m, n, L, row0, col0, cols, k_begin, k_end, shift, last_word;
+    const float* X;
+    const uint32_t* tab;
+    const uint16_t* colI;
+    __device__ __forceinline__ explicit ExactCtx(const unsigned char* smem) {
+        const ExactArgs& a = *reinterpret_cast<const ExactArgs*>(smem + kCallAt);
+        lane = threadIdx.x & 63u; wave = uniform(threadIdx.x >> 6); waves = uniform(blockDim.x / kWave);
+        m = uniform(a.m); n = uniform(a.n); L = uniform(a.L);
+        row0 = uniform(a.row0); col0 = uniform(a.col0); cols = uniform(a.cols); k_begin = uniform(a.k_begin); k_end = uniform(a.k_end);
+        shift = uniform(a.tab_shift); last_word = (1u << shift) - 1u;
+        X = uniform_pointer(a.X); tab = uniform_pointer(a.tab); colI = uniform_pointer(a.colI);
+    }
+};
+
+// A lane's share of the tile's columns where rows of X are loaded four columns per lane: rows of X per load (a power of two), the lane's
+// row and column.  (48 columns: 16 lanes idle.  Columns behind the batch: the next row's, not used for outputs.)
+struct FourColumns {
+    uint32_t lanes, at_once, row, col;
+    __device__ __forceinline__ FourColumns(uint32_t lane, uint32_t cols)
+        : lanes(cols / 4u), at_once(cols == 48u ? 4u : kWave / lanes), row(lane / lanes), col(4u * (lane - row * lanes)) {}
+    __device__ __forceinline__ bool idle() const { return row >= at_once; }
+};
+
+// Of the rows of faint sums, where an input has lost bits: those with elements in these columns of W (or a most frequent value).  The
+// others' sums are zero and lose nothing.
+__device__ __attribute__((noinline)) uint32_t lossy_rows(uint32_t lds, uint32_t faint) {
+    unsigned char* smem = lds_pointer(lds);
+    const ExactCtx a(smem);
+    if (uniform_pointer(reinterpret_cast<const ExactArgs*>(smem + kCallAt)->omega)[0] != 0.f) return faint;
+    for (uint32_t r = a.wave; r < 32u; r += a.waves) {
+        if (((faint >> r) & 1u) == 0u) continue;
+        const uint32_t* record = a.tab + ((size_t)(a.row0 + r) << a.shift);
+        const uint32_t te = uniform(record[a.last_word]);
         bool some = false;
-        for (uint32_t i = tid; i < (end - k_begin) * cols; i += threads)
-            some |= split_lossy(a.X[(size_t)(k_begin + i / cols) * a.L + min(col0 + i % cols, a.L - 1u)]);
-        if (!vote(smem, 2, some)) return;
+        for (uint32_t p = uniform(record[0]); p < te && __ballot(some) == 0ull; p += kWave) {
+            const uint32_t k = a.colI[min(p + a.lane, te - 1u)];
+            some = k >= a.k_begin && k < a.k_end;
+        }
+        if (__ballot(some) != 0ull && a.lane == 0) atomicOr(&flag(smem, kHolds), 1u << r);
     }
-    unsigned char *codes = smem + a.codes, *values = smem + values_at(threads / kWave, a.tab_shift, a.entry);
-    const uint32_t last_word = (1u << a.tab_shift) - 1u;
-    const float omega0 = a.omega[0], base = a.dense ? 0.f : omega0;
-    constexpr uint32_t kOut = 8;  // outputs per thread: at most 4096 of them
-    float sum[kOut] = {};
-    for (uint32_t s0 = k_begin; s0 < end; s0 += a.seg) {
-        const uint32_t len = min(a.seg, end - s0);
-        __syncthreads();
-        for (uint32_t i = tid; i < rows * a.stride / 16u; i += threads) reinterpret_cast<uint4*>(codes)[i] = make_uint4(0, 0, 0, 0);
-        __syncthreads();
-        for (uint32_t r = wave; r < rows && row0 + r < a.m; r += threads / kWave) {
-            uint32_t rec[4] = {};
+    __syncthreads();
+    return faint & uniform(flag(smem, kHolds));
+}
+
+// Rows of the outputs once more, in binary32, as the gathers have them: the sum over the row's indices of (value - most frequent value) . x,
+// and that value times the column sum.  A wave takes a row, 256 positions at a time, and four columns of as many inputs per load as it has
+// lanes for, eight loads in flight.  Calls that repeat every row (all of X near 2^-120, or a column with an infinity): 4096 x 9216, 15 %
+// indexed, batch 32 65 us (25 without, 28 with the gathers), 2048 x 2048, 256 values, batch 16 34 (9.4; 12); with the outputs one per thread,
+// each along W's columns, 1200 and 360.
+__device__ __attribute__((noinline)) void exact_gathered(uint32_t lds, uint32_t rows) {
+    unsigned char* smem = lds_pointer(lds);
+    const ExactCtx a(smem);
+    const ExactArgs& args = *reinterpret_cast<const ExactArgs*>(smem + kCallAt);
+    const FourColumns mine(a.lane, a.cols);
+    const __amdgpu_buffer_rsrc_t xbuf = x_rows(a.X, a.L, 0, a.n);
+    const uint32_t end = min(a.k_end, a.n), columns = (a.col0 + mine.col) * 4u;
+    constexpr uint32_t kNone = 0xFFFFFF00u;  // behind X: loads return zero
+    float* factor = reinterpret_cast<float*>(smem + args.codes);  // by rank
+    double* s_sum = reinterpret_cast<double*>(factor + 256);      // of X's columns: the waves' shares
+    const float* omega = uniform_pointer(args.omega);
+    float* out = uniform_pointer(args.Out);
+    const float omega0 = omega[0];
+    auto lanes_sum = [&](float v) {  // of the lanes that have the same columns
+        double t = 0;
+        for (uint32_t e = 0; e < mine.at_once; ++e) t += __shfl(v, (int)(mine.col / 4u + e * mine.lanes), kWave);
+        return t;
+    };
+    __syncthreads();
+    if (threadIdx.x <= a.last_word) factor[threadIdx.x] = omega[threadIdx.x] - omega0;  // (behind omega's end lies the rest of the handle)
+    float column[4] = {};
+    if (omega0 != 0.f) {
+        float sum[4] = {};
+        constexpr uint32_t kAhead = 8;
+        const uint32_t step = a.waves * mine.at_once;
+        for (uint32_t k = a.k_begin + a.wave * mine.at_once + mine.row; k < end; k += kAhead * step) {
+            uintx4 x[kAhead];
 #pragma unroll
-            for (uint32_t t = 0; t < 4; ++t)
-                if (t <= (last_word >> 6)) rec[t] = a.tab[((size_t)(row0 + r) << a.tab_shift) + min(t * kWave + lane, last_word)];
-            uint4 first[Shape::NW];
-            request_batch(a.colI, first, uniform(rec[0]) & ~((uint32_t)Shape::PPL - 1u), row_end(rec, last_word), lane);
-            uint16_t* ranks = reinterpret_cast<uint16_t*>(values + r * a.row_values);  // the ranks in the values' place
-            if (lane == 0) ranks[0] = 0;
-            scatter_row(a.colI, rec, first, a.tab_shift, smem, wave, s0, a.seg, codes + r * a.stride, lane,
-                        [&](uint32_t at, uint32_t t) { ranks[at] = (uint16_t)(t * kWave + lane + 1u); });
+            for (uint32_t u = 0; u < kAhead; ++u)
+                x[u] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, mine.idle() || k + u * step >= end ? kNone : (k + u * step) * a.L * 4u + columns, 0, 0);
+#pragma unroll
+            for (uint32_t u = 0; u < kAhead; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[e] += __uint_as_float(x[u][e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double t = lanes_sum(sum[e]);
+            if (mine.row == 0) s_sum[a.wave * a.cols + mine.col + e] = t;
         }
         __syncthreads();
-#pragma unroll 1
-        for (uint32_t o = 0; o < kOut; ++o) {
-            const uint32_t i = tid + o * threads;
-            if (i >= rows * cols || row0 + i / cols >= a.m || col0 + i % cols >= a.L) continue;
-            const unsigned char* code = codes + i / cols * a.stride;
-            const uint16_t* ranks = reinterpret_cast<const uint16_t*>(values + i / cols * a.row_values);
-            const float* x = a.X + (size_t)s0 * a.L + col0 + i % cols;
-            float all = 0.f, total = 0.f;
-            for (uint32_t k = 0; k < len;) {
-                float part = 0.f, xs = 0.f;
-                for (const uint32_t stop = min(k + 64u, len); k < stop; ++k) {
-                    const uint32_t r = ranks[code[k]];
-                    const float v = x[(size_t)k * a.L];
-                    if (a.dense || r != 0u) part = fmaf(a.omega[r] - base, v, part);
-                    xs += v;
-                }
-                all += part;
-                total += xs;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            double t = 0;
+            for (uint32_t w = 0; w < a.waves; ++w) t += s_sum[w * a.cols + mine.col + e];
+            column[e] = (float)t;
+        }
+    }
+    __syncthreads();
+    for (uint32_t r = a.wave; r < 32u; r += a.waves) {
+        if (((rows >> r) & 1u) == 0u) continue;
+        const uint32_t* record = a.tab + ((size_t)(a.row0 + r) << a.shift);
+        const uint32_t rs = uniform(record[0]), count = uniform(record[a.last_word]) - rs;
+        uint16_t* ends = reinterpret_cast<uint16_t*>(smem + args.values + r * args.row_values);  // of the row's groups, in its values' place
+        for (uint32_t i = a.lane; i <= a.last_word; i += kWave) ends[i] = (uint16_t)(record[i] - rs);
+        wave_lds_sync();
+        float sum[4] = {};
+        constexpr uint32_t kParts = 4, kAhead = 8;  // of 64 positions; loads
+        for (uint32_t p0 = 0; p0 < count; p0 += kParts * kWave) {
+            uint32_t at[kParts], rank[kParts] = {};  // where the input begins; the last of the row's boundaries at or before the position
+            float f[kParts];
+#pragma unroll
+            for (uint32_t q = 0; q < kParts; ++q) {
+                const uint32_t p = p0 + q * kWave + a.lane, k = p < count ? a.colI[rs + p] : ~0u;
+                at[q] = k >= a.k_begin && k < end ? k * a.L * 4u : kNone;
             }
-            float y = all;
-            if (!a.dense && omega0 != 0.f) y = fmaf(omega0, total, y);
+            for (uint32_t half = (a.last_word + 1u) >> 1; half != 0u; half >>= 1)
 #pragma unroll
-            for (uint32_t q = 0; q < kOut; ++q) sum[q] += q == o ? y : 0.f;
+                for (uint32_t q = 0; q < kParts; ++q)
+                    if (ends[rank[q] + half] <= p0 + q * kWave + a.lane) rank[q] += half;
+#pragma unroll
+            for (uint32_t q = 0; q < kParts; ++q) f[q] = factor[min(rank[q] + 1u, a.last_word)];
+            const uint32_t here = min(count - p0, kParts * kWave);
+            for (uint32_t i0 = 0; i0 < here; i0 += kAhead * mine.at_once) {
+                uintx4 x[kAhead];
+                float w[kAhead];
+#pragma unroll
+                for (uint32_t u = 0; u < kAhead; ++u) {
+                    const uint32_t i = i0 + u * mine.at_once, q = i >> 6;  // (uniform: at_once divides 64)
+                    const int lane = (int)((i + mine.row) & 63u);
+                    const uint32_t from = (uint32_t)__shfl((int)(q == 0u ? at[0] : (q == 1u ? at[1] : (q == 2u ? at[2] : at[3]))), lane, kWave);
+                    w[u] = __shfl(q == 0u ? f[0] : (q == 1u ? f[1] : (q == 2u ? f[2] : f[3])), lane, kWave);
+                    x[u] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, i >= kParts * kWave || mine.idle() || from == kNone ? kNone : from + columns, 0, 0);
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < kAhead; ++u)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[e] = fmaf(w[u], __uint_as_float(x[u][e]), sum[e]);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            double t = lanes_sum(sum[e]);
+            if (omega0 != 0.f) t = fma((double)omega0, (double)column[e], t);
+            const uint32_t c = a.col0 + mine.col + e;
+            if (mine.row == 0 && c < a.L) out[(size_t)(a.row0 + r) * a.L + c] = (float)t;
         }
     }
+}
+
+// The same with every element of W, a zero weight times an infinity too: the rows are decoded once more and multiplied by the fp32 matrix
+// instruction, 32 columns after the other.  1500 x 9000, 16 values, batch 40: 94 us (25 without, 82 with the decoded matrix), 786 x 1952, 32
+// values, batch 113 39 (11; 48); one output per thread: 1970 and 367.
+__device__ __attribute__((noinline)) void exact_dense(uint32_t lds, uint32_t rows) {
+    unsigned char* smem = lds_pointer(lds);
+    const ExactCtx a(smem);
+    const ExactArgs& args = *reinterpret_cast<const ExactArgs*>(smem + kCallAt);
+    const uint32_t tid = threadIdx.x, lane = a.lane, n = a.n, L = a.L, tiles = uniform(args.rows) / 16u, seg = uniform(args.seg), stride = uniform(args.stride);
+    const uint32_t entry = uniform(args.entry), row_values = uniform(args.row_values);
+    const float scale = args.scale;
+    float* out = uniform_pointer(args.Out);
+    unsigned char *codes = smem + uniform(args.codes), *values = smem + uniform(args.values);
+    const uint32_t c16 = lane & 15u, g = lane >> 4;
+    // the value of a weight from its pieces
+    auto value_of = [&](const unsigned char* row, uint32_t code) {
+        if (entry == 2u) return __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(row)[code] << 16);
+        if (entry == 4u) {
+            const uint32_t v = reinterpret_cast<const uint32_t*>(row)[code];
+            return fmaf(scale, __uint_as_float(v << 16), scale * __uint_as_float(v & 0xFFFF0000u));
+        }
+        const uint32_t v = reinterpret_cast<const uint32_t*>(row)[2u * code], w = reinterpret_cast<const uint32_t*>(row)[2u * code + 1u];
+        return __uint_as_float(v << 16) + (__uint_as_float(v & 0xFFFF0000u) + __uint_as_float(w << 16));
+    };
+    const uint32_t col_end = min(a.col0 + a.cols, L);
+#pragma unroll 1
+    for (uint32_t c0 = a.col0; c0 < col_end; c0 += 32u) {
+        floatx4 sum[2][2] = {}, acc[2][2] = {};
+        const bool two = c0 + 16u < col_end;
+        const uint32_t c[2] = {min(c0 + c16, L - 1u), min(c0 + 16u + c16, L - 1u)};
+        uint32_t held = 0;
+#pragma unroll 1
+        for (uint32_t s0 = a.k_begin; s0 < a.k_end; s0 += seg) {
+            const uint32_t steps = (min(a.k_end, s0 + seg) - s0) >> 5;
+            __syncthreads();
+            for (uint32_t i = tid; i < tiles * stride; i += blockDim.x) reinterpret_cast<uint4*>(codes)[i] = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+#pragma unroll 1
+            for (uint32_t r = a.wave; r < 16u * tiles && a.row0 + r < a.m; r += a.waves) {
+                uint32_t rec[4] = {};
 #pragma unroll
-    for (uint32_t q = 0; q < kOut; ++q) {
-        const uint32_t i = tid + q * threads;
-        if (i < rows * cols && row0 + i / cols < a.m && col0 + i % cols < a.L) a.Out[(size_t)(row0 + i / cols) * a.L + col0 + i % cols] = sum[q];
+                for (uint32_t t = 0; t < 4; ++t)
+                    if (t <= (a.last_word >> 6)) rec[t] = a.tab[((size_t)(a.row0 + r) << a.shift) + min(t * kWave + lane, a.last_word)];
+                uint4 first[Shape::NW];
+                request_batch(a.colI, first, uniform(rec[0]) & ~((uint32_t)Shape::PPL - 1u), row_end(rec, a.last_word), lane);
+                scatter_row(a.colI, rec, first, a.shift, smem, a.wave, s0, seg, codes + r * stride, lane, [](uint32_t, uint32_t) {});
+            }
+            __syncthreads();
+            float x[2][2][8];
+            auto load = [&](uint32_t t, float (&v)[2][8]) {
+                const __amdgpu_buffer_rsrc_t xbuf = x_rows(a.X, L, s0 + min(t, steps - 1u) * 32u, n);
+#pragma unroll
+                for (uint32_t j = 0; j < 2; ++j)
+#pragma unroll
+                    for (uint32_t i = 0; i < 8; ++i) v[j][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, ((8u * g + i) * L + c[j]) * 4u, 0, 0));
+            };
+            auto multiply = [&](uint32_t t, const float (&v)[2][8]) {
+#pragma unroll
+                for (uint32_t r = 0; r < 2; ++r) {
+                    if (r >= tiles) break;
+                    const unsigned char* row = values + (16u * r + c16) * row_values;
+                    const uint2 q = *reinterpret_cast<const uint2*>(codes + (16u * r + c16) * stride + 32u * t + 8u * g);
+                    float w[8];
+#pragma unroll
+                    for (uint32_t i = 0; i < 8; ++i) w[i] = value_of(row, ((i < 4 ? q.x : q.y) >> (8 * (i & 3))) & 0xFFu);
+#pragma unroll
+                    for (uint32_t i = 0; i < 8; ++i) {
+                        acc[r][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i], v[0][i], acc[r][0], 0, 0, 0);
+                        if (two) acc[r][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i], v[1][i], acc[r][1], 0, 0, 0);
+                    }
+                }
+                if (++held == 2u) {  // sums of 64 columns
+                    held = 0;
+#pragma unroll
+                    for (uint32_t r = 0; r < 2; ++r)
+#pragma unroll
+                        for (uint32_t j = 0; j < 2; ++j) {
+                            sum[r][j] += acc[r][j];
+                            acc[r][j] = floatx4{};
+                        }
+                }
+            };
+            if (a.wave < steps) load(a.wave, x[0]);
+            for (uint32_t t = a.wave; t < steps; t += 2u * a.waves) {
+                load(t + a.waves, x[1]);
+                multiply(t, x[0]);
+                if (t + a.waves >= steps) break;
+                load(t + 2u * a.waves, x[0]);
+                multiply(t + a.waves, x[1]);
+            }
+        }
+        // the waves' sums meet in LDS as below, 16 columns after the other: [wave][row tile][element][lane]
+        float* s_sum = reinterpret_cast<float*>(codes);
+        const uint32_t half = a.waves / 2u;
+#pragma unroll
+        for (uint32_t j = 0; j < 2; ++j) {
+            if (j == 1 && !two) break;
+#pragma unroll
+            for (int upper = 1; upper >= 0; --upper) {
+                __syncthreads();
+                if ((a.wave >= half) == (upper == 1))
+#pragma unroll
+                    for (uint32_t r = 0; r < 2; ++r)
+#pragma unroll
+                        for (uint32_t e = 0; e < 4; ++e)
+                            if (r < tiles) {
+                                float* at = s_sum + ((a.wave % half * tiles + r) * 4u + e) * kWave + lane;
+                                *at = sum[r][j][e] + acc[r][j][e] + (upper == 1 ? 0.f : *at);
+                            }
+            }
+            __syncthreads();
+            const uint32_t row = 16u * (tid >> 8) + 4u * g + ((tid >> 6) & 3u), col = c0 + 16u * j + c16;
+            if (tid < 256u * tiles && ((rows >> row) & 1u) && a.row0 + row < a.m && col < L) {
+                double total = 0;
+                for (uint32_t w = 0; w < half; ++w) total += s_sum[w * tiles * 256u + tid];
+                out[(size_t)(a.row0 + row) * L + col] = (float)total;
+            }
+        }
     }
 }
 
@@ -365,6 +591,7 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
         for (int i = 0; i < 8; ++i) load_columns<CT>(xbuf, xoff[i], v[i]);
     };
     floatx4 sum[RT][CT] = {}, acc[RT][CT] = {}, lo[RT][CT] = {};
+    uint32_t lost = 0;  // lower half: inputs have bits that their pieces do not reach
     auto joined = [&](int r, int c) {
         floatx4 v = acc[r][c] + lo[r][c];
         if constexpr (kForm == kUniform)
@@ -401,7 +628,7 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
                 }
                 reinterpret_cast<uint2*>(smem)[tid] = make_uint2(lo8, hi8);
             }
-            if (tid < 4u) reinterpret_cast<uint32_t*>(smem + kPrefixBytes)[tid] = 0u;
+            if (tid < 8u) flag(smem, (int)tid) = 0u;
             codes = smem + rest.codes;
             values = smem + values_at(kWaves, tab_shift, entry_bytes(kForm));
             codes0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)codes + c16 * rest.stride + 8u * g;
@@ -445,7 +672,7 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
                     if (t < ntiles) own[t] = reinterpret_cast<const Entry*>(table)[min(t * kWave + lane + 1u, last_word)];
                 if (lane == 0) {
                     reinterpret_cast<Entry*>(v)[0] = zero;
-                    smem[kBlankAt + r] = omega0 == 0.f && uniform(rec[i][0]) == row_end(rec[i], last_word) ? 1 : 0;
+                    if (omega0 == 0.f && uniform(rec[i][0]) == row_end(rec[i], last_word)) atomicOr(&flag(smem, kEmpty), 1u << r);
                 }
                 scatter_row(colI, rec[i], first[i], tab_shift, smem, wave, s0, seg, codes + r * rest.stride, lane,
                             [&](uint32_t at, uint32_t t) { reinterpret_cast<Entry*>(v)[at] = own[t]; });
@@ -499,7 +726,7 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
 #pragma unroll
                 for (int i = 0; i < 8; ++i) xc[i] = v[i][c];
                 uint4 b[3];
-                split3_8_dot(xc, b);
+                split3_8_dot(xc, b, lost);
                 // as mfma_pieces: the small products have a sum of their own
 #pragma unroll
                 for (int s = 2; s >= 0; --s)
@@ -558,6 +785,7 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
     // the waves' sums meet in LDS, first the upper half's, then all: [wave][row tile][element][column of CT][lane]
     float* s_sum = reinterpret_cast<float*>(codes);
     constexpr uint32_t kPer = RT * CT * 4 * kWave;
+    if (__ballot((lost & 0xFFFFu) != 0u) != 0ull && lane == 0) atomicOr(&flag(smem, kLossy), 1u);
     __syncthreads();
     constexpr uint32_t kHalf = kWaves / 2;
     if (wave >= kHalf) {
@@ -580,12 +808,16 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
     __syncthreads();
     // accumulator element e of lane l: row 4 (l / 16) + e, column l % 16
     constexpr uint32_t kVec = RT * 4 * kWave / kThreads > 0 ? RT * 4 * kWave / kThreads : 1;
-    float y[kVec][CT], least = INFINITY, most = 0.f;
+    // What is formed once more: sums that are not finite, subnormal ones (the pieces' products are rounded apart there), and where an input
+    // has lost bits the faint ones, but of rows without elements.
+    const uint32_t empty = flag(smem, kEmpty);
+    const float least = flag(smem, kLossy) != 0u ? rest.faint : 0.f;
+    float y[kVec][CT];
 #pragma unroll
     for (uint32_t q = 0; q < kVec; ++q) {
-        const uint32_t i = tid + q * kThreads, re = i >> 6, row = row0 + 16u * (re >> 2) + 4u * g + (re & 3u);
+        const uint32_t i = tid + q * kThreads, re = i >> 6, r = 16u * (re >> 2) + 4u * g + (re & 3u);
         if (i < RT * 4u * kWave) {
-            const bool blank = smem[kBlankAt + (row - row0)] != 0;  // (its sums are zero and lose nothing)
+            bool odd = false, faint = false;
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
                 const float* s = s_sum + (re * CT + c) * kWave + lane;
@@ -596,18 +828,20 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
 #pragma unroll
                 for (uint32_t h = 1; h < kHalf; ++h) total += part[h];
                 y[q][c] = (float)total;
-                if (row < m) {
-                    most = fabsf(y[q][c]) < INFINITY ? most : INFINITY;  // (a NaN too)
-                    if (!blank) least = fminf(least, fabsf(y[q][c]));
-                }
+                const float size = fabsf(y[q][c]);
+                odd |= !(size < INFINITY);
+                faint |= size < least || (size < 0x1p-126f && size > 0.f);
             }
+            if (odd && row0 + r < m) atomicOr(&flag(smem, kOdd), 1u << r);
+            if (faint && row0 + r < m && !((empty >> r) & 1u)) atomicOr(&flag(smem, kFaint), 1u << r);
         }
     }
+    __syncthreads();
+    const uint32_t odd = flag(smem, kOdd), faint = flag(smem, kFaint);
     float* out = rest.Out + sp * rest.split_stride;
-    const bool look = vote(smem, 0, !(most < INFINITY) || least < rest.faint);
 #pragma unroll
     for (uint32_t q = 0; q < kVec; ++q) {
-        const uint32_t i = tid + q * kThreads, re = i >> 6, row = row0 + 16u * (re >> 2) + 4u * g + (re & 3u);
+        const uint32_t i = tid + q * kThreads, re = i >> 6, r = 16u * (re >> 2) + 4u * g + (re & 3u), row = row0 + r;
         if (i < RT * 4u * kWave && row < m) {
             const uint32_t first = col0 + CT * c16;
 #pragma unroll
@@ -615,18 +849,19 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
                 if (xcol + c >= first) out[(size_t)row * L + xcol + c] = y[q][c];
         }
     }
-    if (look) {
-        static_assert(sizeof(FusedArgs) <= kListsAt - kCallAt, "place of the arguments");
-        if (tid == 0) {  // (a barrier follows in the vote)
-            FusedArgs& a = *reinterpret_cast<FusedArgs*>(smem + kCallAt);
-            static_cast<FusedRest&>(a) = rest;
-            a.Out = out;
-            a.tab = tab; a.colI = colI; a.omega = omega; a.X = X;
-            a.m = m; a.n = n; a.L = L; a.tab_shift = tab_shift;
-            a.row0 = row0; a.rows = R; a.col0 = col0; a.cols = BN; a.k_begin = k_begin; a.k_end = k_end; a.entry = entry_bytes(kForm);
-        }
+    if ((odd | faint) != 0u) {
+        static_assert(sizeof(ExactArgs) <= kListsAt - kCallAt, "place of the arguments");
+        if (tid == 0)
+            *reinterpret_cast<ExactArgs*>(smem + kCallAt) =
+                ExactArgs{out, tab, colI, omega, X, grid.scale, m, n, L, tab_shift, entry_bytes(kForm), row0, R, col0, BN, k_begin, k_end,
+                          rest.seg, rest.stride, rest.codes, values_at(kWaves, tab_shift, entry_bytes(kForm)), rest.row_values};
         __syncthreads();
-        exact_outputs(smem, !(most < INFINITY));
+        const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+        uint32_t rows = uniform(odd);
+        if (faint != 0u) rows |= lossy_rows(lds, uniform(faint));
+        if (rows != 0u) {
+            if (rest.dense) exact_dense(lds, rows); else exact_gathered(lds, rows);
+        }
     }
 }
 

@@ -1,6 +1,6 @@
 """Decode + product in one launch by the library's own choice (csrc/cer_fused.hip): every width of a tile, one and several bf16 pieces,
 one to four tiles of groups, rows of several batches of positions, segments and parts of W's columns, ragged sizes, unaligned X
-and Y, empty and full rows, a non-zero most frequent value, infinities, NaNs and numbers down to the smallest subnormal."""
+and Y, empty and full rows, a non-zero most frequent value, infinities, NaNs and numbers down to the smallest subnormal, and what they cost."""
 import numpy as np
 import pytest
 
@@ -142,21 +142,114 @@ def test_infinities_and_nans(shape, K):
     assert (np.abs(Y - want) <= bound)[:, good].all()
 
 
+def _as_served(W, X, omega0, path):
+    """W.X where X holds infinities: by the gathers, over what a row indexes, and the most frequent value times the column sums; by the
+    decoded matrix, every element."""
+    W, X = W.astype(np.float64), X.astype(np.float64)
+    rows = []
+    with np.errstate(invalid="ignore"):
+        for c in range(X.shape[1]):
+            x = X[:, c]
+            if path == 3:
+                rows.append((W * x).sum(1))
+            else:
+                rows.append(np.where(W == omega0, 0.0, (W - omega0) * x).sum(1) + (omega0 * x.sum() if omega0 != 0 else 0.0))
+    return np.array(rows).T
+
+
+# (m, n, L, K, share of the most frequent value, place of zero in the codebook): every width of a tile, two row tiles, parts of W's columns,
+# segments, one to four words of ranks, both kinds of kernels replaced, batches that end inside four columns
+REPEATED = [(1600, 257, 101, 2, 0.4, 0), (1601, 257, 139, 3, 0.3, 2), (1500, 1600, 15, 256, 0.2, 128), (2048, 2048, 16, 256, 0.5, 128),
+            (1600, 9300, 21, 4, 0.5, 2), (1600, 12000, 40, 32, 0.7, 16), (900, 7000, 30, 200, 0.3, 0), (785, 1000, 33, 64, 0.4, 32),
+            (1000, 2000, 49, 128, 0.5, 64), (900, 20000, 64, 7, 0.6, 0), (800, 3000, 202, 255, 0.2, 127), (3000, 900, 64, 5, 0.5, 2),
+            (1000, 1100, 50, 9, 0.5, 0), (1030, 2537, 42, 130, 0.5, 0), (4096, 9216, 31, 32, 0.85, 16)]
+
+
+@pytest.mark.parametrize("case", REPEATED, ids=[f"{c[0]}x{c[1]}_L{c[2]}_K{c[3]}" for c in REPEATED])
+def test_rows_formed_again(case):
+    """Infinities and NaNs count as in the kernel that is replaced, in every row of the matrix and no other column; what stays finite is as
+    close as ever; so are inputs below 2^-110 in some or all of X."""
+    m, n, L, K, p0, zero = case
+    W, cb, rng = _matrix(m, n, K, p0, zero, m)
+    W[m // 3, : n // 2] = cb[K // 2]     # no indices in the first parts of W's columns
+    h = B.cer_encode(W, cb)
+    omega0, path = B.cer_get_array(h, B.CER_ARRAY_OMEGA)[0], B.cer_matmul_path(h, L)
+    assert B.cer_matmul_fused_rows(h, L) > 0 and path in (1, 3, 5)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    X[n // 3, 1], X[n - 1, L - 1], X[5, 3], X[6, 4], X[7, 4], X[0, 6], X[n // 2, 6] = np.inf, -np.inf, np.nan, np.inf, -np.inf, -np.inf, -np.inf
+    odd = [1, 3, 4, 6, L - 1]
+    Y, want = _product(h, X, m, L), _as_served(W, X[:, odd], float(omega0), path)
+    assert np.array_equal(np.isfinite(Y[:, odd]), np.isfinite(want))
+    bad = ~np.isfinite(want)
+    assert np.array_equal(Y[:, odd][bad], want[bad].astype(np.float32), equal_nan=True)
+    finite = np.where(np.isfinite(X), X, 0)  # (rows that do not index an infinity: the rest of the column)
+    bound = _bound(W, finite) * (1 + (abs(float(omega0)) > 0) * 4) + 1e-5 * abs(float(omega0)) * np.abs(finite).sum(0)
+    close = np.abs(Y - W.astype(np.float64) @ finite.astype(np.float64)) <= bound
+    keep = np.setdiff1d(np.arange(L), odd)
+    assert close[:, keep].all() and close[:, odd][~bad].all()
+    for tiny in (np.ones((1, L), bool), np.arange(L)[None, :] % 2 == 0, rng.random((n, L)) < 0.5):
+        Z = np.where(tiny, np.ldexp(finite, -121), finite).astype(np.float32)
+        bound = 1e-5 * (np.abs(W).astype(np.float64) @ np.abs(Z).astype(np.float64) + abs(float(omega0)) * np.abs(Z.astype(np.float64)).sum(0)) + n * 2.0 ** -150
+        assert (np.abs(_product(h, Z, m, L) - W.astype(np.float64) @ Z.astype(np.float64)) <= bound).all()
+    B.cer_free(h)
+
+
 @pytest.mark.parametrize("K", [16, 33])
-def test_small_inputs_keep_their_bits(K):
-    """Inputs below 2^-110 lose bits in the pieces; sums in which that can show are formed again.  Exact: one group per row, and
-    powers of two as weights of the others, so that the sums of few terms are representable."""
-    m, n, L = 1000, 2000, 49
-    W, cb, rng = _matrix(m, n, K, 0.5, K // 2, K)
-    X = (rng.standard_normal((n, L)) * 2.0 ** rng.integers(-125, -100, size=(1, L))).astype(np.float32)
-    X[:, 7] = rng.integers(-50, 50, size=n) * np.float32(2.0) ** -149
+@pytest.mark.parametrize("shape", [(1000, 2000, 49), (900, 9000, 40), (785, 1000, 33)])
+def test_small_inputs_keep_their_bits(shape, K):
+    """One term per output, inputs of 24 bits from 2^-149 up: products with the powers of two among the weights are exact, whether the pieces
+    reach the bits (from 2^-110 on) or not, and the others are rounded once.  (Zero in the place of a subnormal would be no product.)"""
+    m, n, L = shape
+    rng = np.random.default_rng(K)
+    cb = ((np.arange(K) - K // 2) / np.float32(K)).astype(np.float32)
+    cb[0], cb[-1] = -0.5, 2.0
+    W = rng.choice(cb, size=(m, n), p=np.where(cb == 0, 0.3, 0.7 / (K - 1))).astype(np.float32)
     h = B.cer_encode(W, cb)
     assert B.cer_matmul_fused_rows(h, L) > 0
-    Y = _product(h, X, m, L)
+    power = (W == -0.5) | (W == 2.0) | (W == 0)
+    for exponents in (np.arange(-149, -125), np.arange(-125, -109), np.arange(-110, -101)):
+        X, at = np.zeros((n, L), np.float32), rng.integers(0, n, L)
+        x = np.ldexp(rng.integers(1 << 23, 1 << 24, L).astype(np.float64), rng.choice(exponents, L) - 23).astype(np.float32)
+        X[at, np.arange(L)] = np.where(x == 0, np.float32(2.0) ** -149, x)
+        Y = _product(h, X, m, L)
+        want = W[:, at].astype(np.float64) * X[at, np.arange(L)]
+        exact = power[:, at] & (want.astype(np.float32) == want)
+        assert exact.any() and (want[exact] != 0).any() and np.array_equal(Y[exact], want[exact].astype(np.float32))
+        # (a zero: from pieces whose products are below 2^-150 each, three of them at most)
+        assert (np.abs(Y - want) <= 2.0 ** -23 * np.abs(want) + np.where(Y == 0, 3, 1) * 2.0 ** -150).all()
     B.cer_free(h)
-    want = W.astype(np.float64) @ X.astype(np.float64)
-    bound = 1e-5 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64)) + n * 2.0 ** -149  # every product may be subnormal
-    assert (np.abs(Y - want) <= bound).all()
+
+
+def _microseconds(h, X, Y, L):
+    best = float("inf")
+    for rep in range(6):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        for _ in range(20):
+            B.cer_matmul(h, X, Y, L)
+        end.record()
+        torch.cuda.synchronize()
+        best = min(best, begin.elapsed_time(end) * 50) if rep else best
+    return best
+
+
+@pytest.mark.parametrize("shape", [(4096, 9216, 32, 32, 0.85), (2048, 2048, 16, 256, 0.5), (1000, 12000, 30, 16, 0.5), (1972, 4004, 55, 135, 0.5)])
+def test_zeros_cost_nothing_and_odd_inputs_little(shape):
+    """Outputs that are zero -- a batch filled up, few elements behind an activation, sums that cancel -- take as long as others (3 to 4 times
+    as long where the inputs are looked at again), all rows with a NaN or with inputs below 2^-110 some kernels' time (1.5 to 5.5 times the
+    call; 40 to 70 times with an output per thread)."""
+    m, n, L, K, p0 = shape
+    W, cb, rng = _matrix(m, n, K, p0, K // 2, 1)
+    h = B.cer_encode(W, cb)
+    assert B.cer_matmul_fused_rows(h, L) > 0
+    X, Y = torch.from_numpy(rng.standard_normal((n, L)).astype(np.float32)).cuda(), torch.empty((m, L), device="cuda")
+    filled, cancel, tiny, nan = X.clone(), torch.sign(X), X * 2.0 ** -120, X.clone()
+    filled[:, L // 2:] = 0
+    nan[n // 2, 1] = float("nan")
+    base = _microseconds(h, X, Y, L)
+    for Z, most in ((filled, 1.5), (cancel, 1.5), (tiny, 12), (nan, 12)):
+        assert _microseconds(h, Z, Y, L) < most * base
+    B.cer_free(h)
 
 
 # one piece, three (off any grid, and on one beside zero), two numbers
