@@ -442,6 +442,12 @@ int cer_quantize_encode_device(const float* W_dev, int64_t m, int64_t n, int32_t
                                void* stream, float* codebook_out, int32_t* K_out, cer_handle_t** out);
 int cer_decode_device(const cer_handle_t* h, float* W_dev_out, void* stream);
 
+/* Which of its two kernels the device front-end writes the arrays with, given the handle's matrix and a codebook of K values: 1 where
+ * it sorts rows in LDS (half or more of the elements indexed, 16-bit column indices, the longest row's indices and 32 counters per
+ * value within 64 KiB -- rows of up to about 64000 columns --, where it is estimated to be ahead), else 0.
+ * Errors: CER_E_INVALID, CER_E_HIP (no device copy). */
+int cer_encode_sorts_rows(const cer_handle_t* h, int32_t K);
+
 /*
  * cer_stream_copy -- plain device-to-device copy of `bytes` bytes (rounded down to a multiple of
  * 16; both pointers 16-byte aligned) by a simple HIP kernel.  A measurement aid: a kernel of

@@ -42,7 +42,7 @@ EXPORTS = [
     "csr_clone_device", "csr_free", "cer_cost_model", "csr_cost_model", "dense_cost_model",
     "cer_encode_device", "cer_quantize_uniform", "cer_quantize_encode_device", "cer_matmul_path", "cer_stream_read",
     "cer_decode_device", "cer_trim", "cer_matmul_ex", "cer_matmul_path_ex", "cer_matmul_noalloc", "cer_prepare_strips",
-    "cer_matmul_narrow_columns", "cer_matmul_fused_rows", "cer_matmul_planes",
+    "cer_matmul_narrow_columns", "cer_matmul_fused_rows", "cer_matmul_planes", "cer_encode_sorts_rows",
 ]
 
 CER_FORMAT_CER, CER_FORMAT_CSER = 0, 1
@@ -165,6 +165,8 @@ def lib() -> ctypes.CDLL:
         L.cer_matmul_narrow_columns.argtypes = [vp, i64]
         L.cer_matmul_fused_rows.restype = ctypes.c_int
         L.cer_matmul_fused_rows.argtypes = [vp, i64]
+        L.cer_encode_sorts_rows.restype = ctypes.c_int
+        L.cer_encode_sorts_rows.argtypes = [vp, i32]
         L.cer_matmul_planes.restype = ctypes.c_int
         L.cer_matmul_planes.argtypes = [vp]
         L.cer_prepare_strips.restype = ctypes.c_int
@@ -338,6 +340,14 @@ def cer_matmul_fused_rows(h: Handle, batch: int) -> int:
     if rc < 0:
         _check(rc, "cer_matmul_fused_rows")
     return rc
+
+
+def cer_encode_sorts_rows(h: Handle, K: int) -> bool:
+    """Whether the device encoder sorts the rows of the handle's matrix in LDS, with a codebook of K values."""
+    rc = lib().cer_encode_sorts_rows(h.ptr, K)
+    if rc < 0:
+        _check(rc, "cer_encode_sorts_rows")
+    return bool(rc)
 
 
 def cer_matmul_planes(h: Handle) -> int:

@@ -867,6 +867,12 @@ int cer_matmul_fused_rows(const cer_handle_t* h, int64_t batch) {
     return cer::matmul_fused_rows(h->view, batch);
 }
 
+int cer_encode_sorts_rows(const cer_handle_t* h, int32_t K) {
+    if (!h || K < 1 || K > 256) return CER_E_INVALID;
+    if (h->device < 0 || !h->d_base) return CER_E_HIP;
+    return cer::encode_sorts_rows(h->view, K) ? 1 : 0;
+}
+
 int cer_matmul_planes(const cer_handle_t* h) {
     if (!h) return CER_E_INVALID;
     if (h->device < 0 || !h->d_base) return CER_E_HIP;

@@ -160,6 +160,8 @@ int launch_stream_read(const void* src, int64_t bytes, void* sink, void* stream)
 // Device front-end (frontend.hip): W_dev holds codebook values, or (bits > 0) unquantized weights.
 int encode_device(const float* W_dev, int64_t m, int64_t n, const float* codebook, int32_t K, int32_t bits, bool cser,
                   void* stream, float* codebook_out, int32_t* K_out, cer_matrix** out);
+// Whether encode_device, given the matrix of such a handle and a codebook of K values, sorts its rows in LDS.
+bool encode_sorts_rows(const DeviceView& v, int32_t K);
 int decode_device(const DeviceView& v, float* W_dev, void* stream);
 // The same as bf16 matrices (v.pieces of them, or the two of a uniform grid), `plane` elements apart, in the operand order of the matrix cores: 32 x 16 tiles,
 // [row / 32][column / 16][column / 8 % 2][row % 32][column % 8], columns n .. pitch - 1 zero (pitch: a multiple of 16), rows

@@ -674,7 +674,9 @@ __device__ __forceinline__ void emit_row_pointers(int64_t r, const uint32_t* __r
 // 4000) and 31 KiB, five of them on a compute unit: 60 us for 4096, against 69 with emit_kernel; bound by the LDS, which takes 14 clocks
 // per placed column and wave, and by the phases of five waves.  Where all rows run at once the gain is larger: 300 x 9000 115 -> 89 us.
 constexpr uint32_t kRowCounters = 32;  // words of counters per codebook position
-constexpr int64_t kSortedColumns = 64512;  // 64 runs of a multiple of 16 columns: below 65536, so that slots fit 16 bits
+// 64 runs of a multiple of 16 columns: below 65536, so that slots fit 16 bits.  Half of a row's columns have to fit 64 KiB with the
+// counters (sorted_lds), which ends at about 64000 columns already.
+constexpr int64_t kSortedColumns = 64512;
 inline uint32_t emit_stage_bytes(uint32_t longest) { return ((longest * 2u + 16u + 15u) & ~15u) + 256u; }
 
 __global__ __launch_bounds__(64) void emit_sorted_kernel(const uint8_t* __restrict__ codes, const uint32_t* __restrict__ cnt,
@@ -1389,6 +1391,8 @@ int flags_to_error(uint32_t flags) {
     return CER_OK;
 }
 
+bool mostly_implicit(int64_t nnz, int64_t m, int64_t n) { return (double)nnz * 2.0 < (double)m * (double)n; }
+
 // Whether emit_sorted_kernel is expected to be ahead, for matrices of which half or more is indexed (the others are packed before
 // they are sorted).  Clocks: a row sorted in LDS takes 125 per 64 columns, 60 per codebook position and 10000 (its start, the pointers,
 // the way out), and its LDS limits how many of them a compute unit holds; emit_kernel takes 800 per 64 columns of a row, one after
@@ -1403,15 +1407,20 @@ bool sorted_rows_pay(int64_t m, int64_t n, uint32_t positions, size_t lds) {
     return rounds * (125.0 * columns + 60.0 * positions + 10000.0) < std::max(800.0 * columns, 72.0 * columns * share) + 6000.0;
 }
 
+// LDS per row of emit_sorted_kernel, 0 where emit_kernel serves.  longest: indexed elements of the longest row, sparse: fewer than half of
+// all elements are indexed.
+size_t sorted_lds(int64_t m, int64_t n, uint32_t positions, uint32_t longest, bool sparse) {
+    const size_t lds = emit_stage_bytes(longest) + (size_t)((positions + 7u) & ~7u) * (kRowCounters + 1u) * 4u;
+    return !sparse && n >= 1024 && n <= kSortedColumns && lds <= 64 * 1024 && sorted_rows_pay(m, n, positions, lds) ? lds : 0;
+}
+
 template <typename ColT>
 hipError_t launch_emit(hipStream_t s, const uint8_t* codes, const uint32_t* cnt, const uint2* rowStart, const FrontState* st,
                        int64_t m, int64_t n, int cser, int sparse, const EmitTarget& to, FrontResult* out) {
     if constexpr (sizeof(ColT) == 2) {
-        const uint32_t stage = emit_stage_bytes(out->max_row_nnz), eights = (out->K + 7u) & ~7u;
-        const size_t lds = stage + (size_t)eights * (kRowCounters + 1u) * 4u;
-        if (!sparse && n >= 1024 && n <= kSortedColumns && lds <= 64 * 1024 && sorted_rows_pay(m, n, out->K, lds))
+        if (const size_t lds = sorted_lds(m, n, out->K, out->max_row_nnz, sparse != 0))
             return cer::launch_kernel(emit_sorted_kernel, dim3((unsigned)m + 1u), dim3(64), lds, s, codes, cnt, rowStart, st, m, (uint32_t)n, cser,
-                                      out->K, stage, to, out);
+                                      out->K, emit_stage_bytes(out->max_row_nnz), to, out);
     }
     // rank < K <= 256, so OmegaI is always one byte wide here
     return cer::launch_kernel(emit_kernel<ColT, uint8_t>, dim3((unsigned)((m + 3) / 4 + 1)), dim3(256), 0, s, codes, cnt, rowStart,
@@ -1528,6 +1537,10 @@ int quantize_device(const float* W, int64_t count, int32_t bits, uint8_t* codes,
     return CER_OK;
 }
 
+bool encode_sorts_rows(const DeviceView& v, int32_t K) {
+    return v.colI_bits == 16 && sorted_lds(v.m, v.n, (uint32_t)K, v.longest_row, mostly_implicit(v.nnz, v.m, v.n)) != 0;
+}
+
 int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, int32_t K, int32_t bits, bool cser,
                   void* stream, float* codebook_out, int32_t* K_out, cer_matrix** out) {
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1621,7 +1634,7 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     gap(l.off_tab + (l.tab_shift ? ((size_t)m << l.tab_shift) * 4 : 0), l.total);
     const int cs = cser ? 1 : 0;
     // with fewer than half of the elements indexed the emitter packs them in LDS before it scatters them
-    const int sp = (double)h.nnz * 2.0 < (double)m * (double)n ? 1 : 0;
+    const int sp = mostly_implicit(h.nnz, m, n) ? 1 : 0;
     hipError_t e = hipSuccess;
     switch (hnd->host->colI.bits) {
         case 8: e = launch_emit<uint8_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to, box.p); break;
