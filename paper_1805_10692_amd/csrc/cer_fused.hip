@@ -880,7 +880,7 @@ typedef void (*FusedKernel)(const uint32_t*, const float*, const uint16_t*, cons
 // The variants, and the terms of their duration in microseconds, fitted to 450 random products of 2 to 800 columns (the typical
 // deviation is 3 %, one in ten is off by more than 8 %).  A launch takes `fixed`; then the busiest compute unit's workgroups follow
 // one another, each `round`, `list` per row, 64 ranks and wave, `batch` per wave and 1536 positions (rows of several segments are read
-// several times), `pos` per 64 positions and `step` per 32 columns of W (3 % more than fitted: the look at lost bits).
+// several times), `pos` per 64 positions and `step` per 32 columns of W.
 // The uniform form's steps are 7 % shorter than three pieces' (two tables' words and six products become one and four: 1972 x 4004, 135
 // values, batch 55: 23.0 -> 21.7 us, 883 x 11262, batch 35: 25.8 -> 24.5).
 // Which of them are worth having: without 16 waves for 16 columns 3 % are lost on average, without the tile of 48 columns 4 %,
@@ -891,22 +891,22 @@ struct Variant {
     FusedKernel kernel;
 };
 const Variant kVariants[] = {
-    {1, 1, 1, 16, 1.11f, 3.74f, 0.404f, 0.260f, 0.00290f, 0.0354f, cer_fused_kernel<1, 1, 1, 16>},
-    {1, 1, 2, 16, 1.38f, 4.77f, 0.212f, 0.364f, 0.00232f, 0.0659f, cer_fused_kernel<1, 1, 2, 16>},
-    {1, 1, 3, 8, 1.46f, 4.13f, 0.216f, 0.114f, 0.00409f, 0.0840f, cer_fused_kernel<1, 1, 3, 8>},
-    {1, 1, 4, 8, 1.35f, 4.75f, 0.159f, 0.227f, 0.00360f, 0.1006f, cer_fused_kernel<1, 1, 4, 8>},
-    {1, 2, 2, 8, 1.88f, 5.47f, 0.231f, 0.154f, 0.00401f, 0.0973f, cer_fused_kernel<1, 2, 2, 8>},
-    {1, 2, 4, 8, 1.73f, 5.94f, 0.250f, 0.178f, 0.00407f, 0.1381f, cer_fused_kernel<1, 2, 4, 8>},
-    {3, 1, 1, 16, 1.27f, 3.55f, 0.356f, 0.239f, 0.00310f, 0.0481f, cer_fused_kernel<3, 1, 1, 16>},
-    {3, 1, 2, 8, 1.30f, 4.15f, 0.257f, 0.292f, 0.00309f, 0.0809f, cer_fused_kernel<3, 1, 2, 8>},
-    {3, 1, 3, 8, 1.25f, 4.23f, 0.232f, 0.204f, 0.00360f, 0.1040f, cer_fused_kernel<3, 1, 3, 8>},
-    {3, 1, 4, 8, 1.33f, 4.55f, 0.240f, 0.248f, 0.00356f, 0.1269f, cer_fused_kernel<3, 1, 4, 8>},
-    {3, 2, 2, 8, 1.34f, 4.84f, 0.271f, 0.403f, 0.00262f, 0.1299f, cer_fused_kernel<3, 2, 2, 8>},
-    {kUniform, 1, 1, 16, 1.27f, 3.55f, 0.356f, 0.239f, 0.00310f, 0.0447f, cer_fused_kernel<kUniform, 1, 1, 16>},
-    {kUniform, 1, 2, 8, 1.30f, 4.15f, 0.257f, 0.292f, 0.00309f, 0.0752f, cer_fused_kernel<kUniform, 1, 2, 8>},
-    {kUniform, 1, 3, 8, 1.25f, 4.23f, 0.232f, 0.204f, 0.00360f, 0.0967f, cer_fused_kernel<kUniform, 1, 3, 8>},
-    {kUniform, 1, 4, 8, 1.33f, 4.55f, 0.240f, 0.248f, 0.00356f, 0.1180f, cer_fused_kernel<kUniform, 1, 4, 8>},
-    {kUniform, 2, 2, 8, 1.34f, 4.84f, 0.271f, 0.403f, 0.00262f, 0.1208f, cer_fused_kernel<kUniform, 2, 2, 8>},
+    {1, 1, 1, 16, 1.11f, 3.74f, 0.404f, 0.260f, 0.00290f, 0.0344f, cer_fused_kernel<1, 1, 1, 16>},
+    {1, 1, 2, 16, 1.38f, 4.77f, 0.212f, 0.364f, 0.00232f, 0.0640f, cer_fused_kernel<1, 1, 2, 16>},
+    {1, 1, 3, 8, 1.46f, 4.13f, 0.216f, 0.114f, 0.00409f, 0.0816f, cer_fused_kernel<1, 1, 3, 8>},
+    {1, 1, 4, 8, 1.35f, 4.75f, 0.159f, 0.227f, 0.00360f, 0.0977f, cer_fused_kernel<1, 1, 4, 8>},
+    {1, 2, 2, 8, 1.88f, 5.47f, 0.231f, 0.154f, 0.00401f, 0.0945f, cer_fused_kernel<1, 2, 2, 8>},
+    {1, 2, 4, 8, 1.73f, 5.94f, 0.250f, 0.178f, 0.00407f, 0.1341f, cer_fused_kernel<1, 2, 4, 8>},
+    {3, 1, 1, 16, 1.27f, 3.55f, 0.356f, 0.239f, 0.00310f, 0.0467f, cer_fused_kernel<3, 1, 1, 16>},
+    {3, 1, 2, 8, 1.30f, 4.15f, 0.257f, 0.292f, 0.00309f, 0.0785f, cer_fused_kernel<3, 1, 2, 8>},
+    {3, 1, 3, 8, 1.25f, 4.23f, 0.232f, 0.204f, 0.00360f, 0.1010f, cer_fused_kernel<3, 1, 3, 8>},
+    {3, 1, 4, 8, 1.33f, 4.55f, 0.240f, 0.248f, 0.00356f, 0.1232f, cer_fused_kernel<3, 1, 4, 8>},
+    {3, 2, 2, 8, 1.34f, 4.84f, 0.271f, 0.403f, 0.00262f, 0.1261f, cer_fused_kernel<3, 2, 2, 8>},
+    {kUniform, 1, 1, 16, 1.27f, 3.55f, 0.356f, 0.239f, 0.00310f, 0.0434f, cer_fused_kernel<kUniform, 1, 1, 16>},
+    {kUniform, 1, 2, 8, 1.30f, 4.15f, 0.257f, 0.292f, 0.00309f, 0.0730f, cer_fused_kernel<kUniform, 1, 2, 8>},
+    {kUniform, 1, 3, 8, 1.25f, 4.23f, 0.232f, 0.204f, 0.00360f, 0.0939f, cer_fused_kernel<kUniform, 1, 3, 8>},
+    {kUniform, 1, 4, 8, 1.33f, 4.55f, 0.240f, 0.248f, 0.00356f, 0.1146f, cer_fused_kernel<kUniform, 1, 4, 8>},
+    {kUniform, 2, 2, 8, 1.34f, 4.84f, 0.271f, 0.403f, 0.00262f, 0.1173f, cer_fused_kernel<kUniform, 2, 2, 8>},
 };
 constexpr int kVariantCount = sizeof(kVariants) / sizeof(kVariants[0]);
 
