@@ -46,11 +46,11 @@ struct Block {
 // are mostly those of empty rows: the inputs are looked at first (odd: this thread's inputs had third pieces; without them nothing
 // is lost).  A function of its own, and behind the stores, so that nothing of it is held in registers while the matrix cores work.
 // Small inputs could also be caught on their way: 48 -> 53 us for 512 x 4608, batch 3136.
-// A wave takes tiles of 32 x 32 outputs, 64 columns of W per step, straight from memory; sums of kFlush columns as below.  Product of
+// A wave takes tiles of 32 x 32 outputs, 64 or 32 columns of W per step, straight from memory; sums of kFlush columns as below.  Product of
 // 512 x 4608, batch 3136, one-piece codebook: 68 us, 80 with empty rows, 247 with an infinity in X, 331 with X of about 2^-120.
 template <int kForm>
 __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, bool odd) {
-    constexpr int PW = weight_planes(kForm);
+    constexpr int PW = weight_planes(kForm), NS = kForm == kUniform ? 2 : 4;  // 16 NS columns of W per step
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
     if (!__syncthreads_or(must)) {
         bool some = false;
@@ -74,11 +74,11 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
         const uint32_t xoff = (8u * half * b.L + min(c, b.L - 1u)) * 4u;
         floatx16 sum = {}, acc = {};
         uint32_t held = 0;
-        for (uint32_t k0 = b.k_begin; k0 < b.k_end; k0 += 64u) {  // a multiple of 64 columns
-            float x[4][8];
-            uint4 q[4][PW];
+        for (uint32_t k0 = b.k_begin; k0 < b.k_end; k0 += 16u * NS) {  // a multiple of 64 columns
+            float x[NS][8];
+            uint4 q[NS][PW];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < NS; ++s) {
                 const __amdgpu_buffer_rsrc_t xbuf = x_rows(b.X, b.L, k0 + 16 * s, b.n);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) x[s][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff + i * b.L * 4u, 0, 0));
@@ -86,7 +86,7 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
                 for (int p = 0; p < PW; ++p) q[s][p] = reinterpret_cast<const uint4*>(w + p * b.plane + (size_t)(k0 + 16 * s) * 32)[lane];
             }
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
+            for (int s = 0; s < NS; ++s)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     float v = 0.f;
@@ -98,7 +98,7 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
                     }
                     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v, x[s][i], acc, 0, 0, 0);
                 }
-            if ((held += 64u) >= kFlush) {
+            if ((held += 16u * NS) >= kFlush) {
                 held = 0;
                 sum += acc;
                 acc = floatx16{};
@@ -332,12 +332,16 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
     uint32_t k0 = k_begin + 32u * wave;
     if (k0 >= k_end) return odd;
     load(k0, 0);
+    // (kUniform: the loads of a step stay behind the one before; mixed with it by the compiler they waited for one another: 603 x 6906, three
+    // values, batch 1359 77 us instead of 102, 1320 x 5895, 81 values, batch 691 68 instead of 96)
     for (;;) {
         load(min(k0 + 128u, k_end - 32u), 1);  // behind the end: the last columns once more
         step(0);
+        if constexpr (kForm == kUniform) __builtin_amdgcn_sched_barrier(0);
         if ((k0 += 128u) >= k_end) break;
         load(min(k0 + 128u, k_end - 32u), 0);
         step(1);
+        if constexpr (kForm == kUniform) __builtin_amdgcn_sched_barrier(0);
         if ((k0 += 128u) >= k_end) break;
     }
     if (PW > 1) {
