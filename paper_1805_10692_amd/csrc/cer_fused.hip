@@ -222,7 +222,7 @@ __device__ __forceinline__ floatx4 mfma16(uint4 a, uint4 b, floatx4 c) {
 // x - p of eight numbers and their pieces p, paired: the dot product of a pair (p, p') with (-1, 0) or (0, -1), added to x.  One
 // instruction where unpacking and subtracting take two; exact, as the difference is.  Written out: the compiler's choice is the
 // two-address form, which costs a move for every number of a wide load.  Results of dot products may be read by other
-// instructions three wait states later: the block ends with them.
+// instructions three wait states later: the block ends with them, or with the instructions that take the bits, in the order of the results.
 // lost: takes the bits of the remainders.  Those of the second pieces have eight significant bits at most, so that the lower half of their
 // binary32 form is zero unless they reach below 2^-133, the smallest bf16 number: then the third piece loses something.  (0.5 to 1 us
 // of 11 to 30; looking at the inputs instead, three instructions per two, took 24 -> 27 us for 4096 x 9216, 15 % indexed, batch 32, and
