@@ -219,6 +219,12 @@ int cer_matmul_narrow_columns(const cer_handle_t* h, int64_t batch);
  * cer_matmul_noalloc, never do it.)  Errors: CER_E_INVALID, CER_E_HIP (no device copy). */
 int cer_matmul_fused_rows(const cer_handle_t* h, int64_t batch);
 
+/* Whether cer_matmul / cser_matmul multiply from the tile index of cer_prepare_strips for this handle and batch, in place of the
+ * kernels that cer_matmul_path, cer_matmul_narrow_columns and cer_matmul_fused_rows speak of: the batch columns per workgroup (16 to
+ * 64), 0 where they do not.  Partial sums, infinities and NaNs as with cer_matmul_fused_rows.  (cer_matmul_ex with a path, flags or a
+ * tile width, and cer_matmul_noalloc, never do it.)  Errors: CER_E_INVALID, CER_E_HIP (no device copy). */
+int cer_matmul_tile_columns(const cer_handle_t* h, int64_t batch);
+
 /* The bf16 matrices as which CER_PATH_DENSE writes the handle's matrix: 1 to 3, or 0 where it does not (fp32 instead).
  * Errors: CER_E_INVALID, CER_E_HIP (no device copy). */
 int cer_matmul_planes(const cer_handle_t* h);
@@ -285,6 +291,9 @@ int cer_matmul_path_ex(const cer_handle_t* h, int64_t batch, const cer_matmul_op
  * run a variant that moves half as much through LDS; widths that are not multiples of 4, and X / Y that are only
  * 4-byte aligned, are read and written in smaller pieces).  Once the index exists, cer_matmul / cser_matmul choose kernel 5 by
  * themselves where they expect it to be the fastest (cer_matmul_path tells); cer_matmul_ex can prefer or avoid it.
+ * For handles with 16-bit column indices and at least two values it writes a second one too, the tile index, from which products of
+ * some dozens of columns are formed on the matrix cores (cer_matmul_tile_columns): the elements of 16 rows and 64 columns next to each
+ * other, 4 bytes each, up to 12 bytes of padding and a 4-byte pointer per 16 rows and 64 columns; not where there is no memory for it.
  * Not thread-safe against products running on the same handle: call it before the handle is shared.  A second call
  * is a no-op.  Errors: CER_E_INVALID, CER_E_TOO_LARGE, CER_E_NOMEM, CER_E_HIP (no device copy, allocation failed).
  */

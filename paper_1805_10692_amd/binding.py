@@ -42,7 +42,7 @@ EXPORTS = [
     "csr_clone_device", "csr_free", "cer_cost_model", "csr_cost_model", "dense_cost_model",
     "cer_encode_device", "cer_quantize_uniform", "cer_quantize_encode_device", "cer_matmul_path", "cer_stream_read",
     "cer_decode_device", "cer_trim", "cer_matmul_ex", "cer_matmul_path_ex", "cer_matmul_noalloc", "cer_prepare_strips",
-    "cer_matmul_narrow_columns", "cer_matmul_fused_rows", "cer_matmul_planes", "cer_encode_sorts_rows",
+    "cer_matmul_narrow_columns", "cer_matmul_fused_rows", "cer_matmul_tile_columns", "cer_matmul_planes", "cer_encode_sorts_rows",
 ]
 
 CER_FORMAT_CER, CER_FORMAT_CSER = 0, 1
@@ -165,6 +165,8 @@ def lib() -> ctypes.CDLL:
         L.cer_matmul_narrow_columns.argtypes = [vp, i64]
         L.cer_matmul_fused_rows.restype = ctypes.c_int
         L.cer_matmul_fused_rows.argtypes = [vp, i64]
+        L.cer_matmul_tile_columns.restype = ctypes.c_int
+        L.cer_matmul_tile_columns.argtypes = [vp, i64]
         L.cer_encode_sorts_rows.restype = ctypes.c_int
         L.cer_encode_sorts_rows.argtypes = [vp, i32]
         L.cer_matmul_planes.restype = ctypes.c_int
@@ -339,6 +341,14 @@ def cer_matmul_fused_rows(h: Handle, batch: int) -> int:
     rc = lib().cer_matmul_fused_rows(h.ptr, batch)
     if rc < 0:
         _check(rc, "cer_matmul_fused_rows")
+    return rc
+
+
+def cer_matmul_tile_columns(h: Handle, batch: int) -> int:
+    """Batch columns per workgroup where cer_matmul multiplies from the tile index instead; 0 where it does not."""
+    rc = lib().cer_matmul_tile_columns(h.ptr, batch)
+    if rc < 0:
+        _check(rc, "cer_matmul_tile_columns")
     return rc
 
 

@@ -867,6 +867,12 @@ int cer_matmul_fused_rows(const cer_handle_t* h, int64_t batch) {
     return cer::matmul_fused_rows(h->view, batch);
 }
 
+int cer_matmul_tile_columns(const cer_handle_t* h, int64_t batch) {
+    if (!h || batch < 1) return CER_E_INVALID;
+    if (h->device < 0 || !h->d_base) return CER_E_HIP;
+    return cer::matmul_tile_columns(h->view, batch);
+}
+
 int cer_encode_sorts_rows(const cer_handle_t* h, int32_t K) {
     if (!h || K < 1 || K > 256) return CER_E_INVALID;
     if (h->device < 0 || !h->d_base) return CER_E_HIP;
@@ -1089,6 +1095,24 @@ int cer_prepare_strips(cer_handle_t* h) {
         h->view.n_strips = (uint32_t)ns;
         h->view.strip_rows = (uint32_t)S;
         h->view.strip_chunks = nchunks;
+        // The tile index, written by a kernel.  Products do without it where there is no memory for it.
+        const size_t tile_bytes = cer::tile_index_bytes(h->view);
+        void* tile = nullptr;
+        if (tile_bytes > 0) {
+            e = (hipError_t)cer::handle_alloc(&tile, tile_bytes, nullptr);
+            if (e == hipSuccess) {
+                e = (hipError_t)cer::build_tile_index(h->view, tile, nullptr);
+                const hipError_t f = hipStreamSynchronize(nullptr);
+                if (e == hipSuccess) e = f;
+                if (e != hipSuccess) cer::handle_free(tile, true);
+            }
+            if (e == hipSuccess) {
+                h->d_tile = tile;
+                h->view.tile_index = tile;
+            } else {
+                (void)hipGetLastError();
+            }
+        }
         return CER_OK;
     } catch (const std::bad_alloc&) {
         return CER_E_NOMEM;
@@ -1107,6 +1131,7 @@ void cer_free(cer_handle_t* h) {
     cer::handle_free(h->d_base, null_only);
     cer::handle_free(h->d_split, null_only);
     cer::handle_free(h->d_strip, null_only);
+    cer::handle_free(h->d_tile, null_only);
     delete h;
 }
 

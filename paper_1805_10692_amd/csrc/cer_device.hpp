@@ -418,10 +418,23 @@ NarrowEstimate narrow_estimate(const DeviceView& d, uint32_t L);
 hipError_t launch_narrow(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream);
 
 // cer_fused.hip -- batch > 1, decode + matrix-core product in one launch.  temporaries: partial sums of parts of W's columns are
-// allowed (a second launch adds them up).  fused_rows: rows of W per workgroup, 0 where it is not applicable or would take `below` us.
+// allowed (a second launch adds them up).  fused_rows: rows of W per workgroup, 0 where it is not applicable or would take `below` us;
+// us: what it is expected to take.
 // dense_zeros: infinities and NaNs in X reach every row, as in launch_mfma; else those that index them, as with the gathers.
-int fused_rows(const DeviceView& d, uint32_t L, bool temporaries, double below);
+int fused_rows(const DeviceView& d, uint32_t L, bool temporaries, double below, double* us = nullptr);
 hipError_t launch_fused(const DeviceView& d, const float* X, float* Y, uint32_t L, bool temporaries, bool dense_zeros, hipStream_t stream);
+
+// cer_tile.hip -- batch > 1, matrix cores, tiles of W laid out in LDS from the handle's tile index.  tile_estimate_us: 1e30 where it is
+// not applicable.  temporaries, dense_zeros: as for launch_fused.
+struct TileIndexShape {
+    uint32_t segs = 0, groups = 0;
+    size_t ptr_bytes = 0, bytes = 0;  // of its pointers; all of it
+};
+TileIndexShape tile_index_shape(const DeviceView& d);
+hipError_t launch_tile_index(const DeviceView& d, void* index, hipStream_t stream);
+double tile_estimate_us(const DeviceView& d, uint32_t L, bool temporaries);
+int tile_columns(const DeviceView& d, uint32_t L, bool temporaries);  // of the batch, per workgroup
+hipError_t launch_tile(const DeviceView& d, const float* X, float* Y, uint32_t L, bool temporaries, bool dense_zeros, hipStream_t stream);
 
 // cer_strip.hip -- batch > 1, strips of X resident in LDS (needs the strip-major index of cer_prepare_strips)
 bool strip_applicable(const DeviceView& d, const float* X, const float* Y, uint32_t L);

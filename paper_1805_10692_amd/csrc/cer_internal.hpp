@@ -90,6 +90,7 @@ struct DeviceView {
     uint64_t strip_chunks = 0;
     uint32_t strip_rows = 0;
     uint32_t n_strips = 0;
+    const void* tile_index = nullptr;  // of cer_tile.hip (derived by cer_prepare_strips; null otherwise)
     // Rank table (derived; null unless the codebook has 2 .. 256 values): per row 1 << rank_tab_shift words at a fixed
     // stride, word 0 = the row's first colI position, word k = end of its group of rank k (the previous word when the
     // row has no element of that rank), the same for CER and CSER handles.
@@ -148,11 +149,16 @@ int matmul_path(const DeviceView& v, int64_t L, const MatmulOptions& o);
 int matmul_narrow_columns(const DeviceView& v, int64_t L);
 // Rows of W per workgroup where it runs decode + product in one launch instead (0: it does not).
 int matmul_fused_rows(const DeviceView& v, int64_t L);
+// Batch columns per workgroup where it multiplies from the tile index instead (0: it does not).
+int matmul_tile_columns(const DeviceView& v, int64_t L);
 // bf16 matrices of decode + product (0: it multiplies in fp32).
 int matmul_planes(const DeviceView& v);
 // Fills the handle's rank table (if its layout has one) from the format arrays already in device memory; the launch
 // is ordered on `stream`.  A hipError_t value as int.
 int build_rank_table(const DeviceView& v, void* stream);
+// Tile index (cer_tile.hip): its size (0: not for this handle), and the launch that writes it.  A hipError_t value as int.
+size_t tile_index_bytes(const DeviceView& v);
+int build_tile_index(const DeviceView& v, void* index, void* stream);
 int launch_dense(const float* W, const float* X, float* Y, int64_t m, int64_t n, int64_t L, void* stream);
 int launch_stream_copy(void* dst, const void* src, int64_t bytes, void* stream);
 int launch_stream_read(const void* src, int64_t bytes, void* sink, void* stream);
@@ -205,6 +211,7 @@ struct cer_matrix {
     void* d_base = nullptr;   // the device allocation of the format arrays
     void* d_split = nullptr;  // row order and parts of long rows (a second, small allocation; null: rows of similar length)
     void* d_strip = nullptr;  // strip-major index (cer_prepare_strips; null: not prepared)
+    void* d_tile = nullptr;   // tile index (cer_prepare_strips too; null: not for this handle, or no memory)
     cer::DeviceLayout layout; // where the arrays sit inside it
     size_t d_bytes = 0;       // its size
     int64_t stream_bytes = 0; // bytes of format arrays a product reads

@@ -162,6 +162,10 @@ hipError_t launch_densified(const DeviceView& d, const float* X, float* Y, uint3
 // 0.85 / 0.9 / 0.95 / 1 give 1.125 / 1.133 / 1.132 / 1.138 times the speed on average and make 4 / 5 / 9 / 11 of them slower.
 constexpr double kFusedMargin = 0.9;
 
+// A prepared handle's tile index is used where that is expected to take less than this share of what would run without it (of 100 random
+// products of such handles 33, one of them slower: 21 -> 25 us).
+constexpr double kTileMargin = 0.95;
+
 // Whether the LDS variant is expected to beat the kernel that gathers from L2.  Measured on MI355X: for wide
 // batches it never does -- gathers of 16- or 32-byte pieces at random LDS addresses are bank-conflict bound at
 // 32 - 43 B/clk per CU, while the L2 kernel's gathers of whole 128-byte rows sustain 27 - 48 B/clk per CU and
@@ -225,11 +229,12 @@ double path_estimate_us(const DeviceView& d, uint32_t L, int path) {
 }
 
 // What the library's own choice runs instead of `path` (a path, flags or a tile width of the caller's speak of the others):
-// the stream kernel for several columns (narrow: its columns per pass), or decode + product in one launch (fused: its rows per
-// workgroup; temporaries: it may have partial sums -- only where the kernel it takes the place of has a temporary as well).
+// the stream kernel for several columns (narrow: its columns per pass), decode + product in one launch (fused: its rows per
+// workgroup), or products from the handle's tile index (tile).  temporaries: the last two may have partial sums -- only where the kernel
+// they take the place of has a temporary as well.
 struct Instead {
     int narrow = 0, fused = 0;
-    bool temporaries = false;
+    bool temporaries = false, tile = false;
 };
 Instead choose_instead(const DeviceView& d, uint32_t L, const MatmulOptions& o, int path) {
     Instead r;
@@ -243,8 +248,12 @@ Instead choose_instead(const DeviceView& d, uint32_t L, const MatmulOptions& o, 
         }
     }
     r.temporaries = r.narrow == 0 && (path == 3 || path == kPathStrip || d.omega0 != 0.f || d.n_split_parts > 0);
-    r.fused = fused_rows(d, L, r.temporaries, kFusedMargin * us);
+    r.fused = fused_rows(d, L, r.temporaries, kFusedMargin * us, &us);
     if (r.fused > 0) r.narrow = 0;
+    if (d.tile_index && tile_estimate_us(d, L, r.temporaries) < kTileMargin * us) {
+        r.tile = true;
+        r.narrow = r.fused = 0;
+    }
     return r;
 }
 
@@ -292,6 +301,13 @@ int matmul_fused_rows(const DeviceView& d, int64_t L) {
     return L < 2 || L > 0x7FFFFFFFll ? 0 : choose_instead(d, (uint32_t)L, o, choose_batched_path(d, (uint32_t)L, o, false, nullptr)).fused;
 }
 
+int matmul_tile_columns(const DeviceView& d, int64_t L) {
+    const MatmulOptions o;
+    if (L < 2 || L > 0x7FFFFFFFll) return 0;
+    const Instead i = choose_instead(d, (uint32_t)L, o, choose_batched_path(d, (uint32_t)L, o, false, nullptr));
+    return i.tile ? tile_columns(d, (uint32_t)L, i.temporaries) : 0;
+}
+
 int matmul_planes(const DeviceView& d) { return mfma_applicable(d, 2) ? mfma_planes(d) : 0; }
 
 size_t matmul_workspace_floats(const DeviceView& d, int64_t L, const MatmulOptions& o) {
@@ -333,6 +349,7 @@ int launch_matmul(const DeviceView& d, const float* X, float* Y, int64_t L64, vo
     const int batched_path = L > 1 ? choose_batched_path(d, L, o, no_temporaries, &plan, X, Y) : 0;
     if (!no_temporaries && L > 1) {
         const Instead instead = choose_instead(d, L, o, batched_path);
+        if (instead.tile) return (int)launch_tile(d, X, Y, L, instead.temporaries, batched_path == 3, stream);
         if (instead.narrow > 0) return (int)launch_narrow(d, X, Y, L, stream);
         if (instead.fused > 0) return (int)launch_fused(d, X, Y, L, instead.temporaries, batched_path == 3, stream);
     }
