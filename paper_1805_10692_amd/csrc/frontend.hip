@@ -107,27 +107,33 @@ __global__ __launch_bounds__(256) void range_kernel(const float* __restrict__ W,
     // the bulk in 16-byte pieces (W is aligned by the caller's allocator or the scalar loop below takes it all)
     const int64_t N4 = ((reinterpret_cast<uintptr_t>(W) & 15u) == 0) ? N / 4 : 0;
     const float4* W4 = reinterpret_cast<const float4*>(W);
-    int64_t i = tid;
-    for (; i + 7 * stride < N4; i += 8 * stride) {
-        float4 w[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) w[k] = W4[i + k * stride];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            range_take(w[k].x, lo, hi, bad);
-            range_take(w[k].y, lo, hi, bad);
-            range_take(w[k].z, lo, hi, bad);
-            range_take(w[k].w, lo, hi, bad);
-        }
-    }
-    for (; i < N4; i += stride) {
-        const float4 w = W4[i];
+    const auto take = [&](const float4& w) {
         range_take(w.x, lo, hi, bad);
         range_take(w.y, lo, hi, bad);
         range_take(w.z, lo, hi, bad);
         range_take(w.w, lo, hi, bad);
+    };
+    // Eight loads in flight: 32 KiB in a row per workgroup and round (loads a grid's width apart took 44 us for 4096 x 9216 behind a
+    // decoder's writes, 38 this way), or, where that leaves workgroups without work, a grid's width apart.
+    constexpr int64_t kTile = 8 * 256;
+    if (N4 >= (int64_t)gridDim.x * kTile) {
+        for (int64_t b = (int64_t)blockIdx.x * kTile + threadIdx.x; b < N4; b += (int64_t)gridDim.x * kTile) {
+            float4 w[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[k] = W4[min(b + 256 * k, N4 - 1)];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) take(w[k]);
+        }
+    } else if (tid < N4) {
+        float4 w[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (k * stride < N4) w[k] = W4[min(tid + k * stride, N4 - 1)];  // (uniform)
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (k * stride < N4) take(w[k]);
     }
-    for (i = N4 * 4 + tid; i < N; i += stride) range_take(W[i], lo, hi, bad);
+    for (int64_t i = N4 * 4 + tid; i < N; i += stride) range_take(W[i], lo, hi, bad);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         lo = fminf(lo, __shfl_xor(lo, off, kWave));
@@ -494,22 +500,21 @@ __global__ __launch_bounds__(1024) void row_layout_kernel(const uint32_t* __rest
         s_sum[sub][pos] = s;
     }
     __syncthreads();
-    if (sub == 0) s_h[pos] = pos < K ? s_sum[0][pos] + s_sum[1][pos] + s_sum[2][pos] + s_sum[3][pos] : 0ull;
+    // (count, then the earlier position): no two are equal, so that one comparison tells who comes first
+    if (sub == 0) s_h[pos] = (pos < K ? s_sum[0][pos] + s_sum[1][pos] + s_sum[2][pos] + s_sum[3][pos] : 0ull) << 8 | (255u - pos);
     __syncthreads();
     // the four threads of a position compare it with a quarter of the others each
+    const unsigned long long key = s_h[pos];
     {
-        const unsigned long long c = s_h[pos];
         uint32_t before = 0;
-        const uint32_t j0 = sub * 64u, j1 = min(K, j0 + 64u);
-        for (uint32_t j = j0; j < j1; ++j) {
-            const unsigned long long cj = s_h[j];
-            before += (cj > c) || (cj == c && j < pos);
-        }
+        for (uint32_t j = sub * 64u; j < min(K, sub * 64u + 64u); j += 8u)  // (positions from K on have no count)
+#pragma unroll
+            for (uint32_t i = 0; i < 8; ++i) before += s_h[j + i] > key ? 1u : 0u;
         s_sum[sub][pos] = before;
     }
-    const int occurring = __syncthreads_count(sub == 0 && s_h[pos] > 0);
+    const int occurring = __syncthreads_count(sub == 0 && key >> 8 != 0ull);
     if (sub == 0) {
-        const unsigned long long c = s_h[pos];
+        const unsigned long long c = key >> 8;
         const uint32_t before = (uint32_t)(s_sum[0][pos] + s_sum[1][pos] + s_sum[2][pos] + s_sum[3][pos]);
         s_rank[pos] = c > 0 ? before : 0u;
         if (blockIdx.x == 0) {
@@ -1040,8 +1045,10 @@ __device__ __forceinline__ void scatter_row(const ColT* __restrict__ colI, const
     }
 }
 
-// fp32 output.
-template <typename ColT, typename CodeT, uint32_t kThreads>
+typedef uint32_t Words4 __attribute__((ext_vector_type(4), aligned(4)));  // (the memory path takes them at any such address)
+
+// fp32 output.  kPast: outputs larger than what caches can hold go past them (decode_device).
+template <typename ColT, typename CodeT, uint32_t kThreads, bool kPast>
 __global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict__ colI, DecodeArgs a, float* __restrict__ out) {
     constexpr bool kRanks = sizeof(CodeT) == 1;
     constexpr uint32_t T = kThreads;
@@ -1068,14 +1075,17 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict
         scatter_row<ColT, CodeT, T, false>(colI, a, g0, g1, tid, c0, len, s_ptr, s_grp, code);
         __syncthreads();
         float* o = out + r * a.n + c0;
-        const uint32_t n4 = (reinterpret_cast<uintptr_t>(o) & 15u) == 0 ? len >> 2 : 0u;
         if constexpr (kRanks) {
+            const uint32_t n4 = len >> 2;
             for (uint32_t j = tid; j < n4; j += T) {
                 const uint32_t q = reinterpret_cast<const uint32_t*>(s_seg)[j];
-                reinterpret_cast<uint4*>(o)[j] = make_uint4(s_val[q & 0xFFu], s_val[(q >> 8) & 0xFFu], s_val[(q >> 16) & 0xFFu], s_val[q >> 24]);
+                const Words4 v = {s_val[q & 0xFFu], s_val[(q >> 8) & 0xFFu], s_val[(q >> 16) & 0xFFu], s_val[q >> 24]};
+                if constexpr (kPast) __builtin_nontemporal_store(v, reinterpret_cast<Words4*>(o) + j);
+                else reinterpret_cast<Words4*>(o)[j] = v;
             }
             for (uint32_t j = (n4 << 2) + tid; j < len; j += T) o[j] = __uint_as_float(s_val[code[j]]);
         } else {
+            const uint32_t n4 = (reinterpret_cast<uintptr_t>(o) & 15u) == 0 ? len >> 2 : 0u;
             for (uint32_t j = tid; j < n4; j += T) reinterpret_cast<float4*>(o)[j] = reinterpret_cast<const float4*>(s_seg)[j];
             for (uint32_t j = (n4 << 2) + tid; j < len; j += T) o[j] = (float)code[j];
         }
@@ -1451,6 +1461,11 @@ DecodeArgs decode_args(const DeviceView& v, int64_t nseg, uint32_t multiple) {
     return a;
 }
 
+// From half of the 256 MB cache in front of the memory on, the decoder's stores go past the caches: what they would leave there is written
+// back while the next kernels read.  4096 x 9216 (151 MB): the decoder 42 -> 39 us, the next matrix's range_kernel 38 -> 27; decoder and a
+// reduction of the result 90 -> 88.  Smaller results are read from that cache again (67 MB, decoder and reduction: 42 us, 47 past it).
+constexpr int64_t kPastCaches = 128 << 20;
+
 template <typename ColT, typename CodeT>
 hipError_t launch_decode(const DeviceView& v, float* out, hipStream_t s) {
     // Segments of equal length, at most 32 KiB of LDS; more of them where the rows alone give fewer than eight workgroups
@@ -1460,9 +1475,11 @@ hipError_t launch_decode(const DeviceView& v, float* out, hipStream_t s) {
     const dim3 grid((unsigned)v.m, a.nseg);
     const size_t lds = ((size_t)a.seg * sizeof(CodeT) + 15) & ~(size_t)15;
     const ColT* colI = static_cast<const ColT*>(v.colI);
+    const bool past = v.m * v.n * 4 >= kPastCaches;
     // short rows: one wave per row, four times as many workgroups in flight
-    if (v.n <= 1024) return launch_kernel(decode_kernel<ColT, CodeT, 64>, grid, dim3(64), lds, s, colI, a, out);
-    return launch_kernel(decode_kernel<ColT, CodeT, 256>, grid, dim3(256), lds, s, colI, a, out);
+    if (v.n <= 1024)
+        return launch_kernel(past ? decode_kernel<ColT, CodeT, 64, true> : decode_kernel<ColT, CodeT, 64, false>, grid, dim3(64), lds, s, colI, a, out);
+    return launch_kernel(past ? decode_kernel<ColT, CodeT, 256, true> : decode_kernel<ColT, CodeT, 256, false>, grid, dim3(256), lds, s, colI, a, out);
 }
 
 template <typename ColT, typename CodeT>

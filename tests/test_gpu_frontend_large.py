@@ -1,0 +1,50 @@
+"""The front-end where its kernels change their form: weights and results of more than a round of the range kernel and of 128 MiB, and rows
+of the sorting emitter that stay in registers or do not, one after another."""
+import numpy as np
+import pytest
+
+from paper_1805_10692_amd import binding as B
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape", [(1024, 8192), (1024, 8193), (2049, 4097), (4097, 8193)])
+@pytest.mark.parametrize("ends", ["first", "last"])
+def test_range_and_decode(shape, ends):
+    """The smallest and the largest weight at either end of the matrix, at the sizes where the range is read in another way (8 388 608
+    weights) and where the result goes past the caches (33 554 432); nothing behind the result is written."""
+    m, n = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + n)
+    W = torch.randn((m, n), generator=g, device="cuda").clamp_(-3, 3)
+    flat = W.view(-1)
+    flat[0 if ends == "first" else m * n - 1], flat[1 if ends == "first" else m * n - 2] = -7.0, 8.0
+    h, cb = B.cer_quantize_encode_device(W, m, n, 4, "cer")
+    cb = np.asarray(cb)
+    assert cb[0] == -7 and cb[-1] == 8 and len(cb) == 16   # a grid of whole numbers
+    out = torch.full((m * n + 4,), float("nan"), device="cuda")
+    B.cer_decode_device(h, out[:m * n].view(m, n))
+    B.cer_free(h)
+    assert torch.equal(out[:m * n].view(m, n), torch.round(W + 7) - 7) and torch.isnan(out[m * n:]).all()
+
+
+# rows of at most 12288 columns stay in registers; about 1300 workgroups take rows of 9217 and 12289 columns in turn
+@pytest.mark.parametrize("shape", [(3000, 1024), (2999, 1039), (1500, 4100), (2600, 9217), (700, 12288), (1400, 12289), (300, 20001)])
+@pytest.mark.parametrize("fmt", ["cer", "cser"])
+def test_sorted_rows(shape, fmt):
+    """The same arrays as the host encoder's; rows without an element, full rows, and rows of one value."""
+    m, n = shape
+    rng = np.random.default_rng(m + n)
+    K = 100 if n == 9217 else 24
+    cb = (np.arange(K) - 3).astype(np.float32)
+    W = rng.choice(cb, size=(m, n)).astype(np.float32)
+    W[rng.random((m, n)) < 0.2] = cb[40 % K]
+    W[5], W[m - 1], W[m // 2] = cb[40 % K], cb[K - 1], rng.choice(cb[41 % K:], n)
+    h = B.cer_encode_device(torch.from_numpy(W).cuda(), m, n, cb, fmt)
+    assert B.cer_encode_sorts_rows(h, K)
+    host = (B.cer_encode if fmt == "cer" else B.cser_encode)(W, cb)
+    for which in (B.CER_ARRAY_OMEGA, B.CER_ARRAY_COLI, B.CER_ARRAY_OMEGAPTR, B.CER_ARRAY_ROWPTR) + ((B.CER_ARRAY_OMEGAI,) if fmt == "cser" else ()):
+        assert np.array_equal(B.cer_get_array(h, which), B.cer_get_array(host, which)), which
+    B.cer_free(h)
+    B.cer_free(host)
