@@ -616,41 +616,55 @@ __device__ __forceinline__ void emit_values(const FrontState* __restrict__ st, c
         for (size_t o = to.gap_begin[g] + threadIdx.x; o < to.gap_end[g]; o += blockDim.x) to.base[o] = 0;
 }
 
+// What a wave needs to know of a row: where its groups and indices begin and end, and its values' counts by rank (64 i + lane).
+struct RowHead {
+    uint2 here, next;
+    uint32_t size[kCodes / kWave];
+};
+// Codebook positions by rank, the same for every row.
+__device__ __forceinline__ void load_places(const FrontState* __restrict__ st, uint32_t ranks, uint32_t (&place_of)[kCodes / kWave]) {
+    const uint32_t lane = threadIdx.x & 63u;
+#pragma unroll
+    for (uint32_t i = 0; i < kCodes / kWave; ++i) place_of[i] = i * kWave < ranks ? st->pos_of[i * kWave + lane] & (kCodes - 1u) : 0u;
+}
+__device__ __forceinline__ RowHead load_head(int64_t r, const uint32_t* __restrict__ cnt, const uint2* __restrict__ rowStart, uint32_t ranks,
+                                             const uint32_t (&place_of)[kCodes / kWave]) {
+    RowHead h;
+    h.here = rowStart[r];
+    h.next = rowStart[r + 1];
+#pragma unroll
+    for (uint32_t i = 0; i < kCodes / kWave; ++i) h.size[i] = i * kWave < ranks ? cnt[r * kCodes + place_of[i]] : 0u;
+    return h;
+}
+
 // One wave: everything of row r but its columns -- bucket sizes by rank -> bucket starts (exclusive scan over ranks 1, 2, ...), the
 // pointers and the row's record of the rank table.  place(rank, codebook position, first colI position of the bucket).
 template <typename OiT, typename Place>
-__device__ __forceinline__ void emit_row_pointers(int64_t r, const uint32_t* __restrict__ cnt, const uint2* __restrict__ rowStart,
-                                                  const FrontState* __restrict__ st, int64_t m, int cser, const EmitTarget& to, Place place) {
+__device__ __forceinline__ void emit_row_pointers(int64_t r, const RowHead& head, const uint32_t (&place_of)[kCodes / kWave], uint32_t Kp, uint32_t ranks,
+                                                  int64_t m, int cser, const EmitTarget& to, Place place) {
     uint32_t* omegaPtr = reinterpret_cast<uint32_t*>(to.base + to.off_optr);
     uint32_t* rowPtr = reinterpret_cast<uint32_t*>(to.base + to.off_rptr);
     uint2* rowInfo = reinterpret_cast<uint2*>(to.base + to.off_ri);
     OiT* omegaI = reinterpret_cast<OiT*>(to.base + to.off_oi);
     uint32_t* tab = reinterpret_cast<uint32_t*>(to.base + to.off_tab);
-    const uint32_t lane = threadIdx.x & 63u, Kp = st->Kp;
-    const uint2 here = rowStart[r], next = rowStart[r + 1];
-    const uint32_t g0 = here.x, off0 = here.y;
-    const uint32_t groups = next.x - g0;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t g0 = head.here.x, off0 = head.here.y;
+    const uint32_t groups = head.next.x - g0;
     if (lane == 0) {
         rowPtr[r] = g0;
-        rowInfo[r] = here;
+        rowInfo[r] = head.here;
         if (r == 0) omegaPtr[0] = 0;
         if (r == m - 1) {
-            rowPtr[m] = next.x;
-            rowInfo[m] = next;
+            rowPtr[m] = head.next.x;
+            rowInfo[m] = head.next;
         }
     }
-    const uint32_t ranks = max(Kp, 1u << to.tab_shift);
-    uint32_t place_of[kCodes / kWave], size[kCodes / kWave];  // all on their way before the first is used
-#pragma unroll
-    for (uint32_t i = 0; i < kCodes / kWave; ++i) place_of[i] = i * kWave < ranks ? st->pos_of[i * kWave + lane] & (kCodes - 1u) : 0u;
-#pragma unroll
-    for (uint32_t i = 0; i < kCodes / kWave; ++i) size[i] = i * kWave < ranks ? cnt[r * kCodes + place_of[i]] : 0u;
     uint32_t carry = 0, gcarry = 0;
 #pragma unroll
     for (uint32_t i = 0; i < kCodes / kWave; ++i) {
         if (i * kWave >= ranks) break;  // uniform
         const uint32_t k = i * kWave + lane, pos = place_of[i];
-        const uint32_t c = (k >= 1 && k < Kp) ? size[i] : 0u;
+        const uint32_t c = (k >= 1 && k < Kp) ? head.size[i] : 0u;
         const uint32_t inc = cer::wave_inclusive_scan(c);
         const uint32_t end = off0 + carry + inc;
         place(k, pos, end - c);
@@ -670,20 +684,23 @@ __device__ __forceinline__ void emit_row_pointers(int64_t r, const uint32_t* __r
     }
 }
 
-// One row per workgroup of one wave, whose columns are sorted in LDS; the last workgroup does emit_values.
+// One row at a time per workgroup of one wave, whose columns are sorted in LDS; the last workgroup does emit_values.
 // A lane takes a run of consecutive columns and has a counter of its own per codebook position (16 bits, two lanes to a word), so
 // that counting and placing need neither a vote nor an order among the lanes: count the run's elements, turn the counters into
 // first slots (a scan over the lanes per position, two positions at a time, on top of the bucket starts), then take the slots one
 // after another and write the columns to their places in LDS.  The row goes to memory as it lies there, with 16-byte stores.
-// A row of 9216 columns and 128 positions takes 33000 clocks (start and pointers 6000, counting and the scan 13500, placing 10000, out
-// 4000) and 31 KiB, five of them on a compute unit: 60 us for 4096, against 69 with emit_kernel; bound by the LDS, which takes 14 clocks
-// per placed column and wave, and by the phases of five waves.  Where all rows run at once the gain is larger: 300 x 9000 115 -> 89 us.
+// As many workgroups as fit at once take the rows in turn: a row's codes, pointers and counts come while the row before is sorted.
+// A row of 9216 columns and 128 positions takes 31 KiB, five of them on a compute unit: 56 us for 4096, against 69 with emit_kernel (60
+// with a workgroup per row that loads its codes twice); 3400 clocks of LDS instructions per row (an add 5, a store to any place 6), twice
+// that with five waves to hide their latency.  Where all rows run at once the gain is larger: 300 x 9000 115 -> 89 us.
 constexpr uint32_t kRowCounters = 32;  // words of counters per codebook position
 // 64 runs of a multiple of 16 columns: below 65536, so that slots fit 16 bits.  Half of a row's columns have to fit 64 KiB with the
 // counters (sorted_lds), which ends at about 64000 columns already.
 constexpr int64_t kSortedColumns = 64512;
+constexpr int kSortedPieces = 12;  // sixteens of columns per lane that stay in registers
 inline uint32_t emit_stage_bytes(uint32_t longest) { return ((longest * 2u + 16u + 15u) & ~15u) + 256u; }
 
+template <int kPieces>
 __global__ __launch_bounds__(64) void emit_sorted_kernel(const uint8_t* __restrict__ codes, const uint32_t* __restrict__ cnt,
                                                          const uint2* __restrict__ rowStart, const FrontState* __restrict__ st,
                                                          int64_t m, uint32_t n, int cser, uint32_t positions, uint32_t stage_bytes,
@@ -695,115 +712,152 @@ __global__ __launch_bounds__(64) void emit_sorted_kernel(const uint8_t* __restri
         emit_values(st, to, out);
         return;
     }
-    const int64_t r = blockIdx.x;
     const uint32_t lane = threadIdx.x, eights = (positions + 7u) & ~7u;
-    const uint8_t* crow = codes + r * (int64_t)n;
-    const uint32_t run = ((n + 63u) / 64u + 15u) & ~15u, c0 = lane * run;
-    const uint32_t most = st->pos_of[0];
-    // f(first column, sixteen codes); behind the row's end stands the most frequent value, which takes no part.  Four loads are
-    // in flight (a trip to memory per sixteen columns took two thirds of the time).
-    const uint32_t pieces = run / 16u, blank = most * 0x01010101u;
-    constexpr int kAhead = 4;
-    uint4 ring[kAhead];
-    auto request = [&](uint32_t p, uint4& q) { __builtin_memcpy(&q, crow + min(c0 + 16u * min(p, pieces - 1u), n - 16u), 16); };
-    auto request_first = [&] {
+    const uint32_t run = ((n + 63u) / 64u + 15u) & ~15u, c0 = lane * run, pieces = run / 16u;
+    const uint32_t Kp = st->Kp, ranks = max(Kp, 1u << to.tab_shift), most = st->pos_of[0], blank = most * 0x01010101u;
+    uint32_t place_of[kCodes / kWave];
+    load_places(st, ranks, place_of);
+    // Rows of up to 1024 kPieces columns stay in registers, loaded at once and while the row before is sorted; of longer ones four loads
+    // are in flight (a trip to memory per sixteen columns took two thirds of the time).
+    constexpr int kAhead = kPieces > 0 ? kPieces : 4;
+    const uint32_t stride = gridDim.x - 1u;
+    auto row_codes = [&](int64_t r) { return codes + min(r, m - 1) * (int64_t)n; };
+    // (sixteen codes from a column in front of the row's end on: up to fifteen of the next row's)
+    auto request = [&](const uint8_t* crow, uint32_t p, uint4& q) { __builtin_memcpy(&q, crow + min(c0 + 16u * min(p, pieces - 1u), n - 1u), 16); };
+    auto request_first = [&](const uint8_t* crow, uint4 (&q)[kAhead]) {
 #pragma unroll
-        for (int d = 0; d < kAhead; ++d) request(d, ring[d]);
+        for (int d = 0; d < kAhead; ++d)
+            if (kPieces == 0 || (uint32_t)d < pieces) request(crow, d, q[d]);
     };
-    auto each_sixteen = [&](auto f) {
-        for (uint32_t p0 = 0; p0 < pieces; p0 += kAhead) {
-#pragma unroll
-            for (int d = 0; d < kAhead; ++d) {
-                const uint32_t p = p0 + d, c = c0 + 16u * p;
-                if (p >= pieces) break;  // uniform
-                uint32_t q[4] = {ring[d].x, ring[d].y, ring[d].z, ring[d].w};
-                request(p + kAhead, ring[d]);
-                if (c + 16u > n) {
-#pragma unroll
-                    for (uint32_t i = 0; i < 4; ++i) {
-                        q[i] = blank;
-                        for (uint32_t b = 0; b < 4 && c + 4 * i + b < n; ++b)
-                            q[i] = (q[i] & ~(0xFFu << (8 * b))) | (uint32_t)crow[c + 4 * i + b] << (8 * b);
-                    }
-                }
-                f(c, q);
-            }
-        }
-    };
-    request_first();
     uint32_t* counters = reinterpret_cast<uint32_t*>(s_row + stage_bytes);
     uint32_t* begin = counters + eights * kRowCounters;
-    for (uint32_t i = lane; i < eights * kRowCounters / 4u; i += kWave) reinterpret_cast<uint4*>(counters)[i] = make_uint4(0, 0, 0, 0);
-    const uint32_t off0 = rowStart[r].y, count = rowStart[r + 1].y - off0;
-    for (uint32_t i = lane; i < eights; i += kWave) begin[i] = i == most ? count : 0u;  // the most frequent value: behind all others
-    emit_row_pointers<uint8_t>(r, cnt, rowStart, st, m, cser, to, [&](uint32_t k, uint32_t pos, uint32_t first) {
-        if (k >= 1u && k < st->Kp) begin[pos] = first - off0;
-    });
     typedef unsigned char __attribute__((address_space(3))) * LdsByte;
+    typedef uint32_t __attribute__((address_space(3))) * LdsWord;
+    typedef uint16_t __attribute__((address_space(3))) * LdsCol;
     const uint32_t mine = (uint32_t)(uintptr_t)(LdsByte)(unsigned char*)counters + (lane >> 1) * 4u;
     const uint32_t half = 16u * (lane & 1u), one = 1u << half;
     // the lane's counter of the i-th of four codes: one byte times the distance of the counters, a dot product of bytes
     static_assert(kRowCounters * 4u < 256u, "distance of the counters");
-    typedef uint32_t __attribute__((address_space(3))) * LdsWord;
     auto counter = [&](uint32_t four, int i) {
         return reinterpret_cast<LdsWord>((uintptr_t)__builtin_amdgcn_udot4(four, (kRowCounters * 4u) << (8 * i), mine, false));
     };
     auto add = [&](LdsWord at) { return __hip_atomic_fetch_add(at, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
-    wave_lds_sync();
-    each_sixteen([&](uint32_t, const uint32_t (&q)[4]) {
+    uint4 ring[kAhead], ahead[kAhead];
+    RowHead head = load_head(min((int64_t)blockIdx.x, m - 1), cnt, rowStart, ranks, place_of);
+    request_first(row_codes(blockIdx.x), ring);
+    for (int64_t r = blockIdx.x; r < m; r += stride) {
+        const uint8_t* crow = row_codes(r);
+        uint32_t column0 = c0;
+        asm volatile("" : "+v"(column0));  // (columns are counted from here for every row: hoisted, their numbers would take all registers)
+        // f(first column, sixteen codes); behind the row's end stands the most frequent value, which takes no part
+        auto each_sixteen = [&](auto f) {
+            for (uint32_t p0 = 0; p0 < (kPieces > 0 ? 1u : pieces); p0 += kAhead) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) (void)add(counter(q[i >> 2], i & 3));
-    });
-    wave_lds_sync();
-    request_first();
-    // two positions per instruction, four instructions side by side
-    for (uint32_t i = lane; i < eights * kRowCounters; i += 4u * kWave) {
-        uint32_t word[4], incl[4], start[4];
+                for (int d = 0; d < kAhead; ++d) {
+                    const uint32_t p = p0 + d, c = column0 + 16u * p;
+                    if (p >= pieces) break;  // uniform
+                    uint32_t q[4] = {ring[d].x, ring[d].y, ring[d].z, ring[d].w};
+                    if (kPieces == 0) request(crow, p + kAhead, ring[d]);
+                    if (__ballot(c + 16u > n) != 0ull) {
+                        const int left = (int)n - (int)c;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            word[u] = counters[i + u * kWave];
-            start[u] = begin[(i + u * kWave) / kRowCounters];
-        }
+                        for (int i = 0; i < 4; ++i) {
+                            const int bytes = min(max(left - 4 * i, 0), 4);
+                            const uint32_t keep = bytes == 4 ? 0xFFFFFFFFu : (1u << (8 * bytes)) - 1u;
+                            q[i] = (q[i] & keep) | (blank & ~keep);
+                        }
+                    }
+                    f(c, q);
+                }
+            }
+        };
+        for (uint32_t i = lane; i < eights * kRowCounters / 4u; i += kWave) reinterpret_cast<uint4*>(counters)[i] = make_uint4(0, 0, 0, 0);
+        const uint32_t off0 = head.here.y, count = head.next.y - off0;
+        for (uint32_t i = lane; i < eights; i += kWave) begin[i] = i == most ? count : 0u;  // the most frequent value: behind all others
+        emit_row_pointers<uint8_t>(r, head, place_of, Kp, ranks, m, cser, to, [&](uint32_t k, uint32_t pos, uint32_t first) {
+            if (k >= 1u && k < Kp) begin[pos] = first - off0;
+        });
+        wave_lds_sync();
+        // the next row is on its way
+        head = load_head(min(r + stride, m - 1), cnt, rowStart, ranks, place_of);
+        if (kPieces > 0) request_first(row_codes(r + stride), ahead);
+        each_sixteen([&](uint32_t, const uint32_t (&q)[4]) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) incl[u] = (word[u] & 0xFFFFu) + (word[u] >> 16);
+            for (int i = 0; i < 16; ++i) (void)add(counter(q[i >> 2], i & 3));
+        });
+        wave_lds_sync();
+        if (kPieces == 0) request_first(crow, ring);
+        // two positions per instruction, four instructions side by side, the next four on their way from LDS
+        const uint32_t words = eights * kRowCounters;
+        uint32_t word[4], start[4];
+        auto read = [&](uint32_t i) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                word[u] = counters[i + u * kWave];
+                start[u] = begin[(i + u * kWave) / kRowCounters];
+            }
+        };
+        read(lane);
+        for (uint32_t i = lane; i < words; i += 4u * kWave) {
+            uint32_t incl[4], now[4], from[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                now[u] = word[u];
+                from[u] = start[u];
+                incl[u] = (word[u] & 0xFFFFu) + (word[u] >> 16);
+            }
+            read(i + 4u * kWave < words ? i + 4u * kWave : i);
 #define CER_HALF_SCAN(CTRL, ROWS) \
     _Pragma("unroll") for (int u = 0; u < 4; ++u) incl[u] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl[u], CTRL, ROWS, 0xF, false);
-        CER_HALF_SCAN(0x111, 0xF)  // row_shr:1, 2, 4, 8
-        CER_HALF_SCAN(0x112, 0xF)
-        CER_HALF_SCAN(0x114, 0xF)
-        CER_HALF_SCAN(0x118, 0xF)
-        CER_HALF_SCAN(0x142, 0xA)  // row_bcast:15 into rows 1 and 3
+            CER_HALF_SCAN(0x111, 0xF)  // row_shr:1, 2, 4, 8
+            CER_HALF_SCAN(0x112, 0xF)
+            CER_HALF_SCAN(0x114, 0xF)
+            CER_HALF_SCAN(0x118, 0xF)
+            CER_HALF_SCAN(0x142, 0xA)  // row_bcast:15 into rows 1 and 3
 #undef CER_HALF_SCAN
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t lo = word[u] & 0xFFFFu, first = start[u] + incl[u] - lo - (word[u] >> 16);
-            counters[i + u * kWave] = first | ((first + lo) << 16);
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t lo = now[u] & 0xFFFFu, first = from[u] + incl[u] - lo - (now[u] >> 16);
+                counters[i + u * kWave] = first | ((first + lo) << 16);
+            }
         }
-    }
-    wave_lds_sync();
-    // the row lies in LDS as far from a multiple of 16 bytes as in memory
-    uint16_t* colI = reinterpret_cast<uint16_t*>(to.base) + off0;
-    constexpr uint32_t kPer = 8;
-    const uint32_t shift = off0 & (kPer - 1u);
-    uint16_t* stage = reinterpret_cast<uint16_t*>(s_row) + shift;
-    typedef uint16_t __attribute__((address_space(3))) * LdsCol;
-    const uint32_t stage_at = (uint32_t)(uintptr_t)(LdsByte)(unsigned char*)stage;
-    const uint32_t aside = (uint32_t)(uintptr_t)(LdsByte)s_row + stage_bytes - 256u + lane * 4u;
-    each_sixteen([&](uint32_t c, const uint32_t (&q)[4]) {
-        uint32_t old[16];
+        wave_lds_sync();
+        // the row lies in LDS as far from a multiple of 16 bytes as in memory
+        uint16_t* colI = reinterpret_cast<uint16_t*>(to.base) + off0;
+        constexpr uint32_t kPer = 8;
+        const uint32_t shift = off0 & (kPer - 1u);
+        uint16_t* stage = reinterpret_cast<uint16_t*>(s_row) + shift;
+        const uint32_t stage_at = (uint32_t)(uintptr_t)(LdsByte)(unsigned char*)stage;
+        const uint32_t aside = (uint32_t)(uintptr_t)(LdsByte)s_row + stage_bytes - 256u + lane * 4u;
+        each_sixteen([&](uint32_t c, const uint32_t (&q)[4]) {
+            uint32_t old[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) old[i] = add(counter(q[i >> 2], i & 3));
+            for (int i = 0; i < 16; ++i) old[i] = add(counter(q[i >> 2], i & 3));
 #pragma unroll
-        for (uint32_t i = 0; i < 16; ++i)
-            *reinterpret_cast<LdsCol>((uintptr_t)min(stage_at + ((old[i] >> half) & 0xFFFFu) * 2u, aside)) = (uint16_t)(c | i);
-    });
-    wave_lds_sync();
-    const uint32_t total = shift + count;  // in units of columns, from the 16-byte boundary before the row on
-    for (uint32_t v = lane; v * kPer < total; v += kWave) {
-        if (v * kPer >= shift && (v + 1u) * kPer <= total) {
-            reinterpret_cast<uint4*>(colI - shift)[v] = reinterpret_cast<const uint4*>(s_row)[v];
+            for (uint32_t i = 0; i < 16; ++i)
+                *reinterpret_cast<LdsCol>((uintptr_t)min(stage_at + ((old[i] >> half) & 0xFFFFu) * 2u, aside)) = (uint16_t)(c | i);
+        });
+        wave_lds_sync();
+        const uint32_t total = shift + count;  // in units of columns, from the 16-byte boundary before the row on
+        // whole pieces of 16 bytes, four on their way at a time; what lies in front of the first and behind the last one singly
+        const uint32_t v0 = shift != 0u ? 1u : 0u, v1 = total / kPer;
+        for (uint32_t v = v0 + lane; v < v1; v += 4u * kWave) {
+            uint4 q[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) q[u] = reinterpret_cast<const uint4*>(s_row)[min(v + u * kWave, v1 - 1u)];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u)
+                if (v + u * kWave < v1) reinterpret_cast<uint4*>(colI - shift)[v + u * kWave] = q[u];
+        }
+        const uint32_t head_end = v0 <= v1 ? v0 * kPer : total, tail = max(v0, v1) * kPer;
+        if (lane >= shift && lane < min(head_end, total)) colI[lane - shift] = stage[lane - shift];
+        if (v0 <= v1 && tail + lane < total) colI[tail + lane - shift] = stage[tail + lane - shift];
+        wave_lds_sync();
+        if constexpr (kPieces > 0) {
+#pragma unroll
+            for (int d = 0; d < kAhead; ++d) ring[d] = ahead[d];
         } else {
-            for (uint32_t e = max(v * kPer, shift); e < min((v + 1u) * kPer, total); ++e) colI[e - shift] = stage[e - shift];
+            request_first(row_codes(r + stride), ring);
         }
     }
 }
@@ -833,7 +887,11 @@ __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ c
     uint32_t* fill = s_fill[wave];
     unsigned long long* marks = s_marks[wave];
     const uint32_t Kp = st->Kp;
-    emit_row_pointers<OiT>(r, cnt, rowStart, st, m, cser, to, [&](uint32_t k, uint32_t, uint32_t first) { fill[k] = first; });
+    const uint32_t ranks = max(Kp, 1u << to.tab_shift);
+    uint32_t place_of[kCodes / kWave];
+    load_places(st, ranks, place_of);
+    emit_row_pointers<OiT>(r, load_head(r, cnt, rowStart, ranks, place_of), place_of, Kp, ranks, m, cser, to,
+                           [&](uint32_t k, uint32_t, uint32_t first) { fill[k] = first; });
     wave_lds_sync();
     // stable scatter of the row's columns into the buckets
     const uint32_t nbits = 32u - (uint32_t)__builtin_clz(Kp > 1 ? Kp - 1 : 1u);
@@ -1424,12 +1482,19 @@ size_t sorted_lds(int64_t m, int64_t n, uint32_t positions, uint32_t longest, bo
     return !sparse && n >= 1024 && n <= kSortedColumns && lds <= 64 * 1024 && sorted_rows_pay(m, n, positions, lds) ? lds : 0;
 }
 
+// Waves of emit_sorted_kernel that run at once.
+int64_t sorted_waves(size_t lds) {
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
+    return (int64_t)std::max(cus, 1) * (int64_t)(160 * 1024 / lds);
+}
+
 template <typename ColT>
 hipError_t launch_emit(hipStream_t s, const uint8_t* codes, const uint32_t* cnt, const uint2* rowStart, const FrontState* st,
                        int64_t m, int64_t n, int cser, int sparse, const EmitTarget& to, FrontResult* out) {
     if constexpr (sizeof(ColT) == 2) {
         if (const size_t lds = sorted_lds(m, n, out->K, out->max_row_nnz, sparse != 0))
-            return cer::launch_kernel(emit_sorted_kernel, dim3((unsigned)m + 1u), dim3(64), lds, s, codes, cnt, rowStart, st, m, (uint32_t)n, cser,
+            return cer::launch_kernel(n <= 1024 * kSortedPieces ? emit_sorted_kernel<kSortedPieces> : emit_sorted_kernel<0>, dim3((unsigned)std::min<int64_t>(m, sorted_waves(lds)) + 1u), dim3(64), lds, s, codes, cnt, rowStart, st, m, (uint32_t)n, cser,
                                       out->K, emit_stage_bytes(out->max_row_nnz), to, out);
     }
     // rank < K <= 256, so OmegaI is always one byte wide here
