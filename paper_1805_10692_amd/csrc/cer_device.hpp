@@ -348,7 +348,7 @@ hipError_t launch_kernel(void (*kern)(Params...), dim3 grid, dim3 block, size_t 
         values);
 }
 
-inline uint32_t pow2_ceil(uint32_t x) {
+__host__ __device__ inline uint32_t pow2_ceil(uint32_t x) {
     uint32_t p = 1;
     while (p < x) p <<= 1;
     return p;

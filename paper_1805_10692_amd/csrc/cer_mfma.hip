@@ -9,7 +9,7 @@
 // X is loaded D - 1 steps ahead, W one step, and the LDS stores go one step ahead into the other buffer: one barrier per step,
 // no branch in between (rows of X behind the last one read as zeros: buffer loads with bounds).
 // Per wave and 16 k: 3 . 2 . TN matrix instructions of 32 cycles (one-piece codebook) against TN . 3 KiB out of LDS for all four
-// waves and 2 KiB out of L1.  Counters for 512 x 4608, batch 3136 (48 us, 925 TFLOP/s of bf16): matrix pipes busy 47 % of the
+// waves and 2 KiB out of L1.  Counters for 512 x 4608, batch 3136 (44 us, 1010 TFLOP/s of bf16): matrix pipes busy 54 % of the
 // launch, vector ALU 25 % (the splitting: half of the matrix cores' time), LDS 18 %, no bank conflicts, 8.8 TB/s from L2; a wave
 // waits 47 % of its time to issue and 21 % for data -- two waves per SIMD that meet at the matrix pipe, and a barrier per step.
 #include "cer_device.hpp"
@@ -44,25 +44,44 @@ struct Block {
 // Called (by all threads, through a barrier) where X holds infinities, NaNs or numbers that round to infinity (must: some thread
 // has met one), and where a sum is faint -- so small that what the pieces of small inputs lose can show.  Faint sums alone
 // are mostly those of empty rows: the inputs are looked at first (odd: this thread's inputs had third pieces; without them nothing
-// is lost).  A function of its own, and behind the stores, so that nothing of it is held in registers while the matrix cores work.
-// Small inputs could also be caught on their way: 48 -> 53 us for 512 x 4608, batch 3136.
+// is lost), those of the columns with faint sums (small: a bit per 32 columns, this lane's; looking at all of the workgroup's for a
+// single sum took 10 of 48 us: 1204 x 10213, 224 values, batch 245).  A function of its own, and behind the stores, so that nothing of it is
+// held in registers while the matrix cores work, nor fetched by those who do not come here (2 of 19 us: 506 x 987, batch 1870).  Small inputs could also be caught on their way: a tenth more for
+// 512 x 4608, batch 3136.
 // A wave takes tiles of 32 x 32 outputs, 64 or 32 columns of W per step, straight from memory; sums of kFlush columns as below.  Product of
 // 512 x 4608, batch 3136, one-piece codebook: 68 us, 80 with empty rows, 247 with an infinity in X, 331 with X of about 2^-120.
 template <int kForm>
-__device__ __attribute__((noinline)) void exact_block(const Block b, bool must, bool odd) {
+__device__ __attribute__((noinline)) void exact_block(const Block b, bool must, bool odd, uint32_t small) {
     constexpr int PW = weight_planes(kForm), NS = kForm == kUniform ? 2 : 4;  // 16 NS columns of W per step
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
     if (!__syncthreads_or(must)) {
+        if (!__syncthreads_or(odd)) return;
+        uint32_t at = tid % b.cols, step = 256u / b.cols, begin = tid / b.cols;
+        if (__syncthreads_count(small != 0u) < 16) {
+            // few columns: those alone, by all threads (a few sums in a hundred million come out as zero by themselves: most launches
+            // meet none, some one)
+            __shared__ uint32_t s_small[2];
+            if (tid < 2u) s_small[tid] = 0u;
+            __syncthreads();
+#pragma unroll
+            for (uint32_t j = 0; j < 2; ++j)
+                if ((small >> j) & 1u) atomicOr(&s_small[j], 1u << (lane & 31u));
+            __syncthreads();
+            uint64_t columns = s_small[0] | (uint64_t)s_small[1] << 32;
+            const uint32_t count = (uint32_t)__popcll(columns), across = pow2_ceil(count);
+            for (uint32_t i = tid % across % count; i > 0u; --i) columns &= columns - 1u;
+            at = (uint32_t)__builtin_ctzll(columns);
+            step = 256u / across;
+            begin = tid / across;
+        }
+        const uint32_t xcol = min(b.col0 + at, b.L - 1u), last = min(b.k_end, b.n) - 1u;
         bool some = false;
-        if (__syncthreads_or(odd)) {
-            const uint32_t xcol = min(b.col0 + tid % b.cols, b.L - 1u), step = 256u / b.cols;
-            for (uint32_t k0 = b.k_begin + tid / b.cols; k0 < b.k_end; k0 += 16u * step) {
-                float x[16];
+        for (uint32_t k0 = b.k_begin + begin; k0 < b.k_end; k0 += 16u * step) {
+            float x[16];
 #pragma unroll
-                for (uint32_t i = 0; i < 16; ++i) x[i] = b.X[(size_t)min(k0 + i * step, b.n - 1u) * b.L + xcol];
+            for (uint32_t i = 0; i < 16; ++i) x[i] = b.X[(size_t)min(k0 + i * step, last) * b.L + xcol];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) some |= split_lossy(x[i]);
-            }
+            for (int i = 0; i < 16; ++i) some |= split_lossy(x[i]);
         }
         if (!__syncthreads_or(some)) return;
     }
@@ -74,12 +93,12 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
         const uint32_t xoff = (8u * half * b.L + min(c, b.L - 1u)) * 4u;
         floatx16 sum = {}, acc = {};
         uint32_t held = 0;
-        for (uint32_t k0 = b.k_begin; k0 < b.k_end; k0 += 16u * NS) {  // a multiple of 64 columns
+        for (uint32_t k0 = b.k_begin; k0 < b.k_end; k0 += 16u * NS) {  // behind the end: zeros of X
             float x[NS][8];
             uint4 q[NS][PW];
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                const __amdgpu_buffer_rsrc_t xbuf = x_rows(b.X, b.L, k0 + 16 * s, b.n);
+                const __amdgpu_buffer_rsrc_t xbuf = x_rows(b.X, b.L, k0 + 16 * s, min(b.n, b.k_end));
 #pragma unroll
                 for (int i = 0; i < 8; ++i) x[s][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff + i * b.L * 4u, 0, 0));
 #pragma unroll
@@ -175,11 +194,12 @@ struct MfmaTile {
         load_w(k_begin, 0);
         store_x(0, 0);
         __syncthreads();
-        // D steps per round, so that the register slots are named at compile time; k_end - k_begin is a multiple of D BK
+        // D steps per round, so that the register slots are named at compile time; the last round may be shorter
         uint32_t held = 0;
         for (uint32_t k0 = k_begin; k0 < k_end; k0 += D * BK) {
 #pragma unroll
             for (int t = 0; t < D; ++t) {
+                if (D > 2 && t > 0 && k0 + t * BK >= k_end) break;
                 // behind the end: the last step's once more
                 load_x(min(k0 + (t + D - 1) * BK, k_end - BK), (t + D - 1) % D);
                 load_w(min(k0 + (t + 1) * BK, k_end - BK), (t + 1) & 1);
@@ -211,32 +231,41 @@ struct MfmaTile {
     }
 };
 
+// Steps in flight: as many as the registers allow next to TM x TN tiles of sums.
+constexpr int mfma_depth(int form, uint32_t BN) { return form == 1 && BN == 64 ? 4 : 2; }
+
+// Columns by which the parts of a split may differ: a step where a round holds four, else a round (an exit between two steps costs more
+// than it saves: 2271 x 744, three pieces, batch 2961, no split, 79.6 us instead of 74.5).
+constexpr uint32_t mfma_unit(int form, uint32_t BN) { return 2048 / BN * (mfma_depth(form, BN) > 2 ? 1u : 2u); }
+
+// Where a part of the columns begins: the parts differ by one unit of columns at most (a compute unit with two long ones is what a launch
+// waits for: 512 x 4608, batch 3136, five parts of 8, 8, 8, 8 and 4 rounds of 128 columns 48 us, of 29, 29, 29, 29 and 28 steps of 32 44).
+// The first `longer` ones are a unit longer than kchunk.
+template <uint32_t kUnit>
+__device__ __forceinline__ uint32_t part_begin(uint32_t part, uint32_t kchunk, uint32_t longer) {
+    return part * kchunk + min(part, longer) * kUnit;
+}
+
 // D: steps in flight.
 template <int kForm, int TN, int D>
 __global__ __launch_bounds__(256, kForm == 1 ? 2 : 1) void mfma_product_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
-    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, size_t split_stride,
+    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, uint32_t longer, size_t split_stride,
     float faint, float scale) {
     using Tile = MfmaTile<kForm, TN, D>;
     __shared__ Tile tile;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroups are dealt round-robin to the eight XCDs; every XCD takes a contiguous eighth of the list of work items, in
-    // which those that share columns of X (or, with few column tiles, rows of W) are neighbours: they meet in its L2.
+    // which those that share columns of X (or, with few column tiles, rows of W) are neighbours: they meet in its L2.  The parts of a
+    // split come one after the other, so that an XCD reads its parts of W and X only (with the parts inside, all of W: 980 x 12092, 68 values,
+    // batch 333, 73 us the call, now 68; 703 x 12909, 72 values, batch 449, 75, now 70).
     const uint32_t items = row_tiles * col_tiles * splits, eighth = (items + 7u) >> 3;
     const uint32_t item = (blockIdx.x & 7u) * eighth + (blockIdx.x >> 3);
     if ((blockIdx.x >> 3) >= eighth || item >= items) return;
-    uint32_t rt, ct, sp;
-    if (row_tiles <= col_tiles) {
-        rt = item % row_tiles;
-        sp = (item / row_tiles) % splits;
-        ct = item / row_tiles / splits;
-    } else {
-        ct = item % col_tiles;
-        sp = (item / col_tiles) % splits;
-        rt = item / col_tiles / splits;
-    }
+    const uint32_t sp = item / (row_tiles * col_tiles), in = item % (row_tiles * col_tiles);
+    const uint32_t rt = row_tiles <= col_tiles ? in % row_tiles : in / col_tiles, ct = row_tiles <= col_tiles ? in / row_tiles : in % col_tiles;
     const uint32_t row0 = rt * Tile::BM + wave * 64u, col0 = ct * Tile::BN;
-    const uint32_t k_begin = sp * kchunk, k_end = min(pitch, k_begin + kchunk);
+    const uint32_t k_begin = part_begin<mfma_unit(kForm, Tile::BN)>(sp, kchunk, longer), k_end = part_begin<mfma_unit(kForm, Tile::BN)>(sp + 1u, kchunk, longer);
     Out += sp * split_stride;
     const uint16_t* wtile[Tile::TM];
 #pragma unroll
@@ -268,8 +297,19 @@ __global__ __launch_bounds__(256, kForm == 1 ? 2 : 1) void mfma_product_kernel(
                 if (r < m && c < L) Out[(size_t)r * L + c] = sum[i][j][e];
             }
         }
-    if (look)
-        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, rt * Tile::BM, Tile::BM, col0, Tile::BN, k_begin, k_end, scale}, odd != odd, odd != 0.f);
+    if (look) {
+        uint32_t small = 0;  // bit j: a faint sum in column 32 j + lane % 32 (behind the last row at worst one that is none)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            float low = INFINITY;
+#pragma unroll
+            for (int i = 0; i < Tile::TM; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) low = fminf(low, fabsf(sum[i][j][e]));
+            small |= low < faint ? 1u << j : 0u;
+        }
+        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, rt * Tile::BM, Tile::BM, col0, Tile::BN, k_begin, k_end, scale}, odd != odd, odd != 0.f, small);
+    }
 }
 
 // The same for small problems: 64 x 32 CT outputs per workgroup, the four waves share its columns of W (32 at a time, in turn)
@@ -277,7 +317,7 @@ __global__ __launch_bounds__(256, kForm == 1 ? 2 : 1) void mfma_product_kernel(
 // registers, so there is no LDS and no barrier on the way; 128 columns take the workgroup 0.4 - 0.9 us instead of 2.7 (one
 // piece), and a matrix of 600 rows wastes 40 of them instead of 168.  This kernel alone, against the large tiles: 700 x 1200, batch
 // 60: 9 instead of 19 us, 2048 x 2048, batch 16: 4.6 instead of 9.2, 2728 x 3378, batch 115: 16 instead of 20; 512 x 4608, batch
-// 3136: 66 instead of 48.  Bound by the latency of its loads where the chip is not full (2048 x 2048, batch 16, 128 workgroups:
+// 3136: 66 instead of 44.  Bound by the latency of its loads where the chip is not full (2048 x 2048, batch 16, 128 workgroups:
 // matrix pipes busy 6 % of the launch, vector ALU 11 %, half of a wave's time is waiting for data), else by what L2 delivers (80
 // KiB per 128 columns): the larger tile is the better one where it fills the chip.
 template <int kForm, int CT>
@@ -356,16 +396,16 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
 template <int kForm, int CT>
 __global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUniform) && CT == 1) ? 2 : 1) void mfma_small_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
-    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, size_t split_stride,
+    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, uint32_t longer, size_t split_stride,
     float faint, float scale) {
     __shared__ float s_acc[4][2 * CT][16][64];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t items = row_tiles * col_tiles * splits, eighth = (items + 7u) >> 3;
     const uint32_t item = (blockIdx.x & 7u) * eighth + (blockIdx.x >> 3);  // as above
     if ((blockIdx.x >> 3) >= eighth || item >= items) return;
-    const uint32_t rt = item % row_tiles, sp = (item / row_tiles) % splits, ct = item / row_tiles / splits;
+    const uint32_t rt = item % row_tiles, ct = item / row_tiles % col_tiles, sp = item / row_tiles / col_tiles;
     const uint32_t row0 = rt * 64u, col0 = ct * 32u * CT;
-    const uint32_t k_begin = sp * kchunk, k_end = min(pitch, k_begin + kchunk);
+    const uint32_t k_begin = part_begin<128>(sp, kchunk, longer), k_end = part_begin<128>(sp + 1u, kchunk, longer);
     Out += sp * split_stride;
     const uint16_t* wtile[2];
 #pragma unroll
@@ -397,33 +437,49 @@ __global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUnifor
         if (r < m && c < L) Out[(size_t)r * L + c] = y[q];
     }
     if (look)
-        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, row0, 64u, col0, 32u * CT, k_begin, k_end, scale}, odd != odd, odd != 0.f);
+        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, row0, 64u, col0, 32u * CT, k_begin, k_end, scale}, odd != odd, odd != 0.f, least < faint ? 1u << ((wave * PER >> 4) % CT) : 0u);  // (a wave's share lies in one tile)
 }
 
+// The sums of the parts.  Bound by the bytes: four floats per thread and load, four loads in flight; the parts of 512 x 4608, batch 3136
+// (five of 6.4 MB) 6.6 us, with one float per load 8.3.
+typedef float FourFloats __attribute__((ext_vector_type(4), aligned(4)));
 __global__ __launch_bounds__(256) void mfma_sum_kernel(const float* __restrict__ part, float* __restrict__ Y, size_t count,
                                                        uint32_t splits) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4u;
     if (i >= count) return;
-    float a = 0.f, b = 0.f;
+    const float* p = part + i;
+    // (the last thread's four end behind a part by up to three floats: in the next one or in W, which follows the last)
+    FourFloats a = {}, b = {};
     uint32_t s = 0;
-    for (; s + 1 < splits; s += 2) {
-        a += part[(size_t)s * count + i];
-        b += part[(size_t)(s + 1) * count + i];
+    for (; s + 4u <= splits; s += 4u) {
+        FourFloats v[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const FourFloats*>(p + (size_t)(s + k) * count);
+        a += v[0];
+        b += v[1];
+        a += v[2];
+        b += v[3];
     }
-    if (s < splits) a += part[(size_t)s * count + i];
-    Y[i] = a + b;
+    for (; s < splits; ++s) {
+        const FourFloats v = *reinterpret_cast<const FourFloats*>(p + (size_t)s * count);
+        if (s & 1u) b += v; else a += v;
+    }
+    a += b;
+    if (i + 4u <= count) {
+        *reinterpret_cast<FourFloats*>(Y + i) = a;
+    } else {
+        for (uint32_t k = 0; i + k < count; ++k) Y[i + k] = a[k];
+    }
 }
 
-constexpr uint32_t kPitchStep = 128;  // W's rows are padded to a multiple of this many columns: a round of every variant
 
-// Steps in flight: as many as the registers allow next to TM x TN tiles of sums.
-constexpr int mfma_depth(int form, uint32_t BN) { return form == 1 && BN == 64 ? 4 : 2; }
+constexpr uint32_t kPitchStep = 128;  // W's rows are padded to a multiple of this many columns: a round of every variant
 
 int weight_form(const DeviceView& d) { return d.grid.scale != 0.f ? kUniform : d.pieces; }
 
 struct MfmaShape {
     bool small;
-    uint32_t BM, BN, row_tiles, col_tiles, splits, kchunk;
+    uint32_t BM, BN, row_tiles, col_tiles, splits, unit, per, longer;  // parts of `per` units of columns, the first ones of one more
     double us;  // estimate of the product (without the decode)
 };
 
@@ -435,21 +491,23 @@ struct MfmaShape {
 // of the small ones with the launch's; per round of 64 columns of the large ones 2.1 us, of 128 columns of the small ones 1.45).
 void shape_splits(const DeviceView& d, uint32_t L, uint32_t round, double round_us, double alone, double together,
                   double fixed_us, double each_us, MfmaShape* s) {
-    const uint32_t pitch = ((uint32_t)d.n + kPitchStep - 1) / kPitchStep * kPitchStep, rounds = (pitch + round - 1) / round;
+    const uint32_t pitch = ((uint32_t)d.n + kPitchStep - 1) / kPitchStep * kPitchStep, units = pitch / s->unit, rounds = pitch / round;
     s->row_tiles = (uint32_t)((d.m + s->BM - 1) / s->BM);
     s->col_tiles = (L + s->BN - 1) / s->BN;
-    const double tiles = (double)s->row_tiles * s->col_tiles, units = std::max(d.cus, 1);
-    const uint32_t most = (uint32_t)std::min<double>(std::max(1u, rounds / 4), std::max(1.0, 4.0 * units / tiles));
+    const double tiles = (double)s->row_tiles * s->col_tiles, cus = std::max(d.cus, 1);
+    const uint32_t most = (uint32_t)std::min<double>(std::max(1u, rounds / 4), std::max(1.0, 4.0 * cus / tiles));
     s->us = 1e300;
     for (uint32_t sp = 1; sp <= std::min(most, 64u); ++sp) {
-        const uint32_t per = (rounds + sp - 1) / sp, used = (rounds + per - 1) / per;
-        const double share = std::ceil(tiles * used / units);
-        double us = share * (per * round_us * (share < 2 ? alone : together) + each_us) + fixed_us;
-        if (used > 1) us += (each_us > 0 ? 4.0 : 3.0) + (double)used * d.m * L * 8.0 / 6.5e6;
+        const double share = std::ceil(tiles * sp / cus);
+        // rounds of the busiest one (neighbouring parts, long and short ones, overlap; ones after another may all be long)
+        const double own = (together < 1 ? std::ceil(share * units / sp) : share * std::ceil((double)units / sp)) * s->unit / round;
+        double us = own * round_us * (share < 2 ? alone : together) + share * each_us + fixed_us;
+        if (sp > 1) us += (each_us > 0 ? 4.0 : 3.0) + (double)sp * d.m * L * 8.0 / 6.5e6;
         if (us < s->us) {
             s->us = us;
-            s->splits = used;
-            s->kchunk = per * round;
+            s->splits = sp;
+            s->per = units / sp;
+            s->longer = units % sp;
         }
     }
 }
@@ -461,6 +519,7 @@ MfmaShape mfma_shape(const DeviceView& d, uint32_t L) {
     big.small = false;
     big.BN = L <= 32 ? 32 : 64;
     big.BM = 256;
+    big.unit = mfma_unit(form, big.BN);
     {
         const uint32_t round = mfma_depth(form, big.BN) * 2048 / big.BN;  // columns per round of the kernel
         const double flops = 2.0 * big.BM * big.BN * round * products, bytes = (double)round * (big.BM * 2.0 * planes + big.BN * 4.0);
@@ -471,6 +530,7 @@ MfmaShape mfma_shape(const DeviceView& d, uint32_t L) {
     small.small = true;
     small.BN = L <= 32 ? 32 : 64;
     small.BM = 64;
+    small.unit = 128;
     {
         const double flops = 2.0 * small.BM * small.BN * 128 * products;
         shape_splits(d, L, 128, flops / (form == 1 ? 3.5e6 : (planes == 2 ? 2.9e6 : 2.4e6)), form == 1 && small.BN == 64 ? 1.5 : 1.0, 1.0,
@@ -487,7 +547,7 @@ hipError_t launch_shape(const MfmaShape& s, const uint16_t* W, const float* X, f
     auto* kern = s.small ? (s.BN == 32 ? mfma_small_kernel<kForm, 1> : mfma_small_kernel<kForm, 2>)
                          : (s.BN == 32 ? mfma_product_kernel<kForm, 1, mfma_depth(kForm, 32)> : mfma_product_kernel<kForm, 2, mfma_depth(kForm, 64)>);
     return launch_kernel(kern, grid, dim3(256), 0, stream, W, X, out, m, n, L, pitch, plane, s.row_tiles, s.col_tiles, s.splits,
-                         s.kchunk, count, faint, d.grid.scale);
+                         s.per * s.unit, s.longer, count, faint, d.grid.scale);
 }
 
 }  // namespace
@@ -524,7 +584,7 @@ hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L
         }
     }
     if (e == hipSuccess && s.splits > 1)
-        e = launch_kernel(mfma_sum_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, stream, out, Y, count, s.splits);
+        e = launch_kernel(mfma_sum_kernel, dim3((uint32_t)((count + 1023) / 1024)), dim3(256), 0, stream, out, Y, count, s.splits);
     const hipError_t f = (hipError_t)temp_free(tmp, stream);
     return e == hipSuccess ? f : e;
 }

@@ -165,3 +165,29 @@ def test_nothing_behind_the_inputs_reaches_the_result(pieces):
         B.cer_free(h)
         want = W.astype(np.float64) @ X.astype(np.float64)
         assert (np.abs(Y.cpu().numpy() - want) <= 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64))).all()
+
+
+@pytest.mark.parametrize("pieces", list(CODEBOOKS))
+@pytest.mark.parametrize("shape", [(512, 4500, 640), (1100, 1300, 500), (64, 5000, 45), (300, 2200, 20), (512, 3100, 1000)])
+def test_parts_of_unequal_length(shape, pieces):
+    """Splits along n that do not divide it, with a workgroup's outputs once more in binary32 where X asks for it: one column of zeros, one of
+    inputs with bits below the smallest piece, an infinity in the last row.  Bounds as above."""
+    m, n, L = shape
+    rng = np.random.default_rng(n)
+    W = rng.choice(CODEBOOKS[pieces], size=(m, n), p=[0.4, 0.2, 0.2, 0.2]).astype(np.float32)
+    plain = rng.standard_normal((n, L)).astype(np.float32)
+    for what in ("plain", "zeros", "tiny", "infinite"):
+        X = plain.copy()
+        if what == "zeros":
+            X[:, 3] = 0.0
+        if what == "tiny":
+            X[:, 3], X[:, L - 1] = 0.0, X[:, L - 1] * np.float32(2.0 ** -125)
+        if what == "infinite":
+            X[n - 1, L - 2] = np.inf
+        Y = _product(W, CODEBOOKS[pieces], X)
+        with np.errstate(invalid="ignore"):
+            want = W.astype(np.float64) @ X.astype(np.float64)
+            bound = 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64)) + 7 * n * 2.0 ** -150
+        odd = ~np.isfinite(want)
+        assert np.array_equal(Y[odd], want[odd], equal_nan=True), what
+        assert (np.abs(Y[~odd] - want[~odd]) <= bound[~odd]).all(), what
