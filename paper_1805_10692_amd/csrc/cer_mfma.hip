@@ -1,24 +1,27 @@
 // Decode + matrix-core product: Y = W.X with the decoded matrix as bf16 pieces (cer_split3.hpp) and X split into its three
 // pieces on the way into LDS.
 //
-// Workgroup of four waves, one above the other: 256 rows x BN columns of Y, each wave 64 rows, k steps of BK = 2048 / BN.
+// Workgroup of 256 rows x BN columns of Y, k steps of BK = 2048 / BN: four waves of 64 rows each (codebooks of one piece), or eight of 32.
 // W's pieces go from memory straight into the registers of the wave that owns the rows: the decoder has left them in operand
 // order, a tile of 32 rows x 16 columns in 1 KiB (row-major pieces cost four times as many cache lines per load and ran at 40 %
-// of this speed).  X is loaded as fp32, eight rows of one column per thread, split, and stored to LDS as
-// [piece][k / 8][column][8], so that both the stores and the operand reads are 16 bytes per lane at consecutive addresses.
-// X is loaded D - 1 steps ahead, W one step, and the LDS stores go one step ahead into the other buffer: one barrier per step,
-// no branch in between (rows of X behind the last one read as zeros: buffer loads with bounds).
-// Per wave and 16 k: 3 . 2 . TN matrix instructions of 32 cycles (one-piece codebook) against TN . 3 KiB out of LDS for all four
-// waves and 2 KiB out of L1.  Counters for 512 x 4608, batch 3136 (44 us, 1010 TFLOP/s of bf16): matrix pipes busy 54 % of the
-// launch, vector ALU 25 % (the splitting: half of the matrix cores' time), LDS 18 %, no bank conflicts, 8.8 TB/s from L2; a wave
-// waits 47 % of its time to issue and 21 % for data -- two waves per SIMD that meet at the matrix pipe, and a barrier per step.
+// of this speed).  X is loaded as fp32, eight or four rows of one column per thread, split, and stored to LDS as
+// [piece][k / 8][column][8], so that the operand reads are 16 bytes per lane at consecutive addresses.  X is loaded several steps
+// ahead, W one step, and the LDS stores go one or two steps ahead into other buffers: one barrier per step, no branch in between
+// (rows of X behind the last one read as zeros: buffer loads with bounds).
+// Counters for 512 x 4608, batch 3136, one piece (44 us, 1010 TFLOP/s of bf16; 8.8 TB/s from L2): matrix pipes busy 54 % of the launch,
+// vector ALU 25 % (the splitting), LDS 18 %, no bank conflicts; a wave waits 47 % of its time to issue and 17 % for data -- two waves
+// per SIMD that meet at the matrix pipe, and a barrier per step.  Two workgroups of four waves, whose barriers do not meet, are
+// worth 10 us there against one of eight waves of 32 rows (52 us: the operands of X are read twice as often), and as much as one of
+// 512 rows (42 us; but 481 x 6989, batch 1415, 61 us the call instead of 45).  With more pieces the sums take twice the registers, and a
+// SIMD held one wave of 64 rows: two of 32 took 4 - 14 % off the call (703 x 12909, 72 values, batch 449, 70 -> 64 us; 1549 x 4734, 203
+// values, batch 548, 60 -> 54; 2271 x 744, three pieces, batch 2961, 87 -> 78).
 #include "cer_device.hpp"
 #include "cer_split3.hpp"
 
 namespace cer {
 namespace {
 
-constexpr uint32_t kFlush = 256;
+constexpr uint32_t kFlush = 256;  // (kUniform twice that: its flush rounds once more, its large products are short; 2-norm of the error 2 - 5 % less)
 
 // The two sums of mfma_pieces together.  kUniform: times the scale, with one rounding of the larger.
 template <int kForm>
@@ -36,7 +39,7 @@ struct Block {
     const float* X;
     float* Out;
     size_t plane;
-    uint32_t m, n, L, pitch, row0, rows, col0, cols, k_begin, k_end;
+    uint32_t m, n, L, pitch, row0, rows, col0, cols, k_begin, k_end, threads;
     float scale;  // kUniform
 };
 
@@ -56,7 +59,7 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
     if (!__syncthreads_or(must)) {
         if (!__syncthreads_or(odd)) return;
-        uint32_t at = tid % b.cols, step = 256u / b.cols, begin = tid / b.cols;
+        uint32_t at = tid % b.cols, step = b.threads / b.cols, begin = tid / b.cols;
         if (__syncthreads_count(small != 0u) < 16) {
             // few columns: those alone, by all threads (a few sums in a hundred million come out as zero by themselves: most launches
             // meet none, some one)
@@ -71,7 +74,7 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
             const uint32_t count = (uint32_t)__popcll(columns), across = pow2_ceil(count);
             for (uint32_t i = tid % across % count; i > 0u; --i) columns &= columns - 1u;
             at = (uint32_t)__builtin_ctzll(columns);
-            step = 256u / across;
+            step = b.threads / across;
             begin = tid / across;
         }
         const uint32_t xcol = min(b.col0 + at, b.L - 1u), last = min(b.k_end, b.n) - 1u;
@@ -86,7 +89,7 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
         if (!__syncthreads_or(some)) return;
     }
     const uint32_t across = b.cols / 32u;
-    for (uint32_t t = wave; t < b.rows / 32u * across; t += 4u) {
+    for (uint32_t t = wave; t < b.rows / 32u * across; t += b.threads / kWave) {
         const uint32_t row32 = b.row0 + t / across * 32u, c = b.col0 + t % across * 32u + (lane & 31u);
         if (row32 >= b.m) break;
         const uint16_t* w = b.W + (size_t)(row32 >> 5) * 32 * b.pitch;
@@ -132,29 +135,35 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
     }
 }
 
-template <int kForm, int TN, int D>
+constexpr int mfma_waves(int form) { return form == 1 ? 4 : 8; }
+
+template <int kForm, int TN>
 struct MfmaTile {
-    static constexpr int PW = weight_planes(kForm);
-    static constexpr int TM = 2, BM = 256, BN = 32 * TN, BK = 2048 / BN, KG = BK / 8, KS = BK / 16;
-    uint4 b[2][3][KG][BN];
+    static constexpr int PW = weight_planes(kForm), NW = mfma_waves(kForm);
+    static constexpr int TM = kForm == 1 ? 2 : 1, BM = 32 * TM * NW, BN = 32 * TN, BK = 2048 / BN, KG = BK / 8, KS = BK / 16;
+    // Steps of X in registers; steps that its stores are ahead (two: the next step's first operands are read before the barrier, where there
+    // are registers for them) and its loads; rows of X per thread and step, threads per eight of them.
+    static constexpr int D = 4, kAhead = kForm == 1 ? 1 : 2, kFetch = D - 3 + 2 * kAhead, kBuffers = 2 * kAhead, XR = 32 / NW, XP = 8 / XR;
+    uint4 b[kBuffers][3][KG][BN];
 
     // sum: what is finished; acc: the sum over the current kFlush columns or so (a running sum of thousands of terms would
     // round each of them to the size of the whole).  Returns a NaN if this thread's share of X holds numbers without pieces, and
     // 0 if none of them has a third piece.
     __device__ __forceinline__ float run(const uint16_t* const (&wtile)[TM], size_t plane, const float* X, uint32_t n, uint32_t L,
-                                         uint32_t xcol, uint32_t k_begin, uint32_t k_end, floatx16 (&sum)[TM][TN], float scale) {
+                                         uint32_t col0, uint32_t k_begin, uint32_t k_end, floatx16 (&sum)[TM][TN], float scale) {
         const uint32_t tid = threadIdx.x, lane = tid & 63u;
-        const uint32_t xc = tid % BN, xg = tid / BN;  // this thread's share of X: rows 8 xg .. 8 xg + 7 of a step, one column
-        uint32_t xoff[8];
+        // this thread's share of X: rows 8 xg + XR xp .. of a step, one column
+        const uint32_t xp = tid % XP, xc = tid / XP % BN, xg = tid / XP / BN, xcol = min(col0 + xc, L - 1u);
+        uint32_t xoff[XR];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) xoff[i] = ((8u * xg + i) * L + xcol) * 4u;
-        float xr[D][8];
-        uint4 a[2][KS][TM][PW];
+        for (int i = 0; i < XR; ++i) xoff[i] = ((8u * xg + XR * xp + i) * L + xcol) * 4u;
+        float xr[D][XR];
+        uint4 a[2][KS][TM][PW], bb[kAhead][TN][3];
         float odd = 0.f;
         auto load_x = [&](uint32_t k0, int slot) {
             const __amdgpu_buffer_rsrc_t xbuf = x_rows(X, L, k0, n);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) xr[slot][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff[i], 0, 0));
+            for (int i = 0; i < XR; ++i) xr[slot][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff[i], 0, 0));
         };
         auto load_w = [&](uint32_t k0, int slot) {
 #pragma unroll
@@ -166,10 +175,23 @@ struct MfmaTile {
                         a[slot][s][i][p] = reinterpret_cast<const uint4*>(wtile[i] + p * plane + (size_t)(k0 + 16 * s) * 32)[lane];
         };
         auto store_x = [&](int slot, int buf) {
-            uint4 o[3];
-            odd += split3_8(xr[slot], o);
+            if constexpr (XP == 1) {
+                uint4 o[3];
+                odd += split3_8(xr[slot], o);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) b[buf][p][xg][xc] = o[p];
+                for (int p = 0; p < 3; ++p) b[buf][p][xg][xc] = o[p];
+            } else {
+                uint32_t p0[3], p1[3];
+                odd += split3_pair(xr[slot][0], xr[slot][1], p0) + split3_pair(xr[slot][2], xr[slot][3], p1);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) reinterpret_cast<uint2*>(&b[buf][p][xg][xc])[xp] = make_uint2(p0[p], p1[p]);
+            }
+        };
+        auto read_b = [&](int buf, int s, int to) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) bb[to][j][p] = b[buf][p][2 * s + (lane >> 5)][j * 32 + (lane & 31u)];
         };
         floatx16 acc[TM][TN], lo[TM][TN];
         auto clear = [](floatx16 (&v)[TM][TN]) {
@@ -189,37 +211,40 @@ struct MfmaTile {
         clear(acc);
         clear(lo);
         clear(sum);
+        auto at = [&](uint32_t k) { return min(k, k_end - BK); };  // behind the end: the last step's once more
 #pragma unroll
-        for (int s = 0; s + 1 < D; ++s) load_x(k_begin + s * BK, s);
+        for (int t = 0; t < (kFetch < D ? kFetch : D); ++t) load_x(at(k_begin + t * BK), t);
         load_w(k_begin, 0);
-        store_x(0, 0);
+#pragma unroll
+        for (int t = 0; t < kAhead; ++t) store_x(t, t);
+#pragma unroll
+        for (int t = D; t < kFetch; ++t) load_x(at(k_begin + t * BK), t % D);
         __syncthreads();
+        if constexpr (kAhead > 1) read_b(0, 0, 0);
         // D steps per round, so that the register slots are named at compile time; the last round may be shorter
         uint32_t held = 0;
         for (uint32_t k0 = k_begin; k0 < k_end; k0 += D * BK) {
 #pragma unroll
             for (int t = 0; t < D; ++t) {
-                if (D > 2 && t > 0 && k0 + t * BK >= k_end) break;
-                // behind the end: the last step's once more
-                load_x(min(k0 + (t + D - 1) * BK, k_end - BK), (t + D - 1) % D);
-                load_w(min(k0 + (t + 1) * BK, k_end - BK), (t + 1) & 1);
+                if (t > 0 && k0 + t * BK >= k_end) break;
+                load_x(at(k0 + (t + kFetch) * BK), (t + kFetch) % D);
+                load_w(at(k0 + (t + 1) * BK), (t + 1) & 1);
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
-                    uint4 bb[TN][3];
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-#pragma unroll
-                        for (int p = 0; p < 3; ++p) bb[j][p] = b[t & 1][p][2 * s + (lane >> 5)][j * 32 + (lane & 31u)];
+                    const int q = (t * KS + s) % kAhead;
+                    if constexpr (kAhead == 1) read_b(t % kBuffers, s, 0);
+                    else if (s + 1 < KS) read_b(t, s + 1, q ^ 1);
+                    else read_b((t + 1) % kBuffers, 0, q ^ 1);
 #pragma unroll
                     for (int i = 0; i < TM; ++i)
 #pragma unroll
-                        for (int j = 0; j < TN; ++j) mfma_pieces<kForm>(a[t & 1][s][i], bb[j], acc[i][j], lo[i][j]);
+                        for (int j = 0; j < TN; ++j) mfma_pieces<kForm>(a[t & 1][s][i], bb[q][j], acc[i][j], lo[i][j]);
                 }
-                store_x((t + 1) % D, (t + 1) & 1);
+                store_x((t + kAhead) % D, (t + kAhead) % kBuffers);
                 __syncthreads();
             }
             held += D * BK;
-            if (held >= kFlush) {
+            if (held >= (kForm == kUniform ? 2u * kFlush : kFlush)) {
                 held = 0;
                 flush();
                 clear(acc);
@@ -231,13 +256,6 @@ struct MfmaTile {
     }
 };
 
-// Steps in flight: as many as the registers allow next to TM x TN tiles of sums.
-constexpr int mfma_depth(int form, uint32_t BN) { return form == 1 && BN == 64 ? 4 : 2; }
-
-// Columns by which the parts of a split may differ: a step where a round holds four, else a round (an exit between two steps costs more
-// than it saves: 2271 x 744, three pieces, batch 2961, no split, 79.6 us instead of 74.5).
-constexpr uint32_t mfma_unit(int form, uint32_t BN) { return 2048 / BN * (mfma_depth(form, BN) > 2 ? 1u : 2u); }
-
 // Where a part of the columns begins: the parts differ by one unit of columns at most (a compute unit with two long ones is what a launch
 // waits for: 512 x 4608, batch 3136, five parts of 8, 8, 8, 8 and 4 rounds of 128 columns 48 us, of 29, 29, 29, 29 and 28 steps of 32 44).
 // The first `longer` ones are a unit longer than kchunk.
@@ -246,13 +264,12 @@ __device__ __forceinline__ uint32_t part_begin(uint32_t part, uint32_t kchunk, u
     return part * kchunk + min(part, longer) * kUnit;
 }
 
-// D: steps in flight.
-template <int kForm, int TN, int D>
-__global__ __launch_bounds__(256, kForm == 1 ? 2 : 1) void mfma_product_kernel(
+template <int kForm, int TN>
+__global__ __launch_bounds__(64 * mfma_waves(kForm), 2) void mfma_product_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
     uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, uint32_t longer, size_t split_stride,
     float faint, float scale) {
-    using Tile = MfmaTile<kForm, TN, D>;
+    using Tile = MfmaTile<kForm, TN>;
     __shared__ Tile tile;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroups are dealt round-robin to the eight XCDs; every XCD takes a contiguous eighth of the list of work items, in
@@ -264,15 +281,14 @@ __global__ __launch_bounds__(256, kForm == 1 ? 2 : 1) void mfma_product_kernel(
     if ((blockIdx.x >> 3) >= eighth || item >= items) return;
     const uint32_t sp = item / (row_tiles * col_tiles), in = item % (row_tiles * col_tiles);
     const uint32_t rt = row_tiles <= col_tiles ? in % row_tiles : in / col_tiles, ct = row_tiles <= col_tiles ? in / row_tiles : in % col_tiles;
-    const uint32_t row0 = rt * Tile::BM + wave * 64u, col0 = ct * Tile::BN;
-    const uint32_t k_begin = part_begin<mfma_unit(kForm, Tile::BN)>(sp, kchunk, longer), k_end = part_begin<mfma_unit(kForm, Tile::BN)>(sp + 1u, kchunk, longer);
+    const uint32_t row0 = rt * Tile::BM + wave * 32u * Tile::TM, col0 = ct * Tile::BN;
+    const uint32_t k_begin = part_begin<Tile::BK>(sp, kchunk, longer), k_end = part_begin<Tile::BK>(sp + 1u, kchunk, longer);
     Out += sp * split_stride;
     const uint16_t* wtile[Tile::TM];
 #pragma unroll
     for (int i = 0; i < Tile::TM; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * 32 * pitch;
-    const uint32_t xcol = min(col0 + tid % Tile::BN, L - 1u);
     floatx16 sum[Tile::TM][TN];
-    const float odd = tile.run(wtile, plane, X, n, L, xcol, k_begin, k_end, sum, scale);
+    const float odd = tile.run(wtile, plane, X, n, L, col0, k_begin, k_end, sum, scale);
 
     // The vote comes before the stores (behind them: 2 us more).
     float least = INFINITY;
@@ -308,7 +324,7 @@ __global__ __launch_bounds__(256, kForm == 1 ? 2 : 1) void mfma_product_kernel(
                 for (int e = 0; e < 16; ++e) low = fminf(low, fabsf(sum[i][j][e]));
             small |= low < faint ? 1u << j : 0u;
         }
-        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, rt * Tile::BM, Tile::BM, col0, Tile::BN, k_begin, k_end, scale}, odd != odd, odd != 0.f, small);
+        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, rt * Tile::BM, Tile::BM, col0, Tile::BN, k_begin, k_end, 64u * mfma_waves(kForm), scale}, odd != odd, odd != 0.f, small);
     }
 }
 
@@ -437,7 +453,7 @@ __global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUnifor
         if (r < m && c < L) Out[(size_t)r * L + c] = y[q];
     }
     if (look)
-        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, row0, 64u, col0, 32u * CT, k_begin, k_end, scale}, odd != odd, odd != 0.f, least < faint ? 1u << ((wave * PER >> 4) % CT) : 0u);  // (a wave's share lies in one tile)
+        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, row0, 64u, col0, 32u * CT, k_begin, k_end, 256u, scale}, odd != odd, odd != 0.f, least < faint ? 1u << ((wave * PER >> 4) % CT) : 0u);  // (a wave's share lies in one tile)
 }
 
 // The sums of the parts.  Bound by the bytes: four floats per thread and load, four loads in flight; the parts of 512 x 4608, batch 3136
@@ -488,7 +504,7 @@ struct MfmaShape {
 // Measured per unit: 4.1 - 4.7 TFLOP/s with BN = 64, bound by the operands' bytes with
 // BN = 32; the small tiles 2.4 - 3.5 TFLOP/s.  A split along n costs its partial sums, written and read again.
 // each_us: what a workgroup takes besides its rounds, kUniform only, fitted with the rates to 60 products (8.8 us of the large tiles, 6.5
-// of the small ones with the launch's; per round of 64 columns of the large ones 2.1 us, of 128 columns of the small ones 1.45).
+// of the small ones with the launch's; per 64 columns of the large ones 2.05 us, per 128 of the small ones 1.45).
 void shape_splits(const DeviceView& d, uint32_t L, uint32_t round, double round_us, double alone, double together,
                   double fixed_us, double each_us, MfmaShape* s) {
     const uint32_t pitch = ((uint32_t)d.n + kPitchStep - 1) / kPitchStep * kPitchStep, units = pitch / s->unit, rounds = pitch / round;
@@ -519,11 +535,11 @@ MfmaShape mfma_shape(const DeviceView& d, uint32_t L) {
     big.small = false;
     big.BN = L <= 32 ? 32 : 64;
     big.BM = 256;
-    big.unit = mfma_unit(form, big.BN);
+    big.unit = 2048 / big.BN;
     {
-        const uint32_t round = mfma_depth(form, big.BN) * 2048 / big.BN;  // columns per round of the kernel
+        const uint32_t round = (form == 1 && big.BN == 64 ? 4 : 2) * 2048 / big.BN;  // a part has at least four times as many columns
         const double flops = 2.0 * big.BM * big.BN * round * products, bytes = (double)round * (big.BM * 2.0 * planes + big.BN * 4.0);
-        shape_splits(d, L, round, big.BN == 32 ? std::max(flops / (form == kUniform ? 4.0e6 : 4.3e6), bytes / 3.0e4) : flops / (form == kUniform ? 4.1e6 : 4.4e6),
+        shape_splits(d, L, round, big.BN == 32 ? std::max(flops / (form == kUniform ? 4.0e6 : 4.3e6), bytes / 3.0e4) : flops / (form == 1 ? 4.4e6 : (form == kUniform ? 4.2e6 : 4.6e6)),
                      form == 1 ? 1.12 : 1.0, form == 1 ? 0.95 : 1.0, form == kUniform ? 2.5 : 4.0, form == kUniform ? 6.5 : 0.0, &big);
     }
     MfmaShape small;
@@ -545,8 +561,8 @@ hipError_t launch_shape(const MfmaShape& s, const uint16_t* W, const float* X, f
     const dim3 grid((s.row_tiles * s.col_tiles * s.splits + 7) / 8 * 8);
     const size_t count = (size_t)m * L;
     auto* kern = s.small ? (s.BN == 32 ? mfma_small_kernel<kForm, 1> : mfma_small_kernel<kForm, 2>)
-                         : (s.BN == 32 ? mfma_product_kernel<kForm, 1, mfma_depth(kForm, 32)> : mfma_product_kernel<kForm, 2, mfma_depth(kForm, 64)>);
-    return launch_kernel(kern, grid, dim3(256), 0, stream, W, X, out, m, n, L, pitch, plane, s.row_tiles, s.col_tiles, s.splits,
+                         : (s.BN == 32 ? mfma_product_kernel<kForm, 1> : mfma_product_kernel<kForm, 2>);
+    return launch_kernel(kern, grid, dim3(s.small ? 256 : 64 * mfma_waves(kForm)), 0, stream, W, X, out, m, n, L, pitch, plane, s.row_tiles, s.col_tiles, s.splits,
                          s.per * s.unit, s.longer, count, faint, d.grid.scale);
 }
 
