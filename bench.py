@@ -76,10 +76,13 @@ def make_workload(name: str):
     raise SystemExit(f"unknown workload {name}")
 
 
-def kernel_name(fmt: str, L: int, path, K: int = 0, n: int = 0, narrow: int = 0, fused: int = 0) -> str:
+def kernel_name(fmt: str, L: int, path, K: int = 0, n: int = 0, narrow: int = 0, fused: int = 0,
+                tile: int = 0) -> str:
     """The kernel that dominates a product (cer_matmul_path's numbering for cer / cser).  Batch 1: handles of 2 - 256
-    values whose X fits in LDS (every benchmark configuration) run the rank-table kernel.  narrow, fused: what
-    cer_matmul_narrow_columns and cer_matmul_fused_rows say."""
+    values whose X fits in LDS (every benchmark configuration) run the rank-table kernel.  narrow, fused, tile: what
+    cer_matmul_narrow_columns, cer_matmul_fused_rows and cer_matmul_tile_columns say."""
+    if tile:
+        return "cer_tile_kernel"
     if fused:
         return "cer_fused_kernel"
     if narrow:
@@ -282,6 +285,7 @@ def run_one(name: str, fmt: str, steps: int, warmup: int, warm: bool, with_cpu: 
         "path": None if fmt == "csr" else B.cer_matmul_path_ex(h0, L, opts),
         "narrow_columns": 0 if fmt == "csr" or opts is not None else B.cer_matmul_narrow_columns(h0, L),
         "fused_rows": 0 if fmt == "csr" or opts is not None else B.cer_matmul_fused_rows(h0, L),
+        "tile_columns": 0 if fmt == "csr" or opts is not None else B.cer_matmul_tile_columns(h0, L),
     }
     for h in handles[1:]:
         free(h)
@@ -534,7 +538,8 @@ def main() -> int:
                                      "k_bar", "k_tilde", "cache_state", "path")},
         "roofline": {"bound": "hbm", "achieved": r["algorithmic_GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": r["algorithmic_GBps"] / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_source,
-                     "kernel": kernel_name(args.format, r["L"], r["path"], r["K"], r["n"], r["narrow_columns"], r["fused_rows"]),
+                     "kernel": kernel_name(args.format, r["L"], r["path"], r["K"], r["n"], r["narrow_columns"], r["fused_rows"],
+                                           r["tile_columns"]),
                      "algorithmic_bytes_per_launch": r["algorithmic_bytes"],
                      "event_us_per_launch": r["event_ms_per_step"] * 1e3},
         "cpu_baseline": r.get("cpu_baseline"),

@@ -108,7 +108,7 @@ hipError_t launch_colsum(const float* X, uint32_t n, uint32_t L, float* part, ui
 // stream-ordered temporary (bounded here) and multiplied on the matrix cores: as bf16 pieces (cer_mfma.hip: 2 to 6 bytes per
 // element written, three to six products at about 900 TFLOP/s), or, where the values or the sizes rule that out, as fp32 (4 bytes
 // per element; 90 - 120 TFLOP/s).  Measured on MI355X, gathers against decode + product: 3x3 convolution shape (60 % zeros)
-// batch 3136 391 / 58 us (fp32: 149 us); 7-bit quantizer of the same shape 550 / 112 us.
+// batch 3136 391 / 53 us (fp32: 149 us).
 //
 // Estimated duration (seconds) of the kernel that gathers from L2.
 //   * bytes and steps: gemm_gather_us (lines per index, gather instructions, the walk of the longest row: 543 x 7364, batch 28, 4900
@@ -208,7 +208,7 @@ int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o,
     // gathers from L2 and below that of decode + product, if the latter pays: wide batches of large matrices.  Measured, gathers /
     // strips: AlexNet-fc6 shape, batch 8 / 16 / 32 / 64 / 100 / 128: 30 / 31 / 32 / 57 / 114 / 106 against 15 / 16 / 22 / 34 / 58 / 59
     // us; VGG-fc6 shape, batch 8 / 16 / 64 / 128: 27 / 28 / 53 / 99 against 17 / 18 / 39 / 76 us (batch 32: 30 against 25 us, but the
-    // estimate keeps the gathers); 3x3 convolution shape, batch 3136: 191 us against 58 us decoded and multiplied.
+    // estimate keeps the gathers); 3x3 convolution shape, batch 3136: 191 us against 53 us decoded and multiplied.
     if (o.path < 0 && !no_temporaries && has_elements) {
         double t_gather = 0, t_dense = 0;
         const bool dense_ok = densify_estimates(d, L, &t_gather, &t_dense);

@@ -16,7 +16,7 @@
 // (decoded matrix) -> 42; 1529 x 862, 38 values, batch 167 19.9 (gathers) -> 11.2; 1103 x 14914, 5 values, batch 42 33.6 (one launch) -> 24.7; 100
 // random products of prepared handles: 33 change their kernel, 1.26 times the speed in the geometric mean.
 // What bounds it: 4096 x 9216, batch 99, 68000 clocks: start-up 7500 (bounds, entries and X one after the other from memory), sums 5300;
-// between them the matrix pipes are busy 60 % -- while they are, a SIMD issues other vector instructions every nine clocks only and dot
+// between them the matrix pipes are busy half the time -- while they are, a SIMD issues other vector instructions every nine clocks only and dot
 // products (the splitting) every 22.
 // Errors against fp64 are 0.45 of the replaced kernels' in the mean, at most 0.94 (2-norm; 33 products, X normal, cut at 0, |x| + 1): short
 // running sums per wave, the small products apart, the waves' and the parts' sums in binary64.
