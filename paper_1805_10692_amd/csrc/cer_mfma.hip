@@ -96,7 +96,7 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
         const uint32_t xoff = (8u * half * b.L + min(c, b.L - 1u)) * 4u;
         floatx16 sum = {}, acc = {};
         uint32_t held = 0;
-        for (uint32_t k0 = b.k_begin; k0 < b.k_end; k0 += 16u * NS) {  // behind the end: zeros of X
+        for (uint32_t k0 = b.k_begin; k0 < b.k_end; k0 += 16u * NS) {  // behind the end: zeros of X, W's last columns once more
             float x[NS][8];
             uint4 q[NS][PW];
 #pragma unroll
@@ -105,7 +105,7 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
 #pragma unroll
                 for (int i = 0; i < 8; ++i) x[s][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff + i * b.L * 4u, 0, 0));
 #pragma unroll
-                for (int p = 0; p < PW; ++p) q[s][p] = reinterpret_cast<const uint4*>(w + p * b.plane + (size_t)(k0 + 16 * s) * 32)[lane];
+                for (int p = 0; p < PW; ++p) q[s][p] = reinterpret_cast<const uint4*>(w + p * b.plane + (size_t)min(k0 + 16 * s, b.pitch - 16u) * 32)[lane];
             }
 #pragma unroll
             for (int s = 0; s < NS; ++s)

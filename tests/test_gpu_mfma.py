@@ -168,10 +168,11 @@ def test_nothing_behind_the_inputs_reaches_the_result(pieces):
 
 
 @pytest.mark.parametrize("pieces", list(CODEBOOKS))
-@pytest.mark.parametrize("shape", [(512, 4500, 640), (1100, 1300, 500), (64, 5000, 45), (300, 2200, 20), (512, 3100, 1000), (58000, 50, 10), (289, 33, 1000)])
+@pytest.mark.parametrize("shape", [(512, 4500, 640), (1100, 1300, 500), (64, 5000, 45), (300, 2200, 20), (512, 3100, 1000), (58000, 50, 10), (289, 33, 1000), (1030, 3100, 2000)])
 def test_parts_of_unequal_length(shape, pieces):
     """Splits along n that do not divide it, with a workgroup's outputs once more in binary32 where X asks for it: one column of zeros, one of
-    inputs with bits below the smallest piece, an infinity in the last row.  Bounds as above."""
+    inputs with bits below the smallest piece, an infinity in the last row.  Bounds as above.  (1030, 3100, 2000): the last part has an odd
+    number of steps, and the last tile of rows ends where the pieces of W do."""
     m, n, L = shape
     rng = np.random.default_rng(n)
     W = rng.choice(CODEBOOKS[pieces], size=(m, n), p=[0.4, 0.2, 0.2, 0.2]).astype(np.float32)
