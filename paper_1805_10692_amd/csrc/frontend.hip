@@ -374,7 +374,7 @@ __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W,
 }
 
 // ------------------------------------------------------------------------------------------------
-// layout: per row, the number of indexed elements, of groups and of non-empty groups.  One wave per row, sixteen rows per
+// layout: per row, the number of indexed elements, of groups and of non-empty groups.  One wave per kRows rows, sixteen waves per
 // workgroup; every workgroup first ranks the values for itself, and the last one to finish scans the rows (two launches less
 // than kernels of their own: 20 of the 70 us that a layer of 300 x 700 took went into such steps).
 //
@@ -387,6 +387,34 @@ __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W,
 // ------------------------------------------------------------------------------------------------
 constexpr int kScanRows = 4;
 
+// Of a wave's lanes up to the own one: sums of 64 bits (cer::wave_inclusive_scan takes 32), and the largest.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long lanes_before(unsigned long long x) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), CTRL, ROWS, 0xF, false);
+    return (unsigned long long)hi << 32 | lo;
+}
+__device__ __forceinline__ unsigned long long wave_scan64(unsigned long long x) {
+    x += lanes_before<0x111, 0xF>(x);  // row_shr:1, 2, 4, 8
+    x += lanes_before<0x112, 0xF>(x);
+    x += lanes_before<0x114, 0xF>(x);
+    x += lanes_before<0x118, 0xF>(x);
+    x += lanes_before<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
+    x += lanes_before<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+__device__ __forceinline__ uint32_t wave_largest(uint32_t x) {  // in the last lane
+#define CER_MAX_STEP(CTRL, ROWS) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false));
+    CER_MAX_STEP(0x111, 0xF)
+    CER_MAX_STEP(0x112, 0xF)
+    CER_MAX_STEP(0x114, 0xF)
+    CER_MAX_STEP(0x118, 0xF)
+    CER_MAX_STEP(0x142, 0xA)
+    CER_MAX_STEP(0x143, 0xC)
+#undef CER_MAX_STEP
+    return x;
+}
+
 __device__ void scan_rows(const unsigned long long* rowGN, int64_t m, uint2* __restrict__ rowStart, FrontState* __restrict__ st,
                           FrontResult* __restrict__ out) {
     __shared__ unsigned long long s_g[16], s_n[16], s_p[16];
@@ -394,6 +422,7 @@ __device__ void scan_rows(const unsigned long long* rowGN, int64_t m, uint2* __r
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     unsigned long long carry_g = 0, carry_n = 0, my_p = 0;
     uint32_t my_mx = 0, my_ml = 0;
+    const uint32_t flags = st->flags, K = st->K, Kp = st->Kp;  // on their way with the first rows
     for (int64_t base = 0; base < m; base += 1024 * kScanRows) {
         const int64_t r0 = base + (int64_t)t * kScanRows;
         uint2 v[kScanRows];
@@ -412,15 +441,7 @@ __device__ void scan_rows(const unsigned long long* rowGN, int64_t m, uint2* __r
             g += v[k].x;
             nn += v[k].y;
         }
-        unsigned long long ig = g, in_ = nn;  // inclusive scans inside the wave
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const unsigned long long ug = __shfl_up(ig, off, kWave), un = __shfl_up(in_, off, kWave);
-            if ((int)lane >= off) {
-                ig += ug;
-                in_ += un;
-            }
-        }
+        const unsigned long long ig = wave_scan64(g), in_ = wave_scan64(nn);  // inside the wave
         if (lane == 63) {
             s_g[wave] = ig;
             s_n[wave] = in_;
@@ -445,13 +466,10 @@ __device__ void scan_rows(const unsigned long long* rowGN, int64_t m, uint2* __r
         }
         __syncthreads();
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        my_p += __shfl_xor(my_p, off, kWave);
-        my_mx = max(my_mx, (uint32_t)__shfl_xor((int)my_mx, off, kWave));
-        my_ml = max(my_ml, (uint32_t)__shfl_xor((int)my_ml, off, kWave));
-    }
-    if (lane == 0) {
+    my_p = wave_scan64(my_p);
+    my_mx = wave_largest(my_mx);
+    my_ml = wave_largest(my_ml);
+    if (lane == 63) {
         s_p[wave] = my_p;
         s_mx[wave] = my_mx;
         s_ml[wave] = my_ml;
@@ -468,9 +486,9 @@ __device__ void scan_rows(const unsigned long long* rowGN, int64_t m, uint2* __r
         rowStart[m] = make_uint2((uint32_t)carry_g, (uint32_t)carry_n);
         // the product kernels address colI and OmegaPtr with 32-bit offsets and read ahead of a row's end
         const unsigned long long limit = 0xFFFFFFFFull - 65536;
-        out->flags = st->flags | (carry_g > limit || carry_n > limit ? kFlagTooLarge : 0u);
-        out->K = st->K;
-        out->Kp = st->Kp;
+        out->flags = flags | (carry_g > limit || carry_n > limit ? kFlagTooLarge : 0u);
+        out->K = K;
+        out->Kp = Kp;
         out->max_row_groups = mx;
         out->max_row_nnz = ml;
         out->nnz = carry_n;
@@ -480,6 +498,12 @@ __device__ void scan_rows(const unsigned long long* rowGN, int64_t m, uint2* __r
     }
 }
 
+// Bound by a chain of steps (values ranked, the arrivals, the scan), of which only the arrivals grow with the workgroups: beyond kFewRows
+// rows a wave takes four (the call for 4096 x 9216, 7 bits, with one / two / four / eight rows per wave 187.0 / 185.5 / 184.5 / 185.0 us; 188.3
+// when one row per wave went with shuffles in place of DPP), below one: 2000 x 5000, 8 bits, 110.3 / 110.4 / 110.3 / 111.8, 1024 x 2048, 5 bits, 65.9 /
+// 66.2 / 66.7 / 68.6.
+constexpr int64_t kFewRows = 2048;
+template <int kRows>
 __global__ __launch_bounds__(1024) void row_layout_kernel(const uint32_t* __restrict__ cnt, const unsigned long long* __restrict__ hist,
                                                           int64_t m, int cser, FrontState* __restrict__ st, unsigned long long* __restrict__ rowGN,
                                                           uint2* __restrict__ rowStart, FrontResult* __restrict__ out) {
@@ -488,11 +512,13 @@ __global__ __launch_bounds__(1024) void row_layout_kernel(const uint32_t* __rest
     __shared__ uint32_t s_rank[kCodes];
     __shared__ uint32_t s_last;
     const uint32_t t = threadIdx.x, lane = t & 63u, pos = t & 255u, sub = t >> 8, K = st->K;
-    // the row's histogram is on its way while the values are ranked
-    const int64_t r = (int64_t)blockIdx.x * 16 + (t >> 6);
-    uint32_t c4[kCodes / kWave];
+    // the rows' histograms are on their way while the values are ranked
+    const int64_t r0 = ((int64_t)blockIdx.x * 16 + (t >> 6)) * kRows;
+    uint32_t c4[kRows][kCodes / kWave];
 #pragma unroll
-    for (int i = 0; i < kCodes / kWave; ++i) c4[i] = cnt[min(r, m - 1) * kCodes + lane + 64u * i];
+    for (int k = 0; k < kRows; ++k)
+#pragma unroll
+        for (int i = 0; i < kCodes / kWave; ++i) c4[k][i] = cnt[min(r0 + k, m - 1) * kCodes + lane + 64u * i];
     {
         unsigned long long s = 0;
 #pragma unroll
@@ -528,24 +554,25 @@ __global__ __launch_bounds__(1024) void row_layout_kernel(const uint32_t* __rest
     }
     if (blockIdx.x == 0 && t == 0) st->Kp = (uint32_t)occurring;
     __syncthreads();
-    uint32_t present = 0, topk = 0, nn = 0;
+    uint32_t rank[kCodes / kWave];
 #pragma unroll
-    for (int i = 0; i < kCodes / kWave; ++i) {
-        const uint32_t k = s_rank[lane + 64u * i];
-        if (c4[i] > 0 && k >= 1) {
-            ++present;
-            topk = max(topk, k);
-            nn += c4[i];
-        }
-    }
+    for (int i = 0; i < kCodes / kWave; ++i) rank[i] = s_rank[lane + 64u * i];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        present += __shfl_xor(present, off, kWave);
-        nn += __shfl_xor(nn, off, kWave);
-        topk = max(topk, (uint32_t)__shfl_xor((int)topk, off, kWave));
+    for (int k = 0; k < kRows; ++k) {
+        uint32_t present = 0, topk = 0, nn = 0;
+#pragma unroll
+        for (int i = 0; i < kCodes / kWave; ++i)
+            if (c4[k][i] > 0 && rank[i] >= 1) {
+                ++present;
+                topk = max(topk, rank[i]);
+                nn += c4[k][i];
+            }
+        present = cer::wave_inclusive_scan(present);
+        nn = cer::wave_inclusive_scan(nn);
+        topk = wave_largest(topk);
+        // groups (CER keeps the empty groups below the row's highest rank) | non-empty groups << 16, indexed elements
+        if (lane == 63u && r0 + k < m) rowGN[r0 + k] = ((unsigned long long)nn << 32) | (cser ? present : topk) | (present << 16);
     }
-    // groups (CER keeps the empty groups below the row's highest rank) | non-empty groups << 16, indexed elements
-    if (lane == 0 && r < m) rowGN[r] = ((unsigned long long)nn << 32) | (cser ? present : topk) | (present << 16);
     // The last workgroup to arrive scans the rows.  Thread 0 publishes what the workgroup's threads have written in front of the
     // barrier and takes what the others have: one release and one acquire per workgroup.  (Each release writes an L2 back: 4096
     // rows 16 -> 18 us against relaxed accesses past the caches, which nothing orders; a fence per wave took 80 us.)
@@ -1651,8 +1678,9 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     int rc = run_codes(W, N, m, n, codebook, K, bits, s, sd, reinterpret_cast<float4*>(tp + off_part), codes_d, cnt_d, hist, nullptr);
     if (rc != CER_OK) return rc;
     box.busy = true;
-    HIP_TRY(launch_kernel(row_layout_kernel, dim3((unsigned)((m + 15) / 16)), dim3(1024), 0, s, cnt_d, hist, m, cser ? 1 : 0, sd, rowGN,
-                          rowStart, box.p));
+    const int64_t rows_each = m > kFewRows ? 4 : 1;
+    HIP_TRY(launch_kernel(rows_each > 1 ? row_layout_kernel<4> : row_layout_kernel<1>, dim3((unsigned)((m + 16 * rows_each - 1) / (16 * rows_each))),
+                          dim3(1024), 0, s, cnt_d, hist, m, cser ? 1 : 0, sd, rowGN, rowStart, box.p));
     HIP_TRY(box.wait(s));
     const FrontResult& h = *box.p;
     rc = flags_to_error(h.flags);

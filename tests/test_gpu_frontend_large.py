@@ -48,3 +48,21 @@ def test_sorted_rows(shape, fmt):
         assert np.array_equal(B.cer_get_array(h, which), B.cer_get_array(host, which)), which
     B.cer_free(h)
     B.cer_free(host)
+
+
+@pytest.mark.parametrize("m", [2048, 2049, 2051, 2111, 2112, 2113, 8191])
+@pytest.mark.parametrize("fmt", ["cer", "cser"])
+def test_rows_per_wave_of_the_layout(m, fmt):
+    """Row counts around the 2048 from which on a wave lays out four rows, and around the 64 of a workgroup; rows of one value among them."""
+    n, K = 37, 200
+    rng = np.random.default_rng(m)
+    cb = (np.arange(K) - 3).astype(np.float32)
+    W = cb[np.minimum(rng.geometric(0.2, size=(m, n)) - 1, K - 1)]
+    W[rng.integers(0, m, 20)] = cb[0]
+    W[m - 1], W[0] = cb[K - 1], cb[1]
+    host = (B.cer_encode if fmt == "cer" else B.cser_encode)(W, cb)
+    h = B.cer_encode_device(torch.from_numpy(W).cuda(), m, n, cb, fmt)
+    for which in (B.CER_ARRAY_OMEGA, B.CER_ARRAY_COLI, B.CER_ARRAY_OMEGAPTR, B.CER_ARRAY_ROWPTR) + ((B.CER_ARRAY_OMEGAI,) if fmt == "cser" else ()):
+        assert np.array_equal(B.cer_get_array(h, which), B.cer_get_array(host, which)), which
+    B.cer_free(h)
+    B.cer_free(host)
