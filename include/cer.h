@@ -452,8 +452,8 @@ int cer_quantize_encode_device(const float* W_dev, int64_t m, int64_t n, int32_t
 int cer_decode_device(const cer_handle_t* h, float* W_dev_out, void* stream);
 
 /* Which of its two kernels the device front-end writes the arrays with, given the handle's matrix and a codebook of K values: 1 where
- * it sorts rows in LDS (half or more of the elements indexed, 16-bit column indices, the longest row's indices and 32 counters per
- * value within 64 KiB -- rows of up to about 64000 columns --, where it is estimated to be ahead), else 0.
+ * it sorts rows in LDS (1024 to 64512 columns, 16-bit column indices, the longest row's indices and 32 counters per value within 64
+ * KiB, where it is estimated to be ahead), else 0.
  * Errors: CER_E_INVALID, CER_E_HIP (no device copy). */
 int cer_encode_sorts_rows(const cer_handle_t* h, int32_t K);
 

@@ -721,8 +721,8 @@ __device__ __forceinline__ void emit_row_pointers(int64_t r, const RowHead& head
 // with a workgroup per row that loads its codes twice); 3400 clocks of LDS instructions per row (an add 5, a store to any place 6), twice
 // that with five waves to hide their latency.  Where all rows run at once the gain is larger: 300 x 9000 115 -> 89 us.
 constexpr uint32_t kRowCounters = 32;  // words of counters per codebook position
-// 64 runs of a multiple of 16 columns: below 65536, so that slots fit 16 bits.  Half of a row's columns have to fit 64 KiB with the
-// counters (sorted_lds), which ends at about 64000 columns already.
+// 64 runs of a multiple of 16 columns: below 65536, so that slots fit 16 bits (the most frequent value's lie behind all others: a row has
+// as many slots as columns).
 constexpr int64_t kSortedColumns = 64512;
 constexpr int kSortedPieces = 12;  // sixteens of columns per lane that stay in registers
 inline uint32_t emit_stage_bytes(uint32_t longest) { return ((longest * 2u + 16u + 15u) & ~15u) + 256u; }
@@ -1488,25 +1488,32 @@ int flags_to_error(uint32_t flags) {
 
 bool mostly_implicit(int64_t nnz, int64_t m, int64_t n) { return (double)nnz * 2.0 < (double)m * (double)n; }
 
-// Whether emit_sorted_kernel is expected to be ahead, for matrices of which half or more is indexed (the others are packed before
-// they are sorted).  Clocks: a row sorted in LDS takes 125 per 64 columns, 60 per codebook position and 10000 (its start, the pointers,
-// the way out), and its LDS limits how many of them a compute unit holds; emit_kernel takes 800 per 64 columns of a row, one after
-// another, or 72 of a compute unit's time.  Whole calls, emit_kernel / emit_sorted_kernel, us: 300 x 9000, 7 bits 115 / 90, 8 bits 118 / 97;
-// 1000 x 2000, 6 bits 74 / 67; 4096 x 9216, 7 bits 236 / 233, 8 bits 231 / 275; 2048 x 4096, 7 bits 101 / 99, 8 bits 102 / 122;
-// 4096 x 2050, 7 bits 112 / 119; equally frequent values 4096 x 9216, 100 of them 274 / 163, 256 323 / 226.
-bool sorted_rows_pay(int64_t m, int64_t n, uint32_t positions, size_t lds) {
+// Whether emit_sorted_kernel is expected to be ahead.  Clocks, where half or more is indexed: a row sorted in LDS takes 125 per 64 columns, 60
+// per codebook position and 10000 (its start, the pointers, the way out), and its LDS limits how many of them a compute unit holds;
+// emit_kernel takes 800 per 64 columns of a row, one after another, or 72 of a compute unit's time.  Whole calls, emit_kernel / emit_sorted_kernel,
+// us: 300 x 9000, 7 bits 115 / 90, 8 bits 118 / 97; 1000 x 2000, 6 bits 74 / 67; 4096 x 9216, 7 bits 236 / 233, 8 bits 231 / 275; 2048 x 4096,
+// 7 bits 101 / 99, 8 bits 102 / 122; 4096 x 2050, 7 bits 112 / 119; equally frequent values 4096 x 9216, 100 of them 274 / 163, 256 323 / 226.
+// Where fewer are, emit_kernel packs a row's elements first, which takes 160 per 64 columns, and 640 per 64 elements behind it; the terms are
+// fitted to 68 such matrices (256 to 4096 rows of 1024 to 25088 columns, 2 to 49 % indexed, 4 to 256 values), compressed by either kernel: the
+// one taken is 0.4 % slower than the better one in the mean, always emit_kernel 11 %.  Whole calls: 1024 x 9216, 5 bits 106 / 79; 4096 x 9216, 5
+// bits 182 / 155, 3 bits (2 % indexed) 142 / 147; 1024 x 2048, 5 bits 64.7 / 60.8; 2048 x 1024, 5 bits 64.9 / 67.4; 400 x 25088, 4 values, 40 %
+// indexed 146 / 89; 4096 x 12000, 200 values, 10 % 131 / 171.  With the factor of 0.93 none of the 68 is slower than with emit_kernel (with 1 and 4000 in
+// place of 2500 five of them, by up to 5 %).
+bool sorted_rows_pay(int64_t m, int64_t n, uint32_t positions, size_t lds, double indexed) {
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
     const double columns = (double)n / 64.0, share = std::max((double)m / std::max(cus, 1), 1.0);  // rows per compute unit
     const double rounds = std::ceil(share / std::floor(160.0 * 1024.0 / (double)lds));
-    return rounds * (125.0 * columns + 60.0 * positions + 10000.0) < std::max(800.0 * columns, 72.0 * columns * share) + 6000.0;
+    if (indexed >= 0.5) return rounds * (125.0 * columns + 60.0 * positions + 10000.0) < std::max(800.0 * columns, 72.0 * columns * share) + 6000.0;
+    const double eights = (double)((positions + 7u) & ~7u);
+    const double sorted = std::max(rounds * (45.0 * columns + 72.0 * eights + 8000.0), share * (15.5 * columns + 10.0 * eights + 1000.0));
+    return sorted < 0.93 * (std::max((160.0 + 640.0 * indexed) * columns, share * 110.0 * indexed * columns) + 2500.0);
 }
 
-// LDS per row of emit_sorted_kernel, 0 where emit_kernel serves.  longest: indexed elements of the longest row, sparse: fewer than half of
-// all elements are indexed.
-size_t sorted_lds(int64_t m, int64_t n, uint32_t positions, uint32_t longest, bool sparse) {
+// LDS per row of emit_sorted_kernel, 0 where emit_kernel serves.  longest: indexed elements of the longest row; nnz: of the matrix.
+size_t sorted_lds(int64_t m, int64_t n, uint32_t positions, uint32_t longest, uint64_t nnz) {
     const size_t lds = emit_stage_bytes(longest) + (size_t)((positions + 7u) & ~7u) * (kRowCounters + 1u) * 4u;
-    return !sparse && n >= 1024 && n <= kSortedColumns && lds <= 64 * 1024 && sorted_rows_pay(m, n, positions, lds) ? lds : 0;
+    return n >= 1024 && n <= kSortedColumns && lds <= 64 * 1024 && sorted_rows_pay(m, n, positions, lds, (double)nnz / ((double)m * (double)n)) ? lds : 0;
 }
 
 // Waves of emit_sorted_kernel that run at once.
@@ -1520,7 +1527,7 @@ template <typename ColT>
 hipError_t launch_emit(hipStream_t s, const uint8_t* codes, const uint32_t* cnt, const uint2* rowStart, const FrontState* st,
                        int64_t m, int64_t n, int cser, int sparse, const EmitTarget& to, FrontResult* out) {
     if constexpr (sizeof(ColT) == 2) {
-        if (const size_t lds = sorted_lds(m, n, out->K, out->max_row_nnz, sparse != 0))
+        if (const size_t lds = sorted_lds(m, n, out->K, out->max_row_nnz, out->nnz))
             return cer::launch_kernel(n <= 1024 * kSortedPieces ? emit_sorted_kernel<kSortedPieces> : emit_sorted_kernel<0>, dim3((unsigned)std::min<int64_t>(m, sorted_waves(lds)) + 1u), dim3(64), lds, s, codes, cnt, rowStart, st, m, (uint32_t)n, cser,
                                       out->K, emit_stage_bytes(out->max_row_nnz), to, out);
     }
@@ -1647,7 +1654,7 @@ int quantize_device(const float* W, int64_t count, int32_t bits, uint8_t* codes,
 }
 
 bool encode_sorts_rows(const DeviceView& v, int32_t K) {
-    return v.colI_bits == 16 && sorted_lds(v.m, v.n, (uint32_t)K, v.longest_row, mostly_implicit(v.nnz, v.m, v.n)) != 0;
+    return v.colI_bits == 16 && v.m > 0 && sorted_lds(v.m, v.n, (uint32_t)K, v.longest_row, (uint64_t)v.nnz) != 0;
 }
 
 int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, int32_t K, int32_t bits, bool cser,
@@ -1743,7 +1750,7 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     gap(l.off_ri + (size_t)(m + 1) * 8, l.off_tab);
     gap(l.off_tab + (l.tab_shift ? ((size_t)m << l.tab_shift) * 4 : 0), l.total);
     const int cs = cser ? 1 : 0;
-    // with fewer than half of the elements indexed the emitter packs them in LDS before it scatters them
+    // with fewer than half of the elements indexed emit_kernel packs them in LDS before it scatters them
     const int sp = mostly_implicit(h.nnz, m, n) ? 1 : 0;
     hipError_t e = hipSuccess;
     switch (hnd->host->colI.bits) {

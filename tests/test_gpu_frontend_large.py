@@ -66,3 +66,28 @@ def test_rows_per_wave_of_the_layout(m, fmt):
         assert np.array_equal(B.cer_get_array(h, which), B.cer_get_array(host, which)), which
     B.cer_free(h)
     B.cer_free(host)
+
+
+# (rows, columns, values, share indexed, whether a row is sorted in LDS)
+SPARSE = [(300, 9217, 16, 0.05, True), (1300, 12289, 5, 0.3, True), (257, 4099, 24, 0.45, True), (20, 64512, 3, 0.02, True), (20, 64513, 3, 0.02, False),
+          (300, 5000, 1, 0.0, True), (5, 20000, 256, 0.001, True), (2048, 1024, 16, 0.4, False), (3000, 2500, 250, 0.1, False)]
+
+
+@pytest.mark.parametrize("case", SPARSE, ids=[f"{c[0]}x{c[1]}_K{c[2]}_{c[3]}" for c in SPARSE])
+@pytest.mark.parametrize("fmt", ["cer", "cser"])
+def test_mostly_implicit_rows(case, fmt):
+    """Fewer than half of the elements indexed, by either kernel: the host encoder's arrays.  Rows without an element, one much longer than the
+    others, nothing indexed at all."""
+    m, n, K, share, sorts = case
+    rng = np.random.default_rng(m + n)
+    cb = (np.arange(K) - K // 2).astype(np.float32)
+    W = np.where(rng.random((m, n)) < share, rng.choice(cb, size=(m, n)), np.float32(0)).astype(np.float32)
+    W[m // 2] = 0.0
+    W[m - 1, :n // 4], W[0, n - 1] = cb[K - 1], cb[0]
+    h = B.cer_encode_device(torch.from_numpy(W).cuda(), m, n, cb, fmt)
+    assert B.cer_encode_sorts_rows(h, K) == sorts
+    host = (B.cer_encode if fmt == "cer" else B.cser_encode)(W, cb)
+    for which in (B.CER_ARRAY_OMEGA, B.CER_ARRAY_COLI, B.CER_ARRAY_OMEGAPTR, B.CER_ARRAY_ROWPTR) + ((B.CER_ARRAY_OMEGAI,) if fmt == "cser" else ()):
+        assert np.array_equal(B.cer_get_array(h, which), B.cer_get_array(host, which)), which
+    B.cer_free(h)
+    B.cer_free(host)
