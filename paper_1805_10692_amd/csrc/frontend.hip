@@ -498,7 +498,8 @@ __device__ void scan_rows(const unsigned long long* rowGN, int64_t m, uint2* __r
     }
 }
 
-// Bound by a chain of steps (values ranked, the arrivals, the scan), of which only the arrivals grow with the workgroups: beyond kFewRows
+// Bound by a chain of steps (values ranked, the arrivals, the scan), of which only the arrivals grow with the workgroups (4096 rows 15.2 us
+// with 256 workgroups, 10.8 with 64; 300 rows 8.6): beyond kFewRows
 // rows a wave takes four (the call for 4096 x 9216, 7 bits, with one / two / four / eight rows per wave 187.0 / 185.5 / 184.5 / 185.0 us; 188.3
 // when one row per wave went with shuffles in place of DPP), below one: 2000 x 5000, 8 bits, 110.3 / 110.4 / 110.3 / 111.8, 1024 x 2048, 5 bits, 65.9 /
 // 66.2 / 66.7 / 68.6.
