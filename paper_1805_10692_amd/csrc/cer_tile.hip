@@ -31,10 +31,11 @@ constexpr uint32_t kTileWaves = 8, kTileThreads = kTileWaves * kWave;
 // A bucket's rows and columns of W; bytes per row of them in LDS (rows 36 banks apart: a wave's 16-byte reads of 16 rows meet no conflict).
 constexpr uint32_t kGroupRows = 16, kSegCols = 64, kPitch = 2 * kSegCols + 16, kGroupBytes = kGroupRows * kPitch;
 
-// LDS: [flags, cleared at the kernel's start: columns with sums that are not finite, with faint ones; lossy inputs][arguments of the functions
-// for those][pieces of the codebook's values, by rank][per wave: planes of 16 RT rows]; later the waves' sums
-constexpr uint32_t kTileArgsAt = 32, kTileTableAt = kTileArgsAt + 128;
-constexpr int kOddColumns = 0, kFaintColumns = 2, kTileLossy = 4;  // the flags' words: 64 columns, 64 columns, any
+// LDS: [flags, cleared at the kernel's start: columns with sums that are not finite, with faint ones, left for binary32; lossy inputs]
+// [arguments of the functions for those][what tile_again learns of rows and columns][pieces of the codebook's values, by rank][per wave: planes of
+// 16 RT rows]; later the waves' sums
+constexpr uint32_t kTileArgsAt = 32, kTileBitsAt = kTileArgsAt + 128, kTileSizesAt = kTileBitsAt + 512, kTileTableAt = kTileSizesAt + 128;
+constexpr int kOddColumns = 0, kFaintColumns = 2, kTileLossy = 4, kSlowColumns = 5;  // the flags' words: 64 columns, 64 columns, a bit per 16 lanes' columns, 64 columns
 __host__ __device__ constexpr uint32_t planes_at(int form) { return kTileTableAt + 256u * (form == 1 ? 0u : entry_bytes(form)); }
 __host__ __device__ constexpr uint32_t wave_bytes(int form, int rt) { return (uint32_t)weight_planes(form) * rt * kGroupBytes; }
 
@@ -58,7 +59,7 @@ struct TileRest {
     size_t split_stride;
     const float* omega;
     uint32_t values;  // of the codebook, less one
-    float faint;
+    float faint, most;
     uint32_t dense;   // a zero weight times an infinity counts
 };
 struct TileArgs {
@@ -68,10 +69,10 @@ struct TileArgs {
     const float* omega;
     float* Out;
     double inverse;
-    float scale, unit, least;
+    float scale, unit, least, most;
     uint32_t m, n, L, row0, col0, cols, h0, h1, dense;
 };
-static_assert(sizeof(TileArgs) <= kTileTableAt - kTileArgsAt, "place of the arguments");
+static_assert(sizeof(TileArgs) <= kTileBitsAt - kTileArgsAt, "place of the arguments");
 
 typedef uint32_t TwoBounds __attribute__((ext_vector_type(2), aligned(4)));
 
@@ -147,7 +148,8 @@ struct TileAgain {
     float* out;
     bool rows;  // of the lane's group
     UniformGrid grid;
-    float omega0, least;
+    float omega0, least, most;
+    bool dense;
     __device__ __forceinline__ explicit TileAgain(uint32_t lds) : smem(lds_pointer(lds)) {
         const TileArgs& a = *reinterpret_cast<const TileArgs*>(smem + kTileArgsAt);
         constexpr uint32_t kLanes = kWave / RT;
@@ -161,7 +163,8 @@ struct TileAgain {
         rows = group < groups;
         bounds = uniform_pointer(a.ptr) + (size_t)min(group, groups - 1u) * (segs + 1u);
         grid.scale = a.scale; grid.unit = a.unit; grid.inverse = a.inverse;
-        least = a.least;
+        least = a.least; most = a.most;
+        dense = uniform(a.dense) != 0u;
         omega0 = uniform_pointer(a.omega)[0];
         fill_pieces<kForm>(omega0, grid, fill);
     }
@@ -178,96 +181,260 @@ struct TileAgain {
     }
 };
 
-// Faint sums once more, with X times 2^64, where every input that can count has its pieces.  (Inputs beyond 2^62 are cut: where they count,
-// sums are not faint.)  16 columns after the other.  4096 x 9216, 15 % indexed, batch 99, all of X near 2^-120: 137 us (40
-// otherwise; 65 with the strips).
-template <int kForm, int RT>
-__device__ __attribute__((noinline)) void tile_faint(uint32_t lds, uint32_t columns0, uint32_t columns1) {
+// Columns of outputs once more on the matrix cores, 16 CT after the other; the loop is the kernel's.
+// Not scaled, columns with sums that are not finite: infinities and NaNs of X count as zeros in the sums, and what they make of an output
+// is kept as two bits per row and column (a term that is +infinity, one that is -infinity; a NaN is both), which tells it whatever the
+// order of the sum.  As with the gathers the terms are those of a row's indices, (value - most frequent value) . x, and that value . x, or
+// (dense) as with the decoded matrix those of every element.
+// Scaled, columns with faint sums next to inputs that have lost bits: with X times 2^64 every input has its pieces.  Only where the
+// column's largest input leaves room for that (most): a sum of large terms may be faint as well, by cancelling.
+// Sums that are not finite all the same, and columns with inputs too large to be scaled, are left to tile_slow.
+// 4096 x 9216, 15 % indexed, batch 99 (41 us; without the index 58 for any X): one or eight columns with an infinity 54 us, all of them 88, one
+// column near 2^-120 52, all of X 93; 1103 x 14914, 5 values, batch 42 (26; without the index 33, all of these 470 to 490): 43, 68, 45, 79.  Bound by what
+// the kernel is bound by, which its own loop does for 16 CT columns with fewer registers.
+template <int kForm, int RT, int CT, bool kScaled>
+__device__ __attribute__((noinline)) void tile_again(uint32_t lds, uint32_t columns0, uint32_t columns1) {
     using Tile = TileAgain<kForm, RT>;
     const Tile a(lds);
-    constexpr int PW = Tile::PW;
-    constexpr uint32_t kPlane = RT * kGroupBytes;
+    constexpr int PW = Tile::PW, kQ = 3, kSteps = kSegCols / 32;
+    constexpr uint32_t kPlane = RT * kGroupBytes, kLanes = kWave / RT, R = 16 * RT, kPer = RT * CT * 4 * kWave;
     typedef const uintx4 __attribute__((address_space(3))) * Lds4;
+    typedef const uint16_t __attribute__((address_space(3))) * Lds16;
     const uint64_t columns = (uint64_t)uniform(columns1) << 32 | uniform(columns0);
-    const uint32_t c16 = a.lane & 15u, g = a.lane >> 4;
-    float* s_sum = reinterpret_cast<float*>(a.smem + planes_at(kForm));
+    const uint32_t tid = threadIdx.x, lane = a.lane, c16 = lane & 15u, g = lane >> 4;
+    uint32_t* const flags = reinterpret_cast<uint32_t*>(a.smem);
+    uint32_t* const s_bits = reinterpret_cast<uint32_t*>(a.smem + kTileBitsAt);   // [row][+, -], a bit per column
+    uint32_t* const s_size = reinterpret_cast<uint32_t*>(a.smem + kTileSizesAt);  // scaled: the columns' largest inputs; else: whether a lane's have lost bits
+    float* const s_sum = reinterpret_cast<float*>(a.smem + planes_at(kForm));
+    auto bounds_of = [&](uint32_t h) { return *reinterpret_cast<const TwoBounds*>(a.bounds + min(h, a.segs - 1u)); };
 #pragma unroll 1
-    for (uint32_t c0 = 0; c0 < a.cols; c0 += 16u) {
-        if (((columns >> c0) & 0xFFFFull) == 0ull) continue;
-        const uint32_t col = a.col0 + c0 + c16, from = min(col, a.L - 1u);
-        floatx4 sum[RT] = {};
-        uint32_t lost = 0;
-        __syncthreads();
-#pragma unroll 1
-        for (uint32_t h = a.h0 + a.wave; h < a.h1; h += kTileWaves) {
-            a.lay_out(h);
-            floatx4 acc[RT] = {}, lo[RT] = {};
+    for (uint32_t c0 = 0; c0 < a.cols; c0 += 16u * CT) {
+        const uint32_t mask = (uint32_t)(columns >> c0) & (CT == 2 ? 0xFFFFFFFFu : 0xFFFFu);
+        if (mask == 0u) continue;
+        __syncthreads();  // what lies in LDS has been read
+        if (tid < 2u * R) s_bits[tid] = 0u;
+        if (tid < 32u) s_size[tid] = 0u;
+        const uint32_t first = a.col0 + c0 + CT * c16, xcol = min(first, a.L - (uint32_t)CT);
+        uint32_t xoff[8];
 #pragma unroll
-            for (uint32_t t = 0; t < kSegCols / 32u; ++t) {
-                const __amdgpu_buffer_rsrc_t xbuf = x_rows(a.X, a.L, min(h * kSegCols + 32u * t, a.n), a.n);
-                float x[8];
+        for (uint32_t i = 0; i < 8; ++i) xoff[i] = ((8u * g + i) * a.L + xcol) * 4u;
+        float x[kSteps][8][CT];
+        auto load_x = [&](uint32_t k0, float (&v)[8][CT]) {
+            const __amdgpu_buffer_rsrc_t xbuf = x_rows(a.X, a.L, min(k0, a.n), a.n);
 #pragma unroll
-                for (uint32_t i = 0; i < 8; ++i) {
-                    const float v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, ((8u * g + i) * a.L + from) * 4u, 0, 0));
-                    x[i] = fminf(fmaxf(v, -0x1p62f), 0x1p62f) * 0x1p64f;
+            for (int i = 0; i < 8; ++i) load_columns<CT>(xbuf, xoff[i], v[i]);
+        };
+        TwoBounds bound = bounds_of(a.h0 + a.wave);
+        uint4 q[kQ];
+        uint32_t cb = 0, ce = 0;
+        auto request = [&](uint32_t h) {
+            cb = bound[0] + lane % kLanes;
+            ce = a.rows && h < a.h1 ? bound[1] : 0u;
+#pragma unroll
+            for (int u = 0; u < kQ; ++u) {
+                const uint32_t i = cb + (uint32_t)u * kLanes;
+                q[u] = a.quads[i < ce ? i : 0u];
+            }
+        };
+        floatx4 sum[RT][CT] = {};
+        float largest[CT] = {};
+        uint32_t plus = 0, minus = 0, lost = 0;  // plus, minus: of row lane % R, column xcol + c is bit 16 c + c16
+        // The inputs of a step among which some are not finite, or round to an infinite bf16 number: their pieces.
+        auto take_apart = [&](int s, uint4 (&b)[CT][3]) {
+            uint32_t pieces[CT][3][4];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                uint64_t up[CT], down[CT], none[CT], any = 0;
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    float& v = x[s][i][c];
+                    up[c] = __ballot(v == INFINITY);
+                    down[c] = __ballot(v == -INFINITY);
+                    none[c] = __ballot(v != v);
+                    any |= up[c] | down[c] | none[c];
+                    v = fabsf(v) < INFINITY ? v : 0.f;
+                    lost |= split_lossy(v) ? 1u : 0u;
+                    uint32_t p[3];
+                    split3_finite(kScaled ? v * 0x1p64f : v, p);
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) pieces[c][j][i >> 1] = i & 1 ? pieces[c][j][i >> 1] | p[j] << 16 : p[j] & 0xFFFFu;
                 }
-                uint4 b[3];
-                split3_8_dot(x, b, lost);
+                if (kScaled || any == 0ull) continue;
+#pragma unroll 1
+                for (uint32_t k = 0; k < 4; ++k) {  // row 8 k + i of the step: 16 lanes' columns
+                    uint32_t bits[3] = {};
 #pragma unroll
-                for (int r = 0; r < RT; ++r) {
-                    uint4 w[PW];
+                    for (int c = 0; c < CT; ++c) {
+                        bits[0] |= ((uint32_t)(up[c] >> (16u * k)) & 0xFFFFu) << (16 * c);
+                        bits[1] |= ((uint32_t)(down[c] >> (16u * k)) & 0xFFFFu) << (16 * c);
+                        bits[2] |= ((uint32_t)(none[c] >> (16u * k)) & 0xFFFFu) << (16 * c);
+                    }
+                    const uint32_t one_way = bits[0] | bits[2], other_way = bits[1] | bits[2], all = one_way | other_way;
+                    if (all == 0u) continue;
+                    uint32_t piece[PW];
+                    bool indexed = false;
 #pragma unroll
                     for (int p = 0; p < PW; ++p) {
-                        const uintx4 v = *reinterpret_cast<Lds4>((uintptr_t)(a.mine + c16 * kPitch + t * 64u + g * 16u + (uint32_t)p * kPlane + (uint32_t)r * kGroupBytes));
-                        w[p] = make_uint4(v[0], v[1], v[2], v[3]);
+                        piece[p] = *reinterpret_cast<Lds16>((uintptr_t)(a.mine + (uint32_t)p * kPlane + lane % R * kPitch + 2u * (32u * s + 8u * k + i)));
+                        indexed |= piece[p] != (a.fill[p] & 0xFFFFu);
+                        piece[p] <<= 16;
                     }
+                    float w = __uint_as_float(piece[0]);
+                    if constexpr (kForm == kUniform) w = fmaf(a.grid.scale, w, a.grid.scale * __uint_as_float(piece[PW - 1]));
+                    if constexpr (kForm == 3) w += __uint_as_float(piece[PW > 1 ? 1 : 0]) + __uint_as_float(piece[PW - 1]);
+                    // the terms' signs: of w, or of w - omega0 where indexed, and of omega0
+                    const bool rises = a.dense ? w > 0.f : indexed && w > a.omega0, falls = a.dense ? w < 0.f : indexed && w < a.omega0;
+                    const uint32_t nan = a.dense && !rises && !falls ? all : 0u;
+                    plus |= (rises ? one_way : 0u) | (falls ? other_way : 0u) | nan;
+                    minus |= (rises ? other_way : 0u) | (falls ? one_way : 0u) | nan;
+                    if (!a.dense && a.omega0 != 0.f) {
+                        plus |= a.omega0 > 0.f ? one_way : other_way;
+                        minus |= a.omega0 > 0.f ? other_way : one_way;
+                    }
+                }
+            }
 #pragma unroll
-                    for (int s = 2; s >= 0; --s)
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) b[c][j] = make_uint4(pieces[c][j][0], pieces[c][j][1], pieces[c][j][2], pieces[c][j][3]);
+        };
+        uint32_t h = a.h0 + a.wave;
+        request(h);
+        bound = bounds_of(h + kTileWaves);
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) load_x(h * kSegCols + 32u * s, x[s]);
+        __syncthreads();
+#pragma unroll 1
+        for (; h < a.h1; h += kTileWaves) {
+            wave_lds_sync();
+            clear_planes<kForm, RT>(a.mine, a.fill, lane);
+            const uint32_t to = a.mine + lane / kLanes * kGroupBytes;
+#pragma unroll
+            for (int u = 0; u < kQ; ++u) place_quad<kForm, RT>(to, a.smem, q[u]);
+            for (uint32_t c = cb + (uint32_t)kQ * kLanes; __ballot(c < ce) != 0ull; c += kLanes) place_quad<kForm, RT>(to, a.smem, a.quads[c < ce ? c : 0u]);
+            wave_lds_sync();
+            request(h + kTileWaves);
+            bound = bounds_of(h + 2u * kTileWaves);
+            floatx4 acc[RT][CT] = {}, lo[RT][CT] = {};
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s) {
+                uint4 w[RT][PW], b[CT][3];
+#pragma unroll
+                for (int r = 0; r < RT; ++r)
+#pragma unroll
+                    for (int p = 0; p < PW; ++p) {
+                        const uintx4 v = *reinterpret_cast<Lds4>((uintptr_t)(a.mine + c16 * kPitch + (uint32_t)s * 64u + g * 16u + (uint32_t)p * kPlane + (uint32_t)r * kGroupBytes));
+                        w[r][p] = make_uint4(v[0], v[1], v[2], v[3]);
+                    }
+                uint32_t bits = 0;
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    float xc[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) xc[i] = kScaled ? x[s][i][c] * 0x1p64f : x[s][i][c];
+                    split3_8_dot(xc, b[c], bits);
+                }
+                lost |= bits;
+                // an input without pieces leaves a NaN among the remainders (and inputs from 2^17 on what may look like one)
+                if (__ballot((bits & 0x7F800000u) == 0x7F800000u) != 0ull) take_apart(s, b);
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    if constexpr (kScaled)
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) largest[c] = fmaxf(largest[c], fabsf(x[s][i][c]));
+#pragma unroll
+                    for (int d = 2; d >= 0; --d)
 #pragma unroll
                         for (int i = 0; i < PW; ++i)
-                            if (s - i >= 0 && !(kForm == kUniform && i == 1 && s == 2)) {
-                                floatx4& to = s > 0 ? lo[r] : acc[r];
-                                to = mfma16(w[i], b[s - i], to);
-                            }
+                            if (d - i >= 0 && !(kForm == kUniform && i == 1 && d == 2))
+#pragma unroll
+                                for (int r = 0; r < RT; ++r) {
+                                    floatx4& into = d > 0 ? lo[r][c] : acc[r][c];
+                                    into = mfma16(w[r][i], b[c][d - i], into);
+                                }
                 }
+                load_x((h + kTileWaves) * kSegCols + 32u * s, x[s]);
             }
 #pragma unroll
             for (int r = 0; r < RT; ++r)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sum[r][e] += kForm == kUniform ? fmaf(a.grid.scale, acc[r][e], a.grid.scale * lo[r][e]) : acc[r][e] + lo[r][e];
+                for (int c = 0; c < CT; ++c)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        sum[r][c][e] += kForm == kUniform ? fmaf(a.grid.scale, acc[r][c][e], a.grid.scale * lo[r][c][e]) : acc[r][c][e] + lo[r][c][e];
         }
         __syncthreads();
+        if (plus != 0u) atomicOr(&s_bits[2u * (lane % R)], plus);
+        if (minus != 0u) atomicOr(&s_bits[2u * (lane % R) + 1u], minus);
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            if constexpr (kScaled) atomicMax(&s_size[16u * c + c16], __float_as_uint(largest[c]));
+            else if ((lost & 0xFFFFu) != 0u) s_size[16u * c + c16] = 1u;
+        }
 #pragma unroll
         for (int r = 0; r < RT; ++r)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s_sum[(a.wave * RT * 4u + r * 4 + e) * kWave + a.lane] = sum[r][e];
-        __syncthreads();
-        for (uint32_t re = a.wave; re < RT * 4u; re += kTileWaves) {
-            double total = 0;
+            for (int c = 0; c < CT; ++c)
 #pragma unroll
-            for (uint32_t k = 0; k < kTileWaves; ++k) total += s_sum[(k * RT * 4u + re) * kWave + a.lane];
-            const uint32_t row = a.row0 + 16u * (re >> 2) + 4u * g + (re & 3u);
-            if (row < a.m && col < min(a.L, a.col0 + a.cols)) {
-                float* at = a.out + (size_t)row * a.L + col;
-                const float size = fabsf(*at);
-                if (size < a.least || (size < 0x1p-126f && size > 0.f)) *at = (float)(total * 0x1p-64);
+                for (int e = 0; e < 4; ++e) s_sum[a.wave * kPer + ((r * 4 + e) * CT + c) * kWave + lane] = sum[r][c][e];
+        __syncthreads();
+        uint32_t slow = 0, faint = 0;  // of the lane's columns
+        for (uint32_t re = a.wave; re < RT * 4u; re += kTileWaves) {
+            const uint32_t r = 16u * (re >> 2) + 4u * g + (re & 3u), row = a.row0 + r;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const uint32_t column = xcol + c - a.col0 - c0;  // (the lane's first ones are another lane's where the batch ends)
+                if (row >= a.m || xcol + c < first || ((mask >> column) & 1u) == 0u) continue;
+                double total = 0;
+#pragma unroll
+                for (uint32_t k = 0; k < kTileWaves; ++k) total += s_sum[k * kPer + (re * CT + c) * kWave + lane];
+                const uint32_t size_x = s_size[16u * c + c16];
+                float* at = a.out + (size_t)row * a.L + xcol + c;
+                if constexpr (kScaled) {
+                    const float size = fabsf(*at);
+                    if (size < a.least || (size < 0x1p-126f && size > 0.f)) {
+                        if (__uint_as_float(size_x) < a.most) *at = (float)(total * 0x1p-64); else slow |= 1u << c;
+                    }
+                } else {
+                    const float y = (float)total, size = fabsf(y);
+                    const bool up = (s_bits[2u * r] >> (16 * c + c16)) & 1u, down = (s_bits[2u * r + 1u] >> (16 * c + c16)) & 1u;
+                    if (!(size < INFINITY)) slow |= 1u << c;
+                    if (!up && !down && ((size < a.least && size_x != 0u) || (size < 0x1p-126f && size > 0.f))) faint |= 1u << c;
+                    *at = up && down ? NAN : (up ? INFINITY : (down ? -INFINITY : y));
+                }
             }
         }
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const uint32_t column = xcol + c - a.col0;
+            if ((slow >> c) & 1u) atomicOr(&flags[kSlowColumns + (column >> 5)], 1u << (column & 31u));
+            if ((faint >> c) & 1u) atomicOr(&flags[kFaintColumns + (column >> 5)], 1u << (column & 31u));
+        }
     }
+    __syncthreads();
 }
 
-// Columns with sums that are not finite once more, in binary32, four after the other: a lane takes a row and walks along W's columns.  As
+// 32 columns at a time where both sixteens have some, else sixteen.
+template <int kForm, int RT, int CT, bool kScaled>
+__device__ __forceinline__ void tile_again_columns(uint32_t lds, uint32_t columns0, uint32_t columns1) {
+    const uint32_t wide0 = (columns0 & 0xFFFFu) != 0u && columns0 >> 16 != 0u ? columns0 : 0u, wide1 = (columns1 & 0xFFFFu) != 0u && columns1 >> 16 != 0u ? columns1 : 0u;
+    if constexpr (CT >= 2)
+        if ((wide0 | wide1) != 0u) tile_again<kForm, RT, 2, kScaled>(lds, wide0, wide1);
+    if (((columns0 ^ wide0) | (columns1 ^ wide1)) != 0u) tile_again<kForm, RT, 1, kScaled>(lds, columns0 ^ wide0, columns1 ^ wide1);
+}
+
+// Columns of which nothing else is certain once more, in binary32, four after the other: a lane takes a row and walks along W's columns.  As
 // with the gathers the sum is over a row's indices of (value - most frequent value) . x, and that value times the column sum, or
-// (dense) as with the decoded matrix over every element.  4096 x 9216, 15 % indexed, batch 99: one column 87 us, all
-// of them 330 (40; 62 with the strips); 1103 x 14914, 5 values, batch 42 51 (25; 417 with cer_fused_kernel).
+// (dense) as with the decoded matrix over every element.  4096 x 9216, 15 % indexed, batch 99, a column with sums beyond binary32: 104 us (41;
+// 58 without the index).
 template <int kForm, int RT>
-__device__ __attribute__((noinline)) void tile_odd(uint32_t lds, uint32_t columns0, uint32_t columns1) {
+__device__ __attribute__((noinline)) void tile_slow(uint32_t lds, uint32_t columns0, uint32_t columns1) {
     using Tile = TileAgain<kForm, RT>;
     const Tile a(lds);
     constexpr int PW = Tile::PW;
     constexpr uint32_t kPlane = RT * kGroupBytes, R = 16 * RT;
     typedef const uintx4 __attribute__((address_space(3))) * Lds4;
-    const bool dense = uniform(reinterpret_cast<const TileArgs*>(a.smem + kTileArgsAt)->dense) != 0u;
+    const bool dense = a.dense;
     uint64_t columns = (uint64_t)uniform(columns1) << 32 | uniform(columns0);
     float* s_sum = reinterpret_cast<float*>(a.smem + planes_at(kForm));  // [wave][column][row], [wave][column][lane] of X
     float* s_x = s_sum + kTileWaves * 4u * kWave;
@@ -494,7 +661,7 @@ __global__ __launch_bounds__(kTileThreads) void cer_tile_kernel(const uint4* qua
     // the waves' sums meet in LDS: [wave][row tile][element][column of CT][lane]
     float* s_sum = reinterpret_cast<float*>(smem + planes_at(kForm));
     constexpr uint32_t kPer = RT * CT * 4 * kWave;
-    if (__ballot((lost & 0xFFFFu) != 0u) != 0ull && lane == 0) atomicOr(&flags[kTileLossy], 1u);
+    if ((lost & 0xFFFFu) != 0u) atomicOr(&flags[kTileLossy], 1u << c16);
 #pragma unroll
     for (int r = 0; r < RT; ++r)
 #pragma unroll
@@ -507,7 +674,7 @@ __global__ __launch_bounds__(kTileThreads) void cer_tile_kernel(const uint4* qua
     // accumulator element e of lane l: row 4 (l / 16) + e, column l % 16
     constexpr uint32_t kVec = RT * 4 * kWave / kTileThreads;
     static_assert(kVec >= 1, "threads");
-    const float least = flags[kTileLossy] != 0u ? rest.faint : 0.f;
+    const float least = (flags[kTileLossy] >> c16) & 1u ? rest.faint : 0.f;
     uint32_t odd = 0, faint = 0;  // of the lane's columns
     float* out = rest.Out + sp * rest.split_stride;
 #pragma unroll
@@ -549,15 +716,17 @@ __global__ __launch_bounds__(kTileThreads) void cer_tile_kernel(const uint4* qua
     }
     __syncthreads();
     const uint32_t odd0 = uniform(flags[kOddColumns]), odd1 = uniform(flags[kOddColumns + 1]);
-    const uint32_t faint0 = uniform(flags[kFaintColumns]), faint1 = uniform(flags[kFaintColumns + 1]);
-    if ((odd0 | odd1 | faint0 | faint1) == 0u) return;
+    if ((odd0 | odd1 | flags[kFaintColumns] | flags[kFaintColumns + 1]) == 0u) return;
     // columns with sums that are not finite, and where inputs have lost bits those with faint ones, are formed again
     if (tid == 0)
         *reinterpret_cast<TileArgs*>(smem + kTileArgsAt) =
-            TileArgs{quads, ptr, X, omega, out, grid.inverse, grid.scale, grid.unit, least, m, n, L, row0, col0, BN, h0, h1, rest.dense};
+            TileArgs{quads, ptr, X, omega, out, grid.inverse, grid.scale, grid.unit, rest.faint, rest.most, m, n, L, row0, col0, BN, h0, h1, rest.dense};
     __syncthreads();
-    if ((faint0 | faint1) != 0u) tile_faint<kForm, RT>(lds0, faint0, faint1);
-    if ((odd0 | odd1) != 0u) tile_odd<kForm, RT>(lds0, odd0, odd1);
+    if ((odd0 | odd1) != 0u) tile_again_columns<kForm, RT, CT, false>(lds0, odd0, odd1);
+    const uint32_t faint0 = uniform(flags[kFaintColumns]), faint1 = uniform(flags[kFaintColumns + 1]);
+    if ((faint0 | faint1) != 0u) tile_again_columns<kForm, RT, CT, true>(lds0, faint0, faint1);
+    const uint32_t slow0 = uniform(flags[kSlowColumns]), slow1 = uniform(flags[kSlowColumns + 1]);
+    if ((slow0 | slow1) != 0u) tile_slow<kForm, RT>(lds0, slow0, slow1);
 }
 
 // The tile index of 16 rows, one per wave: their elements are counted by segment, then placed.  An entry: its place in the group's
@@ -831,6 +1000,8 @@ hipError_t launch_tile(const DeviceView& d, const float* X, float* Y, uint32_t L
         a.omega = d.omega;
         a.values = (uint32_t)d.K - 1u;
         a.faint = (float)std::min((double)d.n * d.omega_max * 0x1p-108, 1e38);
+        // sums of terms this large times 2^64 stay below 2^126 on their way; and the inputs below 2^62
+        a.most = (float)(0x1p62 / std::max((double)d.n * d.omega_max, 1.0));
         a.dense = dense_zeros ? 1u : 0u;
         const uint32_t items = p.row_blocks * p.col_tiles * p.splits, eighth = (items + 7u) / 8u;
         const uint32_t magic = p.row_blocks == 1 ? 0u : (uint32_t)(((1ull << 32) + p.row_blocks - 1) / p.row_blocks);

@@ -125,3 +125,50 @@ def test_replayed_from_a_graph():
         torch.cuda.synchronize()
         assert torch.equal(Y, eager), rep
     B.cer_free(h)
+
+
+# codebooks whose numbers come with both signs: one piece, two numbers, three pieces
+SYMMETRIC = {"one_piece": (np.arange(16) - 8).astype(np.float32), "grid": (np.arange(35) - 17).astype(np.float32) / np.float32(17) * 8,
+             "three_pieces": np.sort(np.concatenate([[0.0], s := np.random.default_rng(4).uniform(0.1, 8, 16), -s])).astype(np.float32)}
+
+
+@pytest.mark.parametrize("name,m,n,L", [("one_piece", 1601, 700, 47), ("one_piece", 900, 9000, 130), ("grid", 1601, 700, 191), ("grid", 1030, 12001, 130),
+                                        ("three_pieces", 1601, 700, 401), ("three_pieces", 513, 9000, 130)])
+def test_large_inputs_that_cancel(name, m, n, L):
+    """Sums that are zero or small because large terms cancel, next to inputs whose last bits no piece has (in the same column and in others):
+    they are what the terms give, exact where those are, whatever is formed again; so are sums of inputs near the largest number."""
+    cb = SYMMETRIC[name]
+    rng = np.random.default_rng(m)
+    W = np.where(rng.random((m, n)) < 0.5, rng.choice(cb, size=(m, n)), np.float32(0)).astype(np.float32)
+    a, b, c, d = n // 3, n // 3 + 1, n - 1, 0
+    W[::7] = 0
+    v = rng.choice(cb[cb > 0], size=W[::7].shape[0])
+    W[::7, a], W[::7, b] = v, -v
+    W[::14, c], W[::14, d] = cb[0], cb[-1]       # such a row's faint terms
+    h = _prepared(W, cb)
+    assert B.cer_matmul_tile_columns(h, L) > 0 and B.cer_matmul_planes(h) == {"one_piece": 1, "grid": 2, "three_pieces": 3}[name]
+    W64 = W.astype(np.float64)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    for j, e in enumerate((40, 61, 62, 63, 64, 80, 100, 120)):
+        X[a, j] = np.ldexp(1.0, e)
+    X[b], X[c], X[d] = X[a], 0, 0
+    for lossy in (False, True):
+        if lossy:
+            X[c], X[d] = np.ldexp(1.2345, -130), np.ldexp(-1.7, -140)
+        Y, want = _product(h, X, m, L), W64 @ X.astype(np.float64)
+        assert np.isfinite(Y).all()
+        # those rows are the two faint terms, which a binary32 sum may also have lost next to the large ones
+        tiny, size = W64[::7][:, [c, d]] @ X[[c, d]].astype(np.float64), np.abs(W64[::7][:, [c, d]]) @ np.abs(X[[c, d]]).astype(np.float64)
+        assert (np.abs(Y[::7] - tiny) <= np.where(np.arange(L) < 8, 1, 1e-5) * size + 2.0 ** -148).all()
+        keep = np.arange(m) % 7 != 0
+        assert (np.abs(Y - want) <= _bound(W, X))[keep].all()
+    for scale in (2.0 ** 112, 2.0 ** -118):
+        Z = (np.abs(X) * (np.abs(X) < 8) * scale).astype(np.float32)
+        assert (np.abs(_product(h, Z, m, L) - W64 @ Z.astype(np.float64)) <= 1e-5 * (np.abs(W64) @ Z.astype(np.float64)) + n * 2.0 ** -150).all()
+    Z = np.zeros((n, L), np.float32)             # numbers that round to an infinite bf16 one, times the smallest value
+    Z[np.arange(L) * 5 % n, np.arange(L)] = 3.4e38
+    with np.errstate(over="ignore"):
+        want = (W64 @ Z.astype(np.float64)).astype(np.float32)
+    Y = _product(h, Z, m, L)
+    assert np.array_equal(np.isfinite(Y), np.isfinite(want)) and np.allclose(Y, want, rtol=1e-6, atol=0)
+    B.cer_free(h)
