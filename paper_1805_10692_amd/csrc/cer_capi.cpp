@@ -7,6 +7,7 @@
 #include <memory>
 #include <mutex>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "../../include/cer.h"
@@ -1079,40 +1080,40 @@ int cer_prepare_strips(cer_handle_t* h) {
             idx[(size_t)fill[(size_t)(s * (m + 1) + r)]++] = (uint16_t)((rank << 10) | (uint32_t)(c - s * S));
         });
         const size_t idx_bytes = (idx.size() * 2 + 255) & ~(size_t)255, ptr_bytes = (ptr.size() - 1) * 4;
-        void* base = nullptr;
-        hipError_t e = (hipError_t)cer::handle_alloc(&base, idx_bytes + ptr_bytes + 256, nullptr);
+        // Both indexes, or neither: an error leaves the handle as it was.
+        struct Block {
+            void* p = nullptr;
+            ~Block() { cer::handle_free(p, true); }
+            void* release() { return std::exchange(p, nullptr); }
+        } strips, tile;
+        hipError_t e = (hipError_t)cer::handle_alloc(&strips.p, idx_bytes + ptr_bytes + 256, nullptr);
         if (e != hipSuccess) return hip_fail(e);
-        auto* b8 = static_cast<unsigned char*>(base);
+        auto* b8 = static_cast<unsigned char*>(strips.p);
         if (!idx.empty()) e = hipMemcpy(b8, idx.data(), idx.size() * 2, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(b8 + idx_bytes, ptr.data(), ptr_bytes, hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            cer::handle_free(base, true);
-            return hip_fail(e);
+        if (e != hipSuccess) return hip_fail(e);
+        // The tile index, written by a kernel.  Products do without it where there is no memory for it, and only there.
+        const size_t tile_bytes = cer::tile_index_bytes(h->view);
+        if (tile_bytes > 0) {
+            e = (hipError_t)cer::handle_alloc(&tile.p, tile_bytes, nullptr);
+            if (e == hipErrorOutOfMemory) {
+                (void)hipGetLastError();
+                tile.p = nullptr;
+            } else {
+                if (e == hipSuccess) e = (hipError_t)cer::build_tile_index(h->view, tile.p, nullptr);
+                const hipError_t f = hipStreamSynchronize(nullptr);
+                if (e == hipSuccess) e = f;
+                if (e != hipSuccess) return hip_fail(e);
+            }
         }
-        h->d_strip = base;
-        h->view.strip_idx = base;
+        h->view.strip_idx = strips.p;
         h->view.strip_ptr = reinterpret_cast<const uint32_t*>(b8 + idx_bytes);
         h->view.n_strips = (uint32_t)ns;
         h->view.strip_rows = (uint32_t)S;
         h->view.strip_chunks = nchunks;
-        // The tile index, written by a kernel.  Products do without it where there is no memory for it.
-        const size_t tile_bytes = cer::tile_index_bytes(h->view);
-        void* tile = nullptr;
-        if (tile_bytes > 0) {
-            e = (hipError_t)cer::handle_alloc(&tile, tile_bytes, nullptr);
-            if (e == hipSuccess) {
-                e = (hipError_t)cer::build_tile_index(h->view, tile, nullptr);
-                const hipError_t f = hipStreamSynchronize(nullptr);
-                if (e == hipSuccess) e = f;
-                if (e != hipSuccess) cer::handle_free(tile, true);
-            }
-            if (e == hipSuccess) {
-                h->d_tile = tile;
-                h->view.tile_index = tile;
-            } else {
-                (void)hipGetLastError();
-            }
-        }
+        h->view.tile_index = tile.p;
+        h->d_strip = strips.release();
+        h->d_tile = tile.release();
         return CER_OK;
     } catch (const std::bad_alloc&) {
         return CER_E_NOMEM;

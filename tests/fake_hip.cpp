@@ -1,0 +1,109 @@
+// A HIP runtime without a device, for tests of the host code's error paths: memory is host memory, kernels do not run.  Preloaded into a
+// process of its own.  FAKE_HIP_FAIL=<function>:<text>:<error>: launches of kernels whose name contains the text ("launch"), or the allocation
+// of as many bytes or more as the text says ("malloc"), fail with that error.
+#define __HIP_PLATFORM_AMD__
+#include <hip/hip_runtime_api.h>
+
+#include <atomic>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+
+namespace {
+std::map<const void*, std::string>& names() {
+    static std::map<const void*, std::string> n;
+    return n;
+}
+hipError_t g_last = hipSuccess;
+hipError_t fail(hipError_t e) { return g_last = e; }
+bool wanted(const char* what, std::string* text, hipError_t* error) {
+    const char* f = std::getenv("FAKE_HIP_FAIL");
+    if (!f) return false;
+    const std::string s(f);
+    const size_t a = s.find(':'), b = s.rfind(':');
+    if (a == std::string::npos || a == b || s.substr(0, a) != what) return false;
+    *text = s.substr(a + 1, b - a - 1);
+    *error = (hipError_t)std::atoi(s.c_str() + b + 1);
+    return true;
+}
+std::map<void*, size_t>& blocks() {
+    static std::map<void*, size_t> b;
+    return b;
+}
+hipError_t get(void** p, size_t bytes) {
+    std::string text;
+    hipError_t e;
+    if (wanted("malloc", &text, &e) && bytes >= std::strtoull(text.c_str(), nullptr, 10)) return fail(e);
+    *p = std::calloc(1, bytes + 256);
+    blocks()[*p] = bytes;
+    return hipSuccess;
+}
+hipError_t give(void* p) {
+    blocks().erase(p);
+    std::free(p);
+    return hipSuccess;
+}
+}  // namespace
+
+extern "C" {
+size_t fake_hip_bytes() {  // in device memory
+    size_t s = 0;
+    for (auto& b : blocks()) s += b.second;
+    return s;
+}
+hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
+void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
+void __hipRegisterFunction(void**, const void* f, char*, const char* name, unsigned int, void*, void*, void*, void*, int*) { names()[f] = name; }
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+void __hipUnregisterFatBinary(void**) {}
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
+    *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : a == hipDeviceAttributeMaxSharedMemoryPerBlock || a == hipDeviceAttributeSharedMemPerBlockOptin ? 160 * 1024 : 0;
+    return hipSuccess;
+}
+hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
+    std::memset(p, 0, sizeof *p);
+    p->multiProcessorCount = 256;
+    p->sharedMemPerBlock = p->sharedMemPerBlockOptin = p->maxSharedMemoryPerMultiProcessor = 160 * 1024;
+    p->totalGlobalMem = (size_t)288 << 30;
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
+hipError_t hipGetLastError() { const hipError_t e = g_last; g_last = hipSuccess; return e; }
+hipError_t hipMalloc(void** p, size_t n) { return get(p, n); }
+hipError_t hipMallocAsync(void** p, size_t n, hipStream_t) { return get(p, n); }
+hipError_t hipMallocFromPoolAsync(void** p, size_t n, hipMemPool_t, hipStream_t) { return get(p, n); }
+hipError_t hipFree(void* p) { return give(p); }
+hipError_t hipFreeAsync(void* p, hipStream_t) { return give(p); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned int) { *p = std::calloc(1, n); return hipSuccess; }
+hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemset(void* d, int v, size_t n) { std::memset(d, v, n); return hipSuccess; }
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
+    std::string text;
+    hipError_t e;
+    if (wanted("launch", &text, &e) && names()[f].find(text) != std::string::npos) return fail(e);
+    return hipSuccess;
+}
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipFuncGetAttributes(hipFuncAttributes* a, const void*) { std::memset(a, 0, sizeof *a); return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void* s) { *p = const_cast<void*>(s); return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned int) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)std::calloc(1, 1); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { std::free((void*)e); return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipMemPoolCreate(hipMemPool_t* p, const hipMemPoolProps*) { *p = (hipMemPool_t)std::calloc(1, 1); return hipSuccess; }
+hipError_t hipMemPoolDestroy(hipMemPool_t p) { std::free((void*)p); return hipSuccess; }
+hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void*) { return hipSuccess; }
+hipError_t hipMemPoolTrimTo(hipMemPool_t, size_t) { return hipSuccess; }
+}

@@ -1,0 +1,52 @@
+"""What cer_prepare_strips does where an allocation or a launch fails: on the CPU, with the HIP runtime of tests/fake_hip.cpp in the place of
+the real one (a process of its own for each case)."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_1805_10692_amd import binding as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CHILD = """
+import ctypes, os
+import numpy as np
+from paper_1805_10692_amd import binding as B
+fake = ctypes.CDLL(None)
+fake.fake_hip_bytes.restype = ctypes.c_size_t
+rng = np.random.default_rng(0)
+cb = (np.arange(16) - 8).astype(np.float32) / 16
+W = np.where(rng.random((1601, 700)) < 0.5, rng.choice(cb, size=(1601, 700)), 0).astype(np.float32)
+h = B.cer_encode(W, cb)
+before = fake.fake_hip_bytes()
+rc, error, held = B.lib().cer_prepare_strips(h.ptr), B.lib().cer_last_hip_error(), fake.fake_hip_bytes()
+tile, strips = B.cer_matmul_tile_columns(h, 47), B.cer_matmul_path_ex(h, 64, B.MatmulOpts(path=B.CER_PATH_STRIP)) == B.CER_PATH_STRIP
+os.environ.pop("FAKE_HIP_FAIL", None)
+again = B.lib().cer_prepare_strips(h.ptr)
+print(rc, error if rc else 0, int(tile > 0), int(strips), again, int(B.cer_matmul_tile_columns(h, 47) > 0))
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-w", "-I/opt/rocm/include", os.path.join(HERE, "fake_hip.cpp"), "-o", lib])
+    return lib
+
+
+# what fails -> (code, HIP error, tile index in use, strips in use; a second call's code, tile index in use then).  HIP errors: 2 out of memory, the
+# others anything else.  Device memory: 1.3 MB of format arrays, 1.2 of strips, 2.4 of tiles.
+@pytest.mark.parametrize("what,want", [
+    ("", (0, 0, 1, 1, 0, 1)),
+    ("launch:tile_index:98", (B.CER_E_HIP, 98, 0, 0, 0, 1)),
+    ("launch:tile_index:700", (B.CER_E_HIP, 700, 0, 0, 0, 1)),
+    ("malloc:TILE:2", (0, 0, 0, 1, 0, 0)),
+    ("malloc:TILE:100", (B.CER_E_HIP, 100, 0, 0, 0, 1)),
+], ids=["none", "launch98", "launch700", "no_memory", "no_device"])
+def test_tile_index_errors(fake, what, want):
+    env = dict(os.environ, LD_PRELOAD=fake, PYTHONPATH=os.path.dirname(HERE), FAKE_HIP_FAIL=what.replace("TILE", "2300000"))
+    out = subprocess.run([sys.executable, "-c", CHILD], env=env, capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stderr
+    got = tuple(int(x) for x in out.stdout.split())
+    assert got == want
