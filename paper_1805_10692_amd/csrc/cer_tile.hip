@@ -239,60 +239,70 @@ __device__ __attribute__((noinline)) void tile_again(uint32_t lds, uint32_t colu
         floatx4 sum[RT][CT] = {};
         float largest[CT] = {};
         uint32_t plus = 0, minus = 0, lost = 0;  // plus, minus: of row lane % R, column xcol + c is bit 16 c + c16
-        // The inputs of a step among which some are not finite, or round to an infinite bf16 number: their pieces.
+        // The inputs of a step among which some are not finite, or round to an infinite bf16 number: their pieces.  (Rows one after the other in
+        // a loop: 16 copies of it would be most of the code.)
         auto take_apart = [&](int s, uint4 (&b)[CT][3]) {
+            if constexpr (!kScaled)
+#pragma unroll 1
+                for (uint32_t i = 0; i < 8; ++i) {
+                    uint64_t up[CT], down[CT], none[CT], any = 0;
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) {
+                        float v = x[s][0][c];
+#pragma unroll
+                        for (uint32_t j = 1; j < 8; ++j) v = i == j ? x[s][j][c] : v;
+                        up[c] = __ballot(v == INFINITY);
+                        down[c] = __ballot(v == -INFINITY);
+                        none[c] = __ballot(v != v);
+                        any |= up[c] | down[c] | none[c];
+                    }
+                    if (any == 0ull) continue;
+#pragma unroll 1
+                    for (uint32_t k = 0; k < 4; ++k) {  // row 8 k + i of the step: 16 lanes' columns
+                        uint32_t bits[3] = {};
+#pragma unroll
+                        for (int c = 0; c < CT; ++c) {
+                            bits[0] |= ((uint32_t)(up[c] >> (16u * k)) & 0xFFFFu) << (16 * c);
+                            bits[1] |= ((uint32_t)(down[c] >> (16u * k)) & 0xFFFFu) << (16 * c);
+                            bits[2] |= ((uint32_t)(none[c] >> (16u * k)) & 0xFFFFu) << (16 * c);
+                        }
+                        const uint32_t one_way = bits[0] | bits[2], other_way = bits[1] | bits[2], all = one_way | other_way;
+                        if (all == 0u) continue;
+                        uint32_t piece[PW];
+                        bool indexed = false;
+#pragma unroll
+                        for (int p = 0; p < PW; ++p) {
+                            piece[p] = *reinterpret_cast<Lds16>((uintptr_t)(a.mine + (uint32_t)p * kPlane + lane % R * kPitch + 2u * (32u * s + 8u * k + i)));
+                            indexed |= piece[p] != (a.fill[p] & 0xFFFFu);
+                            piece[p] <<= 16;
+                        }
+                        float w = __uint_as_float(piece[0]);
+                        if constexpr (kForm == kUniform) w = fmaf(a.grid.scale, w, a.grid.scale * __uint_as_float(piece[PW - 1]));
+                        if constexpr (kForm == 3) w += __uint_as_float(piece[PW > 1 ? 1 : 0]) + __uint_as_float(piece[PW - 1]);
+                        // the terms' signs: of w, or of w - omega0 where indexed, and of omega0
+                        const bool rises = a.dense ? w > 0.f : indexed && w > a.omega0, falls = a.dense ? w < 0.f : indexed && w < a.omega0;
+                        const uint32_t nan = a.dense && !rises && !falls ? all : 0u;
+                        plus |= (rises ? one_way : 0u) | (falls ? other_way : 0u) | nan;
+                        minus |= (rises ? other_way : 0u) | (falls ? one_way : 0u) | nan;
+                        if (!a.dense && a.omega0 != 0.f) {
+                            plus |= a.omega0 > 0.f ? one_way : other_way;
+                            minus |= a.omega0 > 0.f ? other_way : one_way;
+                        }
+                    }
+                }
             uint32_t pieces[CT][3][4];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                uint64_t up[CT], down[CT], none[CT], any = 0;
+            for (int c = 0; c < CT; ++c)
 #pragma unroll
-                for (int c = 0; c < CT; ++c) {
+                for (int i = 0; i < 8; ++i) {
                     float& v = x[s][i][c];
-                    up[c] = __ballot(v == INFINITY);
-                    down[c] = __ballot(v == -INFINITY);
-                    none[c] = __ballot(v != v);
-                    any |= up[c] | down[c] | none[c];
                     v = fabsf(v) < INFINITY ? v : 0.f;
                     lost |= split_lossy(v) ? 1u : 0u;
                     uint32_t p[3];
                     split3_finite(kScaled ? v * 0x1p64f : v, p);
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) pieces[c][j][i >> 1] = i & 1 ? pieces[c][j][i >> 1] | p[j] << 16 : p[j] & 0xFFFFu;
+                    for (int j = 0; j < 3; ++j) pieces[c][j][i >> 1] = i & 1 ? pieces[c][j][i >> 1] | p[j] << 16 : p[j];
                 }
-                if (kScaled || any == 0ull) continue;
-#pragma unroll 1
-                for (uint32_t k = 0; k < 4; ++k) {  // row 8 k + i of the step: 16 lanes' columns
-                    uint32_t bits[3] = {};
-#pragma unroll
-                    for (int c = 0; c < CT; ++c) {
-                        bits[0] |= ((uint32_t)(up[c] >> (16u * k)) & 0xFFFFu) << (16 * c);
-                        bits[1] |= ((uint32_t)(down[c] >> (16u * k)) & 0xFFFFu) << (16 * c);
-                        bits[2] |= ((uint32_t)(none[c] >> (16u * k)) & 0xFFFFu) << (16 * c);
-                    }
-                    const uint32_t one_way = bits[0] | bits[2], other_way = bits[1] | bits[2], all = one_way | other_way;
-                    if (all == 0u) continue;
-                    uint32_t piece[PW];
-                    bool indexed = false;
-#pragma unroll
-                    for (int p = 0; p < PW; ++p) {
-                        piece[p] = *reinterpret_cast<Lds16>((uintptr_t)(a.mine + (uint32_t)p * kPlane + lane % R * kPitch + 2u * (32u * s + 8u * k + i)));
-                        indexed |= piece[p] != (a.fill[p] & 0xFFFFu);
-                        piece[p] <<= 16;
-                    }
-                    float w = __uint_as_float(piece[0]);
-                    if constexpr (kForm == kUniform) w = fmaf(a.grid.scale, w, a.grid.scale * __uint_as_float(piece[PW - 1]));
-                    if constexpr (kForm == 3) w += __uint_as_float(piece[PW > 1 ? 1 : 0]) + __uint_as_float(piece[PW - 1]);
-                    // the terms' signs: of w, or of w - omega0 where indexed, and of omega0
-                    const bool rises = a.dense ? w > 0.f : indexed && w > a.omega0, falls = a.dense ? w < 0.f : indexed && w < a.omega0;
-                    const uint32_t nan = a.dense && !rises && !falls ? all : 0u;
-                    plus |= (rises ? one_way : 0u) | (falls ? other_way : 0u) | nan;
-                    minus |= (rises ? other_way : 0u) | (falls ? one_way : 0u) | nan;
-                    if (!a.dense && a.omega0 != 0.f) {
-                        plus |= a.omega0 > 0.f ? one_way : other_way;
-                        minus |= a.omega0 > 0.f ? other_way : one_way;
-                    }
-                }
-            }
 #pragma unroll
             for (int c = 0; c < CT; ++c)
 #pragma unroll
