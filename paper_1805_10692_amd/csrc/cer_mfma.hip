@@ -264,23 +264,31 @@ __device__ __forceinline__ uint32_t part_begin(uint32_t part, uint32_t kchunk, u
     return part * kchunk + min(part, longer) * kUnit;
 }
 
+// A workgroup's tile and part: tiles along the shorter side are neighbours.
+struct Place {
+    uint32_t few, many, part;
+};
+__device__ __forceinline__ Place place_of(uint32_t item, uint32_t few, uint32_t many, uint32_t splits, uint32_t parts_inside) {
+    const uint32_t rest = item / few, next = parts_inside ? splits : many, last = rest / next, middle = rest - last * next;
+    return Place{item - rest * few, parts_inside ? last : middle, parts_inside ? middle : last};
+}
+
 template <int kForm, int TN>
 __global__ __launch_bounds__(64 * mfma_waves(kForm), 2) void mfma_product_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
-    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, uint32_t longer, size_t split_stride,
-    float faint, float scale) {
+    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, uint32_t longer, uint32_t parts_inside,
+    size_t split_stride, float faint, float scale) {
     using Tile = MfmaTile<kForm, TN>;
     __shared__ Tile tile;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroups are dealt round-robin to the eight XCDs; every XCD takes a contiguous eighth of the list of work items, in
-    // which those that share columns of X (or, with few column tiles, rows of W) are neighbours: they meet in its L2.  The parts of a
-    // split come one after the other, so that an XCD reads its parts of W and X only (with the parts inside, all of W: 980 x 12092, 68 values,
-    // batch 333, 73 us the call, now 68; 703 x 12909, 72 values, batch 449, 75, now 70).
+    // which those that share columns of X (or, with few column tiles, rows of W) are neighbours: they meet in its L2.
     const uint32_t items = row_tiles * col_tiles * splits, eighth = (items + 7u) >> 3;
     const uint32_t item = (blockIdx.x & 7u) * eighth + (blockIdx.x >> 3);
     if ((blockIdx.x >> 3) >= eighth || item >= items) return;
-    const uint32_t sp = item / (row_tiles * col_tiles), in = item % (row_tiles * col_tiles);
-    const uint32_t rt = row_tiles <= col_tiles ? in % row_tiles : in / col_tiles, ct = row_tiles <= col_tiles ? in / row_tiles : in % col_tiles;
+    const uint32_t few = min(row_tiles, col_tiles), many = max(row_tiles, col_tiles);
+    const Place at = place_of(item, few, many, splits, parts_inside);
+    const uint32_t rt = row_tiles <= col_tiles ? at.few : at.many, ct = row_tiles <= col_tiles ? at.many : at.few, sp = at.part;
     const uint32_t row0 = rt * Tile::BM + wave * 32u * Tile::TM, col0 = ct * Tile::BN;
     const uint32_t k_begin = part_begin<Tile::BK>(sp, kchunk, longer), k_end = part_begin<Tile::BK>(sp + 1u, kchunk, longer);
     Out += sp * split_stride;
@@ -412,8 +420,8 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
 template <int kForm, int CT>
 __global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUniform) && CT == 1) ? 2 : 1) void mfma_small_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
-    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, uint32_t longer, size_t split_stride,
-    float faint, float scale) {
+    uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, uint32_t longer, uint32_t,
+    size_t split_stride, float faint, float scale) {
     __shared__ float s_acc[4][2 * CT][16][64];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t items = row_tiles * col_tiles * splits, eighth = (items + 7u) >> 3;
@@ -489,6 +497,14 @@ __global__ __launch_bounds__(256) void mfma_sum_kernel(const float* __restrict__
 }
 
 
+// The parts of a split come one after the other, so that an XCD reads its parts of W and X only (with the parts of a tile next to each
+// other, all of W: 707 x 14221, three pieces, batch 452, 109 us the call instead of 90; 727 x 11065, batch 510, 69 instead of 59), but where the decoded
+// matrix and X fit the L2s of the chip together (32 MB) and the parts are not many: what an XCD has read alone makes the next call's decoder
+// slower (885 x 2357, three pieces, batch 477: 12.0 us instead of 9.1 with the product no faster; 2536 x 963, batch 304, 36.0 us the call instead of 33.5).
+// Either order for 53 such products: 0.981 times the time in the mean, 0.92 to 1.05, where the parts are no more than 20 MB; beyond them 1.00 to 1.10
+// (1476 x 1476, three pieces, batch 968, 28.6 MB: 50 us, 55 with the parts inside).  The small tiles keep them outermost: 0.97 to 1.09, 1.00 in the mean.
+constexpr uint64_t kPartsInside = 26 << 20, kFewParts = 20 << 20;
+
 constexpr uint32_t kPitchStep = 128;  // W's rows are padded to a multiple of this many columns: a round of every variant
 
 int weight_form(const DeviceView& d) { return d.grid.scale != 0.f ? kUniform : d.pieces; }
@@ -496,6 +512,7 @@ int weight_form(const DeviceView& d) { return d.grid.scale != 0.f ? kUniform : d
 struct MfmaShape {
     bool small;
     uint32_t BM, BN, row_tiles, col_tiles, splits, unit, per, longer;  // parts of `per` units of columns, the first ones of one more
+    bool parts_inside = false;  // next to each other
     double us;  // estimate of the product (without the decode)
 };
 
@@ -563,7 +580,7 @@ hipError_t launch_shape(const MfmaShape& s, const uint16_t* W, const float* X, f
     auto* kern = s.small ? (s.BN == 32 ? mfma_small_kernel<kForm, 1> : mfma_small_kernel<kForm, 2>)
                          : (s.BN == 32 ? mfma_product_kernel<kForm, 1> : mfma_product_kernel<kForm, 2>);
     return launch_kernel(kern, grid, dim3(s.small ? 256 : 64 * mfma_waves(kForm)), 0, stream, W, X, out, m, n, L, pitch, plane, s.row_tiles, s.col_tiles, s.splits,
-                         s.per * s.unit, s.longer, count, faint, d.grid.scale);
+                         s.per * s.unit, s.longer, s.parts_inside ? 1u : 0u, count, faint, d.grid.scale);
 }
 
 }  // namespace
@@ -577,9 +594,10 @@ bool mfma_applicable(const DeviceView& d, uint32_t L) {
 double mfma_estimate_us(const DeviceView& d, uint32_t L) { return mfma_shape(d, L).us; }
 
 hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream) {
-    const MfmaShape s = mfma_shape(d, L);
+    MfmaShape s = mfma_shape(d, L);
     const int64_t pitch = (d.n + kPitchStep - 1) / kPitchStep * kPitchStep, plane = pitch * ((d.m + 31) / 32 * 32);
     const size_t count = (size_t)d.m * L;
+    s.parts_inside = (uint64_t)plane * 2 * weight_planes(weight_form(d)) + (uint64_t)d.n * L * 4 <= kPartsInside && count * s.splits * 4 <= kFewParts;
     // one temporary: the partial sums, then the pieces
     const size_t part_bytes = s.splits > 1 ? (count * s.splits * 4 + 255) & ~(size_t)255 : 0;
     unsigned char* tmp = nullptr;
