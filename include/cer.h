@@ -293,7 +293,8 @@ int cer_matmul_path_ex(const cer_handle_t* h, int64_t batch, const cer_matmul_op
  * themselves where they expect it to be the fastest (cer_matmul_path tells); cer_matmul_ex can prefer or avoid it.
  * For handles with 16-bit column indices and at least two values it writes a second one too, the tile index, from which products of
  * some dozens of columns are formed on the matrix cores (cer_matmul_tile_columns): the elements of 16 rows and 64 columns next to each
- * other, 4 bytes each, up to 12 bytes of padding and a 4-byte pointer per 16 rows and 64 columns; not where there is no memory for it.
+ * other, 4 bytes each, up to 12 bytes of padding and a 4-byte pointer per 16 rows and 64 columns; not where no batch is expected to be
+ * faster with it (very sparse matrices of few rows), nor where there is no memory for it.
  * Not thread-safe against products running on the same handle: call it before the handle is shared.  A second call
  * is a no-op.  Errors, which leave the handle as it was: CER_E_INVALID, CER_E_TOO_LARGE, CER_E_NOMEM, CER_E_HIP (no device copy; the
  * allocation of the first index, a copy or the launch that writes the second failed).

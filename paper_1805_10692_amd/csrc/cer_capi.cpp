@@ -1092,26 +1092,28 @@ int cer_prepare_strips(cer_handle_t* h) {
         if (!idx.empty()) e = hipMemcpy(b8, idx.data(), idx.size() * 2, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(b8 + idx_bytes, ptr.data(), ptr_bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) return hip_fail(e);
-        // The tile index, written by a kernel.  Products do without it where there is no memory for it, and only there.
-        const size_t tile_bytes = cer::tile_index_bytes(h->view);
+        cer::DeviceView view = h->view;
+        view.strip_idx = strips.p;
+        view.strip_ptr = reinterpret_cast<const uint32_t*>(b8 + idx_bytes);
+        view.n_strips = (uint32_t)ns;
+        view.strip_rows = (uint32_t)S;
+        view.strip_chunks = nchunks;
+        // The tile index, written by a kernel.  Products do without it where no batch would take it or there is no memory for it, and only there.
+        const size_t tile_bytes = cer::tile_index_pays(view) ? cer::tile_index_bytes(view) : 0;
         if (tile_bytes > 0) {
             e = (hipError_t)cer::handle_alloc(&tile.p, tile_bytes, nullptr);
             if (e == hipErrorOutOfMemory) {
                 (void)hipGetLastError();
                 tile.p = nullptr;
             } else {
-                if (e == hipSuccess) e = (hipError_t)cer::build_tile_index(h->view, tile.p, nullptr);
+                if (e == hipSuccess) e = (hipError_t)cer::build_tile_index(view, tile.p, nullptr);
                 const hipError_t f = hipStreamSynchronize(nullptr);
                 if (e == hipSuccess) e = f;
                 if (e != hipSuccess) return hip_fail(e);
             }
         }
-        h->view.strip_idx = strips.p;
-        h->view.strip_ptr = reinterpret_cast<const uint32_t*>(b8 + idx_bytes);
-        h->view.n_strips = (uint32_t)ns;
-        h->view.strip_rows = (uint32_t)S;
-        h->view.strip_chunks = nchunks;
-        h->view.tile_index = tile.p;
+        view.tile_index = tile.p;
+        h->view = view;
         h->d_strip = strips.release();
         h->d_tile = tile.release();
         return CER_OK;

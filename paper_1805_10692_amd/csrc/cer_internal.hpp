@@ -151,6 +151,8 @@ int matmul_narrow_columns(const DeviceView& v, int64_t L);
 int matmul_fused_rows(const DeviceView& v, int64_t L);
 // Batch columns per workgroup where it multiplies from the tile index instead (0: it does not).
 int matmul_tile_columns(const DeviceView& v, int64_t L);
+// Whether some batch would be multiplied from a tile index if the handle had one (its own is not looked at).
+bool tile_index_pays(const DeviceView& v);
 // bf16 matrices of decode + product (0: it multiplies in fp32).
 int matmul_planes(const DeviceView& v);
 // Fills the handle's rank table (if its layout has one) from the format arrays already in device memory; the launch
@@ -211,7 +213,7 @@ struct cer_matrix {
     void* d_base = nullptr;   // the device allocation of the format arrays
     void* d_split = nullptr;  // row order and parts of long rows (a second, small allocation; null: rows of similar length)
     void* d_strip = nullptr;  // strip-major index (cer_prepare_strips; null: not prepared)
-    void* d_tile = nullptr;   // tile index (cer_prepare_strips too; null: not for this handle, or no memory)
+    void* d_tile = nullptr;   // tile index (cer_prepare_strips too; null: of no use to this handle, or no memory)
     cer::DeviceLayout layout; // where the arrays sit inside it
     size_t d_bytes = 0;       // its size
     int64_t stream_bytes = 0; // bytes of format arrays a product reads

@@ -308,6 +308,22 @@ int matmul_tile_columns(const DeviceView& d, int64_t L) {
     return i.tile ? tile_columns(d, (uint32_t)L, i.temporaries) : 0;
 }
 
+// Batches that are looked at: every one of up to 128 columns, then multiples of 16, where a workgroup's columns are all used, and one column less,
+// which other kernels read in smaller pieces; from 1024 on a 32nd apart.  A query takes 1 to 2 us on the host, the index 4 bytes per element on the
+// device.
+bool tile_index_pays(const DeviceView& v) {
+    if (tile_index_bytes(v) == 0) return false;
+    const MatmulOptions o;
+    DeviceView d = v;
+    d.tile_index = &d;  // (the estimates do not read it)
+    auto taken = [&](uint32_t L) { return choose_instead(d, L, o, choose_batched_path(d, L, o, false, nullptr)).tile; };
+    for (uint32_t L = 2; L < 128u; ++L)
+        if (taken(L)) return true;
+    for (uint32_t L = 128; L <= (1u << 20); L += L < 1024u ? 16u : (L / 32u) & ~15u)
+        if (taken(L) || taken(L - 1u)) return true;
+    return false;
+}
+
 int matmul_planes(const DeviceView& d) { return mfma_applicable(d, 2) ? mfma_planes(d) : 0; }
 
 size_t matmul_workspace_floats(const DeviceView& d, int64_t L, const MatmulOptions& o) {

@@ -50,3 +50,33 @@ def test_tile_index_errors(fake, what, want):
     assert out.returncode == 0, out.stderr
     got = tuple(int(x) for x in out.stdout.split())
     assert got == want
+
+
+USES = """
+import ctypes, sys
+import numpy as np
+from paper_1805_10692_amd import binding as B
+fake = ctypes.CDLL(None)
+fake.fake_hip_bytes.restype = ctypes.c_size_t
+m, n, indexed = int(sys.argv[1]), int(sys.argv[2]), float(sys.argv[3])
+rng = np.random.default_rng(0)
+cb = (np.arange(64) - 32).astype(np.float32) / 32
+W = np.where(rng.random((m, n)) < indexed, rng.choice(cb[cb != 0], size=(m, n)), 0).astype(np.float32)
+h = B.cer_encode(W, cb)
+before = fake.fake_hip_bytes()
+assert B.lib().cer_prepare_strips(h.ptr) == 0
+batches = [L for L in range(2, 1000) if B.cer_matmul_tile_columns(h, L) > 0]
+print(fake.fake_hip_bytes() - before, np.count_nonzero(W), len(batches))
+"""
+
+
+@pytest.mark.parametrize("m,n,indexed,used", [(300, 20000, 0.01, False), (1000, 9000, 0.004, False), (1601, 700, 0.5, True), (300, 20000, 0.1, True)])
+def test_tile_index_only_where_it_is_used(fake, m, n, indexed, used):
+    """The tile index (4 bytes per element and more) is written where some batch is multiplied from it, and nowhere else.  The strips take 2
+    bytes per element, up to 14 of padding per row and strip of 1024 columns and 4 for a pointer each."""
+    env = dict(os.environ, LD_PRELOAD=fake, PYTHONPATH=os.path.dirname(HERE))
+    out = subprocess.run([sys.executable, "-c", USES, str(m), str(n), str(indexed)], env=env, capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stderr
+    held, nnz, batches = (int(x) for x in out.stdout.split())
+    strips = 2 * nnz + 18 * m * -(-n // 1024) + 2048
+    assert (batches > 0) == used and (held > strips + 3 * nnz) == used and (used or held <= strips)
