@@ -466,36 +466,41 @@ __global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUnifor
 
 // The sums of the parts.  Bound by the bytes: four floats per thread and load, four loads in flight; the parts of 512 x 4608, batch 3136
 // (five of 6.4 MB) 6.6 us, with one float per load 8.3.
+// Many parts (kManyParts) are added in binary64: each addition rounds the sum once more, and from as many as a part's own running sums have
+// steps of 16 columns (kFlush) they would round more than those.  The same time; 504 products of 200 to 1024 rows of 4000 to 65000 columns
+// end 0.67 times as far from fp64 in the mean (2-norm), 300 x 40000, three pieces, batch 99, X of one sign 2.9e-8 instead of 7.2e-8.
+constexpr uint32_t kManyParts = kFlush / 16;
 typedef float FourFloats __attribute__((ext_vector_type(4), aligned(4)));
+typedef double FourDoubles __attribute__((ext_vector_type(4)));
+template <typename Four>
 __global__ __launch_bounds__(256) void mfma_sum_kernel(const float* __restrict__ part, float* __restrict__ Y, size_t count,
                                                        uint32_t splits) {
     const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4u;
     if (i >= count) return;
     const float* p = part + i;
     // (the last thread's four end behind a part by up to three floats: in the next one or in W, which follows the last)
-    FourFloats a = {}, b = {};
+    Four a = {}, b = {};
     uint32_t s = 0;
     for (; s + 4u <= splits; s += 4u) {
         FourFloats v[4];
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const FourFloats*>(p + (size_t)(s + k) * count);
-        a += v[0];
-        b += v[1];
-        a += v[2];
-        b += v[3];
+        a += __builtin_convertvector(v[0], Four);
+        b += __builtin_convertvector(v[1], Four);
+        a += __builtin_convertvector(v[2], Four);
+        b += __builtin_convertvector(v[3], Four);
     }
     for (; s < splits; ++s) {
-        const FourFloats v = *reinterpret_cast<const FourFloats*>(p + (size_t)s * count);
+        const Four v = __builtin_convertvector(*reinterpret_cast<const FourFloats*>(p + (size_t)s * count), Four);
         if (s & 1u) b += v; else a += v;
     }
-    a += b;
+    const FourFloats y = __builtin_convertvector(a + b, FourFloats);
     if (i + 4u <= count) {
-        *reinterpret_cast<FourFloats*>(Y + i) = a;
+        *reinterpret_cast<FourFloats*>(Y + i) = y;
     } else {
-        for (uint32_t k = 0; i + k < count; ++k) Y[i + k] = a[k];
+        for (uint32_t k = 0; i + k < count; ++k) Y[i + k] = y[k];
     }
 }
-
 
 // The parts of a split come one after the other, so that an XCD reads its parts of W and X only (with the parts of a tile next to each
 // other, all of W: 707 x 14221, three pieces, batch 452, 109 us the call instead of 90; 727 x 11065, batch 510, 69 instead of 59), but where the decoded
@@ -618,7 +623,7 @@ hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L
         }
     }
     if (e == hipSuccess && s.splits > 1)
-        e = launch_kernel(mfma_sum_kernel, dim3((uint32_t)((count + 1023) / 1024)), dim3(256), 0, stream, out, Y, count, s.splits);
+        e = launch_kernel(s.splits < kManyParts ? mfma_sum_kernel<FourFloats> : mfma_sum_kernel<FourDoubles>, dim3((uint32_t)((count + 1023) / 1024)), dim3(256), 0, stream, out, Y, count, s.splits);
     const hipError_t f = (hipError_t)temp_free(tmp, stream);
     return e == hipSuccess ? f : e;
 }

@@ -192,3 +192,30 @@ def test_parts_of_unequal_length(shape, pieces):
         odd = ~np.isfinite(want)
         assert np.array_equal(Y[odd], want[odd], equal_nan=True), what
         assert (np.abs(Y[~odd] - want[~odd]) <= bound[~odd]).all(), what
+
+
+@pytest.mark.parametrize("pieces,m,n,L,fused", [("one", 200, 64990, 99, False), ("two", 200, 64990, 41, False), ("three", 200, 64990, 200, False),
+                                                ("grid", 200, 64990, 41, False), ("three", 300, 40000, 41, True)])
+def test_sums_of_many_parts_are_rounded_once(pieces, m, n, L, fused):
+    """Terms of one sign, so that the parts of W's columns add up to much more than each of them: they are added in binary64, and what is left is
+    the rounding of the result, 2^-24 of it at most and 0.58 of that in the root of the mean square, and the parts' own errors, which are
+    smaller by the root of their number.  (Added in binary32: 0.73 to 1.2 of 2^-24.)  2-norm."""
+    rng = np.random.default_rng(n + L)
+    cb = {"one": np.arange(9) / 8, "two": np.sort(rng.choice(np.arange(257, 32768), 23, replace=False) | 1) / 32768, "three": np.sort(rng.uniform(0, 1, 23)),
+          "grid": np.arange(18) * np.float32(0.0123)}[pieces].astype(np.float32)
+    if cb[0] != 0:
+        cb = np.concatenate([np.zeros(1, np.float32), cb])
+    W = np.where(rng.random((m, n), dtype=np.float32) < (0.15 if fused else 0.5), cb[rng.integers(1, len(cb), size=(m, n))], np.float32(0))
+    X = np.abs(rng.standard_normal((n, L), dtype=np.float32)) + 1
+    h = B.cer_encode(W, cb)
+    assert B.cer_matmul_planes(h) == {"one": 1, "two": 2, "three": 3, "grid": 2}[pieces]
+    Y = torch.empty((m, L), device="cuda")
+    if fused:
+        assert B.cer_matmul_fused_rows(h, L) > 0
+        B.cer_matmul(h, torch.from_numpy(X).cuda(), Y, L)
+    else:
+        B.cer_matmul_ex(h, torch.from_numpy(X).cuda(), Y, L, None, B.MatmulOpts(path=B.CER_PATH_DENSE))
+    torch.cuda.synchronize()
+    B.cer_free(h)
+    want = W.astype(np.float64) @ X.astype(np.float64)
+    assert np.linalg.norm(Y.cpu().numpy() - want) <= 2 / 3 * 2.0 ** -24 * np.linalg.norm(want)
