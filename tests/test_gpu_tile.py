@@ -172,3 +172,32 @@ def test_large_inputs_that_cancel(name, m, n, L):
     Y = _product(h, Z, m, L)
     assert np.array_equal(np.isfinite(Y), np.isfinite(want)) and np.allclose(Y, want, rtol=1e-6, atol=0)
     B.cer_free(h)
+
+
+# (codebook, m, n, share of indexed elements, L, columns per workgroup, rows per workgroup of decode + product in one launch without the index)
+WIDE = [("one_piece", 200, 64990, 0.5, 41, 16, 0), ("one_piece", 300, 40000, 0.15, 99, 48, 0), ("one_piece", 700, 4000, 0.5, 99, 64, 16),
+        ("grid", 200, 64990, 0.5, 200, 48, 0), ("grid", 300, 40000, 0.15, 41, 16, 16), ("three_pieces", 300, 40000, 0.15, 200, 64, 16)]
+
+
+@pytest.mark.parametrize("name,m,n,indexed,L,columns,fused", WIDE)
+def test_long_sums(name, m, n, indexed, L, columns, fused):
+    """Rows up to the widest, where a wave's running sums are longest (an eighth of a part of W's columns for one piece and for grids): not
+    further from fp64 (2-norm) than the strips, the gathers, or decode + product in one launch where that is what runs without the index.  X of one
+    sign: the result's rounding, 0.58 of 2^-24 at most in the root of the mean square, and as much for the waves' sums and their running sums
+    before them together make no more than 2^-24 unless the latter grow with n."""
+    cb = {"one_piece": (np.arange(17) - 8).astype(np.float32) / 8, "grid": ((np.arange(35) - 17) * np.float32(0.0123)).astype(np.float32)}.get(name, OFF_GRID)
+    zero = int(np.argmin(np.abs(cb)))
+    rng = np.random.default_rng(n + L)
+    W = np.where(rng.random((m, n), dtype=np.float32) < indexed, cb[rng.integers(0, len(cb), size=(m, n))], cb[zero]).astype(np.float32)
+    h, plain = _prepared(W, cb), B.cer_encode(W, cb)
+    assert B.cer_matmul_tile_columns(h, L) == columns and B.cer_matmul_fused_rows(plain, L) == fused
+    W64, normal = W.astype(np.float64), rng.standard_normal((n, L), dtype=np.float32)
+    for X in (normal, np.abs(normal) + np.float32(1)):
+        want = W64 @ X.astype(np.float64)
+        err = np.linalg.norm(_product(h, X, m, L) - want)
+        for other in (_product(h, X, m, L, opts=B.MatmulOpts(path=B.CER_PATH_STRIP)), _product(h, X, m, L, opts=B.MatmulOpts(path=B.CER_PATH_GEMM)),
+                      *([_product(plain, X, m, L)] if fused else [])):
+            assert err <= np.linalg.norm(other - want)
+        assert X is normal or err <= 2.0 ** -24 * np.linalg.norm(want)
+    B.cer_free(h)
+    B.cer_free(plain)
