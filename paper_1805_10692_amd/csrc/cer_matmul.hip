@@ -162,10 +162,6 @@ hipError_t launch_densified(const DeviceView& d, const float* X, float* Y, uint3
 // 0.85 / 0.9 / 0.95 / 1 give 1.125 / 1.133 / 1.132 / 1.138 times the speed on average and make 4 / 5 / 9 / 11 of them slower.
 constexpr double kFusedMargin = 0.9;
 
-// A prepared handle's tile index is used where that is expected to take less than this share of what would run without it (of 100 random
-// products of such handles 33, one of them slower: 21 -> 25 us).
-constexpr double kTileMargin = 0.95;
-
 // Whether the LDS variant is expected to beat the kernel that gathers from L2.  Measured on MI355X: for wide
 // batches it never does -- gathers of 16- or 32-byte pieces at random LDS addresses are bank-conflict bound at
 // 32 - 43 B/clk per CU, while the L2 kernel's gathers of whole 128-byte rows sustain 27 - 48 B/clk per CU and
@@ -228,6 +224,29 @@ double path_estimate_us(const DeviceView& d, uint32_t L, int path) {
     return gather_estimate(d, L) * 1e6;
 }
 
+// Estimated duration (microseconds) below which products from a prepared handle's tile index are taken, where `path` runs without it, or (one)
+// decode + product in one launch or the stream kernel, which are expected to take `us`.
+// 11000 random products of prepared handles (256 to 4096 rows of 512 to 25088 columns, 2 to 3136 batch columns, 0.5 to 75 % indexed, 2 to 64
+// values), each with the tile index and without: a fifth takes it, at 1.28 times the speed in the geometric mean; one in ninety is slower by more than
+// 2 %, one in 140 by more than 5 %, 1.25 times at most.  With 0.95 times the estimates that the other choices go by
+// one in fourteen was slower, by up to 3.3 times (3135 x 1433, batch 101, 2 % indexed: 5.5 -> 12 us), because
+//   * a wave of gather_estimate takes 4 us whatever its row holds; rows of some dozens of elements take less (38 % too much; typical deviation
+//     of the terms below 15 %)
+//   * plan_strip has 6 us for workgroups with next to nothing to stream, which small matrices do not take
+//   * the product of the decoded matrix has become faster for uniform codebooks than densify_estimates has it (14 to 22 % too much from 100
+//     columns on).
+// (Those estimates are as the choice between the other kernels was fitted with them.)
+double tile_limit_us(const DeviceView& d, uint32_t L, int path, bool one, double us) {
+    const double colsum = d.omega0 != 0.f ? 5.0 + (double)d.n * L * 4.0 / 4e6 : 0.0;
+    if (one) return 0.95 * us;
+    if (path == kPathStrip && L > 16) return 0.91 * (plan_strip(d, L).fitted_us + colsum);
+    if (path == 3 && d.pieces > 1) return (d.grid.scale == 0.f ? 0.925 : (L < 100 ? 0.95 : 0.75)) * us;
+    if (path != 1 || d.row_order) return 0.95 * us;
+    const double waves = (double)d.m * std::ceil((double)L / 32.0) * std::min(4.0, 0.7 + 0.005 * (double)d.nnz / (double)d.m) / 4096.0;
+    const double gathers = gemm_gather_us(d, L);
+    return 0.78 * (4.0 + std::max(gathers, waves) + 0.3 * std::min(gathers, waves) + colsum);
+}
+
 // What the library's own choice runs instead of `path` (a path, flags or a tile width of the caller's speak of the others):
 // the stream kernel for several columns (narrow: its columns per pass), decode + product in one launch (fused: its rows per
 // workgroup), or products from the handle's tile index (tile).  temporaries: the last two may have partial sums -- only where the kernel
@@ -250,7 +269,7 @@ Instead choose_instead(const DeviceView& d, uint32_t L, const MatmulOptions& o, 
     r.temporaries = r.narrow == 0 && (path == 3 || path == kPathStrip || d.omega0 != 0.f || d.n_split_parts > 0);
     r.fused = fused_rows(d, L, r.temporaries, kFusedMargin * us, &us);
     if (r.fused > 0) r.narrow = 0;
-    if (d.tile_index && tile_estimate_us(d, L, r.temporaries) < kTileMargin * us) {
+    if (d.tile_index && tile_estimate_us(d, L, r.temporaries) < tile_limit_us(d, L, path, r.fused > 0 || r.narrow > 0, us)) {
         r.tile = true;
         r.narrow = r.fused = 0;
     }

@@ -364,6 +364,7 @@ StripPlan plan_strip(const DeviceView& d, uint32_t L) {
     // short rows: some quad of a wave ends a row in nearly every iteration, and the whole wave walks through that branch
     const double per_round = (L <= 16u ? 0.6 : 1.0) * kStripRoundUs * (1.0 + 1.5 / std::max(chunks_per_row, 1.0));
     p.est_us = wg_rounds * (rounds * per_round + 7.0) + 3.0 + (3.0 + 2.0 * partial_bytes / 5e6);
+    p.fitted_us = wg_rounds * (rounds * 1.1 * per_round + 6.0) + 2.0 + (3.0 + 2.0 * partial_bytes / 5e6);
     // workgroups with next to nothing to stream (2048 x 2048 cells: 16 rows each) measure 17 - 21 us whatever they hold
     if (rounds < 8.0) p.est_us += 6.0;
     // the library itself never asks for more than 1 GiB of partial sums (as for the decoded matrix of the dense route)

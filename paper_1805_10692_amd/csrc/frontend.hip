@@ -1492,8 +1492,10 @@ bool mostly_implicit(int64_t nnz, int64_t m, int64_t n) { return (double)nnz * 2
 // Whether emit_sorted_kernel is expected to be ahead.  Clocks, where half or more is indexed: a row sorted in LDS takes 125 per 64 columns, 60
 // per codebook position and 10000 (its start, the pointers, the way out), and its LDS limits how many of them a compute unit holds;
 // emit_kernel takes 800 per 64 columns of a row, one after another, or 72 of a compute unit's time.  Whole calls, emit_kernel / emit_sorted_kernel,
-// us: 300 x 9000, 7 bits 115 / 90, 8 bits 118 / 97; 1000 x 2000, 6 bits 74 / 67; 4096 x 9216, 7 bits 236 / 233, 8 bits 231 / 275; 2048 x 4096,
-// 7 bits 101 / 99, 8 bits 102 / 122; 4096 x 2050, 7 bits 112 / 119; equally frequent values 4096 x 9216, 100 of them 274 / 163, 256 323 / 226.
+// us: 300 x 9000, 7 bits 90 / 65, 8 bits 91 / 70; 1000 x 2000, 6 bits 59 / 54; 4096 x 9216, 7 bits 158 / 148, 8 bits 173 / 192; 2048 x 4096,
+// 7 bits 80 / 76, 8 bits 82 / 96; 4096 x 2050, 7 bits 84 / 86.  Of 165 such matrices it takes the slower one for eight, by up to 11 % (2092 x 2716, 98
+// values, 81 / 73).  Where large matrices have many equally frequent values emit_kernel takes far longer, which the sizes do not tell: 4096 x
+// 9216, 100 of them 313 / 193, but 256 474 / 245, where emit_kernel serves.
 // Where fewer are, emit_kernel packs a row's elements first, which takes 160 per 64 columns, and 640 per 64 elements behind it; the terms are
 // fitted to 68 such matrices (256 to 4096 rows of 1024 to 25088 columns, 2 to 49 % indexed, 4 to 256 values), compressed by either kernel: the
 // one taken is 0.4 % slower than the better one in the mean, always emit_kernel 11 %.  Whole calls: 1024 x 9216, 5 bits 106 / 79; 4096 x 9216, 5

@@ -176,7 +176,7 @@ def test_large_inputs_that_cancel(name, m, n, L):
 
 # (codebook, m, n, share of indexed elements, L, columns per workgroup, rows per workgroup of decode + product in one launch without the index)
 WIDE = [("one_piece", 200, 64990, 0.5, 41, 16, 0), ("one_piece", 300, 40000, 0.15, 99, 48, 0), ("one_piece", 700, 4000, 0.5, 99, 64, 16),
-        ("grid", 200, 64990, 0.5, 200, 48, 0), ("grid", 300, 40000, 0.15, 41, 16, 16), ("three_pieces", 300, 40000, 0.15, 200, 64, 16)]
+        ("grid", 200, 64990, 0.5, 130, 48, 0), ("grid", 640, 25088, 0.4, 99, 48, 16), ("three_pieces", 300, 40000, 0.15, 200, 64, 16)]
 
 
 @pytest.mark.parametrize("name,m,n,indexed,L,columns,fused", WIDE)

@@ -80,3 +80,31 @@ def test_tile_index_only_where_it_is_used(fake, m, n, indexed, used):
     held, nnz, batches = (int(x) for x in out.stdout.split())
     strips = 2 * nnz + 18 * m * -(-n // 1024) + 2048
     assert (batches > 0) == used and (held > strips + 3 * nnz) == used and (used or held <= strips)
+
+
+CHOICES = """
+import sys
+import numpy as np
+from paper_1805_10692_amd import binding as B
+m, n, L, K, indexed = int(sys.argv[1]), int(sys.argv[2]), int(sys.argv[3]), int(sys.argv[4]), float(sys.argv[5])
+rng = np.random.default_rng(0)
+cb = (np.arange(K) - K // 2).astype(np.float32) * np.float32(float(sys.argv[6]))
+W = np.where(rng.random((m, n)) < indexed, rng.choice(cb[cb != 0], size=(m, n)), 0).astype(np.float32)
+h = B.cer_encode(W, cb)
+assert B.lib().cer_prepare_strips(h.ptr) == 0
+print(B.cer_matmul_tile_columns(h, L))
+"""
+
+
+# (m, n, batch, values, share of indexed elements, distance of the values), us with the tile index / without
+@pytest.mark.parametrize("m,n,L,K,indexed,step,taken", [
+    (3135, 1433, 101, 4, 0.015, 0.0123, False),  # 12.1 / 5.4
+    (823, 1385, 380, 16, 0.019, 0.0625, False),  # 9.4 / 5.0
+    (787, 999, 2826, 17, 0.53, 0.0123, False),   # 48 / 40
+    (2174, 22075, 71, 32, 0.2, 0.0625, True),    # 50 / 93
+    (2000, 4000, 64, 16, 0.5, 0.0625, True), (1999, 999, 130, 64, 0.5, 0.0625, True)])
+def test_choice_of_the_tile_index(fake, m, n, L, K, indexed, step, taken):
+    env = dict(os.environ, LD_PRELOAD=fake, PYTHONPATH=os.path.dirname(HERE))
+    out = subprocess.run([sys.executable, "-c", CHOICES, *map(str, (m, n, L, K, indexed, step))], env=env, capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stderr
+    assert (int(out.stdout) > 0) == taken
