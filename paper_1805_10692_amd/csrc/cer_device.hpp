@@ -424,17 +424,23 @@ hipError_t launch_narrow(const DeviceView& d, const float* X, float* Y, uint32_t
 int fused_rows(const DeviceView& d, uint32_t L, bool temporaries, double below, double* us = nullptr);
 hipError_t launch_fused(const DeviceView& d, const float* X, float* Y, uint32_t L, bool temporaries, bool dense_zeros, hipStream_t stream);
 
-// cer_tile.hip -- batch > 1, matrix cores, tiles of W laid out in LDS from the handle's tile index.  tile_estimate_us: 1e30 where it is
-// not applicable.  temporaries, dense_zeros: as for launch_fused.
+// cer_tile.hip -- batch > 1, matrix cores, tiles of W laid out in LDS from the handle's tile index.  plan_tile: the best plan that is expected to
+// take less than `below` microseconds (variant -1: there is none, or no tile index).  temporaries, dense_zeros: as for launch_fused.
 struct TileIndexShape {
     uint32_t segs = 0, groups = 0;
     size_t ptr_bytes = 0, bytes = 0;  // of its pointers; all of it
 };
 TileIndexShape tile_index_shape(const DeviceView& d);
 hipError_t launch_tile_index(const DeviceView& d, void* index, hipStream_t stream);
-double tile_estimate_us(const DeviceView& d, uint32_t L, bool temporaries);
-int tile_columns(const DeviceView& d, uint32_t L, bool temporaries);  // of the batch, per workgroup
-hipError_t launch_tile(const DeviceView& d, const float* X, float* Y, uint32_t L, bool temporaries, bool dense_zeros, hipStream_t stream);
+struct TilePlan {
+    int variant = -1;
+    uint32_t row_blocks = 0, col_tiles = 0, splits = 1, per = 0;
+    size_t lds = 0;
+    double us = 0;
+};
+TilePlan plan_tile(const DeviceView& d, uint32_t L, bool temporaries, double below);
+int tile_columns(const TilePlan& p);  // of the batch, per workgroup
+hipError_t launch_tile(const DeviceView& d, const TilePlan& p, const float* X, float* Y, uint32_t L, bool dense_zeros, hipStream_t stream);
 
 // cer_strip.hip -- batch > 1, strips of X resident in LDS (needs the strip-major index of cer_prepare_strips)
 bool strip_applicable(const DeviceView& d, const float* X, const float* Y, uint32_t L);

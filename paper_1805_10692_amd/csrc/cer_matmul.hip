@@ -116,21 +116,23 @@ hipError_t launch_colsum(const float* X, uint32_t n, uint32_t L, float* part, ui
 //   * waves: every (row, tile) is a wave whose start-up chain (descriptor -> pointers -> indices -> first gathers) takes about
 //     4 us, 4096 of them in flight: what bounds matrices of many short rows (16384 x 512: batch 128 64 - 84 us)
 //   * the column sums of X for a non-zero most frequent value: two launches and a pass over X
-double gather_estimate(const DeviceView& d, uint32_t L) {
+// A call asks for it several times (0.3 us of the host's time each): gathers_us, gemm_gather_us where that is known already.
+double gather_estimate(const DeviceView& d, uint32_t L, double* gathers_us) {
     const double tiles = std::ceil((double)L / 32.0);
     const double t_waves = (double)d.m * tiles * 4e-6 / 4096.0;
-    return 4e-6 + std::max(gemm_gather_us(d, L) * 1e-6, t_waves) + (d.omega0 != 0.f ? 5e-6 + (double)d.n * L * 4.0 / 4e12 : 0.0);
+    if (*gathers_us < 0) *gathers_us = gemm_gather_us(d, L);
+    return 4e-6 + std::max(*gathers_us * 1e-6, t_waves) + (d.omega0 != 0.f ? 5e-6 + (double)d.n * L * 4.0 / 4e12 : 0.0);
 }
 
 // Estimated durations (seconds) of the gathers and of decode + dense; false where the dense route is not available.
-bool densify_estimates(const DeviceView& d, uint32_t L, double* t_gather_out, double* t_dense_out) {
+bool densify_estimates(const DeviceView& d, uint32_t L, double* gathers_us, double* t_gather_out, double* t_dense_out) {
     if (L < 2 || d.m < 128 || d.n < 256) return false;
     const double mn = (double)d.m * (double)d.n;
     if ((double)d.nnz * 10.0 < mn) return false;  // the matrix cores spend ten times the multiply-adds: not worth estimating
     const bool pieces = mfma_applicable(d, L);
     if (mn * (pieces ? 2.0 * mfma_planes(d) : 4.0) > (double)(1ull << 30)) return false;
     const double flops = 2.0 * mn * L;
-    const double t_gather = gather_estimate(d, L);
+    const double t_gather = gather_estimate(d, L, gathers_us);
     double t_dense;
     if (pieces) {
         // the decoder: 7 us (578 x 1013), 9 us (conv shape), 11 us (633 x 5106, three pieces, 2.3 M indices), 15 us (1084 x
@@ -176,7 +178,7 @@ bool xtile_pays(const DeviceView& d, uint32_t L) { return L <= 8 && d.nnz >= 250
 // Which kernel serves a batch of L > 1 columns (cer_matmul_path's numbering: 1, 2 or 3).  A preferred kernel is
 // taken whenever it is applicable; otherwise the estimates decide.  no_temporaries: only kernels that need no
 // temporary memory (the decode + dense route and batches of more than one LDS tile are left out).
-int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o, bool no_temporaries, XtilePlan* plan_out,
+int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o, bool no_temporaries, double* gathers_us, XtilePlan* plan_out,
                         const float* X = nullptr, const float* Y = nullptr) {
     const bool has_elements = d.m > 0 && d.n > 0;
     // strips of X in LDS: on request (and only when the strip-major index was prepared); the partial sums of the strips
@@ -189,7 +191,7 @@ int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o,
     double t_strip = 0;
     if (o.path < 0 && strips_ok && has_elements) {
         t_strip = plan_strip(d, L).est_us * 1e-6;
-        const double t_gather_l2 = gather_estimate(d, L);
+        const double t_gather_l2 = gather_estimate(d, L, gathers_us);
         strips_beat_gathers = t_strip < 0.95 * t_gather_l2;
     }
     // (from 8 columns on the strips are ahead of the LDS tile of all input rows: AlexNet-fc6 shape batch 8 15 against 22 us)
@@ -207,7 +209,7 @@ int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o,
     // estimate keeps the gathers); 3x3 convolution shape, batch 3136: 191 us against 53 us decoded and multiplied.
     if (o.path < 0 && !no_temporaries && has_elements) {
         double t_gather = 0, t_dense = 0;
-        const bool dense_ok = densify_estimates(d, L, &t_gather, &t_dense);
+        const bool dense_ok = densify_estimates(d, L, gathers_us, &t_gather, &t_dense);
         const bool dense_pays = dense_ok && t_gather > 1.05 * t_dense;
         if (strips_beat_gathers && (!dense_pays || t_strip < t_dense)) return kPathStrip;
         if (dense_pays) return 3;
@@ -216,16 +218,16 @@ int choose_batched_path(const DeviceView& d, uint32_t L, const MatmulOptions& o,
 }
 
 // Estimated duration (microseconds) of the kernel that choose_batched_path has named.
-double path_estimate_us(const DeviceView& d, uint32_t L, int path) {
+double path_estimate_us(const DeviceView& d, uint32_t L, int path, double* gathers_us) {
     if (path == kPathStrip) return plan_strip(d, L).est_us;
     if (path == 2) return 4.0 + (double)d.nnz * 3.2e-6;  // AlexNet-fc6 shape batch 2 / 4 / 8: 23 / 13 / 28 us
     double t_gather = 0, t_dense = 0;
-    if (path == 3 && densify_estimates(d, L, &t_gather, &t_dense)) return t_dense * 1e6;
-    return gather_estimate(d, L) * 1e6;
+    if (path == 3 && densify_estimates(d, L, gathers_us, &t_gather, &t_dense)) return t_dense * 1e6;
+    return gather_estimate(d, L, gathers_us) * 1e6;
 }
 
 // Estimated duration (microseconds) below which products from a prepared handle's tile index are taken, where `path` runs without it, or (one)
-// decode + product in one launch or the stream kernel, which are expected to take `us`.
+// decode + product in one launch or the stream kernel, which are expected to take `us`.  gathers: gemm_gather_us.
 // 11000 random products of prepared handles (256 to 4096 rows of 512 to 25088 columns, 2 to 3136 batch columns, 0.5 to 75 % indexed, 2 to 64
 // values), each with the tile index and without: a fifth takes it, at 1.28 times the speed in the geometric mean; one in ninety is slower by more than
 // 2 %, one in 140 by more than 5 %, 1.25 times at most.  With 0.95 times the estimates that the other choices go by
@@ -236,14 +238,13 @@ double path_estimate_us(const DeviceView& d, uint32_t L, int path) {
 //   * the product of the decoded matrix has become faster for uniform codebooks than densify_estimates has it (14 to 22 % too much from 100
 //     columns on).
 // (Those estimates are as the choice between the other kernels was fitted with them.)
-double tile_limit_us(const DeviceView& d, uint32_t L, int path, bool one, double us) {
+double tile_limit_us(const DeviceView& d, uint32_t L, int path, bool one, double us, double gathers) {
     const double colsum = d.omega0 != 0.f ? 5.0 + (double)d.n * L * 4.0 / 4e6 : 0.0;
     if (one) return 0.95 * us;
     if (path == kPathStrip && L > 16) return 0.91 * (plan_strip(d, L).fitted_us + colsum);
     if (path == 3 && d.pieces > 1) return (d.grid.scale == 0.f ? 0.925 : (L < 100 ? 0.95 : 0.75)) * us;
     if (path != 1 || d.row_order) return 0.95 * us;
     const double waves = (double)d.m * std::ceil((double)L / 32.0) * std::min(4.0, 0.7 + 0.005 * (double)d.nnz / (double)d.m) / 4096.0;
-    const double gathers = gemm_gather_us(d, L);
     return 0.78 * (4.0 + std::max(gathers, waves) + 0.3 * std::min(gathers, waves) + colsum);
 }
 
@@ -253,12 +254,13 @@ double tile_limit_us(const DeviceView& d, uint32_t L, int path, bool one, double
 // they take the place of has a temporary as well.
 struct Instead {
     int narrow = 0, fused = 0;
-    bool temporaries = false, tile = false;
+    bool temporaries = false;
+    TilePlan tile;  // variant -1: not taken
 };
-Instead choose_instead(const DeviceView& d, uint32_t L, const MatmulOptions& o, int path) {
+Instead choose_instead(const DeviceView& d, uint32_t L, const MatmulOptions& o, int path, double* gathers_us) {
     Instead r;
     if (L < 2 || o.path >= 0 || o.flags != 0 || o.tile_cols != 0) return r;
-    double us = path_estimate_us(d, L, path);
+    double us = path_estimate_us(d, L, path, gathers_us);
     if (L <= 16) {
         const NarrowEstimate narrow = narrow_estimate(d, L);
         if (narrow.us < us) {
@@ -269,11 +271,19 @@ Instead choose_instead(const DeviceView& d, uint32_t L, const MatmulOptions& o, 
     r.temporaries = r.narrow == 0 && (path == 3 || path == kPathStrip || d.omega0 != 0.f || d.n_split_parts > 0);
     r.fused = fused_rows(d, L, r.temporaries, kFusedMargin * us, &us);
     if (r.fused > 0) r.narrow = 0;
-    if (d.tile_index && tile_estimate_us(d, L, r.temporaries) < tile_limit_us(d, L, path, r.fused > 0 || r.narrow > 0, us)) {
-        r.tile = true;
-        r.narrow = r.fused = 0;
+    if (d.tile_index) {
+        r.tile = plan_tile(d, L, r.temporaries, tile_limit_us(d, L, path, r.fused > 0 || r.narrow > 0, us, *gathers_us));
+        if (r.tile.variant >= 0) r.narrow = r.fused = 0;
     }
     return r;
+}
+
+// What the library runs by its own choice for a batch of L > 1 columns.
+Instead choose_all(const DeviceView& d, uint32_t L) {
+    const MatmulOptions o;
+    double gathers_us = -1;
+    const int path = choose_batched_path(d, L, o, false, &gathers_us, nullptr);
+    return choose_instead(d, L, o, path, &gathers_us);
 }
 
 // Column sums of X for a non-zero most frequent value: shape of the two-stage sum and the floats it needs
@@ -307,24 +317,21 @@ ColsumPlan plan_colsum(uint32_t n, uint32_t L) {
 int matmul_path(const DeviceView& d, int64_t L, const MatmulOptions& o) {
     if (L <= 1) return gemv_path(d, o);
     if (L > 0x7FFFFFFFll) return 1;
-    return choose_batched_path(d, (uint32_t)L, o, false, nullptr);
+    double gathers_us = -1;
+    return choose_batched_path(d, (uint32_t)L, o, false, &gathers_us, nullptr);
 }
 
 int matmul_narrow_columns(const DeviceView& d, int64_t L) {
-    const MatmulOptions o;
-    return L < 2 || L > 16 ? 0 : choose_instead(d, (uint32_t)L, o, choose_batched_path(d, (uint32_t)L, o, false, nullptr)).narrow;
+    return L < 2 || L > 16 ? 0 : choose_all(d, (uint32_t)L).narrow;
 }
 
 int matmul_fused_rows(const DeviceView& d, int64_t L) {
-    const MatmulOptions o;
-    return L < 2 || L > 0x7FFFFFFFll ? 0 : choose_instead(d, (uint32_t)L, o, choose_batched_path(d, (uint32_t)L, o, false, nullptr)).fused;
+    return L < 2 || L > 0x7FFFFFFFll ? 0 : choose_all(d, (uint32_t)L).fused;
 }
 
 int matmul_tile_columns(const DeviceView& d, int64_t L) {
-    const MatmulOptions o;
     if (L < 2 || L > 0x7FFFFFFFll) return 0;
-    const Instead i = choose_instead(d, (uint32_t)L, o, choose_batched_path(d, (uint32_t)L, o, false, nullptr));
-    return i.tile ? tile_columns(d, (uint32_t)L, i.temporaries) : 0;
+    return tile_columns(choose_all(d, (uint32_t)L).tile);
 }
 
 // Batches that are looked at: every one of up to 128 columns, then multiples of 16, where a workgroup's columns are all used, and one column less,
@@ -332,10 +339,9 @@ int matmul_tile_columns(const DeviceView& d, int64_t L) {
 // device.
 bool tile_index_pays(const DeviceView& v) {
     if (tile_index_bytes(v) == 0) return false;
-    const MatmulOptions o;
     DeviceView d = v;
     d.tile_index = &d;  // (the estimates do not read it)
-    auto taken = [&](uint32_t L) { return choose_instead(d, L, o, choose_batched_path(d, L, o, false, nullptr)).tile; };
+    auto taken = [&](uint32_t L) { return choose_all(d, L).tile.variant >= 0; };
     for (uint32_t L = 2; L < 128u; ++L)
         if (taken(L)) return true;
     for (uint32_t L = 128; L <= (1u << 20); L += L < 1024u ? 16u : (L / 32u) & ~15u)
@@ -381,10 +387,11 @@ int launch_matmul(const DeviceView& d, const float* X, float* Y, int64_t L64, vo
     MatmulOptions o = o_in;
     if (no_temporaries) o.flags |= kOptRowsWhole;  // the parts of split rows meet in a temporary
     XtilePlan plan;
-    const int batched_path = L > 1 ? choose_batched_path(d, L, o, no_temporaries, &plan, X, Y) : 0;
+    double gathers_us = -1;
+    const int batched_path = L > 1 ? choose_batched_path(d, L, o, no_temporaries, &gathers_us, &plan, X, Y) : 0;
     if (!no_temporaries && L > 1) {
-        const Instead instead = choose_instead(d, L, o, batched_path);
-        if (instead.tile) return (int)launch_tile(d, X, Y, L, instead.temporaries, batched_path == 3, stream);
+        const Instead instead = choose_instead(d, L, o, batched_path, &gathers_us);
+        if (instead.tile.variant >= 0) return (int)launch_tile(d, instead.tile, X, Y, L, batched_path == 3, stream);
         if (instead.narrow > 0) return (int)launch_narrow(d, X, Y, L, stream);
         if (instead.fused > 0) return (int)launch_fused(d, X, Y, L, instead.temporaries, batched_path == 3, stream);
     }

@@ -898,13 +898,6 @@ constexpr int kVariantCount = sizeof(kVariants) / sizeof(kVariants[0]);
 
 int form_of(const DeviceView& d) { return d.grid.scale != 0.f ? kUniform : (d.pieces == 1 ? 1 : 3); }
 
-struct TilePlan {
-    int variant = -1;
-    uint32_t row_blocks = 0, col_tiles = 0, splits = 1, per = 0;
-    size_t lds = 0;
-    double us = 1e30;
-};
-
 bool index_applicable(const DeviceView& d) {
     if (!d.rank_tab || d.pieces < 1 || d.colI_bits != 16 || d.n < 1 || d.n > 65000 || d.m < 1 || d.m > (1 << 24) || d.lds_per_block < 160 * 1024) return false;
     const TileIndexShape s = tile_index_shape(d);
@@ -915,34 +908,42 @@ bool tile_applicable(const DeviceView& d, uint32_t L) {
     return index_applicable(d) && L >= 2 && L <= (1u << 20) && ((uint64_t)d.n + 600) * L * 4u < (1ull << 32);
 }
 
-// The best plan; temporaries: partial sums of parts of W's columns are allowed.
-TilePlan plan_tile(const DeviceView& d, uint32_t L, bool temporaries) {
+}  // namespace
+
+// A call waits for this search (0.1 to 0.2 us): variants, and numbers of parts, that cannot be below the best so far are not
+// looked at.  For their rounds times the waves' segments are at least the workgroups' segments by the compute units, and parts cost their sum.
+TilePlan plan_tile(const DeviceView& d, uint32_t L, bool temporaries, double below) {
     TilePlan best;
+    best.us = below;
     if (!d.tile_index || !tile_applicable(d, L)) return best;
     const int form = form_of(d);
     const TileIndexShape shape = tile_index_shape(d);
-    const uint32_t segs = shape.segs;
-    const double quads = (double)d.nnz / ((double)segs * shape.groups) / 4.0;
+    const uint32_t segs = shape.segs, cus = (uint32_t)std::max(d.cus, 1);
+    const uint32_t most = temporaries ? std::min((segs + kTileWaves - 1u) / kTileWaves, 16u) : 1u;
+    const double quads = (double)d.nnz / ((double)segs * shape.groups) / 4.0, out_bytes = (double)d.m * L * 4.0;
     for (int v = 0; v < kVariantCount; ++v) {
         const Variant& k = kVariants[v];
+        if (k.form != form || (uint32_t)k.ct > L) continue;
         const double per_lane = quads * k.rt / kWave;
-        if (k.form != form || (uint32_t)k.ct > L || (k.rounds == 1) != (per_lane <= 0.85)) continue;
+        if ((k.rounds == 1) != (per_lane <= 0.85)) continue;
         TilePlan p;
         p.variant = v;
         const uint32_t R = 16u * k.rt;
         p.row_blocks = (uint32_t)((d.m + R - 1) / R);
         p.col_tiles = (L + 16u * k.ct - 1) / (16u * k.ct);
         const uint64_t tiles = (uint64_t)p.row_blocks * p.col_tiles;
-        for (uint32_t sp = 1; sp <= (temporaries ? std::min((segs + kTileWaves - 1u) / kTileWaves, 16u) : 1u); ++sp) {
+        const double each = k.seg + k.quad * std::max(per_lane, 0.5);
+        const double least = k.fixed + k.round + std::max(1.0, (double)tiles * segs / ((double)kTileWaves * cus)) * each;
+        for (uint32_t sp = 1; sp <= most; ++sp) {
+            if (least + (sp > 1 ? k.sum + 3.0 * out_bytes * 1e-6 * k.traffic : 0.0) >= best.us) break;
             p.per = (segs + sp - 1) / sp;
             p.splits = (segs + p.per - 1) / p.per;
-            const double part_bytes = (double)p.splits * (double)d.m * L * 4.0;
+            const double part_bytes = p.splits * out_bytes;
             if (p.splits > 1 && part_bytes > (double)(1ull << 30)) break;
             if (tiles * p.splits * p.row_blocks >= (1ull << 32)) break;  // (the kernel divides by multiplication)
-            const double rounds = std::ceil((double)(tiles * p.splits) / std::max(d.cus, 1));
-            const double waves = (double)((p.per + kTileWaves - 1u) / kTileWaves);
-            p.us = k.fixed + rounds * (k.round + waves * (k.seg + k.quad * std::max(per_lane, 0.5)));
-            if (p.splits > 1) p.us += k.sum + (part_bytes + (double)d.m * L * 4.0) * 1e-6 * k.traffic;
+            const double rounds = (double)((tiles * p.splits + cus - 1u) / cus), waves = (double)((p.per + kTileWaves - 1u) / kTileWaves);
+            p.us = k.fixed + rounds * (k.round + waves * each);
+            if (p.splits > 1) p.us += k.sum + (part_bytes + out_bytes) * 1e-6 * k.traffic;
             if (p.us < best.us) best = p;
         }
     }
@@ -952,8 +953,6 @@ TilePlan plan_tile(const DeviceView& d, uint32_t L, bool temporaries) {
     }
     return best;
 }
-
-}  // namespace
 
 TileIndexShape tile_index_shape(const DeviceView& d) {
     TileIndexShape s;
@@ -983,15 +982,9 @@ size_t tile_index_bytes(const DeviceView& d) { return index_applicable(d) ? tile
 
 int build_tile_index(const DeviceView& d, void* index, void* stream) { return (int)launch_tile_index(d, index, static_cast<hipStream_t>(stream)); }
 
-double tile_estimate_us(const DeviceView& d, uint32_t L, bool temporaries) { return plan_tile(d, L, temporaries).us; }
+int tile_columns(const TilePlan& p) { return p.variant >= 0 ? 16 * kVariants[p.variant].ct : 0; }
 
-int tile_columns(const DeviceView& d, uint32_t L, bool temporaries) {
-    const TilePlan p = plan_tile(d, L, temporaries);
-    return p.variant >= 0 ? 16 * kVariants[p.variant].ct : 0;
-}
-
-hipError_t launch_tile(const DeviceView& d, const float* X, float* Y, uint32_t L, bool temporaries, bool dense_zeros, hipStream_t stream) {
-    const TilePlan p = plan_tile(d, L, temporaries);
+hipError_t launch_tile(const DeviceView& d, const TilePlan& p, const float* X, float* Y, uint32_t L, bool dense_zeros, hipStream_t stream) {
     if (p.variant < 0) return hipErrorInvalidValue;
     const Variant& k = kVariants[p.variant];
     {
