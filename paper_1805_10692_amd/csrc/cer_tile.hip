@@ -12,14 +12,15 @@
 // at the end, parts of W's columns in a second launch.
 // One barrier per 512 columns with planes that all waves fill instead: 4096 x 9216, 15 % indexed, batch 99 41 us instead of 38.  128 rows
 // (half the loads and splits of X): one wave per SIMD 50 us, two with one step of X in registers 41.
-// Against the kernels it takes the place of: that product 56.8 us with the strips -> 34.9; 2593 x 18163, 66 % indexed, batch 41 103
-// (decoded matrix) -> 42; 1529 x 862, 38 values, batch 167 19.9 (gathers) -> 11.2; 1103 x 14914, 5 values, batch 42 33.6 (one launch) -> 24.7; 100
-// random products of prepared handles: 33 change their kernel, 1.26 times the speed in the geometric mean.
+// Against the kernels it takes the place of: that product 56.8 us with the strips -> 35.5; 2593 x 18163, 66 % indexed, batch 41 103
+// (decoded matrix) -> 42; 1529 x 862, 38 values, batch 167 19.9 (gathers) -> 11.2; 1103 x 14914, 5 values, batch 42 33.6 (one launch) -> 24.7; of
+// 11000 random products of prepared handles a fifth takes it (tile_limit_us in cer_matmul.hip), at 1.28 times the speed in the geometric mean.
 // What bounds it: 4096 x 9216, batch 99, 68000 clocks: start-up 7500 (bounds, entries and X one after the other from memory), sums 5300;
 // between them the matrix pipes are busy half the time -- while they are, a SIMD issues other vector instructions every nine clocks only and dot
-// products (the splitting) every 22.
-// Errors against fp64 are 0.45 of the replaced kernels' in the mean, at most 0.94 (2-norm; 33 products, X normal, cut at 0, |x| + 1): short
-// running sums per wave, the small products apart, the waves' and the parts' sums in binary64.
+// products (the splitting) every 22.  The variant of 64 rows and 64 columns takes all 256 registers and spills two; the functions for columns
+// formed again save theirs in scratch (468 bytes per lane).
+// Errors against fp64 are 0.41 of the replaced kernels' in the mean, at most 0.97 (2-norm; 333 products of 4000 to 64990 columns, X normal, cut at
+// 0, |x| + 1): short running sums per wave, the small products apart, the waves' and the parts' sums in binary64.
 #include "cer_exact.hpp"
 
 #include <type_traits>
