@@ -1133,7 +1133,8 @@ __device__ __forceinline__ void scatter_row(const ColT* __restrict__ colI, const
 
 typedef uint32_t Words4 __attribute__((ext_vector_type(4), aligned(4)));  // (the memory path takes them at any such address)
 
-// fp32 output.  kPast: outputs larger than what caches can hold go past them (decode_device).
+// fp32 output.  kPast: large outputs go past the caches (kPastCaches), where nothing puts the halves of a line together: the stores begin at
+// whole lines (4096 x 12300 49 -> 40 us, 4096 x 10250, 3 bits, 42 -> 33; rows of whole lines take the same either way).
 template <typename ColT, typename CodeT, uint32_t kThreads, bool kPast>
 __global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict__ colI, DecodeArgs a, float* __restrict__ out) {
     constexpr bool kRanks = sizeof(CodeT) == 1;
@@ -1142,7 +1143,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict
     __shared__ uint32_t s_ptr[T + 1];
     __shared__ CodeT s_grp[T];
     __shared__ uint32_t s_val[kRanks ? kCodes : 1];  // fp32 value by rank
-    CodeT* code = reinterpret_cast<CodeT*>(s_seg);
+    constexpr bool kLines = kRanks && kPast;
     const uint32_t tid = threadIdx.x;
     const int64_t r = blockIdx.x;
     const uint32_t g0 = a.rowPtr[r], g1 = a.rowPtr[r + 1];
@@ -1153,23 +1154,28 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict
     for (uint32_t si = blockIdx.y; si < a.nseg; si += gridDim.y) {  // uniform over the workgroup
         const int64_t c0 = (int64_t)si * a.seg;
         const uint32_t len = (uint32_t)min((int64_t)a.seg, a.n - c0);  // 1 .. seg
+        float* o = out + r * a.n + c0;
+        // columns in front of the first whole line, and as many bytes in front of their codes that the others begin at a word
+        const uint32_t front = kLines ? min(len, (uint32_t)(-(reinterpret_cast<uintptr_t>(o) >> 2)) & 31u) : 0u, pad = (0u - front) & 3u;
+        CodeT* code = reinterpret_cast<CodeT*>(s_seg) + pad;
         if constexpr (kRanks) {
-            for (uint32_t j = tid; j < (len + 15u) / 16u; j += T) reinterpret_cast<uint4*>(s_seg)[j] = make_uint4(0, 0, 0, 0);
+            for (uint32_t j = tid; j < (len + pad + 15u) / 16u; j += T) reinterpret_cast<uint4*>(s_seg)[j] = make_uint4(0, 0, 0, 0);
         } else {
             for (uint32_t j = tid; j < (len + 3u) / 4u; j += T) reinterpret_cast<float4*>(s_seg)[j] = make_float4(w0, w0, w0, w0);
         }
         scatter_row<ColT, CodeT, T, false>(colI, a, g0, g1, tid, c0, len, s_ptr, s_grp, code);
         __syncthreads();
-        float* o = out + r * a.n + c0;
         if constexpr (kRanks) {
-            const uint32_t n4 = len >> 2;
+            const uint32_t n4 = (len - front) >> 2;
+            const uint32_t* words = reinterpret_cast<const uint32_t*>(s_seg + front + pad);
+            if (kLines && tid < front) o[tid] = __uint_as_float(s_val[code[tid]]);
             for (uint32_t j = tid; j < n4; j += T) {
-                const uint32_t q = reinterpret_cast<const uint32_t*>(s_seg)[j];
+                const uint32_t q = words[j];
                 const Words4 v = {s_val[q & 0xFFu], s_val[(q >> 8) & 0xFFu], s_val[(q >> 16) & 0xFFu], s_val[q >> 24]};
-                if constexpr (kPast) __builtin_nontemporal_store(v, reinterpret_cast<Words4*>(o) + j);
+                if constexpr (kPast) __builtin_nontemporal_store(v, reinterpret_cast<Words4*>(o + front) + j);
                 else reinterpret_cast<Words4*>(o)[j] = v;
             }
-            for (uint32_t j = (n4 << 2) + tid; j < len; j += T) o[j] = __uint_as_float(s_val[code[j]]);
+            for (uint32_t j = front + (n4 << 2) + tid; j < len; j += T) o[j] = __uint_as_float(s_val[code[j]]);
         } else {
             const uint32_t n4 = (reinterpret_cast<uintptr_t>(o) & 15u) == 0 ? len >> 2 : 0u;
             for (uint32_t j = tid; j < n4; j += T) reinterpret_cast<float4*>(o)[j] = reinterpret_cast<const float4*>(s_seg)[j];
@@ -1564,8 +1570,11 @@ DecodeArgs decode_args(const DeviceView& v, int64_t nseg, uint32_t multiple) {
 }
 
 // From half of the 256 MB cache in front of the memory on, the decoder's stores go past the caches: what they would leave there is written
-// back while the next kernels read.  4096 x 9216 (151 MB): the decoder 42 -> 39 us, the next matrix's range_kernel 38 -> 27; decoder and a
-// reduction of the result 90 -> 88.  Smaller results are read from that cache again (67 MB, decoder and reduction: 42 us, 47 past it).
+// back while the next kernels read.  us without / with, 7 bits: 4096 x 9216 (151 MB), into several results in turn 52 / 41, compressed and decoded
+// 222 / 206, one layer after the other 206 / 190 (the next matrix's range_kernel 38 / 27), and reduced 256 / 257; 4096 x 25088 (411 MB) 567 / 531, 549 / 513,
+// 663 / 641.  Programs that only decode and read the result at once lose where it would have stayed: decoded in turn and reduced 4096 x 9216
+// 92 / 93, 4096 x 12288 (201 MB) 98 / 116, 4096 x 25088 254 / 241; into the same memory each time 4096 x 9216 70 / 86.  Smaller results are read from
+// that cache (67 MB, decoder and reduction: 42 us, 47 past it).
 constexpr int64_t kPastCaches = 128 << 20;
 
 template <typename ColT, typename CodeT>
@@ -1575,7 +1584,7 @@ hipError_t launch_decode(const DeviceView& v, float* out, hipStream_t s) {
     const int64_t most = 32768 / (int64_t)sizeof(CodeT);
     const DecodeArgs a = decode_args(v, std::max<int64_t>((v.n + most - 1) / most, std::min<int64_t>((2048 + v.m - 1) / v.m, v.n / 1024)), 8);
     const dim3 grid((unsigned)v.m, a.nseg);
-    const size_t lds = ((size_t)a.seg * sizeof(CodeT) + 15) & ~(size_t)15;
+    const size_t lds = ((size_t)a.seg * sizeof(CodeT) + 18) & ~(size_t)15;  // (up to three bytes in front of the codes)
     const ColT* colI = static_cast<const ColT*>(v.colI);
     const bool past = v.m * v.n * 4 >= kPastCaches;
     // short rows: one wave per row, four times as many workgroups in flight

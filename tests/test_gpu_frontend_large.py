@@ -29,6 +29,25 @@ def test_range_and_decode(shape, ends):
     assert torch.equal(out[:m * n].view(m, n), torch.round(W + 7) - 7) and torch.isnan(out[m * n:]).all()
 
 
+# rows that begin anywhere in a line, shorter than a line, of one wave each and of several segments (65536 columns), with the result as far from a
+# line's start; whole lines among them
+@pytest.mark.parametrize("m,n,shift", [(4100, 8191, 0), (4100, 8191, 3), (4097, 8224, 0), (4097, 8224, 31), (33200, 1011, 1), (1678000, 20, 5), (600, 65003, 2)])
+def test_results_past_the_caches(m, n, shift):
+    """Results of 134 MB and more: the stores of a row begin at a whole line, what lies in front of it is written singly."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + n)
+    cb = (np.arange(13) - 4).astype(np.float32)
+    W = torch.tensor(cb, device="cuda")[torch.randint(0, 13, (m, n), generator=g, device="cuda", dtype=torch.int32)]
+    W[torch.rand((m, n), generator=g, device="cuda") < 0.6] = 0.0
+    h = B.cer_encode_device(W, m, n, cb, "cser" if n & 1 else "cer")
+    out = torch.full((m * n + 64,), float("nan"), device="cuda")
+    B.cer_decode_device(h, out[shift:shift + m * n].view(m, n))
+    B.cer_free(h)
+    assert m * n >= 1 << 25 and torch.equal(out[shift:shift + m * n].view(m, n), W)
+    assert torch.isnan(out[:shift]).all() and torch.isnan(out[shift + m * n:]).all()
+    B.cer_trim()
+
+
 # rows of at most 12288 columns stay in registers; about 1300 workgroups take rows of 9217 and 12289 columns in turn
 @pytest.mark.parametrize("shape", [(3000, 1024), (2999, 1039), (1500, 4100), (2600, 9217), (700, 12288), (1400, 12289), (300, 20001)])
 @pytest.mark.parametrize("fmt", ["cer", "cser"])
