@@ -683,7 +683,7 @@ int upload(cer_matrix* h) {
         img = pageable.data();
     }
     auto put = [&](size_t off, const void* src, size_t bytes, size_t end) {  // an array and the zeros behind it
-        if (bytes) std::memcpy(img + off, src, bytes);
+        cer::copy_host(img + off, src, bytes);
         std::memset(img + off + bytes, 0, end - off - bytes);
     };
     put(l.off_colI, A.colI.bytes.data(), l.colI_bytes, l.off_optr);

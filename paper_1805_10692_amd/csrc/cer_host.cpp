@@ -10,6 +10,7 @@
 // Conversion cost is O(m.n), as the paper notes in Section V.
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <numeric>
@@ -104,15 +105,20 @@ private:
     std::vector<Slot> slots_;
 };
 
-// Threads for `work` elements: one for every 64 Ki of them, at most 16 and never more than there are rows.
+// Threads for `work` elements: one for every 16 Ki of them, at most 16 and never more than there are rows.  (A thread takes 1 to 2 ns per element;
+// waiting for the others costs some us each of five times.  Encode and decode in turn with one for every 64 / 32 / 16 Ki, fifteen layers of 0.2 to 4 M
+// elements: 0.82 / 0.70 / 0.64 of the time before the threads were kept awake and their counters apart; each call 4 ms after the last one:
+// 0.91 / 0.79 / 0.80.)
 int worker_count(int64_t rows, int64_t work) {
     unsigned hw = std::thread::hardware_concurrency();
-    const int64_t t = std::min<int64_t>(std::min<unsigned>(hw ? hw : 1, 16), (work + 65535) / 65536);
+    const int64_t t = std::min<int64_t>(std::min<unsigned>(hw ? hw : 1, 16), (work + 16383) / 16384);
     return (int)std::max<int64_t>(1, std::min<int64_t>(t, rows));
 }
 
-// Threads that wait between calls: starting 15 of them takes 160 us, waking them 20 (a 2048 x 2048 layer is encoded in
-// 500).  At most 15; they sleep on a futex after having looked for work for about 50 us; a fork leaves the child without them
+// Threads that wait between calls: starting 15 of them takes 160 us, waking them 20, and until the last one runs 60 to 100 (a 2048 x 2048
+// layer is encoded in 250).  At most 15; they sleep on a futex after having looked for work for kAwake: a handle that has been encoded is on its
+// way to the device for some 60 us, and what converts a layer often converts it back or goes on with the next (encode and decode in turn,
+// looking for 25 / 250 us, with the counters apart: 1172 x 1576, 50 values, 330 -> 263 us, 779 x 1437, 26 values, 186 -> 140).  A fork leaves the child without them
 // (it starts its own).  One call at a time uses them, a call that finds them busy starts threads for itself.
 class Workers {
 public:
@@ -159,6 +165,7 @@ public:
 
 private:
     static constexpr int kMost = 15;
+    static constexpr std::chrono::microseconds kAwake{250};
     static std::atomic<Workers*>& slot() {
         static std::atomic<Workers*> s{nullptr};
         return s;
@@ -179,9 +186,15 @@ private:
     void loop(int t, uint32_t seen) {
         for (;;) {
             uint32_t now = turn_.load(std::memory_order_acquire);
+            std::chrono::steady_clock::time_point until{};
             for (int spins = 0; now == seen; now = turn_.load(std::memory_order_acquire)) {
                 if (++spins < 1500) {
                     _mm_pause();
+                    continue;
+                }
+                if (spins == 1500) until = std::chrono::steady_clock::now() + kAwake;
+                if (std::chrono::steady_clock::now() < until) {
+                    std::this_thread::yield();  // (others that want the processor get it)
                     continue;
                 }
                 asleep_.fetch_add(1, std::memory_order_seq_cst);
@@ -359,9 +372,13 @@ int encode_rows(const float* W, int64_t m, int64_t n, const float* codebook, int
     // the rows' histograms are kept unless they would be larger than the matrix (few columns, many values)
     const bool keep = (int64_t)Kc <= n;
     std::unique_ptr<uint32_t[]> rows_c(new uint32_t[keep ? (size_t)m * (size_t)Kc : 1]);
-    const size_t Kz = (size_t)std::max(Kc, 1);
-    std::vector<uint32_t> scratch((size_t)T * Kz * 6);  // per thread: four histograms, counts, bucket positions
-    std::vector<int64_t> total((size_t)T * Kz, 0);
+    // What a thread counts in has cache lines of its own: with those of a few values next to each other the threads waited for one another at
+    // every element (659 x 1121, two values: 356 -> 173 us there and back).
+    constexpr size_t kLine = 128;
+    auto lines = [](size_t bytes) { return (bytes + kLine - 1) / kLine * kLine + kLine; };
+    const size_t Kz = (size_t)std::max(Kc, 1), scratch_of = lines(Kz * 6 * 4) / 4, total_of = lines(Kz * 8) / 8;
+    std::vector<uint32_t> scratch((size_t)T * scratch_of);  // per thread: four histograms, counts, bucket positions
+    std::vector<int64_t> total((size_t)T * total_of, 0);
     std::vector<uint64_t> row_nnz((size_t)m + 1, 0), row_groups((size_t)m + 1, 0);
     std::vector<int64_t> nonempty_part((size_t)T, 0);
     std::vector<uint32_t> order;  // rank -> symbol
@@ -371,10 +388,10 @@ int encode_rows(const float* W, int64_t m, int64_t n, const float* codebook, int
     std::atomic<int> rc{CER_OK};
 
     Team::run(T, m, [&](int t, int64_t r0, int64_t r1, Team& team) {
-        uint32_t* h4 = scratch.data() + (size_t)t * Kz * 6;
+        uint32_t* h4 = scratch.data() + (size_t)t * scratch_of;
         uint32_t* own = h4 + 4 * Kz;
         uint32_t* fill = own + Kz;
-        int64_t* sum = total.data() + (size_t)t * Kz;
+        int64_t* sum = total.data() + (size_t)t * total_of;
         bool ok = true;
         int32_t likely = 0;  // the most frequent symbol of the rows so far
         for (int64_t r = r0; r < r1 && ok; ++r) {
@@ -390,7 +407,7 @@ int encode_rows(const float* W, int64_t m, int64_t n, const float* codebook, int
         if (t == 0) {
             // Omega: occurring symbols by count, highest first; stable, so equal counts keep codebook order
             for (int i = 1; i < T; ++i)
-                for (int32_t k = 0; k < Kc; ++k) total[(size_t)k] += total[(size_t)i * Kz + (size_t)k];
+                for (int32_t k = 0; k < Kc; ++k) total[(size_t)k] += total[(size_t)i * total_of + (size_t)k];
             for (int32_t k = 0; k < Kc; ++k)
                 if (total[(size_t)k] > 0) order.push_back((uint32_t)k);
             std::sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
@@ -400,6 +417,7 @@ int encode_rows(const float* W, int64_t m, int64_t n, const float* codebook, int
         }
         team.sync();
         const int32_t K = (int32_t)order.size();
+        int64_t nonempty = 0;
 
         for (int64_t r = r0; r < r1; ++r) {
             const uint32_t* c = keep ? rows_c.get() + (size_t)r * Kz : own;
@@ -409,8 +427,9 @@ int encode_rows(const float* W, int64_t m, int64_t n, const float* codebook, int
                 if (c[order[(size_t)k]]) { ++present; top = (uint64_t)k; }
             row_nnz[(size_t)r] = (uint64_t)n - (K > 0 ? c[order[0]] : 0u);
             row_groups[(size_t)r] = cser ? present : top;
-            nonempty_part[(size_t)t] += (int64_t)present;
+            nonempty += (int64_t)present;
         }
+        nonempty_part[(size_t)t] = nonempty;
         team.sync();
 
         if (t == 0) {
@@ -502,6 +521,19 @@ void decode_rows(const HostMatrix& A, float* W, int64_t r0, int64_t r1) {
 }  // namespace
 
 void stop_host_threads() { Workers::stop(); }
+
+// From 256 KiB on the threads of a conversion share the copy (fifteen layers there and back 0.811 of the time, 0.828 with one thread copying).
+void copy_host(void* to, const void* from, size_t bytes) {
+    const int threads = worker_count(INT64_MAX, (int64_t)(bytes / 4));
+    if (bytes < (size_t)256 << 10 || threads < 2) {
+        if (bytes) std::memcpy(to, from, bytes);
+        return;
+    }
+    Team::run(threads, (int64_t)(bytes / 64), [&](int, int64_t b0, int64_t b1, Team&) {
+        const size_t end = b1 == (int64_t)(bytes / 64) ? bytes : (size_t)b1 * 64;
+        std::memcpy(static_cast<char*>(to) + b0 * 64, static_cast<const char*>(from) + b0 * 64, end - (size_t)b0 * 64);
+    });
+}
 
 int min_index_bits(uint64_t max_value) {
     return max_value <= 0xFFu ? 8 : (max_value <= 0xFFFFu ? 16 : 32);

@@ -5,15 +5,31 @@
 #include <cstdint>
 #include <memory>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 struct cer_matrix;
 
 namespace cer {
 
+// Elements that a vector makes without a value stay as the memory is: arrays of which every element is written anyway, by many threads,
+// are not filled by one first (840 KB of indices, 2048 x 2048 with 10 % indexed: 36 -> 21 us of the encoder's 330 for its scan and them).
+template <typename T>
+struct Unfilled : std::allocator<T> {
+    template <typename U>
+    struct rebind {
+        using other = Unfilled<U>;
+    };
+    template <typename U, typename... Args>
+    void construct(U* p, Args&&... args) {
+        if constexpr (sizeof...(Args) > 0) ::new (static_cast<void*>(p)) U(std::forward<Args>(args)...);
+        else ::new (static_cast<void*>(p)) U;
+    }
+};
+
 // One index array of the format, kept on the host at its minimal width (Section V).
 struct HostArray {
-    std::vector<uint8_t> bytes;
+    std::vector<uint8_t, Unfilled<uint8_t>> bytes;
     int64_t len = 0;
     int32_t bits = 8;
     uint64_t at(int64_t i) const {
@@ -120,6 +136,7 @@ int encode_host(const float* W, int64_t m, int64_t n, const float* codebook, int
                 std::shared_ptr<HostMatrix>* out);
 int decode_host(const HostMatrix& A, float* W_out);
 int min_index_bits(uint64_t max_value);
+void copy_host(void* to, const void* from, size_t bytes);  // memcpy by the threads of both
 void stop_host_threads();  // the threads that both keep asleep between calls
 
 // Per-call choices of cer_matmul_ex (include/cer.h: cer_matmul_opts_t); the defaults are what cer_matmul does.

@@ -60,3 +60,40 @@ def test_threads_come_back_after_they_were_ended():
     except B.CerError:
         pass
     assert _round_trip(3)
+
+
+@pytest.mark.parametrize("values", [1, 2, 3, 17, 200])
+@pytest.mark.parametrize("m,n", [(1, 16384), (2, 8193), (16, 1025), (33, 16385), (301, 1091)])
+def test_shares_of_the_threads(m, n, values):
+    """Around the sizes from which another thread helps; counters of few and of many values."""
+    rng = np.random.default_rng(m * 1000 + values)
+    cb = ((np.arange(values) - values // 2) * 0.5).astype(np.float32)
+    W = cb[np.minimum(rng.geometric(0.4, size=(m, n)) - 1, values - 1)]
+    for encode, decode in ((B.cer_encode, B.cer_decode), (B.cser_encode, B.cser_decode)):
+        h = encode(W, cb)
+        assert np.array_equal(decode(h), W)
+        count = B.cer_get_array(h, B.CER_ARRAY_COUNT)
+        assert np.array_equal(count, np.sort(np.unique(W, return_counts=True)[1])[::-1])
+        B.cer_free(h)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("indexed", [131071, 131072, 131073, 131103, 400001])
+def test_arrays_on_their_way_to_the_device(indexed):
+    """Index arrays around the size from which threads share the copy, in whole and in odd shares."""
+    import torch
+    m, n = 512, 1024
+    cb = np.array([0.0, 1.0, -2.0], np.float32)
+    W = np.zeros(m * n, np.float32)
+    at = np.random.default_rng(indexed).permutation(m * n)[:indexed]
+    W[at] = np.where(at % 3 == 0, np.float32(1.0), np.float32(-2.0))
+    W = W.reshape(m, n)
+    if indexed > m * n // 2:
+        W = np.where(W == 0, np.float32(5.0), W)
+        cb = np.array([5.0, 1.0, -2.0], np.float32)
+    h = B.cer_encode(W, cb)
+    out = torch.empty((m, n), dtype=torch.float32, device="cuda")
+    B.cer_decode_device(h, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), W)
+    B.cer_free(h)
