@@ -895,17 +895,28 @@ hipError_t launch_gemv(const DeviceView& d, const KView& k, const float* X, floa
         // its first gather (the 7-bit layer of 7000 indices per row: 14.3 -> 14.1 us, alternating runs; rows of 1400: no change)
         if (x_bytes <= 48 * 1024 && (uint64_t)d.nnz >= 8ull * GemvShape<IdxT>::WIN * (uint64_t)k.m) waves = std::min(waves, 8);
     }
-    // Few rows (at most 2 per compute unit) of at least 3 windows each: a row is shared by 4 or 8 waves, and a
-    // workgroup holds as many rows as spread the matrix over all compute units.  Measured against whole rows: 512 x
-    // 4608 with 1840 indices per row 4.84 against 5.29 us, 256 x 25088 (1250) 5.2 against 6.8 us, 64 x 4096 (2050)
-    // 4.85 against 5.25 us; with 4 or 8 rows per compute unit (1024 x 9216, 2048 x 9216) or rows of 2 windows (512 x
-    // 2048) sharing lost 0.2 - 0.6 us (every wave builds the row's group list; 16 waves per compute unit contend).
+    // One workgroup per compute unit with `per_unit` rows in each, shared by 2, 4 or 8 waves where the rows are long: a wave alone walks its row at
+    // the pace of its own latencies (a window of 512 positions 0.3 us), while the list of groups that every wave of a row builds for itself
+    // and the contention of 16 waves cost as much as some windows.  Measured against whole rows, geometric means of 1350 random matrices (256 to
+    // 4096 rows of 512 to 25088 columns) by windows per row -- the average, or 0.6 of the longest row's, which is what a launch of unequal rows
+    // waits for:
+    //   1 or 2 rows per compute unit, 3 windows and more: 4 or 8 waves per row 0.95 (4 windows) to 0.5
+    //   3 or 4, from 3 windows on two waves 0.96, 0.93 (6 windows), 0.85 (8), 0.78 (16); four waves ahead of two from 5 windows on with 3 rows
+    //     (12: 0.81 either way, 24: 0.65 and 0.74), from 14 on with 4 (24: 0.75 and 0.77); below 3 windows sharing loses 1 to 4 %
+    //   5 to 8, two waves: 0.99 (6 windows), 0.93 (8), 0.91 (12), 0.86 (24); below 4 windows 1.05 to 1.14
+    //   9 to 15, whole rows: as many waves as rows, and no workgroup of 4 or 8 waves more than the compute units: 0.90 (10 to 16 windows), 0.96
+    //     on average; an X of a few kilobytes and rows of up to 3 windows: 1.02
+    // 848 x 21879, 145 values, 13200 indices per row 13.7 -> 9.1 us; 608 x 7177, 30 values, 5400 6.8 -> 5.3; 2363 x 10312, 158 values, 8900
+    // 15.6 -> 12.2; 650 x 17950, rows of 970 on average, the longest of 17000, 12.6 -> 6.1.
     uint32_t part_shift = 0, rows_shared = 0;
-    if (x_in_lds && (o.flags & kOptRowsWhole) == 0 && k.m > 0 && (uint64_t)k.m <= 2ull * (uint64_t)d.cus &&
-        (uint32_t)d.max_row_groups <= gcap) {
-        const uint32_t per_unit = pow2_ceil((k.m + (uint32_t)d.cus - 1) / (uint32_t)d.cus);  // 1 or 2
-        const uint64_t windows = ((uint64_t)d.nnz / k.m + GemvShape<IdxT>::WIN - 1) / GemvShape<IdxT>::WIN;  // average row
-        uint32_t p = windows >= 3 ? std::min<uint32_t>(8u / per_unit, pow2_ceil((uint32_t)std::min<uint64_t>(windows, 8))) : 1u;
+    const uint32_t per_cu_rows = k.m > 0 ? (k.m + (uint32_t)d.cus - 1) / (uint32_t)d.cus : 0u;
+    const bool may_share = x_in_lds && (o.flags & kOptRowsWhole) == 0 && k.m > 0 && (uint32_t)d.max_row_groups <= gcap;
+    const double mean_row = k.m > 0 ? (double)d.nnz / k.m : 0.0;
+    const double row_windows = (use_tab ? std::max(mean_row, 0.6 * d.longest_row) : mean_row) / GemvShape<IdxT>::WIN;
+    if (may_share && per_cu_rows <= 2) {
+        const uint32_t per_unit = per_cu_rows;
+        const double windows = std::ceil(row_windows);
+        uint32_t p = windows >= 3 ? std::min<uint32_t>(8u / per_unit, pow2_ceil((uint32_t)std::min(windows, 8.0))) : 1u;
         while (p > 1 && fixed + list_bytes((int)(per_unit * p)) > budget) p >>= 1;
         if (p > 1) {
             rows_shared = per_unit;
@@ -914,10 +925,24 @@ hipError_t launch_gemv(const DeviceView& d, const KView& k, const float* X, floa
             waves = (int)std::max<uint32_t>(per_unit * p, std::min<uint32_t>(16u, pow2_ceil((uint32_t)(x_bytes / 8192))));
             while (waves > (int)(per_unit * p) && fixed + list_bytes(waves) > budget) waves >>= 1;
         }
+    } else if (may_share && use_tab && per_cu_rows < 16) {
+        uint32_t shift = 0;
+        if (per_cu_rows <= 4) shift = row_windows > (per_cu_rows == 3 ? 5.0 : 14.0) ? 2u : (row_windows > 3.0 ? 1u : 0u);
+        else if (per_cu_rows <= 8) shift = row_windows > 6.0 ? 1u : 0u;
+        // (waves without a row help to stage a large X: eight loads per thread cover it)
+        auto waves_of = [&](uint32_t sh) { return std::max(per_cu_rows << sh, std::min<uint32_t>(16u, (uint32_t)((x_bytes + 8191) / 8192))); };
+        while (shift > 0 && fixed + list_bytes((int)waves_of(shift)) > budget) --shift;
+        const bool whole = per_cu_rows > 8 && (x_bytes > 24 * 1024 || row_windows > 3.0) && fixed + list_bytes((int)waves_of(0)) <= budget;
+        if (shift > 0 || whole) {
+            part_shift = shift;
+            rows_shared = per_cu_rows;
+            waves = (int)waves_of(shift);
+        }
     }
     // eight 16-byte loads per thread should cover X (what is left is copied by a plain loop)
-    if (x_in_lds) waves = std::max(waves, (int)std::min<uint32_t>(16u, pow2_ceil((uint32_t)((x_bytes / 16 + 511) / 512))));
-    while (fixed + list_bytes(waves) > budget && waves > 4) waves >>= 1;
+    if (x_in_lds && (rows_shared == 0 || per_cu_rows <= 2))
+        waves = std::max(waves, (int)std::min<uint32_t>(16u, pow2_ceil((uint32_t)((x_bytes / 16 + 511) / 512))));
+    while (fixed + list_bytes(waves) > budget && waves > 4 && (rows_shared == 0 || per_cu_rows <= 2)) waves >>= 1;
     while (!use_tab && fixed + list_bytes(waves) > budget && gcap > 64) gcap = std::max<uint32_t>(64u, gcap / 2);
     const size_t lds = fixed + list_bytes(waves);
     if (lds > budget) return hipErrorInvalidValue;

@@ -73,3 +73,38 @@ def test_shared_rows_all_elements(name):
 def test_conv3x3_batch1_full_size(dom):
     full_check(wl.conv3x3(L=1, nonzero_dominant=dom))
     full_check(wl.conv3x3(L=1, nonzero_dominant=dom), opts=NO_TABLE)
+
+
+@pytest.mark.parametrize("m,n,p_dom,K,dominant", [
+    (513, 3300, 0.5, 16, None),      # three rows per compute unit, just above three windows: two waves per row
+    (768, 9001, 0.4, 100, None),     # ten windows: four waves; two tiles of ranks
+    (769, 3001, 0.45, 8, 5),         # four rows, Omega[0] != 0
+    (1024, 16001, 0.5, 4, None),     # fifteen windows: four waves of four rows
+    (1025, 9000, 0.5, 16, 3),        # five rows: ten waves
+    (2048, 7001, 0.5, 5, None),      # eight rows: sixteen waves
+    (2049, 7001, 0.5, 16, 9),        # nine whole rows: nine waves
+    (3840, 1900, 0.1, 200, None),    # fifteen whole rows of a small X
+    (600, 37000, 0.85, 40, None),    # X and the lists of few waves fill LDS
+])
+def test_waves_per_compute_unit(m, n, p_dom, K, dominant):
+    """A workgroup per compute unit of 3 to 15 rows, shared by waves or whole, on both sides of the rule's lines."""
+    kw = {} if dominant is None else {"dominant": dominant}
+    w = wl.random_lowentropy(m=m, n=n, K=K, p_dom=p_dom, L=1, seed=m + n, **kw)
+    full_check(w, want_path=0)
+
+
+def test_few_long_rows_among_short_ones():
+    """Rows of unequal length: the longest row alone asks for shares, those of the short rows are empty."""
+    rng = np.random.default_rng(5)
+    cb = np.array([0.0, 0.5, -1.0, 2.0], np.float32)
+    W = cb[rng.choice(4, size=(700, 9000), p=[0.97, 0.01, 0.01, 0.01])].astype(np.float32)
+    W[17] = cb[rng.integers(1, 4, size=9000)]
+    W[699] = cb[rng.integers(1, 4, size=9000)]
+    W[300] = 0.0
+
+    class Case:
+        pass
+    w = Case()
+    w.name, w.W, w.codebook, w.m, w.n, w.L = "few long rows", W, cb, 700, 9000, 1
+    w.X = rng.standard_normal((9000, 1)).astype(np.float32)
+    full_check(w, want_path=0)
