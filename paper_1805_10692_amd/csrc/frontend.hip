@@ -1194,7 +1194,12 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict
 // before it: a bitmap of the beginnings, counted up per word, as in the batch-1 kernel -- no search, no branch (a binary search
 // and a walk over the boundaries waited for LDS at every step: 633 x 5106, 112 values, 22 us, now 11; 986 x 16765, three
 // values, 42 against 28).  Bound by the phases of a workgroup -- records, list, bitmap, positions, output -- that follow one another
-// (512 x 4608, 128 workgroups, 7.2 us: vector ALU busy 15 % of the launch, LDS 9 %, a wave waits for data or at a barrier 64 %).
+// (512 x 4608, 128 workgroups, 6.7 us: vector ALU busy 15 % of the launch, LDS 9 %, a wave waits for data or at a barrier 64 %).  So the first
+// positions are requested as soon as the records tell where they are, the pieces of the values are made and the bitmap is filled
+// beside the list meanwhile, and the counts are summed by lane moves: 0.4 to 0.8 us of 5.6 to 11.3, 0.985 of the call in the geometric mean of
+// 50 products (2067 x 521, batch 1638, 38.7 -> 37.3 us).  Eight rows in more segments instead of four rows: 1.03 times the call; four rows in more
+// segments 1.01; two rows 1.005.  Stores past the L2 (what a launch leaves there is written back behind it): 0.97 with eight rows and up to
+// 16 MB, but 1.02 - 1.06 with four rows or larger matrices.
 constexpr uint32_t kStretch = 32768;  // positions per bitmap
 template <typename ColT, typename CodeT, int kPieces>
 __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restrict__ colI, DecodeArgs a, int64_t m, int64_t pitch,
@@ -1204,7 +1209,7 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
     __shared__ uint32_t s_ptr[kRanks ? 8 * kCodes : 8 * (kWave + 1)];
     __shared__ uint32_t s_list[kRanks ? 8 * kCodes + 1 : 1];
     __shared__ uint32_t s_bits[kRanks ? kStretch / 32 : 1], s_pre[kRanks ? kStretch / 32 : 1];
-    __shared__ uint32_t s_cnt[8];
+    __shared__ uint32_t s_cnt[8], s_sum[8];
     __shared__ CodeT s_grp[8][kRanks ? 1 : kWave];
     __shared__ uint32_t s_val[kRanks ? kCodes : 1];  // pieces 0 | 1 << 16, by rank
     __shared__ uint32_t s_val2[kRanks && kPieces == 3 ? kCodes : 1];
@@ -1216,30 +1221,46 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
     CodeT* code = reinterpret_cast<CodeT*>(s_seg);
     if constexpr (kRanks) {
         const uint32_t rows = (uint32_t)min((int64_t)a.rows, m - row0), words = rows << a.tab_shift;
+        const float own = a.omega[min(tid, a.K - 1u)];  // (512 threads, at most 256 values)
         for (uint32_t i = tid; i < words; i += 512u) s_ptr[i] = a.tab[((size_t)row0 << a.tab_shift) + i];
-        for (uint32_t k = tid; k < a.K; k += 512u) {
-            if (kPieces == 2 && a.grid.scale != 0.f) {
-                s_val[k] = cer::uniform_pieces(a.omega[k], a.grid);
-                continue;
-            }
-            uint32_t p[3];
-            cer::split3_finite(a.omega[k], p);
-            s_val[k] = p[0] | (p[1] << 16);
-            if constexpr (kPieces == 3) s_val2[k] = p[2];
-        }
         for (uint32_t j = tid; j < a.rows * stride >> 3; j += 512u) reinterpret_cast<uint2*>(s_seg)[j] = make_uint2(0, 0);
+        s_bits[2u * tid] = s_bits[2u * tid + 1u] = 0u;
         __syncthreads();
-        // list of the non-empty groups, in order of their positions: the row's place in s_seg | rank << 16; entry 0 is unused
+        // the first positions are on their way while what tells their groups is made
+        const uint32_t pb = s_ptr[0], pe = s_ptr[words - 1u];
+        uint32_t ahead[2][8];
+        auto request = [&](uint32_t v, uint32_t stop, uint32_t (&to)[8]) {
+            if (v < stop) load_eight(colI + v, to);  // up to seven positions on either side of the rows belong to others
+        };
+        const uint32_t first = pb & ~7u;
+        request(first + tid * 8u, min(pe, first + kStretch), ahead[0]);
+        request(first + tid * 8u + 4096u, min(pe, first + kStretch), ahead[1]);
+        if (tid < a.K) {
+            if (kPieces == 2 && a.grid.scale != 0.f) {
+                s_val[tid] = cer::uniform_pieces(own, a.grid);
+            } else {
+                uint32_t p[3];
+                cer::split3_finite(own, p);
+                s_val[tid] = p[0] | (p[1] << 16);
+                if constexpr (kPieces == 3) s_val2[tid] = p[2];
+            }
+        }
+        // list of the non-empty groups, in order of their positions: the row's place in s_seg | rank << 16; entry 0 is unused; and a bitmap of
+        // the positions that begin a group, of the first stretch of positions
         auto begins = [&](uint32_t i, uint32_t& at) {  // boundary i closes a group that begins at position `at`
             if (i == 0 || i >= words) return false;
             at = s_ptr[i - 1u];
             return s_ptr[i] > at;
+        };
+        auto mark = [&](uint32_t at, uint32_t base) {
+            if (at - base < kStretch) atomicOr(&s_bits[(at - base) >> 5], 1u << ((at - base) & 31u));
         };
         uint32_t groups = 1;
         for (uint32_t c = 0; c < words; c += 512u) {
             uint32_t at;
             const uint32_t i = c + tid;
             const bool some = begins(i, at);
+            if (some) mark(at, first);
             const uint64_t votes = __ballot(some);
             if (lane == 0) s_cnt[wave] = (uint32_t)__popcll(votes);
             __syncthreads();
@@ -1249,32 +1270,30 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
                 groups += s_cnt[w];
             }
             if (some) s_list[pos] = (i >> a.tab_shift) * stride | ((i & ((1u << a.tab_shift) - 1u)) << 16);
-            __syncthreads();
+            if (c + 512u < words) __syncthreads();  // (uniform)
         }
-        const uint32_t pb = s_ptr[0], pe = s_ptr[words - 1u];
         uint32_t seen = 0;  // groups that begin before the current stretch of positions
-        for (uint32_t base = pb & ~7u; base < pe; base += kStretch) {  // uniform over the workgroup
-            // bitmap of the positions that begin a group, and the number of such positions in front of every word
-            for (uint32_t i = tid; i < kStretch / 32u; i += 512u) s_bits[i] = 0u;
-            __syncthreads();
-            for (uint32_t i = tid; i < words; i += 512u) {
-                uint32_t at;
-                if (begins(i, at) && at - base < kStretch) atomicOr(&s_bits[(at - base) >> 5], 1u << ((at - base) & 31u));
+        for (uint32_t base = first; base < pe; base += kStretch) {  // uniform over the workgroup
+            if (base != first) {
+                request(base + tid * 8u, min(pe, base + kStretch), ahead[0]);
+                request(base + tid * 8u + 4096u, min(pe, base + kStretch), ahead[1]);
+                s_bits[2u * tid] = s_bits[2u * tid + 1u] = 0u;
+                __syncthreads();
+                for (uint32_t i = tid; i < words; i += 512u) {
+                    uint32_t at;
+                    if (begins(i, at)) mark(at, base);
+                }
+                __syncthreads();
             }
-            __syncthreads();
+            // the number of beginnings in front of every word
             const uint32_t n0 = (uint32_t)__builtin_popcount(s_bits[2u * tid]), n1 = (uint32_t)__builtin_popcount(s_bits[2u * tid + 1u]);
-            uint32_t incl = n0 + n1;
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-                const uint32_t u = __shfl_up(incl, off, kWave);
-                if ((int)lane >= off) incl += u;
-            }
-            if (lane == 63u) s_cnt[wave] = incl;
+            const uint32_t incl = cer::wave_inclusive_scan(n0 + n1);
+            if (lane == 63u) s_sum[wave] = incl;
             __syncthreads();
             uint32_t before = seen + incl - n0 - n1;
             for (uint32_t w = 0; w < 8; ++w) {
-                if (w < wave) before += s_cnt[w];
-                seen += s_cnt[w];
+                if (w < wave) before += s_sum[w];
+                seen += s_sum[w];
             }
             s_pre[2u * tid] = before;
             s_pre[2u * tid + 1u] = before + n0;
@@ -1295,19 +1314,15 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
                 }
             };
             const uint32_t stop = min(pe, base + kStretch);
-            uint32_t v = base + tid * 8u;
-            uint32_t ahead[2][8];
-            if (v < stop) load_eight(colI + v, ahead[0]);  // up to seven positions on either side of the rows belong to others
-            if (v + 4096u < stop) load_eight(colI + v + 4096u, ahead[1]);
-            for (; v < stop; v += 8192u) {
+            for (uint32_t v = base + tid * 8u; v < stop; v += 8192u) {
                 uint32_t col[2][8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     col[0][i] = ahead[0][i];
                     col[1][i] = ahead[1][i];
                 }
-                if (v + 8192u < stop) load_eight(colI + v + 8192u, ahead[0]);
-                if (v + 12288u < stop) load_eight(colI + v + 12288u, ahead[1]);
+                request(v + 8192u, stop, ahead[0]);
+                request(v + 12288u, stop, ahead[1]);
                 take(v, col[0]);
                 if (v + 4096u < stop) take(v + 4096u, col[1]);
             }

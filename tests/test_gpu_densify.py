@@ -4,6 +4,7 @@ for every kind of matrix and checked element by element against the oracle under
 product, |Y - Y_oracle| <= 1e-5 * sum_c |W[r,c]| |X[c,l]|; then the automatic choice is checked on the
 full-size workloads: it must take the route where the matrix is not sparse enough for the gathers to win
 and leave it alone elsewhere."""
+import numpy as np
 import pytest
 
 from paper_1805_10692_amd import binding as B
@@ -81,3 +82,32 @@ def test_trim_releases_cached_temporaries_and_products_go_on():
     full_check(w, opts=DENSE)
     B.cer_trim()
     B.cer_trim()                                # trimming an empty pool is fine
+
+
+@pytest.mark.parametrize("m,n,values,share", [
+    (5, 20000, 3, 0.1),      # several stretches of positions, the last workgroup with one row
+    (6, 8193, 2, 0.0005),    # a row's positions end just behind a stretch
+    (9, 30011, 256, 0.3),    # lists in two rounds, rows of an odd length
+    (1030, 5200, 250, 0.01),  # eight rows per workgroup, lists in four rounds, two stretches
+    (1025, 700, 40, 0.9),
+])
+def test_decoded_pieces_in_stretches(m, n, values, share):
+    """Matrices whose rows take several bitmaps, or lists of several rounds, against the same product in binary64."""
+    import torch
+    rng = np.random.default_rng(n + values)
+    cb = ((np.arange(values) - values // 2) / 128).astype(np.float32)
+    W = rng.choice(cb, size=(m, n)).astype(np.float32)
+    W[rng.random((m, n)) < share] = cb[values // 2]
+    if values == 2:
+        W[:] = cb[0]
+        W[rng.random((m, n)) < share] = cb[1]
+        cb = np.append(cb, np.float32(0.75))
+        W[0, :n // 2 + 7] = np.float32(0.75)
+    h = B.cer_encode(W, cb)
+    X = rng.standard_normal((n, 40)).astype(np.float32)
+    Xd, Yd = torch.from_numpy(X).cuda(), torch.empty((m, 40), dtype=torch.float32, device="cuda")
+    B.cer_matmul_ex(h, Xd, Yd, 40, opts=B.MatmulOpts(path=B.CER_PATH_DENSE))
+    torch.cuda.synchronize()
+    want, scale = W.astype(np.float64) @ X.astype(np.float64), np.abs(W.astype(np.float64)) @ np.abs(X.astype(np.float64))
+    assert (np.abs(Yd.cpu().numpy() - want) <= 1e-5 * scale + 1e-30).all()
+    B.cer_free(h)
