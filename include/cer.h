@@ -177,7 +177,8 @@ int cer_trim(void);
  *      for a batch of more than one tile a stream-ordered temporary of about the size of X is
  *      used (a tile-major copy of X).
  *   3  CER_PATH_DENSE: decode + dense: the matrix is decoded into a stream-ordered temporary and multiplied
- *      on the matrix cores: as one to three bf16 matrices that add up to it exactly (2.m.n bytes each), with
+ *      on the matrix cores: as one to three bf16 matrices that add up to it exactly (2.m.n bytes each; in place of
+ *      two or three of them also m.n bytes of positions in the codebook, from which the product makes the same numbers), with
  *      X split into three in the same way, or as fp32 (4.m.n bytes) where a value or an index range rules
  *      that out (cer_matmul_planes tells).  Values that would take three but are whole multiples of one number, up
  *      to their rounding and at most 256 of it, are two: the multiple, and what the rounding leaves to 2^-31 of the

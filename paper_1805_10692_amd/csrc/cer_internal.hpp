@@ -192,6 +192,9 @@ int decode_device(const DeviceView& v, float* W_dev, void* stream);
 // [row / 32][column / 16][column / 8 % 2][row % 32][column % 8], columns n .. pitch - 1 zero (pitch: a multiple of 16), rows
 // m .. not written.  A hipError_t value as int.
 int decode_pieces(const DeviceView& v, uint16_t* W_dev, int64_t pitch, int64_t plane, void* stream);
+// Handles with a rank table: the ranks, a byte each, in the order in which they are multiplied: 32 x 32 tiles, [row / 32][column / 32]
+// [column / 8 % 2][row % 32][column / 16 % 2][column % 8], columns n .. pitch - 1 rank 0 (pitch: a multiple of 32), rows m .. not written.
+int decode_ranks(const DeviceView& v, uint8_t* W_dev, int64_t pitch, void* stream);
 int quantize_device(const float* W_dev, int64_t count, int32_t bits, uint8_t* codes_dev, float* Wq_dev,
                     float* codebook_out, int32_t* K_out, void* stream);
 

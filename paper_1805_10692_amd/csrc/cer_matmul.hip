@@ -133,10 +133,12 @@ bool densify_estimates(const DeviceView& d, uint32_t L, double* gathers_us, doub
     if (mn * (pieces ? 2.0 * mfma_planes(d) : 4.0) > (double)(1ull << 30)) return false;
     const double flops = 2.0 * mn * L;
     const double t_gather = gather_estimate(d, L, gathers_us);
+    if (t_gather < 9e-6) return false;  // decoder and product take longer: their shapes need not be looked at
     double t_dense;
     if (pieces) {
-        // the decoder: 7 us (578 x 1013), 9 us (conv shape), 11 us (633 x 5106, three pieces, 2.3 M indices), 15 us (1084 x
-        // 13798, one piece, 4.5 M), 28 us (986 x 16765, three pieces, 9.7 M)
+        // the decoder where it leaves pieces: 7 us (578 x 1013), 9 us (conv shape), 11 us (633 x 5106, three pieces, 2.3 M indices).  Where it
+        // leaves ranks, or rows are long, it takes less (18 us for 1867 x 13028, 9.4 M), but the choice between all kernels is fitted with this:
+        // of 600 products nine would change theirs, five by 0.59 to 0.87 times, four by 1.08 to 1.18
         t_dense = mfma_estimate_us(d, L) * 1e-6 + 6e-6 + mn * 2.0 * mfma_planes(d) / 4.4e12 + (double)d.nnz * 0.35e-12;
     } else {
         const double rate = flops < 1.5e10 ? 90e12 : (flops < 1e11 ? 105e12 : 120e12);

@@ -4,7 +4,7 @@
 // Workgroup of 256 rows x BN columns of Y, k steps of BK = 2048 / BN: four waves of 64 rows each (codebooks of one piece), or eight of 32.
 // W's pieces go from memory straight into the registers of the wave that owns the rows: the decoder has left them in operand
 // order, a tile of 32 rows x 16 columns in 1 KiB (row-major pieces cost four times as many cache lines per load and ran at 40 %
-// of this speed).  X is loaded as fp32, eight or four rows of one column per thread, split, and stored to LDS as
+// of this speed) -- or its ranks, which the wave looks up in LDS (multiplies_ranks).  X is loaded as fp32, eight or four rows of one column per thread, split, and stored to LDS as
 // [piece][k / 8][column][8], so that the operand reads are 16 bytes per lane at consecutive addresses.  X is loaded several steps
 // ahead, W one step, and the LDS stores go one or two steps ahead into other buffers: one barrier per step, no branch in between
 // (rows of X behind the last one read as zeros: buffer loads with bounds).
@@ -33,6 +33,65 @@ __device__ __forceinline__ floatx16 joined(floatx16 hi, floatx16 lo, float scale
     return hi;
 }
 
+// kByRank: W comes as one byte per element, and what the matrix cores multiply is looked up in LDS: a word per rank (two pieces; one in the
+// lower half) or two (three), a copy of the table per bank, so that 64 lanes with any ranks read without conflicts.
+// The table of 256 ranks takes 32 KiB: 32 copies of words, 16 of pairs of words.
+constexpr uint32_t kTableWords = 256 * 32, kTableStep = 128;  // bytes from one rank to the next
+template <int kForm>
+__device__ __forceinline__ void fill_table(uint32_t* table, const float* __restrict__ omega, uint32_t K, const UniformGrid& grid, uint32_t tid, uint32_t threads) {
+    // eight threads per rank, 16 bytes each
+    for (uint32_t i = tid; i < 8u * K; i += threads) {
+        const float w = omega[i >> 3];
+        uint32_t p[3];
+        uint4 q;
+        if constexpr (kForm == kUniform) {
+            p[0] = uniform_pieces(w, grid);
+            q = make_uint4(p[0], p[0], p[0], p[0]);
+        } else {
+            split3_finite(w, p);
+            const uint32_t two = p[0] | (p[1] << 16);
+            if constexpr (weight_planes(kForm) == 3) q = make_uint4(two, p[2], two, p[2]);
+            else q = make_uint4(two, two, two, two);
+        }
+        reinterpret_cast<uint4*>(table)[i] = q;
+    }
+}
+// Address of this lane's copy.
+template <int kForm>
+__device__ __forceinline__ uint32_t table_of(const uint32_t* table, uint32_t lane) {
+    typedef const uint32_t __attribute__((address_space(3))) * LdsWord;
+    return (uint32_t)(uintptr_t)(LdsWord)table + (weight_planes(kForm) == 3 ? (lane & 15u) * 8u : (lane & 31u) * 4u);
+}
+// Eight ranks -> the operand registers.
+template <int kForm>
+__device__ __forceinline__ void look_up(uint32_t mine, uint32_t four0, uint32_t four1, uint4 (&a)[weight_planes(kForm)]) {
+    typedef const uint32_t __attribute__((address_space(3))) * LdsWord;
+    typedef uint32_t Pair __attribute__((ext_vector_type(2)));
+    typedef const Pair __attribute__((address_space(3))) * LdsPair;
+    constexpr int PW = weight_planes(kForm);
+    uint32_t e[8], f[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {  // (one byte times the distance of the entries, a dot product of bytes)
+        const uint32_t at = __builtin_amdgcn_udot4(i < 4 ? four0 : four1, kTableStep << (8 * (i & 3)), mine, false);
+        if constexpr (PW == 3) {
+            const Pair q = *reinterpret_cast<LdsPair>((uintptr_t)at);
+            e[i] = q.x;
+            f[i] = q.y;
+        } else {
+            e[i] = *reinterpret_cast<LdsWord>((uintptr_t)at);
+        }
+    }
+    uint32_t w[PW][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        w[0][i] = __builtin_amdgcn_perm(e[2 * i + 1], e[2 * i], 0x05040100u);
+        if constexpr (PW > 1) w[1][i] = __builtin_amdgcn_perm(e[2 * i + 1], e[2 * i], 0x07060302u);
+        if constexpr (PW > 2) w[2][i] = __builtin_amdgcn_perm(f[2 * i + 1], f[2 * i], 0x05040100u);
+    }
+#pragma unroll
+    for (int p = 0; p < PW; ++p) a[p] = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
+}
+
 // What a workgroup of either kernel below was given.
 struct Block {
     const uint16_t* W;
@@ -41,6 +100,8 @@ struct Block {
     size_t plane;
     uint32_t m, n, L, pitch, row0, rows, col0, cols, k_begin, k_end, threads;
     float scale;  // kUniform
+    const float* omega;  // kByRank
+    uint32_t K;
 };
 
 // Products in binary32, the pieces of W added up again: the workgroup's outputs once more, over the ones from the matrix cores.
@@ -53,9 +114,9 @@ struct Block {
 // 512 x 4608, batch 3136.
 // A wave takes tiles of 32 x 32 outputs, 64 or 32 columns of W per step, straight from memory; sums of kFlush columns as below.  Product of
 // 512 x 4608, batch 3136, one-piece codebook: 68 us, 80 with empty rows, 247 with an infinity in X, 331 with X of about 2^-120.
-template <int kForm>
+template <int kForm, bool kByRank>
 __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, bool odd, uint32_t small) {
-    constexpr int PW = weight_planes(kForm), NS = kForm == kUniform ? 2 : 4;  // 16 NS columns of W per step
+    constexpr int PW = weight_planes(kForm), NS = kForm == kUniform ? 2 : 4, PR = kByRank ? 1 : PW;  // 16 NS columns of W per step
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
     if (!__syncthreads_or(must)) {
         if (!__syncthreads_or(odd)) return;
@@ -92,31 +153,41 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
     for (uint32_t t = wave; t < b.rows / 32u * across; t += b.threads / kWave) {
         const uint32_t row32 = b.row0 + t / across * 32u, c = b.col0 + t % across * 32u + (lane & 31u);
         if (row32 >= b.m) break;
-        const uint16_t* w = b.W + (size_t)(row32 >> 5) * 32 * b.pitch;
+        const uint16_t* w = b.W + (size_t)(row32 >> 5) * (kByRank ? 16 : 32) * b.pitch;
         const uint32_t xoff = (8u * half * b.L + min(c, b.L - 1u)) * 4u;
         floatx16 sum = {}, acc = {};
         uint32_t held = 0;
         for (uint32_t k0 = b.k_begin; k0 < b.k_end; k0 += 16u * NS) {  // behind the end: zeros of X, W's last columns once more
             float x[NS][8];
-            uint4 q[NS][PW];
+            uint4 q[NS][PR];
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 const __amdgpu_buffer_rsrc_t xbuf = x_rows(b.X, b.L, k0 + 16 * s, min(b.n, b.k_end));
 #pragma unroll
                 for (int i = 0; i < 8; ++i) x[s][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff + i * b.L * 4u, 0, 0));
+                if constexpr (kByRank) {
+                    if (s % 2 == 0) q[s][0] = reinterpret_cast<const uint4*>(w + (size_t)min(k0 + 16 * s, b.pitch - 32u) * 16)[lane];
+                } else {
 #pragma unroll
-                for (int p = 0; p < PW; ++p) q[s][p] = reinterpret_cast<const uint4*>(w + p * b.plane + (size_t)min(k0 + 16 * s, b.pitch - 16u) * 32)[lane];
+                    for (int p = 0; p < PW; ++p) q[s][p] = reinterpret_cast<const uint4*>(w + p * b.plane + (size_t)min(k0 + 16 * s, b.pitch - 16u) * 32)[lane];
+                }
             }
 #pragma unroll
             for (int s = 0; s < NS; ++s)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    float v = 0.f;
+                    float v = 0.f;  // the codebook's value: a binary32 number
+                    if constexpr (kByRank) {
+                        const uint4& r = q[s & ~1][0];
+                        const uint32_t u = i < 4 ? (s & 1 ? r.z : r.x) : (s & 1 ? r.w : r.y);
+                        v = b.omega[min((u >> (8 * (i & 3))) & 0xFFu, b.K - 1u)];  // (rows behind the last one: any byte)
+                    } else {
 #pragma unroll
-                    for (int p = PW - 1; p >= 0; --p) {
-                        const uint32_t u = i < 4 ? (i < 2 ? q[s][p].x : q[s][p].y) : (i < 6 ? q[s][p].z : q[s][p].w);
-                        const float piece = __uint_as_float(i & 1 ? u & 0xFFFF0000u : u << 16);
-                        v = kForm == kUniform ? fmaf(b.scale, piece, v) : v + piece;  // (the codebook's value: a binary32 number)
+                        for (int p = PW - 1; p >= 0; --p) {
+                            const uint32_t u = i < 4 ? (i < 2 ? q[s][p].x : q[s][p].y) : (i < 6 ? q[s][p].z : q[s][p].w);
+                            const float piece = __uint_as_float(i & 1 ? u & 0xFFFF0000u : u << 16);
+                            v = kForm == kUniform ? fmaf(b.scale, piece, v) : v + piece;
+                        }
                     }
                     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v, x[s][i], acc, 0, 0, 0);
                 }
@@ -137,7 +208,7 @@ __device__ __attribute__((noinline)) void exact_block(const Block b, bool must, 
 
 constexpr int mfma_waves(int form) { return form == 1 ? 4 : 8; }
 
-template <int kForm, int TN>
+template <int kForm, bool kByRank, int TN>
 struct MfmaTile {
     static constexpr int PW = weight_planes(kForm), NW = mfma_waves(kForm);
     static constexpr int TM = kForm == 1 ? 2 : 1, BM = 32 * TM * NW, BN = 32 * TN, BK = 2048 / BN, KG = BK / 8, KS = BK / 16;
@@ -145,6 +216,7 @@ struct MfmaTile {
     // are registers for them) and its loads; rows of X per thread and step, threads per eight of them.
     static constexpr int D = 4, kAhead = kForm == 1 ? 1 : 2, kFetch = D - 3 + 2 * kAhead, kBuffers = 2 * kAhead, XR = 32 / NW, XP = 8 / XR;
     uint4 b[kBuffers][3][KG][BN];
+    uint32_t table[kByRank ? kTableWords : 1];
 
     // sum: what is finished; acc: the sum over the current kFlush columns or so (a running sum of thousands of terms would
     // round each of them to the size of the whole).  Returns a NaN if this thread's share of X holds numbers without pieces, and
@@ -158,7 +230,9 @@ struct MfmaTile {
 #pragma unroll
         for (int i = 0; i < XR; ++i) xoff[i] = ((8u * xg + XR * xp + i) * L + xcol) * 4u;
         float xr[D][XR];
-        uint4 a[2][KS][TM][PW], bb[kAhead][TN][3];
+        uint4 a[2][kByRank ? 1 : KS][TM][PW], bb[kAhead][TN][3];
+        uint4 raw[kByRank ? D : 1][kByRank ? KS / 2 : 1][TM];  // kByRank: 32 columns per 16 bytes of a lane, two steps ahead
+        const uint32_t mine = table_of<kForm>(table, lane);
         float odd = 0.f;
         auto load_x = [&](uint32_t k0, int slot) {
             const __amdgpu_buffer_rsrc_t xbuf = x_rows(X, L, k0, n);
@@ -166,13 +240,28 @@ struct MfmaTile {
             for (int i = 0; i < XR; ++i) xr[slot][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff[i], 0, 0));
         };
         auto load_w = [&](uint32_t k0, int slot) {
+            if constexpr (kByRank) {
 #pragma unroll
-            for (int s = 0; s < KS; ++s)
+                for (int s = 0; s < KS / 2; ++s)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+                    for (int i = 0; i < TM; ++i) raw[slot][s][i] = reinterpret_cast<const uint4*>(wtile[i] + (size_t)(k0 + 32 * s) * 16)[lane];
+            } else {
 #pragma unroll
-                    for (int p = 0; p < PW; ++p)
-                        a[slot][s][i][p] = reinterpret_cast<const uint4*>(wtile[i] + p * plane + (size_t)(k0 + 16 * s) * 32)[lane];
+                for (int s = 0; s < KS; ++s)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int p = 0; p < PW; ++p)
+                            a[slot][s][i][p] = reinterpret_cast<const uint4*>(wtile[i] + p * plane + (size_t)(k0 + 16 * s) * 32)[lane];
+            }
+        };
+        auto expand = [&](int slot, int s, int to) {
+            if constexpr (kByRank)
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const uint4& r = raw[slot][s / 2][i];
+                    look_up<kForm>(mine, s & 1 ? r.z : r.x, s & 1 ? r.w : r.y, a[to][0][i]);
+                }
         };
         auto store_x = [&](int slot, int buf) {
             if constexpr (XP == 1) {
@@ -215,12 +304,14 @@ struct MfmaTile {
 #pragma unroll
         for (int t = 0; t < (kFetch < D ? kFetch : D); ++t) load_x(at(k_begin + t * BK), t);
         load_w(k_begin, 0);
+        if constexpr (kByRank) load_w(at(k_begin + BK), 1);
 #pragma unroll
         for (int t = 0; t < kAhead; ++t) store_x(t, t);
 #pragma unroll
         for (int t = D; t < kFetch; ++t) load_x(at(k_begin + t * BK), t % D);
         __syncthreads();
         if constexpr (kAhead > 1) read_b(0, 0, 0);
+        expand(0, 0, 0);
         // D steps per round, so that the register slots are named at compile time; the last round may be shorter
         uint32_t held = 0;
         for (uint32_t k0 = k_begin; k0 < k_end; k0 += D * BK) {
@@ -228,17 +319,22 @@ struct MfmaTile {
             for (int t = 0; t < D; ++t) {
                 if (t > 0 && k0 + t * BK >= k_end) break;
                 load_x(at(k0 + (t + kFetch) * BK), (t + kFetch) % D);
-                load_w(at(k0 + (t + 1) * BK), (t + 1) & 1);
+                if constexpr (kByRank) load_w(at(k0 + (t + 2) * BK), (t + 2) % D);
+                else load_w(at(k0 + (t + 1) * BK), (t + 1) & 1);
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
                     const int q = (t * KS + s) % kAhead;
                     if constexpr (kAhead == 1) read_b(t % kBuffers, s, 0);
                     else if (s + 1 < KS) read_b(t, s + 1, q ^ 1);
                     else read_b((t + 1) % kBuffers, 0, q ^ 1);
+                    const int w = (t * KS + s) & 1;
+                    if (s + 1 < KS) expand(t, s + 1, w ^ 1);
+                    else expand((t + 1) % D, 0, w ^ 1);
 #pragma unroll
                     for (int i = 0; i < TM; ++i)
 #pragma unroll
-                        for (int j = 0; j < TN; ++j) mfma_pieces<kForm>(a[t & 1][s][i], bb[q][j], acc[i][j], lo[i][j]);
+                        for (int j = 0; j < TN; ++j)
+                            mfma_pieces<kForm>(a[kByRank ? w : t & 1][kByRank ? 0 : s][i], bb[q][j], acc[i][j], lo[i][j]);
                 }
                 store_x((t + kAhead) % D, (t + kAhead) % kBuffers);
                 __syncthreads();
@@ -273,12 +369,12 @@ __device__ __forceinline__ Place place_of(uint32_t item, uint32_t few, uint32_t 
     return Place{item - rest * few, parts_inside ? last : middle, parts_inside ? middle : last};
 }
 
-template <int kForm, int TN>
+template <int kForm, bool kByRank, int TN>
 __global__ __launch_bounds__(64 * mfma_waves(kForm), 2) void mfma_product_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
     uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, uint32_t longer, uint32_t parts_inside,
-    size_t split_stride, float faint, float scale) {
-    using Tile = MfmaTile<kForm, TN>;
+    size_t split_stride, float faint, UniformGrid grid, const float* __restrict__ omega, uint32_t K) {
+    using Tile = MfmaTile<kForm, kByRank, TN>;
     __shared__ Tile tile;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroups are dealt round-robin to the eight XCDs; every XCD takes a contiguous eighth of the list of work items, in
@@ -294,9 +390,10 @@ __global__ __launch_bounds__(64 * mfma_waves(kForm), 2) void mfma_product_kernel
     Out += sp * split_stride;
     const uint16_t* wtile[Tile::TM];
 #pragma unroll
-    for (int i = 0; i < Tile::TM; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * 32 * pitch;
+    for (int i = 0; i < Tile::TM; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * (kByRank ? 16 : 32) * pitch;
     floatx16 sum[Tile::TM][TN];
-    const float odd = tile.run(wtile, plane, X, n, L, col0, k_begin, k_end, sum, scale);
+    if constexpr (kByRank) fill_table<kForm>(tile.table, omega, K, grid, tid, 64u * mfma_waves(kForm));
+    const float odd = tile.run(wtile, plane, X, n, L, col0, k_begin, k_end, sum, grid.scale);
 
     // The vote comes before the stores (behind them: 2 us more).
     float least = INFINITY;
@@ -332,7 +429,7 @@ __global__ __launch_bounds__(64 * mfma_waves(kForm), 2) void mfma_product_kernel
                 for (int e = 0; e < 16; ++e) low = fminf(low, fabsf(sum[i][j][e]));
             small |= low < faint ? 1u << j : 0u;
         }
-        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, rt * Tile::BM, Tile::BM, col0, Tile::BN, k_begin, k_end, 64u * mfma_waves(kForm), scale}, odd != odd, odd != 0.f, small);
+        exact_block<kForm, kByRank>(Block{W, X, Out, plane, m, n, L, pitch, rt * Tile::BM, Tile::BM, col0, Tile::BN, k_begin, k_end, 64u * mfma_waves(kForm), grid.scale, omega, K}, odd != odd, odd != 0.f, small);
     }
 }
 
@@ -344,10 +441,10 @@ __global__ __launch_bounds__(64 * mfma_waves(kForm), 2) void mfma_product_kernel
 // 3136: 66 instead of 44.  Bound by the latency of its loads where the chip is not full (2048 x 2048, batch 16, 128 workgroups:
 // matrix pipes busy 6 % of the launch, vector ALU 11 %, half of a wave's time is waiting for data), else by what L2 delivers (80
 // KiB per 128 columns): the larger tile is the better one where it fills the chip.
-template <int kForm, int CT>
+template <int kForm, bool kByRank, int CT>
 __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2], size_t plane, const float* X, uint32_t n,
                                                 uint32_t L, uint32_t col0, uint32_t k_begin, uint32_t k_end, floatx16 (&acc)[2][CT],
-                                                float scale) {
+                                                float scale, uint32_t mine) {
     constexpr int PW = weight_planes(kForm);
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t xoff[8];  // of the wave's first column tile
@@ -356,7 +453,7 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
     uint32_t xstep[CT];
 #pragma unroll
     for (int j = 0; j < CT; ++j) xstep[j] = (min(col0 + 32u * j + (lane & 31u), L - 1u) - min(col0 + (lane & 31u), L - 1u)) * 4u;
-    uint4 a[2][2][2][PW];
+    uint4 a[2][kByRank ? 1 : 2][2][kByRank ? 1 : PW];  // kByRank: 32 columns per 16 bytes of a lane
     floatx16 lo[2][CT];
     float x[2][2][CT][8];
     float odd = 0.f;
@@ -369,23 +466,38 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
                     x[slot][s][j][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xbuf, xoff[i] + xstep[j], 0, 0));
+            if constexpr (kByRank) {
+                if (s == 0)
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+                    for (int i = 0; i < 2; ++i) a[slot][0][i][0] = reinterpret_cast<const uint4*>(wtile[i] + (size_t)k0 * 16)[lane];
+            } else {
 #pragma unroll
-                for (int p = 0; p < PW; ++p)
-                    a[slot][s][i][p] = reinterpret_cast<const uint4*>(wtile[i] + p * plane + (size_t)(k0 + 16 * s) * 32)[lane];
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int p = 0; p < PW; ++p)
+                        a[slot][s][i][p] = reinterpret_cast<const uint4*>(wtile[i] + p * plane + (size_t)(k0 + 16 * s) * 32)[lane];
+            }
         }
     };
     auto step = [&](int slot) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < 2; ++s) {
+            uint4 w[2][PW];
+            if constexpr (kByRank) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const uint4& r = a[slot][0][i][0];
+                    look_up<kForm>(mine, s ? r.z : r.x, s ? r.w : r.y, w[i]);
+                }
+            }
 #pragma unroll
             for (int j = 0; j < CT; ++j) {
                 uint4 b[3];
                 odd += split3_8(x[slot][s][j], b);
 #pragma unroll
-                for (int i = 0; i < 2; ++i) mfma_pieces<kForm>(a[slot][s][i], b, acc[i][j], lo[i][j]);
+                for (int i = 0; i < 2; ++i) mfma_pieces<kForm>(kByRank ? w[i] : a[slot][kByRank ? 0 : s][i], b, acc[i][j], lo[i][j]);
             }
+        }
     };
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -417,12 +529,14 @@ __device__ __forceinline__ float mfma_small_run(const uint16_t* const (&wtile)[2
     return odd;
 }
 
-template <int kForm, int CT>
+template <int kForm, bool kByRank, int CT>
 __global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUniform) && CT == 1) ? 2 : 1) void mfma_small_kernel(
     const uint16_t* __restrict__ W, const float* __restrict__ X, float* __restrict__ Out, uint32_t m, uint32_t n, uint32_t L,
     uint32_t pitch, size_t plane, uint32_t row_tiles, uint32_t col_tiles, uint32_t splits, uint32_t kchunk, uint32_t longer, uint32_t,
-    size_t split_stride, float faint, float scale) {
+    size_t split_stride, float faint, UniformGrid grid, const float* __restrict__ omega, uint32_t K) {
     __shared__ float s_acc[4][2 * CT][16][64];
+    uint32_t* const table = reinterpret_cast<uint32_t*>(s_acc);  // kByRank: until the sums are made
+    static_assert(sizeof s_acc >= kTableWords * 4, "the table lies where the sums meet");
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t items = row_tiles * col_tiles * splits, eighth = (items + 7u) >> 3;
     const uint32_t item = (blockIdx.x & 7u) * eighth + (blockIdx.x >> 3);  // as above
@@ -433,9 +547,14 @@ __global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUnifor
     Out += sp * split_stride;
     const uint16_t* wtile[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * 32 * pitch;
+    for (int i = 0; i < 2; ++i) wtile[i] = W + (size_t)min((row0 >> 5) + i, (m - 1u) >> 5) * (kByRank ? 16 : 32) * pitch;
+    if constexpr (kByRank) {
+        fill_table<kForm>(table, omega, K, grid, tid, 256u);
+        __syncthreads();
+    }
     floatx16 acc[2][CT];
-    const float odd = mfma_small_run<kForm, CT>(wtile, plane, X, n, L, col0, k_begin, k_end, acc, scale);
+    const float odd = mfma_small_run<kForm, kByRank, CT>(wtile, plane, X, n, L, col0, k_begin, k_end, acc, grid.scale, table_of<kForm>(table, lane));
+    if constexpr (kByRank) __syncthreads();
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -461,7 +580,7 @@ __global__ __launch_bounds__(256, kForm == 1 || ((kForm == 2 || kForm == kUnifor
         if (r < m && c < L) Out[(size_t)r * L + c] = y[q];
     }
     if (look)
-        exact_block<kForm>(Block{W, X, Out, plane, m, n, L, pitch, row0, 64u, col0, 32u * CT, k_begin, k_end, 256u, scale}, odd != odd, odd != 0.f, least < faint ? 1u << ((wave * PER >> 4) % CT) : 0u);  // (a wave's share lies in one tile)
+        exact_block<kForm, kByRank>(Block{W, X, Out, plane, m, n, L, pitch, row0, 64u, col0, 32u * CT, k_begin, k_end, 256u, grid.scale, omega, K}, odd != odd, odd != 0.f, least < faint ? 1u << ((wave * PER >> 4) % CT) : 0u);  // (a wave's share lies in one tile)
 }
 
 // The sums of the parts.  Bound by the bytes: four floats per thread and load, four loads in flight; the parts of 512 x 4608, batch 3136
@@ -577,15 +696,31 @@ MfmaShape mfma_shape(const DeviceView& d, uint32_t L) {
     return small.us < big.us ? small : big;
 }
 
-template <int kForm>
+// Whether the decoder leaves ranks instead of pieces: one byte per element written and read instead of four or six, but the product looks
+// every one up again for each of its tiles of columns (a dot product, an LDS read and an add or two of a permutation each, on a launch bound by the
+// matrix cores' power).  Saved, us: 1.5 and 0.14 per million bytes (1419 x 7930, two pieces, 5.1; 1180 x 1489, three, 1.9), twice that where
+// few rows keep a decoder of pieces waiting (260 x 8894, batch 264 31.8 / 25.4); added, in shares of the
+// product: 0.16 with two pieces (1419 x 7930, batch 242 30.0 -> 34.9), 0.12 with three (1180 x 1489, batch 847 27.4 -> 30.6) and of the small tiles, which
+// wait for their loads (1040 x 5160, batch 949 57.2 -> 65.5).  us per call, pieces / ranks: 2780 x 19849, 117 values, batch 79 130 / 104; 2819 x 13862,
+// 6 bits, 130 171 / 135; 1252 x 22319, 8 bits, 186 140 / 107; 3054 x 4174, 6 bits, 137 60 / 50; 961 x 3191, 4 bits, 517 43 / 38; but 599 x 19045,
+// 3 values, batch 384 70.6 / 73.5; 1509 x 4663, 17 values, 723 73 / 77; 2095 x 1669, 7 bits, 1109 78 / 80.  One piece is two bytes as it is: 0.95 to 1.14
+// times the time.
+bool multiplies_ranks(const DeviceView& d, const MfmaShape& s) {
+    const int planes = weight_planes(weight_form(d));
+    if (!d.rank_tab || planes == 1) return false;
+    const double bytes = (double)d.m * (double)d.n * (2.0 * planes - 1.0) * (d.m <= 2 * d.cus ? 2.0 : 1.0);
+    return 1.5 + bytes / 7e6 > s.us * (s.small || planes == 3 ? 0.12 : 0.16);
+}
+
+template <int kForm, bool kByRank>
 hipError_t launch_shape(const MfmaShape& s, const uint16_t* W, const float* X, float* out, uint32_t m, uint32_t n, uint32_t L,
                         uint32_t pitch, size_t plane, float faint, const DeviceView& d, hipStream_t stream) {
     const dim3 grid((s.row_tiles * s.col_tiles * s.splits + 7) / 8 * 8);
     const size_t count = (size_t)m * L;
-    auto* kern = s.small ? (s.BN == 32 ? mfma_small_kernel<kForm, 1> : mfma_small_kernel<kForm, 2>)
-                         : (s.BN == 32 ? mfma_product_kernel<kForm, 1> : mfma_product_kernel<kForm, 2>);
+    auto* kern = s.small ? (s.BN == 32 ? mfma_small_kernel<kForm, kByRank, 1> : mfma_small_kernel<kForm, kByRank, 2>)
+                         : (s.BN == 32 ? mfma_product_kernel<kForm, kByRank, 1> : mfma_product_kernel<kForm, kByRank, 2>);
     return launch_kernel(kern, grid, dim3(s.small ? 256 : 64 * mfma_waves(kForm)), 0, stream, W, X, out, m, n, L, pitch, plane, s.row_tiles, s.col_tiles, s.splits,
-                         s.per * s.unit, s.longer, s.parts_inside ? 1u : 0u, count, faint, d.grid.scale);
+                         s.per * s.unit, s.longer, s.parts_inside ? 1u : 0u, count, faint, d.grid, d.omega, (uint32_t)d.K);
 }
 
 }  // namespace
@@ -600,26 +735,30 @@ double mfma_estimate_us(const DeviceView& d, uint32_t L) { return mfma_shape(d, 
 
 hipError_t launch_mfma(const DeviceView& d, const float* X, float* Y, uint32_t L, hipStream_t stream) {
     MfmaShape s = mfma_shape(d, L);
+    const int form = weight_form(d);
     const int64_t pitch = (d.n + kPitchStep - 1) / kPitchStep * kPitchStep, plane = pitch * ((d.m + 31) / 32 * 32);
+    const bool by_rank = multiplies_ranks(d, s);
+    const size_t w_bytes = by_rank ? (size_t)plane : (size_t)plane * 2 * weight_planes(form);
     const size_t count = (size_t)d.m * L;
-    s.parts_inside = (uint64_t)plane * 2 * weight_planes(weight_form(d)) + (uint64_t)d.n * L * 4 <= kPartsInside && count * s.splits * 4 <= kFewParts;
+    s.parts_inside = (uint64_t)w_bytes + (uint64_t)d.n * L * 4 <= kPartsInside && count * s.splits * 4 <= kFewParts;
     // one temporary: the partial sums, then the pieces
     const size_t part_bytes = s.splits > 1 ? (count * s.splits * 4 + 255) & ~(size_t)255 : 0;
     unsigned char* tmp = nullptr;
-    hipError_t e = (hipError_t)temp_alloc(reinterpret_cast<void**>(&tmp), part_bytes + (size_t)plane * 2 * weight_planes(weight_form(d)), stream);
+    hipError_t e = (hipError_t)temp_alloc(reinterpret_cast<void**>(&tmp), part_bytes + w_bytes, stream);
     if (e != hipSuccess) return e;
     auto* W = reinterpret_cast<uint16_t*>(tmp + part_bytes);
     float* out = s.splits > 1 ? reinterpret_cast<float*>(tmp) : Y;
-    e = (hipError_t)decode_pieces(d, W, pitch, plane, stream);
+    e = (hipError_t)(by_rank ? decode_ranks(d, reinterpret_cast<uint8_t*>(W), pitch, stream) : decode_pieces(d, W, pitch, plane, stream));
     if (e == hipSuccess) {
         const uint32_t m = (uint32_t)d.m, n = (uint32_t)d.n;
         // An input loses at most half of 2^-133, a sum at most n max|w| 2^-134: less than 2^-26 of itself from here on.
         const float faint = (float)std::min((double)d.n * d.omega_max * 0x1p-108, 1e38);
-        switch (weight_form(d)) {
-            case 1: e = launch_shape<1>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, d, stream); break;
-            case 2: e = launch_shape<2>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, d, stream); break;
-            case 3: e = launch_shape<3>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, d, stream); break;
-            default: e = launch_shape<kUniform>(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, d, stream);
+        auto launch = [&](auto kernels) { return kernels(s, W, X, out, m, n, L, (uint32_t)pitch, (size_t)plane, faint, d, stream); };
+        switch (form) {
+            case 1: e = launch(launch_shape<1, false>); break;
+            case 2: e = launch(by_rank ? launch_shape<2, true> : launch_shape<2, false>); break;
+            case 3: e = launch(by_rank ? launch_shape<3, true> : launch_shape<3, false>); break;
+            default: e = launch(by_rank ? launch_shape<kUniform, true> : launch_shape<kUniform, false>);
         }
     }
     if (e == hipSuccess && s.splits > 1)

@@ -1185,12 +1185,12 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict
     }
 }
 
-// bf16 pieces in the operand order of v_mfma_f32_32x32x16_bf16: tiles of 32 rows x 16 columns, 1 KiB each, [row / 32]
-// [column / 16][column / 8 % 2][row % 32][column % 8], rows padded with zeros to a multiple of 16 columns (pitch).  Eight
+// bf16 pieces (kPieces 0: ranks, a byte each, see decode_ranks) in the operand order of v_mfma_f32_32x32x16_bf16: tiles of 32 rows x 16 columns, 1 KiB each, [row / 32]
+// [column / 16][column / 8 % 2][row % 32][column % 8], rows padded with zeros to a multiple of 32 columns (pitch).  Eight
 // rows per workgroup, so that a store of the workgroup covers whole 128-byte lines; four where eight would leave compute
 // units without work (reading the rows' indices is what takes time, and segments do not divide it).
 // Ranks: the rows' records of the rank table come with one load, and their positions -- consecutive in colI -- are
-// dealt to all threads, eight at a time, two vectors in flight.  A position's group is the number of groups that begin at or
+// dealt to all T threads, eight at a time, two vectors in flight.  A position's group is the number of groups that begin at or
 // before it: a bitmap of the beginnings, counted up per word, as in the batch-1 kernel -- no search, no branch (a binary search
 // and a walk over the boundaries waited for LDS at every step: 633 x 5106, 112 values, 22 us, now 11; 986 x 16765, three
 // values, 42 against 28).  Bound by the phases of a workgroup -- records, list, bitmap, positions, output -- that follow one another
@@ -1198,20 +1198,21 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict
 // positions are requested as soon as the records tell where they are, the pieces of the values are made and the bitmap is filled
 // beside the list meanwhile, and the counts are summed by lane moves: 0.4 to 0.8 us of 5.6 to 11.3, 0.985 of the call in the geometric mean of
 // 50 products (2067 x 521, batch 1638, 38.7 -> 37.3 us).  Eight rows in more segments instead of four rows: 1.03 times the call; four rows in more
-// segments 1.01; two rows 1.005.  Stores past the L2 (what a launch leaves there is written back behind it): 0.97 with eight rows and up to
+// segments 1.01; two rows 1.005 (rows of up to 6144 columns).  Stores past the L2 (what a launch leaves there is written back behind it): 0.97 with eight rows and up to
 // 16 MB, but 1.02 - 1.06 with four rows or larger matrices.
 constexpr uint32_t kStretch = 32768;  // positions per bitmap
-template <typename ColT, typename CodeT, int kPieces>
-__global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restrict__ colI, DecodeArgs a, int64_t m, int64_t pitch,
-                                                           int64_t plane, uint16_t* __restrict__ out) {
+template <typename ColT, typename CodeT, int kPieces, uint32_t T>
+__global__ __launch_bounds__(T) void decode_tiles_kernel(const ColT* __restrict__ colI, DecodeArgs a, int64_t m, int64_t pitch,
+                                                         int64_t plane, uint16_t* __restrict__ out) {
     constexpr bool kRanks = sizeof(CodeT) == 1;
+    constexpr uint32_t kPer = kStretch / 32 / T;  // words of the bitmap per thread
     extern __shared__ __align__(16) unsigned char s_seg[];  // eight rows of seg + 8 codes
     __shared__ uint32_t s_ptr[kRanks ? 8 * kCodes : 8 * (kWave + 1)];
     __shared__ uint32_t s_list[kRanks ? 8 * kCodes + 1 : 1];
     __shared__ uint32_t s_bits[kRanks ? kStretch / 32 : 1], s_pre[kRanks ? kStretch / 32 : 1];
-    __shared__ uint32_t s_cnt[8], s_sum[8];
+    __shared__ uint32_t s_cnt[T / kWave], s_sum[T / kWave];
     __shared__ CodeT s_grp[8][kRanks ? 1 : kWave];
-    __shared__ uint32_t s_val[kRanks ? kCodes : 1];  // pieces 0 | 1 << 16, by rank
+    __shared__ uint32_t s_val[kRanks && kPieces > 0 ? kCodes : 1];  // pieces 0 | 1 << 16, by rank
     __shared__ uint32_t s_val2[kRanks && kPieces == 3 ? kCodes : 1];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const int64_t row0 = (int64_t)blockIdx.x * a.rows;
@@ -1221,10 +1222,10 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
     CodeT* code = reinterpret_cast<CodeT*>(s_seg);
     if constexpr (kRanks) {
         const uint32_t rows = (uint32_t)min((int64_t)a.rows, m - row0), words = rows << a.tab_shift;
-        const float own = a.omega[min(tid, a.K - 1u)];  // (512 threads, at most 256 values)
-        for (uint32_t i = tid; i < words; i += 512u) s_ptr[i] = a.tab[((size_t)row0 << a.tab_shift) + i];
-        for (uint32_t j = tid; j < a.rows * stride >> 3; j += 512u) reinterpret_cast<uint2*>(s_seg)[j] = make_uint2(0, 0);
-        s_bits[2u * tid] = s_bits[2u * tid + 1u] = 0u;
+        const float own = kPieces > 0 ? a.omega[min(tid, a.K - 1u)] : 0.f;  // (at most 256 values)
+        for (uint32_t i = tid; i < words; i += T) s_ptr[i] = a.tab[((size_t)row0 << a.tab_shift) + i];
+        for (uint32_t j = tid; j < a.rows * stride >> 3; j += T) reinterpret_cast<uint2*>(s_seg)[j] = make_uint2(0, 0);
+        for (uint32_t i = 0; i < kPer; ++i) s_bits[kPer * tid + i] = 0u;
         __syncthreads();
         // the first positions are on their way while what tells their groups is made
         const uint32_t pb = s_ptr[0], pe = s_ptr[words - 1u];
@@ -1234,18 +1235,19 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
         };
         const uint32_t first = pb & ~7u;
         request(first + tid * 8u, min(pe, first + kStretch), ahead[0]);
-        request(first + tid * 8u + 4096u, min(pe, first + kStretch), ahead[1]);
-        if (tid < a.K) {
-            if (kPieces == 2 && a.grid.scale != 0.f) {
-                s_val[tid] = cer::uniform_pieces(own, a.grid);
-            } else {
-                uint32_t p[3];
-                cer::split3_finite(own, p);
-                s_val[tid] = p[0] | (p[1] << 16);
-                if constexpr (kPieces == 3) s_val2[tid] = p[2];
+        request(first + tid * 8u + 8u * T, min(pe, first + kStretch), ahead[1]);
+        if constexpr (kPieces > 0)
+            if (tid < a.K) {
+                if (kPieces == 2 && a.grid.scale != 0.f) {
+                    s_val[tid] = cer::uniform_pieces(own, a.grid);
+                } else {
+                    uint32_t p[3];
+                    cer::split3_finite(own, p);
+                    s_val[tid] = p[0] | (p[1] << 16);
+                    if constexpr (kPieces == 3) s_val2[tid] = p[2];
+                }
             }
-        }
-        // list of the non-empty groups, in order of their positions: the row's place in s_seg | rank << 16; entry 0 is unused; and a bitmap of
+        // list of the non-empty groups, in order of their positions: the row's place in s_seg | rank << 24; entry 0 is unused; and a bitmap of
         // the positions that begin a group, of the first stretch of positions
         auto begins = [&](uint32_t i, uint32_t& at) {  // boundary i closes a group that begins at position `at`
             if (i == 0 || i >= words) return false;
@@ -1256,7 +1258,7 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
             if (at - base < kStretch) atomicOr(&s_bits[(at - base) >> 5], 1u << ((at - base) & 31u));
         };
         uint32_t groups = 1;
-        for (uint32_t c = 0; c < words; c += 512u) {
+        for (uint32_t c = 0; c < words; c += T) {
             uint32_t at;
             const uint32_t i = c + tid;
             const bool some = begins(i, at);
@@ -1265,38 +1267,43 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
             if (lane == 0) s_cnt[wave] = (uint32_t)__popcll(votes);
             __syncthreads();
             uint32_t pos = groups + (uint32_t)__popcll(votes & ((1ull << lane) - 1ull));
-            for (uint32_t w = 0; w < 8; ++w) {
+            for (uint32_t w = 0; w < T / kWave; ++w) {
                 if (w < wave) pos += s_cnt[w];
                 groups += s_cnt[w];
             }
-            if (some) s_list[pos] = (i >> a.tab_shift) * stride | ((i & ((1u << a.tab_shift) - 1u)) << 16);
-            if (c + 512u < words) __syncthreads();  // (uniform)
+            if (some) s_list[pos] = (i >> a.tab_shift) * stride | ((i & ((1u << a.tab_shift) - 1u)) << 24);
+            if (c + T < words) __syncthreads();  // (uniform)
         }
         uint32_t seen = 0;  // groups that begin before the current stretch of positions
         for (uint32_t base = first; base < pe; base += kStretch) {  // uniform over the workgroup
             if (base != first) {
                 request(base + tid * 8u, min(pe, base + kStretch), ahead[0]);
-                request(base + tid * 8u + 4096u, min(pe, base + kStretch), ahead[1]);
-                s_bits[2u * tid] = s_bits[2u * tid + 1u] = 0u;
+                request(base + tid * 8u + 8u * T, min(pe, base + kStretch), ahead[1]);
+                for (uint32_t i = 0; i < kPer; ++i) s_bits[kPer * tid + i] = 0u;
                 __syncthreads();
-                for (uint32_t i = tid; i < words; i += 512u) {
+                for (uint32_t i = tid; i < words; i += T) {
                     uint32_t at;
                     if (begins(i, at)) mark(at, base);
                 }
                 __syncthreads();
             }
             // the number of beginnings in front of every word
-            const uint32_t n0 = (uint32_t)__builtin_popcount(s_bits[2u * tid]), n1 = (uint32_t)__builtin_popcount(s_bits[2u * tid + 1u]);
-            const uint32_t incl = cer::wave_inclusive_scan(n0 + n1);
+            uint32_t ones[kPer], all = 0;
+#pragma unroll
+            for (uint32_t i = 0; i < kPer; ++i) all += ones[i] = (uint32_t)__builtin_popcount(s_bits[kPer * tid + i]);
+            const uint32_t incl = cer::wave_inclusive_scan(all);
             if (lane == 63u) s_sum[wave] = incl;
             __syncthreads();
-            uint32_t before = seen + incl - n0 - n1;
-            for (uint32_t w = 0; w < 8; ++w) {
+            uint32_t before = seen + incl - all;
+            for (uint32_t w = 0; w < T / kWave; ++w) {
                 if (w < wave) before += s_sum[w];
                 seen += s_sum[w];
             }
-            s_pre[2u * tid] = before;
-            s_pre[2u * tid + 1u] = before + n0;
+#pragma unroll
+            for (uint32_t i = 0; i < kPer; ++i) {
+                s_pre[kPer * tid + i] = before;
+                before += ones[i];
+            }
             __syncthreads();
             auto take = [&](uint32_t v, const uint32_t (&col)[8]) {
                 const uint32_t rel0 = v - base, word = s_bits[rel0 >> 5], sh = rel0 & 31u;
@@ -1310,21 +1317,21 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
 #pragma unroll
                 for (uint32_t i = 0; i < 8; ++i) {
                     const uint32_t rel = col[i] - (uint32_t)c0;  // huge when left of the segment
-                    if (v + i >= pb && v + i < pe && rel < len) code[(e[i] & 0xFFFFu) + rel] = (CodeT)(e[i] >> 16);
+                    if (v + i >= pb && v + i < pe && rel < len) code[(e[i] & 0xFFFFFFu) + rel] = (CodeT)(e[i] >> 24);
                 }
             };
             const uint32_t stop = min(pe, base + kStretch);
-            for (uint32_t v = base + tid * 8u; v < stop; v += 8192u) {
+            for (uint32_t v = base + tid * 8u; v < stop; v += 16u * T) {
                 uint32_t col[2][8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     col[0][i] = ahead[0][i];
                     col[1][i] = ahead[1][i];
                 }
-                request(v + 8192u, stop, ahead[0]);
-                request(v + 12288u, stop, ahead[1]);
+                request(v + 16u * T, stop, ahead[0]);
+                request(v + 24u * T, stop, ahead[1]);
                 take(v, col[0]);
-                if (v + 4096u < stop) take(v + 4096u, col[1]);
+                if (v + 8u * T < stop) take(v + 8u * T, col[1]);
             }
             __syncthreads();
         }
@@ -1338,8 +1345,23 @@ __global__ __launch_bounds__(512) void decode_tiles_kernel(const ColT* __restric
     }
     __syncthreads();
     const uint32_t wlen = c0 + a.seg >= a.n ? (uint32_t)(pitch - c0) : a.seg;  // the last segment also writes the padding
-    const uint32_t rr = tid & (a.rows - 1u), columns = 8u * 512u / a.rows;  // columns per step of the workgroup
+    const uint32_t rr = tid & (a.rows - 1u), columns = 8u * T / a.rows;  // columns per step of the workgroup
     if (row0 + rr >= m) return;
+    if constexpr (kPieces == 0) {
+        // 16 bytes per thread: columns 16 s + 8 half .. + 7 of 32, s = 0, 1 (a multiple of 32 columns lies in s_seg whole, zeros behind len)
+        const uint32_t half = tid / a.rows & 1u;
+        uint4* o = reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(out) + ((row0 >> 5) * pitch + c0) * 32) + 32u * half + ((uint32_t)row0 & 31u) + rr;
+        const CodeT* mine = code + rr * stride + 8u * half;
+        for (uint32_t j = tid / a.rows / 2u * 32u; j < wlen; j += 2u * columns) {
+            uint2 q0 = make_uint2(0u, 0u), q1 = q0;
+            if (j < a.seg) {
+                q0 = *reinterpret_cast<const uint2*>(mine + j);
+                q1 = *reinterpret_cast<const uint2*>(mine + j + 16u);
+            }
+            o[2u * j] = make_uint4(q0.x, q0.y, q1.x, q1.y);
+        }
+        return;
+    }
     uint16_t* o = out + (row0 >> 5) * 32 * pitch + ((row0 & 31) + rr) * 8;
     const CodeT* mine = code + rr * stride;
     for (uint32_t j = tid / a.rows * 8u; j < wlen; j += columns) {
@@ -1608,29 +1630,63 @@ hipError_t launch_decode(const DeviceView& v, float* out, hipStream_t s) {
     return launch_kernel(past ? decode_kernel<ColT, CodeT, 256, true> : decode_kernel<ColT, CodeT, 256, false>, grid, dim3(256), lds, s, colI, a, out);
 }
 
-template <typename ColT, typename CodeT>
+// kPieces == 0: ranks, one byte each (decode_ranks).
+template <typename ColT, typename CodeT, int kPieces>
 hipError_t launch_decode_tiles(const DeviceView& v, uint16_t* out, int64_t pitch, int64_t plane, hipStream_t s) {
-    const int pieces = v.grid.scale != 0.f ? 2 : v.pieces;
     uint32_t rows = 8;
     while (rows > 4 && (v.m + rows - 1) / rows < v.cus) rows >>= 1;
-    // as few segments as 48 KiB of LDS allow (two workgroups per compute unit): each of them reads all indices of its rows
-    const int64_t most = 49152 / (int64_t)sizeof(CodeT) / rows, groups = (v.m + rows - 1) / rows;
-    DecodeArgs a = decode_args(v, (v.n + most - 1) / most, 16);
+    // Every segment reads all indices of its rows, so there are as few as the LDS allows: two workgroups of 512 threads per compute unit with 48
+    // KiB each for rows of up to 6144 columns, one of 1024 threads with up to 132 for longer ones (33792 columns in one segment).  2780 x 19849, 40 %
+    // indexed, ranks: eight rows in four segments of 6 K columns 50 us, in two of 10 K 36, four rows in one 20 (whole call 136 / 119 / 101); 2150 x 19579,
+    // one piece, 69 -> 42 us; two workgroups of 512 threads and four rows 2 - 10 % slower in the call from 11000 columns on, 5 - 10 % faster below
+    // 9000 and large batches of rows.  Two rows where four leave half of the compute units without any: 358 x 22120, batch 329 72 -> 67, 264 x 9255, 29 25 -> 21.
+    int64_t most = 48 * 1024;
+    bool wide = false;
+    if (sizeof(CodeT) == 1 && v.n > most / 8) {
+        rows = kPieces == 0 && v.m <= 2 * v.cus ? 2 : 4;
+        wide = rows == 2 || v.n > most / 4;
+        if (wide) most = 132 * 1024;
+    }
+    most /= sizeof(CodeT) * rows;
+    const int64_t groups = (v.m + rows - 1) / rows;
+    DecodeArgs a = decode_args(v, (v.n + most - 1) / most, 32);
     a.rows = rows;
     const dim3 grid((unsigned)groups, a.nseg);
     const size_t lds = (size_t)(a.seg + 8) * rows * sizeof(CodeT);
+    auto* kern = decode_tiles_kernel<ColT, CodeT, kPieces, 512>;
+    if constexpr (sizeof(CodeT) == 1)
+        if (wide) kern = decode_tiles_kernel<ColT, CodeT, kPieces, 1024>;
     {   // with the static part more than 64 KiB
-        static cer::LdsGrant<3> grant;
-        const void* kern = pieces == 1 ? (const void*)decode_tiles_kernel<ColT, CodeT, 1>
-                                         : (pieces == 2 ? (const void*)decode_tiles_kernel<ColT, CodeT, 2> : (const void*)decode_tiles_kernel<ColT, CodeT, 3>);
-        const hipError_t e = grant.ensure(pieces - 1, kern, 56 * 1024);
+        static cer::LdsGrant<2> grant;
+        const hipError_t e = grant.ensure(wide, (const void*)kern, 133 * 1024);
         if (e != hipSuccess) return e;
     }
-    const ColT* colI = static_cast<const ColT*>(v.colI);
+    return launch_kernel(kern, grid, dim3(wide ? 1024 : 512), lds, s, static_cast<const ColT*>(v.colI), a, v.m, pitch, plane, out);
+}
+
+// The pieces of the values, or (pieces 0) their ranks.
+template <typename ColT>
+hipError_t decode_tiles_by(const DeviceView& v, int pieces, uint16_t* out, int64_t pitch, int64_t plane, hipStream_t s) {
+    if (v.rank_tab) {
+        switch (pieces) {
+            case 0: return launch_decode_tiles<ColT, uint8_t, 0>(v, out, pitch, plane, s);
+            case 1: return launch_decode_tiles<ColT, uint8_t, 1>(v, out, pitch, plane, s);
+            case 2: return launch_decode_tiles<ColT, uint8_t, 2>(v, out, pitch, plane, s);
+            default: return launch_decode_tiles<ColT, uint8_t, 3>(v, out, pitch, plane, s);
+        }
+    }
     switch (pieces) {
-        case 1: return launch_kernel(decode_tiles_kernel<ColT, CodeT, 1>, grid, dim3(512), lds, s, colI, a, v.m, pitch, plane, out);
-        case 2: return launch_kernel(decode_tiles_kernel<ColT, CodeT, 2>, grid, dim3(512), lds, s, colI, a, v.m, pitch, plane, out);
-        default: return launch_kernel(decode_tiles_kernel<ColT, CodeT, 3>, grid, dim3(512), lds, s, colI, a, v.m, pitch, plane, out);
+        case 1: return launch_decode_tiles<ColT, float, 1>(v, out, pitch, plane, s);
+        case 2: return launch_decode_tiles<ColT, float, 2>(v, out, pitch, plane, s);
+        default: return launch_decode_tiles<ColT, float, 3>(v, out, pitch, plane, s);
+    }
+}
+int decode_tiles(const DeviceView& v, int pieces, uint16_t* out, int64_t pitch, int64_t plane, void* stream) {
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    switch (v.colI_bits) {
+        case 8: return (int)decode_tiles_by<uint8_t>(v, pieces, out, pitch, plane, s);
+        case 16: return (int)decode_tiles_by<uint16_t>(v, pieces, out, pitch, plane, s);
+        default: return (int)decode_tiles_by<uint32_t>(v, pieces, out, pitch, plane, s);
     }
 }
 }  // namespace
@@ -1651,13 +1707,11 @@ int decode_device(const DeviceView& v, float* W, void* stream) {
 }
 
 int decode_pieces(const DeviceView& v, uint16_t* W, int64_t pitch, int64_t plane, void* stream) {
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool ranks = v.rank_tab != nullptr;
-    switch (v.colI_bits) {
-        case 8: return (int)(ranks ? launch_decode_tiles<uint8_t, uint8_t>(v, W, pitch, plane, s) : launch_decode_tiles<uint8_t, float>(v, W, pitch, plane, s));
-        case 16: return (int)(ranks ? launch_decode_tiles<uint16_t, uint8_t>(v, W, pitch, plane, s) : launch_decode_tiles<uint16_t, float>(v, W, pitch, plane, s));
-        default: return (int)(ranks ? launch_decode_tiles<uint32_t, uint8_t>(v, W, pitch, plane, s) : launch_decode_tiles<uint32_t, float>(v, W, pitch, plane, s));
-    }
+    return decode_tiles(v, v.grid.scale != 0.f ? 2 : v.pieces, W, pitch, plane, stream);
+}
+
+int decode_ranks(const DeviceView& v, uint8_t* W, int64_t pitch, void* stream) {
+    return decode_tiles(v, 0, reinterpret_cast<uint16_t*>(W), pitch, 0, stream);
 }
 
 int quantize_device(const float* W, int64_t count, int32_t bits, uint8_t* codes, float* Wq, float* codebook_out,

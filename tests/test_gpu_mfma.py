@@ -219,3 +219,38 @@ def test_sums_of_many_parts_are_rounded_once(pieces, m, n, L, fused):
     B.cer_free(h)
     want = W.astype(np.float64) @ X.astype(np.float64)
     assert np.linalg.norm(Y.cpu().numpy() - want) <= 2 / 3 * 2.0 ** -24 * np.linalg.norm(want)
+
+
+# The decoder's ranks and what the product looks up for them, both tiles, and wide batches where pieces take their place: rows of more columns than
+# a segment of eight or four rows holds (6144, 12288; one segment of 33792 behind them), two rows per workgroup, remainders of 32 columns and rows,
+# all 256 ranks.
+def _grid(K):
+    return (np.arange(K) - K // 2).astype(np.float32) / np.float32(K / 2.0)
+
+
+@pytest.mark.parametrize("case", [
+    ("three", 1300, 200, 100), ("three", 1300, 200, 1897), ("grid113", 2200, 700, 128), ("grid113", 2200, 700, 1289), ("two", 33, 500, 24),
+    ("two", 33, 500, 2025), ("any256", 290, 777, 66), ("grid113", 37, 6144, 40), ("any256", 67, 6145, 33), ("three", 1100, 6177, 34),
+    ("two", 600, 12288, 5), ("any256", 520, 12289, 20), ("two", 5, 33792, 20), ("grid113", 3, 33793, 70), ("one", 19, 6200, 35),
+    ("one", 9, 12300, 35), ("any256", 515, 70001, 3)])
+def test_ranks_and_the_lines_of_their_choice(case):
+    name, m, n, L = case
+    rng = np.random.default_rng(m * L)
+    cb = {"grid113": _grid(113), "any256": np.sort(rng.standard_normal(256)).astype(np.float32)}.get(name, CODEBOOKS.get(name))
+    p = np.full(len(cb), 0.5 / (len(cb) - 1))
+    p[len(cb) // 2] = 0.5
+    W = rng.choice(cb, size=(m, n), p=p).astype(np.float32)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    Y = _product(W, cb, X, "cser" if m % 2 else "cer")
+    want = W.astype(np.float64) @ X.astype(np.float64)
+    assert (np.abs(Y - want) <= 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64))).all()
+    X[n // 3, 1], X[n - 1, 0] = np.inf, np.nan  # the products in binary32 take their weights from the ranks as well
+    Y = _product(W, cb, X, "cser" if m % 2 else "cer")
+    with np.errstate(invalid="ignore"):
+        want = W.astype(np.float64) @ X.astype(np.float64)
+        scale = np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64)
+    assert (np.isnan(Y) == np.isnan(want)).all() and np.isnan(Y[:, 0]).all()
+    inf = np.isinf(want)
+    assert (Y[inf] == want[inf]).all()
+    fine = np.isfinite(want)
+    assert (np.abs(Y[fine] - want[fine]) <= 1e-6 * scale[fine]).all()
