@@ -52,18 +52,24 @@ struct FrontState {
     uint32_t pos_of[kCodes];           // rank -> codebook position
 };
 
-// What the host needs to know, in pinned host memory: first the sizes, before it can allocate the handle (`ready` last);
-// the values with the handle's arrays (nobody waits for them on their way).
+// What the host needs to know, in pinned host memory: first what the handle's memory and the emitter are chosen by, as soon as the values are
+// ranked; then the sizes that the rows add up to; the values with the handle's arrays (read when the stream has been waited for).  Every word
+// says for itself that it is there (kWritten), so that nothing orders them: a release for the host writes the L2 back (4096 x 9216, 7 bits, 3 us).
+constexpr unsigned long long kWritten = 1ull << 63;
 struct FrontResult {
-    uint32_t flags, K, Kp;
-    uint32_t max_row_groups;
-    uint32_t max_row_nnz;  // indexed elements of the longest row
-    unsigned long long nnz, G, nonempty;
-    uint32_t ready;
+    unsigned long long early[2];   // longest row's indexed elements | K << 32 | Kp << 41 | flags << 50; indexed elements
+    unsigned long long totals[3];  // groups; non-empty ones; largest group count of a row | flags << 50
     unsigned long long count[kCodes];
     float codebook[kCodes];
     float omega[kCodes];
 };
+struct FrontSizes {
+    uint32_t flags, K, Kp, longest;
+    unsigned long long nnz;
+};
+__device__ __forceinline__ void tell(unsigned long long* word, unsigned long long value) {
+    __hip_atomic_store(word, value | kWritten, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // LDS traffic of one wave is ordered; this only keeps the compiler from moving accesses across.
 __device__ __forceinline__ void wave_lds_sync() {
@@ -85,9 +91,14 @@ __device__ __forceinline__ void range_take(float w, float& lo, float& hi, uint32
 
 // The global histogram is gathered in kHistParts copies (workgroups of codes_kernel add theirs to one of them each), cleared
 // by the kernel in front.
+// Behind them, in as many copies, lies how often a value occurs in a row at least.
 constexpr int kHistParts = 16;
+__device__ __forceinline__ uint32_t* least_of(unsigned long long* hist) { return reinterpret_cast<uint32_t*>(hist + kHistParts * kCodes); }
 __device__ __forceinline__ void clear_histogram(unsigned long long* hist, FrontState* st) {  // one workgroup of 256 threads
-    for (int i = 0; i < kHistParts; ++i) hist[i * kCodes + threadIdx.x] = 0ull;
+    for (int i = 0; i < kHistParts; ++i) {
+        hist[i * kCodes + threadIdx.x] = 0ull;
+        least_of(hist)[i * kCodes + threadIdx.x] = 0xFFFFFFFFu;
+    }
     if (threadIdx.x == 0) {
         st->flags = 0;
         st->done = 0;
@@ -303,6 +314,7 @@ __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W,
     c.hpos = s_hpos;
     bool missing = false;
     unsigned long long total_t = 0;  // occurrences of codebook position t in this workgroup's rows
+    uint32_t least_t = 0xFFFFFFFFu;  // ... in the row that has fewest
     for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
         const float* row = W + r * row_len;
         uint8_t* crow = codes ? codes + r * row_len : nullptr;
@@ -366,10 +378,15 @@ __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W,
             }
             cnt[r * kCodes + t] = sum;
             total_t += sum;
+            least_t = min(least_t, sum);
             __syncthreads();
         }
     }
-    if (cnt && total_t) atomicAdd(&hist[(blockIdx.x & (kHistParts - 1)) * kCodes + t], total_t);
+    if (cnt && t < c.K) {
+        const uint32_t at = (blockIdx.x & (kHistParts - 1)) * kCodes + t;
+        if (total_t) atomicAdd(&hist[at], total_t);
+        atomicMin(&least_of(hist)[at], least_t);
+    }
     if (__syncthreads_or(missing) && t == 0) atomicOr(&st->flags, kFlagMissing);
 }
 
@@ -382,8 +399,11 @@ __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ W,
 // (Section III-A, step 1).  Each thread finds its own value's position by counting who comes before it.
 //
 // scan: exclusive prefix sums of the rows' groups and indexed elements (m + 1 entries {groups, elements}), the number of
-// non-empty groups and the largest group count of a row; kScanRows consecutive rows per thread and round.  The sizes go to
-// the host from here.
+// non-empty groups and the largest group count of a row; kScanRows consecutive rows per thread and round.
+//
+// One workgroup more has no rows: it tells the host what follows from the values' counts alone -- the number of indexed elements, of values, and the
+// longest row's elements: all but the most frequent value's, of which codes_kernel leaves the least count (looked for here, in one count per row, it
+// took 4 us of 4096 rows).
 // ------------------------------------------------------------------------------------------------
 constexpr int kScanRows = 4;
 
@@ -418,11 +438,11 @@ __device__ __forceinline__ uint32_t wave_largest(uint32_t x) {  // in the last l
 __device__ void scan_rows(const unsigned long long* rowGN, int64_t m, uint2* __restrict__ rowStart, FrontState* __restrict__ st,
                           FrontResult* __restrict__ out) {
     __shared__ unsigned long long s_g[16], s_n[16], s_p[16];
-    __shared__ uint32_t s_mx[16], s_ml[16];
+    __shared__ uint32_t s_mx[16];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     unsigned long long carry_g = 0, carry_n = 0, my_p = 0;
-    uint32_t my_mx = 0, my_ml = 0;
-    const uint32_t flags = st->flags, K = st->K, Kp = st->Kp;  // on their way with the first rows
+    uint32_t my_mx = 0;
+    const uint32_t flags = st->flags;  // on its way with the first rows
     for (int64_t base = 0; base < m; base += 1024 * kScanRows) {
         const int64_t r0 = base + (int64_t)t * kScanRows;
         uint2 v[kScanRows];
@@ -437,7 +457,6 @@ __device__ void scan_rows(const unsigned long long* rowGN, int64_t m, uint2* __r
             my_p += v[k].x >> 16;
             v[k].x &= 0xFFFFu;
             my_mx = max(my_mx, v[k].x);
-            my_ml = max(my_ml, v[k].y);
             g += v[k].x;
             nn += v[k].y;
         }
@@ -468,33 +487,24 @@ __device__ void scan_rows(const unsigned long long* rowGN, int64_t m, uint2* __r
     }
     my_p = wave_scan64(my_p);
     my_mx = wave_largest(my_mx);
-    my_ml = wave_largest(my_ml);
     if (lane == 63) {
         s_p[wave] = my_p;
         s_mx[wave] = my_mx;
-        s_ml[wave] = my_ml;
     }
     __syncthreads();
     if (t == 0) {
         unsigned long long p = 0;
-        uint32_t mx = 0, ml = 0;
+        uint32_t mx = 0;
         for (int w = 0; w < 16; ++w) {
             p += s_p[w];
             mx = max(mx, s_mx[w]);
-            ml = max(ml, s_ml[w]);
         }
         rowStart[m] = make_uint2((uint32_t)carry_g, (uint32_t)carry_n);
         // the product kernels address colI and OmegaPtr with 32-bit offsets and read ahead of a row's end
         const unsigned long long limit = 0xFFFFFFFFull - 65536;
-        out->flags = flags | (carry_g > limit || carry_n > limit ? kFlagTooLarge : 0u);
-        out->K = K;
-        out->Kp = Kp;
-        out->max_row_groups = mx;
-        out->max_row_nnz = ml;
-        out->nnz = carry_n;
-        out->G = carry_g;
-        out->nonempty = p;
-        __hip_atomic_store(&out->ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        tell(&out->totals[0], carry_g);
+        tell(&out->totals[1], p);
+        tell(&out->totals[2], mx | (unsigned long long)(flags | (carry_g > limit || carry_n > limit ? kFlagTooLarge : 0u)) << 50);
     }
 }
 
@@ -506,13 +516,14 @@ __device__ void scan_rows(const unsigned long long* rowGN, int64_t m, uint2* __r
 constexpr int64_t kFewRows = 2048;
 template <int kRows>
 __global__ __launch_bounds__(1024) void row_layout_kernel(const uint32_t* __restrict__ cnt, const unsigned long long* __restrict__ hist,
-                                                          int64_t m, int cser, FrontState* __restrict__ st, unsigned long long* __restrict__ rowGN,
+                                                          int64_t m, int64_t n, int cser, FrontState* __restrict__ st, unsigned long long* __restrict__ rowGN,
                                                           uint2* __restrict__ rowStart, FrontResult* __restrict__ out) {
     __shared__ unsigned long long s_sum[4][kCodes];
     __shared__ unsigned long long s_h[kCodes];
     __shared__ uint32_t s_rank[kCodes];
     __shared__ uint32_t s_last;
     const uint32_t t = threadIdx.x, lane = t & 63u, pos = t & 255u, sub = t >> 8, K = st->K;
+    const bool tells = blockIdx.x == gridDim.x - 1u;
     // the rows' histograms are on their way while the values are ranked
     const int64_t r0 = ((int64_t)blockIdx.x * 16 + (t >> 6)) * kRows;
     uint32_t c4[kRows][kCodes / kWave];
@@ -554,6 +565,21 @@ __global__ __launch_bounds__(1024) void row_layout_kernel(const uint32_t* __rest
         }
     }
     if (blockIdx.x == 0 && t == 0) st->Kp = (uint32_t)occurring;
+    if (tells) {
+        if (sub == 0 && key >> 8 != 0ull && s_rank[pos] == 0u) {
+            s_last = pos;
+            s_h[0] = key >> 8;
+        }
+        __syncthreads();
+        if (t < kWave) {
+            const uint32_t* least = reinterpret_cast<const uint32_t*>(hist + kHistParts * kCodes) + (occurring ? s_last : 0u);
+            const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)wave_largest(~least[(t & (kHistParts - 1)) * kCodes]), 63);
+            if (t != 0) return;
+            tell(&out->early[0], ((uint32_t)n - ~all) | (unsigned long long)K << 32 | (unsigned long long)(uint32_t)occurring << 41 | (unsigned long long)st->flags << 50);
+            tell(&out->early[1], (unsigned long long)(m * n) - (occurring ? s_h[0] : 0ull));
+        }
+        return;
+    }
     __syncthreads();
     uint32_t rank[kCodes / kWave];
 #pragma unroll
@@ -578,7 +604,7 @@ __global__ __launch_bounds__(1024) void row_layout_kernel(const uint32_t* __rest
     // barrier and takes what the others have: one release and one acquire per workgroup.  (Each release writes an L2 back: 4096
     // rows 16 -> 18 us against relaxed accesses past the caches, which nothing orders; a fence per wave took 80 us.)
     __syncthreads();
-    if (t == 0) s_last = __hip_atomic_fetch_add(&st->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u ? 1u : 0u;
+    if (t == 0) s_last = __hip_atomic_fetch_add(&st->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 2u ? 1u : 0u;
     __syncthreads();
     if (s_last) scan_rows(rowGN, m, rowStart, st, out);
 }
@@ -627,10 +653,11 @@ struct EmitTarget {
     int32_t tab_shift;  // rank table: 1 << tab_shift words per row; 0: none
     int32_t ngaps;
     size_t gap_begin[8], gap_end[8];
+    uint32_t gap_group[8];  // bytes per group that stand between begin and the gap
 };
 
 // What one workgroup of an emitter does besides the rows: Omega, the gaps, and the values for the host.
-__device__ __forceinline__ void emit_values(const FrontState* __restrict__ st, const EmitTarget& to, FrontResult* __restrict__ out) {
+__device__ __forceinline__ void emit_values(const FrontState* __restrict__ st, const EmitTarget& to, uint32_t groups, FrontResult* __restrict__ out) {
     for (uint32_t t = threadIdx.x; t < kCodes; t += blockDim.x) {
         if (t < st->Kp) {
             const float w = st->omega[t];
@@ -640,8 +667,11 @@ __device__ __forceinline__ void emit_values(const FrontState* __restrict__ st, c
         }
         if (t < st->K) out->codebook[t] = st->codebook[t];
     }
-    for (int g = 0; g < to.ngaps; ++g)
-        for (size_t o = to.gap_begin[g] + threadIdx.x; o < to.gap_end[g]; o += blockDim.x) to.base[o] = 0;
+    for (int g = 0; g < to.ngaps; ++g) {
+        // (behind the groups there may be room for more of them, which nobody reads but for the first bytes)
+        const size_t begin = to.gap_begin[g] + (size_t)to.gap_group[g] * groups, end = to.gap_group[g] ? min(to.gap_end[g], begin + 512) : to.gap_end[g];
+        for (size_t o = begin + threadIdx.x; o < end; o += blockDim.x) to.base[o] = 0;
+    }
 }
 
 // What a wave needs to know of a row: where its groups and indices begin and end, and its values' counts by rank (64 i + lane).
@@ -737,7 +767,7 @@ __global__ __launch_bounds__(64) void emit_sorted_kernel(const uint8_t* __restri
     // positions rounded up to eight
     extern __shared__ __align__(16) unsigned char s_row[];
     if (blockIdx.x == gridDim.x - 1) {
-        emit_values(st, to, out);
+        emit_values(st, to, rowStart[m].x, out);
         return;
     }
     const uint32_t lane = threadIdx.x, eights = (positions + 7u) & ~7u;
@@ -901,7 +931,7 @@ __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ c
     __shared__ uint32_t s_stage[4][kEmitStage];  // (column << 8) | rank of the columns waiting for the scatter
     __shared__ unsigned long long s_marks[4][kCodes];  // per rank: the lanes of the current batch that hold it
     if (blockIdx.x == gridDim.x - 1) {
-        emit_values(st, to, out);
+        emit_values(st, to, rowStart[m].x, out);
         return;
     }
     ColT* colI = reinterpret_cast<ColT*>(to.base);
@@ -1497,29 +1527,48 @@ struct Mailbox {
             if (e != hipSuccess) return e;
             p = static_cast<FrontResult*>(q);
         }
-        __atomic_store_n(&p->ready, 0u, __ATOMIC_RELEASE);
+        for (unsigned long long* word : {&p->early[0], &p->early[1], &p->totals[0], &p->totals[1], &p->totals[2]}) __atomic_store_n(word, 0ull, __ATOMIC_RELEASE);
         return hipSuccess;
     }
-    // Returns when the result is there.  A copy and a synchronisation of the stream take 30 us more than looking at the
-    // word that the kernel writes last; the stream is asked now and then, so that a failed launch ends the wait.
-    hipError_t wait(hipStream_t s) {
-        for (uint32_t spins = 1;; ++spins) {
-            if (__atomic_load_n(&p->ready, __ATOMIC_ACQUIRE)) break;
+    // Returns when the words are there.  A copy and a synchronisation of the stream take 30 us more than looking at them; the stream is asked
+    // now and then, so that a failed launch ends the wait.
+    template <size_t kWords>
+    hipError_t wait(hipStream_t s, const unsigned long long (&words)[kWords]) {
+        auto there = [&] {
+            for (size_t i = 0; i < kWords; ++i)
+                if (!__atomic_load_n(&words[i], __ATOMIC_ACQUIRE)) return false;
+            return true;
+        };
+        for (uint32_t spins = 1; !there(); ++spins) {
             if (spins % 8192u == 0) {
                 hipError_t e = spins > (1u << 20) ? hipStreamSynchronize(s) : hipStreamQuery(s);
                 if (e == hipErrorNotReady) {
                     (void)hipGetLastError();
                     continue;
                 }
-                if (e == hipSuccess && !__atomic_load_n(&p->ready, __ATOMIC_ACQUIRE)) e = hipErrorLaunchFailure;
+                if (e == hipSuccess && !there()) e = hipErrorLaunchFailure;
                 if (e != hipSuccess) return e;
                 break;
             }
             __builtin_ia32_pause();
         }
-        busy = false;
         return hipSuccess;
     }
+    hipError_t wait_sizes(hipStream_t s, FrontSizes* sizes) {
+        const hipError_t e = wait(s, p->early);
+        const unsigned long long q = p->early[0];
+        *sizes = FrontSizes{(uint32_t)(q >> 50) & 0xFu, (uint32_t)(q >> 32) & 0x1FFu, (uint32_t)(q >> 41) & 0x1FFu, (uint32_t)q, p->early[1] & ~kWritten};
+        return e;
+    }
+    hipError_t wait_totals(hipStream_t s) {  // the last that a kernel writes before the emitter
+        const hipError_t e = wait(s, p->totals);
+        if (e == hipSuccess) busy = false;
+        return e;
+    }
+    unsigned long long groups() const { return p->totals[0] & ~kWritten; }
+    unsigned long long nonempty() const { return p->totals[1] & ~kWritten; }
+    uint32_t max_row_groups() const { return (uint32_t)p->totals[2]; }
+    uint32_t flags() const { return (uint32_t)(p->totals[2] >> 50) & 0xFu; }
 };
 
 int flags_to_error(uint32_t flags) {
@@ -1571,11 +1620,11 @@ int64_t sorted_waves(size_t lds) {
 
 template <typename ColT>
 hipError_t launch_emit(hipStream_t s, const uint8_t* codes, const uint32_t* cnt, const uint2* rowStart, const FrontState* st,
-                       int64_t m, int64_t n, int cser, int sparse, const EmitTarget& to, FrontResult* out) {
+                       int64_t m, int64_t n, int cser, int sparse, const EmitTarget& to, const FrontSizes& sizes, FrontResult* out) {
     if constexpr (sizeof(ColT) == 2) {
-        if (const size_t lds = sorted_lds(m, n, out->K, out->max_row_nnz, out->nnz))
+        if (const size_t lds = sorted_lds(m, n, sizes.K, sizes.longest, sizes.nnz))
             return cer::launch_kernel(n <= 1024 * kSortedPieces ? emit_sorted_kernel<kSortedPieces> : emit_sorted_kernel<0>, dim3((unsigned)std::min<int64_t>(m, sorted_waves(lds)) + 1u), dim3(64), lds, s, codes, cnt, rowStart, st, m, (uint32_t)n, cser,
-                                      out->K, emit_stage_bytes(out->max_row_nnz), to, out);
+                                      sizes.K, emit_stage_bytes(sizes.longest), to, out);
     }
     // rank < K <= 256, so OmegaI is always one byte wide here
     return cer::launch_kernel(emit_kernel<ColT, uint8_t>, dim3((unsigned)((m + 3) / 4 + 1)), dim3(256), 0, s, codes, cnt, rowStart,
@@ -1746,11 +1795,11 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     HIP_TRY(hipGetDevice(&dev));
 
     // one stream-ordered temporary: [state][codes: N bytes][per-row histograms][{groups, elements} per row: m][their prefix
-    // sums: m + 1][partial histograms][partial ranges]
+    // sums: m + 1][partial histograms and least counts][partial ranges]
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t off_codes = up(sizeof(FrontState)), off_cnt = off_codes + up((size_t)N);
     const size_t off_gn = off_cnt + up((size_t)m * kCodes * 4), off_start = off_gn + up((size_t)m * 8);
-    const size_t off_hist = off_start + up((size_t)(m + 1) * 8), off_part = off_hist + (size_t)kHistParts * kCodes * 8;
+    const size_t off_hist = off_start + up((size_t)(m + 1) * 8), off_part = off_hist + (size_t)kHistParts * kCodes * (8 + 4);
     Mailbox box;
     HIP_TRY(box.get());
     DeviceBuf tmp;
@@ -1767,49 +1816,59 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     if (rc != CER_OK) return rc;
     box.busy = true;
     const int64_t rows_each = m > kFewRows ? 4 : 1;
-    HIP_TRY(launch_kernel(rows_each > 1 ? row_layout_kernel<4> : row_layout_kernel<1>, dim3((unsigned)((m + 16 * rows_each - 1) / (16 * rows_each))),
-                          dim3(1024), 0, s, cnt_d, hist, m, cser ? 1 : 0, sd, rowGN, rowStart, box.p));
-    HIP_TRY(box.wait(s));
-    const FrontResult& h = *box.p;
-    rc = flags_to_error(h.flags);
-    if (rc != CER_OK) return rc;
-
-    // sizes are known: the handle's own allocation, filled in place by the emit kernel
+    HIP_TRY(launch_kernel(rows_each > 1 ? row_layout_kernel<4> : row_layout_kernel<1>, dim3((unsigned)((m + 16 * rows_each - 1) / (16 * rows_each)) + 1u),
+                          dim3(1024), 0, s, cnt_d, hist, m, n, cser ? 1 : 0, sd, rowGN, rowStart, box.p));
+    // what can be done before the sizes are here
     auto A = std::make_shared<HostMatrix>();
     A->cser = cser;
     A->m = m;
     A->n = n;
-    A->K = (int32_t)h.Kp;
-    A->nnz = (int64_t)h.nnz;
-    A->G = (int64_t)h.G;
-    A->nonempty_groups = (int64_t)h.nonempty;
-    A->max_row_groups = (int64_t)h.max_row_groups;
-    // the index arrays stay on the device until somebody asks for them on the host
-    A->colI.len = A->nnz;
     A->colI.bits = min_index_bits(n > 0 ? (uint64_t)(n - 1) : 0);
-    A->omegaPtr.len = A->G + 1;
-    A->omegaPtr.bits = min_index_bits((uint64_t)A->nnz);
     A->rowPtr.len = m + 1;
-    A->rowPtr.bits = min_index_bits((uint64_t)A->G);
-    if (cser) {
-        A->omegaI.len = A->G;
-        A->omegaI.bits = min_index_bits(A->K > 0 ? (uint64_t)(A->K - 1) : 0);
-    }
-    A->arrays_on_host.store(false);
-    const size_t colI_bytes = (size_t)A->nnz * (size_t)(A->colI.bits / 8);
-    const size_t oi_bytes = cser ? (size_t)A->G * (size_t)(A->omegaI.bits / 8) : 0;
-    const DeviceLayout l = DeviceLayout::make(colI_bytes, A->G, m, oi_bytes, A->K);
-    A->omega.resize(h.Kp);
-    A->count.resize(h.Kp);
+    A->omega.reserve(kCodes);
+    A->count.reserve(kCodes);
+    A->arrays_on_host.store(false);  // the index arrays stay on the device until somebody asks for them on the host
     std::unique_ptr<cer_matrix, void (*)(cer_handle_t*)> hnd(new cer_matrix(), cer_free);
     hnd->host = A;
     if (s) hnd->off_null_stream.store(true, std::memory_order_relaxed);
-    void* base = nullptr;
-    HIP_TRY((hipError_t)handle_alloc(&base, l.total, s));
-    hnd->d_base = base;
-
     EmitTarget to;
     std::memset(&to, 0, sizeof to);
+
+    FrontSizes sizes;
+    HIP_TRY(box.wait_sizes(s, &sizes));
+    const FrontResult& h = *box.p;
+    rc = flags_to_error(sizes.flags);
+    // The emitter is launched while the rows are added up -- the host's and the launch's time were between the two: compressed and decoded 256 x 512, 5
+    // bits, 53 -> 49 us, 1024 x 2048, 6 bits, 61.7 -> 58.9, 4096 x 9216, 7 bits, 182 -> 177 --, with room for as many groups as there may be: a row has at
+    // most one per value but one.  Where that room could be more than half of all other parts (few indexed elements per value and
+    // row), their number is waited for.
+    const uint64_t limit = 0xFFFFFFFFull - 65536;
+    uint64_t room = (uint64_t)m * (sizes.Kp > 0 ? sizes.Kp - 1u : 0u);
+    if (cser) room = std::min<uint64_t>(room, sizes.nnz);
+    const size_t colI_bytes = (size_t)sizes.nnz * (size_t)(A->colI.bits / 8), oi_width = cser ? 1 : 0;  // (ranks below 256)
+    auto layout = [&] { return DeviceLayout::make(colI_bytes, (int64_t)room, m, (size_t)room * oi_width, (int32_t)sizes.Kp); };
+    bool known = rc != CER_OK || sizes.nnz > limit || room > limit;
+    DeviceLayout l;
+    if (!known) {
+        l = layout();
+        known = (l.total - room * 4) / 2 < room * 4;
+    }
+    if (known) {
+        HIP_TRY(box.wait_totals(s));
+        if (rc == CER_OK) rc = flags_to_error(box.flags());
+        if (rc != CER_OK) return rc;
+        room = box.groups();
+        l = layout();
+    }
+
+    // the handle's own allocation, filled in place by the emit kernel
+    void* base = nullptr;
+    if (const int e = handle_alloc(&base, l.total, s)) {
+        (void)box.wait_totals(s);
+        HIP_TRY((hipError_t)e);
+    }
+    hnd->d_base = base;
+
     to.base = static_cast<unsigned char*>(base);
     to.off_optr = l.off_optr;
     to.off_rptr = l.off_rptr;
@@ -1819,39 +1878,55 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     to.off_tab = l.off_tab;
     to.tab_shift = l.tab_shift;
     // the read-ahead padding and the gaps are cleared; the arrays themselves are written completely
-    auto gap = [&](size_t begin, size_t end) {
+    auto gap = [&](size_t begin, size_t end, size_t per_group = 0) {
         to.gap_begin[to.ngaps] = begin;
+        to.gap_group[to.ngaps] = (uint32_t)per_group;
         to.gap_end[to.ngaps++] = end;
     };
     gap(colI_bytes, l.off_optr);
-    gap(l.off_optr + (size_t)(h.G + 1) * 4, l.off_rptr);
+    gap(l.off_optr + 4, l.off_rptr, 4);
     gap(l.off_rptr + (size_t)(m + 1) * 4, l.off_oi);
-    gap(l.off_oi + oi_bytes, l.off_om);
-    gap(l.off_om + (size_t)h.Kp * 4, l.off_ri);
+    gap(l.off_oi, l.off_om, oi_width);
+    gap(l.off_om + (size_t)sizes.Kp * 4, l.off_ri);
     gap(l.off_ri + (size_t)(m + 1) * 8, l.off_tab);
     gap(l.off_tab + (l.tab_shift ? ((size_t)m << l.tab_shift) * 4 : 0), l.total);
     const int cs = cser ? 1 : 0;
     // with fewer than half of the elements indexed emit_kernel packs them in LDS before it scatters them
-    const int sp = mostly_implicit(h.nnz, m, n) ? 1 : 0;
+    const int sp = mostly_implicit((int64_t)sizes.nnz, m, n) ? 1 : 0;
     hipError_t e = hipSuccess;
     switch (hnd->host->colI.bits) {
-        case 8: e = launch_emit<uint8_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to, box.p); break;
-        case 16: e = launch_emit<uint16_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to, box.p); break;
-        default: e = launch_emit<uint32_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to, box.p);
+        case 8: e = launch_emit<uint8_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to, sizes, box.p); break;
+        case 16: e = launch_emit<uint16_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to, sizes, box.p); break;
+        default: e = launch_emit<uint32_t>(s, codes_d, cnt_d, rowStart, sd, m, n, cs, sp, to, sizes, box.p);
     }
     box.busy = true;
     HIP_TRY(e);
+    A->K = (int32_t)sizes.Kp;
+    A->nnz = (int64_t)sizes.nnz;
+    A->colI.len = A->nnz;
+    A->omegaPtr.bits = min_index_bits((uint64_t)A->nnz);
+    if (cser) A->omegaI.bits = min_index_bits(A->K > 0 ? (uint64_t)(A->K - 1) : 0);
+    A->omega.resize(sizes.Kp);
+    A->count.resize(sizes.Kp);
     HIP_TRY(hipStreamSynchronize(s));  // the handle is complete for every stream; errors surface here
     box.busy = false;
-    std::copy_n(h.omega, h.Kp, A->omega.begin());
-    std::copy_n(h.count, h.Kp, A->count.begin());
+    if (!known && (rc = flags_to_error(box.flags())) != CER_OK) return rc;
+    A->G = (int64_t)box.groups();
+    A->nonempty_groups = (int64_t)box.nonempty();
+    A->max_row_groups = (int64_t)box.max_row_groups();
+    A->omegaPtr.len = A->G + 1;
+    A->rowPtr.bits = min_index_bits((uint64_t)A->G);
+    if (cser) A->omegaI.len = A->G;
+    l.omegaI_bytes = (size_t)A->G * oi_width;
+    std::copy_n(h.omega, sizes.Kp, A->omega.begin());
+    std::copy_n(h.count, sizes.Kp, A->count.begin());
     bind_device(hnd.get(), dev, base, l);
-    hnd->view.longest_row = h.max_row_nnz;
-    if (K_out) *K_out = (int32_t)h.K;
-    if (codebook_out) std::memcpy(codebook_out, h.codebook, (size_t)h.K * 4);
+    hnd->view.longest_row = sizes.longest;
+    if (K_out) *K_out = (int32_t)sizes.K;
+    if (codebook_out) std::memcpy(codebook_out, h.codebook, (size_t)sizes.K * 4);
     // rows of unequal length: the batched product wants them ordered (and the longest in parts); the row starts
     // come back from the device only when the longest row says that the table will be built
-    if (row_schedule_wanted((uint64_t)h.nnz, (uint64_t)m, (uint64_t)h.max_row_nnz)) {
+    if (row_schedule_wanted((uint64_t)sizes.nnz, (uint64_t)m, (uint64_t)sizes.longest)) {
         std::vector<uint32_t> info((size_t)(m + 1) * 2);
         HIP_TRY(hipMemcpy(info.data(), to.base + l.off_ri, info.size() * 4, hipMemcpyDeviceToHost));
         std::vector<uint64_t> start((size_t)m + 1);

@@ -1,0 +1,59 @@
+"""Compressing on the GPU: the emitter starts before the number of groups is known (csrc/frontend.hip), with room for one group per value and row, or
+waits for it where that room would be large.  Both ways leave the arrays of the host encoder, and products that read behind their ends."""
+import numpy as np
+import pytest
+
+from paper_1805_10692_amd import binding as B
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+# (rows, columns, values, share of the most frequent one): many groups per row, hardly any (the number of groups is waited for), rows in one
+# and in several workgroups of either row_layout_kernel, one value, two values, one row
+@pytest.mark.parametrize("fmt", ["cer", "cser"])
+@pytest.mark.parametrize("case", [(300, 700, 16, 0.5), (17, 300, 256, 0.999), (1000, 200, 256, 0.99), (2049, 520, 97, 0.3), (4100, 64, 5, 0.9),
+                                  (1, 5000, 200, 0.2), (33, 40, 1, 1.0), (64, 1, 2, 0.5), (16, 70000, 3, 0.97)])
+def test_arrays_and_products(case, fmt):
+    m, n, K, p0 = case
+    rng = np.random.default_rng(m * n + K)
+    cb = (np.arange(K) - K // 2).astype(np.float32)
+    p = np.full(K, (1.0 - p0) / max(K - 1, 1))
+    p[K // 2] = p0 if K > 1 else 1.0
+    W = rng.choice(cb, size=(m, n), p=p).astype(np.float32)
+    W[m // 2] = cb[K // 2]  # a row without indexed elements
+    if m > 2 and K > 2:
+        W[0, :] = cb[0]     # and one that is all indexed, with a single group
+    # memory of an earlier handle, full of something else
+    B.cer_free(B.cer_encode_device(torch.full((m, n), 3.0, device="cuda"), m, n, np.array([3.0], np.float32), fmt))
+    d = B.cer_encode_device(torch.from_numpy(W).cuda(), m, n, cb, fmt)
+    h = (B.cer_encode if fmt == "cer" else B.cser_encode)(W, cb)
+    assert B.cer_get_dims(d) == B.cer_get_dims(h) and B.cer_storage_bits(d) == B.cer_storage_bits(h)
+    for which in range(5 if fmt == "cser" else 4):
+        assert np.array_equal(B.cer_get_array(d, which), B.cer_get_array(h, which))
+    out = torch.empty((m, n), device="cuda")
+    B.cer_decode_device(d, out)
+    assert np.array_equal(out.cpu().numpy(), W)
+    c = B.cer_clone_device(d)
+    for L in (1, 3, 70):
+        X = torch.from_numpy(rng.standard_normal((n, L)).astype(np.float32)).cuda()
+        Y = [torch.empty((m, L), device="cuda") for _ in range(3)]
+        for handle, y in zip((d, h, c), Y):
+            (B.cer_matmul if fmt == "cer" else B.cser_matmul)(handle, X, y, L)
+        torch.cuda.synchronize()
+        assert torch.equal(Y[0], Y[1]) and torch.equal(Y[0], Y[2])
+
+
+def test_errors_leave_the_call_usable():
+    W = torch.ones((2100, 300), device="cuda")
+    for bad, cb in ((float("nan"), [0.0, 1.0]), (float("inf"), [0.0, 1.0]), (0.5, [0.0, 1.0])):
+        W[2099, 299] = bad
+        with pytest.raises(Exception):
+            B.cer_encode_device(W, 2100, 300, np.array(cb, np.float32), "cer")
+    W[2099, 299] = float("nan")
+    for _ in range(12):  # (more than the mailboxes that are kept)
+        with pytest.raises(Exception):
+            B.cer_quantize_encode_device(W, 2100, 300, 4, "cer")
+    W[2099, 299] = 0.0
+    h = B.cer_encode_device(W, 2100, 300, np.array([0.0, 1.0], np.float32), "cer")
+    assert B.cer_get_dims(h)["nnz"] == 1
