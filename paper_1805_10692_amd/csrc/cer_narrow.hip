@@ -30,8 +30,11 @@ struct NarrowArgs {
     uint32_t tab_shift, part_shift, row_blocks, rows_per_block;
 };
 
-template <typename IdxT, int V>
-__global__ __launch_bounds__(1024) void cer_narrow_kernel(NarrowArgs a) {
+// kFew: fewer than 16 waves (X and that many lists do not fit LDS) do not cover the latency of LDS and of the loads of X one for another, so
+// a wave has more of them on their way: all of a window's reads, eight loads.  us per call before and after: 2303 x 19624, 3 values, batch 4
+// 25.0 -> 20.0; 2140 x 14927, 37 values, 3 12.9 -> 11.1; 1412 x 13527, 10 values, 5 17.3 -> 14.4; 914 x 11814, 33 values, 12 19.2 -> 17.2.
+template <typename IdxT, int V, bool kFew>
+__global__ __launch_bounds__(kFew ? 512 : 1024) void cer_narrow_kernel(NarrowArgs a) {
     using S = GemvShape<IdxT, sizeof(IdxT) == 2 ? 2 : 1>;
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t nthreads = blockDim.x, nwaves = nthreads >> 6;
@@ -79,13 +82,14 @@ __global__ __launch_bounds__(1024) void cer_narrow_kernel(NarrowArgs a) {
         const float* src = a.X + col0;
         Vec* dst = reinterpret_cast<Vec*>(xs);
         const uint32_t behind = (uint32_t)V > a.L ? ((uint32_t)V - 1u) / a.L : 0u, nvec = a.n > behind ? a.n - behind : 0u;
+        constexpr uint32_t kLoads = kFew ? 8 : 4;
         uint32_t i = threadIdx.x;
-        for (; i + 3u * nthreads < nvec; i += 4u * nthreads) {
-            Vec q[4];
+        for (; i + (kLoads - 1u) * nthreads < nvec; i += kLoads * nthreads) {
+            Vec q[kLoads];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) q[k] = reinterpret_cast<const Row*>(src + (size_t)(i + k * nthreads) * a.L)->v;
+            for (uint32_t k = 0; k < kLoads; ++k) q[k] = reinterpret_cast<const Row*>(src + (size_t)(i + k * nthreads) * a.L)->v;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) dst[i + k * nthreads] = q[k];
+            for (uint32_t k = 0; k < kLoads; ++k) dst[i + k * nthreads] = q[k];
         }
         for (; i < nvec; i += nthreads) dst[i] = reinterpret_cast<const Row*>(src + (size_t)i * a.L)->v;
         for (i = nvec + threadIdx.x; i < a.n; i += nthreads)
@@ -160,12 +164,24 @@ __global__ __launch_bounds__(1024) void cer_narrow_kernel(NarrowArgs a) {
                     if (W > 0 && b + (uint32_t)W * S::WIN >= te) break;  // wave-uniform
                     float wl[S::PPL];
                     window_weights<S>(W, bmp, wpre, wts, lane, wl);
+                    // The reads of X in front of their products where that is faster: with both in one loop the compiler waits for every second
+                    // read right behind its request.  Two columns: 0.95 to 0.98 times the time; 16 waves with 4 or 8: 0.93 to 1.07, and so they stay in one.
+                    constexpr int kTogether = kFew || V <= 2 ? std::min<int>(S::PPL, 64 / V) : 1;
 #pragma unroll
-                    for (int k = 0; k < S::PPL; ++k) {
-                        typedef const Vec __attribute__((address_space(3))) * LdsVec;
-                        const Cols<V> x = __builtin_bit_cast(Cols<V>, *reinterpret_cast<LdsVec>((uintptr_t)(xbase + packed_offset<IdxT>(q[W], k, shift))));
+                    for (int k0 = 0; k0 < S::PPL; k0 += kTogether) {
+                        Vec x[kTogether];
 #pragma unroll
-                        for (int v = 0; v < V; ++v) acc[v] = fmaf(x.v[v], wl[k], acc[v]);
+                        for (int k = 0; k < kTogether; ++k) {
+                            typedef const Vec __attribute__((address_space(3))) * LdsVec;
+                            x[k] = *reinterpret_cast<LdsVec>((uintptr_t)(xbase + packed_offset<IdxT>(q[W], k0 + k, shift)));
+                        }
+                        if constexpr (kFew) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int k = 0; k < kTogether; ++k) {
+                            const Cols<V> c = __builtin_bit_cast(Cols<V>, x[k]);
+#pragma unroll
+                            for (int v = 0; v < V; ++v) acc[v] = fmaf(c.v[v], wl[k0 + k], acc[v]);
+                        }
                     }
                 }
             };
@@ -272,16 +288,19 @@ NarrowPlan plan_narrow(const DeviceView& d, uint32_t L) {
 template <typename IdxT>
 hipError_t launch_narrow_t(const NarrowPlan& p, const NarrowArgs& a, size_t budget, hipStream_t stream) {
     void (*kern)(NarrowArgs);
+    // (8-bit indices: an X of 256 rows leaves room for 16 waves)
+    constexpr bool kWide = sizeof(IdxT) > 1;
+    const bool few = kWide && p.waves < 16;
     int slot;
     switch (p.V) {
-        case 8: kern = cer_narrow_kernel<IdxT, 8>; slot = 3; break;
-        case 4: kern = cer_narrow_kernel<IdxT, 4>; slot = 2; break;
-        case 2: kern = cer_narrow_kernel<IdxT, 2>; slot = 1; break;
-        default: kern = cer_narrow_kernel<IdxT, 1>; slot = 0;
+        case 8: kern = few ? cer_narrow_kernel<IdxT, 8, kWide> : cer_narrow_kernel<IdxT, 8, false>; slot = 3; break;
+        case 4: kern = few ? cer_narrow_kernel<IdxT, 4, kWide> : cer_narrow_kernel<IdxT, 4, false>; slot = 2; break;
+        case 2: kern = few ? cer_narrow_kernel<IdxT, 2, kWide> : cer_narrow_kernel<IdxT, 2, false>; slot = 1; break;
+        default: kern = few ? cer_narrow_kernel<IdxT, 1, kWide> : cer_narrow_kernel<IdxT, 1, false>; slot = 0;
     }
     if (p.lds > 48 * 1024) {
-        static LdsGrant<4> grant;
-        const hipError_t e = grant.ensure(slot, reinterpret_cast<const void*>(kern), budget);
+        static LdsGrant<8> grant;
+        const hipError_t e = grant.ensure(slot + (few ? 4 : 0), reinterpret_cast<const void*>(kern), budget);
         if (e != hipSuccess) return e;
     }
     return launch_kernel(kern, dim3(p.row_blocks * p.passes), dim3(p.waves * kWave), p.lds, stream, a);

@@ -87,3 +87,15 @@ def test_the_library_takes_the_kernel_this_file_is_about(case):
     bound = 1e-5 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64)) + 1e-30
     for y in (Y, other):
         assert (np.abs(y.cpu().numpy() - want) <= bound).all()
+
+
+# (m, n, K, share of the most frequent value, columns of X): X and the lists of 16 waves do not fit LDS -- 8 waves or 4; the rounds of loads full, one more, one less
+FEW = [(1100, 4800, 9, 0.95, 8), (2100, 4609, 60, 0.97, 8), (2100, 4608, 130, 0.97, 7), (1100, 9728, 20, 0.95, 4), (1100, 9727, 9, 0.95, 3), (2100, 8193, 130, 0.97, 4),
+       (1100, 19300, 9, 0.95, 2), (2100, 16385, 130, 0.97, 2), (300, 33000, 130, 0.8, 2), (1100, 33000, 130, 0.95, 2), (300, 37000, 130, 0.8, 3)]
+
+
+@pytest.mark.parametrize("case", FEW, ids=[f"{c[0]}x{c[1]}_K{c[2]}_L{c[4]}" for c in FEW])
+def test_fewer_than_16_waves(case):
+    m, n, K, p0, L = case
+    _check(m, n, L, K, p0, K // 2, "cser" if n % 2 else "cer", shift=n % 4)
+    _check(m, n, L, K, p0, 0, "cer", shift=0)
