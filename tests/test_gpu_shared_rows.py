@@ -81,9 +81,12 @@ def test_conv3x3_batch1_full_size(dom):
     (769, 3001, 0.45, 8, 5),         # four rows, Omega[0] != 0
     (1024, 16001, 0.5, 4, None),     # fifteen windows: four waves of four rows
     (1025, 9000, 0.5, 16, 3),        # five rows: ten waves
-    (2048, 7001, 0.5, 5, None),      # eight rows: sixteen waves
+    (2048, 7001, 0.5, 5, None),      # eight rows of fewer than nine windows: whole
+    (2048, 9801, 0.5, 5, None),      # of more: sixteen waves
+    (1700, 9801, 0.5, 16, 3),        # seven rows: fourteen waves
     (2049, 7001, 0.5, 16, 9),        # nine whole rows: nine waves
-    (3840, 1900, 0.1, 200, None),    # fifteen whole rows of a small X
+    (3840, 1900, 0.1, 200, None),    # fifteen whole rows of a small X: workgroups of eight waves
+    (3840, 4001, 0.1, 200, None),    # of more than six windows: fifteen waves
     (600, 37000, 0.85, 40, None),    # X and the lists of few waves fill LDS
 ])
 def test_waves_per_compute_unit(m, n, p_dom, K, dominant):
