@@ -247,9 +247,12 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
                     t_load = advance(t_load);
                     values_of(q, e);
                     ranks_of(q);
-                    __builtin_amdgcn_sched_barrier(0);
+                    // (tiles of several columns: matrix and LDS instructions by turns, 4096 x 9216, 32 values, batch 32 24.1 -> 23.6 us, 3795 x 1900,
+                    // two values, 23 10.0 -> 9.5, 3111 x 2217, 17 values, 56 16.1 -> 15.8; of one, where the splitting is short, 1 to 3 % slower)
+                    if constexpr (CT > 1) __builtin_amdgcn_iglp_opt(0);
+                    else __builtin_amdgcn_sched_barrier(0);
                     multiply(w, x[s]);
-                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (CT == 1) __builtin_amdgcn_sched_barrier(0);
                     pack(e, w);
                     if (--left == 0) break;
                 }
