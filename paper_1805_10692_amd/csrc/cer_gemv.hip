@@ -32,7 +32,10 @@ namespace {
 // that start at or behind the row's end (te) are skipped.
 // kLds: X is in LDS at byte address xlds (a literal 0 where the kernel has no static LDS: the gather's address is then
 // the shifted index itself); otherwise xsrc points to X in global memory.
-template <typename S, typename IdxT, bool kLds>
+// kFew: all of a window's reads of LDS are on their way before the first is waited for.  The compiler waits for each of the first window's where
+// the registers of further windows are short, and up to eight waves do not cover that: 1584 x 15661, 16 values, 5.10 -> 4.94 us, 1256 x 23698, 19
+// values, 5.00 -> 4.92, 1936 x 19351, 130 values, 6.96 -> 6.83; twelve waves and more are up to 2 % slower that way.
+template <typename S, typename IdxT, bool kLds, bool kFew = false>
 __device__ __forceinline__ void gemv_batch(const uint4 (&ix)[S::NW], const float* xsrc, uint32_t xlds, uint32_t b0,
                                            uint32_t te, const float (&wl)[S::NW][S::PPL],
                                            float& acc0, float& acc1) {
@@ -47,6 +50,7 @@ __device__ __forceinline__ void gemv_batch(const uint4 (&ix)[S::NW], const float
 #pragma unroll
             for (int k = 0; k < S::PPL; ++k)
                 xv[k] = *reinterpret_cast<LdsFloatPtr>((uintptr_t)(xlds + packed_offset<IdxT>(ix[W], k, two)));
+            if constexpr (kFew) __builtin_amdgcn_sched_barrier(0);
         } else {
 #pragma unroll
             for (int k = 0; k < S::PPL; ++k) xv[k] = xsrc[packed_index<IdxT>(ix[W], k)];
@@ -394,7 +398,8 @@ __global__ __launch_bounds__(1024) void cer_gemv_kernel(const void* __restrict__
 // Everything else -- batches, windows, bitmap, shared rows, the staging of X -- is as in the kernel above.
 // kBigX: every wave of the workgroup has six whole 16-byte loads of X (6 x the workgroup size x 16 bytes <= 4n).
 // kShortBatch: batches of two windows (16-bit indices, rows of more than three windows on average).
-template <typename IdxT, bool kVec4, bool kOneRow, bool kBigX, bool kShortBatch = false>
+// kFew: at most eight waves of a compute unit have a row or a share of one (see gemv_batch).
+template <typename IdxT, bool kVec4, bool kOneRow, bool kBigX, bool kShortBatch = false, bool kFew = false>
 __global__ __launch_bounds__(1024) void cer_gemv_tab_kernel(const uint32_t* __restrict__ tab, const float* __restrict__ X,
                                                             const float* __restrict__ omega_, const void* __restrict__ colI_,
                                                             float* __restrict__ Y, uint32_t n, uint32_t m,
@@ -617,7 +622,7 @@ __global__ __launch_bounds__(1024) void cer_gemv_tab_kernel(const uint32_t* __re
 
     // (6) the stream: the first batch from the prefetched indices, then the rest of the row, then further rows
     float acc0 = 0.f, acc1 = 0.f;
-    if (run0) gemv_batch<S, IdxT, true>(idx0, xs, 0u, b00, re0, wl0, acc0, acc1);
+    if (run0) gemv_batch<S, IdxT, true, kFew>(idx0, xs, 0u, b00, re0, wl0, acc0, acc1);
     bool first_row = true;
     float y_share = 0.f;
     for (; r < row_end; r += nwaves) {
@@ -655,7 +660,7 @@ __global__ __launch_bounds__(1024) void cer_gemv_tab_kernel(const uint32_t* __re
     bitmap_build<S>(ends, (uint32_t)count + 1u, first, b, bmp, wpre, lane);                      \
     _Pragma("unroll") for (int W = 0; W < S::NW; ++W)                                            \
         if (W == 0 || (b) + (uint32_t)W * S::WIN < te) window_weights<S>(W, bmp, wpre, wts, lane, wl[W]); \
-    gemv_batch<S, IdxT, true>(ix, xs, 0u, b, te, wl, acc0, acc1);
+    gemv_batch<S, IdxT, true, kFew>(ix, xs, 0u, b, te, wl, acc0, acc1);
             CER_REQUEST(ixa, b0)
             for (;;) {
                 const uint32_t b1 = b0 + S::BATCH;
@@ -973,17 +978,23 @@ hipError_t launch_gemv(const DeviceView& d, const KView& k, const float* X, floa
         if (shortb)
             tk = bigx ? (one ? cer_gemv_tab_kernel<IdxT, true, true, true, true> : cer_gemv_tab_kernel<IdxT, true, false, true, true>)
                       : (one ? cer_gemv_tab_kernel<IdxT, true, true, false, true> : cer_gemv_tab_kernel<IdxT, true, false, false, true>);
+        // (a compute unit's only workgroup; 8-bit indices come with an X too small for it to show)
+        const bool few = sizeof(IdxT) == 2 && vec4 && one && blocks <= (uint32_t)d.cus && (rows_per_block << part_shift) <= 8u;
+        if (few)
+            if constexpr (sizeof(IdxT) == 2)
+                tk = shortb ? (bigx ? cer_gemv_tab_kernel<IdxT, true, true, true, true, true> : cer_gemv_tab_kernel<IdxT, true, true, false, true, true>)
+                            : (bigx ? cer_gemv_tab_kernel<IdxT, true, true, true, false, true> : cer_gemv_tab_kernel<IdxT, true, true, false, false, true>);
+        const int variant = (few ? 12 : 0) + (shortb ? 6 : 0) + (bigx ? 4 : (vec4 ? 2 : 0)) + (one ? 1 : 0);
         if (lds > 48 * 1024) {
-            static LdsGrant<36> grant;
+            static LdsGrant<72> grant;
             const int wslot = sizeof(IdxT) == 1 ? 0 : (sizeof(IdxT) == 2 ? 1 : 2);
-            const hipError_t e = grant.ensure(wslot * 12 + (shortb ? 6 : 0) + (bigx ? 4 : (vec4 ? 2 : 0)) + (one ? 1 : 0),
-                                              reinterpret_cast<const void*>(tk), budget);
+            const hipError_t e = grant.ensure(wslot * 24 + variant, reinterpret_cast<const void*>(tk), budget);
             if (e != hipSuccess) return e;
         }
         {   // the kernel takes LDS address 0 for X: it must not have static LDS in front of the dynamic array
-            static std::atomic<int> checked[3][12] = {};
+            static std::atomic<int> checked[3][24] = {};
             const int wslot = sizeof(IdxT) == 1 ? 0 : (sizeof(IdxT) == 2 ? 1 : 2);
-            std::atomic<int>& c = checked[wslot][(shortb ? 6 : 0) + (bigx ? 4 : (vec4 ? 2 : 0)) + (one ? 1 : 0)];
+            std::atomic<int>& c = checked[wslot][variant];
             if (c.load(std::memory_order_acquire) == 0) {
                 hipFuncAttributes fa;
                 const hipError_t e = hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(tk));

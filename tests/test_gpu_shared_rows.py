@@ -84,6 +84,10 @@ def test_conv3x3_batch1_full_size(dom):
     (2048, 7001, 0.5, 5, None),      # eight rows of fewer than nine windows: whole
     (2048, 9801, 0.5, 5, None),      # of more: sixteen waves
     (1700, 9801, 0.5, 16, 3),        # seven rows: fourteen waves
+    (1300, 5000, 0.3, 64, None),     # six rows of seven windows: twelve waves
+    (1300, 5000, 0.55, 64, 7),       # of five: whole
+    (1279, 24004, 0.93, 16, None),   # five whole rows, X of 96 KB
+    (500, 2048, 0.7, 9, None),       # two whole rows of two windows
     (2049, 7001, 0.5, 16, 9),        # nine whole rows: nine waves
     (3840, 1900, 0.1, 200, None),    # fifteen whole rows of a small X: workgroups of eight waves
     (3840, 4001, 0.1, 200, None),    # of more than six windows: fifteen waves
