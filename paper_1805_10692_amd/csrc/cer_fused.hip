@@ -44,6 +44,10 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
     constexpr int PW = weight_planes(kForm), kWords = kForm == 3 ? 2 : 1;  // bf16 numbers and dwords per value
     constexpr uint32_t kWaves = NW, kThreads = NW * kWave;
     constexpr uint32_t R = 16 * RT, RW = R / kWaves, BN = 16 * CT;
+    // Matrix and LDS instructions by turns in tiles of several columns, one piece and uniform grids: 4096 x 9216, 32 values, batch 32 24.1 -> 23.6
+    // us, 3795 x 1900, two values, 23 10.0 -> 9.5, 3111 x 2217, 17 values, 56 16.1 -> 15.8; with three pieces 1.02 to 1.07 times the time (1099 x
+    // 8992, 5 bits, 163 47.8 -> 51.4), with one column, where the splitting is short, 1.01 to 1.03.
+    constexpr bool kTurns = CT > 1 && kForm != 3;
     constexpr int D = NW == 16 ? 2 : (CT == 1 ? 4 : (CT == 2 ? 3 : 2));  // steps of X in registers: the current one and what is on its way
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uniform(tid >> 6);
@@ -247,12 +251,10 @@ __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
                     t_load = advance(t_load);
                     values_of(q, e);
                     ranks_of(q);
-                    // (tiles of several columns: matrix and LDS instructions by turns, 4096 x 9216, 32 values, batch 32 24.1 -> 23.6 us, 3795 x 1900,
-                    // two values, 23 10.0 -> 9.5, 3111 x 2217, 17 values, 56 16.1 -> 15.8; of one, where the splitting is short, 1 to 3 % slower)
-                    if constexpr (CT > 1) __builtin_amdgcn_iglp_opt(0);
+                    if constexpr (kTurns) __builtin_amdgcn_iglp_opt(0);
                     else __builtin_amdgcn_sched_barrier(0);
                     multiply(w, x[s]);
-                    if constexpr (CT == 1) __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (!kTurns) __builtin_amdgcn_sched_barrier(0);
                     pack(e, w);
                     if (--left == 0) break;
                 }

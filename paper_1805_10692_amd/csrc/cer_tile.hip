@@ -650,8 +650,8 @@ __global__ __launch_bounds__(kTileThreads) void cer_tile_kernel(const uint4* qua
         scatter();
         wave_lds_sync();
         // (matrix and LDS instructions by turns: 1737 x 8986, 36 values, batch 198 54.3 -> 49.2 us, 4052 x 10595, 9 values, 87 46.2 -> 44.6,
-        // 2247 x 10262, 3 values, 63 28.5 -> 27.8; one piece, AlexNet-fc6 shape, 99 36.6 -> 37.8)
-        if constexpr (kForm != 1) __builtin_amdgcn_iglp_opt(1);
+        // 2247 x 10262, 3 values, 63 28.5 -> 27.8; one piece, AlexNet-fc6 shape, 99 36.6 -> 37.8; three pieces 1.00 times the time)
+        if constexpr (kForm == kUniform) __builtin_amdgcn_iglp_opt(1);
         request(h + kTileWaves);
         bound = bounds_of(h + 2u * kTileWaves);
 #pragma unroll
