@@ -908,8 +908,8 @@ hipError_t launch_gemv(const DeviceView& d, const KView& k, const float* X, floa
     //   1 or 2 rows per compute unit, 3 windows and more: 4 or 8 waves per row 0.95 (4 windows) to 0.5
     //   3 or 4, from 3 windows on two waves 0.96, 0.93 (6 windows), 0.85 (8), 0.78 (16); four waves ahead of two from 5 windows on with 3 rows
     //     (12: 0.81 either way, 24: 0.65 and 0.74), from 14 on with 4 (24: 0.75 and 0.77); below 3 windows sharing loses 1 to 4 %
-    //   5 or 6, two waves: 1.0 (4 to 6 windows), 0.90 (6 to 9), 0.86 (9 to 12); 7: 1.0 up to 8 windows, 0.95 beyond; 8: 1.03 to 1.06 from 6.5 to 9
-    //     windows, 0.95 beyond; 5 to 8, 24 windows: 0.86; below 4 windows 1.05 to 1.14
+    //   5 or 6, two waves: 1.0 (4 to 6 windows), 0.90 (6 to 9), 0.86 (9 to 12); 7: 1.0 up to 8 windows, 0.95 beyond; 8: 1.03 to 1.06 from 6.5 to 9.3
+    //     windows, 0.95 from 10 on, 0.92 (16), 0.88 (23); 5 to 7, 24 windows: 0.85; below 4 windows 1.05 to 1.14
     //   9 to 15, whole rows: as many waves as rows, and no workgroup of 4 or 8 waves more than the compute units: 0.90 (10 to 16 windows), 0.96
     //     on average; an X of up to 24 KiB: 1.02 up to 6.5 windows, 0.97 beyond
     // 848 x 21879, 145 values, 13200 indices per row 13.7 -> 9.1 us; 608 x 7177, 30 values, 5400 6.8 -> 5.3; 2363 x 10312, 158 values, 8900
@@ -934,7 +934,7 @@ hipError_t launch_gemv(const DeviceView& d, const KView& k, const float* X, floa
     } else if (may_share && use_tab && per_cu_rows < 16) {
         uint32_t shift = 0;
         if (per_cu_rows <= 4) shift = row_windows > (per_cu_rows == 3 ? 5.0 : 14.0) ? 2u : (row_windows > 3.0 ? 1u : 0u);
-        else if (per_cu_rows <= 8) shift = row_windows > (per_cu_rows <= 6 ? 6.0 : (per_cu_rows == 7 ? 8.0 : 9.0)) ? 1u : 0u;
+        else if (per_cu_rows <= 8) shift = row_windows > (per_cu_rows <= 6 ? 6.0 : (per_cu_rows == 7 ? 8.0 : 9.5)) ? 1u : 0u;
         // (waves without a row help to stage a large X: eight loads per thread cover it)
         auto waves_of = [&](uint32_t sh) { return std::max(per_cu_rows << sh, std::min<uint32_t>(16u, (uint32_t)((x_bytes + 8191) / 8192))); };
         while (shift > 0 && fixed + list_bytes((int)waves_of(shift)) > budget) --shift;
