@@ -1079,7 +1079,7 @@ struct DecodeArgs {
     uint32_t seg, nseg;  // columns per segment: a multiple of 8
     const uint32_t* tab;  // rank table
     uint32_t tab_shift;
-    uint32_t rows;        // decode_tiles_kernel: rows per workgroup, 8 or 4
+    uint32_t rows;        // decode_tiles_kernel: rows per workgroup, 8, 4 or 2
     cer::UniformGrid grid;  // ... and the grid of the values
 };
 
@@ -1397,7 +1397,7 @@ __global__ __launch_bounds__(T) void decode_tiles_kernel(const ColT* __restrict_
     for (uint32_t j = tid / a.rows * 8u; j < wlen; j += columns) {
         uint32_t p01[8], p2[8];
         if constexpr (kRanks) {
-            const uint2 q = *reinterpret_cast<const uint2*>(mine + j);  // the stride leaves eight more codes behind a segment
+            const uint2 q = *reinterpret_cast<const uint2*>(mine + j);  // (behind len: anything, up to what launch_decode_tiles leaves behind the last row)
 #pragma unroll
             for (uint32_t i = 0; i < 8; ++i) {
                 const uint32_t k = ((i < 4 ? q.x : q.y) >> (8 * (i & 3u))) & 0xFFu;
@@ -1701,7 +1701,9 @@ hipError_t launch_decode_tiles(const DeviceView& v, uint16_t* out, int64_t pitch
     DecodeArgs a = decode_args(v, (v.n + most - 1) / most, 32);
     a.rows = rows;
     const dim3 grid((unsigned)groups, a.nseg);
-    const size_t lds = (size_t)(a.seg + 8) * rows * sizeof(CodeT);
+    // The last segment's rows are read up to the pitch, the last of them behind all others.
+    const size_t behind = (size_t)std::max<int64_t>(pitch - (int64_t)(a.nseg - 1) * a.seg - (int64_t)(a.seg + 8), 0);
+    const size_t lds = ((size_t)(a.seg + 8) * rows + behind) * sizeof(CodeT);
     auto* kern = decode_tiles_kernel<ColT, CodeT, kPieces, 512>;
     if constexpr (sizeof(CodeT) == 1)
         if (wide) kern = decode_tiles_kernel<ColT, CodeT, kPieces, 1024>;

@@ -1,6 +1,6 @@
 // A HIP runtime without a device, for tests of the host code's error paths: memory is host memory, kernels do not run.  Preloaded into a
 // process of its own.  FAKE_HIP_FAIL=<function>:<text>:<error>: launches of kernels whose name contains the text ("launch"), or the allocation
-// of as many bytes or more as the text says ("malloc"), fail with that error.
+// of as many bytes or more as the text says ("malloc"), fail with that error.  The launches are kept (fake_hip_launch).
 #define __HIP_PLATFORM_AMD__
 #include <hip/hip_runtime_api.h>
 
@@ -10,8 +10,17 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <vector>
 
 namespace {
+struct Launch {
+    std::string name;
+    unsigned grid[3], threads, lds;
+};
+std::vector<Launch>& launches() {
+    static std::vector<Launch> l;
+    return l;
+}
 std::map<const void*, std::string>& names() {
     static std::map<const void*, std::string> n;
     return n;
@@ -53,6 +62,17 @@ size_t fake_hip_bytes() {  // in device memory
     for (auto& b : blocks()) s += b.second;
     return s;
 }
+// The latest launch of a kernel whose (mangled) name contains the text: its name, and grid, threads of a workgroup, bytes of dynamic LDS.
+const char* fake_hip_launch(const char* text, unsigned* shape) {
+    for (size_t i = launches().size(); i-- > 0;) {
+        const Launch& l = launches()[i];
+        if (l.name.find(text) == std::string::npos) continue;
+        const unsigned s[5] = {l.grid[0], l.grid[1], l.grid[2], l.threads, l.lds};
+        std::memcpy(shape, s, sizeof s);
+        return l.name.c_str();
+    }
+    return nullptr;
+}
 hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
 void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
@@ -83,10 +103,11 @@ hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemset(void* d, int v, size_t n) { std::memset(d, v, n); return hipSuccess; }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void**, size_t lds, hipStream_t) {
     std::string text;
     hipError_t e;
     if (wanted("launch", &text, &e) && names()[f].find(text) != std::string::npos) return fail(e);
+    launches().push_back(Launch{names()[f], {grid.x, grid.y, grid.z}, block.x, (unsigned)lds});
     return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
