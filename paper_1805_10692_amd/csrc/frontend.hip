@@ -1855,19 +1855,28 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
         l = layout();
         known = (l.total - room * 4) / 2 < room * 4;
     }
-    if (known) {
+    auto exact = [&]() -> int {  // waits for the number of groups
         HIP_TRY(box.wait_totals(s));
         if (rc == CER_OK) rc = flags_to_error(box.flags());
         if (rc != CER_OK) return rc;
+        known = true;
         room = box.groups();
         l = layout();
-    }
+        return CER_OK;
+    };
+    if (known && (rc = exact()) != CER_OK) return rc;
 
     // the handle's own allocation, filled in place by the emit kernel
     void* base = nullptr;
-    if (const int e = handle_alloc(&base, l.total, s)) {
+    int got = handle_alloc(&base, l.total, s);
+    if (got == (int)hipErrorOutOfMemory && !known) {  // there may be enough for the handle without the room
+        (void)hipGetLastError();
+        if ((rc = exact()) != CER_OK) return rc;
+        got = handle_alloc(&base, l.total, s);
+    }
+    if (got != (int)hipSuccess) {
         (void)box.wait_totals(s);
-        HIP_TRY((hipError_t)e);
+        HIP_TRY((hipError_t)got);
     }
     hnd->d_base = base;
 

@@ -1,6 +1,7 @@
 // A HIP runtime without a device, for tests of the host code's error paths: memory is host memory, kernels do not run.  Preloaded into a
 // process of its own.  FAKE_HIP_FAIL=<function>:<text>:<error>: launches of kernels whose name contains the text ("launch"), or the allocation
 // of as many bytes or more as the text says ("malloc"), fail with that error.  The launches are kept (fake_hip_launch).
+// FAKE_HIP_SIZES=<five numbers, :>: what row_layout_kernel tells the host (csrc/frontend.hip, FrontResult: early and totals).
 #define __HIP_PLATFORM_AMD__
 #include <hip/hip_runtime_api.h>
 
@@ -103,10 +104,18 @@ hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemset(void* d, int v, size_t n) { std::memset(d, v, n); return hipSuccess; }
-hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void**, size_t lds, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, hipStream_t) {
     std::string text;
     hipError_t e;
     if (wanted("launch", &text, &e) && names()[f].find(text) != std::string::npos) return fail(e);
+    if (const char* words = std::getenv("FAKE_HIP_SIZES"); words && names()[f].find("row_layout_kernel") != std::string::npos) {
+        auto* told = *static_cast<unsigned long long**>(args[8]);
+        for (int i = 0; i < 5; ++i) {
+            char* end;
+            told[i] = std::strtoull(words, &end, 10) | 1ull << 63;
+            words = end + (*end == ':');
+        }
+    }
     launches().push_back(Launch{names()[f], {grid.x, grid.y, grid.z}, block.x, (unsigned)lds});
     return hipSuccess;
 }

@@ -1,0 +1,48 @@
+"""Memory of a handle that is compressed on the device (csrc/frontend.hip): it is allocated before the number of groups is known, with room for one
+group per value and row.  On the CPU, with the HIP runtime of tests/fake_hip.cpp, which tells the sizes in the kernels' place."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_1805_10692_amd import binding as B
+from test_prepare_errors import fake  # noqa: F401  (the library of that runtime)
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CHILD = """
+import ctypes, os, sys
+import numpy as np
+from paper_1805_10692_amd import binding as B
+fake = ctypes.CDLL(None)
+fake.fake_hip_bytes.restype = ctypes.c_size_t
+fake.fake_hip_launch.restype = ctypes.c_char_p
+m, n, K, cser = (int(a) for a in sys.argv[1:5])
+cb = np.arange(K, dtype=np.float32)
+out = ctypes.c_void_p()
+rc = B.lib().cer_encode_device(ctypes.c_void_p(4096), m, n, ctypes.c_void_p(cb.ctypes.data), K, cser, None, ctypes.byref(out))
+groups = B.cer_get_dims(B.Handle(out.value, "cser" if cser else "cer"))["groups"] if rc == 0 else -1
+error = B.lib().cer_last_hip_error() if rc else 0
+again = ctypes.c_void_p()
+os.environ.pop("FAKE_HIP_FAIL", None)
+print(rc, error, groups, B.lib().cer_encode_device(ctypes.c_void_p(4096), m, n, ctypes.c_void_p(cb.ctypes.data), K, cser, None, ctypes.byref(again)))
+"""
+
+
+def encode(lib, m, n, K, cser, longest, nnz, groups, most, fail=""):
+    sizes = (longest | K << 32 | K << 41, nnz, groups, groups, most)
+    env = dict(os.environ, LD_PRELOAD=lib, PYTHONPATH=os.path.dirname(HERE), FAKE_HIP_FAIL=fail, FAKE_HIP_SIZES=":".join(map(str, sizes)))
+    out = subprocess.run([sys.executable, "-c", CHILD, *map(str, (m, n, K, cser))], env=env, capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stderr
+    return [int(x) for x in out.stdout.split()]
+
+
+# 64 rows of 3000 indexed elements and 100 of 255 groups: 486 KB, 526 with the room (allocated in steps of 64 KiB); the temporary takes less
+@pytest.mark.parametrize("fail,want", [
+    ("", (0, 0, 6400, 0)),
+    ("malloc:525000:2", (0, 0, 6400, 0)),   # the handle itself fits
+    ("malloc:480000:2", (B.CER_E_HIP, 2, -1, 0)),
+    ("malloc:480000:100", (B.CER_E_HIP, 100, -1, 0)),
+], ids=["plenty", "no_room", "no_memory", "no_device"])
+def test_a_handle_that_fits_without_the_room(fake, fail, want):  # noqa: F811
+    assert tuple(encode(fake, 64, 4096, 256, 0, 3000, 64 * 3000, 6400, 100, fail)) == want
