@@ -422,7 +422,9 @@ int dense_cost_model(int64_t m, int64_t n, int convention, cer_cost_t* out);
  * kernels on `stream`; only the encoded arrays travel to the host (the handle's host mirror).
  * `codebook` is a HOST array of K <= 256 values (CER_E_TOO_LARGE above that); `format` is
  * CER_FORMAT_CER or CER_FORMAT_CSER.  The handle is identical, array for array and bit for bit, to
- * the one cer_encode / cser_encode builds from the same matrix.  The call returns after the stream
+ * the one cer_encode / cser_encode builds from the same matrix.  Its device memory is allocated before
+ * the number of groups is known and may be up to half as large again, for as long as it lives (room for
+ * one group per value and row; without it where memory is short).  The call returns after the stream
  * has drained.  Errors: those of cer_encode, CER_E_HIP (also: no device).
  *
  * cer_quantize_uniform: the uniform quantizer.  Takes the range [w_min, w_max] of the `count`

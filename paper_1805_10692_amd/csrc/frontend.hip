@@ -1853,7 +1853,8 @@ int encode_device(const float* W, int64_t m, int64_t n, const float* codebook, i
     DeviceLayout l;
     if (!known) {
         l = layout();
-        known = (l.total - room * 4) / 2 < room * 4;
+        const size_t room_bytes = room * (4 + oi_width);
+        known = (l.total - room_bytes) / 2 < room_bytes;
     }
     auto exact = [&]() -> int {  // waits for the number of groups
         HIP_TRY(box.wait_totals(s));

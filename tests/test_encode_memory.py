@@ -21,11 +21,21 @@ m, n, K, cser = (int(a) for a in sys.argv[1:5])
 cb = np.arange(K, dtype=np.float32)
 out = ctypes.c_void_p()
 rc = B.lib().cer_encode_device(ctypes.c_void_p(4096), m, n, ctypes.c_void_p(cb.ctypes.data), K, cser, None, ctypes.byref(out))
-groups = B.cer_get_dims(B.Handle(out.value, "cser" if cser else "cer"))["groups"] if rc == 0 else -1
+groups = -1
 error = B.lib().cer_last_hip_error() if rc else 0
 again = ctypes.c_void_p()
 os.environ.pop("FAKE_HIP_FAIL", None)
-print(rc, error, groups, B.lib().cer_encode_device(ctypes.c_void_p(4096), m, n, ctypes.c_void_p(cb.ctypes.data), K, cser, None, ctypes.byref(again)))
+if rc == 0:
+    h = B.Handle(out.value, "cser" if cser else "cer")
+    groups = B.cer_get_dims(h)["groups"]
+    B.lib().cer_trim()
+    held = fake.fake_hip_bytes()
+    B.cer_free(h)
+    B.lib().cer_trim()
+    held -= fake.fake_hip_bytes()
+else:
+    held = 0
+print(held, rc, error, groups, B.lib().cer_encode_device(ctypes.c_void_p(4096), m, n, ctypes.c_void_p(cb.ctypes.data), K, cser, None, ctypes.byref(again)))
 """
 
 
@@ -45,4 +55,24 @@ def encode(lib, m, n, K, cser, longest, nnz, groups, most, fail=""):
     ("malloc:480000:100", (B.CER_E_HIP, 100, -1, 0)),
 ], ids=["plenty", "no_room", "no_memory", "no_device"])
 def test_a_handle_that_fits_without_the_room(fake, fail, want):  # noqa: F811
-    assert tuple(encode(fake, 64, 4096, 256, 0, 3000, 64 * 3000, 6400, 100, fail)) == want
+    assert tuple(encode(fake, 64, 4096, 256, 0, 3000, 64 * 3000, 6400, 100, fail)[1:]) == want
+
+
+def block(size):
+    """Handles' memory comes in steps of an eighth of its power of two."""
+    step = 65536
+    while step * 16 <= size:
+        step *= 2
+    return -(-int(size) // step) * step
+
+
+# Rows of one group each: next to nothing of the room is used.  Bytes per row: two per index, 4 + 8 of pointers, 1024 of the rank table; room for 255
+# groups of four bytes, in CSER one more for the rank.
+@pytest.mark.parametrize("cser", [0, 1])
+@pytest.mark.parametrize("indexed", [300, 500, 750, 1100, 2000])
+def test_room_is_at_most_half_of_the_rest(fake, cser, indexed):  # noqa: F811
+    m, K = 4096, 256
+    held, rc, *_ = encode(fake, m, 4096, K, cser, indexed, m * indexed, m, 1)
+    assert rc == 0
+    exact = 2 * m * indexed + 8192 + (4 + cser) * m + 12 * (m + 1) + 4 * K + 4 * K * m + 256
+    assert block(exact) <= held <= block(1.5 * exact + 2048)
