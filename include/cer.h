@@ -147,7 +147,9 @@ int cer_matmul_noalloc(const cer_handle_t* h, const float* X_dev, float* Y_dev, 
  * blocks the library keeps on the current device; they are kept (at most 2 GiB of them) because getting
  * a few hundred megabytes from the system again costs more than the product that needs them.  The
  * device memory of freed handles is kept in the same way for later handles (at most 1 GiB), and the host
- * conversions keep up to 15 sleeping threads and 16 MiB of pinned memory.  cer_trim
+ * conversions keep up to 15 threads and 16 MiB of pinned memory.  (The threads sleep within some dozens
+ * of microseconds of a call that stands alone; behind one that began within 250 us of the last one they
+ * look for work for another 250 us, giving way to whatever wants their processors.)  cer_trim
  * releases whatever is not in use at the moment of the call on the current device; it may be called at
  * any time.  It may wait for work queued on the null stream, and where it has memory of freed handles to
  * release it waits for everything queued on the device (hipFree does).  Errors: CER_E_HIP.

@@ -729,6 +729,7 @@ int encode_any(const float* W, int64_t m, int64_t n, const float* codebook, int3
     if ((m > 0 && n > 0 && !W) || (K > 0 && !codebook)) return CER_E_INVALID;
     if (m > 0 && n > 0 && K == 0) return CER_E_NOT_IN_CODEBOOK;
     if (m > 0x7FFFFFFFll) return CER_E_TOO_LARGE;
+    const cer::HostCall call;
     try {
         std::shared_ptr<cer::HostMatrix> host;
         int rc = cer::encode_host(W, m, n, codebook, K, cser, &host);
@@ -801,6 +802,7 @@ int decode_any(const cer_handle_t* h, bool want_cser, float* W_out) {
     if (!h) return CER_E_INVALID;
     if (h->host->cser != want_cser) return CER_E_FORMAT;
     if (!W_out && h->host->m * h->host->n > 0) return CER_E_INVALID;
+    const cer::HostCall call;
     try {
         const int rc = cer::ensure_host_arrays(h);
         if (rc != CER_OK) return rc;
@@ -955,6 +957,7 @@ int cer_get_stats(const cer_handle_t* h, double* H, double* p0, double* k_bar, d
 int cer_clone_device(const cer_handle_t* h, cer_handle_t** out) {
     if (!h || !out) return CER_E_INVALID;
     *out = nullptr;
+    const cer::HostCall call;
     try {
         int rc = cer::ensure_host_arrays(h);
         if (rc != CER_OK) return rc;

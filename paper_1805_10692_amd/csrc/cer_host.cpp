@@ -118,7 +118,9 @@ int worker_count(int64_t rows, int64_t work) {
 // Threads that wait between calls: starting 15 of them takes 160 us, waking them 20, and until the last one runs 60 to 100 (a 2048 x 2048
 // layer is encoded in 250).  At most 15; they sleep on a futex after having looked for work for kAwake: a handle that has been encoded is on its
 // way to the device for some 60 us, and what converts a layer often converts it back or goes on with the next (encode and decode in turn,
-// looking for 25 / 250 us, with the counters apart: 1172 x 1576, 50 values, 330 -> 263 us, 779 x 1437, 26 values, 186 -> 140).  A fork leaves the child without them
+// looking for 25 / 250 us, with the counters apart: 1172 x 1576, 50 values, 330 -> 263 us, 779 x 1437, 26 values, 186 -> 140).  Behind a call
+// that stands alone nobody comes, and 15 threads would spend 4 ms of processor time for nothing: they look for work while a call lasts, and
+// afterwards only if it began within kAwake of the one before (HostCall).  A fork leaves the child without them
 // (it starts its own).  One call at a time uses them, a call that finds them busy starts threads for itself.
 class Workers {
 public:
@@ -139,6 +141,7 @@ public:
         w->job_ = job;
         w->ctx_ = ctx;
         w->members_ = threads;
+        w->linger_.store(true, std::memory_order_relaxed);
         w->left_.store(w->started_, std::memory_order_relaxed);
         w->turn_.fetch_add(1, std::memory_order_seq_cst);
         if (w->asleep_.load(std::memory_order_seq_cst) > 0) syscall(SYS_futex, &w->turn_, FUTEX_WAKE_PRIVATE, INT_MAX, nullptr, nullptr, 0);
@@ -147,6 +150,12 @@ public:
             if (spins < 4000) _mm_pause(); else std::this_thread::yield();
         }
         return true;
+    }
+
+    static constexpr std::chrono::microseconds kAwake{250};
+    // The call that has used the threads ends; no other follows at once.
+    static void rest() {
+        if (Workers* w = slot().load(std::memory_order_acquire)) w->linger_.store(false, std::memory_order_relaxed);
     }
 
     // Ends the threads (they are started again when needed), unless they are busy.
@@ -165,7 +174,6 @@ public:
 
 private:
     static constexpr int kMost = 15;
-    static constexpr std::chrono::microseconds kAwake{250};
     static std::atomic<Workers*>& slot() {
         static std::atomic<Workers*> s{nullptr};
         return s;
@@ -193,7 +201,7 @@ private:
                     continue;
                 }
                 if (spins == 1500) until = std::chrono::steady_clock::now() + kAwake;
-                if (std::chrono::steady_clock::now() < until) {
+                if (linger_.load(std::memory_order_relaxed) && std::chrono::steady_clock::now() < until) {
                     std::this_thread::yield();  // (others that want the processor get it)
                     continue;
                 }
@@ -212,6 +220,7 @@ private:
     std::mutex mu_;
     std::atomic<uint32_t> turn_{0};
     std::atomic<int> asleep_{0}, left_{0};
+    std::atomic<bool> linger_{false};
     int started_ = 0, members_ = 0;
     bool quit_ = false;
     Job job_ = nullptr;
@@ -521,6 +530,16 @@ void decode_rows(const HostMatrix& A, float* W, int64_t r0, int64_t r1) {
 }  // namespace
 
 void stop_host_threads() { Workers::stop(); }
+
+namespace {
+std::atomic<int64_t> g_last_call{INT64_MIN / 2};  // when it ended, ns
+int64_t now_ns() { return std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now().time_since_epoch()).count(); }
+}  // namespace
+HostCall::HostCall() : follows_(now_ns() - g_last_call.load(std::memory_order_relaxed) < std::chrono::nanoseconds(Workers::kAwake).count()) {}
+HostCall::~HostCall() {
+    g_last_call.store(now_ns(), std::memory_order_relaxed);
+    if (!follows_) Workers::rest();
+}
 
 // From 256 KiB on the threads of a conversion share the copy (fifteen layers there and back 0.811 of the time, 0.828 with one thread copying).
 void copy_host(void* to, const void* from, size_t bytes) {

@@ -137,7 +137,18 @@ int encode_host(const float* W, int64_t m, int64_t n, const float* codebook, int
 int decode_host(const HostMatrix& A, float* W_out);
 int min_index_bits(uint64_t max_value);
 void copy_host(void* to, const void* from, size_t bytes);  // memcpy by the threads of both
-void stop_host_threads();  // the threads that both keep asleep between calls
+void stop_host_threads();  // the threads that both keep between calls
+// One call of the library that uses them; they stay awake behind it for a while if it follows another one closely.
+class HostCall {
+public:
+    HostCall();
+    ~HostCall();
+    HostCall(const HostCall&) = delete;
+    HostCall& operator=(const HostCall&) = delete;
+
+private:
+    bool follows_;
+};
 
 // Per-call choices of cer_matmul_ex (include/cer.h: cer_matmul_opts_t); the defaults are what cer_matmul does.
 struct MatmulOptions {
