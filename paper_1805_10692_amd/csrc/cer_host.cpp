@@ -105,48 +105,42 @@ private:
     std::vector<Slot> slots_;
 };
 
-// Threads for `work` elements: one for every 16 Ki of them, at most 16 and never more than there are rows.  (A thread takes 1 to 2 ns per element;
-// waiting for the others costs some us each of five times.  Encode and decode in turn with one for every 64 / 32 / 16 Ki, fifteen layers of 0.2 to 4 M
-// elements: 0.82 / 0.70 / 0.64 of the time before the threads were kept awake and their counters apart; each call 4 ms after the last one:
-// 0.91 / 0.79 / 0.80.)
-int worker_count(int64_t rows, int64_t work) {
-    unsigned hw = std::thread::hardware_concurrency();
-    const int64_t t = std::min<int64_t>(std::min<unsigned>(hw ? hw : 1, 16), (work + 16383) / 16384);
-    return (int)std::max<int64_t>(1, std::min<int64_t>(t, rows));
-}
-
 // Threads that wait between calls: starting 15 of them takes 160 us, waking them 20, and until the last one runs 60 to 100 (a 2048 x 2048
 // layer is encoded in 250).  At most 15; they sleep on a futex after having looked for work for kAwake: a handle that has been encoded is on its
 // way to the device for some 60 us, and what converts a layer often converts it back or goes on with the next (encode and decode in turn,
 // looking for 25 / 250 us, with the counters apart: 1172 x 1576, 50 values, 330 -> 263 us, 779 x 1437, 26 values, 186 -> 140).  Behind a call
 // that stands alone nobody comes, and 15 threads would spend 4 ms of processor time for nothing: they look for work while a call lasts, and
 // afterwards only if it began within kAwake of the one before (HostCall).  A fork leaves the child without them
-// (it starts its own).  One call at a time uses them, a call that finds them busy starts threads for itself.
+// (it starts its own).  One call at a time uses them (Crew).
 class Workers {
 public:
     using Job = void (*)(void* ctx, int t);
-    // job(ctx, t) for t = 0 .. threads - 1, 0 on the calling thread; returns false (nothing has run) if they are busy
-    static bool run(int threads, Job job, void* ctx) {
+    // For the caller alone until it lets go; null: they are busy.
+    static Workers* hold() {
         Workers* w = instance();
-        if (!w || threads > kMost + 1 || !w->mu_.try_lock()) return false;
-        std::lock_guard<std::mutex> hold(w->mu_, std::adopt_lock);
-        while (w->started_ < threads - 1) {
+        return w && w->mu_.try_lock() ? w : nullptr;
+    }
+    void let_go() { mu_.unlock(); }
+    // job(ctx, t) for t = 0 .. threads - 1, 0 on the calling thread, which holds them; returns false (nothing has run) if there are too few
+    bool run(int threads, Job job, void* ctx) {
+        if (threads > kMost + 1) return false;
+        while (started_ < threads - 1) {
             try {
-                std::thread(&Workers::loop, w, w->started_ + 1, w->turn_.load(std::memory_order_relaxed)).detach();
+                std::thread(&Workers::loop, this, started_ + 1, turn_.load(std::memory_order_relaxed)).detach();
             } catch (...) {  // no more threads, or no memory for one
                 return false;
             }
-            ++w->started_;
+            ++started_;
         }
-        w->job_ = job;
-        w->ctx_ = ctx;
-        w->members_ = threads;
-        w->linger_.store(true, std::memory_order_relaxed);
-        w->left_.store(w->started_, std::memory_order_relaxed);
-        w->turn_.fetch_add(1, std::memory_order_seq_cst);
-        if (w->asleep_.load(std::memory_order_seq_cst) > 0) syscall(SYS_futex, &w->turn_, FUTEX_WAKE_PRIVATE, INT_MAX, nullptr, nullptr, 0);
+        job_ = job;
+        ctx_ = ctx;
+        members_ = threads;
+        linger_.store(true, std::memory_order_relaxed);
+        left_.store(started_, std::memory_order_relaxed);
+        turn_.fetch_add(1, std::memory_order_seq_cst);
+        if (asleep_.load(std::memory_order_seq_cst) > 0) syscall(SYS_futex, &turn_, FUTEX_WAKE_PRIVATE, INT_MAX, nullptr, nullptr, 0);
         job(ctx, 0);
-        for (int spins = 0; w->left_.load(std::memory_order_acquire) > 0; ++spins) {
+        for (int spins = 0; left_.load(std::memory_order_acquire) > 0; ++spins) {
             if (spins < 4000) _mm_pause(); else std::this_thread::yield();
         }
         return true;
@@ -227,12 +221,42 @@ private:
     void* ctx_ = nullptr;
 };
 
+// Who works on `work` elements: the waiting threads, one for every 16 Ki elements, or, where those are busy with another call, threads started for it,
+// one for every 64 Ki; at most 16 and never more than there are rows.  (A thread takes 1 to 2 ns per element; waiting for the others costs some us
+// each of five times, starting one 10 us.  Encode and decode in turn with one for every 64 / 32 / 16 Ki, fifteen layers of 0.2 to 4 M
+// elements: 0.82 / 0.70 / 0.64 of the time before the threads were kept awake and their counters apart; each call 4 ms after the last one:
+// 0.91 / 0.79 / 0.80.)
+class Crew {
+public:
+    Crew(int64_t rows, int64_t work) {
+        if (count(rows, work, 16384) > 1) waiting_ = Workers::hold();
+        size_ = count(rows, work, waiting_ ? 16384 : 65536);
+    }
+    ~Crew() {
+        if (waiting_) waiting_->let_go();
+    }
+    Crew(const Crew&) = delete;
+    Crew& operator=(const Crew&) = delete;
+    int size() const { return size_; }
+    Workers* waiting() const { return waiting_; }
+
+private:
+    static int count(int64_t rows, int64_t work, int64_t each) {
+        const unsigned hw = std::thread::hardware_concurrency();
+        const int64_t t = std::min<int64_t>(std::min<unsigned>(hw ? hw : 1, 16), (work + each - 1) / each);
+        return (int)std::max<int64_t>(1, std::min<int64_t>(t, rows));
+    }
+    Workers* waiting_ = nullptr;
+    int size_ = 1;
+};
+
 // A team runs body(t, r0, r1, team) on its threads, each with a contiguous share of m rows; sync() waits for all of them.
 // The bodies must not throw (what they need is allocated before).
 class Team {
 public:
     template <typename F>
-    static void run(int threads, int64_t m, F&& body) {
+    static void run(const Crew& crew, int64_t m, F&& body) {
+        const int threads = crew.size();
         Team team;
         auto work = [&](int t) {
             const int n = team.size_.load(std::memory_order_relaxed);
@@ -241,7 +265,7 @@ public:
         team.size_.store(threads, std::memory_order_relaxed);
         if (threads == 1) return work(0);
         using Work = decltype(work);
-        if (Workers::run(threads, [](void* ctx, int t) { (*static_cast<Work*>(ctx))(t); }, &work)) return;
+        if (crew.waiting() && crew.waiting()->run(threads, [](void* ctx, int t) { (*static_cast<Work*>(ctx))(t); }, &work)) return;
         team.size_.store(0, std::memory_order_relaxed);
         std::vector<std::thread> pool;
         pool.reserve((size_t)threads - 1);
@@ -376,11 +400,12 @@ int encode_rows(const float* W, int64_t m, int64_t n, const float* codebook, int
                 HostMatrix& A) {
     const int64_t N = m * n;
     const bool cser = A.cser;
-    const int T = worker_count(m, N);
     std::unique_ptr<SymT[]> sym(new SymT[(size_t)std::max<int64_t>(N, 1)]);
     // the rows' histograms are kept unless they would be larger than the matrix (few columns, many values)
     const bool keep = (int64_t)Kc <= n;
     std::unique_ptr<uint32_t[]> rows_c(new uint32_t[keep ? (size_t)m * (size_t)Kc : 1]);
+    const Crew crew(m, N);  // (behind the large allocations: others may use the threads meanwhile)
+    const int T = crew.size();
     // What a thread counts in has cache lines of its own: with those of a few values next to each other the threads waited for one another at
     // every element (659 x 1121, two values: 356 -> 173 us there and back).
     constexpr size_t kLine = 128;
@@ -396,7 +421,7 @@ int encode_rows(const float* W, int64_t m, int64_t n, const float* codebook, int
     std::atomic<bool> missing{false};
     std::atomic<int> rc{CER_OK};
 
-    Team::run(T, m, [&](int t, int64_t r0, int64_t r1, Team& team) {
+    Team::run(crew, m, [&](int t, int64_t r0, int64_t r1, Team& team) {
         uint32_t* h4 = scratch.data() + (size_t)t * scratch_of;
         uint32_t* own = h4 + 4 * Kz;
         uint32_t* fill = own + Kz;
@@ -541,14 +566,15 @@ HostCall::~HostCall() {
     if (!follows_) Workers::rest();
 }
 
-// From 256 KiB on the threads of a conversion share the copy (fifteen layers there and back 0.811 of the time, 0.828 with one thread copying).
+// From 256 KiB on the waiting threads share the copy (fifteen layers there and back 0.811 of the time, 0.828 with one thread copying); none are
+// started for it (one thread copies 256 KiB in some 20 us, starting 15 takes 160).
 void copy_host(void* to, const void* from, size_t bytes) {
-    const int threads = worker_count(INT64_MAX, (int64_t)(bytes / 4));
-    if (bytes < (size_t)256 << 10 || threads < 2) {
+    const Crew crew(INT64_MAX, bytes < (size_t)256 << 10 ? 0 : (int64_t)(bytes / 4));
+    if (!crew.waiting()) {
         if (bytes) std::memcpy(to, from, bytes);
         return;
     }
-    Team::run(threads, (int64_t)(bytes / 64), [&](int, int64_t b0, int64_t b1, Team&) {
+    Team::run(crew, (int64_t)(bytes / 64), [&](int, int64_t b0, int64_t b1, Team&) {
         const size_t end = b1 == (int64_t)(bytes / 64) ? bytes : (size_t)b1 * 64;
         std::memcpy(static_cast<char*>(to) + b0 * 64, static_cast<const char*>(from) + b0 * 64, end - (size_t)b0 * 64);
     });
@@ -578,7 +604,7 @@ int encode_host(const float* W, int64_t m, int64_t n, const float* codebook, int
 int decode_host(const HostMatrix& A, float* W) {
     if (A.m * A.n == 0) return CER_OK;
     if (A.K < 1) return CER_E_INVALID;
-    Team::run(worker_count(A.m, A.m * A.n), A.m, [&](int, int64_t r0, int64_t r1, Team&) {
+    Team::run(Crew(A.m, A.m * A.n), A.m, [&](int, int64_t r0, int64_t r1, Team&) {
         if (A.colI.bits == 8) decode_rows<uint8_t>(A, W, r0, r1);
         else if (A.colI.bits == 16) decode_rows<uint16_t>(A, W, r0, r1);
         else decode_rows<uint32_t>(A, W, r0, r1);

@@ -3,7 +3,9 @@
 // of as many bytes or more as the text says ("malloc"), fail with that error.  The launches are kept (fake_hip_launch).
 // FAKE_HIP_SIZES=<five numbers, :>: what row_layout_kernel tells the host (csrc/frontend.hip, FrontResult: early and totals).
 #define __HIP_PLATFORM_AMD__
+#include <dlfcn.h>
 #include <hip/hip_runtime_api.h>
+#include <pthread.h>
 
 #include <atomic>
 #include <cstdio>
@@ -62,6 +64,13 @@ size_t fake_hip_bytes() {  // in device memory
     size_t s = 0;
     for (auto& b : blocks()) s += b.second;
     return s;
+}
+static thread_local int g_started;
+int fake_hip_threads() { return g_started; }  // threads that the calling thread has started
+int pthread_create(pthread_t* t, const pthread_attr_t* a, void* (*f)(void*), void* arg) {
+    static const auto real = reinterpret_cast<int (*)(pthread_t*, const pthread_attr_t*, void* (*)(void*), void*)>(dlsym(RTLD_NEXT, "pthread_create"));
+    ++g_started;
+    return real(t, a, f, arg);
 }
 // The latest launch of a kernel whose (mangled) name contains the text: its name, and grid, threads of a workgroup, bytes of dynamic LDS.
 const char* fake_hip_launch(const char* text, unsigned* shape) {

@@ -1,6 +1,8 @@
 """The host conversions' threads: calls at the same time, after the threads were ended, and in a forked child."""
 import multiprocessing
 import os
+import subprocess
+import sys
 import threading
 import time
 
@@ -8,6 +10,7 @@ import numpy as np
 import pytest
 
 from paper_1805_10692_amd import binding as B
+from test_prepare_errors import HERE, fake  # noqa: F401  (a HIP runtime without a device that counts the threads a thread starts)
 
 
 def _round_trip(seed, m=300, n=1100):
@@ -82,6 +85,47 @@ def test_threads_sleep_after_a_call_that_stands_alone():
         B.cer_free(h)
     # (polling: 1 to 2.2 ms with seven threads; without 0.03 to 1, the lowest quarter up to 0.3)
     assert sorted(spent)[8] < 100e-6 * others
+
+
+BUSY = """
+import ctypes, threading
+import numpy as np
+from paper_1805_10692_amd import binding as B
+fake = ctypes.CDLL(None)
+rng = np.random.default_rng(0)
+cb = np.array([0.0, 1.0, 2.0], np.float32)
+large, W = (rng.choice(cb, size=s, p=[0.4, 0.3, 0.3]).astype(np.float32) for s in ((2048, 4096), (512, 600)))
+B.cer_free(B.cer_encode(large, cb))  # the waiting threads are there
+stop = threading.Event()
+
+def others():
+    while not stop.is_set():
+        B.cer_free(B.cer_encode(large, cb))
+
+t = threading.Thread(target=others)
+t.start()
+started, out = [], np.empty_like(W)
+for _ in range(60):
+    a = fake.fake_hip_threads()
+    h = B.cer_encode(W, cb)
+    b = fake.fake_hip_threads()
+    assert np.array_equal(B.cer_decode(h), W)
+    started += [b - a, fake.fake_hip_threads() - b]
+    B.cer_free(h)
+stop.set()
+t.join()
+print(max(started))
+"""
+
+
+def test_few_threads_are_started_where_the_waiting_ones_are_busy(fake):  # noqa: F811
+    """Starting a thread takes some 10 us: one for every 64 Ki elements beside another conversion, none for the copy of the arrays (400 KB)."""
+    if len(os.sched_getaffinity(0)) < 8:
+        pytest.skip("as many processors as threads")
+    env = dict(os.environ, LD_PRELOAD=fake, PYTHONPATH=os.path.dirname(HERE))
+    out = subprocess.run([sys.executable, "-c", BUSY], env=env, capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stderr
+    assert 0 < int(out.stdout) <= (512 * 600 + 65535) // 65536 - 1
 
 
 @pytest.mark.parametrize("values", [1, 2, 3, 17, 200])
