@@ -1,7 +1,7 @@
 // A HIP runtime without a device, for tests of the host code's error paths: memory is host memory, kernels do not run.  Preloaded into a
 // process of its own.  FAKE_HIP_FAIL=<function>:<text>:<error>: launches of kernels whose name contains the text ("launch"), or the allocation
 // of as many bytes or more as the text says ("malloc"), fail with that error.  The launches are kept (fake_hip_launch).
-// FAKE_HIP_SIZES=<five numbers, :>: what row_layout_kernel tells the host (csrc/frontend.hip, FrontResult: early and totals).
+// FAKE_HIP_SIZES=<up to five numbers, :>: what row_layout_kernel tells the host (csrc/frontend.hip, FrontResult: early and totals).
 #define __HIP_PLATFORM_AMD__
 #include <dlfcn.h>
 #include <hip/hip_runtime_api.h>
@@ -18,7 +18,7 @@
 namespace {
 struct Launch {
     std::string name;
-    unsigned grid[3], threads, lds;
+    unsigned grid[3], threads, lds, args[2];
 };
 std::vector<Launch>& launches() {
     static std::vector<Launch> l;
@@ -72,17 +72,19 @@ int pthread_create(pthread_t* t, const pthread_attr_t* a, void* (*f)(void*), voi
     ++g_started;
     return real(t, a, f, arg);
 }
-// The latest launch of a kernel whose (mangled) name contains the text: its name, and grid, threads of a workgroup, bytes of dynamic LDS.
+// The latest launch of a kernel whose (mangled) name contains the text: its name, and grid, threads of a workgroup, bytes of dynamic LDS; of
+// cer_gemv_tab_kernel the rows per workgroup and `meta` as well.
 const char* fake_hip_launch(const char* text, unsigned* shape) {
     for (size_t i = launches().size(); i-- > 0;) {
         const Launch& l = launches()[i];
         if (l.name.find(text) == std::string::npos) continue;
-        const unsigned s[5] = {l.grid[0], l.grid[1], l.grid[2], l.threads, l.lds};
+        const unsigned s[7] = {l.grid[0], l.grid[1], l.grid[2], l.threads, l.lds, l.args[0], l.args[1]};
         std::memcpy(shape, s, sizeof s);
         return l.name.c_str();
     }
     return nullptr;
 }
+void fake_hip_forget() { launches().clear(); }
 hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
 void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
@@ -119,13 +121,16 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
     if (wanted("launch", &text, &e) && names()[f].find(text) != std::string::npos) return fail(e);
     if (const char* words = std::getenv("FAKE_HIP_SIZES"); words && names()[f].find("row_layout_kernel") != std::string::npos) {
         auto* told = *static_cast<unsigned long long**>(args[8]);
-        for (int i = 0; i < 5; ++i) {
+        for (int i = 0; i < 5 && *words; ++i) {
             char* end;
             told[i] = std::strtoull(words, &end, 10) | 1ull << 63;
             words = end + (*end == ':');
         }
     }
-    launches().push_back(Launch{names()[f], {grid.x, grid.y, grid.z}, block.x, (unsigned)lds});
+    Launch l{names()[f], {grid.x, grid.y, grid.z}, block.x, (unsigned)lds, {0, 0}};
+    if (l.name.find("cer_gemv_tab_kernel") != std::string::npos)
+        for (int i = 0; i < 2; ++i) l.args[i] = *static_cast<unsigned*>(args[7 + i]);
+    launches().push_back(l);
     return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }

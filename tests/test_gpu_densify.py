@@ -87,8 +87,9 @@ def test_trim_releases_cached_temporaries_and_products_go_on():
 @pytest.mark.parametrize("m,n,values,share", [
     (5, 20000, 3, 0.1),      # several stretches of positions, the last workgroup with one row
     (6, 8193, 2, 0.0005),    # a row's positions end just behind a stretch
-    (9, 30011, 256, 0.3),    # lists in two rounds, rows of an odd length
-    (1030, 5200, 250, 0.01),  # eight rows per workgroup, lists in four rounds, two stretches
+    (9, 30011, 256, 0.3),    # four rows per workgroup of 1024 threads, several stretches, rows of an odd length
+    (1030, 5200, 250, 0.01),  # four rows per workgroup of 512 threads, lists in two rounds
+    (2041, 5200, 250, 0.01),  # eight rows per workgroup, lists in four rounds, two stretches
     (1025, 700, 40, 0.9),
 ])
 def test_decoded_pieces_in_stretches(m, n, values, share):
@@ -107,6 +108,34 @@ def test_decoded_pieces_in_stretches(m, n, values, share):
     X = rng.standard_normal((n, 40)).astype(np.float32)
     Xd, Yd = torch.from_numpy(X).cuda(), torch.empty((m, 40), dtype=torch.float32, device="cuda")
     B.cer_matmul_ex(h, Xd, Yd, 40, opts=B.MatmulOpts(path=B.CER_PATH_DENSE))
+    torch.cuda.synchronize()
+    want, scale = W.astype(np.float64) @ X.astype(np.float64), np.abs(W.astype(np.float64)) @ np.abs(X.astype(np.float64))
+    assert (np.abs(Yd.cpu().numpy() - want) <= 1e-5 * scale + 1e-30).all()
+    B.cer_free(h)
+
+
+# Two and three pieces per value, and what takes the place of either in narrow batches: the values' ranks (tests/test_launch_shapes.py says which).
+EIGHT_ROWS = [(2041, 5200, kind, L) for kind in ("grid", "any") for L in (40, 1200)]
+
+
+def eight_rows(m, n, kind, L):
+    """(W, codebook): nearly all elements indexed, 250 values on a grid (two pieces) or anywhere (three)."""
+    rng = np.random.default_rng(n + L)
+    cb = ((np.arange(250) - 125) * 0.0123).astype(np.float32) if kind == "grid" else rng.standard_normal(250).astype(np.float32)
+    W = rng.choice(cb, size=(m, n)).astype(np.float32)
+    W[5], W[m - 2, : n // 2] = cb[3], cb[125]
+    return W, cb
+
+
+@pytest.mark.parametrize("case", EIGHT_ROWS)
+def test_decoded_in_eight_rows_and_two_stretches(case):
+    import torch
+    m, n, kind, L = case
+    W, cb = eight_rows(*case)
+    h = B.cser_encode(W, cb) if kind == "any" else B.cer_encode(W, cb)
+    X = np.random.default_rng(L).standard_normal((n, L)).astype(np.float32)
+    Xd, Yd = torch.from_numpy(X).cuda(), torch.empty((m, L), dtype=torch.float32, device="cuda")
+    B.cer_matmul_ex(h, Xd, Yd, L, opts=B.MatmulOpts(path=B.CER_PATH_DENSE))
     torch.cuda.synchronize()
     want, scale = W.astype(np.float64) @ X.astype(np.float64), np.abs(W.astype(np.float64)) @ np.abs(X.astype(np.float64))
     assert (np.abs(Yd.cpu().numpy() - want) <= 1e-5 * scale + 1e-30).all()

@@ -10,12 +10,14 @@ pytestmark = pytest.mark.gpu
 
 
 # (rows, columns, values, share of the most frequent one): many groups per row, hardly any (the number of groups is waited for), rows in one
-# and in several workgroups of either row_layout_kernel, one value, two values, one row
-@pytest.mark.parametrize("fmt", ["cer", "cser"])
-@pytest.mark.parametrize("case", [(300, 700, 16, 0.5), (17, 300, 256, 0.999), (1000, 200, 256, 0.99), (2049, 520, 97, 0.3), (4100, 64, 5, 0.9),
-                                  (1, 5000, 200, 0.2), (33, 40, 1, 1.0), (64, 1, 2, 0.5), (16, 70000, 3, 0.97)])
-def test_arrays_and_products(case, fmt):
-    m, n, K, p0 = case
+# and in several workgroups of either row_layout_kernel, one value, two values, one and two rows.  Behind each: whether the emitter starts early in CER, in CSER (tests/test_launch_shapes.py
+# holds the calls against it).
+CASES = [((300, 700, 16, 0.5), (True, True)), ((17, 300, 256, 0.999), (True, True)), ((1000, 200, 256, 0.99), (False, True)), ((1000, 200, 256, 0.01), (False, False)),
+         ((2049, 520, 97, 0.3), (True, True)), ((4100, 64, 5, 0.9), (True, True)), ((1, 5000, 200, 0.2), (True, True)), ((2, 5000, 200, 0.2), (True, True)),
+         ((33, 40, 1, 1.0), (True, True)), ((64, 1, 2, 0.5), (True, True)), ((16, 70000, 3, 0.97), (True, True))]
+
+
+def matrix(m, n, K, p0):
     rng = np.random.default_rng(m * n + K)
     cb = (np.arange(K) - K // 2).astype(np.float32)
     p = np.full(K, (1.0 - p0) / max(K - 1, 1))
@@ -24,6 +26,14 @@ def test_arrays_and_products(case, fmt):
     W[m // 2] = cb[K // 2]  # a row without indexed elements
     if m > 2 and K > 2:
         W[0, :] = cb[0]     # and one that is all indexed, with a single group
+    return W, cb, rng
+
+
+@pytest.mark.parametrize("fmt", ["cer", "cser"])
+@pytest.mark.parametrize("case", [case for case, _ in CASES])
+def test_arrays_and_products(case, fmt):
+    m, n, K, p0 = case
+    W, cb, rng = matrix(*case)
     # memory of an earlier handle, full of something else
     B.cer_free(B.cer_encode_device(torch.full((m, n), 3.0, device="cuda"), m, n, np.array([3.0], np.float32), fmt))
     d = B.cer_encode_device(torch.from_numpy(W).cuda(), m, n, cb, fmt)

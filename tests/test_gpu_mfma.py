@@ -228,24 +228,42 @@ def _grid(K):
     return (np.arange(K) - K // 2).astype(np.float32) / np.float32(K / 2.0)
 
 
-@pytest.mark.parametrize("case", [
-    ("three", 1300, 200, 100), ("three", 1300, 200, 1897), ("grid113", 2200, 700, 128), ("grid113", 2200, 700, 1289), ("two", 33, 500, 24),
-    ("two", 33, 500, 2025), ("any256", 290, 777, 66), ("grid113", 37, 6144, 40), ("any256", 67, 6145, 33), ("three", 1100, 6177, 34),
-    ("two", 600, 12288, 5), ("any256", 520, 12289, 20), ("two", 5, 33792, 20), ("grid113", 3, 33793, 70), ("one", 19, 6200, 35),
-    ("one", 9, 12300, 35), ("any256", 515, 70001, 3)])
-def test_ranks_and_the_lines_of_their_choice(case):
-    name, m, n, L = case
+# Behind each case: rows per workgroup of the decoder and its threads, whether it leaves ranks, whether the product's tile is the large one
+# (tests/test_launch_shapes.py holds the launches against it).
+RANKS = [
+    (("three", 1300, 200, 100), (4, 512, True, False)), (("three", 1300, 200, 1897), (4, 512, False, True)),
+    (("grid113", 2200, 700, 128), (8, 512, True, False)), (("grid113", 2200, 700, 1289), (8, 512, False, True)),
+    (("two", 33, 500, 24), (4, 512, True, False)), (("two", 33, 500, 2025), (4, 512, True, False)),
+    (("two", 600, 500, 2025), (4, 512, False, False)), (("two", 1200, 500, 2025), (4, 512, False, True)),
+    (("any256", 290, 777, 66), (4, 512, False, True)), (("grid113", 37, 6144, 40), (4, 512, False, False)),
+    (("any256", 67, 6145, 33), (4, 512, False, False)), (("three", 1100, 6177, 34), (4, 512, True, False)),
+    (("two", 600, 12288, 5), (4, 512, True, False)), (("any256", 520, 12289, 20), (4, 1024, True, False)),
+    (("two", 5, 33792, 20), (2, 1024, True, False)), (("grid113", 3, 33793, 70), (4, 1024, False, False)),
+    (("any256", 33, 13000, 40), (4, 1024, False, True)), (("one", 19, 6200, 35), (4, 512, False, False)),
+    (("one", 9, 12300, 35), (4, 1024, False, False)), (("any256", 515, 70001, 3), (4, 1024, True, False)),
+    (("two", 1300, 6200, 130), (4, 512, True, True)), (("any256", 1300, 6200, 130), (4, 512, True, True)),
+    (("grid113", 1301, 6200, 130), (4, 512, True, True)), (("any256", 600, 13000, 150), (4, 1024, True, True))]
+
+
+def rank_case(name, m, n, L):
+    """(W, codebook, whether it is a CSER matrix, generator)"""
     rng = np.random.default_rng(m * L)
     cb = {"grid113": _grid(113), "any256": np.sort(rng.standard_normal(256)).astype(np.float32)}.get(name, CODEBOOKS.get(name))
     p = np.full(len(cb), 0.5 / (len(cb) - 1))
     p[len(cb) // 2] = 0.5
-    W = rng.choice(cb, size=(m, n), p=p).astype(np.float32)
+    return rng.choice(cb, size=(m, n), p=p).astype(np.float32), cb, m % 2 == 1, rng
+
+
+@pytest.mark.parametrize("case", [case for case, _ in RANKS])
+def test_ranks_and_the_lines_of_their_choice(case):
+    name, m, n, L = case
+    W, cb, cser, rng = rank_case(*case)
     X = rng.standard_normal((n, L)).astype(np.float32)
-    Y = _product(W, cb, X, "cser" if m % 2 else "cer")
+    Y = _product(W, cb, X, "cser" if cser else "cer")
     want = W.astype(np.float64) @ X.astype(np.float64)
     assert (np.abs(Y - want) <= 1e-6 * (np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64))).all()
     X[n // 3, 1], X[n - 1, 0] = np.inf, np.nan  # the products in binary32 take their weights from the ranks as well
-    Y = _product(W, cb, X, "cser" if m % 2 else "cer")
+    Y = _product(W, cb, X, "cser" if cser else "cer")
     with np.errstate(invalid="ignore"):
         want = W.astype(np.float64) @ X.astype(np.float64)
         scale = np.abs(W).astype(np.float64) @ np.abs(X).astype(np.float64)

@@ -75,26 +75,35 @@ def test_conv3x3_batch1_full_size(dom):
     full_check(wl.conv3x3(L=1, nonzero_dominant=dom), opts=NO_TABLE)
 
 
-@pytest.mark.parametrize("m,n,p_dom,K,dominant", [
-    (513, 3300, 0.5, 16, None),      # three rows per compute unit, just above three windows: two waves per row
-    (768, 9001, 0.4, 100, None),     # ten windows: four waves; two tiles of ranks
-    (769, 3001, 0.45, 8, 5),         # four rows, Omega[0] != 0
-    (1024, 16001, 0.5, 4, None),     # fifteen windows: four waves of four rows
-    (1025, 9000, 0.5, 16, 3),        # five rows: ten waves
-    (2048, 7001, 0.5, 5, None),      # eight rows of fewer than nine windows: whole
-    (2048, 9801, 0.5, 5, None),      # of more: sixteen waves
-    (1700, 9801, 0.5, 16, 3),        # seven rows: fourteen waves
-    (1300, 5000, 0.3, 64, None),     # six rows of seven windows: twelve waves
-    (1300, 5000, 0.55, 64, 7),       # of five: whole
-    (1279, 24004, 0.93, 16, None),   # five whole rows, X of 96 KB
-    (500, 2048, 0.7, 9, None),       # two whole rows of two windows
-    (2049, 7001, 0.5, 16, 9),        # nine whole rows: nine waves
-    (3840, 1900, 0.1, 200, None),    # fifteen whole rows of a small X: workgroups of eight waves
-    (3840, 4001, 0.1, 200, None),    # of more than six windows: fifteen waves
-    (600, 37000, 0.85, 40, None),    # X and the lists of few waves fill LDS
-])
+SHAPES = [  # (m, n, p_dom, K, dominant), (rows, waves per row, waves) of a workgroup
+    ((513, 3300, 0.5, 16, None), (3, 2, 6)),  # just above three windows: two waves per row
+    ((768, 9001, 0.4, 100, None), (3, 4, 12)),  # ten windows: four; two tiles of ranks
+    ((769, 3001, 0.45, 8, 5), (4, 2, 8)),  # Omega[0] != 0
+    ((1024, 16001, 0.5, 4, None), (4, 4, 16)),  # fifteen windows
+    ((1025, 9000, 0.5, 16, 3), (5, 2, 10)),
+    ((2048, 7001, 0.5, 5, None), (8, 1, 8)),  # fewer than nine windows: whole
+    ((2048, 9801, 0.5, 5, None), (8, 2, 16)),  # more than nine and a half
+    ((1700, 9801, 0.5, 16, 3), (7, 2, 14)),
+    ((1300, 5000, 0.3, 64, None), (6, 2, 12)),  # seven windows
+    ((1300, 5000, 0.55, 64, 7), (4, 1, 4)),  # four: whole, an X of 20 KB
+    ((1279, 24004, 0.93, 16, None), (5, 1, 16)),  # whole, X of 96 KB
+    ((500, 2048, 0.7, 9, None), (2, 1, 4)),  # two windows
+    ((2049, 7001, 0.5, 16, 9), (9, 1, 9)),  # nine whole rows
+    ((3840, 1900, 0.1, 200, None), (4, 1, 4)),  # whole rows of a small X: workgroups of four waves
+    ((3840, 4001, 0.1, 200, None), (4, 1, 4)),  # of fewer than six and a half windows as well
+    ((3840, 5001, 0.1, 200, None), (15, 1, 15)),  # of more: one workgroup of as many waves as rows
+    ((3840, 6201, 0.5, 5, None), (15, 1, 15)),    # an X of more than 24 KiB
+    ((1700, 7001, 0.5, 16, 3), (7, 1, 8)),        # seven rows of fewer than eight windows: whole
+    ((1024, 12001, 0.5, 4, None), (4, 2, 8)),     # four rows of fewer than fourteen
+    ((768, 3801, 0.4, 100, None), (3, 2, 6)),     # three rows of fewer than five
+    ((600, 37000, 0.85, 40, None), (3, 4, 16)),  # X and the lists of few waves fill LDS
+]
+
+
+@pytest.mark.parametrize("m,n,p_dom,K,dominant", [case for case, _ in SHAPES])
 def test_waves_per_compute_unit(m, n, p_dom, K, dominant):
-    """A workgroup per compute unit of 3 to 15 rows, shared by waves or whole, on both sides of the rule's lines."""
+    """A workgroup per compute unit of 3 to 15 rows, shared by waves or whole, on both sides of the rule's lines
+    (tests/test_launch_shapes.py holds what a workgroup gets against the list)."""
     kw = {} if dominant is None else {"dominant": dominant}
     w = wl.random_lowentropy(m=m, n=n, K=K, p_dom=p_dom, L=1, seed=m + n, **kw)
     full_check(w, want_path=0)
