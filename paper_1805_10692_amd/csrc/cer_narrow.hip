@@ -253,6 +253,7 @@ NarrowPlan plan_narrow_t(const DeviceView& d, uint32_t L) {
         while (p.waves > 4 && lds(p.waves) > budget) p.waves >>= 1;
         p.lds = lds(p.waves);
         if (p.lds > budget) continue;
+        if (V == 8 && p.waves < 16) continue;  // by the estimate below four columns and twice the waves are always ahead
         const uint64_t units = std::max<uint64_t>(1, (uint64_t)d.cus / p.passes);
         p.rows_per_block = (uint32_t)std::max<uint64_t>(1, ((uint64_t)d.m + units - 1) / units);
         const uint64_t windows = ((uint64_t)d.nnz / (uint64_t)d.m + S::WIN - 1) / S::WIN;  // average row
@@ -293,7 +294,7 @@ hipError_t launch_narrow_t(const NarrowPlan& p, const NarrowArgs& a, size_t budg
     const bool few = kWide && p.waves < 16;
     int slot;
     switch (p.V) {
-        case 8: kern = few ? cer_narrow_kernel<IdxT, 8, kWide> : cer_narrow_kernel<IdxT, 8, false>; slot = 3; break;
+        case 8: kern = cer_narrow_kernel<IdxT, 8, false>; slot = 3; break;
         case 4: kern = few ? cer_narrow_kernel<IdxT, 4, kWide> : cer_narrow_kernel<IdxT, 4, false>; slot = 2; break;
         case 2: kern = few ? cer_narrow_kernel<IdxT, 2, kWide> : cer_narrow_kernel<IdxT, 2, false>; slot = 1; break;
         default: kern = few ? cer_narrow_kernel<IdxT, 1, kWide> : cer_narrow_kernel<IdxT, 1, false>; slot = 0;

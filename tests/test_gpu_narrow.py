@@ -9,14 +9,19 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-def _check(m, n, L, K, p0, zero, fmt, shift=0):
-    """zero: position of 0 in the codebook (K // 2: 0 is the most frequent value)."""
+def matrix(m, n, L, K, p0, zero):
+    """(W, codebook, generator); zero: position of 0 in the codebook (K // 2: 0 is the most frequent value)."""
     rng = np.random.default_rng(m * 7 + n + L)
     cb = (np.arange(K) - zero).astype(np.float32) / np.float32(K)
     p = np.full(K, (1 - p0) / (K - 1))
     p[K // 2] = p0
     W = rng.choice(cb, size=(m, n), p=p).astype(np.float32)
     W[m // 2] = cb[K // 2]                                         # a row without indices
+    return W, cb, rng
+
+
+def _check(m, n, L, K, p0, zero, fmt, shift=0):
+    W, cb, rng = matrix(m, n, L, K, p0, zero)
     X = rng.standard_normal((n, L)).astype(np.float32)
     h = (B.cer_encode if fmt == "cer" else B.cser_encode)(W, cb)
     buf = torch.zeros(n * L + 4, device="cuda")
@@ -89,12 +94,17 @@ def test_the_library_takes_the_kernel_this_file_is_about(case):
         assert (np.abs(y.cpu().numpy() - want) <= bound).all()
 
 
-# (m, n, K, share of the most frequent value, columns of X): X and the lists of 16 waves do not fit LDS -- 8 waves or 4; the rounds of loads full, one more, one less
-FEW = [(1100, 4800, 9, 0.95, 8), (2100, 4609, 60, 0.97, 8), (2100, 4608, 130, 0.97, 7), (1100, 9728, 20, 0.95, 4), (1100, 9727, 9, 0.95, 3), (2100, 8193, 130, 0.97, 4),
-       (1100, 19300, 9, 0.95, 2), (2100, 16385, 130, 0.97, 2), (300, 33000, 130, 0.8, 2), (1100, 33000, 130, 0.95, 2), (300, 37000, 130, 0.8, 3)]
+# (m, n, K, share of the most frequent value, columns of X) around the sizes at which X and the lists of 16 waves do not fit LDS: with eight columns
+# per pass those of 4, with four those of 2, ... are taken then, or 8 or 4 waves; the rounds of loads full, one more, one less.  Behind each: columns per
+# pass and waves with Omega[0] == 0 and != 0, None: another kernel (tests/test_launch_shapes.py holds the launches against it).
+FEW = [
+    ((1100, 4800, 9, 0.95, 8), None, (4, 16)), ((2100, 4609, 60, 0.97, 8), (4, 16), (4, 16)), ((2100, 4608, 130, 0.97, 7), None, (4, 16)),
+    ((1100, 9728, 20, 0.95, 4), (4, 8), (2, 16)), ((1100, 9727, 9, 0.95, 3), (4, 8), (1, 16)), ((2100, 8193, 130, 0.97, 4), None, (2, 16)),
+    ((1100, 19300, 9, 0.95, 2), (2, 8), (1, 16)), ((2100, 16385, 130, 0.97, 2), (2, 8), (2, 8)), ((2303, 19624, 3, 0.95, 4), (2, 8), (2, 8)),
+    ((300, 33000, 130, 0.8, 2), (1, 8), (1, 8)), ((1100, 33000, 130, 0.95, 2), (1, 8), (1, 8)), ((300, 37000, 130, 0.8, 3), (1, 4), (1, 4))]
 
 
-@pytest.mark.parametrize("case", FEW, ids=[f"{c[0]}x{c[1]}_K{c[2]}_L{c[4]}" for c in FEW])
+@pytest.mark.parametrize("case", [f[0] for f in FEW], ids=[f"{c[0]}x{c[1]}_K{c[2]}_L{c[4]}" for c, *_ in FEW])
 def test_fewer_than_16_waves(case):
     m, n, K, p0, L = case
     _check(m, n, L, K, p0, K // 2, "cser" if n % 2 else "cer", shift=n % 4)

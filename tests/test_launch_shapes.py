@@ -12,6 +12,7 @@ import pytest
 import test_gpu_densify
 import test_gpu_early_sizes
 import test_gpu_mfma
+import test_gpu_narrow
 import test_gpu_shared_rows
 from paper_1805_10692_amd import binding as B
 from test_prepare_errors import fake  # noqa: F401  (the library of that runtime)
@@ -24,7 +25,7 @@ import ctypes, json, sys
 import numpy as np
 from paper_1805_10692_amd import binding as B
 from paper_1805_10692_amd import workloads as wl
-import test_gpu_densify, test_gpu_mfma
+import test_gpu_densify, test_gpu_mfma, test_gpu_narrow
 fake = ctypes.CDLL(None)
 fake.fake_hip_launch.restype = ctypes.c_char_p
 
@@ -48,6 +49,10 @@ for case in cases:
         m, n, p_dom, K, dominant = case
         w = wl.random_lowentropy(m=m, n=n, K=K, p_dom=p_dom, L=1, seed=m + n, **({} if dominant is None else {"dominant": dominant}))
         got = product(w.W, w.codebook, False, 1, -1, "cer_gemv_tab_kernel")
+    elif kind == "narrow":
+        (m, n, K, p0, L), zero = case
+        W, cb, _ = test_gpu_narrow.matrix(m, n, L, K, p0, zero)
+        got = product(W, cb, n % 2 == 1 and zero > 0, L, -1, "cer_narrow_kernel")
     else:
         if kind == "ranks":
             W, cb, cser, _ = test_gpu_mfma.rank_case(*case)
@@ -85,6 +90,17 @@ def test_rows_and_waves_of_batch_1(fake):  # noqa: F811
     for case, [(_, (_, _, _, threads, _, rows, meta))] in products(fake, "rows", list(want)):
         assert threads == 64 * (meta >> 16)
         assert (rows, 1 << ((meta >> 13) & 7), meta >> 16) == want[case], case
+
+
+def test_columns_and_waves_of_narrow_batches(fake):  # noqa: F811
+    want = {(case, zero): w for case, *both in test_gpu_narrow.FEW for zero, w in zip((case[2] // 2, 0), both)}
+    for key, [(name, (_, _, _, threads, *_))] in products(fake, "narrow", list(want)):
+        got = None
+        if name:
+            columns, few = re.search(r"cer_narrow_kernelI[a-z]Li(\d)ELb(\d)E", name).groups()
+            got = (int(columns), threads // 64)
+            assert (few == "1") == (threads < 1024)
+        assert got == want[key], key
 
 
 def _decoded(got):
