@@ -31,8 +31,10 @@ struct NarrowArgs {
 };
 
 // kFew: fewer than 16 waves (X and that many lists do not fit LDS) do not cover the latency of LDS and of the loads of X one for another, so
-// a wave has more of them on their way: all of a window's reads, eight loads.  us per call before and after: 2303 x 19624, 3 values, batch 4
-// 25.0 -> 20.0; 2140 x 14927, 37 values, 3 12.9 -> 11.1; 1412 x 13527, 10 values, 5 17.3 -> 14.4; 914 x 11814, 33 values, 12 19.2 -> 17.2.
+// a wave has more of them on their way: all of a window's reads, eight loads.  us per call before and after: one column, four waves 822 x 38457, 3
+// values, batch 3 23.9 -> 18.8, eight 300 x 33000, 130 values, 2 8.8 -> 8.7; two columns, four 1900 x 19872, 3 values, 9 73 -> 55, eight 2303 x
+// 19624, 3 values, 4 12.2 -> 10.8; four columns, four 2286 x 9957, 33 values, 8 17.4 -> 16.3, eight 1065 x 9467, 33 values, 8 14.7 -> 13.5.
+// Four columns and eight waves gain where a wave has several rows that are long or have short lists, and lose else (plan_narrow_t).
 template <typename IdxT, int V, bool kFew>
 __global__ __launch_bounds__(kFew ? 512 : 1024) void cer_narrow_kernel(NarrowArgs a) {
     using S = GemvShape<IdxT, sizeof(IdxT) == 2 ? 2 : 1>;
@@ -82,15 +84,19 @@ __global__ __launch_bounds__(kFew ? 512 : 1024) void cer_narrow_kernel(NarrowArg
         const float* src = a.X + col0;
         Vec* dst = reinterpret_cast<Vec*>(xs);
         const uint32_t behind = (uint32_t)V > a.L ? ((uint32_t)V - 1u) / a.L : 0u, nvec = a.n > behind ? a.n - behind : 0u;
-        constexpr uint32_t kLoads = kFew ? 8 : 4;
         uint32_t i = threadIdx.x;
-        for (; i + (kLoads - 1u) * nthreads < nvec; i += kLoads * nthreads) {
-            Vec q[kLoads];
+        auto copy = [&](auto loads) {
+            constexpr uint32_t kLoads = decltype(loads)::value;
+            for (; i + (kLoads - 1u) * nthreads < nvec; i += kLoads * nthreads) {
+                Vec q[kLoads];
 #pragma unroll
-            for (uint32_t k = 0; k < kLoads; ++k) q[k] = reinterpret_cast<const Row*>(src + (size_t)(i + k * nthreads) * a.L)->v;
+                for (uint32_t k = 0; k < kLoads; ++k) q[k] = reinterpret_cast<const Row*>(src + (size_t)(i + k * nthreads) * a.L)->v;
 #pragma unroll
-            for (uint32_t k = 0; k < kLoads; ++k) dst[i + k * nthreads] = q[k];
-        }
+                for (uint32_t k = 0; k < kLoads; ++k) dst[i + k * nthreads] = q[k];
+            }
+        };
+        if constexpr (kFew) copy(std::integral_constant<uint32_t, 8>{});
+        copy(std::integral_constant<uint32_t, 4>{});
         for (; i < nvec; i += nthreads) dst[i] = reinterpret_cast<const Row*>(src + (size_t)i * a.L)->v;
         for (i = nvec + threadIdx.x; i < a.n; i += nthreads)
 #pragma unroll
@@ -165,7 +171,8 @@ __global__ __launch_bounds__(kFew ? 512 : 1024) void cer_narrow_kernel(NarrowArg
                     float wl[S::PPL];
                     window_weights<S>(W, bmp, wpre, wts, lane, wl);
                     // The reads of X in front of their products where that is faster: with both in one loop the compiler waits for every second
-                    // read right behind its request.  Two columns: 0.95 to 0.98 times the time; 16 waves with 4 or 8: 0.93 to 1.07, and so they stay in one.
+                    // read right behind its request.  One or two columns, 16 waves: 1412 x 13527, 10 values, batch 5 11.4 -> 9.8 us, 914 x 11814, 33
+                    // values, 12 16.2 -> 14.5, 100 products 0.93 times the time; four or eight columns 0.93 to 1.07, and so they stay in one.
                     constexpr int kTogether = kFew || V <= 2 ? std::min<int>(S::PPL, 64 / V) : 1;
 #pragma unroll
                     for (int k0 = 0; k0 < S::PPL; k0 += kTogether) {
@@ -232,6 +239,7 @@ __global__ __launch_bounds__(kFew ? 512 : 1024) void cer_narrow_kernel(NarrowArg
 struct NarrowPlan {
     int V = 0;  // 0: not applicable
     uint32_t waves = 0, part_shift = 0, rows_per_block = 0, row_blocks = 0, passes = 0;
+    bool few = false;  // cer_narrow_kernel's kFew
     size_t lds = 0;
     double us = 0;  // estimate
 };
@@ -259,6 +267,10 @@ NarrowPlan plan_narrow_t(const DeviceView& d, uint32_t L) {
         const uint64_t windows = ((uint64_t)d.nnz / (uint64_t)d.m + S::WIN - 1) / S::WIN;  // average row
         while ((2u << p.part_shift) * p.rows_per_block <= p.waves && (1u << p.part_shift) < 8u && (1u << p.part_shift) < windows) ++p.part_shift;
         p.row_blocks = (uint32_t)(((uint64_t)d.m + p.rows_per_block - 1) / p.rows_per_block);
+        // (8-bit indices: an X of 256 rows leaves room for 16 waves.)  Four columns, eight waves, kFew against the other way, 48 products: more than
+        // eight rows per workgroup and lists of up to 64 values 0.91 to 0.99, longer lists 0.93 to 0.95 from five windows per row on and 1.00
+        // to 1.02 at fewer than four; up to eight rows 0.98 to 1.03
+        p.few = sizeof(IdxT) > 1 && p.waves < 16 && (V < 4 || p.waves < 8 || (p.rows_per_block > 8 && (d.rank_tab_shift <= 6 || windows > 4)));
         // Clocks, fitted to 220 random shapes of 2 to 16 columns (the typical deviation is 12 %).  A compute unit: per 64 indexed
         // elements, 13, 15, 23, 58 for 1, 2, 4, 8 columns -- the weights and their bookkeeping, and from 4 columns on the
         // LDS -- and per row its list.  Against that the longest row, walked by its waves alone.  Before either, the staging: 21
@@ -289,9 +301,8 @@ NarrowPlan plan_narrow(const DeviceView& d, uint32_t L) {
 template <typename IdxT>
 hipError_t launch_narrow_t(const NarrowPlan& p, const NarrowArgs& a, size_t budget, hipStream_t stream) {
     void (*kern)(NarrowArgs);
-    // (8-bit indices: an X of 256 rows leaves room for 16 waves)
     constexpr bool kWide = sizeof(IdxT) > 1;
-    const bool few = kWide && p.waves < 16;
+    const bool few = p.few;
     int slot;
     switch (p.V) {
         case 8: kern = cer_narrow_kernel<IdxT, 8, false>; slot = 3; break;

@@ -96,12 +96,16 @@ def test_the_library_takes_the_kernel_this_file_is_about(case):
 
 # (m, n, K, share of the most frequent value, columns of X) around the sizes at which X and the lists of 16 waves do not fit LDS: with eight columns
 # per pass those of 4, with four those of 2, ... are taken then, or 8 or 4 waves; the rounds of loads full, one more, one less.  Behind each: columns per
-# pass and waves with Omega[0] == 0 and != 0, None: another kernel (tests/test_launch_shapes.py holds the launches against it).
+# pass, waves and whether they read ahead (kFew), with Omega[0] == 0 and != 0, None: another kernel (tests/test_launch_shapes.py holds the launches
+# against it).
 FEW = [
-    ((1100, 4800, 9, 0.95, 8), None, (4, 16)), ((2100, 4609, 60, 0.97, 8), (4, 16), (4, 16)), ((2100, 4608, 130, 0.97, 7), None, (4, 16)),
-    ((1100, 9728, 20, 0.95, 4), (4, 8), (2, 16)), ((1100, 9727, 9, 0.95, 3), (4, 8), (1, 16)), ((2100, 8193, 130, 0.97, 4), None, (2, 16)),
-    ((1100, 19300, 9, 0.95, 2), (2, 8), (1, 16)), ((2100, 16385, 130, 0.97, 2), (2, 8), (2, 8)), ((2303, 19624, 3, 0.95, 4), (2, 8), (2, 8)),
-    ((300, 33000, 130, 0.8, 2), (1, 8), (1, 8)), ((1100, 33000, 130, 0.95, 2), (1, 8), (1, 8)), ((300, 37000, 130, 0.8, 3), (1, 4), (1, 4))]
+    ((1100, 4800, 9, 0.95, 8), None, (4, 16, False)), ((2100, 4609, 60, 0.97, 8), (4, 16, False), (4, 16, False)), ((2100, 4608, 130, 0.97, 7), None, (4, 16, False)),
+    ((1100, 9728, 20, 0.95, 4), (4, 8, False), (2, 16, False)), ((1100, 9727, 9, 0.95, 3), (4, 8, False), (1, 16, False)), ((2100, 8193, 130, 0.97, 4), None, (2, 16, False)),
+    ((1100, 19300, 9, 0.95, 2), (2, 8, True), (1, 16, False)), ((2100, 16385, 130, 0.97, 2), (2, 8, True), (2, 8, True)), ((2303, 19624, 3, 0.95, 4), (2, 8, True), (2, 8, True)),
+    ((300, 33000, 130, 0.8, 2), (1, 8, True), (1, 8, True)), ((1100, 33000, 130, 0.95, 2), (1, 8, True), (1, 8, True)), ((300, 37000, 130, 0.8, 3), (1, 4, True), (1, 4, True)),
+    ((1065, 9467, 33, 0.5, 8), (4, 8, True), (2, 16, False)), ((1303, 9428, 130, 0.5, 8), (4, 4, True), (4, 4, True)), ((1048, 9633, 130, 0.8, 12), (4, 4, True), (4, 4, True)),
+    ((975, 9483, 3, 0.5, 4), (4, 8, False), (2, 16, False)), ((900, 9957, 33, 0.8, 8), (4, 4, True), (2, 16, False)), ((803, 19918, 3, 0.7, 4), (2, 4, True), (2, 4, True)),
+    ((410, 38038, 3, 0.7, 3), (1, 8, True), (1, 8, True)), ((192, 18844, 64, 0.8, 2), (2, 8, True), (1, 16, False))]
 
 
 @pytest.mark.parametrize("case", [f[0] for f in FEW], ids=[f"{c[0]}x{c[1]}_K{c[2]}_L{c[4]}" for c, *_ in FEW])

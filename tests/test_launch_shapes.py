@@ -98,8 +98,7 @@ def test_columns_and_waves_of_narrow_batches(fake):  # noqa: F811
         got = None
         if name:
             columns, few = re.search(r"cer_narrow_kernelI[a-z]Li(\d)ELb(\d)E", name).groups()
-            got = (int(columns), threads // 64)
-            assert (few == "1") == (threads < 1024)
+            got = (int(columns), threads // 64, few == "1")
         assert got == want[key], key
 
 
