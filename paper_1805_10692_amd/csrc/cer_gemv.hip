@@ -908,10 +908,14 @@ hipError_t launch_gemv(const DeviceView& d, const KView& k, const float* X, floa
     //   1 or 2 rows per compute unit, 3 windows and more: 4 or 8 waves per row 0.95 (4 windows) to 0.5
     //   3 or 4, from 3 windows on two waves 0.96, 0.93 (6 windows), 0.85 (8), 0.78 (16); four waves ahead of two from 5 windows on with 3 rows
     //     (12: 0.81 either way, 24: 0.65 and 0.74), from 14 on with 4 (24: 0.75 and 0.77); below 3 windows sharing loses 1 to 4 %
-    //   5 or 6, two waves: 1.0 (4 to 6 windows), 0.90 (6 to 9), 0.86 (9 to 12); 7: 1.0 up to 8 windows, 0.95 beyond; 8: 1.03 to 1.06 from 6.5 to 9.3
-    //     windows, 0.95 from 10 on, 0.92 (16), 0.88 (23); 5 to 7, 24 windows: 0.85; below 4 windows 1.05 to 1.14
+    //   5 or 6, two waves: 1.0 (4 to 6 windows), 0.90 (6 to 9), 0.86 (9 to 12); below 4 windows 1.05 to 1.14
+    //   7, an X of more than 64 KiB (whole rows take 16 waves to stage it): 0.95 from 8 windows on; a smaller X 1.01 to 1.03 from 8 to 9, 0.98 to 1.00 up to
+    //     9.7, then 0.95; more than 128 values 1.02 to 1.05 up to 9.8; 24 windows: 0.85
+    //   8, 1.03 to 1.06 from 6.5 to 9.3 windows; more than 64 KiB 0.93 to 0.99 from 9.5 on; a smaller X 1.01 to 1.05 up to 9.75, 0.97 to 1.00 beyond; more
+    //     than 128 values 0.99 to 1.07 up to 11.4, 0.96 to 1.00 beyond; 0.92 (16 windows), 0.88 (23)
     //   9 to 15, whole rows: as many waves as rows, and no workgroup of 4 or 8 waves more than the compute units: 0.90 (10 to 16 windows), 0.96
-    //     on average; an X of up to 24 KiB: 1.02 up to 6.5 windows, 0.97 beyond
+    //     on average; an X of up to 24 KiB, for which workgroups of four waves are the other way: 1.02 up to 6.5 windows, 0.97 beyond; 11 and 15 rows,
+    //     nearly whole workgroups of four, 1.00 to 1.01 up to 7.5 windows, 0.98 beyond; 12 rows, three of them, 1.005 to 1.02
     // 848 x 21879, 145 values, 13200 indices per row 13.7 -> 9.1 us; 608 x 7177, 30 values, 5400 6.8 -> 5.3; 2363 x 10312, 158 values, 8900
     // 15.6 -> 12.2; 650 x 17950, rows of 970 on average, the longest of 17000, 12.6 -> 6.1.
     uint32_t part_shift = 0, rows_shared = 0;
@@ -934,11 +938,14 @@ hipError_t launch_gemv(const DeviceView& d, const KView& k, const float* X, floa
     } else if (may_share && use_tab && per_cu_rows < 16) {
         uint32_t shift = 0;
         if (per_cu_rows <= 4) shift = row_windows > (per_cu_rows == 3 ? 5.0 : 14.0) ? 2u : (row_windows > 3.0 ? 1u : 0u);
-        else if (per_cu_rows <= 8) shift = row_windows > (per_cu_rows <= 6 ? 6.0 : (per_cu_rows == 7 ? 8.0 : 9.5)) ? 1u : 0u;
+        else if (per_cu_rows <= 6) shift = row_windows > 6.0 ? 1u : 0u;
+        else if (per_cu_rows == 7) shift = row_windows > (x_bytes > 64 * 1024 ? 8.0 : (k.K <= 128 ? 9.0 : 9.8)) ? 1u : 0u;
+        else if (per_cu_rows == 8) shift = row_windows > (x_bytes > 64 * 1024 ? 9.5 : (k.K <= 128 ? 9.8 : 11.5)) ? 1u : 0u;
         // (waves without a row help to stage a large X: eight loads per thread cover it)
         auto waves_of = [&](uint32_t sh) { return std::max(per_cu_rows << sh, std::min<uint32_t>(16u, (uint32_t)((x_bytes + 8191) / 8192))); };
         while (shift > 0 && fixed + list_bytes((int)waves_of(shift)) > budget) --shift;
-        const bool whole = per_cu_rows > 8 && (x_bytes > 24 * 1024 || row_windows > 6.5) && fixed + list_bytes((int)waves_of(0)) <= budget;
+        const bool uneven = per_cu_rows % 4 != 0 && row_windows > (per_cu_rows % 4 == 3 ? 7.5 : 6.5);
+        const bool whole = per_cu_rows > 8 && (x_bytes > 24 * 1024 || uneven) && fixed + list_bytes((int)waves_of(0)) <= budget;
         if (shift > 0 || whole) {
             part_shift = shift;
             rows_shared = per_cu_rows;

@@ -76,27 +76,35 @@ def test_conv3x3_batch1_full_size(dom):
 
 
 SHAPES = [  # (m, n, p_dom, K, dominant), (rows, waves per row, waves) of a workgroup
-    ((513, 3300, 0.5, 16, None), (3, 2, 6)),  # just above three windows: two waves per row
-    ((768, 9001, 0.4, 100, None), (3, 4, 12)),  # ten windows: four; two tiles of ranks
-    ((769, 3001, 0.45, 8, 5), (4, 2, 8)),  # Omega[0] != 0
-    ((1024, 16001, 0.5, 4, None), (4, 4, 16)),  # fifteen windows
+    ((513, 3300, 0.5, 16, None), (3, 2, 6)),         # just above three windows
+    ((768, 3801, 0.4, 100, None), (3, 2, 6)),        # fewer than five
+    ((768, 9001, 0.4, 100, None), (3, 4, 12)),       # ten; two tiles of ranks
+    ((600, 37000, 0.85, 40, None), (3, 4, 16)),      # X and the lists of few waves fill LDS
+    ((769, 3001, 0.45, 8, 5), (4, 2, 8)),            # Omega[0] != 0
+    ((1024, 12001, 0.5, 4, None), (4, 2, 8)),        # fewer than fourteen windows
+    ((1024, 16001, 0.5, 4, None), (4, 4, 16)),       # fifteen
     ((1025, 9000, 0.5, 16, 3), (5, 2, 10)),
-    ((2048, 7001, 0.5, 5, None), (8, 1, 8)),  # fewer than nine windows: whole
-    ((2048, 9801, 0.5, 5, None), (8, 2, 16)),  # more than nine and a half
+    ((1279, 24004, 0.93, 16, None), (5, 1, 16)),     # whole rows, X of 96 KB
+    ((1300, 5000, 0.3, 64, None), (6, 2, 12)),       # seven windows
+    ((1300, 5000, 0.55, 64, 7), (4, 1, 4)),          # four: whole, an X of 20 KB
+    ((1700, 8601, 0.5, 16, 3), (7, 1, 8)),           # fewer than nine
     ((1700, 9801, 0.5, 16, 3), (7, 2, 14)),
-    ((1300, 5000, 0.3, 64, None), (6, 2, 12)),  # seven windows
-    ((1300, 5000, 0.55, 64, 7), (4, 1, 4)),  # four: whole, an X of 20 KB
-    ((1279, 24004, 0.93, 16, None), (5, 1, 16)),  # whole, X of 96 KB
-    ((500, 2048, 0.7, 9, None), (2, 1, 4)),  # two windows
-    ((2049, 7001, 0.5, 16, 9), (9, 1, 9)),  # nine whole rows
-    ((3840, 1900, 0.1, 200, None), (4, 1, 4)),  # whole rows of a small X: workgroups of four waves
-    ((3840, 4001, 0.1, 200, None), (4, 1, 4)),  # of fewer than six and a half windows as well
-    ((3840, 5001, 0.1, 200, None), (15, 1, 15)),  # of more: one workgroup of as many waves as rows
-    ((3840, 6201, 0.5, 5, None), (15, 1, 15)),    # an X of more than 24 KiB
-    ((1700, 7001, 0.5, 16, 3), (7, 1, 8)),        # seven rows of fewer than eight windows: whole
-    ((1024, 12001, 0.5, 4, None), (4, 2, 8)),     # four rows of fewer than fourteen
-    ((768, 3801, 0.4, 100, None), (3, 2, 6)),     # three rows of fewer than five
-    ((600, 37000, 0.85, 40, None), (3, 4, 16)),  # X and the lists of few waves fill LDS
+    ((1700, 20001, 0.79, 16, 3), (7, 2, 14)),        # more than eight, X of more than 64 KiB
+    ((1700, 9801, 0.5, 200, None), (7, 1, 8)),       # fewer than 9.8, more than 128 values
+    ((2048, 7001, 0.5, 5, None), (8, 1, 8)),
+    ((2048, 9801, 0.5, 5, None), (8, 1, 8)),         # fewer than 9.8
+    ((2048, 10401, 0.5, 5, None), (8, 2, 16)),       # more
+    ((2048, 16501, 0.7, 5, None), (8, 2, 16)),       # more than 9.5, X of more than 64 KiB
+    ((2048, 11301, 0.5, 200, None), (8, 1, 8)),      # fewer than 11.5, more than 128 values
+    ((2048, 12301, 0.5, 200, None), (8, 2, 16)),
+    ((500, 2048, 0.7, 9, None), (2, 1, 4)),          # two windows
+    ((2049, 7001, 0.5, 16, 9), (9, 1, 9)),           # nine whole rows
+    ((2049, 4601, 0.1, 200, None), (9, 1, 9)),       # an X of up to 24 KiB, more than 6.5 windows
+    ((3072, 5001, 0.1, 200, None), (4, 1, 4)),       # twelve rows of an X of up to 24 KiB: workgroups of four waves
+    ((3840, 1900, 0.1, 200, None), (4, 1, 4)),       # fifteen rows of few windows: the same
+    ((3840, 4001, 0.1, 200, None), (4, 1, 4)),       # of fewer than 7.5 as well
+    ((3840, 5001, 0.1, 200, None), (15, 1, 15)),     # of more: one workgroup of as many waves as rows
+    ((3840, 6201, 0.5, 5, None), (15, 1, 15)),       # an X of more than 24 KiB
 ]
 
 
@@ -105,7 +113,7 @@ def test_waves_per_compute_unit(m, n, p_dom, K, dominant):
     """A workgroup per compute unit of 3 to 15 rows, shared by waves or whole, on both sides of the rule's lines
     (tests/test_launch_shapes.py holds what a workgroup gets against the list)."""
     kw = {} if dominant is None else {"dominant": dominant}
-    w = wl.random_lowentropy(m=m, n=n, K=K, p_dom=p_dom, L=1, seed=m + n, **kw)
+    w = wl.random_lowentropy(m=m, n=n, K=K, p_dom=p_dom, L=1, seed=m + n, ratio=0.99 if K > 128 else 0.7, **kw)  # (every value occurs)
     full_check(w, want_path=0)
 
 

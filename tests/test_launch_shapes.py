@@ -47,7 +47,7 @@ kind, cases = json.load(sys.stdin)
 for case in cases:
     if kind == "rows":
         m, n, p_dom, K, dominant = case
-        w = wl.random_lowentropy(m=m, n=n, K=K, p_dom=p_dom, L=1, seed=m + n, **({} if dominant is None else {"dominant": dominant}))
+        w = wl.random_lowentropy(m=m, n=n, K=K, p_dom=p_dom, L=1, seed=m + n, ratio=0.99 if K > 128 else 0.7, **({} if dominant is None else {"dominant": dominant}))
         got = product(w.W, w.codebook, False, 1, -1, "cer_gemv_tab_kernel")
     elif kind == "narrow":
         (m, n, K, p0, L), zero = case
