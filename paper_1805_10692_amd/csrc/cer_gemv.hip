@@ -398,7 +398,7 @@ __global__ __launch_bounds__(1024) void cer_gemv_kernel(const void* __restrict__
 // Everything else -- batches, windows, bitmap, shared rows, the staging of X -- is as in the kernel above.
 // kBigX: every wave of the workgroup has six whole 16-byte loads of X (6 x the workgroup size x 16 bytes <= 4n).
 // kShortBatch: batches of two windows (16-bit indices, rows of more than three windows on average).
-// kFew: at most eight waves of a compute unit have a row or a share of one (see gemv_batch).
+// kFew: at most eight waves of a compute unit have one of at least three such rows, or a share of it (see gemv_batch).
 template <typename IdxT, bool kVec4, bool kOneRow, bool kBigX, bool kShortBatch = false, bool kFew = false>
 __global__ __launch_bounds__(1024) void cer_gemv_tab_kernel(const uint32_t* __restrict__ tab, const float* __restrict__ X,
                                                             const float* __restrict__ omega_, const void* __restrict__ colI_,
@@ -985,21 +985,20 @@ hipError_t launch_gemv(const DeviceView& d, const KView& k, const float* X, floa
         if (shortb)
             tk = bigx ? (one ? cer_gemv_tab_kernel<IdxT, true, true, true, true> : cer_gemv_tab_kernel<IdxT, true, false, true, true>)
                       : (one ? cer_gemv_tab_kernel<IdxT, true, true, false, true> : cer_gemv_tab_kernel<IdxT, true, false, false, true>);
-        // (a compute unit's only workgroup; 8-bit indices come with an X too small for it to show)
-        const bool few = sizeof(IdxT) == 2 && vec4 && one && blocks <= (uint32_t)d.cus && (rows_per_block << part_shift) <= 8u;
+        // A compute unit's only workgroup, at least three rows of more than three windows: 54 matrices 0.96 to 1.00 times the time.  Shorter rows and
+        // one or two of them 0.97 to 1.03, 1.00 in the mean (8-bit indices come with an X too small for it to show).
+        const bool few = shortb && one && blocks <= (uint32_t)d.cus && rows_per_block > 2u && (rows_per_block << part_shift) <= 8u;
         if (few)
-            if constexpr (sizeof(IdxT) == 2)
-                tk = shortb ? (bigx ? cer_gemv_tab_kernel<IdxT, true, true, true, true, true> : cer_gemv_tab_kernel<IdxT, true, true, false, true, true>)
-                            : (bigx ? cer_gemv_tab_kernel<IdxT, true, true, true, false, true> : cer_gemv_tab_kernel<IdxT, true, true, false, false, true>);
-        const int variant = (few ? 12 : 0) + (shortb ? 6 : 0) + (bigx ? 4 : (vec4 ? 2 : 0)) + (one ? 1 : 0);
+            if constexpr (sizeof(IdxT) == 2) tk = bigx ? cer_gemv_tab_kernel<IdxT, true, true, true, true, true> : cer_gemv_tab_kernel<IdxT, true, true, false, true, true>;
+        const int variant = (few ? 12 : (shortb ? 6 : 0)) + (bigx ? 4 : (vec4 ? 2 : 0)) + (one ? 1 : 0);
         if (lds > 48 * 1024) {
-            static LdsGrant<72> grant;
+            static LdsGrant<54> grant;
             const int wslot = sizeof(IdxT) == 1 ? 0 : (sizeof(IdxT) == 2 ? 1 : 2);
-            const hipError_t e = grant.ensure(wslot * 24 + variant, reinterpret_cast<const void*>(tk), budget);
+            const hipError_t e = grant.ensure(wslot * 18 + variant, reinterpret_cast<const void*>(tk), budget);
             if (e != hipSuccess) return e;
         }
         {   // the kernel takes LDS address 0 for X: it must not have static LDS in front of the dynamic array
-            static std::atomic<int> checked[3][24] = {};
+            static std::atomic<int> checked[3][18] = {};
             const int wslot = sizeof(IdxT) == 1 ? 0 : (sizeof(IdxT) == 2 ? 1 : 2);
             std::atomic<int>& c = checked[wslot][variant];
             if (c.load(std::memory_order_acquire) == 0) {

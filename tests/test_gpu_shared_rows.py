@@ -75,36 +75,38 @@ def test_conv3x3_batch1_full_size(dom):
     full_check(wl.conv3x3(L=1, nonzero_dominant=dom), opts=NO_TABLE)
 
 
-SHAPES = [  # (m, n, p_dom, K, dominant), (rows, waves per row, waves) of a workgroup
-    ((513, 3300, 0.5, 16, None), (3, 2, 6)),         # just above three windows
-    ((768, 3801, 0.4, 100, None), (3, 2, 6)),        # fewer than five
-    ((768, 9001, 0.4, 100, None), (3, 4, 12)),       # ten; two tiles of ranks
-    ((600, 37000, 0.85, 40, None), (3, 4, 16)),      # X and the lists of few waves fill LDS
-    ((769, 3001, 0.45, 8, 5), (4, 2, 8)),            # Omega[0] != 0
-    ((1024, 12001, 0.5, 4, None), (4, 2, 8)),        # fewer than fourteen windows
-    ((1024, 16001, 0.5, 4, None), (4, 4, 16)),       # fifteen
-    ((1025, 9000, 0.5, 16, 3), (5, 2, 10)),
-    ((1279, 24004, 0.93, 16, None), (5, 1, 16)),     # whole rows, X of 96 KB
-    ((1300, 5000, 0.3, 64, None), (6, 2, 12)),       # seven windows
-    ((1300, 5000, 0.55, 64, 7), (4, 1, 4)),          # four: whole, an X of 20 KB
-    ((1700, 8601, 0.5, 16, 3), (7, 1, 8)),           # fewer than nine
-    ((1700, 9801, 0.5, 16, 3), (7, 2, 14)),
-    ((1700, 20001, 0.79, 16, 3), (7, 2, 14)),        # more than eight, X of more than 64 KiB
-    ((1700, 9801, 0.5, 200, None), (7, 1, 8)),       # fewer than 9.8, more than 128 values
-    ((2048, 7001, 0.5, 5, None), (8, 1, 8)),
-    ((2048, 9801, 0.5, 5, None), (8, 1, 8)),         # fewer than 9.8
-    ((2048, 10401, 0.5, 5, None), (8, 2, 16)),       # more
-    ((2048, 16501, 0.7, 5, None), (8, 2, 16)),       # more than 9.5, X of more than 64 KiB
-    ((2048, 11301, 0.5, 200, None), (8, 1, 8)),      # fewer than 11.5, more than 128 values
-    ((2048, 12301, 0.5, 200, None), (8, 2, 16)),
-    ((500, 2048, 0.7, 9, None), (2, 1, 4)),          # two windows
-    ((2049, 7001, 0.5, 16, 9), (9, 1, 9)),           # nine whole rows
-    ((2049, 4601, 0.1, 200, None), (9, 1, 9)),       # an X of up to 24 KiB, more than 6.5 windows
-    ((3072, 5001, 0.1, 200, None), (4, 1, 4)),       # twelve rows of an X of up to 24 KiB: workgroups of four waves
-    ((3840, 1900, 0.1, 200, None), (4, 1, 4)),       # fifteen rows of few windows: the same
-    ((3840, 4001, 0.1, 200, None), (4, 1, 4)),       # of fewer than 7.5 as well
-    ((3840, 5001, 0.1, 200, None), (15, 1, 15)),     # of more: one workgroup of as many waves as rows
-    ((3840, 6201, 0.5, 5, None), (15, 1, 15)),       # an X of more than 24 KiB
+SHAPES = [  # (m, n, p_dom, K, dominant), (rows, waves per row, waves, whether the reads of X are all on their way) of a workgroup
+    ((513, 3300, 0.5, 16, None), (3, 2, 6, True)),              # just above three windows
+    ((768, 3801, 0.4, 100, None), (3, 2, 6, True)),             # fewer than five
+    ((768, 9001, 0.4, 100, None), (3, 4, 12, False)),           # ten; two tiles of ranks
+    ((600, 37000, 0.85, 40, None), (3, 4, 16, False)),          # X and the lists of few waves fill LDS
+    ((769, 3001, 0.45, 8, 5), (4, 2, 8, True)),                 # Omega[0] != 0
+    ((1024, 12001, 0.5, 4, None), (4, 2, 8, True)),             # fewer than fourteen windows
+    ((1024, 16001, 0.5, 4, None), (4, 4, 16, False)),           # fifteen
+    ((1025, 9000, 0.5, 16, 3), (5, 2, 10, False)),
+    ((1279, 24004, 0.93, 16, None), (5, 1, 16, True)),          # whole rows, X of 96 KB
+    ((1300, 5000, 0.3, 64, None), (6, 2, 12, False)),           # seven windows
+    ((1300, 5000, 0.55, 64, 7), (4, 1, 4, False)),              # four: whole, an X of 20 KB
+    ((1700, 8601, 0.5, 16, 3), (7, 1, 8, True)),                # fewer than nine
+    ((1700, 9801, 0.5, 16, 3), (7, 2, 14, False)),
+    ((1700, 20001, 0.79, 16, 3), (7, 2, 14, False)),            # more than eight, X of more than 64 KiB
+    ((1700, 9801, 0.5, 200, None), (7, 1, 8, True)),            # fewer than 9.8, more than 128 values
+    ((1700, 13001, 0.8, 16, None), (7, 1, 8, True)),            # six loads of X for every wave
+    ((2048, 7001, 0.5, 5, None), (8, 1, 8, True)),
+    ((2048, 9801, 0.5, 5, None), (8, 1, 8, True)),              # fewer than 9.8
+    ((2048, 10401, 0.5, 5, None), (8, 2, 16, False)),           # more
+    ((2048, 16501, 0.7, 5, None), (8, 2, 16, False)),           # more than 9.5, X of more than 64 KiB
+    ((2048, 11301, 0.5, 200, None), (8, 1, 8, True)),           # fewer than 11.5, more than 128 values
+    ((2048, 12301, 0.5, 200, None), (8, 2, 16, False)),
+    ((500, 2048, 0.7, 9, None), (2, 1, 4, False)),              # two windows
+    ((500, 9001, 0.5, 9, None), (2, 4, 8, False)),
+    ((2049, 7001, 0.5, 16, 9), (9, 1, 9, False)),               # nine whole rows
+    ((2049, 4601, 0.1, 200, None), (9, 1, 9, False)),           # an X of up to 24 KiB, more than 6.5 windows
+    ((3072, 5001, 0.1, 200, None), (4, 1, 4, False)),           # twelve rows of an X of up to 24 KiB: workgroups of four waves
+    ((3840, 1900, 0.1, 200, None), (4, 1, 4, False)),           # fifteen rows of few windows: the same
+    ((3840, 4001, 0.1, 200, None), (4, 1, 4, False)),           # of fewer than 7.5 as well
+    ((3840, 5001, 0.1, 200, None), (15, 1, 15, False)),         # of more: one workgroup of as many waves as rows
+    ((3840, 6201, 0.5, 5, None), (15, 1, 15, False)),           # an X of more than 24 KiB
 ]
 
 

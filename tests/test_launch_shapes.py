@@ -85,11 +85,12 @@ def test_decoder_reads_no_codes_behind_its_memory(fake):  # noqa: F811
 
 
 def test_rows_and_waves_of_batch_1(fake):  # noqa: F811
-    """Batch 1: rows per workgroup, waves per row and waves, on both sides of the rule's lines."""
+    """Batch 1: rows per workgroup, waves per row, waves and the reads of X, on both sides of the rule's lines."""
     want = dict(test_gpu_shared_rows.SHAPES)
-    for case, [(_, (_, _, _, threads, _, rows, meta))] in products(fake, "rows", list(want)):
+    for case, [(name, (_, _, _, threads, _, rows, meta))] in products(fake, "rows", list(want)):
         assert threads == 64 * (meta >> 16)
-        assert (rows, 1 << ((meta >> 13) & 7), meta >> 16) == want[case], case
+        few = re.search(r"cer_gemv_tab_kernelI[a-z](?:Lb[01]E){4}Lb([01])E", name)[1] == "1"
+        assert (rows, 1 << ((meta >> 13) & 7), meta >> 16, few) == want[case], case
 
 
 def test_columns_and_waves_of_narrow_batches(fake):  # noqa: F811
