@@ -12,7 +12,7 @@
 // Against the two or three launches of decode_tiles_kernel + mfma_product_kernel (+ the sum of the parts) it saves the launches, 2 to 6
 // bytes of memory per element of W written and read, and a decoder that waits for its phases (786 x 1952, 32 values, batch 113: 18.9
 // -> 11.4 us; 842 x 3509, 190 values, batch 161: 37 -> 23), against the gathers the lines (4096 x 9216, 15 % indexed, batch 32: 28.4 ->
-// 23.7; 2048 x 2048, 256 values, batch 16, four passes of the narrow kernel: 12.0 -> 9.2).  What it pays: every workgroup loads and
+// 24.1; 2048 x 2048, 256 values, batch 16, four passes of the narrow kernel: 12.0 -> 9.2).  What it pays: every workgroup loads and
 // splits all of its X, so that products of many rows and columns stay with the large tiles.
 // What a product lasts (4096 x 9216, 32 values, batch 32; 256 workgroups, clocks): arguments and records 3000, X and indices requested,
 // bytes cleared 3500, scatter 5300, product 38000 -- X alone, 1.2 MB per compute unit at 36 bytes per clock, takes 33000 --, sums 2000.
@@ -37,17 +37,19 @@ struct FusedRest {
     uint32_t dense;              // a zero weight times an infinity counts (exact_dense)
 };
 
-template <int kForm, int RT, int CT, int NW>
+// kTurns: matrix and LDS instructions by turns (the compiler's hint for such loops instead of the fences).  One piece, 16 rows x 32 columns and 16 waves:
+// 26 products 0.966 times the time, 0.984 at most (4096 x 9216, 32 values, batch 32 24.5 -> 24.1 us).  Uniform grids, 16 x 48 and 16 x 64: 0.97 to 1.00
+// where a workgroup multiplies few columns of W (2994 x 2804, 36 values, 72 31.4 -> 30.6), 1.01 to 1.03 where they are many (1360 x 13925, 12 values,
+// 136 65.9 -> 68.0); launch_fused draws the line.  Elsewhere, 26 products of each: one piece 16 x 64 1.026 (1666 x 2968, 4 values, 124 17.8 -> 18.6),
+// 32 x 64 1.02, up to 1.08 (1921 x 4736, 32 values, 210 28.7 -> 30.9), 16 x 48 and 32 x 32 1.00; uniform grids 16 x 32 and 32 x 32 1.005; three pieces
+// up to 1.07.
+template <int kForm, int RT, int CT, int NW, bool kTurns = kForm == 1 && RT == 1 && CT == 2 && NW == 16>
 __global__ __launch_bounds__(NW * kWave) void cer_fused_kernel(
     const uint32_t* tab, const float* X, const uint16_t* colI, const float* omega, uint32_t m, uint32_t n, uint32_t L, uint32_t row_magic,
     uint32_t eighth, uint32_t packed, FusedRest rest, UniformGrid grid) {
     constexpr int PW = weight_planes(kForm), kWords = kForm == 3 ? 2 : 1;  // bf16 numbers and dwords per value
     constexpr uint32_t kWaves = NW, kThreads = NW * kWave;
     constexpr uint32_t R = 16 * RT, RW = R / kWaves, BN = 16 * CT;
-    // Matrix and LDS instructions by turns in tiles of several columns, one piece and uniform grids: 4096 x 9216, 32 values, batch 32 24.1 -> 23.6
-    // us, 3795 x 1900, two values, 23 10.0 -> 9.5, 3111 x 2217, 17 values, 56 16.1 -> 15.8; with three pieces 1.02 to 1.07 times the time (1099 x
-    // 8992, 5 bits, 163 47.8 -> 51.4), with one column, where the splitting is short, 1.01 to 1.03.
-    constexpr bool kTurns = CT > 1 && kForm != 3;
     constexpr int D = NW == 16 ? 2 : (CT == 1 ? 4 : (CT == 2 ? 3 : 2));  // steps of X in registers: the current one and what is on its way
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uniform(tid >> 6);
@@ -386,6 +388,7 @@ struct Variant {
     uint8_t form, rt, ct, waves;
     float fixed, round, list, batch, pos, step;
     FusedKernel kernel;
+    FusedKernel turns = nullptr;  // kTurns, where launch_fused chooses between the two
 };
 const Variant kVariants[] = {
     {1, 1, 1, 16, 1.11f, 3.74f, 0.404f, 0.260f, 0.00290f, 0.0344f, cer_fused_kernel<1, 1, 1, 16>},
@@ -401,8 +404,8 @@ const Variant kVariants[] = {
     {3, 2, 2, 8, 1.34f, 4.84f, 0.271f, 0.403f, 0.00262f, 0.1261f, cer_fused_kernel<3, 2, 2, 8>},
     {kUniform, 1, 1, 16, 1.27f, 3.55f, 0.356f, 0.239f, 0.00310f, 0.0434f, cer_fused_kernel<kUniform, 1, 1, 16>},
     {kUniform, 1, 2, 8, 1.30f, 4.15f, 0.257f, 0.292f, 0.00309f, 0.0730f, cer_fused_kernel<kUniform, 1, 2, 8>},
-    {kUniform, 1, 3, 8, 1.25f, 4.23f, 0.232f, 0.204f, 0.00360f, 0.0939f, cer_fused_kernel<kUniform, 1, 3, 8>},
-    {kUniform, 1, 4, 8, 1.33f, 4.55f, 0.240f, 0.248f, 0.00356f, 0.1146f, cer_fused_kernel<kUniform, 1, 4, 8>},
+    {kUniform, 1, 3, 8, 1.25f, 4.23f, 0.232f, 0.204f, 0.00360f, 0.0939f, cer_fused_kernel<kUniform, 1, 3, 8>, cer_fused_kernel<kUniform, 1, 3, 8, true>},
+    {kUniform, 1, 4, 8, 1.33f, 4.55f, 0.240f, 0.248f, 0.00356f, 0.1146f, cer_fused_kernel<kUniform, 1, 4, 8>, cer_fused_kernel<kUniform, 1, 4, 8, true>},
     {kUniform, 2, 2, 8, 1.34f, 4.84f, 0.271f, 0.403f, 0.00262f, 0.1173f, cer_fused_kernel<kUniform, 2, 2, 8>},
 };
 constexpr int kVariantCount = sizeof(kVariants) / sizeof(kVariants[0]);
@@ -481,9 +484,13 @@ hipError_t launch_fused(const DeviceView& d, const float* X, float* Y, uint32_t 
     const FusedPlan p = plan_fused(d, L, temporaries, 1e30);
     if (p.variant < 0) return hipErrorInvalidValue;
     const Variant& k = kVariants[p.variant];
+    // Turns / fences by columns per workgroup: 16 x 48 854 to 6957 0.976 to 1.000, 12431 and more 1.03; 16 x 64 1195 to 4986 0.973 to 1.000, 5057 to
+    // 9448 1.00 to 1.03.
+    const bool turns = k.turns != nullptr && std::min<int64_t>(p.kchunk, d.n) <= (k.ct == 3 ? 7000 : 5000);
+    const auto kernel = turns ? k.turns : k.kernel;
     {
-        static LdsGrant<kVariantCount> grant;
-        const hipError_t e = grant.ensure(p.variant, reinterpret_cast<const void*>(k.kernel), d.lds_per_block);
+        static LdsGrant<2 * kVariantCount> grant;
+        const hipError_t e = grant.ensure(p.variant + (turns ? kVariantCount : 0), reinterpret_cast<const void*>(kernel), d.lds_per_block);
         if (e != hipSuccess) return e;
     }
     FusedRest a;
@@ -504,7 +511,7 @@ hipError_t launch_fused(const DeviceView& d, const float* X, float* Y, uint32_t 
     const uint32_t items = p.row_blocks * p.col_tiles * p.splits, eighth = (items + 7u) / 8u;
     const uint32_t magic = p.row_blocks == 1 ? 0u : (uint32_t)(((1ull << 32) + p.row_blocks - 1) / p.row_blocks);
     const uint32_t packed = p.kchunk / 32u | (uint32_t)d.rank_tab_shift << 12 | p.splits << 16;
-    hipError_t e = launch_kernel(k.kernel, dim3(eighth * 8u), dim3(k.waves * kWave), p.lds, stream, d.rank_tab, X,
+    hipError_t e = launch_kernel(kernel, dim3(eighth * 8u), dim3(k.waves * kWave), p.lds, stream, d.rank_tab, X,
                                  static_cast<const uint16_t*>(d.colI), d.omega, (uint32_t)d.m, (uint32_t)d.n, L, magic, eighth, packed, a, d.grid);
     if (part) {
         if (e == hipSuccess)

@@ -49,6 +49,12 @@ for case in cases:
         m, n, p_dom, K, dominant = case
         w = wl.random_lowentropy(m=m, n=n, K=K, p_dom=p_dom, L=1, seed=m + n, ratio=0.99 if K > 128 else 0.7, **({} if dominant is None else {"dominant": dominant}))
         got = product(w.W, w.codebook, False, 1, -1, "cer_gemv_tab_kernel")
+    elif kind == "fused":
+        m, n, K, p0, L = case
+        rng = np.random.default_rng(0)
+        cb = (np.arange(K) - K // 2).astype(np.float32) / np.float32(max(K / 2, 1))
+        W = np.where(rng.random((m, n)) > p0, rng.choice(cb[cb != 0], size=(m, n)), 0).astype(np.float32)
+        got = product(W, cb, False, L, -1, "cer_fused_kernel")
     elif kind == "narrow":
         (m, n, K, p0, L), zero = case
         W, cb, _ = test_gpu_narrow.matrix(m, n, L, K, p0, zero)
@@ -158,3 +164,15 @@ def test_early_emitter(fake):  # noqa: F811
     assert out.returncode == 0, out.stderr
     got = [tuple(map(int, line.split())) for line in out.stdout.splitlines()]
     assert got == want, [c for c, g, w in zip(calls, got, want) if g != w]
+
+
+# Decode + product in one launch, by turns or fenced: (rows, columns, values, share of zeros, batch) on a uniform grid or of one piece -> (form, rows / 16,
+# columns / 16 of a tile, waves, by turns)
+TURNS = {(2994, 2804, 36, 0.432, 35): (4, 1, 3, 8, True), (1360, 13925, 12, 0.507, 136): (4, 1, 3, 8, False), (982, 1195, 73, 0.6, 228): (4, 1, 4, 8, True),
+         (1319, 9448, 12, 0.763, 160): (4, 1, 4, 8, False), (2697, 3684, 64, 0.487, 25): (1, 1, 2, 16, True), (2047, 2349, 2, 0.733, 122): (1, 1, 4, 8, False)}
+
+
+def test_turns_of_the_product_in_one_launch(fake):  # noqa: F811
+    for case, [(name, _)] in products(fake, "fused", list(TURNS)):
+        form, rt, ct, waves, turns = map(int, re.search(r"cer_fused_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d+)ELb(\d)E", name).groups())
+        assert (form, rt, ct, waves, turns == 1) == TURNS[case], case
