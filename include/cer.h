@@ -159,8 +159,8 @@ int cer_trim(void);
 /*
  * cer_matmul_path -- which kernel cer_matmul / cser_matmul runs for this handle and batch:
  *   0  CER_PATH_GEMV: batch-1 kernel, always taken for batch 1: X staged in LDS per workgroup (read
- *      from global memory when it does not fit), one wave per row (4 or 8 waves per row in matrices
- *      of at most two rows per compute unit), colI read with 16-byte loads, the weight of every
+ *      from global memory when it does not fit), one wave per row (2, 4 or 8 waves per row in matrices
+ *      of at most eight rows per compute unit whose rows are long), colI read with 16-byte loads, the weight of every
  *      position derived from a bitmap of the group boundaries, one multiply-add per position.
  *      Handles of 2 - 256 values with X in LDS use their rank table (below) to find the boundaries
  *   4  CER_PATH_GEMV_EXPAND: an earlier batch-1 kernel, only on request: the group values are

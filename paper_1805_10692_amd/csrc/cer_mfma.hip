@@ -8,8 +8,8 @@
 // [piece][k / 8][column][8], so that the operand reads are 16 bytes per lane at consecutive addresses.  X is loaded several steps
 // ahead, W one step, and the LDS stores go one or two steps ahead into other buffers: one barrier per step, no branch in between
 // (rows of X behind the last one read as zeros: buffer loads with bounds).
-// Counters for 512 x 4608, batch 3136, one piece (44 us, 1020 TFLOP/s of bf16; 9.6 TB/s from L2): matrix pipes busy 55 % of the launch,
-// vector ALU 26 % (the splitting), LDS 21 %, no bank conflicts; a wave waits 49 % of its time to issue and 17 % for data -- two waves
+// Counters for 512 x 4608, batch 3136, one piece (42 us, 1050 TFLOP/s of bf16; 10 TB/s from L2): matrix pipes busy 59 % of the launch,
+// vector ALU 28 % (the splitting), LDS 22 %, no bank conflicts; a wave waits 48 % of its time to issue and 16 % for data -- two waves
 // per SIMD that meet at the matrix pipe, and a barrier per step.  Two workgroups of four waves, whose barriers do not meet, are
 // worth 10 us there against one of eight waves of 32 rows (52 us: the operands of X are read twice as often), and as much as one of
 // 512 rows (42 us; but 481 x 6989, batch 1415, 61 us the call instead of 45).  With more pieces the sums take twice the registers, and a

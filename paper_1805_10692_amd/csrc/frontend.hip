@@ -1224,7 +1224,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const ColT* __restrict
 // before it: a bitmap of the beginnings, counted up per word, as in the batch-1 kernel -- no search, no branch (a binary search
 // and a walk over the boundaries waited for LDS at every step: 633 x 5106, 112 values, 22 us, now 11; 986 x 16765, three
 // values, 42 against 28).  Bound by the phases of a workgroup -- records, list, bitmap, positions, output -- that follow one another
-// (512 x 4608, 128 workgroups, 6.7 us: vector ALU busy 15 % of the launch, LDS 9 %, a wave waits for data or at a barrier 64 %).  So the first
+// (512 x 4608, 128 workgroups, 6.7 us: vector ALU busy 16 % of the launch, LDS 9 %, a wave waits for data or at a barrier 60 %).  So the first
 // positions are requested as soon as the records tell where they are, the pieces of the values are made and the bitmap is filled
 // beside the list meanwhile, and the counts are summed by lane moves: 0.4 to 0.8 us of 5.6 to 11.3, 0.985 of the call in the geometric mean of
 // 50 products (2067 x 521, batch 1638, 38.7 -> 37.3 us).  Eight rows in more segments instead of four rows: 1.03 times the call; four rows in more
