@@ -85,18 +85,22 @@ __global__ __launch_bounds__(kFew ? 512 : 1024) void cer_narrow_kernel(NarrowArg
         Vec* dst = reinterpret_cast<Vec*>(xs);
         const uint32_t behind = (uint32_t)V > a.L ? ((uint32_t)V - 1u) / a.L : 0u, nvec = a.n > behind ? a.n - behind : 0u;
         uint32_t i = threadIdx.x;
-        auto copy = [&](auto loads) {
-            constexpr uint32_t kLoads = decltype(loads)::value;
-            for (; i + (kLoads - 1u) * nthreads < nvec; i += kLoads * nthreads) {
-                Vec q[kLoads];
+        if constexpr (kFew) {  // (what is left four at a time: 192 x 18844, batch 2 5.99 -> 5.80 us)
+            for (; i + 7u * nthreads < nvec; i += 8u * nthreads) {
+                Vec q[8];
 #pragma unroll
-                for (uint32_t k = 0; k < kLoads; ++k) q[k] = reinterpret_cast<const Row*>(src + (size_t)(i + k * nthreads) * a.L)->v;
+                for (int k = 0; k < 8; ++k) q[k] = reinterpret_cast<const Row*>(src + (size_t)(i + k * nthreads) * a.L)->v;
 #pragma unroll
-                for (uint32_t k = 0; k < kLoads; ++k) dst[i + k * nthreads] = q[k];
+                for (int k = 0; k < 8; ++k) dst[i + k * nthreads] = q[k];
             }
-        };
-        if constexpr (kFew) copy(std::integral_constant<uint32_t, 8>{});
-        copy(std::integral_constant<uint32_t, 4>{});
+        }
+        for (; i + 3u * nthreads < nvec; i += 4u * nthreads) {
+            Vec q[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) q[k] = reinterpret_cast<const Row*>(src + (size_t)(i + k * nthreads) * a.L)->v;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) dst[i + k * nthreads] = q[k];
+        }
         for (; i < nvec; i += nthreads) dst[i] = reinterpret_cast<const Row*>(src + (size_t)i * a.L)->v;
         for (i = nvec + threadIdx.x; i < a.n; i += nthreads)
 #pragma unroll
