@@ -221,16 +221,21 @@ private:
     void* ctx_ = nullptr;
 };
 
-// Who works on `work` elements: the waiting threads, one for every 16 Ki elements, or, where those are busy with another call, threads started for it,
-// one for every 64 Ki; at most 16 and never more than there are rows.  (A thread takes 1 to 2 ns per element; waiting for the others costs some us
-// each of five times, starting one 10 us.  Encode and decode in turn with one for every 64 / 32 / 16 Ki, fifteen layers of 0.2 to 4 M
-// elements: 0.82 / 0.70 / 0.64 of the time before the threads were kept awake and their counters apart; each call 4 ms after the last one:
-// 0.91 / 0.79 / 0.80.)
+// Who works on `work` elements: the waiting threads, or, where those are busy with another call, threads started for it.  One for every 64 Ki elements;
+// the waiting ones, whom it costs nothing to start, one for every 16 Ki, but no more than three quarters of the processors for that: whoever else
+// wants one of them (the runtime's threads, another call) stops a thread that all others wait for.  At most 16 and never more than there are rows.
+// us there and back on 16 processors, one for every 64 Ki / one for every 16 Ki, up to 16 / up to 12: 300 x 900, 30 values, in turn 250 / 141, one call in
+// ten 830 to 990 / 146, in two threads at once 360 / 1540 / 295, in four 690 / 3760 / 720; 498 x 848, 214 values 380 / 230 (740) / 245, in two 610 /
+// 1960 / 840, in four 1600 / 4490 / 1840.  (A thread takes 1 to 2 ns per element; waiting for the others costs some us each of five times, starting one
+// 10 us.)
 class Crew {
 public:
     Crew(int64_t rows, int64_t work) {
-        if (count(rows, work, 16384) > 1) waiting_ = Workers::hold();
-        size_ = count(rows, work, waiting_ ? 16384 : 65536);
+        const int64_t processors = std::max(1u, std::thread::hardware_concurrency());
+        const int64_t few = std::max<int64_t>(1, std::min<int64_t>({16, processors, rows, (work + 65535) / 65536}));
+        const int64_t more = std::min<int64_t>({16, processors * 3 / 4, rows, (work + 16383) / 16384});
+        size_ = (int)std::max(few, more);
+        if (size_ > 1 && !(waiting_ = Workers::hold())) size_ = (int)few;
     }
     ~Crew() {
         if (waiting_) waiting_->let_go();
@@ -241,11 +246,6 @@ public:
     Workers* waiting() const { return waiting_; }
 
 private:
-    static int count(int64_t rows, int64_t work, int64_t each) {
-        const unsigned hw = std::thread::hardware_concurrency();
-        const int64_t t = std::min<int64_t>(std::min<unsigned>(hw ? hw : 1, 16), (work + each - 1) / each);
-        return (int)std::max<int64_t>(1, std::min<int64_t>(t, rows));
-    }
     Workers* waiting_ = nullptr;
     int size_ = 1;
 };

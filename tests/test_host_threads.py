@@ -118,6 +118,32 @@ print(max(started))
 """
 
 
+ALONE = """
+import ctypes, os
+import numpy as np
+from paper_1805_10692_amd import binding as B
+fake = ctypes.CDLL(None)
+cb = np.array([0.0, 1.0, 2.0], np.float32)
+W = np.random.default_rng(0).choice(cb, size=(SHAPE)).astype(np.float32)
+before = fake.fake_hip_threads()
+h = B.cer_encode(W, cb)
+assert np.array_equal(B.cer_decode(h), W)
+print(fake.fake_hip_threads() - before)
+"""
+
+
+@pytest.mark.parametrize("m,n", [(16, 1000), (300, 900), (1100, 1200)])
+def test_processors_are_left_to_others(fake, m, n):  # noqa: F811
+    """A thread per 16 Ki elements on three quarters of the processors, on more only where there is one for every 64 Ki."""
+    processors = len(os.sched_getaffinity(0))
+    work = m * n
+    few, more = min(16, processors, m, -(-work // 65536)), min(16, processors * 3 // 4, m, -(-work // 16384))
+    env = dict(os.environ, LD_PRELOAD=fake, PYTHONPATH=os.path.dirname(HERE))
+    out = subprocess.run([sys.executable, "-c", ALONE.replace("SHAPE", f"{m}, {n}")], env=env, capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stderr
+    assert int(out.stdout) == max(1, few, more) - 1
+
+
 def test_few_threads_are_started_where_the_waiting_ones_are_busy(fake):  # noqa: F811
     """Starting a thread takes some 10 us: one for every 64 Ki elements beside another conversion, none for the copy of the arrays (400 KB)."""
     if len(os.sched_getaffinity(0)) < 8:
